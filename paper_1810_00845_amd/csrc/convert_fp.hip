@@ -1,0 +1,818 @@
+// Inverse transform -> fast base conversion -> forward transform, in exact fp64, for N = 2^12 .. 2^15 and primes below
+// 2^50: the ModUp and the ModDown of key switching and the division of a rescale, as three launches whose units of
+// work are single waves (rows) or small workgroups (columns).
+//
+// A coefficient index is (a : log2 N - 10)(b : 5)(c : 5).  The log2 N - 10 levels on `a` pair coefficients a multiple
+// of 1024 apart ("columns"), the ten levels on b and c stay inside a row of 1024 neighbours.
+//   rows_inv     one wave per row: the inverse levels on c, then b
+//   columns      one workgroup per tile of columns of one digit of one entry: the inverse levels on `a` of all its source
+//                limbs (-> centred conversion inputs, kept in LDS), then per target limb the conversion sum and the
+//                forward levels on `a`
+//   rows_fwd     one wave per row: the forward levels on b, then c, and the store stage of the operation
+// Why this split: a workgroup that transforms a whole polynomial (ntt_fp.hip) occupies one compute unit for 20-36 us
+// whatever else is idle, so a call with fewer limb-polynomials than compute units is bound by that latency.  Here a
+// polynomial at N = 2^15 is 32 waves of rows and 32 tiles of columns, nothing waits for a whole polynomial except
+// the launch boundary, and the conversion inputs never travel through memory.
+//
+// A wave holds 1024 coefficients, 16 per lane.  Five levels on a five-bit field take four in registers and the one on
+// the field's lowest bit after exchanging that bit (lane bit 5) with a register bit by v_permlane32_swap, so a row needs
+// two passes through LDS in all (one 64-bit exchange each way) and loads and stores are whole 512-byte lines.
+//
+// Ranges: values are exact integers |v| <= m p with m p < 2^53; every butterfly knows the bound m of its operands at
+// compile time (Bound below: plain floats that fold away after unrolling) and normalises only where the result could
+// leave 8 p.
+#include <cstdio>
+
+#include "fp_device.hpp"
+
+#define ROW_LDS 1056     // doubles per wave: 32 x 33, one pad word per 32
+#define ROWS_NT 256
+#define HEAD 64          // per-prime table: [HEAD] column twiddles, then SPLIT_ROW per row (layout: split_tables)
+
+// Position of a limb -> its prime: the l limbs of q first, special limbs behind them.
+__device__ __forceinline__ int prime_at(int pos, int l, int L) { return pos < l ? pos : pos + (L - l); }
+
+struct Modulus { double p, pinv; };
+__device__ __forceinline__ Modulus modulus(const FpPrime* f, int prime) {
+    return Modulus{as_const(&f[prime].p)[0], as_const(&f[prime].p)[1]};
+}
+
+#define BOUND_LIMIT 7.99f
+__device__ __forceinline__ float product_bound(float my, float mw) { return 0.501f + 0.375f * my * mw; }   // fp_mulmod
+
+// forward butterfly: (x, y) -> (x + w y, x - w y)
+__device__ __forceinline__ void fwd_bfly(double& x, double& y, float& bx, float& by, double w, float mw, Modulus q) {
+    const float bt = product_bound(by, mw);
+    if (bx + bt > BOUND_LIMIT) { x = fp_norm(x, q.p, q.pinv); bx = 0.501f; }
+    const double t = fp_mulmod(y, w, q.p, q.pinv);
+    y = x - t;
+    x = x + t;
+    bx = by = bx + bt;
+}
+
+// inverse butterfly: (x, y) -> (x + y, (x - y) w)
+__device__ __forceinline__ void inv_bfly(double& x, double& y, float& bx, float& by, double w, float mw, Modulus q) {
+    if (bx + by > BOUND_LIMIT) {
+        x = fp_norm(x, q.p, q.pinv);
+        y = fp_norm(y, q.p, q.pinv);
+        bx = by = 0.501f;
+    }
+    const double d = x - y;
+    x = x + y;
+    bx = bx + by;
+    y = fp_mulmod(d, w, q.p, q.pinv);
+    by = product_bound(bx, mw);
+}
+
+// exchange lane bit 5 with the register bit that tells x from y: afterwards x holds what the lanes of the lower half had
+// in (x, y), y what those of the upper half had
+__device__ __forceinline__ void swap_halves(double& x, double& y) {
+    const auto lo = __builtin_amdgcn_permlane32_swap(lo32(x), lo32(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(hi32(x), hi32(y), false, false);
+    x = mk64(lo[0], hi[0]);
+    y = mk64(lo[1], hi[1]);
+}
+
+// Five forward levels on a five-bit field.  In: register r of a lane in half h holds element 2 r + h; out: element
+// 4 (r >> 1) + 2 h + (r & 1).  tw(j, g): twiddle of level j < 4, group g; last[k]: of level 4, group 2 k + h.
+template <class TW>
+__device__ __forceinline__ void fwd_levels5(double (&v)[16], float (&m)[16], TW tw, float mw, const double (&last)[8], Modulus q) {
+#pragma unroll
+    for (int j = 0; j < 4; j++) {
+        const int half = 3 - j;
+#pragma unroll
+        for (int g = 0; g < (1 << j); g++) {
+            const double w = tw(j, g);
+#pragma unroll
+            for (int lo = 0; lo < (1 << half); lo++) {
+                const int r0 = (g << (half + 1)) | lo, r1 = r0 + (1 << half);
+                fwd_bfly(v[r0], v[r1], m[r0], m[r1], w, mw, q);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        swap_halves(v[2 * k], v[2 * k + 1]);
+        m[2 * k] = m[2 * k + 1] = fmaxf(m[2 * k], m[2 * k + 1]);
+        fwd_bfly(v[2 * k], v[2 * k + 1], m[2 * k], m[2 * k + 1], last[k], 0.5f, q);
+    }
+}
+
+// The inverse levels, undone in reverse order.  In: element 4 (r >> 1) + 2 h + (r & 1); out: 2 r + h.
+template <class TW>
+__device__ __forceinline__ void inv_levels5(double (&v)[16], float (&m)[16], TW tw, float mw, const double (&last)[8], Modulus q,
+                                            int lowest_level = 0) {
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        inv_bfly(v[2 * k], v[2 * k + 1], m[2 * k], m[2 * k + 1], last[k], 0.5f, q);
+        swap_halves(v[2 * k], v[2 * k + 1]);
+        m[2 * k] = m[2 * k + 1] = fmaxf(m[2 * k], m[2 * k + 1]);
+    }
+#pragma unroll
+    for (int j = 3; j >= 0; j--) {
+        if (j < lowest_level) continue;
+        const int half = 3 - j;
+#pragma unroll
+        for (int g = 0; g < (1 << j); g++) {
+            const double w = tw(j, g);
+#pragma unroll
+            for (int lo = 0; lo < (1 << half); lo++) {
+                const int r0 = (g << (half + 1)) | lo, r1 = r0 + (1 << half);
+                inv_bfly(v[r0], v[r1], m[r0], m[r1], w, mw, q);
+            }
+        }
+    }
+}
+
+// the largest bound of all registers becomes everyone's (values change lanes and registers in an exchange); what could
+// be larger than `cap` is normalised first
+__device__ __forceinline__ void cap_bounds(double (&v)[16], float (&m)[16], float cap, Modulus q) {
+    float top = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        if (m[r] > cap) { v[r] = fp_norm(v[r], q.p, q.pinv); m[r] = 0.501f; }
+        top = fmaxf(top, m[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r++) m[r] = top;
+}
+
+// Byte offsets of the elements that sigma_g moves to 1024 row + 64 r + lane.  The exponent of index i is 2 bitrev(i) + 1,
+// its product with g splits into a term of the lane (one multiplication) and a uniform term of (row, r); shifting both left
+// by 31 - log2 N makes the 32-bit sum wrap modulo 2N, and reversing its bits gives the source index with the bit of the
+// always-odd exponent above it.
+struct Gather {
+    uint32_t lane_term, shift, row, log_n;
+};
+__device__ __forceinline__ Gather make_gather(u64 g, uint32_t row, int lane, int log_n) {
+    const uint32_t gs = (uint32_t)g << (31 - log_n);
+    uint32_t lane_term = (2u * (__brev((uint32_t)lane) >> (32 - log_n)) + 1u) * gs;
+    asm volatile("" : "+v"(lane_term));      // otherwise the sum of products below becomes a product per register again
+    return Gather{lane_term, gs, row, (uint32_t)log_n};
+}
+__device__ __forceinline__ uint32_t gather_offset(const Gather& t, int r) {
+    const uint32_t u = t.lane_term + 2u * (__brev(t.row * 1024u + (uint32_t)r * 64u) >> (32 - t.log_n)) * t.shift;
+    return (__brev(u) << 3) - (8u << t.log_n);
+}
+
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, double& x, double& y) {
+    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
+    x = mk64(d.x, d.y);
+    y = mk64(d.z, d.w);
+}
+
+// Wave-level tasks, ordered (limb, row, entry): the entries of a row share its twiddles (5 KB beside 8 KB of data) and, in
+// the inner product, its key rows (16 KB a digit), so the four waves of a workgroup find them in the L1 and the workgroups
+// of an XCD (round-robin by id, hence the contiguous range per XCD) in its L2.
+__device__ __forceinline__ int row_task(int n_tasks) {
+    const int n_blocks = (n_tasks + 3) >> 2, per = (n_blocks + 7) >> 3;
+    const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per) return -1;
+    const int task = blk * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    return task < n_tasks ? task : -1;
+}
+
+// What a wave keeps of the twiddles of its row (layout: split_table_words)
+struct RowTwiddles {
+    double last_c[8], last_b[8], base[4];
+    const double *head, *tab;
+};
+__device__ __forceinline__ void row_tables(RowTwiddles& w, const double* table, u64 stride, int prime, uint32_t row) {
+    w.head = table + (u64)prime * stride;
+    w.tab = w.head + HEAD + (u64)row * SPLIT_ROW;
+}
+__device__ __forceinline__ void load_twiddles_b(RowTwiddles& w, int lane) {
+    const rsrc_t r = make_rsrc(w.tab, SPLIT_ROW * 8);
+#pragma unroll
+    for (int k = 0; k < 4; k++) bload2(r, (uint32_t)(lane >> 5) * 64u, 128u + (uint32_t)k * 16u, w.last_b[2 * k], w.last_b[2 * k + 1]);
+}
+__device__ __forceinline__ void load_twiddles_c(RowTwiddles& w, int lane) {
+    const rsrc_t r = make_rsrc(w.tab, SPLIT_ROW * 8);
+#pragma unroll
+    for (int k = 0; k < 4; k++) bload2(r, (uint32_t)lane * 16u, 160u * 8u + (uint32_t)k * 1024u, w.last_c[2 * k], w.last_c[2 * k + 1]);
+#pragma unroll
+    for (int j = 0; j < 4; j++) w.base[j] = bloadf(r, (uint32_t)(lane & 31) * 8u, 32u * 8u + (uint32_t)j * 256u);
+}
+__device__ __forceinline__ void load_row_twiddles(RowTwiddles& w, const double* table, u64 stride, int prime, uint32_t row, int lane) {
+    row_tables(w, table, stride, prime, row);
+    load_twiddles_c(w, lane);
+    load_twiddles_b(w, lane);
+}
+
+// The ten levels of a row; register r of lane i is coefficient 64 r + i before and after.  m: bounds, in and out.
+// LATE: the twiddles of c are fetched behind the levels on b (a caller short of registers).  LEAVE: the result stays in
+// the wave's LDS part, coefficient i at i + i / 32.
+template <bool LATE = false, bool LEAVE = false>
+__device__ __forceinline__ void row_forward(double (&v)[16], float (&m)[16], RowTwiddles& w, double* lds, int lane, Modulus q, float cap) {
+    const int h = lane >> 5, s = lane & 31;
+    fwd_levels5(v, m, [&](int j, int g) { return as_const(w.tab)[(1 << j) + g]; }, 0.5f, w.last_b, q);
+    cap_bounds(v, m, BOUND_LIMIT, q);
+    if (LATE) {
+        SCHED_FENCE();
+        load_twiddles_c(w, lane);
+    }
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) lds[(2 * h + (r >> 1) * 4 + (r & 1)) * 33 + s] = v[r];
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) v[r] = lds[s * 33 + h + 2 * r];
+    fwd_levels5(v, m, [&](int j, int g) { return g == 0 ? w.base[j] : fp_mulmod(w.base[j], as_const(w.head)[32 + g], q.p, q.pinv); },
+                0.6f, w.last_c, q);
+    cap_bounds(v, m, cap, q);
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) lds[s * 33 + 2 * h + (r >> 1) * 4 + (r & 1)] = v[r];
+    if (LEAVE) return;
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) v[r] = lds[66 * r + lane + h];
+}
+
+__device__ __forceinline__ void row_inverse(double (&v)[16], float (&m)[16], RowTwiddles& w, double* lds, int lane, Modulus q) {
+    const int h = lane >> 5, s = lane & 31;
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = v[r];
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) v[r] = lds[s * 33 + 2 * h + (r >> 1) * 4 + (r & 1)];     // lane b = s, elements of c
+    inv_levels5(v, m, [&](int j, int g) { return g == 0 ? w.base[j] : fp_mulmod(w.base[j], as_const(w.head)[32 + g], q.p, q.pinv); },
+                0.6f, w.last_c, q);
+    cap_bounds(v, m, 2.01f, q);
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) lds[s * 33 + h + 2 * r] = v[r];
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) v[r] = lds[(2 * h + (r >> 1) * 4 + (r & 1)) * 33 + s];   // lane c = s, elements of b
+    inv_levels5(v, m, [&](int j, int g) { return as_const(w.tab)[(1 << j) + g]; }, 0.5f, w.last_b, q);
+    cap_bounds(v, m, 1.01f, q);
+}
+
+// the row's 1024 words of a limb, read through sigma_g when galois != 0
+template <int K3>
+__device__ __forceinline__ void load_row_through(double (&v)[16], const u64* limb, u64 galois, uint32_t row, int lane) {
+    if (galois) {
+        const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
+        const Gather t = make_gather(galois, row, lane, 10 + K3);
+#pragma unroll
+        for (int r = 0; r < 16; r++) v[r] = bloadf(src, gather_offset(t, r), 0);
+    } else {
+        const rsrc_t src = make_rsrc(limb + row * 1024u, 8192u);
+#pragma unroll
+        for (int r = 0; r < 16; r++) v[r] = bloadf(src, (uint32_t)lane * 8u, (uint32_t)r * 512u);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// rows, inverse
+// ---------------------------------------------------------------------------
+template <int K3>
+__device__ __forceinline__ void rows_inverse(const ConvertArgs& a, int n_tasks, double* lds_all) {
+    const int task = row_task(n_tasks);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63;
+    double* lds = lds_all + (threadIdx.x >> 6) * ROW_LDS;
+    const uint32_t unit = (uint32_t)task / a.n_entries, b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t row = unit & ((1u << K3) - 1), k = unit >> K3;
+    const int prime = prime_at(a.src_pos0 + (int)k, a.l, a.L);
+    const Modulus q = modulus(a.fprimes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    double v[16];
+    float m[16];
+    const u64* src_p = a.in + (u64)b * a.in_bs + (u64)(a.src_pos0 + (int)k) * n;
+    load_row_through<K3>(v, src_p, a.galois, row, lane);
+    RowTwiddles w;
+    load_row_twiddles(w, a.sinv, a.table_stride, prime, row, lane);
+#pragma unroll
+    for (int r = 0; r < 16; r++) {
+        v[r] = fp_from_u64((u64)__double_as_longlong(v[r]));
+        m[r] = 1.0f;
+    }
+    row_inverse(v, m, w, lds, lane, q);
+    const rsrc_t dst = make_rsrc(a.mid + ((u64)b * a.n_src + k) * n + row * 1024u, 8192u);
+#pragma unroll
+    for (int r = 0; r < 16; r++) bstoref(dst, (uint32_t)lane * 8u, (uint32_t)r * 512u, v[r]);
+}
+
+// ---------------------------------------------------------------------------
+// columns
+// ---------------------------------------------------------------------------
+template <int RB>
+struct Col {
+    static constexpr int NR = RB == 5 ? 16 : (1 << RB);      // coefficients per lane
+    static constexpr int WIDTH = RB == 5 ? 32 : 64;          // columns per tile
+};
+
+// Inverse levels on `a`, the last one with the limb's factor f folded in.  RB = 5: in / out elements as inv_levels5.
+template <int RB>
+__device__ __forceinline__ void inv_columns(double (&v)[Col<RB>::NR], const double* head, const double (&last)[8], double f, double fw,
+                                            Modulus q) {
+    constexpr int NR = Col<RB>::NR;
+    float m[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) m[r] = 1.01f;
+    if constexpr (RB == 5) {
+        inv_levels5(v, m, [&](int j, int g) { return as_const(head)[(1 << j) + g]; }, 0.5f, last, q, 1);
+    } else {
+#pragma unroll
+        for (int j = RB - 1; j >= 1; j--) {
+            const int half = RB - 1 - j;
+#pragma unroll
+            for (int g = 0; g < (1 << j); g++)
+#pragma unroll
+                for (int lo = 0; lo < (1 << half); lo++) {
+                    const int r0 = (g << (half + 1)) | lo, r1 = r0 + (1 << half);
+                    inv_bfly(v[r0], v[r1], m[r0], m[r1], as_const(head)[(1 << j) + g], 0.5f, q);
+                }
+        }
+    }
+#pragma unroll
+    for (int r = 0; r < NR / 2; r++) {
+        double &x = v[r], &y = v[r + NR / 2];
+        if (m[r] + m[r + NR / 2] > BOUND_LIMIT) { x = fp_norm(x, q.p, q.pinv); y = fp_norm(y, q.p, q.pinv); }
+        const double s = x + y, d = x - y;
+        x = fp_norm(fp_mulmod(s, f, q.p, q.pinv), q.p, q.pinv);
+        y = fp_norm(fp_mulmod(d, fw, q.p, q.pinv), q.p, q.pinv);
+    }
+}
+
+template <int RB>
+__device__ __forceinline__ void fwd_columns(double (&v)[Col<RB>::NR], const double* head, const double (&last)[8], Modulus q) {
+    constexpr int NR = Col<RB>::NR;
+    float m[NR];
+#pragma unroll
+    for (int r = 0; r < NR; r++) m[r] = 0.501f;
+    if constexpr (RB == 5) {
+        fwd_levels5(v, m, [&](int j, int g) { return as_const(head)[(1 << j) + g]; }, 0.5f, last, q);
+    } else {
+#pragma unroll
+        for (int j = 0; j < RB; j++) {
+            const int half = RB - 1 - j;
+#pragma unroll
+            for (int g = 0; g < (1 << j); g++)
+#pragma unroll
+                for (int lo = 0; lo < (1 << half); lo++) {
+                    const int r0 = (g << (half + 1)) | lo, r1 = r0 + (1 << half);
+                    fwd_bfly(v[r0], v[r1], m[r0], m[r1], as_const(head)[(1 << j) + g], 0.5f, q);
+                }
+        }
+    }
+}
+#define COLUMNS_BOUND 4.85f   // of the stored values: five levels from normalised sums
+
+// ylds: [source of the chunk][NR][64 lanes]
+template <int RB>
+__device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
+    constexpr int NR = Col<RB>::NR, WIDTH = Col<RB>::WIDTH, TILES = 1024 / WIDTH;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
+    const int tile = blockIdx.x & (TILES - 1), part = blockIdx.x / TILES, digit = part % a.n_digits, split = part / a.n_digits;
+    constexpr u64 n = (u64)1 << (10 + RB);
+    const u64 b = blockIdx.y;
+    const int src0 = a.dg[digit].src0, n_src = a.dg[digit].a, own_lo = a.dg[digit].own_lo, own_n = a.dg[digit].own_n;
+    const int n_tgt = a.ext_limbs - own_n;
+    const int per_split = (n_tgt + a.n_splits - 1) / a.n_splits;
+    const int t_first = split * per_split, t_end = min(t_first + per_split, n_tgt);
+    const int col = tile * WIDTH + (RB == 5 ? (lane & 31) : lane);
+    // lane part and register part of a row's address before the forward / after the inverse levels; RB = 5 keeps two rows
+    // per register, one in each half of the wave
+    const uint32_t in_lane = (uint32_t)((RB == 5 ? 2 * h * 1024 : 0) + col) * 8u;
+    const rsrc_t mid = make_rsrc(a.mid + (b * a.n_src + src0) * n, (uint32_t)(n_src * n * 8u));
+    const int rounds = (t_end - t_first + waves - 1) / waves;
+    const bool resident = n_src <= a.chunk;
+    for (int round = 0; round < rounds; round++) {
+        const int t = t_first + round * waves + wave;
+        const bool mine = t < t_end;
+        const int e = t < own_lo ? t : t + own_n;
+        const int prime = mine ? prime_at(e, a.l, a.L) : 0;
+        const Modulus q = modulus(a.fprimes, prime);
+        const double* head = a.sfwd + (u64)prime * a.table_stride;
+        double v[NR];
+#pragma unroll
+        for (int r = 0; r < NR; r++) v[r] = 0.0;
+        int since = 0;
+        for (int c0 = 0; c0 < n_src; c0 += a.chunk) {
+            const int c1 = min(c0 + a.chunk, n_src);
+            if (!resident || round == 0) {
+                if (c0 || round) __syncthreads();      // every wave is done with the chunk before
+                for (int i = c0 + wave; i < c1; i += waves) {
+                    const int sp = prime_at(a.src_pos0 + src0 + i, a.l, a.L);
+                    const Modulus qs = modulus(a.fprimes, sp);
+                    const double* shead = a.sinv + (u64)sp * a.table_stride;
+                    double w[NR], last[8] = {};
+#pragma unroll
+                    for (int r = 0; r < NR; r++)
+                        w[r] = bloadf(mid, in_lane, (uint32_t)(i * n * 8u) + (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u);
+                    if (RB == 5) {
+                        const rsrc_t hr = make_rsrc(shead, HEAD * 8);
+#pragma unroll
+                        for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
+                    }
+                    double f = as_const(&a.fprimes[sp].p)[3];                     // N^-1, times the limb's factor
+                    if (a.post) f = fp_mulmod(f, as_const(a.post)[src0 + i], qs.p, qs.pinv);
+                    const double fw = fp_mulmod(f, as_const(shead)[1], qs.p, qs.pinv);
+                    inv_columns<RB>(w, shead, last, f, fw, qs);
+                    double* y = ylds + (i - c0) * NR * 64 + lane;
+#pragma unroll
+                    for (int r = 0; r < NR; r += 2) { y[r * 64] = w[r]; y[r * 64 + 64] = w[r + 1]; }
+                }
+                __syncthreads();
+            }
+            if (mine) {
+                for (int i = c0; i < c1; i++) {
+                    const double hat = as_const(a.dg[digit].hat)[(u64)i * a.total + prime];
+                    const double* y = ylds + (i - c0) * NR * 64 + lane;
+#pragma unroll
+                    for (int r = 0; r < NR; r++) v[r] += fp_mulmod(y[r * 64], hat, q.p, q.pinv);
+                    if (++since == 12) {           // twelve terms of at most 0.6 p on top of a normalised sum
+                        since = 0;
+#pragma unroll
+                        for (int r = 0; r < NR; r++) v[r] = fp_norm(v[r], q.p, q.pinv);
+                    }
+                }
+            }
+        }
+        if (mine) {
+            double last[8] = {};
+            if (RB == 5) {
+                const rsrc_t hr = make_rsrc(head, HEAD * 8);
+#pragma unroll
+                for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
+            }
+#pragma unroll
+            for (int r = 0; r < NR; r++) v[r] = fp_norm(v[r], q.p, q.pinv);
+            fwd_columns<RB>(v, head, last, q);
+            const rsrc_t dst = make_rsrc((double*)a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n, (uint32_t)n * 8u);
+#pragma unroll
+            for (int r = 0; r < NR; r++)
+                bstoref(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u, v[r]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// rows, forward
+// ---------------------------------------------------------------------------
+template <int K3, int MODE>
+__device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, double* lds_all) {
+    const int task = row_task(n_tasks);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63;
+    double* lds = lds_all + (threadIdx.x >> 6) * ROW_LDS;
+    const uint32_t unit = (uint32_t)task / a.n_entries;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t row = unit & ((1u << K3) - 1);
+    int t = (int)(unit >> K3);
+    int digit = 0;
+    while (digit + 1 < a.n_digits && t >= a.ext_limbs - a.dg[digit].own_n) { t -= a.ext_limbs - a.dg[digit].own_n; digit++; }
+    const int e = t < a.dg[digit].own_lo ? t : t + a.dg[digit].own_n;
+    const int prime = prime_at(e, a.l, a.L);
+    const Modulus q = modulus(a.fprimes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    u64* out_p = a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n + row * 1024u;
+    const rsrc_t dst = make_rsrc(out_p, 8192u);
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+
+    double v[16];
+    float m[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) { v[r] = bloadf(dst, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+    RowTwiddles w;
+    load_row_twiddles(w, a.sfwd, a.table_stride, prime, row, lane);
+    row_forward(v, m, w, lds, lane, q, MODE == FP_FWD_CONV ? BOUND_LIMIT : 5.2f);    // 5.2 p and the accumulator's 2.75 p stay below 8 p
+
+    if (MODE == FP_FWD_CONV) {
+        // the extended digits stay doubles: their only readers multiply them by key values in the same arithmetic
+#pragma unroll
+        for (int r = 0; r < 16; r++) bstoref(dst, lane8, (uint32_t)r * 512u, fp_norm(v[r], q.p, q.pinv));
+        return;
+    }
+    const rsrc_t acc = make_rsrc(a.acc + b * a.acc_bs + (u64)e * n + row * 1024u, 8192u);
+    if (MODE == FP_FWD_SUB) {      // out = acc - transform: acc already is (sum * P^-1 + addend), the table carries the P^-1
+        double va[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) va[r] = bloadf(acc, lane8, (uint32_t)r * 512u);
+#pragma unroll
+        for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(va[r] - v[r], q.p, q.pinv));
+        return;
+    }
+    // out = (acc - transform) * P^-1 (+ addend)
+    const double pin = as_const(a.pinv_tab)[prime];
+    const bool with_add = a.add && (int)(b % a.add_div) < a.add_polys;
+    u64 va[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) va[r] = bload(acc, lane8, (uint32_t)r * 512u);
+    if (with_add) {
+        const u64 add_ct = a.step_B ? (b / a.add_div) % (u64)a.step_B : b / a.add_div;
+        const u64 add_g = a.step_B ? (u64)a.galois_tab[(b / a.add_div) / (u64)a.step_B] : a.add_galois;
+        double vb[16];
+        load_row_through<K3>(vb, a.add + add_ct * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, add_g, row, lane);
+#pragma unroll
+        for (int r = 0; r < 16; r++)
+            bstore(dst, lane8, (uint32_t)r * 512u,
+                   fp_canonical(fp_mulmod(fp_from_u64(va[r]) - v[r], pin, q.p, q.pinv) + fp_from_u64((u64)__double_as_longlong(vb[r])), q.p, q.pinv));
+    } else {
+#pragma unroll
+        for (int r = 0; r < 16; r++)
+            bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(fp_mulmod(fp_from_u64(va[r]) - v[r], pin, q.p, q.pinv), q.p, q.pinv));
+    }
+}
+
+// ---------------------------------------------------------------------------
+// rows, forward, with the key inner product and the inverse rows of the ModDown's sources
+// ---------------------------------------------------------------------------
+// One pair of waves per (limb x, row, entry).  The digits' rows are shared out between the two: forward levels (or, for the
+// limb's own digit, the input polynomial itself, read through sigma_g), result left in LDS; then wave p multiplies all of
+// them by the key's rows of polynomial p.  The sums never leave the registers before they are what the next launch reads:
+// limbs below n_acc leave as sum * c1[x] + addend * c2[x], limbs from n_acc on (the sources of the division that follows)
+// go straight through the inverse levels of the row.  A wave that kept both sums beside a row and its twiddles needed 168
+// registers and spilled; a pair keeps each wave within 128, four waves per SIMD.
+// Per entry the launch reads (digits' limbs) + own + addend and writes 2 (n_acc + sources) limbs: bound by memory.
+// Bounds, keys and constants centred: a term is at most 0.501 + 3/16 * 5.5 = 1.54 p, four of them 6.2 p; sum * c1 at most
+// 0.501 + 3/16 * 6.2 = 1.7 p; with the addend 2.7 p.
+#define IP_CAP 5.5f
+template <int K3, int MODE>
+__device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs& g, int n_tasks, double* lds_all) {
+    const int per = (n_tasks + 7) >> 3;
+    const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if (task >= n_tasks) return;
+    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int poly = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    double* lds = lds_all + poly * ROW_LDS;
+    const uint32_t unit = (uint32_t)task / a.n_entries;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t row = unit & ((1u << K3) - 1);
+    const int x = g.x_end - 1 - (int)(unit >> K3);              // the limbs with the inverse levels, the longest tasks, first
+    const int prime = prime_at(x, a.l, a.L);
+    const Modulus q = modulus(a.fprimes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+    double sum[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) sum[r] = 0.0;
+    for (int d0 = 0; d0 < a.n_digits; d0 += 2) {
+        const int d = d0 + poly;
+        if (d0) __syncthreads();           // both waves are done with the rows of the two digits before
+        if (d < a.n_digits) {
+            double v[16];
+            if (x >= a.dg[d].own_lo && x < a.dg[d].own_lo + a.dg[d].own_n) {
+                load_row_through<K3>(v, g.own + b * g.own_bs + (u64)x * n, g.galois, row, lane);
+#pragma unroll
+                for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = fp_from_u64((u64)__double_as_longlong(v[r]));
+            } else {
+                const rsrc_t src = make_rsrc((const double*)a.out + b * a.out_bs + (u64)(a.dg[d].out_pos0 + x) * n + row * 1024u, 8192u);
+                float m[16];
+#pragma unroll
+                for (int r = 0; r < 16; r++) { v[r] = bloadf(src, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+                RowTwiddles w;
+                row_tables(w, a.sfwd, a.table_stride, prime, row);
+                int tl = lane;
+                asm volatile("" : "+v"(tl));       // keeps the twiddle loads inside the loop: hoisted they cost 40 registers
+                load_twiddles_b(w, tl);
+                row_forward<true, true>(v, m, w, lds, tl, q, IP_CAP);
+            }
+        }
+        SCHED_FENCE();
+        const double* key_p = (const double*)g.key + (((u64)d0 * 2 + poly) * a.total + prime) * n + row * 1024u;
+        const bool two = d0 + 1 < a.n_digits;
+        const rsrc_t k0r = make_rsrc(key_p, 8192u), k1r = make_rsrc(two ? key_p + (u64)2 * a.total * n : key_p, 8192u);
+        double k0[16], k1[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) k0[r] = bloadf(k0r, lane8, (uint32_t)r * 512u);
+        // (also without a second digit, then of the first: words left undefined would stay live through the loop)
+#pragma unroll
+        for (int r = 0; r < 16; r++) k1[r] = bloadf(k1r, lane8, (uint32_t)r * 512u);
+        SCHED_FENCE();
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(lds_all[66 * r + lane + h], k0[r], q.p, q.pinv);
+        if (two) {
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(lds_all[ROW_LDS + 66 * r + lane + h], k1[r], q.p, q.pinv);
+        }
+        if (d0 % 4 == 2 && d0 + 2 < a.n_digits) {
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum[r] = fp_norm(sum[r], q.p, q.pinv);
+        }
+    }
+    const double c1 = as_const(g.c1)[x];
+    const bool source = MODE == FP_INV_D_TO_Y && x >= g.n_acc;
+#pragma unroll
+    for (int r = 0; r < 16; r++) sum[r] = fp_mulmod(sum[r], c1, q.p, q.pinv);
+    SCHED_FENCE();
+    if (x < a.l && poly < g.add_polys) {
+        double t[16];
+        load_row_through<K3>(t, g.add + b * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, g.galois, row, lane);
+        const double c2 = g.c2 ? as_const(g.c2)[x] : 1.0;
+        if (g.c2) {
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(fp_from_u64((u64)__double_as_longlong(t[r])), c2, q.p, q.pinv);
+        } else {
+#pragma unroll
+            for (int r = 0; r < 16; r++) sum[r] += fp_from_u64((u64)__double_as_longlong(t[r]));
+        }
+    }
+    SCHED_FENCE();
+    const u64 out_limb = source ? (b * 2 + poly) * (u64)(a.ext_limbs - g.n_acc) + (u64)(x - g.n_acc) : (b * 2 + poly) * (u64)g.n_acc + (u64)x;
+    double* dst_p = (source ? g.down : MODE == FP_FWD_CONV_SUB ? (double*)g.out : g.acc) + out_limb * n + row * 1024u;
+    const rsrc_t dst = make_rsrc(dst_p, 8192u);
+    if (source) {
+        __syncthreads();                   // uniform in the workgroup: the other wave still reads this one's row
+        float m[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) m[r] = 2.75f;
+        RowTwiddles w;
+        load_row_twiddles(w, a.sinv, a.table_stride, prime, row, lane);
+        row_inverse(sum, m, w, lds, lane, q);
+    } else if (MODE == FP_FWD_CONV_SUB) {  // the division's columns are there already: its rows, and the difference
+        double v[16];
+        float m[16];
+#pragma unroll
+        for (int r = 0; r < 16; r++) { v[r] = bloadf(dst, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+        RowTwiddles w;
+        load_row_twiddles(w, a.sfwd, a.table_stride, prime, row, lane);
+        __syncthreads();
+        row_forward(v, m, w, lds, lane, q, 5.2f);
+#pragma unroll
+        for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(sum[r] - v[r], q.p, q.pinv));
+        return;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r++) bstoref(dst, lane8, (uint32_t)r * 512u, sum[r]);
+}
+
+// ---------------------------------------------------------------------------
+// the kernel family and its launches
+// ---------------------------------------------------------------------------
+// MODE (enum FpMode) names the stage a launch belongs to, so that a profile tells the ModUp's columns from the ModDown's;
+// COLUMNS: the launch in which all target limbs of a digit share one pass over its sources, else the rows.
+constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : (mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB) ? 128 : ROWS_NT; }
+
+template <int K3, int MODE, bool COLUMNS>
+__global__ __launch_bounds__(fp_threads(MODE, COLUMNS), 4) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
+    if constexpr (COLUMNS) {
+        extern __shared__ double ylds[];
+        columns<K3>(a, ylds);
+    } else {
+        __shared__ double lds[fp_threads(MODE, false) / 64 * ROW_LDS];
+        if constexpr (MODE == FP_INV_TO_Y) rows_inverse<K3>(a, n_tasks, lds);
+        else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE>(a, g, n_tasks, lds);
+        else rows_forward<K3, MODE>(a, n_tasks, lds);
+    }
+}
+
+// Twiddles of one prime for the three kernels, psi^(sign bitrev(i)) as the caller's w(i) gives them (centred doubles):
+//   [0 .. 31]   column levels: entry 2^j + g; N = 2^15: the 16 of level 4 as [half h][k], group 2 k + h
+//   [32 .. 47]  w(g), g < 16: the factors that turn a thread's twiddle of group 0 into that of group g
+//   then per row a, SPLIT_ROW entries (R = N / 1024):
+//   [0 .. 31]   levels on b: entry 2^j + g = w(((R + a) 2^j) + g), level 4 as [h][k]
+//   [32 .. 159] levels on c, j < 4: [j][b] = w((32 (R + a) + b) 2^j)
+//   [160 ..]    level 4 on c: [k / 2][h][b][k & 1] = w(16 (32 (R + a) + b) + 2 k + h)
+size_t split_table_words(int log_n) { return HEAD + ((size_t)SPLIT_ROW << (log_n - 10)); }
+
+// every pointer a launch dereferences is set and every limb it names has a prime: a mistake is a host error
+static bool convert_args_ok(const ConvertArgs& a, u64* targets) {
+    if (a.log_n < 12 || a.log_n > 15 || a.n_entries > 65535 || a.n_digits < 1 || a.n_digits > FP_MAX_DIGITS) return false;
+    if (!a.fprimes || !a.sfwd || !a.sinv || !a.mid || !a.out || a.n_src < 1 || a.l < 1 || a.L < a.l || a.total < 1) return false;
+    if (a.src_pos0 < 0 || a.ext_limbs < 1) return false;
+    auto prime_of = [&](int pos) { return pos < a.l ? pos : pos + (a.L - a.l); };
+    if (prime_of(a.src_pos0 + a.n_src - 1) >= a.total || prime_of(a.ext_limbs - 1) >= a.total) return false;
+    *targets = 0;
+    for (int d = 0; d < a.n_digits; d++) {
+        const ConvertArgs::Digit& g = a.dg[d];
+        if (!g.hat || g.a < 1 || g.src0 < 0 || g.src0 + g.a > a.n_src || g.own_n < 0 || g.own_lo < 0 || g.own_lo + g.own_n > a.ext_limbs ||
+            g.out_pos0 < 0)
+            return false;
+        *targets += (u64)(a.ext_limbs - g.own_n);
+    }
+    return (((u64)a.n_src * a.n_entries) << (a.log_n - 10)) <= 0x7fffff00u && ((*targets * a.n_entries) << (a.log_n - 10)) <= 0x7fffff00u;
+}
+
+template <int K3, int MODE, bool COLUMNS>
+static hipError_t launch_one(dim3 grid, unsigned threads, size_t lds, const ConvertArgs& a, const InnerArgs& g, u64 tasks, hipStream_t st) {
+    static char name[40] = "";      // what rocprofv3 prints for this instantiation
+    if (!name[0]) snprintf(name, sizeof name, "ntt_fp_kernel<%d, %d, %s>", K3, MODE, COLUMNS ? "true" : "false");
+    ProfScope prof__(name, st);
+    hipLaunchKernelGGL((ntt_fp_kernel<K3, MODE, COLUMNS>), grid, dim3(threads), lds, st, a, g, (int)tasks);
+    return hipGetLastError();
+}
+
+template <int MODE>
+static hipError_t launch_rows(const ConvertArgs& a, const InnerArgs& g, u64 limbs, hipStream_t st) {
+    const u64 tasks = (limbs * a.n_entries) << (a.log_n - 10);
+    if (tasks > 0x7fffff00u) return hipErrorInvalidValue;
+    constexpr unsigned threads = fp_threads(MODE, false);
+    const u64 per_block = threads == 128 ? 1 : threads / 64;     // a pair of waves shares a task of the inner products
+    const dim3 grid((unsigned)(((tasks + per_block - 1) / per_block + 7) / 8 * 8));
+    switch (a.log_n) {
+        case 12: return launch_one<2, MODE, false>(grid, threads, 0, a, g, tasks, st);
+        case 13: return launch_one<3, MODE, false>(grid, threads, 0, a, g, tasks, st);
+        case 14: return launch_one<4, MODE, false>(grid, threads, 0, a, g, tasks, st);
+        default: return launch_one<5, MODE, false>(grid, threads, 0, a, g, tasks, st);
+    }
+}
+
+template <int K3, int MODE>
+static hipError_t launch_columns_k3(const ConvertArgs& a_in, hipStream_t st) {
+    ConvertArgs a = a_in;
+    constexpr int NR = Col<K3>::NR, TILES = 1024 / Col<K3>::WIDTH;
+    constexpr int PER_SRC = NR * 64 * 8, MAX_CHUNK = 20 * 8192 / PER_SRC;
+    int most = 1;
+    for (int d = 0; d < a.n_digits; d++) most = a.dg[d].a > most ? a.dg[d].a : most;
+    a.chunk = most < MAX_CHUNK ? most : MAX_CHUNK;
+    const size_t lds = (size_t)a.chunk * PER_SRC;
+    static bool attr_set = false;
+    if (!attr_set) {
+        hipError_t e = hipFuncSetAttribute((const void*)ntt_fp_kernel<K3, MODE, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           MAX_CHUNK * PER_SRC);
+        if (e != hipSuccess) return e;
+        attr_set = true;
+    }
+    // sixteen waves where only one workgroup fits a compute unit's LDS, else eight
+    const unsigned threads = lds > 81920 ? 1024 : 512;
+    // Few entries: several workgroups share a tile's targets (each forms the conversion inputs for itself), so that the
+    // launch reaches about two workgroups per compute unit before a workgroup takes a second round of targets.
+    const int waves = (int)(threads / 64);
+    int rounds = 1;
+    for (int d = 0; d < a.n_digits; d++) {
+        const int r = (a.ext_limbs - a.dg[d].own_n + waves - 1) / waves;
+        rounds = r > rounds ? r : rounds;
+    }
+    a.n_splits = 1;
+    while (a.n_splits < rounds && (u64)a.n_entries * a.n_digits * TILES * (a.n_splits + 1) <= 512) a.n_splits++;
+    return launch_one<K3, MODE, true>(dim3((unsigned)(TILES * a.n_digits * a.n_splits), a.n_entries), threads, lds, a, InnerArgs{}, 0, st);
+}
+
+template <int MODE>
+static hipError_t launch_columns(const ConvertArgs& a, hipStream_t st) {
+    switch (a.log_n) {
+        case 12: return launch_columns_k3<2, MODE>(a, st);
+        case 13: return launch_columns_k3<3, MODE>(a, st);
+        case 14: return launch_columns_k3<4, MODE>(a, st);
+        default: return launch_columns_k3<5, MODE>(a, st);
+    }
+}
+
+hipError_t launch_inverse_rows_fp(const ConvertArgs& a, hipStream_t st) {
+    DRY_RUN_RETURN();
+    if (a.n_entries == 0) return hipSuccess;
+    u64 targets = 0;
+    if (!convert_args_ok(a, &targets) || !a.in) return hipErrorInvalidValue;
+    return launch_rows<FP_INV_TO_Y>(a, InnerArgs{}, (u64)a.n_src, st);
+}
+
+hipError_t launch_columns_fp(int mode, const ConvertArgs& a, hipStream_t st) {
+    DRY_RUN_RETURN();
+    if (a.n_entries == 0) return hipSuccess;
+    u64 targets = 0;
+    if (!convert_args_ok(a, &targets)) return hipErrorInvalidValue;
+    switch (mode) {
+        case FP_FWD_CONV: return launch_columns<FP_FWD_CONV>(a, st);
+        case FP_FWD_CONV_FINAL: return launch_columns<FP_FWD_CONV_FINAL>(a, st);
+        case FP_FWD_CONV_SUB: return launch_columns<FP_FWD_CONV_SUB>(a, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st) {
+    DRY_RUN_RETURN();
+    if (a.n_entries == 0) return hipSuccess;
+    u64 targets = 0;
+    if (!convert_args_ok(a, &targets)) return hipErrorInvalidValue;
+    if (mode != FP_FWD_CONV && (!a.acc || a.n_digits != 1)) return hipErrorInvalidValue;
+    if (mode == FP_FWD_CONV_FINAL) {
+        if (!a.pinv_tab || (a.add && a.add_div <= 0)) return hipErrorInvalidValue;
+        // rotation-major entries: every entry's rotation index must fall inside galois_tab
+        if (a.add && (a.step_B < 0 ||
+            (a.step_B > 0 && ((u64)a.n_entries + (u64)a.add_div * a.step_B - 1) / ((u64)a.add_div * a.step_B) > FP_MAX_STEPS)))
+            return hipErrorInvalidValue;
+    }
+    switch (mode) {
+        case FP_FWD_CONV: return launch_rows<FP_FWD_CONV>(a, InnerArgs{}, targets, st);
+        case FP_FWD_CONV_FINAL: return launch_rows<FP_FWD_CONV_FINAL>(a, InnerArgs{}, targets, st);
+        case FP_FWD_SUB: return launch_rows<FP_FWD_SUB>(a, InnerArgs{}, targets, st);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, hipStream_t st) {
+    DRY_RUN_RETURN();
+    if (a.n_entries == 0) return hipSuccess;
+    u64 targets = 0;
+    if (!convert_args_ok(a, &targets)) return hipErrorInvalidValue;
+    const u64 n = (u64)1 << a.log_n;
+    if (!g.key || !g.own || !g.c1 || g.n_acc < 1 || g.n_acc >= a.ext_limbs || g.n_acc > a.l) return hipErrorInvalidValue;
+    if (g.x_begin < 0 || g.x_begin >= g.x_end || g.x_end > a.ext_limbs) return hipErrorInvalidValue;
+    if (g.own_bs < (u64)a.l * n || g.add_polys < 0 || g.add_polys > 2 || (g.add_polys && !g.add)) return hipErrorInvalidValue;
+    if (g.add_polys && (g.add_bs < (u64)g.add_polys * a.l * n || (g.add_polys > 1 && g.add_ps < (u64)a.l * n))) return hipErrorInvalidValue;
+    const u64 limbs = (u64)(g.x_end - g.x_begin);
+    if (mode == FP_INV_D_TO_Y) {
+        if ((g.x_begin < g.n_acc && !g.acc) || (g.x_end > g.n_acc && !g.down)) return hipErrorInvalidValue;
+        return launch_rows<FP_INV_D_TO_Y>(a, g, limbs, st);
+    }
+    if (mode != FP_FWD_CONV_SUB || g.x_end > g.n_acc || !g.out) return hipErrorInvalidValue;
+    return launch_rows<FP_FWD_CONV_SUB>(a, g, limbs, st);
+}

@@ -5,6 +5,7 @@
 // [..][limb][N] arrays once: they are bound by HBM bandwidth.
 #include "hisa_internal.hpp"
 #include "modarith.hpp"
+#include "fparith.hpp"
 
 #define NT 256
 
@@ -297,6 +298,34 @@ hipError_t launch_key_combine(const PrimeConst* primes, const u64* secret, const
     ProfScope prof__("key_combine_kernel", st);
     hipLaunchKernelGGL(key_combine_kernel, grid, dim3(NT), 0, st, primes, secret, target, e, pmod_all, key_digit, total, L,
                        alpha, digit, log_n);
+    return hipGetLastError();
+}
+
+// residues [n_rows][total][N] -> centred doubles in place, and back: what the fused key switch multiplies by is converted
+// once per key instead of on every use
+__global__ __launch_bounds__(NT) void key_to_doubles_kernel(const FpPrime* fprimes, u64* key, int log_n) {
+    const FpPrime f = fprimes[blockIdx.y];
+    const u64 off = (((u64)blockIdx.z * gridDim.y + blockIdx.y) << log_n) + (u64)blockIdx.x * NT + threadIdx.x;
+    key[off] = (u64)__double_as_longlong(fp_centred_from_u64(key[off], f.p, f.half));
+}
+
+__global__ __launch_bounds__(NT) void key_to_residues_kernel(const FpPrime* fprimes, const u64* key, u64* out, int log_n) {
+    const FpPrime f = fprimes[blockIdx.y];
+    const u64 off = (((u64)blockIdx.z * gridDim.y + blockIdx.y) << log_n) + (u64)blockIdx.x * NT + threadIdx.x;
+    out[off] = fp_canonical(__longlong_as_double((long long)key[off]), f.p, f.pinv);
+}
+
+hipError_t launch_key_to_doubles(const FpPrime* fprimes, u64* key, int n_rows, int total, int log_n, hipStream_t st) {
+    DRY_RUN_RETURN();
+    ProfScope prof__("key_to_doubles_kernel", st);
+    hipLaunchKernelGGL(key_to_doubles_kernel, dim3((1u << log_n) / NT, total, n_rows), dim3(NT), 0, st, fprimes, key, log_n);
+    return hipGetLastError();
+}
+
+hipError_t launch_key_to_residues(const FpPrime* fprimes, const u64* key, u64* out, int n_rows, int total, int log_n, hipStream_t st) {
+    DRY_RUN_RETURN();
+    ProfScope prof__("key_to_residues_kernel", st);
+    hipLaunchKernelGGL(key_to_residues_kernel, dim3((1u << log_n) / NT, total, n_rows), dim3(NT), 0, st, fprimes, key, out, log_n);
     return hipGetLastError();
 }
 

@@ -309,6 +309,28 @@ static hipError_t upload(T** dst, const std::vector<T>& src) {
 
 static double centred_double(u64 x, u64 q) { return x > q / 2 ? -(double)(q - x) : (double)x; }
 
+// one prime's row and column twiddles from psi^(+-bitrev(i)), i < N (layout: convert_fp.hip)
+static void fill_split_table(uint32_t log_n, const u64* w, u64 q, double* out) {
+    const size_t rows = (size_t)1 << (log_n - 10);
+    auto at = [&](size_t i) { return centred_double(w[i], q); };
+    for (size_t j = 0; j + 10 < log_n; j++)
+        for (size_t g = 0; g < ((size_t)1 << j); g++)
+            out[j == 4 ? 16 + (g & 1) * 8 + (g >> 1) : ((size_t)1 << j) + g] = at(((size_t)1 << j) + g);
+    for (size_t g = 0; g < 16; g++) out[32 + g] = at(g);
+    for (size_t a = 0; a < rows; a++) {
+        double* t = out + 64 + a * SPLIT_ROW;
+        for (size_t j = 0; j < 5; j++)
+            for (size_t g = 0; g < ((size_t)1 << j); g++)
+                t[j == 4 ? 16 + (g & 1) * 8 + (g >> 1) : ((size_t)1 << j) + g] = at(((rows + a) << j) + g);
+        for (size_t b = 0; b < 32; b++) {
+            const size_t node = 32 * (rows + a) + b;
+            for (size_t j = 0; j < 4; j++) t[32 + j * 32 + b] = at(node << j);
+            for (size_t k = 0; k < 8; k++)
+                for (size_t h = 0; h < 2; h++) t[160 + (k >> 1) * 128 + (h * 32 + b) * 2 + (k & 1)] = at(16 * node + 2 * k + h);
+        }
+    }
+}
+
 static void build_conv_table_host(const hisa_ctx* ctx, const std::vector<int>& src, std::vector<u64>& inv_hat,
                                   std::vector<u64>& inv_hat_sh, std::vector<u64>& hat, std::vector<u64>& dmod) {
     const int a = (int)src.size(), total = (int)ctx->total;
@@ -378,6 +400,7 @@ static int modup_table(hisa_ctx* ctx, int digit, int a, ConvTable** out) {
 
 static int sample_secret(hisa_ctx* ctx);
 static int fp_post_tables(hisa_ctx* ctx, int l, double** post_q, double** post_p, bool lookup_only);
+static int fp_inner_tables(hisa_ctx* ctx, int l, double** c1, bool lookup_only);
 static std::vector<u64> gauss_table(double sigma);
 
 extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** out) {
@@ -440,7 +463,7 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
     HIP_TRY(ctx, upload(&ctx->d_tw_sh, tw_sh));
     HIP_TRY(ctx, upload(&ctx->d_itw, itw));
     HIP_TRY(ctx, upload(&ctx->d_itw_sh, itw_sh));
-    ctx->tabs = NttTables{ctx->d_primes, ctx->d_tw, ctx->d_tw_sh, ctx->d_itw, ctx->d_itw_sh, 0, nullptr, nullptr, nullptr, nullptr};
+    ctx->tabs = NttTables{ctx->d_primes, ctx->d_tw, ctx->d_tw_sh, ctx->d_itw, ctx->d_itw_sh, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     // fp64 path: every prime below 2^50 and a ring degree the single-launch transform covers
     {
         bool fp_ok = ctx->log_n >= 12 && ctx->log_n <= 15;
@@ -451,6 +474,7 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
             for (uint32_t i = 0; i < ctx->total; i++) {
                 const u64 q = ctx->mod[i];
                 fpr[i].p = (double)q; fpr[i].pinv = 1.0 / (double)q; fpr[i].half = (double)(q / 2);
+                fpr[i].ninv = centred_double(ctx->pc[i].n_inv, q);
                 const u64 psi_inv = hm::inv(ctx->psi[i], q);
                 bwd[0] = 1;
                 for (u64 e = 1; e < n; e++) bwd[e] = hm::mul(bwd[e - 1], psi_inv, q);   // psi^-e
@@ -470,6 +494,17 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
                     for (u64 k = 0; k < m; k++) utw[o + m + k] = centred_double(bwd[k * (n / m)], q);
             }
             HIP_TRY(ctx, upload(&ctx->d_fprimes, fpr));
+            {   // row and column twiddles (layout: convert_fp.hip, split_table_words)
+                const size_t words = split_table_words((int)ctx->log_n);
+                std::vector<double> sf(words * ctx->total, 0.0), si(sf.size(), 0.0);
+                for (uint32_t i = 0; i < ctx->total; i++) {
+                    fill_split_table(ctx->log_n, &tw[(size_t)i * n], ctx->mod[i], &sf[i * words]);
+                    fill_split_table(ctx->log_n, &itw[(size_t)i * n], ctx->mod[i], &si[i * words]);
+                }
+                HIP_TRY(ctx, upload(&ctx->d_sfwd, sf));
+                HIP_TRY(ctx, upload(&ctx->d_sinv, si));
+                ctx->tabs.sfwd = ctx->d_sfwd; ctx->tabs.sinv = ctx->d_sinv;
+            }
             HIP_TRY(ctx, upload(&ctx->d_ftw, ftw));
             HIP_TRY(ctx, upload(&ctx->d_utw, utw));
             HIP_TRY(ctx, upload(&ctx->d_vtw, vtw));
@@ -499,7 +534,7 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
             std::vector<double> pf(ctx->total, 0.0);
             for (uint32_t i = 0; i < ctx->L; i++) pf[i] = centred_double(pinv[i], ctx->mod[i]);
             HIP_TRY(ctx, upload(&ctx->d_pinv_f, pf));
-            {   // (P/p_m) P^-1 mod q_i: the conversion of FP_FWD_CONV_SUB
+            {   // (P/p_m) P^-1 mod q_i: the conversion of the folded ModDown
                 std::vector<u64> ih, ihs, hat, dmod;
                 build_conv_table_host(ctx, src, ih, ihs, hat, dmod);
                 std::vector<double> hp((size_t)ctx->K * ctx->total, 0.0);
@@ -508,8 +543,6 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
                         hp[(size_t)m * ctx->total + i] = centred_double(hm::mul(hat[(size_t)m * ctx->total + i], pinv[i], ctx->mod[i]), ctx->mod[i]);
                 HIP_TRY(ctx, upload(&ctx->d_moddown_hat_pin, hp));
             }
-            ctx->fp_scratch_polys = ctx->log_n <= 13 ? 1024 : 512;
-            HIP_TRY(ctx, hipMalloc(&ctx->d_fp_scratch, (size_t)ctx->fp_scratch_polys * ctx->N * sizeof(double)));
         }
     }
     // 2N-th roots of unity for encode / decode
@@ -538,7 +571,10 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
     if (ctx->tabs.fp_ok && ctx->dnum <= 8) {
         // the small per-level tables of the fused key switch, so that no later call has to build (and allocate) one
         double *pq, *pp;
-        for (uint32_t l = 1; l <= ctx->L; l++) TRY(fp_post_tables(ctx, (int)l, &pq, &pp, false));
+        for (uint32_t l = 1; l <= ctx->L; l++) {
+            TRY(fp_post_tables(ctx, (int)l, &pq, &pp, false));
+            TRY(fp_inner_tables(ctx, (int)l, &pq, false));
+        }
     }
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return HISA_OK;
@@ -561,8 +597,8 @@ extern "C" int hisa_destroy(hisa_ctx* ctx) {
     (void)hipFree(ctx->d_primes); (void)hipFree(ctx->d_tw); (void)hipFree(ctx->d_tw_sh); (void)hipFree(ctx->d_itw);
     (void)hipFree(ctx->d_itw_sh); (void)hipFree(ctx->d_secret); (void)hipFree(ctx->d_pinv); (void)hipFree(ctx->d_pinv_sh);
     (void)hipFree(ctx->d_fprimes); (void)hipFree(ctx->d_ftw); (void)hipFree(ctx->d_utw); (void)hipFree(ctx->d_vtw);
+    (void)hipFree(ctx->d_sfwd); (void)hipFree(ctx->d_sinv);
     (void)hipFree(ctx->d_pinv_f); (void)hipFree(ctx->d_moddown_hat_pin);
-    (void)hipFree(ctx->d_fp_scratch);
     (void)hipFree(ctx->d_pmod); (void)hipFree(ctx->d_cos); (void)hipFree(ctx->d_sin); (void)hipFree(ctx->d_pow5);
     (void)hipFree(ctx->d_gauss_cdt);
     delete ctx;
@@ -668,6 +704,8 @@ static int fill_switch_key(hisa_ctx* ctx, u64 key_id, const u64* target, const S
         HIP_TRY(ctx, launch_key_combine(ctx->d_primes, ctx->d_secret, target, e.u(), ctx->d_pmod, digit, (int)total,
                                         (int)ctx->L, (int)ctx->alpha, (int)j, (int)ctx->log_n, ctx->stream));
     }
+    if (fused_key_switch_available(ctx))
+        HIP_TRY(ctx, launch_key_to_doubles(ctx->d_fprimes, key.data, (int)ctx->dnum * 2, (int)total, (int)ctx->log_n, ctx->stream));
     return HISA_OK;
 }
 
@@ -1304,18 +1342,19 @@ static int fp_post_tables(hisa_ctx* ctx, int l, double** post_q, double** post_p
     return HISA_OK;
 }
 
-// Hybrid key switch of B polynomials with the fused fp64 kernels (all primes below 2^50):
-//   A  inverse transform of d (read through sigma_g if galois != 0) times (D_j/q_i)^-1  -> y, centred doubles
-//   B  per digit: base conversion of y to every other prime fused into the forward transform -> ext
-//   IP inner product with the key; a digit's own limbs are read from d itself             -> acc (l + K limbs, b|a)
-//   C  inverse transform of the K special limbs of acc times (P/p_m)^-1                    -> y2
-//   D  base conversion of y2 to q_i fused into the forward transform, then (acc - conv) P^-1 + addend -> out
-// A and B (the decomposition and ModUp) are one function, IP, C and D another, so that several rotations of the same
-// ciphertexts can share the first: the conversion works coefficient by coefficient on centred values, so it commutes
-// with the automorphism, which then becomes a gather on the extended digits inside IP.
+// Hybrid key switch of B polynomials with the fp64 row and column kernels (convert_fp.hip; all primes below 2^50):
+//   A  inverse rows of d (read through sigma_g if galois != 0)                                              -> y
+//   B  columns: y to centred conversion inputs, base conversion to every other prime, forward levels         -> ext
+//   then one rotation / relinearisation (key_switch_fused_fp):
+//   C  rows of the special limbs: forward levels of ext, inner product with the key, inverse levels          -> down
+//   D  columns: conversion of the special limbs to q_i, forward levels                                       -> out
+//   E  rows of the limbs of q: forward levels of ext, inner product, forward levels of out, difference       -> out
+//   or several that share A and B: forward rows of ext, inner products, then the division by P of the accumulators.
+// A and B (the decomposition and ModUp) can be shared because the conversion works coefficient by coefficient on centred
+// values, so it commutes with the automorphism, which then becomes a gather on the extended digits.
 struct FpExt {
     Temp y, ext;       // pooled buffers, or empty when the caller brought a workspace
-    double* yp;        // [B][l][N] centred doubles
+    double* yp;        // [B][l][N] doubles
     double* extp;      // [B][digits][l + K][N], lazily reduced doubles
     int l, digits, ext_limbs;
     u64 ext_bs;
@@ -1334,50 +1373,20 @@ struct FpExt {
     bool ok() const { return yp && extp; }
 };
 
-static FpArgs fp_base(hisa_ctx* ctx) {
-    FpArgs base = {};
-    base.fprimes = ctx->tabs.fprimes; base.ftw = ctx->tabs.ftw; base.utw = ctx->tabs.utw; base.vtw = ctx->tabs.vtw;
-    base.scratch = ctx->d_fp_scratch; base.scratch_polys = ctx->fp_scratch_polys;
-    return base;
+static ConvertArgs convert_base(hisa_ctx* ctx, int l, size_t entries) {
+    ConvertArgs c = {};
+    c.fprimes = ctx->tabs.fprimes; c.sfwd = ctx->tabs.sfwd; c.sinv = ctx->tabs.sinv;
+    c.table_stride = split_table_words((int)ctx->log_n);
+    c.log_n = (int)ctx->log_n; c.l = l; c.L = (int)ctx->L; c.total = (int)ctx->total; c.n_entries = (unsigned)entries;
+    return c;
 }
-
-static int key_switch_modup_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, FpExt& x, bool no_alloc = false) {
-    const size_t n = ctx->N;
-    const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total, l = x.l;
-    const int log_n = (int)ctx->log_n;
-    hipStream_t st = ctx->stream;
-    double *post_q, *post_p;
-    TRY(fp_post_tables(ctx, l, &post_q, &post_p, no_alloc));
-    FpArgs base = fp_base(ctx);
-    if (no_alloc) { base.scratch = nullptr; base.scratch_polys = 0; base.no_pair = 1; }
-    {   // A
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = l;
-        for (int i = 0; i < l; i++) { tk.pos[i] = (int16_t)i; tk.prime[i] = (int16_t)i; }
-        a.in = d; a.in_bs = d_bs; a.galois = galois; a.post = post_q;
-        a.yout = x.yp; a.yout_bs = (u64)l * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_INV_TO_Y, log_n, a, tk, B, st));
-    }
-    // B.  One launch per digit, or one for all digits (single target limbs) where that takes fewer rounds of
-    // workgroups: small batches, whose per-digit launches would each run one sparse round after the other
-    size_t all_targets = 0;
-    double separate = 0.0;
+// the digits of a key switch at level x.l, converted into x.ext through x.y
+static int modup_digits(hisa_ctx* ctx, ConvertArgs& c, const FpExt& x, bool no_alloc) {
+    const int alpha = (int)ctx->alpha;
+    c.src_pos0 = 0; c.n_src = x.l; c.mid = x.yp;
+    c.n_digits = x.digits; c.ext_limbs = x.ext_limbs; c.out = (u64*)x.extp; c.out_bs = x.ext_bs;
     for (int j = 0; j < x.digits; j++) {
-        const int own = std::min(j * alpha + alpha, l) - j * alpha;
-        all_targets += (size_t)(x.ext_limbs - own);
-        separate += fp_conversion_cost(log_n, own, x.ext_limbs - own, B, nullptr);
-    }
-    const u64 resident = fp_resident_workgroups(log_n);
-    const bool one_launch = x.digits > 1 && x.digits <= FP_MAX_DIGITS && all_targets <= HISA_MAX_PRIMES &&
-                            (double)((B * all_targets + resident - 1) / resident) <= separate;
-    FpArgs a = base;
-    FpTask tk = {};
-    int cnt = 0;
-    a.y = x.yp; a.y_bs = (u64)l * n; a.total = total;
-    a.out = (u64*)x.extp; a.out_bs = x.ext_bs;
-    for (int j = 0; j < x.digits; j++) {
-        const int lo = j * alpha, hi = std::min(lo + alpha, l);
+        const int lo = j * alpha, hi = std::min(lo + alpha, x.l);
         ConvTable* tab;
         if (no_alloc) {   // built with the level's tables when the context was made
             auto it = ctx->modup_tabs.find(std::make_pair(j, hi - lo));
@@ -1386,62 +1395,69 @@ static int key_switch_modup_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois
         } else {
             TRY(modup_table(ctx, j, hi - lo, &tab));
         }
-        const int slot = one_launch ? j : 0;
-        a.dg[slot].hat = tab->d_hat_f; a.dg[slot].y_pos0 = lo; a.dg[slot].conv_a = hi - lo;
-        if (!one_launch) cnt = 0;
-        for (int e = 0; e < x.ext_limbs; e++) {
-            if (e >= lo && e < hi) continue;
-            tk.pos[cnt] = (int16_t)(j * x.ext_limbs + e);
-            tk.prime[cnt] = (int16_t)(e < l ? e : L + (e - l));
-            tk.digit[cnt] = (int8_t)slot;
-            cnt++;
-        }
-        if (!one_launch || j == x.digits - 1) {
-            tk.period = cnt;
-            a.n_digits = one_launch ? x.digits : 1;
-            HIP_TRY(ctx, launch_ntt_fp(FP_FWD_CONV, log_n, a, tk, B, st));
-        }
+        c.dg[j] = {tab->d_hat_f, lo, hi - lo, lo, hi - lo, j * x.ext_limbs};
     }
     return HISA_OK;
 }
 
-// IP, C, D.  `galois` is applied to the own-digit limbs read from d, to the addend, and (gather_ext) to the digits.
-// C, D: acc [B][2][l + K][N] (NTT form) -> out[B][2][l][N] = ModDown(acc) (+ addend, gathered through add_galois if set)
-int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64 add_galois,
-                   u64* out, double* y2_ws) {
-    const size_t n = ctx->N;
-    const int K = (int)ctx->K, L = (int)ctx->L, total = (int)ctx->total, ext_limbs = l + K, log_n = (int)ctx->log_n;
-    hipStream_t st = ctx->stream;
-    // y2_ws: the caller's memory for the conversion input ([B][2][K][N] doubles); then nothing is allocated here
-    const bool no_alloc = y2_ws != nullptr;
-    Temp y2_t(ctx, B * 2 * (size_t)K * n * sizeof(double), !no_alloc);
-    if (!no_alloc && !y2_t.ok()) return HISA_ERR_OOM;
-    double* y2 = no_alloc ? y2_ws : y2_t.as<double>();
-    double *post_q, *post_p;
-    TRY(fp_post_tables(ctx, l, &post_q, &post_p, no_alloc));
-    FpArgs base = fp_base(ctx);
-    if (no_alloc) { base.scratch = nullptr; base.scratch_polys = 0; base.no_pair = 1; }
-    {   // C: batch entries are (ciphertext, b|a) pairs
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = K;
-        for (int m = 0; m < K; m++) { tk.pos[m] = (int16_t)m; tk.prime[m] = (int16_t)(L + m); }
-        a.in = acc; a.in_bs = (u64)ext_limbs * n; a.in_pos_shift = l; a.post = post_p;
-        a.yout = y2; a.yout_bs = (u64)K * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_INV_TO_Y, log_n, a, tk, B * 2, st));
+// P^-1 mod q_i of the l limbs of q, then (P/p_m)^-1 mod p_m of the special ones: what the accumulators of a key switch
+// are multiplied by before the division by P
+static int fp_inner_tables(hisa_ctx* ctx, int l, double** c1, bool lookup_only) {
+    const u64 KEY = 16384 + (u64)l;
+    auto it = ctx->aux.find(KEY);
+    if (it == ctx->aux.end() && lookup_only) return fail(ctx, HISA_ERR_ARG, "no inner-product constants for level %d", l);
+    if (it == ctx->aux.end()) {
+        std::vector<double> t((size_t)l + ctx->K);
+        for (int i = 0; i < l; i++) {
+            u64 pm = 1 % ctx->mod[i];
+            for (uint32_t m = 0; m < ctx->K; m++) pm = hm::mul(pm, ctx->mod[ctx->L + m] % ctx->mod[i], ctx->mod[i]);
+            t[i] = centred_double(hm::inv(pm, ctx->mod[i]), ctx->mod[i]);
+        }
+        for (uint32_t m = 0; m < ctx->K; m++) t[l + m] = centred_double(ctx->moddown_tab->inv_hat[m], ctx->mod[ctx->L + m]);
+        double* d = nullptr;
+        HIP_TRY(ctx, upload(&d, t));
+        it = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{d, t.size() * sizeof(double), 1}, (u64*)d}).first;
     }
-    {   // D
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = l;
-        for (int i = 0; i < l; i++) { tk.pos[i] = (int16_t)i; tk.prime[i] = (int16_t)i; }
-        a.y = y2; a.y_bs = (u64)K * n; a.y_pos0 = 0; a.conv_a = K; a.total = total; a.hat = ctx->moddown_tab->d_hat_f;
-        a.acc = acc; a.acc_bs = (u64)ext_limbs * n; a.acc_pos_shift = 0; a.pinv_tab = ctx->d_pinv_f;
-        a.add = add; a.add_bs = add_bs; a.add_ps = (u64)l * n; a.add_div = 2; a.add_polys = add_polys; a.add_galois = add_galois;
-        a.out = out; a.out_bs = (u64)l * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_FWD_CONV_FINAL, log_n, a, tk, B * 2, st));
-    }
+    *c1 = (double*)it->second.data;
     return HISA_OK;
+}
+
+// A, B and the forward rows: the extended digits in x.ext
+static int key_switch_modup_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, size_t B, FpExt& x) {
+    double *post_q, *post_p;
+    TRY(fp_post_tables(ctx, x.l, &post_q, &post_p, false));
+    ConvertArgs c = convert_base(ctx, x.l, B);
+    TRY(modup_digits(ctx, c, x, false));
+    c.in = d; c.in_bs = d_bs; c.post = post_q;
+    HIP_TRY(ctx, launch_inverse_rows_fp(c, ctx->stream));
+    HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV, c, ctx->stream));
+    HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_CONV, c, ctx->stream));
+    return HISA_OK;
+}
+
+// a division: inverse rows, columns and final rows of accumulators on ext limbs
+static int divide_fp(hisa_ctx* ctx, const ConvertArgs& c) {
+    HIP_TRY(ctx, launch_inverse_rows_fp(c, ctx->stream));
+    HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV_FINAL, c, ctx->stream));
+    HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_CONV_FINAL, c, ctx->stream));
+    return HISA_OK;
+}
+
+// acc [B][2][l + K][N] (NTT form) -> out[B][2][l][N] = ModDown(acc) (+ addend, gathered through add_galois if set)
+int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64 add_galois,
+                   u64* out) {
+    const size_t n = ctx->N;
+    const int K = (int)ctx->K, ext_limbs = l + K;
+    Temp y2(ctx, B * 2 * (size_t)K * n * sizeof(double));
+    if (!y2.ok()) return HISA_ERR_OOM;
+    double *post_q, *post_p;
+    TRY(fp_post_tables(ctx, l, &post_q, &post_p, false));
+    ConvertArgs c = convert_base(ctx, l, B * 2);      // entries are (ciphertext, b|a) pairs
+    c.in = acc; c.in_bs = (u64)ext_limbs * n; c.src_pos0 = l; c.n_src = K; c.post = post_p; c.mid = y2.as<double>();
+    c.n_digits = 1; c.dg[0] = {ctx->moddown_tab->d_hat_f, 0, K, 0, 0, 0}; c.ext_limbs = l; c.out = out; c.out_bs = (u64)l * n;
+    c.acc = acc; c.acc_bs = (u64)ext_limbs * n; c.pinv_tab = ctx->d_pinv_f;
+    c.add = add; c.add_bs = add_bs; c.add_ps = (u64)l * n; c.add_div = 2; c.add_polys = add_polys; c.add_galois = add_galois;
+    return divide_fp(ctx, c);
 }
 
 // Tables of the combined division at level l: sources q_{l-1}, p_0 .. p_{K-1} (conversion table; (D/s_m)^-1 as centred
@@ -1482,7 +1498,7 @@ int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add,
     if (!fused_key_switch_available(ctx)) return fail(ctx, HISA_ERR_ARG, "no fused key-switch path for these parameters");
     if (l < 2) return fail(ctx, HISA_ERR_DEPTH_EXHAUSTED, "no level to rescale into");
     const size_t n = ctx->N;
-    const int K = (int)ctx->K, L = (int)ctx->L, total = (int)ctx->total, ext_limbs = l + K, log_n = (int)ctx->log_n;
+    const int K = (int)ctx->K, ext_limbs = l + K, log_n = (int)ctx->log_n;
     hipStream_t st = ctx->stream;
     ConvTable* tab;
     double *post, *dinv;
@@ -1492,86 +1508,16 @@ int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add,
     if (add)
         HIP_TRY(ctx, launch_fold_addend(ctx->d_primes, acc, (u64)ext_limbs * n, add, add_bs, (u64)l * n, add_polys, ctx->d_pmod, B, l,
                                         log_n, st));
-    const FpArgs base = fp_base(ctx);
-    {   // the limb of q_{l-1} and the special limbs to coefficient form, times (D/s_m)^-1
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = K + 1;
-        for (int m = 0; m <= K; m++) { tk.pos[m] = (int16_t)m; tk.prime[m] = (int16_t)(m == 0 ? l - 1 : L + m - 1); }
-        a.in = acc; a.in_bs = (u64)ext_limbs * n; a.in_pos_shift = l - 1; a.post = post;
-        a.yout = y2.as<double>(); a.yout_bs = (u64)(K + 1) * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_INV_TO_Y, log_n, a, tk, B * 2, st));
-    }
-    {   // conversion to q_0 .. q_{l-2}, forward transform, (acc - conv) D^-1
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = l - 1;
-        for (int i = 0; i < l - 1; i++) { tk.pos[i] = (int16_t)i; tk.prime[i] = (int16_t)i; }
-        a.y = y2.as<double>(); a.y_bs = (u64)(K + 1) * n; a.y_pos0 = 0; a.conv_a = K + 1; a.total = total; a.hat = tab->d_hat_f;
-        a.acc = acc; a.acc_bs = (u64)ext_limbs * n; a.acc_pos_shift = 0; a.pinv_tab = dinv;
-        a.out = out; a.out_bs = (u64)(l - 1) * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_FWD_CONV_FINAL, log_n, a, tk, B * 2, st));
-    }
-    return HISA_OK;
+    ConvertArgs c = convert_base(ctx, l, B * 2);
+    c.in = acc; c.in_bs = (u64)ext_limbs * n; c.src_pos0 = l - 1; c.n_src = K + 1; c.post = post; c.mid = y2.as<double>();
+    c.n_digits = 1; c.dg[0] = {tab->d_hat_f, 0, K + 1, 0, 0, 0}; c.ext_limbs = l - 1; c.out = out; c.out_bs = (u64)(l - 1) * n;
+    c.acc = acc; c.acc_bs = (u64)ext_limbs * n; c.pinv_tab = dinv;
+    return divide_fp(ctx, c);
 }
 
-// C and D for accumulators that carry the elementwise ends of the ModDown already (launch_inner_product_fold_fp):
-// the special limbs hold sum * (P/p_m)^-1 as doubles, the limbs of q hold sum * P^-1 + addend.  out = ModDown + addend.
-static int moddown_folded_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, u64* out, double* y2_ws) {
-    const size_t n = ctx->N;
-    const int K = (int)ctx->K, L = (int)ctx->L, total = (int)ctx->total, ext_limbs = l + K, log_n = (int)ctx->log_n;
-    hipStream_t st = ctx->stream;
-    const bool no_alloc = y2_ws != nullptr;
-    Temp y2_t(ctx, B * 2 * (size_t)K * n * sizeof(double), !no_alloc);
-    if (!no_alloc && !y2_t.ok()) return HISA_ERR_OOM;
-    double* y2 = no_alloc ? y2_ws : y2_t.as<double>();
-    FpArgs base = fp_base(ctx);
-    if (no_alloc) { base.scratch = nullptr; base.scratch_polys = 0; base.no_pair = 1; }
-    {   // C: batch entries are (ciphertext, b|a) pairs
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = K;
-        for (int m = 0; m < K; m++) { tk.pos[m] = (int16_t)m; tk.prime[m] = (int16_t)(L + m); }
-        a.in = acc; a.in_bs = (u64)ext_limbs * n; a.in_pos_shift = l;
-        a.yout = y2; a.yout_bs = (u64)K * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_INV_D_TO_Y, log_n, a, tk, B * 2, st));
-    }
-    {   // D
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = l;
-        for (int i = 0; i < l; i++) { tk.pos[i] = (int16_t)i; tk.prime[i] = (int16_t)i; }
-        a.y = y2; a.y_bs = (u64)K * n; a.y_pos0 = 0; a.conv_a = K; a.total = total; a.hat = ctx->d_moddown_hat_pin;
-        a.acc = acc; a.acc_bs = (u64)ext_limbs * n; a.acc_pos_shift = 0;
-        a.out = out; a.out_bs = (u64)l * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_FWD_CONV_SUB, log_n, a, tk, B * 2, st));
-    }
-    return HISA_OK;
-}
-
-static int key_switch_finish_fp(hisa_ctx* ctx, const FpExt& x, const u64* d, u64 d_bs, u64 galois, int gather_ext, size_t B,
-                                const SwitchKey& key, const u64* add, u64 add_bs, int add_polys, u64* out,
-                                u64* acc_ws = nullptr, double* y2_ws = nullptr) {
-    const size_t n = ctx->N;
-    const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total, l = x.l;
-    const int ext_limbs = x.ext_limbs, log_n = (int)ctx->log_n;
-    // acc_ws, y2_ws: the caller's memory for the accumulators and the ModDown input; both or neither
-    if ((acc_ws == nullptr) != (y2_ws == nullptr)) return fail(ctx, HISA_ERR_ARG, "half a workspace");
-    Temp acc_t(ctx, B * 2 * (size_t)ext_limbs * n * sizeof(u64), acc_ws == nullptr);
-    if (!acc_ws && !acc_t.ok()) return HISA_ERR_OOM;
-    u64* acc = acc_ws ? acc_ws : acc_t.u();
-    double *post_q, *post_p;
-    TRY(fp_post_tables(ctx, l, &post_q, &post_p, acc_ws != nullptr));
-    // the addend is gathered through the same automorphism as the own-digit limbs
-    IpFold fold = {ctx->d_pinv_f, post_p, add_polys > 0 ? add : nullptr, add_bs, (u64)l * n, add_polys};
-    HIP_TRY(ctx, launch_inner_product_fold_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, key.data, total, d,
-                                              d_bs, galois, gather_ext, acc, (u64)2 * ext_limbs * n, B, log_n, fold, ctx->stream));
-    return moddown_folded_fp(ctx, acc, B, l, out, y2_ws);
-}
-
-// IP, C, D for n_steps rotations of the same B ciphertexts in one set of launches (entries rotation-major): a
+// Inner products and division for n_steps rotations of the same B ciphertexts in one set of launches (entries rotation-major): a
 // convolution's taps rotate few ciphertexts many times, and a launch over B entries alone would leave most of the chip
-// idle.  out: [n_steps][B] ciphertexts.  Same arithmetic per entry as key_switch_finish_fp with gather_ext = 1.
+// idle.  out: [n_steps][B] ciphertexts.
 static int key_switch_finish_steps_fp(hisa_ctx* ctx, const FpExt& x, const u64* d, u64 d_bs, const u64* galois,
                                       const SwitchKey* const* keys, int n_steps, size_t B, const u64* add, u64 add_bs, u64* out) {
     const size_t n = ctx->N, E = (size_t)n_steps * B;
@@ -1584,34 +1530,18 @@ static int key_switch_finish_steps_fp(hisa_ctx* ctx, const FpExt& x, const u64* 
     if (!acc.ok() || !y2.ok()) return HISA_ERR_OOM;
     double *post_q, *post_p;
     TRY(fp_post_tables(ctx, l, &post_q, &post_p, false));
-    const FpArgs base = fp_base(ctx);
     IpSteps steps = {};
     for (int s = 0; s < n_steps; s++) { steps.key[s] = keys[s]->data; steps.galois[s] = (uint32_t)galois[s]; }
     HIP_TRY(ctx, launch_inner_product_steps_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, steps, n_steps,
                                                total, d, d_bs, acc.u(), (u64)2 * ext_limbs * n, B, log_n, st));
-    {   // C
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = K;
-        for (int m = 0; m < K; m++) { tk.pos[m] = (int16_t)m; tk.prime[m] = (int16_t)(L + m); }
-        a.in = acc.u(); a.in_bs = (u64)ext_limbs * n; a.in_pos_shift = l; a.post = post_p;
-        a.yout = y2.as<double>(); a.yout_bs = (u64)K * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_INV_TO_Y, log_n, a, tk, E * 2, st));
-    }
-    {   // D
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = l;
-        for (int i = 0; i < l; i++) { tk.pos[i] = (int16_t)i; tk.prime[i] = (int16_t)i; }
-        a.y = y2.as<double>(); a.y_bs = (u64)K * n; a.y_pos0 = 0; a.conv_a = K; a.total = total; a.hat = ctx->moddown_tab->d_hat_f;
-        a.acc = acc.u(); a.acc_bs = (u64)ext_limbs * n; a.acc_pos_shift = 0; a.pinv_tab = ctx->d_pinv_f;
-        a.add = add; a.add_bs = add_bs; a.add_ps = (u64)l * n; a.add_div = 2; a.add_polys = 1;
-        a.step_B = (int)B;
-        for (int s = 0; s < n_steps; s++) a.galois_tab[s] = (uint32_t)galois[s];
-        a.out = out; a.out_bs = (u64)l * n;
-        HIP_TRY(ctx, launch_ntt_fp(FP_FWD_CONV_FINAL, log_n, a, tk, E * 2, st));
-    }
-    return HISA_OK;
+    ConvertArgs c = convert_base(ctx, l, E * 2);
+    c.in = acc.u(); c.in_bs = (u64)ext_limbs * n; c.src_pos0 = l; c.n_src = K; c.post = post_p; c.mid = y2.as<double>();
+    c.n_digits = 1; c.dg[0] = {ctx->moddown_tab->d_hat_f, 0, K, 0, 0, 0}; c.ext_limbs = l; c.out = out; c.out_bs = (u64)l * n;
+    c.acc = acc.u(); c.acc_bs = (u64)ext_limbs * n; c.pinv_tab = ctx->d_pinv_f;
+    c.add = add; c.add_bs = add_bs; c.add_ps = (u64)l * n; c.add_div = 2; c.add_polys = 1;
+    c.step_B = (int)B;
+    for (int s = 0; s < n_steps; s++) c.galois_tab[s] = (uint32_t)galois[s];
+    return divide_fp(ctx, c);
 }
 
 bool fused_key_switch_available(const hisa_ctx* ctx) { return ctx->tabs.fp_ok && ctx->dnum <= 8; }
@@ -1637,7 +1567,7 @@ int rotation_accumulators_fp(hisa_ctx* ctx, const u64* cts, u64 ct_bs, size_t B,
     FpExt x(ctx, B, l, K, alpha);
     if (!x.ok()) return HISA_ERR_OOM;
     const u64* c1 = cts + (size_t)l * n;
-    TRY(key_switch_modup_fp(ctx, c1, ct_bs, 0, B, x));
+    TRY(key_switch_modup_fp(ctx, c1, ct_bs, B, x));
     const u64 acc_bs = (u64)2 * ext_limbs * n;
     for (int g0 = 0; g0 < n_steps; g0 += FP_MAX_STEPS) {
         const int cnt = std::min(FP_MAX_STEPS, n_steps - g0);
@@ -1689,7 +1619,7 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
     Temp addend(ctx, Bn * 2 * (size_t)l * n * sizeof(u64));
     if (!x.ok() || !acc.ok() || !addend.ok()) return HISA_ERR_OOM;
     const u64* c1 = rot + (size_t)l * n;
-    TRY(key_switch_modup_fp(ctx, c1, ct_bs, 0, E, x));
+    TRY(key_switch_modup_fp(ctx, c1, ct_bs, E, x));
     HIP_TRY(ctx, launch_inner_product_sum_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, st, n_steps, total,
                                              c1, ct_bs, acc.u(), (u64)2 * ext_limbs * n, Bn, shared_input ? 1 : 0, (int)ctx->log_n,
                                              ctx->stream));
@@ -1718,7 +1648,7 @@ int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n_
     Temp acc(ctx, n_cts * 2 * (size_t)ext_limbs * n * sizeof(u64));
     if (!x.ok() || !acc.ok()) return HISA_ERR_OOM;
     const u64* d2 = cts3 + 2 * lw;
-    TRY(key_switch_modup_fp(ctx, d2, stride, 0, n_cts, x));
+    TRY(key_switch_modup_fp(ctx, d2, stride, n_cts, x));
     HIP_TRY(ctx, launch_inner_product_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, it->second.data, total, d2,
                                          stride, 0, 0, acc.u(), (u64)2 * ext_limbs * n, n_cts, (int)ctx->log_n, ctx->stream));
     return moddown_rescale_fp(ctx, acc.u(), n_cts, l, cts3, stride, 2, out);
@@ -1789,12 +1719,51 @@ extern "C" int hisa_rot_left_sum_batch(hisa_ctx* ctx, const hisa_ct* const* in, 
     return rc;
 }
 
+// One key switch of B polynomials as five launches (A to E above).  acc != null ([B][2][l][N] doubles): the limbs of q are
+// summed in launch C too and E only subtracts -- the shorter chain of launches where they do not fill the chip.
+static int key_switch_fused_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, const SwitchKey& key, const u64* add,
+                               u64 add_bs, int add_polys, u64* out, const FpExt& x, double* acc, double* down, bool no_alloc) {
+    const size_t n = ctx->N;
+    const int K = (int)ctx->K, l = x.l;
+    double *post_q, *post_p, *c1;
+    TRY(fp_post_tables(ctx, l, &post_q, &post_p, no_alloc));
+    TRY(fp_inner_tables(ctx, l, &c1, no_alloc));
+    ConvertArgs c = convert_base(ctx, l, B);
+    TRY(modup_digits(ctx, c, x, no_alloc));
+    c.in = d; c.in_bs = d_bs; c.galois = galois; c.post = post_q;
+    HIP_TRY(ctx, launch_inverse_rows_fp(c, ctx->stream));
+    HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV, c, ctx->stream));
+    InnerArgs g = {};
+    g.key = key.data; g.own = d; g.own_bs = d_bs; g.galois = galois; g.n_acc = l; g.c1 = c1;
+    g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = add ? add_polys : 0;
+    g.acc = acc; g.down = down;
+    g.x_begin = acc ? 0 : l; g.x_end = x.ext_limbs;
+    HIP_TRY(ctx, launch_inner_rows_fp(FP_INV_D_TO_Y, c, g, ctx->stream));
+    ConvertArgs m = convert_base(ctx, l, B * 2);      // entries are (ciphertext, b|a) pairs
+    m.src_pos0 = l; m.n_src = K; m.mid = down;
+    m.n_digits = 1; m.dg[0] = {ctx->d_moddown_hat_pin, 0, K, 0, 0, 0}; m.ext_limbs = l; m.out = out; m.out_bs = (u64)l * n;
+    HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV_SUB, m, ctx->stream));
+    if (acc) {
+        m.acc = (const u64*)acc; m.acc_bs = (u64)l * n;
+        HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_SUB, m, ctx->stream));
+    } else {
+        g.out = out; g.x_begin = 0; g.x_end = l;
+        HIP_TRY(ctx, launch_inner_rows_fp(FP_FWD_CONV_SUB, c, g, ctx->stream));
+    }
+    return HISA_OK;
+}
+
 static int key_switch_core_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key,
                               const u64* add, u64 add_bs, int add_polys, u64* out) {
     FpExt x(ctx, B, l, (int)ctx->K, (int)ctx->alpha);
-    if (!x.ok()) return HISA_ERR_OOM;
-    TRY(key_switch_modup_fp(ctx, d, d_bs, galois, B, x));
-    return key_switch_finish_fp(ctx, x, d, d_bs, galois, 0, B, key, add, add_bs, add_polys, out);
+    // Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic
+    // (rotLeft of 64 at N = 2^15, 16 limbs: 1.34 ms against 1.52), but makes the last launch's chain longer (one
+    // rotation at N = 2^13: 36 us against 33).  The two meet where the rows of one launch fill about half of the chip.
+    const bool stored = B * (size_t)x.ext_limbs * (ctx->N >> 10) < 1024;
+    Temp acc(ctx, B * 2 * (size_t)l * ctx->N * sizeof(double), stored), down(ctx, B * 2 * (size_t)ctx->K * ctx->N * sizeof(double));
+    if (!x.ok() || (stored && !acc.ok()) || !down.ok()) return HISA_ERR_OOM;
+    return key_switch_fused_fp(ctx, d, d_bs, galois, B, key, add, add_bs, add_polys, out, x, stored ? acc.as<double>() : nullptr,
+                               down.as<double>(), false);
 }
 
 extern "C" int hisa_analysis_begin(hisa_ctx* ctx) {
@@ -1919,7 +1888,7 @@ extern "C" int hisa_rot_left_hoisted_batch(hisa_ctx* ctx, const hisa_ct* const* 
         {
             FpExt x(ctx, n, l, (int)ctx->K, (int)ctx->alpha);
             if (!x.ok()) rc = HISA_ERR_OOM;
-            if (rc == HISA_OK) rc = key_switch_modup_fp(ctx, bi.base + lw, bi.stride, 0, n, x);
+            if (rc == HISA_OK) rc = key_switch_modup_fp(ctx, bi.base + lw, bi.stride, n, x);
             // rotations by a multiple of the slot count are copies; the others go through the key switch in groups
             // of at most FP_MAX_STEPS rotations (and a bounded number of entries) per set of launches
             std::vector<size_t> sw;
@@ -1983,9 +1952,8 @@ extern "C" int hisa_rot_right_assign(hisa_ctx* ctx, hisa_ct* a, int32_t steps) {
 }
 
 // rotLeft of one ciphertext into an existing one, for callers that cannot allocate: the intermediates live in the
-// library's static scratch array, the small tables were built with the context, and the conversion kernels run one
-// target limb per task (the paired form parks partial sums in a buffer of its own).  Same launches otherwise, so the
-// result is bit for bit hisa_rot_left's.
+// library's static scratch array, the small tables were built with the context, and the launches
+// are hisa_rot_left's, so the result is bit for bit the same.
 extern "C" int hisa_rot_left_noalloc(hisa_ctx* ctx, const hisa_ct* a, int32_t steps, hisa_ct* out) {
     if (!ctx) return HISA_ERR_ARG;
     if (!valid_ct(a) || !valid_ct(out)) return fail(ctx, HISA_ERR_ARG, "not a ciphertext");
@@ -2032,9 +2000,8 @@ extern "C" int hisa_rot_left_noalloc(hisa_ctx* ctx, const hisa_ct* a, int32_t st
     unsigned char* ws = (unsigned char*)ctx->noalloc_ws;
     FpExt x(ctx, l, K, alpha, (double*)ws, (double*)(ws + y_b));
     const size_t lw = (size_t)l * n;
-    TRY(key_switch_modup_fp(ctx, a->data + lw, words, g, 1, x, true));
-    TRY(key_switch_finish_fp(ctx, x, a->data + lw, words, g, 0, 1, it->second, a->data, words, 1, out->data,
-                             (u64*)(ws + y_b + ext_b), (double*)(ws + y_b + ext_b + acc_b)));
+    TRY(key_switch_fused_fp(ctx, a->data + lw, words, g, 1, it->second, a->data, words, 1, out->data, x,
+                            (double*)(ws + y_b + ext_b), (double*)(ws + y_b + ext_b + acc_b), true));
     out->scale = a->scale;
     return HISA_OK;
 }
@@ -2124,35 +2091,19 @@ static int fp_rescale_tables(hisa_ctx* ctx, int l, double** ones, double** qlinv
 }
 
 // Rescale with the fused fp64 kernels: the last limb goes to centred coefficient form (one inverse transform per
-// polynomial), and one launch reduces it to every remaining prime, transforms it and forms (c_i - r) q_{l-1}^-1.
+// polynomial), is reduced to every remaining prime and transformed, and (c_i - r) q_{l-1}^-1 is formed.
 // It is the special-prime division of the key switch with a single "special" prime q_{l-1}.
 static int rescale_core_fp(hisa_ctx* ctx, const u64* in, size_t n_bp, int l, u64* out) {
     const size_t nn = ctx->N;
-    const int log_n = (int)ctx->log_n;
     Temp y(ctx, n_bp * nn * sizeof(double));
     if (!y.ok()) return HISA_ERR_OOM;
     double *ones, *qlinv;
     TRY(fp_rescale_tables(ctx, l, &ones, &qlinv));
-    const FpArgs base = fp_base(ctx);
-    {
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = 1; tk.pos[0] = 0; tk.prime[0] = (int16_t)(l - 1);
-        a.in = in; a.in_bs = (u64)l * nn; a.in_pos_shift = l - 1; a.post = ones;
-        a.yout = y.as<double>(); a.yout_bs = nn;
-        HIP_TRY(ctx, launch_ntt_fp(FP_INV_TO_Y, log_n, a, tk, n_bp, ctx->stream));
-    }
-    {
-        FpArgs a = base;
-        FpTask tk = {};
-        tk.period = l - 1;
-        for (int i = 0; i < l - 1; i++) { tk.pos[i] = (int16_t)i; tk.prime[i] = (int16_t)i; }
-        a.y = y.as<double>(); a.y_bs = nn; a.y_pos0 = 0; a.conv_a = 1; a.total = (int)ctx->total; a.hat = ones;
-        a.acc = in; a.acc_bs = (u64)l * nn; a.acc_pos_shift = 0; a.pinv_tab = qlinv;
-        a.out = out; a.out_bs = (u64)(l - 1) * nn;
-        HIP_TRY(ctx, launch_ntt_fp(FP_FWD_CONV_FINAL, log_n, a, tk, n_bp, ctx->stream));
-    }
-    return HISA_OK;
+    ConvertArgs c = convert_base(ctx, l, n_bp);
+    c.in = in; c.in_bs = (u64)l * nn; c.src_pos0 = l - 1; c.n_src = 1; c.post = ones; c.mid = y.as<double>();
+    c.n_digits = 1; c.dg[0] = {ones, 0, 1, 0, 0, 0}; c.ext_limbs = l - 1; c.out = out; c.out_bs = (u64)(l - 1) * nn;
+    c.acc = in; c.acc_bs = (u64)l * nn; c.pinv_tab = qlinv;
+    return divide_fp(ctx, c);
 }
 
 extern "C" int hisa_rescale_batch(hisa_ctx* ctx, hisa_ct* const* cts, size_t n) {
@@ -2312,6 +2263,15 @@ extern "C" int hisa_key_export(hisa_ctx* ctx, uint64_t key_id, uint64_t* host) {
     auto it = ctx->keys.find(key_id);
     if (it == ctx->keys.end()) return fail(ctx, HISA_ERR_NO_KEY, "no key %llu", (unsigned long long)key_id);
     const size_t words = (size_t)ctx->dnum * 2 * ctx->total * ctx->N;
+    if (fused_key_switch_available(ctx)) {
+        Temp res(ctx, words * sizeof(u64));
+        if (!res.ok()) return HISA_ERR_OOM;
+        HIP_TRY(ctx, launch_key_to_residues(ctx->d_fprimes, it->second.data, res.u(), (int)ctx->dnum * 2, (int)ctx->total, (int)ctx->log_n,
+                                            ctx->stream));
+        HIP_TRY(ctx, hipMemcpyAsync(host, res.u(), words * sizeof(u64), hipMemcpyDeviceToHost, ctx->stream));
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+        return HISA_OK;
+    }
     HIP_TRY(ctx, hipMemcpyAsync(host, it->second.data, words * sizeof(u64), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return HISA_OK;

@@ -28,6 +28,7 @@ struct PrimeConst {
 // fp64 view of a prime below 2^50 (exact modular arithmetic in doubles)
 struct FpPrime {
     double p, pinv, half;
+    double ninv;       // N^-1 mod p, centred
 };
 
 // Device pointers to the per-prime tables, [prime][N] each.
@@ -43,6 +44,7 @@ struct NttTables {
     const double* ftw;  // psi^bitrev(i), centred
     const double* utw;  // utw[m + k] = psi^(-k N/m), k < m = 2^t: inverse decimation-in-time twiddles
     const double* vtw;  // psi^-j / N
+    const double *sfwd, *sinv;   // twiddles of the row / column kernels (convert_fp.hip), split_table_words(log_n) per prime
 };
 
 // Which polynomials a batched NTT launch touches: polynomial p (0 <= p <
@@ -103,7 +105,7 @@ struct hisa_pt {
 
 struct SwitchKey {
     DevBlock* blk;
-    u64* data;  // [dnum][2][total][N]: b then a, NTT form
+    u64* data;  // [dnum][2][total][N]: b then a, NTT form; centred doubles where the fused path is available, else residues
 };
 
 struct hisa_ctx {
@@ -129,13 +131,12 @@ struct hisa_ctx {
     double *d_cos, *d_sin;  // [2N] roots of unity exp(i*pi*t/N)
     FpPrime* d_fprimes;     // fp64 path tables (null when not applicable)
     double *d_ftw, *d_utw, *d_vtw, *d_pinv_f;
+    double *d_sfwd = nullptr, *d_sinv = nullptr;   // row and column twiddles
     u64* d_gauss_cdt = nullptr;            // [gauss_cdt_n] floor(2^63 P(|X| <= k)) of the error distribution
     int gauss_cdt_n = 0;
     std::vector<i64> sparse_secret;        // secret_kind = 1: the secret's coefficients, drawn on the host
     double* d_moddown_hat_pin = nullptr;   // [K][total] (P/p_m) * P^-1 mod q_i, centred: ModDown's conversion with the division folded in
     uint32_t* d_pow5;       // [N/2] 5^j mod 2N
-    double* d_fp_scratch;   // fp64 path: one polynomial per resident workgroup of the conversion kernels
-    int fp_scratch_polys;
     std::unordered_map<size_t, std::vector<void*>> pool;
     size_t pool_bytes;
     std::map<uintptr_t, size_t> live;   // blocks handed out by dev_alloc and not yet back in the pool: start -> bytes
@@ -219,7 +220,7 @@ int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add,
 // together with the divScalar by q_{l-1}: out [n][2][l - 1][N] = ((d0, d1) + KS_relin(d2)) / q_{l-1}.
 int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n, int l, u64* out);
 int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64 add_galois,
-                   u64* out, double* y2_ws = nullptr);
+                   u64* out);
 // exact integer nearest to the double v (ties away from zero), reduced modulo q
 u64 double_to_residue(double v, u64 q);
 
@@ -258,27 +259,27 @@ hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride
 hipError_t launch_intt(const NttTables& t, int log_n, u64* data, u64 batch_stride, int n_polys, const PolyMap& map,
                        const InttExtra* extra, hipStream_t st);
 
-// ---- fp64 single-launch transforms with fused neighbours (ntt_fp.hip) ----
+// ---- fp64 transforms (primes below 2^50, N = 2^12 .. 2^15) ----
+// The stages a launch can belong to: 0 and 1 are the whole-polynomial transforms of ntt_fp.hip, the others the row and
+// column kernels of convert_fp.hip.
 enum FpMode {
     FP_FWD_PLAIN = 0,      // u64 coefficients in, u64 NTT form out
     FP_INV_PLAIN = 1,      // u64 NTT form in (optionally gathered through sigma_g), u64 coefficients out
-    FP_INV_TO_Y = 2,       // as INV_PLAIN, times a per-limb constant, output = centred doubles (input of base conversion)
-    FP_FWD_CONV = 3,       // input = fast base conversion of `a` source limbs (centred doubles); NTT form out as lazily
-                           // reduced doubles (|v| <= p/2): the extended digits, which only the inner products read
-    FP_FWD_CONV_FINAL = 4, // as FWD_CONV, then out = (acc - ntt) * P^-1 (+ addend, optionally through sigma_g), u64
-    FP_INV_D_TO_Y = 5,     // as INV_TO_Y for input that already is doubles times the per-limb constant (no gather)
-    FP_FWD_CONV_SUB = 6,   // as FWD_CONV, then out = acc - ntt, u64: the conversion table and acc carry the P^-1, acc the addend
-    FP_N_MODES = 7
+    FP_INV_TO_Y = 2,       // rows: inverse levels of the source limbs of a conversion
+    FP_FWD_CONV = 3,       // columns, rows: conversion of the digits and forward levels -> extended digits (doubles)
+    FP_FWD_CONV_FINAL = 4, // columns, rows: the same for a division: out = (acc - transform) * P^-1 (+ addend), canonical
+    FP_INV_D_TO_Y = 5,     // rows: forward levels of the digits, key inner product, inverse levels of the division's sources
+    FP_FWD_CONV_SUB = 6,   // columns: the division's conversion; rows: key inner product minus the division's transform
+    FP_FWD_SUB = 7,        // rows: stored accumulators minus the division's transform (small calls)
 };
 
 struct FpTask {
     int32_t period;                      // tasks per batch entry
     int16_t pos[HISA_MAX_PRIMES];        // limb position of the task's polynomial inside a batch entry (output side)
     int16_t prime[HISA_MAX_PRIMES];      // its prime
-    int8_t digit[HISA_MAX_PRIMES];       // base-conversion modes: which FpArgs::dg entry describes its source limbs
 };
 
-#define FP_MAX_DIGITS 8  // digits whose conversions one launch can hold
+#define FP_MAX_DIGITS 8   // digits whose conversions one launch can hold
 #define FP_MAX_STEPS 32   // rotations per launch of the shared-decomposition path
 struct FpArgs {
     const FpPrime* fprimes;
@@ -286,59 +287,78 @@ struct FpArgs {
     const double* utw;
     const double* vtw;
     int n_tasks;                       // filled in by the launcher
-    const u64* in; u64 in_bs;          // u64 input [batch][..][N]
-    u64* out; u64 out_bs;              // u64 output
-    double* yout; u64 yout_bs;         // double output (FP_INV_TO_Y)
+    const u64* in; u64 in_bs;          // input [batch][..][N]
+    u64* out; u64 out_bs;
     int in_pos_shift;                  // input limb position = pos + in_pos_shift
-    u64 galois;                        // inverse modes: gather through sigma_g (0 = none)
-    const double* post;                // FP_INV_TO_Y: per task entry constant (centred)
-    // base conversion (FP_FWD_CONV*)
-    const double* y; u64 y_bs;         // [batch][..][N] centred doubles, source limbs at y_pos0 ..
-    int y_pos0, conv_a, total;
-    const double* hat;                 // [a][total] (D/c_i) mod t, centred
-    // Several digits in one launch (each task entry names its digit in FpTask::digit): n_digits > 1 and dg[] filled
-    // in by the caller.  n_digits = 0: one digit, the launcher copies y_pos0, conv_a, hat into dg[0].
+    u64 galois;                        // inverse: gather through sigma_g (0 = none)
+};
+hipError_t launch_ntt_fp(int mode, int log_n, const FpArgs& a, const FpTask& tk, u64 n_batch, hipStream_t st);
+
+// ---- inverse transform -> base conversion -> forward transform by rows and columns (convert_fp.hip) ----
+#define SPLIT_ROW 672                        // table words per row of 1024 coefficients
+size_t split_table_words(int log_n);         // table words per prime
+// Entries [b]; limb position x of an entry belongs to prime x for x < l, L + x - l above.  Sources: limbs
+// src_pos0 .. src_pos0 + n_src - 1 of `in`; digit d converts sources src0 .. src0 + a - 1 to every limb 0 .. ext_limbs - 1
+// outside [own_lo, own_lo + own_n) and leaves limb x at position out_pos0 + x of the output entry.
+struct ConvertArgs {
+    const FpPrime* fprimes;
+    const double *sfwd, *sinv;
+    u64 table_stride;
+    int log_n, l, L, total;
+    unsigned n_entries;
+    const u64* in; u64 in_bs;            // NTT form
+    u64 galois;                          // `in` is read through sigma_g (0 = none)
+    int src_pos0, n_src;
+    const double* post;                  // [n_src] (D/c_i)^-1 of the source's digit, or null: the input carries it
+    double* mid;                         // workspace [n_entries][n_src][N]
     int n_digits;
-    struct Digit { const double* hat; int y_pos0, conv_a; } dg[FP_MAX_DIGITS];
-    double* scratch; int scratch_polys; // one polynomial of doubles per workgroup (at most scratch_polys workgroups)
-    int no_pair;                        // one target limb per task whatever the sizes: `scratch` is then never touched
-    // final combine (FP_FWD_CONV_FINAL): batch entries are (ciphertext, polynomial) pairs
-    const u64* acc; u64 acc_bs; int acc_pos_shift;
-    const double* pinv_tab;            // [prime] P^-1 mod q, centred
-    const u64* add; u64 add_bs, add_ps; int add_div, add_polys;  // addend of entry b: add + (b / add_div) * add_bs +
-    u64 add_galois;                                              // (b % add_div) * add_ps, if b % add_div < add_polys
+    struct Digit { const double* hat; int src0, a, own_lo, own_n, out_pos0; } dg[8];   // hat: [a][total] (D/c_i) mod t
+    int ext_limbs;
+    u64* out; u64 out_bs;
+    int chunk, n_splits;                 // filled in by the launcher
+    // FP_FWD_CONV_FINAL (residues) and FP_FWD_SUB (doubles, |acc| <= 2.75 p): accumulators, limbs in place
+    const u64* acc; u64 acc_bs;
+    const double* pinv_tab;              // [prime] P^-1 mod q, centred
+    // FP_FWD_CONV_FINAL: addend of entry b: add + (b / add_div) * add_bs + (b % add_div) * add_ps, if b % add_div < add_polys
+    const u64* add; u64 add_bs, add_ps; int add_div, add_polys;
+    u64 add_galois;
     // several rotations of the same step_B ciphertexts in one launch (entries ordered rotation-major): entry b's
     // addend is that of ciphertext (b / add_div) % step_B, gathered through galois_tab[(b / add_div) / step_B];
     // step_B = 0: one rotation, add_galois applies
     int step_B;
     uint32_t galois_tab[FP_MAX_STEPS];
 };
-hipError_t launch_ntt_fp(int mode, int log_n, const FpArgs& a, const FpTask& tk, u64 n_batch, hipStream_t st);
-// workgroups of the transform kernel that the chip holds at once (about: 16 waves per compute unit)
-u64 fp_resident_workgroups(int log_n);
-// estimated time of one base-conversion launch (conv_a source limbs, `period` target limbs per batch entry), in units
-// of one single-target task: rounds of workgroups times the task's relative cost, for the cheaper of the two forms
-double fp_conversion_cost(int log_n, int conv_a, int period, u64 n_batch, bool* paired);
+hipError_t launch_inverse_rows_fp(const ConvertArgs& a, hipStream_t st);              // in -> mid
+hipError_t launch_columns_fp(int mode, const ConvertArgs& a, hipStream_t st);         // mid -> out (modes 3, 4, 6)
+hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st);    // out, in place (modes 3, 4, 7)
+// The rows behind the columns of a key switch's digits (ConvertArgs::out: [n_entries][digits][ext_limbs][N]), with the inner
+// product with `key` and the neighbouring halves of the division that follows, for the limbs x_begin .. x_end - 1.
+// FP_INV_D_TO_Y: limbs from n_acc on are sources of that division: down [n_entries * 2][ext_limbs - n_acc][N] =
+// (sum * c1[x] (+ addend * c2[x])) after the inverse rows, `mid` of the division's columns; limbs below n_acc leave as
+// acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend * c2[x]), lazily reduced doubles for FP_FWD_SUB.
+// FP_FWD_CONV_SUB (limbs below n_acc): out holds the division's columns and receives its result.
+// Own digits and addend are read through sigma_g.
+struct InnerArgs {
+    const u64* key;
+    const u64* own; u64 own_bs;
+    u64 galois;
+    int n_acc, x_begin, x_end;
+    const double *c1, *c2;               // [ext_limbs]; c2 null: ones
+    const u64* add; u64 add_bs, add_ps; int add_polys;
+    double* acc;
+    u64* out;
+    double* down;
+};
+hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, hipStream_t st);
+// switching keys of the fused path are kept as centred doubles: [n_rows][total][N] in place; back to canonical residues
+hipError_t launch_key_to_doubles(const FpPrime* fprimes, u64* key, int n_rows, int total, int log_n, hipStream_t st);
+hipError_t launch_key_to_residues(const FpPrime* fprimes, const u64* key, u64* out, int n_rows, int total, int log_n, hipStream_t st);
 
 // acc[b][p][x] = sum_j e_j[x] * key[j][p][prime(x)] in fp64; e_j[x] comes from ext unless x lies in digit j, then
 // from own_src (the NTT-form input itself, read through sigma_g when galois != 0)
 hipError_t launch_inner_product_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
                                    int alpha, const u64* key, int total, const u64* own_src, u64 own_bs, u64 galois,
                                    int gather_ext, u64* acc, u64 acc_bs, u64 n_batch, int log_n, hipStream_t st);
-// The same with the elementwise ends of the ModDown folded in (this kernel waits for memory, the transforms for the
-// vector ALU).  On the limbs of q:   acc = sum * P^-1 + addend  (canonical residues; addend [batch][add_polys][l][N],
-// read through sigma_g like the own-digit limbs, null for none), so that the last kernel only subtracts its transform;
-// on the special limbs:  acc = sum * (P/p_m)^-1  as lazily reduced doubles, the input of FP_INV_D_TO_Y.
-// pin_tab: [prime] P^-1 mod q_i; post_p: [K] (P/p_m)^-1 mod p_m; both centred doubles.
-struct IpFold {
-    const double* pin_tab;
-    const double* post_p;
-    const u64* add; u64 add_bs, add_ps; int add_polys;
-};
-hipError_t launch_inner_product_fold_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
-                                        int alpha, const u64* key, int total, const u64* own_src, u64 own_bs, u64 galois,
-                                        int gather_ext, u64* acc, u64 acc_bs, u64 n_batch, int log_n, const IpFold& fold,
-                                        hipStream_t st);
 // The same for n_steps rotations of the same n_batch ciphertexts (extended digits computed once from the unrotated
 // polynomial): rotation s uses keys[s] and gathers through galois[s]; acc entries are ordered rotation-major.
 // c0_src (with pmod[i] = P mod q_i): the b accumulator also takes P * sigma_s(c0) on the limbs of q, c0 read at

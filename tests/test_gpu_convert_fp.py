@@ -1,0 +1,52 @@
+"""The row and column kernels of the fp64 key switch at the edges of their ranges, bit for bit against the oracle: more source
+limbs than the conversion's LDS holds at once, eight digits (running sums normalised on the way), one source limb, a
+ragged last digit, batches on both sides of the line between stored and register-held accumulators."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# (log_n, q_bits, dnum, special_bits, limbs of the ciphertexts, batch)
+POINTS = [
+    (14, [50] * 21, 1, 50, 21, 1),                     # 21 sources in chunks of 20, 21 targets
+    (15, [50] * 22, 1, 50, 22, 1),
+    (12, [50, 40, 45, 50, 36, 50, 44, 50], 8, 50, 8, 3),
+    (12, [50, 49, 48, 47, 46, 45, 44], 6, 50, 6, 80),  # digits of two limbs and an empty one, register-held accumulators
+    (13, [50, 45, 45, 45, 45, 45, 45], 4, 49, 5, 5),   # ragged last digit below the top level
+    (13, [50, 50], 1, 50, 2, 33),
+    (15, [50, 50, 50, 50], 4, 50, 3, 9),
+]
+
+
+@pytest.mark.parametrize("log_n,q_bits,dnum,special,l,batch", POINTS)
+def test_key_switch_and_rescale(log_n, q_bits, dnum, special, l, batch):
+    from oracle import Oracle
+    from paper_1810_00845_amd import hisa, synth
+    print("[case]", log_n, len(q_bits), dnum, l, batch, flush=True)
+    g, o = hisa.Context(log_n, q_bits, dnum, special, 5), Oracle(log_n, q_bits, dnum, special, 5)
+    g.keygen(); o.keygen()
+    steps = [3, g.slots - 1]
+    g.gen_rot_keys(steps); o.gen_rot_keys(steps)
+    coeff = synth.uniform_residues(log_n + l + batch, (batch, 2, l, g.N), g.primes[:l])
+    coeff[0, :, :, :3] = 0
+    for i in range(l):
+        coeff[0, :, i, 3:6] = g.primes[i] - 1
+    cts = g.ct_import_batch(coeff, 2.0 ** 50)
+    sample = sorted({0, batch - 1})
+    ref = {i: o.import_ct(coeff[i], 2.0 ** 50) for i in sample}
+    out = g.rot_left_batch(cts, 3)
+    hoisted = g.rot_left_hoisted_batch(cts, steps)
+    prod = g.mul_no_relin_batch(cts, cts)
+    g.relinearize_batch(prod)
+    g.rescale_batch(prod)
+    summed = g.rot_left_sum_batch([cts, cts], steps)
+    for i in sample:
+        want = o.export(o.rot_left(ref[i], 3))
+        assert np.array_equal(g.ct_export(out[i]), want)
+        assert np.array_equal(g.ct_export(hoisted[0][i]), want)
+        assert np.array_equal(g.ct_export(hoisted[1][i]), o.export(o.rot_left(ref[i], steps[1])))
+        assert np.array_equal(g.ct_export(prod[i]), o.export(o.rescale(o.mul(ref[i], ref[i]))))
+    from oracle.layers import SharedModDown
+    want = SharedModDown(o, [ref[0]]).total([(0, r, 1, None) for r in steps], ref[0].scale)
+    assert np.array_equal(g.ct_export(summed[0]), o.export(want))
+    g.close()
