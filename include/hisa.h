@@ -107,6 +107,8 @@ int hisa_gen_rot_keys(hisa_ctx* ctx, const int32_t* left_steps, size_t n);
 int hisa_encode(hisa_ctx* ctx, const double* re, const double* im, size_t count, double scale, uint32_t limbs,
                 hisa_pt** out);
 int hisa_decode(hisa_ctx* ctx, const hisa_pt* pt, double* re, double* im, size_t count);
+/* the same slots as (re, im) pairs, values[2 * count] */
+int hisa_decode_complex(hisa_ctx* ctx, const hisa_pt* pt, double* values, size_t count);
 /* Exact route for parity tests: signed integer coefficients host_coeffs[N]. */
 int hisa_pt_from_coeffs(hisa_ctx* ctx, const int64_t* host_coeffs, double scale, uint32_t limbs, hisa_pt** out);
 /* host[limbs][N], coefficient form, canonical residues. */

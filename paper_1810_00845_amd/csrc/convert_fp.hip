@@ -24,6 +24,8 @@
 #include <cstdio>
 
 #include "fp_device.hpp"
+#include "modarith.hpp"
+#include "sampling.hpp"
 
 #define ROW_LDS 1056     // doubles per wave: 32 x 33, one pad word per 32
 #define ROWS_NT 256
@@ -645,6 +647,204 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
 }
 
 // ---------------------------------------------------------------------------
+// whole polynomials by columns and rows: calls with few of them (encode, decode, encryption of a few vectors)
+// ---------------------------------------------------------------------------
+// The single-launch transform of ntt_fp.hip reads and writes a polynomial once but takes 13 / 20 / 35 us at N = 2^13 / 14 /
+// 15 however few there are; this form moves it twice and takes about 5 us a launch until the chip is full.
+// Tasks are waves, (limb, entry, tile of columns) or (limb, entry, row).
+
+__device__ __forceinline__ double residue_of_i64(i64 v, Modulus q) {     // any 64-bit integer, as a normalised double
+    const double hi = (double)(v >> 30), lo = (double)(v & 0x3fffffff);  // |hi| <= 2^33
+    return fp_norm(fp_mulmod(hi, 1073741824.0, q.p, q.pinv) + lo, q.p, q.pinv);
+}
+
+template <int K3>
+__device__ __forceinline__ void load_last(double (&last)[8], const double* head, int h) {
+    if (K3 != 5) return;
+    const rsrc_t hr = make_rsrc(head, HEAD * 8);
+#pragma unroll
+    for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
+}
+
+// byte offset of register r's row before the forward / after the inverse levels on `a` (FIRST), and on the other side
+template <int K3, bool FIRST>
+__device__ __forceinline__ uint32_t column_row(int r) { return (uint32_t)(K3 != 5 ? r : FIRST ? 2 * r : (r >> 1) * 4 + (r & 1)) * 8192u; }
+template <int K3, bool FIRST>
+__device__ __forceinline__ uint32_t column_lane(int tile, int lane) {
+    return (uint32_t)(K3 != 5 ? tile * 64 + lane : tile * 32 + (lane & 31) + (lane >> 5) * (FIRST ? 1024 : 2048)) * 8u;
+}
+
+template <int K3, bool INV>
+__device__ __forceinline__ void plain_columns(const FpArgs& a, const FpTask& tk) {
+    constexpr int NR = Col<K3>::NR, TILES = 1024 / Col<K3>::WIDTH;
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const int task = row_task(a.n_tasks);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63, tile = task & (TILES - 1), unit = task / TILES;
+    const int e = unit / a.n_entries;
+    const u64 b = unit - e * a.n_entries;
+    const int prime = tk.prime[e];
+    const Modulus q = modulus(a.fprimes, prime);
+    const double* head = (INV ? a.sinv : a.sfwd) + (u64)prime * a.table_stride;
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)tk.pos[e] * n, (uint32_t)n * 8u);
+    const uint32_t first = column_lane<K3, true>(tile, lane), other = column_lane<K3, false>(tile, lane);
+    double v[NR], last[8] = {};
+    load_last<K3>(last, head, lane >> 5);
+    if (INV) {
+#pragma unroll
+        for (int r = 0; r < NR; r++) v[r] = bloadf(dst, other, column_row<K3, false>(r));
+        const double f = as_const(&a.fprimes[prime].p)[3], fw = fp_mulmod(f, as_const(head)[1], q.p, q.pinv);
+        inv_columns<K3>(v, head, last, f, fw, q);
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            if (a.centred_out) bstoref(dst, first, column_row<K3, true>(r), v[r]);
+            else bstore(dst, first, column_row<K3, true>(r), fp_to_u64(v[r] < 0.0 ? v[r] + q.p : v[r]));
+        }
+    } else {
+        if (a.coeffs) {
+            const rsrc_t src = make_rsrc(a.coeffs + b * n, (uint32_t)n * 8u);
+            u64 c[NR];
+#pragma unroll
+            for (int r = 0; r < NR; r++) c[r] = bload(src, first, column_row<K3, true>(r));
+#pragma unroll
+            for (int r = 0; r < NR; r++) v[r] = residue_of_i64((i64)c[r], q);
+        } else {
+            const rsrc_t src = make_rsrc(a.in + b * a.in_bs + (u64)(tk.pos[e] + a.in_pos_shift) * n, (uint32_t)n * 8u);
+            u64 c[NR];
+#pragma unroll
+            for (int r = 0; r < NR; r++) c[r] = bload(src, first, column_row<K3, true>(r));
+#pragma unroll
+            for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_from_u64(c[r]), q.p, q.pinv);
+        }
+        fwd_columns<K3>(v, head, last, q);
+#pragma unroll
+        for (int r = 0; r < NR; r++) bstoref(dst, other, column_row<K3, false>(r), v[r]);
+    }
+}
+
+template <int K3, bool INV>
+__device__ __forceinline__ void plain_rows(const FpArgs& a, const FpTask& tk, double* lds_all) {
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const int task = row_task(a.n_tasks);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63, row = task & ((1 << K3) - 1), unit = task >> K3;
+    double* lds = lds_all + (threadIdx.x >> 6) * ROW_LDS;
+    const int e = unit / a.n_entries;
+    const u64 b = unit - e * a.n_entries;
+    const int prime = tk.prime[e];
+    const Modulus q = modulus(a.fprimes, prime);
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)tk.pos[e] * n + (u64)row * 1024u, 8192u);
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+    double v[16];
+    float m[16];
+    RowTwiddles w;
+    if (INV) {
+        load_row_through<K3>(v, a.in + b * a.in_bs + (u64)(tk.pos[e] + a.in_pos_shift) * n, a.galois, (uint32_t)row, lane);
+        load_row_twiddles(w, a.sinv, a.table_stride, prime, (uint32_t)row, lane);
+#pragma unroll
+        for (int r = 0; r < 16; r++) { v[r] = fp_from_u64((u64)__double_as_longlong(v[r])); m[r] = 1.0f; }
+        row_inverse(v, m, w, lds, lane, q);
+#pragma unroll
+        for (int r = 0; r < 16; r++) bstoref(dst, lane8, (uint32_t)r * 512u, v[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 16; r++) { v[r] = bloadf(dst, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+        load_row_twiddles(w, a.sfwd, a.table_stride, prime, (uint32_t)row, lane);
+        row_forward(v, m, w, lds, lane, q, BOUND_LIMIT);
+#pragma unroll
+        for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(v[r], q.p, q.pinv));
+    }
+}
+
+template <int K3, int MODE, bool COLUMNS>
+__global__ __launch_bounds__(ROWS_NT, 4) void ntt_fp_split_kernel(FpArgs a, FpTask tk) {
+    if constexpr (COLUMNS) {
+        plain_columns<K3, MODE == FP_INV_PLAIN>(a, tk);
+    } else {
+        __shared__ double lds[4 * ROW_LDS];
+        plain_rows<K3, MODE == FP_INV_PLAIN>(a, tk, lds);
+    }
+}
+
+// Encryption of a batch: the columns launch draws the uniform polynomial a (into polynomial 1 of the ciphertexts) and the
+// error e (polynomial 0) while it loads them, the rows launch finishes both transforms of a row and stores (-a s + e + m, a).
+template <int K3>
+__global__ __launch_bounds__(ROWS_NT, 4) void encrypt_columns_kernel(EncryptArgs a) {
+    constexpr int NR = Col<K3>::NR, TILES = 1024 / Col<K3>::WIDTH;
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const int task = row_task(a.n_entries * a.limbs * 2 * TILES);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63, tile = task & (TILES - 1), unit = task / TILES;
+    const int poly = unit & 1, limb = (unit >> 1) / a.n_entries;
+    const u64 b = (unit >> 1) - limb * a.n_entries;
+    const Modulus q = modulus(a.fprimes, limb);
+    const double* head = a.sfwd + (u64)limb * a.table_stride;
+    const uint32_t first = column_lane<K3, true>(tile, lane);
+    double v[NR], last[8] = {};
+    load_last<K3>(last, head, lane >> 5);
+    const u64 key = stream_key(a.seed, poly ? 2 : 3, a.ctr + b);
+    if (poly) {
+        const PrimeConst pc = a.primes[limb];
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            const u64 j = (first + column_row<K3, true>(r)) >> 3;
+            v[r] = fp_norm(fp_from_u64(barrett128(0, rnd_at(key, (u64)limb * n + j), pc.q, pc.r1, pc.r0)), q.p, q.pinv);
+        }
+    } else {
+#pragma unroll
+        for (int r = 0; r < NR; r++) {
+            const u64 j = (first + column_row<K3, true>(r)) >> 3;
+            v[r] = a.noise_on ? (double)gaussian_from_word(rnd_at(key, j), a.cdt, a.cdt_n) : 0.0;
+        }
+    }
+    fwd_columns<K3>(v, head, last, q);
+    const rsrc_t dst = make_rsrc(a.ct + ((b * 2 + poly) * a.limbs + limb) * n, (uint32_t)n * 8u);
+    const uint32_t other = column_lane<K3, false>(tile, lane);
+#pragma unroll
+    for (int r = 0; r < NR; r++) bstoref(dst, other, column_row<K3, false>(r), v[r]);
+}
+
+template <int K3>
+__global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a) {
+    __shared__ double lds_all[4 * ROW_LDS];
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const int task = row_task((a.n_entries * a.limbs) << K3);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63;
+    double* lds = lds_all + (threadIdx.x >> 6) * ROW_LDS;
+    const int unit = task / a.n_entries;
+    const u64 b = task - unit * a.n_entries;
+    const int row = unit & ((1 << K3) - 1), limb = unit >> K3;
+    const Modulus q = modulus(a.fprimes, limb);
+    const uint32_t lane8 = (uint32_t)lane * 8u;
+    u64* c0 = a.ct + ((b * 2) * a.limbs + limb) * n + (u64)row * 1024u;
+    const rsrc_t r0 = make_rsrc(c0, 8192u), r1 = make_rsrc(c0 + a.limbs * n, 8192u);
+    const rsrc_t sk = make_rsrc(a.secret + limb * n + (u64)row * 1024u, 8192u), pt = make_rsrc(a.pt[b] + limb * n + (u64)row * 1024u, 8192u);
+    double e[16], v[16];
+    float m[16];
+    RowTwiddles w;
+    load_row_twiddles(w, a.sfwd, a.table_stride, limb, (uint32_t)row, lane);
+#pragma unroll
+    for (int r = 0; r < 16; r++) { e[r] = bloadf(r0, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+    row_forward(e, m, w, lds, lane, q, 3.0f);       // 3 + 1 (message) + 2.5 (a s, below) stays within 8 p
+#pragma unroll
+    for (int r = 0; r < 16; r++) { v[r] = bloadf(r1, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+    row_forward(v, m, w, lds, lane, q, 5.2f);
+    u64 s[16];
+#pragma unroll
+    for (int r = 0; r < 16; r++) s[r] = bload(sk, lane8, (uint32_t)r * 512u);
+#pragma unroll
+    for (int r = 0; r < 16; r++) bstore(r1, lane8, (uint32_t)r * 512u, fp_canonical(v[r], q.p, q.pinv));
+#pragma unroll
+    for (int r = 0; r < 16; r++) e[r] -= fp_mulmod(v[r], fp_from_u64(s[r]), q.p, q.pinv);
+    SCHED_FENCE();
+#pragma unroll
+    for (int r = 0; r < 16; r++) s[r] = bload(pt, lane8, (uint32_t)r * 512u);
+#pragma unroll
+    for (int r = 0; r < 16; r++) bstore(r0, lane8, (uint32_t)r * 512u, fp_canonical(e[r] + fp_from_u64(s[r]), q.p, q.pinv));
+}
+
+// ---------------------------------------------------------------------------
 // the kernel family and its launches
 // ---------------------------------------------------------------------------
 // MODE (enum FpMode) names the stage a launch belongs to, so that a profile tells the ModUp's columns from the ModDown's;
@@ -815,4 +1015,77 @@ hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs&
     }
     if (mode != FP_FWD_CONV_SUB || g.x_end > g.n_acc || !g.out) return hipErrorInvalidValue;
     return launch_rows<FP_FWD_CONV_SUB>(a, g, limbs, st);
+}
+
+// ---- whole polynomials ----
+template <int MODE>
+static hipError_t launch_split(int log_n, FpArgs a, const FpTask& tk, bool columns, hipStream_t st) {
+    const u64 polys = (u64)tk.period * a.n_entries;
+    const int tiles = log_n == 15 ? 32 : 16;
+    a.n_tasks = (int)(columns ? polys * tiles : polys << (log_n - 10));
+    const dim3 grid((unsigned)((((u64)a.n_tasks + 3) / 4 + 7) / 8 * 8));
+    static char names[4][2][40];
+    char* name = names[log_n - 12][columns];
+    if (!name[0]) snprintf(name, 40, "ntt_fp_split_kernel<%d, %d, %s>", log_n - 10, MODE, columns ? "true" : "false");
+    ProfScope prof__(name, st);
+#define SPLIT_CASE(K3)                                                                                             \
+    case 10 + K3:                                                                                                  \
+        if (columns) hipLaunchKernelGGL((ntt_fp_split_kernel<K3, MODE, true>), grid, dim3(ROWS_NT), 0, st, a, tk); \
+        else hipLaunchKernelGGL((ntt_fp_split_kernel<K3, MODE, false>), grid, dim3(ROWS_NT), 0, st, a, tk);        \
+        break;
+    switch (log_n) {
+        SPLIT_CASE(2) SPLIT_CASE(3) SPLIT_CASE(4) SPLIT_CASE(5)
+        default: return hipErrorInvalidValue;
+    }
+#undef SPLIT_CASE
+    return hipGetLastError();
+}
+
+hipError_t launch_ntt_fp_split(int mode, int log_n, const FpArgs& a_in, const FpTask& tk, u64 n_batch, hipStream_t st) {
+    FpArgs a = a_in;
+    if (log_n < 12 || log_n > 15 || !a.sfwd || !a.sinv || !a.out || n_batch == 0 || ((u64)tk.period * n_batch << (log_n - 5)) > 0x7fffff00u)
+        return hipErrorInvalidValue;
+    a.n_entries = (int)n_batch;
+    a.table_stride = split_table_words(log_n);
+    hipError_t e;
+    if (mode == FP_INV_PLAIN) {
+        if (!a.in) return hipErrorInvalidValue;
+        e = launch_split<FP_INV_PLAIN>(log_n, a, tk, false, st);
+        return e == hipSuccess ? launch_split<FP_INV_PLAIN>(log_n, a, tk, true, st) : e;
+    }
+    if (mode != FP_FWD_PLAIN || (!a.in && !a.coeffs)) return hipErrorInvalidValue;
+    e = launch_split<FP_FWD_PLAIN>(log_n, a, tk, true, st);
+    return e == hipSuccess ? launch_split<FP_FWD_PLAIN>(log_n, a, tk, false, st) : e;
+}
+
+template <int K3>
+static hipError_t launch_encrypt_k3(const EncryptArgs& a, hipStream_t st) {
+    const u64 cols = (u64)a.n_entries * a.limbs * 2 * (1024 / Col<K3>::WIDTH), rows = ((u64)a.n_entries * a.limbs) << K3;
+    {
+        ProfScope prof__("encrypt_columns_kernel", st);
+        hipLaunchKernelGGL(encrypt_columns_kernel<K3>, dim3((unsigned)(((cols + 3) / 4 + 7) / 8 * 8)), dim3(ROWS_NT), 0, st, a);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    ProfScope prof__("encrypt_rows_kernel", st);
+    hipLaunchKernelGGL(encrypt_rows_kernel<K3>, dim3((unsigned)(((rows + 3) / 4 + 7) / 8 * 8)), dim3(ROWS_NT), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_encrypt_fp(int log_n, const EncryptArgs& a_in, hipStream_t st) {
+    DRY_RUN_RETURN();
+    EncryptArgs a = a_in;
+    if (!a.fprimes || !a.primes || !a.sfwd || !a.secret || !a.ct || a.limbs < 1 || a.n_entries < 1 || a.n_entries > ENCRYPT_MAX ||
+        (a.noise_on && (!a.cdt || a.cdt_n < 1)))
+        return hipErrorInvalidValue;
+    for (int b = 0; b < a.n_entries; b++)
+        if (!a.pt[b]) return hipErrorInvalidValue;
+    a.table_stride = split_table_words(log_n);
+    switch (log_n) {
+        case 12: return launch_encrypt_k3<2>(a, st);
+        case 13: return launch_encrypt_k3<3>(a, st);
+        case 14: return launch_encrypt_k3<4>(a, st);
+        case 15: return launch_encrypt_k3<5>(a, st);
+        default: return hipErrorInvalidValue;
+    }
 }

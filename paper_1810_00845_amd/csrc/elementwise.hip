@@ -6,20 +6,9 @@
 #include "hisa_internal.hpp"
 #include "modarith.hpp"
 #include "fparith.hpp"
+#include "sampling.hpp"
 
 #define NT 256
-
-// ---- counter-based generator: rnd(seed, kind, ctr, idx) -------------------
-__device__ __forceinline__ u64 mix64(u64 x) {
-    x ^= x >> 32; x *= 0x6a09e667f3bcc909ULL;
-    x ^= x >> 29; x *= 0xbb67ae8584caa73bULL;
-    x ^= x >> 32;
-    return x;
-}
-__device__ __forceinline__ u64 stream_key(u64 seed, u64 kind, u64 ctr) {
-    return mix64(seed + 0x3c6ef372fe94f82bULL * (((kind << 56) | ctr) + 1));
-}
-__device__ __forceinline__ u64 rnd_at(u64 key, u64 idx) { return mix64(key + 0x3c6ef372fe94f82bULL * (idx + 1)); }
 
 __global__ __launch_bounds__(NT) void sample_uniform_kernel(const PrimeConst* primes, u64 seed, u64 kind, u64 ctr,
                                                             PolyMap map, u64 batch_stride, u64 ctr_step, u64* out,
@@ -62,10 +51,7 @@ __global__ __launch_bounds__(NT) void sample_small_kernel(const PrimeConst* prim
         u64 t = w % 3;
         v = t == 0 ? 0 : (t == 1 ? 1 : -1);
     } else if (noise_on) {
-        u64 mag_src = w >> 1;
-        i64 mag = 0;
-        for (int k = 0; k < cdt_n; k++) mag += (mag_src >= cdt[k]);
-        v = (w & 1) ? -mag : mag;
+        v = gaussian_from_word(w, cdt, cdt_n);
     } else {
         v = 0;
     }
@@ -251,10 +237,12 @@ hipError_t launch_encrypt_combine(const PrimeConst* primes, const u64* secret, c
 }
 
 // pt = c0 + c1*s (+ c2*s^2)
-__global__ __launch_bounds__(NT) void decrypt_kernel(const PrimeConst* primes, const u64* secret, const u64* ct, u64* pt,
+__global__ __launch_bounds__(NT) void decrypt_kernel(const PrimeConst* primes, const u64* secret, const u64* ct, u64 ct_bs, u64* pt,
                                                      int limbs, int polys, int log_n) {
     const u64 n = (u64)1 << log_n;
     const int limb = blockIdx.y;
+    ct += (u64)blockIdx.z * ct_bs;
+    pt += (u64)blockIdx.z * limbs * n;
     const PrimeConst pc = primes[limb];
     const u64 off = (u64)limb * n + (u64)blockIdx.x * NT + threadIdx.x;
     const u64 s = secret[off];
@@ -266,12 +254,13 @@ __global__ __launch_bounds__(NT) void decrypt_kernel(const PrimeConst* primes, c
     pt[off] = acc;
 }
 
-hipError_t launch_decrypt(const PrimeConst* primes, const u64* secret, const u64* ct, u64* pt, int limbs, int polys,
-                          int log_n, hipStream_t st) {
+hipError_t launch_decrypt(const PrimeConst* primes, const u64* secret, const u64* ct, u64 ct_bs, u64* pt, int limbs, int polys,
+                          u64 n_batch, int log_n, hipStream_t st) {
     DRY_RUN_RETURN();
-    dim3 grid((1u << log_n) / NT, limbs);
+    if (n_batch == 0 || n_batch > 65535) return hipErrorInvalidValue;
+    dim3 grid((1u << log_n) / NT, limbs, (unsigned)n_batch);
     ProfScope prof__("decrypt_kernel", st);
-    hipLaunchKernelGGL(decrypt_kernel, grid, dim3(NT), 0, st, primes, secret, ct, pt, limbs, polys, log_n);
+    hipLaunchKernelGGL(decrypt_kernel, grid, dim3(NT), 0, st, primes, secret, ct, ct_bs, pt, limbs, polys, log_n);
     return hipGetLastError();
 }
 

@@ -234,6 +234,28 @@ void dev_release(hisa_ctx* ctx, DevBlock* b) {
 
 
 
+void* pinned_block(hisa_ctx* ctx, size_t bytes) {
+    bytes = (bytes + 255) & ~(size_t)255;
+    if (bytes > PIN_BYTES) return nullptr;
+    if (!ctx->pin) {
+        if (hipHostMalloc((void**)&ctx->pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            ctx->pin = nullptr;
+            fail(ctx, HISA_ERR_OOM, "no pinned host memory");
+            return nullptr;
+        }
+        ctx->pin_bytes = PIN_BYTES;
+        ctx->pin_pos = 0;
+    }
+    if (ctx->pin_pos + bytes > ctx->pin_bytes) {
+        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return nullptr;
+        ctx->pin_pos = 0;
+    }
+    void* p = ctx->pin + ctx->pin_pos;
+    ctx->pin_pos += bytes;
+    return p;
+}
+
 // n ciphertext handles that are views of one allocation, [n][polys][limbs][N]
 int alloc_ct_batch(hisa_ctx* ctx, size_t n, uint32_t polys, uint32_t limbs, double scale, hisa_ct** out) {
     size_t words = ct_words(ctx, polys, limbs);
@@ -555,10 +577,18 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
         }
         HIP_TRY(ctx, upload(&ctx->d_cos, cs));
         HIP_TRY(ctx, upload(&ctx->d_sin, sn));
+        // stage twiddles of the transform over the slot order: exp(i pi (5^j mod 4 len) / (2 len)), len = 2 half
+        std::vector<double> tw2(n, 0.0);
         std::vector<uint32_t> pow5(n / 2);
         uint32_t g = 1;
         for (u64 j = 0; j < n / 2; j++) { pow5[j] = g; g = (g * 5u) & (uint32_t)(2 * n - 1); }
-        HIP_TRY(ctx, upload(&ctx->d_pow5, pow5));
+        for (u64 half = 1; half < n / 2; half <<= 1)
+            for (u64 j = 0; j < half; j++) {
+                const u64 e = (pow5[j] & (8 * half - 1)) * (n / (4 * half));
+                tw2[2 * (half + j)] = cs[e];
+                tw2[2 * (half + j) + 1] = sn[e];
+            }
+        HIP_TRY(ctx, upload(&ctx->d_sfft_tw, tw2));
     }
     {
         const std::vector<u64> cdt = gauss_table(prm->sigma == 0.0 ? 3.2 : prm->sigma);
@@ -599,7 +629,8 @@ extern "C" int hisa_destroy(hisa_ctx* ctx) {
     (void)hipFree(ctx->d_fprimes); (void)hipFree(ctx->d_ftw); (void)hipFree(ctx->d_utw); (void)hipFree(ctx->d_vtw);
     (void)hipFree(ctx->d_sfwd); (void)hipFree(ctx->d_sinv);
     (void)hipFree(ctx->d_pinv_f); (void)hipFree(ctx->d_moddown_hat_pin);
-    (void)hipFree(ctx->d_pmod); (void)hipFree(ctx->d_cos); (void)hipFree(ctx->d_sin); (void)hipFree(ctx->d_pow5);
+    (void)hipFree(ctx->d_pmod); (void)hipFree(ctx->d_cos); (void)hipFree(ctx->d_sin); (void)hipFree(ctx->d_sfft_tw);
+    if (ctx->pin) (void)hipHostFree(ctx->pin);
     (void)hipFree(ctx->d_gauss_cdt);
     delete ctx;
     return HISA_OK;
@@ -778,8 +809,7 @@ extern "C" int hisa_pt_from_coeffs(hisa_ctx* ctx, const int64_t* host_coeffs, do
     HIP_TRY(ctx, hipMemcpyAsync(co.blk->ptr, host_coeffs, ctx->N * sizeof(i64), hipMemcpyHostToDevice, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));  // the host buffer may be reused by the caller
     TRY(alloc_pt(ctx, limbs, scale, out));
-    HIP_TRY(ctx, launch_reduce_i64(ctx->d_primes, co.as<i64>(), (*out)->data, (int)limbs, 1, (int)ctx->log_n, ctx->stream));
-    HIP_TRY(ctx, launch_ntt(ctx->tabs, (int)ctx->log_n, (*out)->data, 0, (int)limbs, identity_map((int)limbs), ctx->stream));
+    HIP_TRY(ctx, launch_ntt_i64(ctx->tabs, (int)ctx->log_n, co.as<i64>(), (*out)->data, (int)limbs, 1, ctx->stream));
     return HISA_OK;
 }
 
@@ -788,26 +818,21 @@ extern "C" int hisa_encode(hisa_ctx* ctx, const double* re, const double* im, si
     if (!ctx || !out || (!re && count) || limbs < 1 || limbs > ctx->L || count > ctx->N / 2 || !(scale > 0))
         return fail(ctx, HISA_ERR_ARG, "bad argument");
     // coefficients must fit a signed 64-bit integer: |m_k| <= scale * max|z| * ~1
-    Temp buf(ctx, (2 * count + 2) * sizeof(double));
-    Temp co(ctx, ctx->N * sizeof(i64));
-    if (!buf.ok() || !co.ok()) return HISA_ERR_OOM;
-    double* d_re = buf.as<double>();
-    double* d_im = im ? d_re + count : nullptr;
-    if (count) HIP_TRY(ctx, hipMemcpyAsync(d_re, re, count * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    if (im && count) HIP_TRY(ctx, hipMemcpyAsync(d_im, im, count * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
-    if (count > 64) {   // the O(N log N) transform over the slot order; a handful of slots is cheaper summed directly
-        Temp work(ctx, (ctx->N / 2) * 2 * sizeof(double));
-        if (!work.ok()) return HISA_ERR_OOM;
-        HIP_TRY(ctx, launch_encode_fft(ctx->d_cos, ctx->d_sin, ctx->d_pow5, d_re, d_im, nullptr, (int)count, 1,
-                                       2.0 * scale / (double)ctx->N, work.blk->ptr, co.as<i64>(), (int)ctx->log_n, ctx->stream));
-    } else {
-        HIP_TRY(ctx, launch_encode(ctx->d_cos, ctx->d_sin, ctx->d_pow5, d_re, d_im, (int)count, 1, 2.0 * scale / (double)ctx->N,
-                                   co.as<i64>(), (int)ctx->log_n, ctx->stream));
-    }
+    double* v = (double*)pinned_block(ctx, (im ? 2 : 1) * count * sizeof(double));
+    if (!v) return HISA_ERR_OOM;
+    if (count) memcpy(v, re, count * sizeof(double));
+    if (im && count) memcpy(v + count, im, count * sizeof(double));
     TRY(alloc_pt(ctx, limbs, scale, out));
-    HIP_TRY(ctx, launch_reduce_i64(ctx->d_primes, co.as<i64>(), (*out)->data, (int)limbs, 1, (int)ctx->log_n, ctx->stream));
-    HIP_TRY(ctx, launch_ntt(ctx->tabs, (int)ctx->log_n, (*out)->data, 0, (int)limbs, identity_map((int)limbs), ctx->stream));
+    return encode_dense(ctx, v, im ? v + count : nullptr, (int)count, 1, scale, (int)limbs, (*out)->data);
+}
+
+int encode_dense(hisa_ctx* ctx, const double* re, const double* im, int count, int n_pts, double scale, int limbs, u64* out) {
+    const size_t n = ctx->N;
+    Temp co(ctx, n_pts * n * sizeof(i64)), work(ctx, n_pts * n * sizeof(double));
+    if (!co.ok() || !work.ok()) return HISA_ERR_OOM;
+    HIP_TRY(ctx, launch_encode_fft(ctx->d_sfft_tw, re, im, nullptr, count, n_pts, 2.0 * scale / (double)n, work.blk->ptr, co.as<i64>(),
+                                   (int)ctx->log_n, ctx->stream));
+    HIP_TRY(ctx, launch_ntt_i64(ctx->tabs, (int)ctx->log_n, co.as<i64>(), out, limbs, n_pts, ctx->stream));
     return HISA_OK;
 }
 
@@ -835,34 +860,73 @@ static int garner_tables(hisa_ctx* ctx, u64** inv, u64** inv_sh) {
     return HISA_OK;
 }
 
+// the same inverses as centred doubles, [m * L + i] = q_m^-1 mod q_i
+static int garner_tables_fp(hisa_ctx* ctx, double** inv) {
+    static const u64 KEY = 2;
+    auto it = ctx->aux.find(KEY);
+    if (it == ctx->aux.end()) {
+        const size_t L = ctx->L;
+        std::vector<double> t(L * L, 0.0);
+        for (size_t m = 0; m < L; m++)
+            for (size_t i = 0; i < L; i++)
+                if (i != m) t[m * L + i] = centred_double(hm::inv(ctx->mod[m] % ctx->mod[i], ctx->mod[i]), ctx->mod[i]);
+        double* d = nullptr;
+        HIP_TRY(ctx, upload(&d, t));
+        it = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{d, t.size() * sizeof(double), 1}, (u64*)d}).first;
+    }
+    *inv = (double*)it->second.data;
+    return HISA_OK;
+}
+
+int decode_dense(hisa_ctx* ctx, const u64* pts, int n_pts, int limbs, double scale, int count, double* z) {
+    const size_t n = ctx->N;
+    const int log_n = (int)ctx->log_n;
+    if (count == 0 || n_pts == 0) return HISA_OK;
+    Temp co(ctx, (size_t)n_pts * limbs * n * sizeof(u64)), m(ctx, n_pts * n * sizeof(double));
+    if (!co.ok() || !m.ok()) return HISA_ERR_OOM;
+    if (ctx->tabs.fp_ok) {
+        double* ginv;
+        TRY(garner_tables_fp(ctx, &ginv));
+        HIP_TRY(ctx, launch_intt_centred(ctx->tabs, log_n, pts, co.as<double>(), limbs, n_pts, ctx->stream));
+        HIP_TRY(ctx, launch_crt_fp(ctx->d_fprimes, co.as<double>(), limbs, ginv, (int)ctx->L, 1.0 / scale, m.as<double>(), n_pts, log_n,
+                                   ctx->stream));
+    } else {
+        InttExtra ex = {};
+        ex.in = pts; ex.in_batch_stride = (u64)limbs * n;
+        HIP_TRY(ctx, launch_intt(ctx->tabs, log_n, co.u(), (u64)limbs * n, n_pts * limbs, identity_map(limbs), &ex, ctx->stream));
+        u64 *ginv, *ginv_sh;
+        TRY(garner_tables(ctx, &ginv, &ginv_sh));
+        HIP_TRY(ctx, launch_crt_to_double(ctx->d_primes, co.u(), limbs, ginv, ginv_sh, (int)ctx->L, 1.0 / scale, m.as<double>(), n_pts,
+                                          log_n, ctx->stream));
+    }
+    if (count > 16) {
+        Temp work(ctx, n_pts * n * sizeof(double));
+        if (!work.ok()) return HISA_ERR_OOM;
+        HIP_TRY(ctx, launch_decode_fft(ctx->d_sfft_tw, m.as<double>(), count, n_pts, work.blk->ptr, z, log_n, ctx->stream));
+    } else {
+        HIP_TRY(ctx, launch_decode(ctx->d_cos, ctx->d_sin, m.as<double>(), count, n_pts, z, log_n, ctx->stream));
+    }
+    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    return HISA_OK;
+}
+
 extern "C" int hisa_decode(hisa_ctx* ctx, const hisa_pt* pt, double* re, double* im, size_t count) {
     if (!ctx || !valid_pt(pt) || !re || count > ctx->N / 2) return fail(ctx, HISA_ERR_ARG, "bad argument");
-    const size_t n = ctx->N;
-    Temp co(ctx, (size_t)pt->limbs * n * sizeof(u64));
-    Temp m(ctx, n * sizeof(double));
-    Temp z(ctx, (2 * count + 2) * sizeof(double));
-    if (!co.ok() || !m.ok() || !z.ok()) return HISA_ERR_OOM;
-    InttExtra ex = {};
-    ex.in = pt->data;
-    HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, co.u(), 0, (int)pt->limbs, identity_map((int)pt->limbs), &ex,
-                             ctx->stream));
-    u64 *ginv, *ginv_sh;
-    TRY(garner_tables(ctx, &ginv, &ginv_sh));
-    HIP_TRY(ctx, launch_crt_to_double(ctx->d_primes, co.u(), (int)pt->limbs, ginv, ginv_sh, (int)ctx->L, 1.0 / pt->scale,
-                                      m.as<double>(), (int)ctx->log_n, ctx->stream));
-    double* d_re = z.as<double>();
-    double* d_im = d_re + count;
-    if (count > 16) {
-        Temp work(ctx, (n / 2) * 2 * sizeof(double));
-        if (!work.ok()) return HISA_ERR_OOM;
-        HIP_TRY(ctx, launch_decode_fft(ctx->d_cos, ctx->d_sin, ctx->d_pow5, m.as<double>(), (int)count, work.blk->ptr, d_re, d_im,
-                                       (int)ctx->log_n, ctx->stream));
-    } else {
-        HIP_TRY(ctx, launch_decode(ctx->d_cos, ctx->d_sin, m.as<double>(), (int)count, d_re, d_im, (int)ctx->log_n, ctx->stream));
-    }
-    if (count) HIP_TRY(ctx, hipMemcpyAsync(re, d_re, count * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    if (im && count) HIP_TRY(ctx, hipMemcpyAsync(im, d_im, count * sizeof(double), hipMemcpyDeviceToHost, ctx->stream));
-    HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
+    const double* z = (const double*)pinned_block(ctx, 2 * count * sizeof(double));
+    if (!z) return HISA_ERR_OOM;
+    TRY(decode_dense(ctx, pt->data, 1, (int)pt->limbs, pt->scale, (int)count, (double*)z));
+    for (size_t j = 0; j < count; j++) re[j] = z[2 * j];
+    if (im)
+        for (size_t j = 0; j < count; j++) im[j] = z[2 * j + 1];
+    return HISA_OK;
+}
+
+extern "C" int hisa_decode_complex(hisa_ctx* ctx, const hisa_pt* pt, double* values, size_t count) {
+    if (!ctx || !valid_pt(pt) || !values || count > ctx->N / 2) return fail(ctx, HISA_ERR_ARG, "bad argument");
+    const void* z = pinned_block(ctx, 2 * count * sizeof(double));
+    if (!z) return HISA_ERR_OOM;
+    TRY(decode_dense(ctx, pt->data, 1, (int)pt->limbs, pt->scale, (int)count, (double*)z));
+    memcpy(values, z, 2 * count * sizeof(double));
     return HISA_OK;
 }
 
@@ -901,6 +965,19 @@ extern "C" int hisa_encrypt_batch(hisa_ctx* ctx, const hisa_pt* const* pts, size
     TRY(alloc_ct_batch(ctx, n, 2, l, pts[0]->scale, out));
     for (size_t i = 0; i < n; i++) out[i]->scale = pts[i]->scale;
     u64* ct = out[0]->data;
+    if (ctx->tabs.fp_ok) {
+        for (size_t i0 = 0; i0 < n; i0 += ENCRYPT_MAX) {
+            EncryptArgs a = {};
+            a.fprimes = ctx->d_fprimes; a.primes = ctx->d_primes; a.sfwd = ctx->d_sfwd; a.secret = ctx->d_secret;
+            a.limbs = (int)l; a.n_entries = (int)std::min<size_t>(ENCRYPT_MAX, n - i0); a.noise_on = (int)ctx->prm.noise;
+            a.ct = ct + i0 * 2 * lw; a.seed = ctx->prm.seed; a.ctr = ctx->enc_counter + i0;
+            a.cdt = ctx->d_gauss_cdt; a.cdt_n = ctx->gauss_cdt_n;
+            for (int b = 0; b < a.n_entries; b++) a.pt[b] = pts[i0 + b]->data;
+            HIP_TRY(ctx, launch_encrypt_fp((int)ctx->log_n, a, ctx->stream));
+        }
+        ctx->enc_counter += n;
+        return HISA_OK;
+    }
     Temp e(ctx, n * lw * sizeof(u64));
     Temp ptbuf(ctx, n * lw * sizeof(u64));
     if (!e.ok() || !ptbuf.ok()) return HISA_ERR_OOM;
@@ -939,7 +1016,7 @@ extern "C" int hisa_set_enc_counter(hisa_ctx* ctx, uint64_t counter) {
 extern "C" int hisa_decrypt(hisa_ctx* ctx, const hisa_ct* ct, hisa_pt** out) {
     if (!ctx || !valid_ct(ct) || !out) return fail(ctx, HISA_ERR_ARG, "bad argument");
     TRY(alloc_pt(ctx, ct->limbs, ct->scale, out));
-    HIP_TRY(ctx, launch_decrypt(ctx->d_primes, ctx->d_secret, ct->data, (*out)->data, (int)ct->limbs, (int)ct->polys,
+    HIP_TRY(ctx, launch_decrypt(ctx->d_primes, ctx->d_secret, ct->data, 0, (*out)->data, (int)ct->limbs, (int)ct->polys, 1,
                                 (int)ctx->log_n, ctx->stream));
     return HISA_OK;
 }

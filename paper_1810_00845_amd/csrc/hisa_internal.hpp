@@ -136,7 +136,9 @@ struct hisa_ctx {
     int gauss_cdt_n = 0;
     std::vector<i64> sparse_secret;        // secret_kind = 1: the secret's coefficients, drawn on the host
     double* d_moddown_hat_pin = nullptr;   // [K][total] (P/p_m) * P^-1 mod q_i, centred: ModDown's conversion with the division folded in
-    uint32_t* d_pow5;       // [N/2] 5^j mod 2N
+    double* d_sfft_tw = nullptr;           // [N/2] complex: stage twiddles of the encode / decode transform
+    unsigned char* pin = nullptr;          // pinned host memory that uploads and decoded values pass through (pinned_block)
+    size_t pin_bytes = 0, pin_pos = 0;
     std::unordered_map<size_t, std::vector<void*>> pool;
     size_t pool_bytes;
     std::map<uintptr_t, size_t> live;   // blocks handed out by dev_alloc and not yet back in the pool: start -> bytes
@@ -167,6 +169,15 @@ DevBlock* dev_alloc(hisa_ctx* ctx, size_t bytes);   // from the context's pool; 
 void dev_release(hisa_ctx* ctx, DevBlock* b);
 // 8-byte words from p to the end of the live pool block that holds p; 0 when no live block does
 u64 dev_words_behind(const hisa_ctx* ctx, const void* p);
+
+// `bytes` of pinned host memory, readable and writable by kernels, valid until later calls have asked for PIN_BYTES more
+// (the memory is a ring: before it is handed out again the stream is waited for); null on failure or beyond PIN_BYTES
+#define PIN_BYTES ((size_t)4 << 20)
+void* pinned_block(hisa_ctx* ctx, size_t bytes);
+// slot values in pinned memory, [n_pts][count] -> plaintexts out [n_pts][limbs][N]; im may be null
+int encode_dense(hisa_ctx* ctx, const double* re, const double* im, int count, int n_pts, double scale, int limbs, u64* out);
+// plaintexts [n_pts][limbs][N] (device) -> the first `count` slots, complex z [n_pts][count] in pinned memory; waits
+int decode_dense(hisa_ctx* ctx, const u64* pts, int n_pts, int limbs, double scale, int count, double* z);
 
 struct Temp {  // pooled scratch buffer for the duration of one call
     hisa_ctx* ctx;
@@ -256,6 +267,10 @@ struct ProfScope {
 // ---- launch wrappers (every one enqueues on `st` and returns hipGetLastError) ----
 hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride, int n_polys, const PolyMap& map,
                       hipStream_t st);
+// signed coefficients [n_pts][N] -> their residues modulo primes 0 .. limbs - 1 in NTT form, out [n_pts][limbs][N]
+hipError_t launch_ntt_i64(const NttTables& t, int log_n, const i64* coeffs, u64* out, int limbs, int n_pts, hipStream_t st);
+// NTT form [n_pts][limbs][N] -> coefficients as centred doubles (fp64 contexts only)
+hipError_t launch_intt_centred(const NttTables& t, int log_n, const u64* in, double* out, int limbs, int n_pts, hipStream_t st);
 hipError_t launch_intt(const NttTables& t, int log_n, u64* data, u64 batch_stride, int n_polys, const PolyMap& map,
                        const InttExtra* extra, hipStream_t st);
 
@@ -291,8 +306,32 @@ struct FpArgs {
     u64* out; u64 out_bs;
     int in_pos_shift;                  // input limb position = pos + in_pos_shift
     u64 galois;                        // inverse: gather through sigma_g (0 = none)
+    // by columns and rows (launch_ntt_fp_split)
+    const double *sfwd, *sinv;
+    u64 table_stride;                  // filled in by the launcher, like n_entries
+    int n_entries;
+    const i64* coeffs;                 // forward: signed coefficients [batch][N] for all limbs of an entry, instead of `in`
+    int centred_out;                   // inverse: coefficients as centred doubles instead of residues
 };
 hipError_t launch_ntt_fp(int mode, int log_n, const FpArgs& a, const FpTask& tk, u64 n_batch, hipStream_t st);
+hipError_t launch_ntt_fp_split(int mode, int log_n, const FpArgs& a, const FpTask& tk, u64 n_batch, hipStream_t st);
+
+// symmetric encryption of up to ENCRYPT_MAX plaintexts pt[b] ([limbs][N], NTT form): ct [n_entries][2][limbs][N]
+#define ENCRYPT_MAX 64
+struct EncryptArgs {
+    const FpPrime* fprimes;
+    const PrimeConst* primes;
+    const double* sfwd;
+    u64 table_stride;                  // filled in by the launcher
+    const u64* secret;
+    u64* ct;
+    int limbs, n_entries, noise_on;
+    u64 seed, ctr;                     // entry b uses the streams ctr + b
+    const u64* cdt;
+    int cdt_n;
+    const u64* pt[ENCRYPT_MAX];
+};
+hipError_t launch_encrypt_fp(int log_n, const EncryptArgs& a, hipStream_t st);
 
 // ---- inverse transform -> base conversion -> forward transform by rows and columns (convert_fp.hip) ----
 #define SPLIT_ROW 672                        // table words per row of 1024 coefficients
@@ -400,8 +439,9 @@ hipError_t launch_mul_no_relin(const PrimeConst* primes, const u64* a, const u64
                                u64 a_bs, u64 b_bs, u64 o_bs, int log_n, hipStream_t st);
 hipError_t launch_encrypt_combine(const PrimeConst* primes, const u64* secret, const u64* pt, const u64* e, u64* ct,
                                   int limbs, u64 n_batch, u64 pt_bs, int log_n, hipStream_t st);
-hipError_t launch_decrypt(const PrimeConst* primes, const u64* secret, const u64* ct, u64* pt, int limbs, int polys,
-                          int log_n, hipStream_t st);
+// n_batch ciphertexts ct_bs words apart -> pt [n_batch][limbs][N]
+hipError_t launch_decrypt(const PrimeConst* primes, const u64* secret, const u64* ct, u64 ct_bs, u64* pt, int limbs, int polys,
+                          u64 n_batch, int log_n, hipStream_t st);
 hipError_t launch_key_combine(const PrimeConst* primes, const u64* secret, const u64* target, const u64* e,
                               const u64* pmod_all, u64* key_digit, int total, int L, int alpha, int digit, int log_n,
                               hipStream_t st);
@@ -472,13 +512,13 @@ hipError_t launch_encode_basis(const double* cs, const uint32_t* g, const int* s
                                hipStream_t st);
 hipError_t launch_encode_combine(const double* basis, int nb, const double* v, int n_pts, double factor, i64* coeffs,
                                  int log_n, hipStream_t st);
-// the same maps through the O(N log N) transform over the slot order (encode.hip); pow5: [N/2] 5^j mod 2N
-hipError_t launch_decode_fft(const double* cs, const double* sn, const uint32_t* pow5, const double* m, int count, void* work,
-                             double* re, double* im, int log_n, hipStream_t st);
-hipError_t launch_encode_fft(const double* cs, const double* sn, const uint32_t* pow5, const double* re, const double* im,
-                             const uint32_t* slots, int count, int n_pts, double factor, void* work, i64* coeffs, int log_n,
-                             hipStream_t st);
+// the same maps through the O(N log N) transform over the slot order (encode.hip); tw: [N/2] complex, entry half + j the
+// twiddle j of the stage of length 2 half; slot values and z may lie in pinned host memory
+hipError_t launch_decode_fft(const void* tw, const double* m, int count, int n_pts, void* work, void* z, int log_n, hipStream_t st);
+hipError_t launch_encode_fft(const void* tw, const double* re, const double* im, const uint32_t* slots, int count, int n_pts,
+                             double factor, void* work, i64* coeffs, int log_n, hipStream_t st);
 hipError_t launch_crt_to_double(const PrimeConst* primes, const u64* coeff_form, int limbs, const u64* garner_inv,
-                                const u64* garner_inv_sh, int L, double inv_scale, double* out, int log_n, hipStream_t st);
-hipError_t launch_decode(const double* cs, const double* sn, const double* m, int count, double* re, double* im, int log_n,
-                         hipStream_t st);
+                                const u64* garner_inv_sh, int L, double inv_scale, double* out, int n_pts, int log_n, hipStream_t st);
+hipError_t launch_crt_fp(const FpPrime* fprimes, const double* centred, int limbs, const double* garner_inv, int L, double inv_scale,
+                         double* out, int n_pts, int log_n, hipStream_t st);
+hipError_t launch_decode(const double* cs, const double* sn, const double* m, int count, int n_pts, void* z, int log_n, hipStream_t st);

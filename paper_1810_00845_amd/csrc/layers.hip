@@ -913,7 +913,7 @@ static int encode_sparse_batch(hisa_ctx* ctx, const std::vector<uint32_t>& slots
     if (fft) {
         for (size_t p0 = 0; p0 < n_pts; p0 += group) {
             const int cnt = (int)std::min<size_t>(group, n_pts - p0);
-            HIP_TRY(ctx, launch_encode_fft(ctx->d_cos, ctx->d_sin, ctx->d_pow5, dv.as<double>() + p0 * nnz, nullptr, dg.as<uint32_t>(),
+            HIP_TRY(ctx, launch_encode_fft(ctx->d_sfft_tw, dv.as<double>() + p0 * nnz, nullptr, dg.as<uint32_t>(),
                                            (int)nnz, cnt, 2.0 * scale / (double)n, work.blk->ptr, co.as<i64>() + p0 * n,
                                            (int)ctx->log_n, ctx->stream));
             HIP_TRY(ctx, launch_reduce_i64(ctx->d_primes, co.as<i64>() + p0 * n, out + p0 * limbs * n, limbs, cnt,
@@ -2804,7 +2804,18 @@ extern "C" int hisa_tensor_encrypt(hisa_ctx* ctx, const double* x, double scale,
     }
     DevBlock* blk = dev_alloc(ctx, nct * limbs * n * sizeof(u64));
     if (!blk) return HISA_ERR_OOM;
-    int rc = encode_sparse_batch(ctx, slots, values, nct, scale, (int)limbs, (u64*)blk->ptr);
+    // a few ciphertexts: their slot vectors are laid out in pinned memory, from which the first launch of the encoding reads
+    const size_t top = (size_t)*std::max_element(slots.begin(), slots.end()) + 1;
+    double* dense = nct * top * sizeof(double) <= PIN_BYTES / 4 ? (double*)pinned_block(ctx, nct * top * sizeof(double)) : nullptr;
+    int rc;
+    if (dense) {
+        memset(dense, 0, nct * top * sizeof(double));
+        for (size_t i = 0; i < nct; i++)
+            for (size_t k = 0; k < slots.size(); k++) dense[i * top + slots[k]] = values[i * slots.size() + k];
+        rc = encode_dense(ctx, dense, nullptr, (int)top, (int)nct, scale, (int)limbs, (u64*)blk->ptr);
+    } else {
+        rc = encode_sparse_batch(ctx, slots, values, nct, scale, (int)limbs, (u64*)blk->ptr);
+    }
     std::vector<hisa_pt*> pts(nct, nullptr);
     if (rc == HISA_OK) {
         blk->refs = (int)nct + 1;
@@ -2825,16 +2836,31 @@ extern "C" int hisa_tensor_decrypt(hisa_ctx* ctx, const hisa_tensor* t, double* 
     const uint32_t ci = t_ci(t);
     const std::vector<uint32_t> slots = tensor_slots(t);
     const size_t count = (size_t)*std::max_element(slots.begin(), slots.end()) + 1;
-    std::vector<double> re(count);
-    for (size_t i = 0; i < nct; i++) {
-        hisa_pt* pt = nullptr;
-        TRY(hisa_decrypt(ctx, t->cts[i], &pt));
-        int rc = hisa_decode(ctx, pt, re.data(), nullptr, count);
-        hisa_free(ctx, pt);
+    const uint32_t l = t->cts[0]->limbs, polys = t->cts[0]->polys;
+    // as many ciphertexts of one scale as the pinned memory holds the slots of go through one set of launches and one wait
+    const size_t most = std::max<size_t>(1, PIN_BYTES / 2 / (2 * count * sizeof(double)));
+    for (size_t i = 0; i < nct;) {
+        size_t cnt = 1;
+        while (i + cnt < nct && cnt < most && t->cts[i + cnt]->scale == t->cts[i]->scale) cnt++;
+        BatchIn bi;
+        TRY(gather_batch(ctx, (const hisa_ct* const*)t->cts + i, cnt, &bi));
+        Temp pt(ctx, cnt * l * ctx->N * sizeof(u64));
+        double* z = (double*)pinned_block(ctx, cnt * 2 * count * sizeof(double));
+        int rc = pt.ok() && z ? HISA_OK : HISA_ERR_OOM;
+        if (rc == HISA_OK) {
+            hipError_t e = launch_decrypt(ctx->d_primes, ctx->d_secret, bi.base, bi.stride, pt.u(), (int)l, (int)polys, cnt, (int)ctx->log_n,
+                                          ctx->stream);
+            if (e != hipSuccess) rc = fail(ctx, HISA_ERR_HIP, "decrypt: %s", hipGetErrorString(e));
+        }
+        if (rc == HISA_OK) rc = decode_dense(ctx, pt.u(), (int)cnt, (int)l, t->cts[i]->scale, (int)count, z);
+        dev_release(ctx, bi.tmp);
         if (rc != HISA_OK) return rc;
-        const size_t b = i / per, c0 = (i % per) * ci;
-        for (size_t c = c0; c < std::min<size_t>(c0 + ci, t->channels); c++)
-            for (size_t k = 0; k < hw; k++) x[(b * t->channels + c) * hw + k] = re[slots[(c - c0) * hw + k]];
+        for (size_t k = 0; k < cnt; k++) {
+            const size_t b = (i + k) / per, c0 = ((i + k) % per) * ci;
+            for (size_t c = c0; c < std::min<size_t>(c0 + ci, t->channels); c++)
+                for (size_t p = 0; p < hw; p++) x[(b * t->channels + c) * hw + p] = z[2 * (k * count + slots[(c - c0) * hw + p])];
+        }
+        i += cnt;
     }
     return HISA_OK;
 }

@@ -144,8 +144,40 @@ static bool fp_tasks(const NttTables& t, int log_n, const PolyMap& map, int n_po
 
 static FpArgs fp_base_args(const NttTables& t) {
     FpArgs a = {};
-    a.fprimes = t.fprimes; a.ftw = t.ftw; a.utw = t.utw; a.vtw = t.vtw;
+    a.fprimes = t.fprimes; a.ftw = t.ftw; a.utw = t.utw; a.vtw = t.vtw; a.sfwd = t.sfwd; a.sinv = t.sinv;
     return a;
+}
+
+// By columns and rows up to about the number of polynomials the single-launch transform keeps resident: it takes as long
+// for one as for that many.
+static bool few_polynomials(int log_n, u64 polys) { return (polys << log_n) <= ((u64)1 << 22); }
+
+static hipError_t transform_fp(int mode, int log_n, const FpArgs& a, const FpTask& tk, u64 n_batch, hipStream_t st) {
+    return few_polynomials(log_n, n_batch * (u64)tk.period) ? launch_ntt_fp_split(mode, log_n, a, tk, n_batch, st)
+                                                            : launch_ntt_fp(mode, log_n, a, tk, n_batch, st);
+}
+
+hipError_t launch_ntt_i64(const NttTables& t, int log_n, const i64* coeffs, u64* out, int limbs, int n_pts, hipStream_t st) {
+    DRY_RUN_RETURN();
+    if (n_pts <= 0) return hipSuccess;
+    const PolyMap map = identity_map(limbs);
+    FpTask tk;
+    if (fp_tasks(t, log_n, map, n_pts * limbs, 0, &tk) && few_polynomials(log_n, (u64)n_pts * limbs)) {
+        FpArgs fa = fp_base_args(t);
+        fa.coeffs = coeffs; fa.out = out; fa.out_bs = (u64)limbs << log_n;
+        return launch_ntt_fp_split(FP_FWD_PLAIN, log_n, fa, tk, (u64)n_pts, st);
+    }
+    hipError_t e = launch_reduce_i64(t.primes, coeffs, out, limbs, n_pts, log_n, st);
+    return e == hipSuccess ? launch_ntt(t, log_n, out, (u64)limbs << log_n, n_pts * limbs, map, st) : e;
+}
+
+hipError_t launch_intt_centred(const NttTables& t, int log_n, const u64* in, double* out, int limbs, int n_pts, hipStream_t st) {
+    DRY_RUN_RETURN();
+    FpTask tk;
+    if (!fp_tasks(t, log_n, identity_map(limbs), n_pts * limbs, 0, &tk)) return hipErrorInvalidValue;
+    FpArgs fa = fp_base_args(t);
+    fa.in = in; fa.in_bs = (u64)limbs << log_n; fa.out = (u64*)out; fa.out_bs = (u64)limbs << log_n; fa.centred_out = 1;
+    return launch_ntt_fp_split(FP_INV_PLAIN, log_n, fa, tk, (u64)n_pts, st);
 }
 
 hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride, int n_polys, const PolyMap& map,
@@ -156,7 +188,7 @@ hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride
     if (fp_tasks(t, log_n, map, n_polys, 0, &tk)) {
         FpArgs fa = fp_base_args(t);
         fa.in = data; fa.in_bs = batch_stride; fa.out = data; fa.out_bs = batch_stride;
-        return launch_ntt_fp(FP_FWD_PLAIN, log_n, fa, tk, (u64)(n_polys / map.period), st);
+        return transform_fp(FP_FWD_PLAIN, log_n, fa, tk, (u64)(n_polys / map.period), st);
     }
     PassArgs a = {};
     a.data = data; a.in = nullptr; a.batch_stride = batch_stride; a.log_n = log_n;
@@ -183,7 +215,7 @@ hipError_t launch_intt(const NttTables& t, int log_n, u64* data, u64 batch_strid
         fa.in_pos_shift = extra ? extra->out_entry0 : 0;
         fa.galois = extra ? extra->galois : 0;
         fa.out = data; fa.out_bs = batch_stride;
-        return launch_ntt_fp(FP_INV_PLAIN, log_n, fa, tk, (u64)(n_polys / map.period), st);
+        return transform_fp(FP_INV_PLAIN, log_n, fa, tk, (u64)(n_polys / map.period), st);
     }
     PassArgs a = {};
     a.data = data; a.batch_stride = batch_stride; a.log_n = log_n;

@@ -243,9 +243,12 @@ class Context:
 
     def decode(self, pt, count=None):
         count = self.slots if count is None else count
-        re, im = np.zeros(count), np.zeros(count)
-        self._ck(load().hisa_decode(self._vp, C.c_void_p(pt.h), _dp(re), _dp(im), C.c_size_t(count)))
-        return re + 1j * im
+        return self.decode_complex(pt, count)
+
+    def decode_complex(self, pt, count):
+        out = np.empty(count, dtype=np.complex128)
+        self._ck(load().hisa_decode_complex(self._vp, C.c_void_p(pt.h), _dp(out), C.c_size_t(count)))
+        return out
 
     def pt_from_coeffs(self, coeffs, scale, limbs):
         a = np.ascontiguousarray(coeffs, dtype=np.int64)

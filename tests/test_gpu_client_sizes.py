@@ -1,0 +1,59 @@
+"""Encode, encrypt, decrypt and decode over ring degrees, limb counts and slot counts: the edges of the transforms over the
+slot order (one chunk, one to five long stages, a prefix of the slots), of the digit recurrence's register forms, of the
+encryption's plaintext table, and of the line between transforms by columns and rows and the single-launch ones."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# (log_n, q_bits, special_bits, vectors, slots)
+POINTS = [
+    (10, [30, 25], 30, 3, 512),
+    (11, [40, 30, 30], 45, 2, 17),
+    (12, [50], 50, 65, 2048),                   # one limb; one vector more than an encryption launch takes
+    (12, [50, 40, 40, 40, 40], 50, 1, 16),
+    (13, [50] + [40] * 8, 50, 2, 1),
+    (14, [50] + [40] * 16, 50, 17, 8191),       # above the line: the single-launch transforms
+    (15, [50] + [38] * 24, 50, 1, 16384),
+    (16, [58, 50], 60, 1, 32768),
+]
+
+
+@pytest.mark.parametrize("log_n,q_bits,special,vectors,count", POINTS)
+def test_round_trip(log_n, q_bits, special, vectors, count):
+    from oracle import Oracle
+    from paper_1810_00845_amd import hisa
+    print("[case]", log_n, len(q_bits), vectors, count, flush=True)
+    g, o = hisa.Context(log_n, q_bits, 1, special, 5), Oracle(log_n, q_bits, 1, special, 5)
+    g.keygen(); o.keygen()
+    rng = np.random.default_rng(log_n + count)
+    limbs, scale = len(q_bits), 2.0 ** 20
+    x = rng.uniform(-1, 1, (vectors, count)) + 1j * rng.uniform(-1, 1, (vectors, count))
+    pts = [g.encode(v, scale, limbs) for v in x]
+    cts = g.encrypt_batch(pts)
+    for i in sorted({0, vectors - 1}):
+        coeffs = g.pt_export(pts[i])[0].astype(np.int64)          # coefficients are far below the first prime
+        coeffs[coeffs > g.primes[0] // 2] -= g.primes[0]
+        e = np.asarray(coeffs, dtype=np.float64)
+        z = np.zeros(g.slots, dtype=np.complex128)
+        z[:count] = x[i]
+        full = np.zeros(2 * g.N, dtype=np.complex128)             # slot j at exp(i pi 5^j / N), conjugates opposite
+        p = np.array([pow(5, j, 2 * g.N) for j in range(g.slots)])
+        full[p], full[2 * g.N - p] = z, z.conj()
+        want = np.fft.fft(full)[:g.N].real * scale / g.N
+        assert np.abs(e - want).max() <= 0.5 + 1e-6 * scale / 2 ** 20
+        assert np.array_equal(g.pt_export(pts[i]), o.pt_export(o.pt_from_coeffs(coeffs, scale, limbs)))
+        got = g.decode(pts[i], count)
+        assert np.abs(got - x[i]).max() < 1e-3
+        wide = g.decode(pts[i])
+        assert np.allclose(wide[:count], got, rtol=0, atol=1e-12) and np.abs(wide[count:]).max(initial=0.0) < 1e-3
+    for i in range(vectors):                                      # streams in order, whatever the batch
+        if i in (0, vectors - 1):
+            ct = o.encrypt(o.pt_from_coeffs(np.where((c := g.pt_export(pts[i])[0].astype(np.int64)) > g.primes[0] // 2,
+                                                     c - g.primes[0], c), scale, limbs))
+            assert np.array_equal(g.ct_export(cts[i]), o.export(ct))
+        else:
+            o.enc_counter += 1
+    for i in sorted({0, vectors - 1}):
+        assert np.abs(g.decode(g.decrypt(cts[i]), count) - x[i]).max() < 1e-1
+    g.close()
