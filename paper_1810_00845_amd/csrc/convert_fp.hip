@@ -27,12 +27,7 @@
 #include "modarith.hpp"
 #include "sampling.hpp"
 
-#define ROW_LDS 1056     // doubles per wave: 32 x 33, one pad word per 32
-#define ROWS_NT 256
 #define HEAD 64          // per-prime table: [HEAD] column twiddles, then SPLIT_ROW per row (layout: split_tables)
-
-// Position of a limb -> its prime: the l limbs of q first, special limbs behind them.
-__device__ __forceinline__ int prime_at(int pos, int l, int L) { return pos < l ? pos : pos + (L - l); }
 
 struct Modulus { double p, pinv; };
 __device__ __forceinline__ Modulus modulus(const FpPrime* f, int prime) {
@@ -139,40 +134,11 @@ __device__ __forceinline__ void cap_bounds(double (&v)[16], float (&m)[16], floa
     for (int r = 0; r < 16; r++) m[r] = top;
 }
 
-// Byte offsets of the elements that sigma_g moves to 1024 row + 64 r + lane.  The exponent of index i is 2 bitrev(i) + 1,
-// its product with g splits into a term of the lane (one multiplication) and a uniform term of (row, r); shifting both left
-// by 31 - log2 N makes the 32-bit sum wrap modulo 2N, and reversing its bits gives the source index with the bit of the
-// always-odd exponent above it.
-struct Gather {
-    uint32_t lane_term, shift, row, log_n;
-};
-__device__ __forceinline__ Gather make_gather(u64 g, uint32_t row, int lane, int log_n) {
-    const uint32_t gs = (uint32_t)g << (31 - log_n);
-    uint32_t lane_term = (2u * (__brev((uint32_t)lane) >> (32 - log_n)) + 1u) * gs;
-    asm volatile("" : "+v"(lane_term));      // otherwise the sum of products below becomes a product per register again
-    return Gather{lane_term, gs, row, (uint32_t)log_n};
-}
-__device__ __forceinline__ uint32_t gather_offset(const Gather& t, int r) {
-    const uint32_t u = t.lane_term + 2u * (__brev(t.row * 1024u + (uint32_t)r * 64u) >> (32 - t.log_n)) * t.shift;
-    return (__brev(u) << 3) - (8u << t.log_n);
-}
-
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, double& x, double& y) {
     const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
     x = mk64(d.x, d.y);
     y = mk64(d.z, d.w);
-}
-
-// Wave-level tasks, ordered (limb, row, entry): the entries of a row share its twiddles (5 KB beside 8 KB of data) and, in
-// the inner product, its key rows (16 KB a digit), so the four waves of a workgroup find them in the L1 and the workgroups
-// of an XCD (round-robin by id, hence the contiguous range per XCD) in its L2.
-__device__ __forceinline__ int row_task(int n_tasks) {
-    const int n_blocks = (n_tasks + 3) >> 2, per = (n_blocks + 7) >> 3;
-    const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per) return -1;
-    const int task = blk * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    return task < n_tasks ? task : -1;
 }
 
 // What a wave keeps of the twiddles of its row (layout: split_table_words)

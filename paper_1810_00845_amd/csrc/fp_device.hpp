@@ -68,3 +68,38 @@ __device__ __forceinline__ uint32_t galois_src_fp(uint32_t i, u64 g, int log_n) 
     return __brev((e2 - 1) >> 1) >> (32 - log_n);
 }
 
+// ---- rows of 1024 coefficients, one wave each (convert_fp.hip, convert_int.hip) ----
+#define ROW_LDS 1056     // 64-bit words per wave: 32 x 33, one pad word per 32
+#define ROWS_NT 256
+
+// Position of a limb -> its prime: the l limbs of q first, special limbs behind them.
+__device__ __forceinline__ int prime_at(int pos, int l, int L) { return pos < l ? pos : pos + (L - l); }
+
+// Byte offsets of the elements that sigma_g moves to 1024 row + 64 r + lane.  The exponent of index i is 2 bitrev(i) + 1,
+// its product with g splits into a term of the lane (one multiplication) and a uniform term of (row, r); shifting both left
+// by 31 - log2 N makes the 32-bit sum wrap modulo 2N, and reversing its bits gives the source index with the bit of the
+// always-odd exponent above it.
+struct Gather {
+    uint32_t lane_term, shift, row, log_n;
+};
+__device__ __forceinline__ Gather make_gather(u64 g, uint32_t row, int lane, int log_n) {
+    const uint32_t gs = (uint32_t)g << (31 - log_n);
+    uint32_t lane_term = (2u * (__brev((uint32_t)lane) >> (32 - log_n)) + 1u) * gs;
+    asm volatile("" : "+v"(lane_term));      // otherwise the sum of products below becomes a product per register again
+    return Gather{lane_term, gs, row, (uint32_t)log_n};
+}
+__device__ __forceinline__ uint32_t gather_offset(const Gather& t, int r) {
+    const uint32_t u = t.lane_term + 2u * (__brev(t.row * 1024u + (uint32_t)r * 64u) >> (32 - t.log_n)) * t.shift;
+    return (__brev(u) << 3) - (8u << t.log_n);
+}
+
+// Wave-level tasks, ordered (limb, row, entry): the entries of a row share its twiddles (5 KB beside 8 KB of data) and, in
+// the inner product, its key rows (16 KB a digit), so the four waves of a workgroup find them in the L1 and the workgroups
+// of an XCD (round-robin by id, hence the contiguous range per XCD) in its L2.
+__device__ __forceinline__ int row_task(int n_tasks) {
+    const int n_blocks = (n_tasks + 3) >> 2, per = (n_blocks + 7) >> 3;
+    const int blk = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per) return -1;
+    const int task = blk * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    return task < n_tasks ? task : -1;
+}

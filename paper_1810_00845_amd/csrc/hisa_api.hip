@@ -353,17 +353,15 @@ static void fill_split_table(uint32_t log_n, const u64* w, u64 q, double* out) {
     }
 }
 
-static void build_conv_table_host(const hisa_ctx* ctx, const std::vector<int>& src, std::vector<u64>& inv_hat,
-                                  std::vector<u64>& inv_hat_sh, std::vector<u64>& hat, std::vector<u64>& dmod) {
+static void build_conv_table_host(const hisa_ctx* ctx, const std::vector<int>& src, std::vector<u64>& inv_hat, std::vector<u64>& hat) {
     const int a = (int)src.size(), total = (int)ctx->total;
-    inv_hat.assign(a, 0); inv_hat_sh.assign(a, 0); hat.assign((size_t)a * total, 0); dmod.assign(total, 0);
+    inv_hat.assign(a, 0); hat.assign((size_t)a * total, 0);
     for (int i = 0; i < a; i++) {
         const u64 ci = ctx->mod[src[i]];
         u64 prod = 1 % ci;
         for (int m = 0; m < a; m++)
             if (m != i) prod = hm::mul(prod, ctx->mod[src[m]] % ci, ci);
         inv_hat[i] = hm::inv(prod, ci);
-        inv_hat_sh[i] = hm::shoup(inv_hat[i], ci);
         for (int t = 0; t < total; t++) {
             const u64 qt = ctx->mod[t];
             u64 h = 1 % qt;
@@ -372,29 +370,17 @@ static void build_conv_table_host(const hisa_ctx* ctx, const std::vector<int>& s
             hat[(size_t)i * total + t] = h;
         }
     }
-    for (int t = 0; t < total; t++) {
-        const u64 qt = ctx->mod[t];
-        u64 d = 1 % qt;
-        for (int m = 0; m < a; m++) d = hm::mul(d, ctx->mod[src[m]] % qt, qt);
-        dmod[t] = d;
-    }
 }
 
 static int make_conv_table(hisa_ctx* ctx, const std::vector<int>& src, ConvTable* tab) {
-    std::vector<u64> ih, ihs, hat, dmod;
-    build_conv_table_host(ctx, src, ih, ihs, hat, dmod);
+    build_conv_table_host(ctx, src, tab->inv_hat, tab->hat);
     tab->a = (int)src.size();
     for (int i = 0; i < tab->a; i++) tab->src[i] = src[i];
-    tab->inv_hat = ih;
-    HIP_TRY(ctx, upload(&tab->d_inv_hat, ih));
-    HIP_TRY(ctx, upload(&tab->d_inv_hat_sh, ihs));
-    HIP_TRY(ctx, upload(&tab->d_hat, hat));
-    HIP_TRY(ctx, upload(&tab->d_dmod, dmod));
     tab->d_hat_f = nullptr;
     if (ctx->tabs.fp_ok) {
-        std::vector<double> hf(hat.size());
+        std::vector<double> hf(tab->hat.size());
         for (int i = 0; i < tab->a; i++)
-            for (uint32_t t = 0; t < ctx->total; t++) hf[(size_t)i * ctx->total + t] = centred_double(hat[(size_t)i * ctx->total + t], ctx->mod[t]);
+            for (uint32_t t = 0; t < ctx->total; t++) hf[(size_t)i * ctx->total + t] = centred_double(tab->hat[(size_t)i * ctx->total + t], ctx->mod[t]);
         HIP_TRY(ctx, upload(&tab->d_hat_f, hf));
     }
     return HISA_OK;
@@ -402,7 +388,6 @@ static int make_conv_table(hisa_ctx* ctx, const std::vector<int>& src, ConvTable
 
 static void free_conv_table(ConvTable* t) {
     (void)hipFree(t->d_hat_f);
-    (void)hipFree(t->d_inv_hat); (void)hipFree(t->d_inv_hat_sh); (void)hipFree(t->d_hat); (void)hipFree(t->d_dmod);
 }
 
 // conversion table of digit j restricted to `a` present primes
@@ -485,7 +470,22 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
     HIP_TRY(ctx, upload(&ctx->d_tw_sh, tw_sh));
     HIP_TRY(ctx, upload(&ctx->d_itw, itw));
     HIP_TRY(ctx, upload(&ctx->d_itw_sh, itw_sh));
-    ctx->tabs = NttTables{ctx->d_primes, ctx->d_tw, ctx->d_tw_sh, ctx->d_itw, ctx->d_itw_sh, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+    {
+        std::vector<u64> consts;
+        for (uint32_t i = 0; i < ctx->total; i++) {
+            const u64 q = ctx->mod[i];
+            for (u64 c : {ctx->pc[i].n_inv, hm::mul(ctx->pc[i].n_inv, itw[(size_t)i * n + 1], q)}) {
+                consts.push_back(c);
+                consts.push_back(hm::shoup(c, q));
+            }
+            const int bits = 64 - __builtin_clzll(q);
+            consts.push_back((u64)(((u128)1 << (63 + bits)) / q));
+            consts.push_back((u64)(bits - 1));
+            ctx->last_itw.push_back(itw[(size_t)i * n + 1]);
+        }
+        HIP_TRY(ctx, upload(&ctx->d_consts, consts));
+    }
+    ctx->tabs = NttTables{ctx->d_primes, ctx->d_tw, ctx->d_tw_sh, ctx->d_itw, ctx->d_itw_sh, ctx->d_consts, 0, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
     // fp64 path: every prime below 2^50 and a ring degree the single-launch transform covers
     {
         bool fp_ok = ctx->log_n >= 12 && ctx->log_n <= 15;
@@ -557,8 +557,7 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
             for (uint32_t i = 0; i < ctx->L; i++) pf[i] = centred_double(pinv[i], ctx->mod[i]);
             HIP_TRY(ctx, upload(&ctx->d_pinv_f, pf));
             {   // (P/p_m) P^-1 mod q_i: the conversion of the folded ModDown
-                std::vector<u64> ih, ihs, hat, dmod;
-                build_conv_table_host(ctx, src, ih, ihs, hat, dmod);
+                const std::vector<u64>& hat = ctx->moddown_tab->hat;
                 std::vector<double> hp((size_t)ctx->K * ctx->total, 0.0);
                 for (uint32_t m = 0; m < ctx->K; m++)
                     for (uint32_t i = 0; i < ctx->L; i++)
@@ -629,7 +628,7 @@ extern "C" int hisa_destroy(hisa_ctx* ctx) {
     (void)hipFree(ctx->d_fprimes); (void)hipFree(ctx->d_ftw); (void)hipFree(ctx->d_utw); (void)hipFree(ctx->d_vtw);
     (void)hipFree(ctx->d_sfwd); (void)hipFree(ctx->d_sinv);
     (void)hipFree(ctx->d_pinv_f); (void)hipFree(ctx->d_moddown_hat_pin);
-    (void)hipFree(ctx->d_pmod); (void)hipFree(ctx->d_cos); (void)hipFree(ctx->d_sin); (void)hipFree(ctx->d_sfft_tw);
+    (void)hipFree(ctx->d_pmod); (void)hipFree(ctx->d_consts); (void)hipFree(ctx->d_cos); (void)hipFree(ctx->d_sin); (void)hipFree(ctx->d_sfft_tw);
     if (ctx->pin) (void)hipHostFree(ctx->pin);
     (void)hipFree(ctx->d_gauss_cdt);
     delete ctx;
@@ -1263,135 +1262,97 @@ extern "C" int hisa_mul_no_relin(hisa_ctx* ctx, const hisa_ct* a, const hisa_ct*
 // ---------------------------------------------------------------------------
 // hybrid key switching
 // ---------------------------------------------------------------------------
-// Per-level factors that close the inverse transform of the polynomial to be
-// switched: N^-1 * (D_j / q_i)^-1 mod q_i for limb i in digit j.
-struct LevelPost {
-    u64* d;  // [l] values then [l] Shoup companions
-};
+// Conversion tables of the integer kernels (layout: IntArgs), one allocation: the digits of level l at 2^15 + l, the division
+// by P at 2^16, the rescale of level l at 2^17 + l
+struct IntTables { const u64 *close, *hat, *off, *factor, *factor_sh; };
+static u64 pack30(u64 x) { return ((x >> 30) << 32) | (x & 0x3fffffff); }
 
-static int level_post(hisa_ctx* ctx, int l, u64** post, u64** post_sh) {
-    const u64 KEY = 16 + (u64)l;
-    auto it = ctx->aux.find(KEY);
+static int int_tables(hisa_ctx* ctx, u64 key, int src_prime0, int n_src, int alpha, const std::vector<u64>& factor, IntTables* out) {
+    const size_t total = ctx->total, digits = (n_src + alpha - 1) / alpha;
+    auto it = ctx->aux.find(key);
     if (it == ctx->aux.end()) {
-        std::vector<u64> t(2 * (size_t)l);
-        const int digits = (l + (int)ctx->alpha - 1) / (int)ctx->alpha;
-        for (int j = 0; j < digits; j++) {
-            const int lo = j * (int)ctx->alpha, hi = std::min(lo + (int)ctx->alpha, l);
-            ConvTable* tab;
-            TRY(modup_table(ctx, j, hi - lo, &tab));
-            for (int i = lo; i < hi; i++) {
-                const u64 q = ctx->mod[i];
-                t[i] = hm::mul(ctx->pc[i].n_inv, tab->inv_hat[i - lo], q);
-                t[l + i] = hm::shoup(t[i], q);
+        std::vector<u64> close, hat, off(digits * total, 0), fac, fac_sh;
+        for (size_t j = 0; j < digits; j++) {
+            std::vector<int> src;
+            for (int i = (int)j * alpha; i < n_src && i < (int)(j + 1) * alpha; i++) src.push_back(src_prime0 + i);
+            std::vector<u64> ih, h;
+            build_conv_table_host(ctx, src, ih, h);
+            for (size_t i = 0; i < src.size(); i++) {
+                const u64 c = ctx->mod[src[i]], f = hm::mul(ctx->pc[src[i]].n_inv, ih[i], c);
+                for (u64 v : {f, hm::mul(f, ctx->last_itw[src[i]], c)}) {
+                    close.push_back(v);
+                    close.push_back(hm::shoup(v, c));
+                }
+                for (size_t t = 0; t < total; t++) {
+                    const u64 q = ctx->mod[t], v = h[i * total + t];
+                    hat.push_back(pack30(v));
+                    off[j * total + t] = (off[j * total + t] + q - hm::mul(v, (c / 2) % q, q)) % q;
+                }
             }
         }
+        for (size_t i = 0; i < factor.size(); i++) fac_sh.push_back(hm::shoup(factor[i], ctx->mod[i]));
+        fac = close;
+        for (const std::vector<u64>* v : std::initializer_list<const std::vector<u64>*>{&hat, &off, &factor, &fac_sh}) fac.insert(fac.end(), v->begin(), v->end());
         u64* d = nullptr;
-        HIP_TRY(ctx, upload(&d, t));
-        it = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{d, t.size() * sizeof(u64), 1}, d}).first;
+        HIP_TRY(ctx, upload(&d, fac));
+        it = ctx->aux.emplace(key, SwitchKey{new DevBlock{d, fac.size() * sizeof(u64), 1}, d}).first;
     }
-    *post = it->second.data;
-    *post_sh = it->second.data + l;
+    out->close = it->second.data;
+    out->hat = out->close + 4 * (size_t)n_src;
+    out->off = out->hat + (size_t)n_src * total;
+    out->factor = out->off + digits * total;
+    out->factor_sh = out->factor + factor.size();
     return HISA_OK;
 }
 
-static int moddown_post(hisa_ctx* ctx, u64** post, u64** post_sh) {
-    const u64 KEY = 1;
-    auto it = ctx->aux.find(KEY);
-    if (it == ctx->aux.end()) {
-        // laid out for a PolyMap of period l + K is not possible (l varies), so the table is indexed by
-        // special-prime number and the caller offsets the pointer by -l
-        std::vector<u64> t(2 * (size_t)ctx->K);
-        for (uint32_t m = 0; m < ctx->K; m++) {
-            const u64 q = ctx->mod[ctx->L + m];
-            t[m] = hm::mul(ctx->pc[ctx->L + m].n_inv, ctx->moddown_tab->inv_hat[m], q);
-            t[ctx->K + m] = hm::shoup(t[m], q);
-        }
-        u64* d = nullptr;
-        HIP_TRY(ctx, upload(&d, t));
-        it = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{d, t.size() * sizeof(u64), 1}, d}).first;
-    }
-    *post = it->second.data;
-    *post_sh = it->second.data + ctx->K;
-    return HISA_OK;
+static IntArgs int_convert_args(const hisa_ctx* ctx, int l, size_t entries, const IntTables& t) {
+    IntArgs a = int_base_args(ctx->tabs, (int)ctx->log_n);
+    a.l = l; a.L = (int)ctx->L; a.total = (int)ctx->total;
+    a.n_entries = (unsigned)entries;
+    a.close = t.close; a.hat = t.hat; a.off = t.off; a.factor = t.factor; a.factor_sh = t.factor_sh;
+    return a;
 }
 
-// Key switch of B polynomials d[b] (NTT form, l limbs, at d + b*d_bs) under `key`;
-// out[b] = (ks0 + add0, ks1 + add1) with the optional addends taken from
-// add + b*add_bs (add_polys polynomials of l limbs, read through sigma_g when add_galois != 0).
-static int key_switch_core(hisa_ctx* ctx, const u64* d, u64 d_bs, size_t B, int l, const SwitchKey& key, const u64* add,
-                           u64 add_bs, int add_polys, u64 add_galois, u64* out) {
+// Key switch of B polynomials d[b] (NTT form, l limbs, at d + b*d_bs, read through sigma_g when galois != 0) under `key`;
+// out[b] = (ks0 + add0, ks1 + add1) with the optional addends taken from add + b*add_bs (add_polys polynomials of l limbs,
+// read through sigma_g as well).
+static int key_switch_core_int(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key,
+                               const u64* add, u64 add_bs, int add_polys, u64* out) {
     const size_t n = ctx->N;
-    const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total;
-    const int ext_limbs = l + K;
-    const int digits = (l + alpha - 1) / alpha;
-    const int log_n = (int)ctx->log_n;
-    hipStream_t st = ctx->stream;
-
-    Temp y(ctx, B * l * n * sizeof(u64));
-    Temp ext(ctx, B * (size_t)digits * ext_limbs * n * sizeof(u64));
-    Temp acc(ctx, B * 2 * (size_t)ext_limbs * n * sizeof(u64));
-    Temp conv(ctx, B * 2 * (size_t)l * n * sizeof(u64));
-    if (!y.ok() || !ext.ok() || !acc.ok() || !conv.ok()) return HISA_ERR_OOM;
-    const u64 ext_bs = (u64)digits * ext_limbs * n;
-
-    // 1. coefficient form, each limb pre-multiplied by (D_j/q_i)^-1
-    u64 *post, *post_sh;
-    TRY(level_post(ctx, l, &post, &post_sh));
-    InttExtra ex = {};
-    ex.in = d; ex.in_batch_stride = d_bs; ex.post = post; ex.post_sh = post_sh;
-    HIP_TRY(ctx, launch_intt(ctx->tabs, log_n, y.u(), (u64)l * n, (int)(B * l), identity_map(l), &ex, st));
-
-    // 2.-3. per digit: convert to every other prime, transform; own primes keep the input's NTT form
-    for (int j = 0; j < digits; j++) {
-        const int lo = j * alpha, hi = std::min(lo + alpha, l);
-        ConvTable* tab;
-        TRY(modup_table(ctx, j, hi - lo, &tab));
-        ConvArgs ca = {};
-        ca.y = y.u(); ca.y_bs = (u64)l * n; ca.src_pos0 = lo; ca.src_prime0 = lo; ca.a = hi - lo;
-        ca.hat = tab->d_hat; ca.dmod = tab->d_dmod; ca.total = total;
-        ca.out = ext.u() + (size_t)j * ext_limbs * n; ca.out_bs = ext_bs;
-        PolyMap pm = {};
-        pm.period = ext_limbs;
-        int nt = 0;
-        for (int x = 0; x < ext_limbs; x++) {
-            const int prime = x < l ? x : L + (x - l);
-            const bool own = x >= lo && x < hi;
-            pm.prime_of[x] = own ? (int16_t)-1 : (int16_t)prime;
-            if (!own) { ca.tgt_pos[nt] = (int16_t)x; ca.tgt_prime[nt] = (int16_t)prime; nt++; }
-        }
-        ca.n_targets = nt;
-        HIP_TRY(ctx, launch_base_conv(ctx->d_primes, ca, B, log_n, st));
-        HIP_TRY(ctx, launch_copy_limbs(d + (size_t)lo * n, d_bs, ext.u() + ((size_t)j * ext_limbs + lo) * n, ext_bs, hi - lo, B,
-                                       log_n, st));
-        // batch entries of this digit are ext_bs apart
-        HIP_TRY(ctx, launch_ntt(ctx->tabs, log_n, ext.u() + (size_t)j * ext_limbs * n, ext_bs, (int)(B * ext_limbs), pm, st));
+    const int K = (int)ctx->K, alpha = (int)ctx->alpha, ext_limbs = l + K, digits = (l + alpha - 1) / alpha;
+    IntTables up, down;
+    TRY(int_tables(ctx, ((u64)1 << 15) + (u64)l, 0, l, alpha, {}, &up));
+    std::vector<u64> pinv;
+    for (uint32_t i = 0; i < ctx->L; i++) {
+        u64 p = 1;
+        for (int m = 0; m < K; m++) p = hm::mul(p, ctx->mod[ctx->L + m] % ctx->mod[i], ctx->mod[i]);
+        pinv.push_back(hm::inv(p, ctx->mod[i]));
     }
-
-    // 4. inner product with the key
-    HIP_TRY(ctx, launch_inner_product(ctx->d_primes, ext.u(), ext_bs, digits, l, K, L, key.data, total, acc.u(),
-                                      (u64)2 * ext_limbs * n, B, log_n, st));
-
-    // 5. mod-down: special limbs to coefficient form (pre-multiplied by (P/p_m)^-1), convert, transform, combine
-    u64 *mpost, *mpost_sh;
-    TRY(moddown_post(ctx, &mpost, &mpost_sh));
-    {
-        PolyMap pm = {};
-        pm.period = ext_limbs;
-        for (int x = 0; x < ext_limbs; x++) pm.prime_of[x] = x < l ? (int16_t)-1 : (int16_t)(L + x - l);
-        InttExtra ex2 = {};
-        ex2.post = mpost - l; ex2.post_sh = mpost_sh - l;  // entry x >= l reads post[x - l]
-        HIP_TRY(ctx, launch_intt(ctx->tabs, log_n, acc.u(), (u64)ext_limbs * n, (int)(B * 2 * ext_limbs), pm, &ex2, st));
-        ConvArgs ca = {};
-        ca.y = acc.u(); ca.y_bs = (u64)ext_limbs * n; ca.src_pos0 = l; ca.src_prime0 = L; ca.a = K;
-        ca.hat = ctx->moddown_tab->d_hat; ca.dmod = ctx->moddown_tab->d_dmod; ca.total = total;
-        ca.out = conv.u(); ca.out_bs = (u64)l * n; ca.n_targets = l;
-        for (int i = 0; i < l; i++) { ca.tgt_pos[i] = (int16_t)i; ca.tgt_prime[i] = (int16_t)i; }
-        HIP_TRY(ctx, launch_base_conv(ctx->d_primes, ca, B * 2, log_n, st));
-        HIP_TRY(ctx, launch_ntt(ctx->tabs, log_n, conv.u(), (u64)l * n, (int)(B * 2 * l), identity_map(l), st));
+    TRY(int_tables(ctx, (u64)1 << 16, (int)ctx->L, K, K, pinv, &down));
+    // the launches take at most 65535 entries, two per polynomial in the division
+    const size_t chunk = std::min<size_t>(B, 32767);
+    Temp mid(ctx, chunk * l * n * sizeof(u64)), ext(ctx, chunk * (size_t)digits * ext_limbs * n * sizeof(u64));
+    Temp sums(ctx, chunk * 2 * (size_t)l * n * sizeof(u64)), dn(ctx, chunk * 2 * (size_t)K * n * sizeof(u64));
+    if (!mid.ok() || !ext.ok() || !sums.ok() || !dn.ok()) return HISA_ERR_OOM;
+    for (size_t b0 = 0; b0 < B; b0 += chunk) {
+        const size_t cnt = std::min(chunk, B - b0);
+        IntArgs c = int_convert_args(ctx, l, cnt, up);
+        c.in = d + b0 * d_bs; c.in_bs = d_bs; c.galois = galois;
+        c.src_pos0 = 0; c.n_src = l; c.alpha = alpha; c.n_digits = digits; c.own = 1; c.ext_limbs = ext_limbs;
+        c.mid = mid.u(); c.out = ext.u(); c.out_bs = (u64)digits * ext_limbs * n;
+        HIP_TRY(ctx, launch_inverse_rows_int(c, ctx->stream));
+        HIP_TRY(ctx, launch_columns_int(c, ctx->stream));
+        c.ext = ext.u(); c.ext_bs = c.out_bs; c.key = key.data; c.sums = sums.u(); c.down = dn.u();
+        HIP_TRY(ctx, launch_inner_rows_int(c, ctx->stream));
+        IntArgs m = int_convert_args(ctx, l, cnt * 2, down);
+        m.src_pos0 = l; m.n_src = K; m.alpha = K; m.n_digits = 1; m.ext_limbs = l;
+        m.mid = dn.u(); m.out = out + b0 * 2 * l * n; m.out_bs = (u64)l * n;
+        HIP_TRY(ctx, launch_columns_int(m, ctx->stream));
+        m.acc = sums.u(); m.acc_bs = (u64)l * n;
+        m.add = add ? add + b0 * add_bs : nullptr; m.add_bs = add_bs; m.add_ps = (u64)l * n; m.add_div = 2; m.add_polys = add_polys;
+        m.add_galois = galois;
+        HIP_TRY(ctx, launch_divide_rows_int(m, ctx->stream));
     }
-    HIP_TRY(ctx, launch_moddown_final(ctx->d_primes, acc.u(), (u64)2 * ext_limbs * n, conv.u(), (u64)2 * l * n, ctx->d_pinv,
-                                      ctx->d_pinv_sh, add, add_bs, add_polys, add_galois, out, (u64)2 * l * n, l, K, B, log_n,
-                                      st));
     return HISA_OK;
 }
 
@@ -1843,6 +1804,12 @@ static int key_switch_core_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois,
                                down.as<double>(), false);
 }
 
+static int key_switch_core(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key, const u64* add,
+                           u64 add_bs, int add_polys, u64* out) {
+    return fused_key_switch_available(ctx) ? key_switch_core_fp(ctx, d, d_bs, galois, B, l, key, add, add_bs, add_polys, out)
+                                           : key_switch_core_int(ctx, d, d_bs, galois, B, l, key, add, add_bs, add_polys, out);
+}
+
 extern "C" int hisa_analysis_begin(hisa_ctx* ctx) {
     if (!ctx) return HISA_ERR_ARG;
     if (t_analysis) return fail(ctx, HISA_ERR_ARG, "a context of this thread is already in analysis mode");
@@ -1902,26 +1869,11 @@ extern "C" int hisa_rot_left_batch(hisa_ctx* ctx, const hisa_ct* const* in, size
     TRY(gather_batch(ctx, in, n, &bi));
     const size_t nn = ctx->N, lw = (size_t)l * nn;
     int rc = HISA_OK;
-    if (ctx->tabs.fp_ok && ctx->dnum <= 8) {
-        // fused fp64 pipeline: both automorphisms are gathers inside its first and last kernels
-        rc = alloc_ct_batch(ctx, n, 2, (uint32_t)l, 0.0, out);
-        if (rc == HISA_OK) {
-            for (size_t i = 0; i < n; i++) out[i]->scale = in[i]->scale;
-            rc = key_switch_core_fp(ctx, bi.base + lw, bi.stride, g, n, l, it->second, bi.base, bi.stride, 1, out[0]->data);
-        }
-    } else {
-        // sigma_g(c1) in NTT form (a gather); sigma_g(c0) is gathered inside the last kernel
-        Temp r1(ctx, n * lw * sizeof(u64));
-        if (!r1.ok()) rc = HISA_ERR_OOM;
-        if (rc == HISA_OK) {
-            hipError_t e = launch_automorph_ntt(bi.base + lw, bi.stride, r1.u(), lw, g, l, n, (int)ctx->log_n, ctx->stream);
-            if (e != hipSuccess) rc = fail(ctx, HISA_ERR_HIP, "automorph: %s", hipGetErrorString(e));
-        }
-        if (rc == HISA_OK) rc = alloc_ct_batch(ctx, n, 2, (uint32_t)l, 0.0, out);
-        if (rc == HISA_OK) {
-            for (size_t i = 0; i < n; i++) out[i]->scale = in[i]->scale;
-            rc = key_switch_core(ctx, r1.u(), lw, n, l, it->second, bi.base, bi.stride, 1, g, out[0]->data);
-        }
+    // both automorphisms are gathers inside the first and last kernels
+    rc = alloc_ct_batch(ctx, n, 2, (uint32_t)l, 0.0, out);
+    if (rc == HISA_OK) {
+        for (size_t i = 0; i < n; i++) out[i]->scale = in[i]->scale;
+        rc = key_switch_core(ctx, bi.base + lw, bi.stride, g, n, l, it->second, bi.base, bi.stride, 1, out[0]->data);
     }
     dev_release(ctx, bi.tmp);
     return rc;
@@ -2108,10 +2060,7 @@ extern "C" int hisa_relinearize_batch(hisa_ctx* ctx, hisa_ct* const* cts, size_t
     std::vector<hisa_ct*> fresh(n);
     int rc = alloc_ct_batch(ctx, n, 2, (uint32_t)l, 0.0, fresh.data());
     if (rc == HISA_OK) {
-        if (ctx->tabs.fp_ok && ctx->dnum <= 8)
-            rc = key_switch_core_fp(ctx, bi.base + 2 * lw, bi.stride, 0, n, l, it->second, bi.base, bi.stride, 2, fresh[0]->data);
-        else
-            rc = key_switch_core(ctx, bi.base + 2 * lw, bi.stride, n, l, it->second, bi.base, bi.stride, 2, 0, fresh[0]->data);
+        rc = key_switch_core(ctx, bi.base + 2 * lw, bi.stride, 0, n, l, it->second, bi.base, bi.stride, 2, fresh[0]->data);
         for (size_t i = 0; i < n; i++) {
             fresh[i]->scale = cts[i]->scale;
             if (rc == HISA_OK) adopt(ctx, cts[i], fresh[i]);
@@ -2183,6 +2132,27 @@ static int rescale_core_fp(hisa_ctx* ctx, const u64* in, size_t n_bp, int l, u64
     return divide_fp(ctx, c);
 }
 
+// the same in integers
+static int rescale_core_int(hisa_ctx* ctx, const u64* in, size_t n_bp, int l, u64* out) {
+    const size_t nn = ctx->N, chunk = std::min<size_t>(n_bp, 65535);
+    std::vector<u64> qlinv;
+    for (int i = 0; i < l - 1; i++) qlinv.push_back(hm::inv(ctx->mod[l - 1] % ctx->mod[i], ctx->mod[i]));
+    IntTables t;
+    TRY(int_tables(ctx, ((u64)1 << 17) + (u64)l, l - 1, 1, 1, qlinv, &t));
+    Temp mid(ctx, chunk * nn * sizeof(u64));
+    if (!mid.ok()) return HISA_ERR_OOM;
+    for (size_t b0 = 0; b0 < n_bp; b0 += chunk) {
+        IntArgs c = int_convert_args(ctx, l, std::min(chunk, n_bp - b0), t);
+        c.in = in + b0 * l * nn; c.in_bs = (u64)l * nn; c.src_pos0 = l - 1; c.n_src = 1; c.alpha = 1; c.n_digits = 1; c.ext_limbs = l - 1;
+        c.mid = mid.u(); c.out = out + b0 * (l - 1) * nn; c.out_bs = (u64)(l - 1) * nn;
+        c.acc = c.in; c.acc_bs = (u64)l * nn;
+        HIP_TRY(ctx, launch_inverse_rows_int(c, ctx->stream));
+        HIP_TRY(ctx, launch_columns_int(c, ctx->stream));
+        HIP_TRY(ctx, launch_divide_rows_int(c, ctx->stream));
+    }
+    return HISA_OK;
+}
+
 extern "C" int hisa_rescale_batch(hisa_ctx* ctx, hisa_ct* const* cts, size_t n) {
     if (!ctx) return HISA_ERR_ARG;
     TRY(check_batch_shape(ctx, (const hisa_ct* const*)cts, n, 0));
@@ -2194,47 +2164,13 @@ extern "C" int hisa_rescale_batch(hisa_ctx* ctx, hisa_ct* const* cts, size_t n) 
     TRY(gather_batch(ctx, (const hisa_ct* const*)cts, n, &bi));
     int rc = HISA_OK;
     std::vector<hisa_ct*> fresh(n);
-    if (ctx->tabs.fp_ok) {
-        rc = alloc_ct_batch(ctx, n, (uint32_t)polys, (uint32_t)(l - 1), 0.0, fresh.data());
-        if (rc == HISA_OK) {
-            rc = rescale_core_fp(ctx, bi.base, n_bp, l, fresh[0]->data);
-            for (size_t i = 0; i < n; i++) {
-                fresh[i]->scale = cts[i]->scale / (double)ctx->mod[l - 1];
-                if (rc == HISA_OK) adopt(ctx, cts[i], fresh[i]);
-                else hisa_free(ctx, fresh[i]);
-            }
-        }
-    } else {
-        Temp last(ctx, n_bp * nn * sizeof(u64));
-        Temp r(ctx, n_bp * (size_t)(l - 1) * nn * sizeof(u64));
-        if (!last.ok() || !r.ok()) rc = HISA_ERR_OOM;
-        if (rc == HISA_OK) rc = alloc_ct_batch(ctx, n, (uint32_t)polys, (uint32_t)(l - 1), 0.0, fresh.data());
-        if (rc == HISA_OK) {
-            hipError_t e;
-            PolyMap pm = {};
-            pm.period = l;
-            for (int i = 0; i < l; i++) pm.prime_of[i] = i == l - 1 ? (int16_t)(l - 1) : (int16_t)-1;
-            InttExtra ex = {};
-            ex.in = bi.base; ex.in_batch_stride = (u64)l * nn; ex.out_entry0 = l - 1;
-            e = launch_intt(ctx->tabs, (int)ctx->log_n, last.u(), nn, (int)(n_bp * l), pm, &ex, ctx->stream);
-            if (e == hipSuccess) e = launch_rescale_spread(ctx->d_primes, last.u(), r.u(), l, n_bp, (int)ctx->log_n, ctx->stream);
-            if (e == hipSuccess)
-                e = launch_ntt(ctx->tabs, (int)ctx->log_n, r.u(), (u64)(l - 1) * nn, (int)(n_bp * (l - 1)), identity_map(l - 1),
-                               ctx->stream);
-            u64 qlinv[HISA_MAX_Q], qlinv_sh[HISA_MAX_Q];
-            for (int i = 0; i < l - 1; i++) {
-                qlinv[i] = hm::inv(ctx->mod[l - 1] % ctx->mod[i], ctx->mod[i]);
-                qlinv_sh[i] = hm::shoup(qlinv[i], ctx->mod[i]);
-            }
-            if (e == hipSuccess)
-                e = launch_rescale_final(ctx->d_primes, bi.base, r.u(), qlinv, qlinv_sh, fresh[0]->data, l, n_bp, (int)ctx->log_n,
-                                         ctx->stream);
-            if (e != hipSuccess) rc = fail(ctx, HISA_ERR_HIP, "rescale: %s", hipGetErrorString(e));
-            for (size_t i = 0; i < n; i++) {
-                fresh[i]->scale = cts[i]->scale / (double)ctx->mod[l - 1];
-                if (rc == HISA_OK) adopt(ctx, cts[i], fresh[i]);
-                else hisa_free(ctx, fresh[i]);
-            }
+    rc = alloc_ct_batch(ctx, n, (uint32_t)polys, (uint32_t)(l - 1), 0.0, fresh.data());
+    if (rc == HISA_OK) {
+        rc = ctx->tabs.fp_ok ? rescale_core_fp(ctx, bi.base, n_bp, l, fresh[0]->data) : rescale_core_int(ctx, bi.base, n_bp, l, fresh[0]->data);
+        for (size_t i = 0; i < n; i++) {
+            fresh[i]->scale = cts[i]->scale / (double)ctx->mod[l - 1];
+            if (rc == HISA_OK) adopt(ctx, cts[i], fresh[i]);
+            else hisa_free(ctx, fresh[i]);
         }
     }
     dev_release(ctx, bi.tmp);

@@ -38,6 +38,7 @@ struct NttTables {
     const u64* tw_sh;  // Shoup companions
     const u64* itw;    // psi^-bitrev(i)
     const u64* itw_sh;
+    const u64* consts; // per prime: N^-1 and N^-1 times itw[1] with companions, floor(2^(63 + bits) / q), bits - 1 (convert_int.hip)
     // fp64 path (all primes below 2^50, 12 <= log2 N <= 15), else fp_ok = 0 and the pointers are null
     int fp_ok;
     const FpPrime* fprimes;
@@ -61,8 +62,6 @@ struct InttExtra {
     const u64* in;          // read from here instead of data (same PolyMap addressing with in_batch_stride); may be null
     u64 in_batch_stride;
     u64 galois;             // != 0: input index i reads the element that sigma_g moves to i (NTT-form automorphism)
-    const u64* post;        // per period entry: final factor replacing N^-1 (already multiplied by N^-1), may be null
-    const u64* post_sh;
     int out_entry0;         // output polynomial of entry e sits at (e - out_entry0) * N within its batch slot
 };
 
@@ -70,11 +69,8 @@ struct InttExtra {
 struct ConvTable {
     int a;
     int src[HISA_MAX_Q];
-    u64* d_inv_hat;     // [a]   (D/c_i)^-1 mod c_i
-    u64* d_inv_hat_sh;  // [a]
-    u64* d_hat;         // [a][total]  (D/c_i) mod t
-    u64* d_dmod;        // [total]     D mod t
-    std::vector<u64> inv_hat; // host copy
+    std::vector<u64> inv_hat; // [a]         (D/c_i)^-1 mod c_i
+    std::vector<u64> hat;     // [a][total]  (D/c_i) mod t
     double* d_hat_f;    // [a][total]  (D/c_i) mod t as centred doubles (fp64 path), may be null
 };
 
@@ -127,6 +123,8 @@ struct hisa_ctx {
     ConvTable* moddown_tab;
     u64* d_pinv;      // [L] P^-1 mod q_i
     u64* d_pinv_sh;
+    u64* d_consts;    // NttTables::consts
+    std::vector<u64> last_itw;   // inverse twiddle of the level that pairs the two halves, per prime
     u64* d_pmod;      // [L] P mod q_i
     double *d_cos, *d_sin;  // [2N] roots of unity exp(i*pi*t/N)
     FpPrime* d_fprimes;     // fp64 path tables (null when not applicable)
@@ -389,6 +387,52 @@ struct InnerArgs {
     double* down;
 };
 hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, hipStream_t st);
+
+// ---- the same division of work in 64-bit integers (convert_int.hip): any ring degree, primes up to 60 bits, any number of
+// digits.  Digit d converts sources d * alpha .. (at most n_src) to every limb 0 .. ext_limbs - 1 (with `own`: outside its
+// own) and leaves limb x at position d * ext_limbs + x of the output entry.
+enum IntMode { INT_INVERSE, INT_FORWARD, INT_CONVERT, INT_INNER };
+struct IntTasks {
+    int32_t n;                           // polynomials per batch entry
+    int16_t pos[HISA_MAX_PERIOD];        // limb position on the output side
+    int16_t prime[HISA_MAX_PERIOD];
+};
+struct IntArgs {
+    const PrimeConst* primes;
+    const u64 *tw, *tw_sh, *itw, *itw_sh, *consts;
+    int log_n, l, L, total;
+    unsigned n_entries;
+    const u64* in; u64 in_bs;            // NTT form
+    int in_pos_shift;                    // input polynomial of task i at pos[i] + in_pos_shift
+    u64 galois;                          // `in` is read through sigma_g (0 = none)
+    const i64* coeffs;                   // forward transforms: signed coefficients [entry][N] instead of `in`
+    u64* out; u64 out_bs;
+    int whole;                           // set by the launcher
+    u64* mid;                            // conversions: workspace [n_entries][n_src][N]
+    int src_pos0, n_src, alpha, n_digits, own, ext_limbs;
+    const u64* close;                    // [n_src] factor of the source, the same times the last inverse twiddle, with companions
+    const u64* hat;                      // [n_src][total] (D / c_i) mod t in 30-bit halves
+    const u64* off;                      // [n_digits][total] -sum_i floor(c_i / 2) (D / c_i) mod t
+    int chunk, n_splits;                 // set by the launcher
+    // division rows: out = (acc - transform) * factor[limb] (+ addend of entry b: add + (b / add_div) * add_bs +
+    // (b % add_div) * add_ps, if b % add_div < add_polys, through sigma of add_galois); acc below 8 q
+    const u64* acc; u64 acc_bs;
+    const u64 *factor, *factor_sh;
+    const u64* add; u64 add_bs, add_ps; int add_div, add_polys;
+    u64 add_galois;
+    // inner product rows: ext [n_entries][n_digits][ext_limbs][N] behind the columns, own digits from `in`;
+    // sums [n_entries][2][l][N] (below 8 q), down [n_entries][2][ext_limbs - l][N] (behind the inverse rows)
+    const u64* ext; u64 ext_bs;
+    const u64* key;
+    u64 *sums, *down;
+};
+hipError_t launch_ntt_int(const IntArgs& a, const IntTasks& tk, hipStream_t st);
+hipError_t launch_intt_int(const IntArgs& a, const IntTasks& tk, hipStream_t st);
+hipError_t launch_inverse_rows_int(const IntArgs& a, hipStream_t st);   // in -> mid
+hipError_t launch_columns_int(const IntArgs& a, hipStream_t st);        // mid -> out
+hipError_t launch_inner_rows_int(const IntArgs& a, hipStream_t st);     // ext, in -> sums, down
+hipError_t launch_divide_rows_int(const IntArgs& a, hipStream_t st);    // out, in place
+IntArgs int_base_args(const NttTables& t, int log_n);
 // switching keys of the fused path are kept as centred doubles: [n_rows][total][N] in place; back to canonical residues
 hipError_t launch_key_to_doubles(const FpPrime* fprimes, u64* key, int n_rows, int total, int log_n, hipStream_t st);
 hipError_t launch_key_to_residues(const FpPrime* fprimes, const u64* key, u64* out, int n_rows, int total, int log_n, hipStream_t st);
@@ -466,42 +510,6 @@ hipError_t launch_reduce_i64(const PrimeConst* primes, const i64* coeffs, u64* o
 // the same with the output entries out_limbs limbs apart (residues on a second list of primes go behind the first)
 hipError_t launch_reduce_i64(const PrimeConst* primes, const i64* coeffs, u64* out, int limbs, int out_limbs, int n_pts,
                              int log_n, hipStream_t st);
-
-// Fast base conversion (centred): for every batch entry and target,
-//   out[target] = ( sum_i y[src_pos0+i] * hat[i][prime(target)]  -  #{i : y_i > c_i/2} * D ) mod t
-// with y_i the source residues already multiplied by (D/c_i)^-1 mod c_i.
-struct ConvArgs {
-    const u64* y;      // [batch][..][N], coefficient form
-    u64 y_bs;
-    int src_pos0;      // first source limb position inside a batch entry of y
-    int src_prime0;    // its prime index
-    int a;             // number of source limbs
-    const u64* hat;    // [a][total]
-    const u64* dmod;   // [total]
-    int total;
-    u64* out;          // [batch][..][N]
-    u64 out_bs;
-    int n_targets;
-    int16_t tgt_pos[HISA_MAX_PRIMES];   // limb position inside a batch entry of out
-    int16_t tgt_prime[HISA_MAX_PRIMES];
-};
-hipError_t launch_base_conv(const PrimeConst* primes, const ConvArgs& args, u64 n_batch, int log_n, hipStream_t st);
-
-// acc[b][p][x] = sum_j ext[b][j][x] * key[j][p][prime(x)], x over l + K limbs (prime(x) = x for x < l, L + x - l above)
-hipError_t launch_inner_product(const PrimeConst* primes, const u64* ext, u64 ext_bs, int digits, int l, int K, int L,
-                                const u64* key, int total, u64* acc, u64 acc_bs, u64 n_batch, int log_n, hipStream_t st);
-// out[b][p][i] = (acc[b][p][i] - conv[b][p][i]) * P^-1 + add[b][p][i]   (p < add_polys; through sigma_g if galois != 0)
-hipError_t launch_moddown_final(const PrimeConst* primes, const u64* acc, u64 acc_bs, const u64* conv, u64 conv_bs,
-                                const u64* pinv, const u64* pinv_sh, const u64* add, u64 add_bs, int add_polys, u64 galois,
-                                u64* out, u64 out_bs, int l, int K, u64 n_batch, int log_n, hipStream_t st);
-hipError_t launch_copy_limbs(const u64* src, u64 src_bs, u64* dst, u64 dst_bs, int limbs, u64 n_batch, int log_n,
-                             hipStream_t st);
-
-// rescale pieces: r[bp][i] = centred remainder of the last limb modulo q_i; out = (ct - NTT(r)) * q_last^-1
-hipError_t launch_rescale_spread(const PrimeConst* primes, const u64* last, u64* r, int l, u64 n_bp, int log_n,
-                                 hipStream_t st);
-hipError_t launch_rescale_final(const PrimeConst* primes, const u64* ct, const u64* r, const u64* qlinv, const u64* qlinv_sh,
-                                u64* out, int l, u64 n_bp, int log_n, hipStream_t st);
 
 // encode / decode
 hipError_t launch_encode(const double* cs, const double* sn, const uint32_t* g, const double* re, const double* im,

@@ -1,0 +1,49 @@
+"""The row and column kernels of the 64-bit integer key switch and rescale at the edges of their ranges, bit for bit against
+the oracle: every ring degree, digits with more limbs than one chunk of conversion inputs, more digits than one chunk of the
+inner product (and than the fp64 path takes), ragged last digits, one limb, mixed prime sizes up to 60 bits."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+# (log_n, q_bits, dnum, special_bits, limbs of the ciphertexts, batch)
+POINTS = [
+    (10, [60, 30, 25], 3, 60, 3, 3),
+    (10, [60] * 10, 1, 60, 10, 1),               # ten sources, no levels on the columns
+    (11, [60, 59, 58, 57, 56], 2, 60, 4, 9),     # ragged last digit below the top level
+    (12, [60] * 9, 9, 60, 9, 2),                 # nine digits of one limb
+    (12, [30, 30, 30], 3, 60, 2, 5),
+    (12, [50, 40, 45, 50, 36, 50, 44, 50, 41, 40], 10, 50, 10, 2),   # more digits than the fp64 path takes
+    (13, [58] * 21, 2, 60, 19, 1),               # chunks of conversion inputs, three rounds of targets
+    (14, [55, 51, 51, 51, 51], 4, 60, 5, 4),
+    (15, [60, 51], 1, 60, 2, 3),
+    (15, [58] * 8, 1, 60, 8, 1),
+    (16, [60] * 6, 1, 60, 6, 1),                 # more sources than fit the LDS at once
+    (16, [52, 51, 30], 3, 60, 3, 2),
+]
+
+
+@pytest.mark.parametrize("log_n,q_bits,dnum,special,l,batch", POINTS)
+def test_key_switch_and_rescale(log_n, q_bits, dnum, special, l, batch):
+    from oracle import Oracle
+    from paper_1810_00845_amd import hisa, synth
+    print("[case]", log_n, len(q_bits), dnum, l, batch, flush=True)
+    g, o = hisa.Context(log_n, q_bits, dnum, special, 5), Oracle(log_n, q_bits, dnum, special, 5)
+    g.keygen(); o.keygen()
+    g.gen_rot_keys([3]); o.gen_rot_keys([3])
+    coeff = synth.uniform_residues(log_n + l + batch, (batch, 2, l, g.N), g.primes[:l])
+    coeff[0, :, :, :3] = 0
+    for i in range(l):
+        coeff[0, :, i, 3:6] = g.primes[i] - 1
+    cts = g.ct_import_batch(coeff, 2.0 ** 50)
+    sample = sorted({0, batch - 1})
+    ref = {i: o.import_ct(coeff[i], 2.0 ** 50) for i in sample}
+    assert np.array_equal(g.ct_export(cts[0]), coeff[0])
+    out = g.rot_left_batch(cts, 3)
+    prod = g.mul_no_relin_batch(cts, cts)
+    g.relinearize_batch(prod)
+    g.rescale_batch(prod)
+    for i in sample:
+        assert np.array_equal(g.ct_export(out[i]), o.export(o.rot_left(ref[i], 3)))
+        assert np.array_equal(g.ct_export(prod[i]), o.export(o.rescale(o.mul(ref[i], ref[i]))))
+    g.close()
