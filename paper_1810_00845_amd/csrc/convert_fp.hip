@@ -12,7 +12,10 @@
 // Why this split: a workgroup that transforms a whole polynomial (ntt_fp.hip) occupies one compute unit for 20-36 us
 // whatever else is idle, so a call with fewer limb-polynomials than compute units is bound by that latency.  Here a
 // polynomial at N = 2^15 is 32 waves of rows and 32 tiles of columns, nothing waits for a whole polynomial except
-// the launch boundary, and the conversion inputs never travel through memory.
+// the launch boundary, and the conversion inputs never travel through memory.  rotLeft against whole-polynomial workgroups
+// (which also sent the extended digits through memory once more): 64 ciphertexts at N = 2^15, 16 limbs, 1.84 -> 1.33 ms;
+// 3 at 17 limbs 223 -> 109 us; one at N = 2^13, 8 limbs, 64 -> 32 us.  Large batches are bound by fp64 issue in the columns
+// and by memory in the rows, single ciphertexts by five launches of 5-8 us, each a chain of dependent levels.
 //
 // A wave holds 1024 coefficients, 16 per lane.  Five levels on a five-bit field take four in registers and the one on
 // the field's lowest bit after exchanging that bit (lane bit 5) with a register bit by v_permlane32_swap, so a row needs
@@ -841,7 +844,7 @@ size_t split_table_words(int log_n) { return HEAD + ((size_t)SPLIT_ROW << (log_n
 
 // every pointer a launch dereferences is set and every limb it names has a prime: a mistake is a host error
 static bool convert_args_ok(const ConvertArgs& a, u64* targets) {
-    if (a.log_n < 12 || a.log_n > 15 || a.n_entries > 65535 || a.n_digits < 1 || a.n_digits > FP_MAX_DIGITS) return false;
+    if (a.log_n < 12 || a.log_n > 15 || a.n_digits < 1 || a.n_digits > FP_MAX_DIGITS) return false;
     if (!a.fprimes || !a.sfwd || !a.sinv || !a.mid || !a.out || a.n_src < 1 || a.l < 1 || a.L < a.l || a.total < 1) return false;
     if (a.src_pos0 < 0 || a.ext_limbs < 1) return false;
     auto prime_of = [&](int pos) { return pos < a.l ? pos : pos + (a.L - a.l); };
@@ -909,7 +912,16 @@ static hipError_t launch_columns_k3(const ConvertArgs& a_in, hipStream_t st) {
     }
     a.n_splits = 1;
     while (a.n_splits < rounds && (u64)a.n_entries * a.n_digits * TILES * (a.n_splits + 1) <= 512) a.n_splits++;
-    return launch_one<K3, MODE, true>(dim3((unsigned)(TILES * a.n_digits * a.n_splits), a.n_entries), threads, lds, a, InnerArgs{}, 0, st);
+    // a grid has at most 65535 rows of entries: a larger batch takes several launches
+    for (unsigned e0 = 0; e0 < a_in.n_entries; e0 += 65535) {
+        a.n_entries = a_in.n_entries - e0 < 65535 ? a_in.n_entries - e0 : 65535;
+        a.mid = a_in.mid + (u64)e0 * a.n_src * ((u64)1 << a.log_n);
+        a.out = a_in.out + (u64)e0 * a.out_bs;
+        hipError_t e = launch_one<K3, MODE, true>(dim3((unsigned)(TILES * a.n_digits * a.n_splits), a.n_entries), threads, lds, a,
+                                                  InnerArgs{}, 0, st);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 template <int MODE>

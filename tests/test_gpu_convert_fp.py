@@ -50,3 +50,25 @@ def test_key_switch_and_rescale(log_n, q_bits, dnum, special, l, batch):
     want = SharedModDown(o, [ref[0]]).total([(0, r, 1, None) for r in steps], ref[0].scale)
     assert np.array_equal(g.ct_export(summed[0]), o.export(want))
     g.close()
+
+
+def test_more_entries_than_a_grid_has_rows():
+    """The ModDown's columns of 32769 ciphertexts are 65538 entries, three more than one launch takes: the first ciphertexts, those
+    on both sides of the line and the last equal single calls."""
+    from paper_1810_00845_amd import hisa
+    print("[case] 32769 ciphertexts, N = 2^12, 2 limbs", flush=True)
+    g = hisa.Context(12, [50, 45], 1, 50, 5)
+    g.gen_rot_keys([3])
+    two = g.ct_random_batch(2, 2, 2.0 ** 40, 9)
+    n = 32769
+    out = g.rot_left_batch([two[i % 2] for i in range(n)], 3)
+    want = [g.ct_export(g.rot_left(ct, 3)) for ct in two]
+    for i in (0, 1, 32766, 32767, 32768):
+        assert np.array_equal(g.ct_export(out[i]), want[i % 2])
+    g.rescale_batch(out)
+    single = [g.rot_left(ct, 3) for ct in two]
+    for ct in single:
+        g.rescale_batch([ct])
+    for i in (0, 1, 32766, 32767, 32768):
+        assert np.array_equal(g.ct_export(out[i]), g.ct_export(single[i % 2]))
+    g.close()
