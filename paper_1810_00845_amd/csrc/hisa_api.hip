@@ -1,7 +1,7 @@
 // Host side of libhisa: context set-up (primes, roots, tables, keys), handle
 // and device-memory management, argument checks, and the launch sequences
 // behind every C-ABI entry point.  No arithmetic on polynomial data happens
-// here; the kernels are in ntt.hip, elementwise.hip, keyswitch.hip, encode.hip.
+// here; the kernels are in ntt.hip, ntt_fp.hip, convert_fp.hip, convert_int.hip, elementwise.hip, encode.hip.
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
