@@ -477,10 +477,8 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
 #pragma unroll
     for (int r = 0; r < 16; r++) va[r] = bload(acc, lane8, (uint32_t)r * 512u);
     if (with_add) {
-        const u64 add_ct = a.step_B ? (b / a.add_div) % (u64)a.step_B : b / a.add_div;
-        const u64 add_g = a.step_B ? (u64)a.galois_tab[(b / a.add_div) / (u64)a.step_B] : a.add_galois;
         double vb[16];
-        load_row_through<K3>(vb, a.add + add_ct * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, add_g, row, lane);
+        load_row_through<K3>(vb, a.add + (b / a.add_div) * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, a.add_galois, row, lane);
 #pragma unroll
         for (int r = 0; r < 16; r++)
             bstore(dst, lane8, (uint32_t)r * 512u,
@@ -504,8 +502,13 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
 // Per entry the launch reads (digits' limbs) + own + addend and writes 2 (n_acc + sources) limbs: bound by memory.
 // Bounds, keys and constants centred: a term is at most 0.501 + 3/16 * 5.5 = 1.54 p, four of them 6.2 p; sum * c1 at most
 // 0.501 + 3/16 * 6.2 = 1.7 p; with the addend 2.7 p.
+// Several rotations of the same digits (STEPS): the digits come transformed and their rows are read through sigma_g, which maps
+// rows to rows; the rest is the same.  The entries of a row, all rotations of it, are neighbours in the order of the tasks, so
+// the digits of a limb (the same for all of them) stay in the L2; the keys, each read once, are what the launches stream.
+// 24 rotations of one ciphertext at N = 2^14, 12 limbs: 187 -> 162 us against inner products and a division as separate
+// launches with the accumulators in memory between them.
 #define IP_CAP 5.5f
-template <int K3, int MODE>
+template <int K3, int MODE, bool STEPS>
 __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs& g, int n_tasks, double* lds_all) {
     const int per = (n_tasks + 7) >> 3;
     const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
@@ -521,6 +524,10 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     const Modulus q = modulus(a.fprimes, prime);
     constexpr u64 n = (u64)1 << (10 + K3);
     const uint32_t lane8 = (uint32_t)lane * 8u;
+    const uint32_t step = STEPS ? (uint32_t)b / g.step_B : 0u;
+    const u64 ct = STEPS ? (uint32_t)b - step * g.step_B : b;
+    const u64 galois = STEPS ? (u64)g.steps.galois[step] : g.galois;
+    const u64* key = STEPS ? g.steps.key[step] : g.key;
     double sum[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) sum[r] = 0.0;
@@ -530,9 +537,13 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
         if (d < a.n_digits) {
             double v[16];
             if (x >= a.dg[d].own_lo && x < a.dg[d].own_lo + a.dg[d].own_n) {
-                load_row_through<K3>(v, g.own + b * g.own_bs + (u64)x * n, g.galois, row, lane);
+                load_row_through<K3>(v, g.own + ct * g.own_bs + (u64)x * n, galois, row, lane);
 #pragma unroll
                 for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = fp_from_u64((u64)__double_as_longlong(v[r]));
+            } else if (STEPS) {
+                load_row_through<K3>(v, a.out + ct * a.out_bs + (u64)(a.dg[d].out_pos0 + x) * n, galois, row, lane);
+#pragma unroll
+                for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = v[r];
             } else {
                 const rsrc_t src = make_rsrc((const double*)a.out + b * a.out_bs + (u64)(a.dg[d].out_pos0 + x) * n + row * 1024u, 8192u);
                 float m[16];
@@ -547,7 +558,7 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
             }
         }
         SCHED_FENCE();
-        const double* key_p = (const double*)g.key + (((u64)d0 * 2 + poly) * a.total + prime) * n + row * 1024u;
+        const double* key_p = (const double*)key + (((u64)d0 * 2 + poly) * a.total + prime) * n + row * 1024u;
         const bool two = d0 + 1 < a.n_digits;
         const rsrc_t k0r = make_rsrc(key_p, 8192u), k1r = make_rsrc(two ? key_p + (u64)2 * a.total * n : key_p, 8192u);
         double k0[16], k1[16];
@@ -576,7 +587,7 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     SCHED_FENCE();
     if (x < a.l && poly < g.add_polys) {
         double t[16];
-        load_row_through<K3>(t, g.add + b * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, g.galois, row, lane);
+        load_row_through<K3>(t, g.add + ct * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, galois, row, lane);
         const double c2 = g.c2 ? as_const(g.c2)[x] : 1.0;
         if (g.c2) {
 #pragma unroll
@@ -818,7 +829,9 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a)
 // ---------------------------------------------------------------------------
 // MODE (enum FpMode) names the stage a launch belongs to, so that a profile tells the ModUp's columns from the ModDown's;
 // COLUMNS: the launch in which all target limbs of a digit share one pass over its sources, else the rows.
-constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : (mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB) ? 128 : ROWS_NT; }
+constexpr bool fp_steps(int mode) { return mode == FP_STEPS_TO_Y || mode == FP_STEPS_SUB; }
+constexpr bool fp_inner(int mode) { return mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB || fp_steps(mode); }
+constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : fp_inner(mode) ? 128 : ROWS_NT; }
 
 template <int K3, int MODE, bool COLUMNS>
 __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), 4) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
@@ -828,7 +841,8 @@ __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), 4) void ntt_fp_kernel(Co
     } else {
         __shared__ double lds[fp_threads(MODE, false) / 64 * ROW_LDS];
         if constexpr (MODE == FP_INV_TO_Y) rows_inverse<K3>(a, n_tasks, lds);
-        else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE>(a, g, n_tasks, lds);
+        else if constexpr (fp_inner(MODE))
+            rows_inner<K3, MODE == FP_INV_D_TO_Y || MODE == FP_STEPS_TO_Y ? FP_INV_D_TO_Y : FP_FWD_CONV_SUB, fp_steps(MODE)>(a, g, n_tasks, lds);
         else rows_forward<K3, MODE>(a, n_tasks, lds);
     }
 }
@@ -963,10 +977,6 @@ hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st
     if (mode != FP_FWD_CONV && (!a.acc || a.n_digits != 1)) return hipErrorInvalidValue;
     if (mode == FP_FWD_CONV_FINAL) {
         if (!a.pinv_tab || (a.add && a.add_div <= 0)) return hipErrorInvalidValue;
-        // rotation-major entries: every entry's rotation index must fall inside galois_tab
-        if (a.add && (a.step_B < 0 ||
-            (a.step_B > 0 && ((u64)a.n_entries + (u64)a.add_div * a.step_B - 1) / ((u64)a.add_div * a.step_B) > FP_MAX_STEPS)))
-            return hipErrorInvalidValue;
     }
     switch (mode) {
         case FP_FWD_CONV: return launch_rows<FP_FWD_CONV>(a, InnerArgs{}, targets, st);
@@ -982,17 +992,23 @@ hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs&
     u64 targets = 0;
     if (!convert_args_ok(a, &targets)) return hipErrorInvalidValue;
     const u64 n = (u64)1 << a.log_n;
-    if (!g.key || !g.own || !g.c1 || g.n_acc < 1 || g.n_acc >= a.ext_limbs || g.n_acc > a.l) return hipErrorInvalidValue;
+    const bool steps = fp_steps(mode);
+    if (steps) {        // every entry belongs to a rotation with its key and Galois element
+        if (g.step_B < 1 || a.n_entries % g.step_B || a.n_entries / g.step_B > FP_MAX_STEPS) return hipErrorInvalidValue;
+        for (unsigned s = 0; s < a.n_entries / g.step_B; s++)
+            if (!g.steps.key[s] || g.steps.galois[s] == 0) return hipErrorInvalidValue;
+    }
+    if ((!steps && !g.key) || !g.own || !g.c1 || g.n_acc < 1 || g.n_acc >= a.ext_limbs || g.n_acc > a.l) return hipErrorInvalidValue;
     if (g.x_begin < 0 || g.x_begin >= g.x_end || g.x_end > a.ext_limbs) return hipErrorInvalidValue;
     if (g.own_bs < (u64)a.l * n || g.add_polys < 0 || g.add_polys > 2 || (g.add_polys && !g.add)) return hipErrorInvalidValue;
     if (g.add_polys && (g.add_bs < (u64)g.add_polys * a.l * n || (g.add_polys > 1 && g.add_ps < (u64)a.l * n))) return hipErrorInvalidValue;
     const u64 limbs = (u64)(g.x_end - g.x_begin);
-    if (mode == FP_INV_D_TO_Y) {
+    if (mode == FP_INV_D_TO_Y || mode == FP_STEPS_TO_Y) {
         if ((g.x_begin < g.n_acc && !g.acc) || (g.x_end > g.n_acc && !g.down)) return hipErrorInvalidValue;
-        return launch_rows<FP_INV_D_TO_Y>(a, g, limbs, st);
+        return steps ? launch_rows<FP_STEPS_TO_Y>(a, g, limbs, st) : launch_rows<FP_INV_D_TO_Y>(a, g, limbs, st);
     }
-    if (mode != FP_FWD_CONV_SUB || g.x_end > g.n_acc || !g.out) return hipErrorInvalidValue;
-    return launch_rows<FP_FWD_CONV_SUB>(a, g, limbs, st);
+    if ((mode != FP_FWD_CONV_SUB && mode != FP_STEPS_SUB) || g.x_end > g.n_acc || !g.out) return hipErrorInvalidValue;
+    return steps ? launch_rows<FP_STEPS_SUB>(a, g, limbs, st) : launch_rows<FP_FWD_CONV_SUB>(a, g, limbs, st);
 }
 
 // ---- whole polynomials ----

@@ -1553,35 +1553,6 @@ int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add,
     return divide_fp(ctx, c);
 }
 
-// Inner products and division for n_steps rotations of the same B ciphertexts in one set of launches (entries rotation-major): a
-// convolution's taps rotate few ciphertexts many times, and a launch over B entries alone would leave most of the chip
-// idle.  out: [n_steps][B] ciphertexts.
-static int key_switch_finish_steps_fp(hisa_ctx* ctx, const FpExt& x, const u64* d, u64 d_bs, const u64* galois,
-                                      const SwitchKey* const* keys, int n_steps, size_t B, const u64* add, u64 add_bs, u64* out) {
-    const size_t n = ctx->N, E = (size_t)n_steps * B;
-    const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total, l = x.l;
-    const int ext_limbs = x.ext_limbs, log_n = (int)ctx->log_n;
-    hipStream_t st = ctx->stream;
-    if (n_steps < 1 || n_steps > FP_MAX_STEPS) return fail(ctx, HISA_ERR_ARG, "bad rotation count");
-    Temp acc(ctx, E * 2 * (size_t)ext_limbs * n * sizeof(u64));
-    Temp y2(ctx, E * 2 * (size_t)K * n * sizeof(double));
-    if (!acc.ok() || !y2.ok()) return HISA_ERR_OOM;
-    double *post_q, *post_p;
-    TRY(fp_post_tables(ctx, l, &post_q, &post_p, false));
-    IpSteps steps = {};
-    for (int s = 0; s < n_steps; s++) { steps.key[s] = keys[s]->data; steps.galois[s] = (uint32_t)galois[s]; }
-    HIP_TRY(ctx, launch_inner_product_steps_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, steps, n_steps,
-                                               total, d, d_bs, acc.u(), (u64)2 * ext_limbs * n, B, log_n, st));
-    ConvertArgs c = convert_base(ctx, l, E * 2);
-    c.in = acc.u(); c.in_bs = (u64)ext_limbs * n; c.src_pos0 = l; c.n_src = K; c.post = post_p; c.mid = y2.as<double>();
-    c.n_digits = 1; c.dg[0] = {ctx->moddown_tab->d_hat_f, 0, K, 0, 0, 0}; c.ext_limbs = l; c.out = out; c.out_bs = (u64)l * n;
-    c.acc = acc.u(); c.acc_bs = (u64)ext_limbs * n; c.pinv_tab = ctx->d_pinv_f;
-    c.add = add; c.add_bs = add_bs; c.add_ps = (u64)l * n; c.add_div = 2; c.add_polys = 1;
-    c.step_B = (int)B;
-    for (int s = 0; s < n_steps; s++) c.galois_tab[s] = (uint32_t)galois[s];
-    return divide_fp(ctx, c);
-}
-
 bool fused_key_switch_available(const hisa_ctx* ctx) { return ctx->tabs.fp_ok && ctx->dnum <= 8; }
 
 // The key-switch accumulators -- before the division by P -- of n_steps rotations of B ciphertexts (cts: [B][2][l][N],
@@ -1757,12 +1728,35 @@ extern "C" int hisa_rot_left_sum_batch(hisa_ctx* ctx, const hisa_ct* const* in, 
     return rc;
 }
 
-// One key switch of B polynomials as five launches (A to E above).  acc != null ([B][2][l][N] doubles): the limbs of q are
-// summed in launch C too and E only subtracts -- the shorter chain of launches where they do not fill the chip.
+// C, D and E: the inner products of `entries` key switches on the digits that c names, and the division by P.
+// g.acc != null ([entries][2][l][N] doubles): the limbs of q are summed in launch C too and E only subtracts -- the shorter
+// chain of launches where they do not fill the chip.
+static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, int l, size_t entries, u64* out) {
+    const size_t n = ctx->N;
+    const int K = (int)ctx->K;
+    g.n_acc = l;
+    g.x_begin = g.acc ? 0 : l; g.x_end = l + K;
+    c.n_entries = (unsigned)entries;
+    HIP_TRY(ctx, launch_inner_rows_fp(g.step_B ? FP_STEPS_TO_Y : FP_INV_D_TO_Y, c, g, ctx->stream));
+    ConvertArgs m = convert_base(ctx, l, entries * 2);      // entries are (ciphertext, b|a) pairs
+    m.src_pos0 = l; m.n_src = K; m.mid = g.down;
+    m.n_digits = 1; m.dg[0] = {ctx->d_moddown_hat_pin, 0, K, 0, 0, 0}; m.ext_limbs = l; m.out = out; m.out_bs = (u64)l * n;
+    HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV_SUB, m, ctx->stream));
+    if (g.acc) {
+        m.acc = (const u64*)g.acc; m.acc_bs = (u64)l * n;
+        HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_SUB, m, ctx->stream));
+    } else {
+        g.out = out; g.x_begin = 0; g.x_end = l;
+        HIP_TRY(ctx, launch_inner_rows_fp(g.step_B ? FP_STEPS_SUB : FP_FWD_CONV_SUB, c, g, ctx->stream));
+    }
+    return HISA_OK;
+}
+
+// One key switch of B polynomials as five launches (A to E above).  acc: see key_switch_divide_fp.
 static int key_switch_fused_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, const SwitchKey& key, const u64* add,
                                u64 add_bs, int add_polys, u64* out, const FpExt& x, double* acc, double* down, bool no_alloc) {
     const size_t n = ctx->N;
-    const int K = (int)ctx->K, l = x.l;
+    const int l = x.l;
     double *post_q, *post_p, *c1;
     TRY(fp_post_tables(ctx, l, &post_q, &post_p, no_alloc));
     TRY(fp_inner_tables(ctx, l, &c1, no_alloc));
@@ -1772,32 +1766,47 @@ static int key_switch_fused_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois
     HIP_TRY(ctx, launch_inverse_rows_fp(c, ctx->stream));
     HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV, c, ctx->stream));
     InnerArgs g = {};
-    g.key = key.data; g.own = d; g.own_bs = d_bs; g.galois = galois; g.n_acc = l; g.c1 = c1;
+    g.key = key.data; g.own = d; g.own_bs = d_bs; g.galois = galois; g.c1 = c1;
     g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = add ? add_polys : 0;
     g.acc = acc; g.down = down;
-    g.x_begin = acc ? 0 : l; g.x_end = x.ext_limbs;
-    HIP_TRY(ctx, launch_inner_rows_fp(FP_INV_D_TO_Y, c, g, ctx->stream));
-    ConvertArgs m = convert_base(ctx, l, B * 2);      // entries are (ciphertext, b|a) pairs
-    m.src_pos0 = l; m.n_src = K; m.mid = down;
-    m.n_digits = 1; m.dg[0] = {ctx->d_moddown_hat_pin, 0, K, 0, 0, 0}; m.ext_limbs = l; m.out = out; m.out_bs = (u64)l * n;
-    HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV_SUB, m, ctx->stream));
-    if (acc) {
-        m.acc = (const u64*)acc; m.acc_bs = (u64)l * n;
-        HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_SUB, m, ctx->stream));
-    } else {
-        g.out = out; g.x_begin = 0; g.x_end = l;
-        HIP_TRY(ctx, launch_inner_rows_fp(FP_FWD_CONV_SUB, c, g, ctx->stream));
-    }
-    return HISA_OK;
+    return key_switch_divide_fp(ctx, c, g, l, B, out);
+}
+
+// Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic
+// (rotLeft of 64 at N = 2^15, 16 limbs: 1.34 ms against 1.52), but makes the last launch's chain longer (one
+// rotation at N = 2^13: 36 us against 33).  The two meet where the rows of one launch fill about half of the chip.
+static bool store_accumulators(const hisa_ctx* ctx, size_t entries, int ext_limbs) {
+    return entries * (size_t)ext_limbs * (ctx->N >> 10) < 1024;
+}
+
+// C, D and E for n_steps rotations of the same B ciphertexts (entries rotation-major) whose digits are in x: a convolution's
+// taps rotate few ciphertexts many times, and a launch over B entries alone would leave most of the chip idle.
+// out: [n_steps][B] ciphertexts.
+static int key_switch_finish_steps_fp(hisa_ctx* ctx, const FpExt& x, const u64* d, u64 d_bs, const u64* galois,
+                                      const SwitchKey* const* keys, int n_steps, size_t B, const u64* add, u64 add_bs, u64* out) {
+    const size_t n = ctx->N, E = (size_t)n_steps * B;
+    const int l = x.l;
+    if (n_steps < 1 || n_steps > FP_MAX_STEPS) return fail(ctx, HISA_ERR_ARG, "bad rotation count");
+    const bool stored = store_accumulators(ctx, E, x.ext_limbs);
+    Temp acc(ctx, E * 2 * (size_t)l * n * sizeof(double), stored), down(ctx, E * 2 * (size_t)ctx->K * n * sizeof(double));
+    if ((stored && !acc.ok()) || !down.ok()) return HISA_ERR_OOM;
+    double* c1;
+    TRY(fp_inner_tables(ctx, l, &c1, false));
+    ConvertArgs c = convert_base(ctx, l, B);
+    TRY(modup_digits(ctx, c, x, false));
+    InnerArgs g = {};
+    g.own = d; g.own_bs = d_bs; g.c1 = c1;
+    g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = 1;
+    g.acc = stored ? acc.as<double>() : nullptr; g.down = down.as<double>();
+    g.step_B = (unsigned)B;
+    for (int s = 0; s < n_steps; s++) { g.steps.key[s] = keys[s]->data; g.steps.galois[s] = (uint32_t)galois[s]; }
+    return key_switch_divide_fp(ctx, c, g, l, E, out);
 }
 
 static int key_switch_core_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key,
                               const u64* add, u64 add_bs, int add_polys, u64* out) {
     FpExt x(ctx, B, l, (int)ctx->K, (int)ctx->alpha);
-    // Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic
-    // (rotLeft of 64 at N = 2^15, 16 limbs: 1.34 ms against 1.52), but makes the last launch's chain longer (one
-    // rotation at N = 2^13: 36 us against 33).  The two meet where the rows of one launch fill about half of the chip.
-    const bool stored = B * (size_t)x.ext_limbs * (ctx->N >> 10) < 1024;
+    const bool stored = store_accumulators(ctx, B, x.ext_limbs);
     Temp acc(ctx, B * 2 * (size_t)l * ctx->N * sizeof(double), stored), down(ctx, B * 2 * (size_t)ctx->K * ctx->N * sizeof(double));
     if (!x.ok() || (stored && !acc.ok()) || !down.ok()) return HISA_ERR_OOM;
     return key_switch_fused_fp(ctx, d, d_bs, galois, B, key, add, add_bs, add_polys, out, x, stored ? acc.as<double>() : nullptr,

@@ -284,6 +284,8 @@ enum FpMode {
     FP_INV_D_TO_Y = 5,     // rows: forward levels of the digits, key inner product, inverse levels of the division's sources
     FP_FWD_CONV_SUB = 6,   // columns: the division's conversion; rows: key inner product minus the division's transform
     FP_FWD_SUB = 7,        // rows: stored accumulators minus the division's transform (small calls)
+    FP_STEPS_TO_Y = 8,     // 5 for several rotations of the same extended digits, whose rows are transformed already
+    FP_STEPS_SUB = 9,      // the rows of 6 for such rotations
 };
 
 struct FpTask {
@@ -359,11 +361,6 @@ struct ConvertArgs {
     // FP_FWD_CONV_FINAL: addend of entry b: add + (b / add_div) * add_bs + (b % add_div) * add_ps, if b % add_div < add_polys
     const u64* add; u64 add_bs, add_ps; int add_div, add_polys;
     u64 add_galois;
-    // several rotations of the same step_B ciphertexts in one launch (entries ordered rotation-major): entry b's
-    // addend is that of ciphertext (b / add_div) % step_B, gathered through galois_tab[(b / add_div) / step_B];
-    // step_B = 0: one rotation, add_galois applies
-    int step_B;
-    uint32_t galois_tab[FP_MAX_STEPS];
 };
 hipError_t launch_inverse_rows_fp(const ConvertArgs& a, hipStream_t st);              // in -> mid
 hipError_t launch_columns_fp(int mode, const ConvertArgs& a, hipStream_t st);         // mid -> out (modes 3, 4, 6)
@@ -375,6 +372,13 @@ hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st
 // acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend * c2[x]), lazily reduced doubles for FP_FWD_SUB.
 // FP_FWD_CONV_SUB (limbs below n_acc): out holds the division's columns and receives its result.
 // Own digits and addend are read through sigma_g.
+// FP_STEPS_TO_Y and FP_STEPS_SUB: several rotations of the same step_B ciphertexts, entry b being rotation b / step_B of
+// ciphertext b % step_B.  ConvertArgs::out, own and add then hold step_B entries, out fully transformed, normalised digits, and
+// all three are read through the rotation's Galois element; sums and results are rotation-major.
+struct IpSteps {
+    const u64* key[FP_MAX_STEPS];
+    uint32_t galois[FP_MAX_STEPS];
+};
 struct InnerArgs {
     const u64* key;
     const u64* own; u64 own_bs;
@@ -385,6 +389,8 @@ struct InnerArgs {
     double* acc;
     u64* out;
     double* down;
+    unsigned step_B;
+    IpSteps steps;
 };
 hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, hipStream_t st);
 
@@ -446,10 +452,6 @@ hipError_t launch_inner_product_fp(const FpPrime* fprimes, const double* ext, u6
 // polynomial): rotation s uses keys[s] and gathers through galois[s]; acc entries are ordered rotation-major.
 // c0_src (with pmod[i] = P mod q_i): the b accumulator also takes P * sigma_s(c0) on the limbs of q, c0 read at
 // c0_src + b * own_bs like the own-digit limbs.
-struct IpSteps {
-    const u64* key[FP_MAX_STEPS];
-    uint32_t galois[FP_MAX_STEPS];
-};
 hipError_t launch_inner_product_steps_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
                                          int alpha, const IpSteps& steps, int n_steps, int total, const u64* own_src,
                                          u64 own_bs, u64* acc, u64 acc_bs, u64 n_batch, int log_n, hipStream_t st,
