@@ -31,29 +31,20 @@ def algorithmic_bytes_rot_left(N, l, K, alpha, B):
     ext = l + K
     digits = (l + alpha - 1) // alpha
     sizes = [min(alpha, l - j * alpha) for j in range(digits)]
-    out = {}
-    out["automorph_ntt_kernel"] = 2 * l * LP * B
-    out["ntt_pass_kernel<true>"] = 2 * LP * B * (l + 2 * K)
-    out["ntt_pass_kernel<false>"] = 2 * LP * B * (sum(ext - a for a in sizes) + 2 * l)
-    out["base_conv_kernel"] = LP * B * (sum(a + (ext - a) for a in sizes) + 2 * (K + l))
-    out["copy_limbs_kernel"] = 2 * l * LP * B
-    out["inner_product_kernel"] = LP * (B * (digits * ext + 2 * ext) + digits * 2 * ext)
-    out["moddown_final_kernel"] = 7 * l * LP * B
-    # fused fp64 pipeline (primes below 2^50): what each launch set must read and write once
     conv_out = sum(ext - a for a in sizes)
-    # kernel names as rocprofv3 prints them: ntt_fp_kernel<log2 N - 10, mode>; mode 2 = inverse transform to the
-    # conversion input, 3 = base conversion + forward transform, 4 = the same + final combine
+    # kernel names as rocprofv3 prints them, without the third argument (the launch over columns or over rows): the
+    # stages of convert_fp.hip, what each must read and write once
     k3 = "%d" % (N.bit_length() - 1 - 10)
-    # 2 = stage A (c1 to the conversion input), 5 = stage C (special limbs of the accumulators to the ModDown's
-    # conversion input), 6 = stage D (conversion + transform + subtraction from the folded accumulators)
-    out["ntt_fp_kernel<%s, 2>" % k3] = 2 * LP * B * l
-    out["ntt_fp_kernel<%s, 5>" % k3] = 2 * LP * B * 2 * K
-    out["ntt_fp_kernel<%s, 3>" % k3] = LP * B * (l + conv_out)
-    out["inner_product_fp_kernel"] = LP * (B * (conv_out + l + 2 * ext) + digits * 2 * ext)
-    out["inner_product_fold_fp_kernel"] = LP * (B * (conv_out + l + l + 2 * ext) + digits * 2 * ext)   # + the addend c0
-    out["ntt_fp_kernel<%s, 4>" % k3] = LP * B * (2 * K + 2 * l + l + 2 * l)
-    out["ntt_fp_kernel<%s, 6>" % k3] = LP * B * (2 * K + 2 * l + 2 * l)
-    return out
+    return {
+        # inverse rows of c1
+        "ntt_fp_kernel<%s, 2>" % k3: 2 * LP * B * l,
+        # columns: the limbs of c1 to the extended digits
+        "ntt_fp_kernel<%s, 3>" % k3: LP * B * (l + conv_out),
+        # rows of the special limbs: extended digits and key to the sources of the division by P
+        "ntt_fp_kernel<%s, 5>" % k3: LP * (B * (digits * K + 2 * K) + digits * 2 * K),
+        # the division's columns; rows of the limbs of q: extended digits, own limbs, addend, key and columns to the result
+        "ntt_fp_kernel<%s, 6>" % k3: LP * (B * (2 * K + 2 * l + sum(l - a for a in sizes) + l + l + 2 * l + 2 * l) + digits * 2 * l),
+    }
 
 
 def algorithmic_flops_rot_left(N, l, K, alpha, B):
@@ -65,21 +56,19 @@ def algorithmic_flops_rot_left(N, l, K, alpha, B):
     ext = l + K
     digits = (l + alpha - 1) // alpha
     sizes = [min(alpha, l - j * alpha) for j in range(digits)]
-    ntt = 10 * (N // 2) * log_n
+    rows, cols = 10 * (N // 2) * 10, 10 * (N // 2) * (log_n - 10)      # the levels inside a row of 1024 and those across rows
     k3 = "%d" % (log_n - 10)
-    out = {}
-    out["ntt_fp_kernel<%s, 2>" % k3] = B * l * (ntt + 2 * 8 * N)                    # + untwist and (D/q)^-1 products
-    out["ntt_fp_kernel<%s, 5>" % k3] = B * 2 * K * (ntt + 8 * N)                    # + untwist
-    out["ntt_fp_kernel<%s, 6>" % k3] = B * 2 * l * (ntt + 9 * K * N + N)            # + acc - conv
-    out["inner_product_fold_fp_kernel"] = B * ext * N * 2 * (9 * digits + 8)
-    out["ntt_fp_kernel<%s, 3>" % k3] = B * sum((ext - a) * (ntt + 9 * a * N) for a in sizes)
-    out["ntt_fp_kernel<%s, 4>" % k3] = B * 2 * l * (ntt + 9 * K * N + 10 * N)       # + (acc - conv) P^-1 + addend
-    out["inner_product_fp_kernel"] = B * ext * N * 2 * 9 * digits
-    return out
+    return {
+        "ntt_fp_kernel<%s, 2>" % k3: B * l * rows,
+        "ntt_fp_kernel<%s, 3>" % k3: B * (l * (cols + 8 * N) + sum((ext - a) * (cols + 9 * a * N) for a in sizes)),
+        "ntt_fp_kernel<%s, 5>" % k3: B * (digits * K * rows + 2 * K * (9 * digits * N + 8 * N + rows)),
+        "ntt_fp_kernel<%s, 6>" % k3: B * (2 * K * (cols + 8 * N) + 2 * l * (cols + 9 * K * N)
+                                          + sum(l - a for a in sizes) * rows + 2 * l * (9 * digits * N + 9 * N + rows)),
+    }
 
 
 COUNTER_FILE = os.path.join(ROOT, "profiles", "rot_left_n15_l16_dnum3_b64_counters.md")
-KERNEL_SOURCES = ("ntt_fp.hip", "fparith.hpp", "elementwise.hip")
+KERNEL_SOURCES = ("convert_fp.hip", "fp_device.hpp", "fparith.hpp", "elementwise.hip")
 
 
 def kernel_source_sha():
@@ -365,8 +354,7 @@ def main():
     ctx.profile_enable(False)
     alg = algorithmic_bytes_rot_left(N, L, K, alpha, B)
     flops = algorithmic_flops_rot_left(N, L, K, alpha, B)
-    # the transform kernel's name carries a third template argument (two conversion targets per pass or one); the
-    # launches of a stage are summed whatever their form
+    # the transform kernel's name carries a third template argument (columns or rows); the launches of a stage are summed
     merged = {}
     for name, (cnt, ms) in prof.items():
         key = re.sub(r", (true|false)>$", ">", name)
@@ -399,14 +387,23 @@ def main():
                 "algorithmic_bytes_per_launch": int(alg.get(dom, 0) / launches)}
     cnt = counters.get(counter_key(dom), {})
     if dom in flops:
-        # the transform kernels are bound by the vector ALU, not by HBM (counters: 55-65 % of the issue slots busy,
-        # a fifth of the HBM peak), so the roofline is the fp64 vector peak; the HBM reading stays beside it
+        # rows move a limb for ten levels, columns convert many limbs for each they move: the bound is the resource of
+        # whose measured rate the kernel reaches more, the other reading stays beside it
         tf = kernels[dom]["algorithmic_TFLOPs"]
-        roofline = {"kernel": dom, "bound": "alu", "achieved": tf, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
-                    "frac": round(tf / FP64_PEAK_TFLOPS, 4),
-                    "peak_measured": round(fp64_measured, 2), "frac_of_measured": round(tf / fp64_measured, 4),
-                    "algorithmic_flops_per_launch": int(flops[dom] / launches),
-                    "valu_issue_busy": cnt.get("valu_issue_busy"), "hbm": hbm_side}
+        alu_side = {"achieved_TFLOPs": tf, "frac": round(tf / FP64_PEAK_TFLOPS, 4), "frac_of_measured": round(tf / fp64_measured, 4),
+                    "algorithmic_flops_per_launch": int(flops[dom] / launches)}
+        if (hbm_side["frac_of_measured_copy"] or 0.0) > alu_side["frac_of_measured"]:
+            roofline = {"kernel": dom, "bound": "hbm", "achieved": hbm_side["achieved_GBs"], "peak": HBM_PEAK_GBS,
+                        "unit": "GB/s", "frac": hbm_side["frac"],
+                        "peak_measured": round(cal["copy_GBs"], 1), "frac_of_measured": hbm_side["frac_of_measured_copy"],
+                        "algorithmic_bytes_per_launch": hbm_side["algorithmic_bytes_per_launch"],
+                        "valu_issue_busy": cnt.get("valu_issue_busy"), "alu": alu_side}
+        else:
+            roofline = {"kernel": dom, "bound": "alu", "achieved": tf, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
+                        "frac": alu_side["frac"],
+                        "peak_measured": round(fp64_measured, 2), "frac_of_measured": alu_side["frac_of_measured"],
+                        "algorithmic_flops_per_launch": alu_side["algorithmic_flops_per_launch"],
+                        "valu_issue_busy": cnt.get("valu_issue_busy"), "hbm": hbm_side}
     else:
         roofline = {"kernel": dom, "bound": "hbm", "achieved": hbm_side["achieved_GBs"], "peak": HBM_PEAK_GBS,
                     "unit": "GB/s", "frac": hbm_side["frac"],
