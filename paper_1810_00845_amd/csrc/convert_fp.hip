@@ -25,6 +25,7 @@
 // compile time (Bound below: plain floats that fold away after unrolling) and normalises only where the result could
 // leave 8 p.
 #include <cstdio>
+#include <type_traits>
 
 #include "fp_device.hpp"
 #include "modarith.hpp"
@@ -508,8 +509,10 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
 // 24 rotations of one ciphertext at N = 2^14, 12 limbs: 187 -> 162 us against inner products and a division as separate
 // launches with the accumulators in memory between them.
 #define IP_CAP 5.5f
-template <int K3, int MODE, bool STEPS>
-__device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs& g, int n_tasks, double* lds_all) {
+struct OneStep {};
+template <int K3, int MODE, class S>
+__device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs& g, const S& s, int n_tasks, double* lds_all) {
+    constexpr bool STEPS = !std::is_same<S, OneStep>::value;
     const int per = (n_tasks + 7) >> 3;
     const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     if (task >= n_tasks) return;
@@ -524,10 +527,14 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     const Modulus q = modulus(a.fprimes, prime);
     constexpr u64 n = (u64)1 << (10 + K3);
     const uint32_t lane8 = (uint32_t)lane * 8u;
-    const uint32_t step = STEPS ? (uint32_t)b / g.step_B : 0u;
-    const u64 ct = STEPS ? (uint32_t)b - step * g.step_B : b;
-    const u64 galois = STEPS ? (u64)g.steps.galois[step] : g.galois;
-    const u64* key = STEPS ? g.steps.key[step] : g.key;
+    u64 ct = b, galois = g.galois;
+    const u64* key = g.key;
+    if constexpr (STEPS) {
+        const uint32_t step = (uint32_t)b / s.step_B;
+        ct = (uint32_t)b - step * s.step_B;
+        galois = s.steps.galois[step];
+        key = s.steps.key[step];
+    }
     double sum[16];
 #pragma unroll
     for (int r = 0; r < 16; r++) sum[r] = 0.0;
@@ -829,9 +836,7 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a)
 // ---------------------------------------------------------------------------
 // MODE (enum FpMode) names the stage a launch belongs to, so that a profile tells the ModUp's columns from the ModDown's;
 // COLUMNS: the launch in which all target limbs of a digit share one pass over its sources, else the rows.
-constexpr bool fp_steps(int mode) { return mode == FP_STEPS_TO_Y || mode == FP_STEPS_SUB; }
-constexpr bool fp_inner(int mode) { return mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB || fp_steps(mode); }
-constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : fp_inner(mode) ? 128 : ROWS_NT; }
+constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : (mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB) ? 128 : ROWS_NT; }
 
 template <int K3, int MODE, bool COLUMNS>
 __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), 4) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
@@ -841,10 +846,16 @@ __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), 4) void ntt_fp_kernel(Co
     } else {
         __shared__ double lds[fp_threads(MODE, false) / 64 * ROW_LDS];
         if constexpr (MODE == FP_INV_TO_Y) rows_inverse<K3>(a, n_tasks, lds);
-        else if constexpr (fp_inner(MODE))
-            rows_inner<K3, MODE == FP_INV_D_TO_Y || MODE == FP_STEPS_TO_Y ? FP_INV_D_TO_Y : FP_FWD_CONV_SUB, fp_steps(MODE)>(a, g, n_tasks, lds);
+        else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE>(a, g, OneStep{}, n_tasks, lds);
         else rows_forward<K3, MODE>(a, n_tasks, lds);
     }
+}
+
+// the inner products' rows for several rotations of the same digits
+template <int K3, int MODE>
+__global__ __launch_bounds__(128, 4) void inner_product_steps_rows_kernel(ConvertArgs a, InnerArgs g, StepArgs s, int n_tasks) {
+    __shared__ double lds[2 * ROW_LDS];
+    rows_inner<K3, MODE>(a, g, s, n_tasks, lds);
 }
 
 // Twiddles of one prime for the three kernels, psi^(sign bitrev(i)) as the caller's w(i) gives them (centred doubles):
@@ -896,6 +907,24 @@ static hipError_t launch_rows(const ConvertArgs& a, const InnerArgs& g, u64 limb
         case 14: return launch_one<4, MODE, false>(grid, threads, 0, a, g, tasks, st);
         default: return launch_one<5, MODE, false>(grid, threads, 0, a, g, tasks, st);
     }
+}
+
+template <int MODE>
+static hipError_t launch_step_rows(const ConvertArgs& a, const InnerArgs& g, const StepArgs& s, u64 limbs, hipStream_t st) {
+    const u64 tasks = (limbs * a.n_entries) << (a.log_n - 10);
+    if (tasks > 0x7fffff00u) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)((tasks + 7) / 8 * 8));
+    ProfScope prof__("inner_product_steps_rows_kernel", st);
+#define STEPS_CASE(K3)                                                                                                           \
+    case 10 + K3:                                                                                                                \
+        hipLaunchKernelGGL((inner_product_steps_rows_kernel<K3, MODE>), grid, dim3(128), 0, st, a, g, s, (int)tasks);            \
+        break;
+    switch (a.log_n) {
+        STEPS_CASE(2) STEPS_CASE(3) STEPS_CASE(4) STEPS_CASE(5)
+        default: return hipErrorInvalidValue;
+    }
+#undef STEPS_CASE
+    return hipGetLastError();
 }
 
 template <int K3, int MODE>
@@ -986,29 +1015,28 @@ hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st
     }
 }
 
-hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, hipStream_t st) {
+hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, const StepArgs* steps, hipStream_t st) {
     DRY_RUN_RETURN();
     if (a.n_entries == 0) return hipSuccess;
     u64 targets = 0;
     if (!convert_args_ok(a, &targets)) return hipErrorInvalidValue;
     const u64 n = (u64)1 << a.log_n;
-    const bool steps = fp_steps(mode);
     if (steps) {        // every entry belongs to a rotation with its key and Galois element
-        if (g.step_B < 1 || a.n_entries % g.step_B || a.n_entries / g.step_B > FP_MAX_STEPS) return hipErrorInvalidValue;
-        for (unsigned s = 0; s < a.n_entries / g.step_B; s++)
-            if (!g.steps.key[s] || g.steps.galois[s] == 0) return hipErrorInvalidValue;
+        if (steps->step_B < 1 || a.n_entries % steps->step_B || a.n_entries / steps->step_B > FP_MAX_STEPS) return hipErrorInvalidValue;
+        for (unsigned s = 0; s < a.n_entries / steps->step_B; s++)
+            if (!steps->steps.key[s] || steps->steps.galois[s] == 0) return hipErrorInvalidValue;
     }
     if ((!steps && !g.key) || !g.own || !g.c1 || g.n_acc < 1 || g.n_acc >= a.ext_limbs || g.n_acc > a.l) return hipErrorInvalidValue;
     if (g.x_begin < 0 || g.x_begin >= g.x_end || g.x_end > a.ext_limbs) return hipErrorInvalidValue;
     if (g.own_bs < (u64)a.l * n || g.add_polys < 0 || g.add_polys > 2 || (g.add_polys && !g.add)) return hipErrorInvalidValue;
     if (g.add_polys && (g.add_bs < (u64)g.add_polys * a.l * n || (g.add_polys > 1 && g.add_ps < (u64)a.l * n))) return hipErrorInvalidValue;
     const u64 limbs = (u64)(g.x_end - g.x_begin);
-    if (mode == FP_INV_D_TO_Y || mode == FP_STEPS_TO_Y) {
+    if (mode == FP_INV_D_TO_Y) {
         if ((g.x_begin < g.n_acc && !g.acc) || (g.x_end > g.n_acc && !g.down)) return hipErrorInvalidValue;
-        return steps ? launch_rows<FP_STEPS_TO_Y>(a, g, limbs, st) : launch_rows<FP_INV_D_TO_Y>(a, g, limbs, st);
+        return steps ? launch_step_rows<FP_INV_D_TO_Y>(a, g, *steps, limbs, st) : launch_rows<FP_INV_D_TO_Y>(a, g, limbs, st);
     }
-    if ((mode != FP_FWD_CONV_SUB && mode != FP_STEPS_SUB) || g.x_end > g.n_acc || !g.out) return hipErrorInvalidValue;
-    return steps ? launch_rows<FP_STEPS_SUB>(a, g, limbs, st) : launch_rows<FP_FWD_CONV_SUB>(a, g, limbs, st);
+    if (mode != FP_FWD_CONV_SUB || g.x_end > g.n_acc || !g.out) return hipErrorInvalidValue;
+    return steps ? launch_step_rows<FP_FWD_CONV_SUB>(a, g, *steps, limbs, st) : launch_rows<FP_FWD_CONV_SUB>(a, g, limbs, st);
 }
 
 // ---- whole polynomials ----

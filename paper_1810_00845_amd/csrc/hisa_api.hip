@@ -1731,13 +1731,13 @@ extern "C" int hisa_rot_left_sum_batch(hisa_ctx* ctx, const hisa_ct* const* in, 
 // C, D and E: the inner products of `entries` key switches on the digits that c names, and the division by P.
 // g.acc != null ([entries][2][l][N] doubles): the limbs of q are summed in launch C too and E only subtracts -- the shorter
 // chain of launches where they do not fill the chip.
-static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, int l, size_t entries, u64* out) {
+static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, const StepArgs* steps, int l, size_t entries, u64* out) {
     const size_t n = ctx->N;
     const int K = (int)ctx->K;
     g.n_acc = l;
     g.x_begin = g.acc ? 0 : l; g.x_end = l + K;
     c.n_entries = (unsigned)entries;
-    HIP_TRY(ctx, launch_inner_rows_fp(g.step_B ? FP_STEPS_TO_Y : FP_INV_D_TO_Y, c, g, ctx->stream));
+    HIP_TRY(ctx, launch_inner_rows_fp(FP_INV_D_TO_Y, c, g, steps, ctx->stream));
     ConvertArgs m = convert_base(ctx, l, entries * 2);      // entries are (ciphertext, b|a) pairs
     m.src_pos0 = l; m.n_src = K; m.mid = g.down;
     m.n_digits = 1; m.dg[0] = {ctx->d_moddown_hat_pin, 0, K, 0, 0, 0}; m.ext_limbs = l; m.out = out; m.out_bs = (u64)l * n;
@@ -1747,7 +1747,7 @@ static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, int
         HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_SUB, m, ctx->stream));
     } else {
         g.out = out; g.x_begin = 0; g.x_end = l;
-        HIP_TRY(ctx, launch_inner_rows_fp(g.step_B ? FP_STEPS_SUB : FP_FWD_CONV_SUB, c, g, ctx->stream));
+        HIP_TRY(ctx, launch_inner_rows_fp(FP_FWD_CONV_SUB, c, g, steps, ctx->stream));
     }
     return HISA_OK;
 }
@@ -1769,7 +1769,7 @@ static int key_switch_fused_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois
     g.key = key.data; g.own = d; g.own_bs = d_bs; g.galois = galois; g.c1 = c1;
     g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = add ? add_polys : 0;
     g.acc = acc; g.down = down;
-    return key_switch_divide_fp(ctx, c, g, l, B, out);
+    return key_switch_divide_fp(ctx, c, g, nullptr, l, B, out);
 }
 
 // Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic
@@ -1798,9 +1798,10 @@ static int key_switch_finish_steps_fp(hisa_ctx* ctx, const FpExt& x, const u64* 
     g.own = d; g.own_bs = d_bs; g.c1 = c1;
     g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = 1;
     g.acc = stored ? acc.as<double>() : nullptr; g.down = down.as<double>();
-    g.step_B = (unsigned)B;
-    for (int s = 0; s < n_steps; s++) { g.steps.key[s] = keys[s]->data; g.steps.galois[s] = (uint32_t)galois[s]; }
-    return key_switch_divide_fp(ctx, c, g, l, E, out);
+    StepArgs st = {};
+    st.step_B = (unsigned)B;
+    for (int s = 0; s < n_steps; s++) { st.steps.key[s] = keys[s]->data; st.steps.galois[s] = (uint32_t)galois[s]; }
+    return key_switch_divide_fp(ctx, c, g, &st, l, E, out);
 }
 
 static int key_switch_core_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key,

@@ -284,8 +284,6 @@ enum FpMode {
     FP_INV_D_TO_Y = 5,     // rows: forward levels of the digits, key inner product, inverse levels of the division's sources
     FP_FWD_CONV_SUB = 6,   // columns: the division's conversion; rows: key inner product minus the division's transform
     FP_FWD_SUB = 7,        // rows: stored accumulators minus the division's transform (small calls)
-    FP_STEPS_TO_Y = 8,     // 5 for several rotations of the same extended digits, whose rows are transformed already
-    FP_STEPS_SUB = 9,      // the rows of 6 for such rotations
 };
 
 struct FpTask {
@@ -372,9 +370,9 @@ hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st
 // acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend * c2[x]), lazily reduced doubles for FP_FWD_SUB.
 // FP_FWD_CONV_SUB (limbs below n_acc): out holds the division's columns and receives its result.
 // Own digits and addend are read through sigma_g.
-// FP_STEPS_TO_Y and FP_STEPS_SUB: several rotations of the same step_B ciphertexts, entry b being rotation b / step_B of
-// ciphertext b % step_B.  ConvertArgs::out, own and add then hold step_B entries, out fully transformed, normalised digits, and
-// all three are read through the rotation's Galois element; sums and results are rotation-major.
+// With StepArgs: several rotations of the same step_B ciphertexts, entry b being rotation b / step_B of ciphertext b % step_B.
+// ConvertArgs::out, own and add then hold step_B entries, out fully transformed, normalised digits, and all three are read through
+// the rotation's Galois element (key and galois of InnerArgs are not used); sums and results are rotation-major.
 struct IpSteps {
     const u64* key[FP_MAX_STEPS];
     uint32_t galois[FP_MAX_STEPS];
@@ -389,10 +387,12 @@ struct InnerArgs {
     double* acc;
     u64* out;
     double* down;
+};
+struct StepArgs {
     unsigned step_B;
     IpSteps steps;
 };
-hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, hipStream_t st);
+hipError_t launch_inner_rows_fp(int mode, const ConvertArgs& a, const InnerArgs& g, const StepArgs* steps, hipStream_t st);
 
 // ---- the same division of work in 64-bit integers (convert_int.hip): any ring degree, primes up to 60 bits, any number of
 // digits.  Digit d converts sources d * alpha .. (at most n_src) to every limb 0 .. ext_limbs - 1 (with `own`: outside its
