@@ -175,7 +175,17 @@ void* pinned_block(hisa_ctx* ctx, size_t bytes);
 // slot values in pinned memory, [n_pts][count] -> plaintexts out [n_pts][limbs][N]; im may be null
 int encode_dense(hisa_ctx* ctx, const double* re, const double* im, int count, int n_pts, double scale, int limbs, u64* out);
 // plaintexts [n_pts][limbs][N] (device) -> the first `count` slots, complex z [n_pts][count] in pinned memory; waits
+// (n_pts: at most what client_group allows)
 int decode_dense(hisa_ctx* ctx, const u64* pts, int n_pts, int limbs, double scale, int count, double* z);
+
+// Coefficients of a set of transforms up to which the two launches over columns and rows are used (ntt.hip)
+#define FEW_COEFFS ((u64)1 << 22)
+// Plaintexts of `limbs` limbs that one set of encode or decode launches takes: FEW_COEFFS coefficients (4096 rows, which
+// fill the chip) bound its scratch to under 100 MB whatever the tensor, and, with N >= 2^10, its grids to 4096 rows of entries.
+inline size_t client_group(const hisa_ctx* ctx, size_t limbs) {
+    const size_t most = (size_t)FEW_COEFFS / (limbs * ctx->N);
+    return most ? most : 1;
+}
 
 struct Temp {  // pooled scratch buffer for the duration of one call
     hisa_ctx* ctx;

@@ -2837,8 +2837,9 @@ extern "C" int hisa_tensor_decrypt(hisa_ctx* ctx, const hisa_tensor* t, double* 
     const std::vector<uint32_t> slots = tensor_slots(t);
     const size_t count = (size_t)*std::max_element(slots.begin(), slots.end()) + 1;
     const uint32_t l = t->cts[0]->limbs, polys = t->cts[0]->polys;
-    // as many ciphertexts of one scale as the pinned memory holds the slots of go through one set of launches and one wait
-    const size_t most = std::max<size_t>(1, PIN_BYTES / 2 / (2 * count * sizeof(double)));
+    // as many ciphertexts of one scale as the pinned memory holds the slots of, and one set of launches takes, go through
+    // with one wait
+    const size_t most = std::max<size_t>(1, std::min(client_group(ctx, l), PIN_BYTES / 2 / (2 * count * sizeof(double))));
     for (size_t i = 0; i < nct;) {
         size_t cnt = 1;
         while (i + cnt < nct && cnt < most && t->cts[i + cnt]->scale == t->cts[i]->scale) cnt++;

@@ -43,7 +43,7 @@ static FpArgs fp_base_args(const NttTables& t) {
 
 // By columns and rows up to about the number of polynomials the single-launch transform keeps resident: it takes as long
 // for one as for that many.
-static bool few_polynomials(int log_n, u64 polys) { return (polys << log_n) <= ((u64)1 << 22); }
+static bool few_polynomials(int log_n, u64 polys) { return (polys << log_n) <= FEW_COEFFS; }
 
 static hipError_t transform_fp(int mode, int log_n, const FpArgs& a, const FpTask& tk, u64 n_batch, hipStream_t st) {
     return few_polynomials(log_n, n_batch * (u64)tk.period) ? launch_ntt_fp_split(mode, log_n, a, tk, n_batch, st)
@@ -72,6 +72,7 @@ hipError_t launch_ntt_i64(const NttTables& t, int log_n, const i64* coeffs, u64*
     return e == hipSuccess ? launch_ntt(t, log_n, out, (u64)limbs << log_n, n_pts * limbs, map, st) : e;
 }
 
+// (in the form for few polynomials: what is decoded comes in groups below that line)
 hipError_t launch_intt_centred(const NttTables& t, int log_n, const u64* in, double* out, int limbs, int n_pts, hipStream_t st) {
     DRY_RUN_RETURN();
     FpTask tk;

@@ -57,3 +57,33 @@ def test_round_trip(log_n, q_bits, special, vectors, count):
     for i in sorted({0, vectors - 1}):
         assert np.abs(g.decode(g.decrypt(cts[i]), count) - x[i]).max() < 1e-1
     g.close()
+
+
+@pytest.mark.parametrize("log_n,q_bits,special,batch,side", [
+    (12, [50], 50, 65537, 1),                    # more ciphertexts than a grid has rows of entries
+    (13, [50] + [40] * 7, 50, 1000, 2),          # sixteen groups, the last one ragged
+    (13, [58] * 8, 60, 130, 2),                  # integer arithmetic, two full groups and two ciphertexts
+])
+def test_tensor_decrypt_in_groups(log_n, q_bits, special, batch, side):
+    """Tensors of many ciphertexts of a few slots each, made of three ciphertexts used over and over: every image equals its
+    ciphertext's, and the scratch memory does not grow with the tensor."""
+    import torch
+    from paper_1810_00845_amd import hisa
+    print("[case] decrypt", log_n, len(q_bits), batch, side, flush=True)
+    g = hisa.Context(log_n, q_bits, 1, special, 5)
+    g.keygen()
+    x = np.random.default_rng(batch).uniform(-1, 1, (3, 1, side, side))
+    three = g.tensor_encrypt(x, 2.0 ** 30, len(q_bits))
+    want = g.tensor_decrypt(three)
+    assert np.abs(want - x).max() < 1e-4         # fresh noise: 3.2 sqrt(N) / scale a slot, 30 times that
+    many = hisa.CipherTensor(g, [three.cts[i % 3] for i in range(batch)], batch, 1, side, side, three.h_stride, three.w_stride,
+                             three.offset, 1, three.c_inner, three.c_stride)
+    g.sync()
+    free = torch.cuda.mem_get_info()[0]
+    got = g.tensor_decrypt(many)
+    grown = free - torch.cuda.mem_get_info()[0]
+    assert np.array_equal(got, want[np.arange(batch) % 3])
+    # plaintexts and coefficient forms of 2^22 coefficients, the lifted values and the transform's work: 32 MB each, and a
+    # copy of the group's ciphertexts side by side, 64 MB; a ragged last group takes blocks of its own size
+    assert grown <= 2 * (4 * 32 + 64) << 20, grown
+    g.close()
