@@ -2812,7 +2812,11 @@ extern "C" int hisa_tensor_encrypt(hisa_ctx* ctx, const double* x, double scale,
         memset(dense, 0, nct * top * sizeof(double));
         for (size_t i = 0; i < nct; i++)
             for (size_t k = 0; k < slots.size(); k++) dense[i * top + slots[k]] = values[i * slots.size() + k];
-        rc = encode_dense(ctx, dense, nullptr, (int)top, (int)nct, scale, (int)limbs, (u64*)blk->ptr);
+        const size_t group = client_group(ctx, limbs);
+        rc = HISA_OK;
+        for (size_t i = 0; i < nct && rc == HISA_OK; i += group)
+            rc = encode_dense(ctx, dense + i * top, nullptr, (int)top, (int)std::min(group, nct - i), scale, (int)limbs,
+                              (u64*)blk->ptr + i * limbs * n);
     } else {
         rc = encode_sparse_batch(ctx, slots, values, nct, scale, (int)limbs, (u64*)blk->ptr);
     }

@@ -87,3 +87,25 @@ def test_tensor_decrypt_in_groups(log_n, q_bits, special, batch, side):
     # copy of the group's ciphertexts side by side, 64 MB; a ragged last group takes blocks of its own size
     assert grown <= 2 * (4 * 32 + 64) << 20, grown
     g.close()
+
+
+@pytest.mark.parametrize("log_n,q_bits,special,batch,height,width", [
+    (12, [50], 50, 65537, 1, 1),                 # more ciphertexts than a grid has rows of entries
+    (13, [50] + [40] * 7, 50, 150, 2, 3),        # three groups, the last one ragged
+    (11, [58, 50], 60, 64, 16, 64),              # integer arithmetic
+    (12, [50], 50, 64, 32, 64),                  # 2^17 slot values: the most that are laid out in pinned memory
+    (12, [50], 50, 65, 32, 64),                  # one ciphertext more: values scattered on the device
+])
+def test_tensor_encrypt_in_groups(log_n, q_bits, special, batch, height, width):
+    """Every image of a tensor decrypts to itself, on both sides of the lines between one group of plaintexts and several and
+    between slot vectors laid out on the host and on the device."""
+    from paper_1810_00845_amd import hisa
+    print("[case] encrypt", log_n, len(q_bits), batch, height, width, flush=True)
+    g = hisa.Context(log_n, q_bits, 1, special, 5)
+    g.keygen()
+    x = np.random.default_rng(batch).uniform(-1, 1, (batch, 1, height, width))
+    got = g.tensor_decrypt(g.tensor_encrypt(x, 2.0 ** 30, len(q_bits)))
+    # a slot's noise is a sum of N coefficients of 3.2 and of N roundings: 3.3 sqrt(N) / scale = 2.8e-7 at most, of 65537
+    # slots the largest below seven times that
+    assert np.abs(got - x).max() < 2e-6
+    g.close()
