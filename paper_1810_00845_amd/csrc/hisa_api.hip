@@ -541,27 +541,26 @@ extern "C" int hisa_create(const hisa_params* prm, void* hip_stream, hisa_ctx** 
         for (uint32_t m = 0; m < ctx->K; m++) src.push_back((int)(ctx->L + m));
         ctx->moddown_tab = new ConvTable();
         TRY(make_conv_table(ctx, src, ctx->moddown_tab));
-        std::vector<u64> pinv(ctx->L), pinv_sh(ctx->L), pmod(ctx->total, 0);
+        std::vector<u64> pmod(ctx->total, 0);
+        ctx->pinv.resize(ctx->L);
         for (uint32_t i = 0; i < ctx->total; i++) {
             const u64 q = ctx->mod[i];
             u64 pm = 1 % q;
             for (uint32_t m = 0; m < ctx->K; m++) pm = hm::mul(pm, ctx->mod[ctx->L + m] % q, q);
             pmod[i] = pm;
-            if (i < ctx->L) { pinv[i] = hm::inv(pm, q); pinv_sh[i] = hm::shoup(pinv[i], q); }
+            if (i < ctx->L) ctx->pinv[i] = hm::inv(pm, q);
         }
-        HIP_TRY(ctx, upload(&ctx->d_pinv, pinv));
-        HIP_TRY(ctx, upload(&ctx->d_pinv_sh, pinv_sh));
         HIP_TRY(ctx, upload(&ctx->d_pmod, pmod));
         if (ctx->tabs.fp_ok) {
             std::vector<double> pf(ctx->total, 0.0);
-            for (uint32_t i = 0; i < ctx->L; i++) pf[i] = centred_double(pinv[i], ctx->mod[i]);
+            for (uint32_t i = 0; i < ctx->L; i++) pf[i] = centred_double(ctx->pinv[i], ctx->mod[i]);
             HIP_TRY(ctx, upload(&ctx->d_pinv_f, pf));
             {   // (P/p_m) P^-1 mod q_i: the conversion of the folded ModDown
                 const std::vector<u64>& hat = ctx->moddown_tab->hat;
                 std::vector<double> hp((size_t)ctx->K * ctx->total, 0.0);
                 for (uint32_t m = 0; m < ctx->K; m++)
                     for (uint32_t i = 0; i < ctx->L; i++)
-                        hp[(size_t)m * ctx->total + i] = centred_double(hm::mul(hat[(size_t)m * ctx->total + i], pinv[i], ctx->mod[i]), ctx->mod[i]);
+                        hp[(size_t)m * ctx->total + i] = centred_double(hm::mul(hat[(size_t)m * ctx->total + i], ctx->pinv[i], ctx->mod[i]), ctx->mod[i]);
                 HIP_TRY(ctx, upload(&ctx->d_moddown_hat_pin, hp));
             }
         }
@@ -624,7 +623,7 @@ extern "C" int hisa_destroy(hisa_ctx* ctx) {
     for (auto& kv : ctx->modup_tabs) free_conv_table(&kv.second);
     if (ctx->moddown_tab) { free_conv_table(ctx->moddown_tab); delete ctx->moddown_tab; }
     (void)hipFree(ctx->d_primes); (void)hipFree(ctx->d_tw); (void)hipFree(ctx->d_tw_sh); (void)hipFree(ctx->d_itw);
-    (void)hipFree(ctx->d_itw_sh); (void)hipFree(ctx->d_secret); (void)hipFree(ctx->d_pinv); (void)hipFree(ctx->d_pinv_sh);
+    (void)hipFree(ctx->d_itw_sh); (void)hipFree(ctx->d_secret);
     (void)hipFree(ctx->d_fprimes); (void)hipFree(ctx->d_ftw); (void)hipFree(ctx->d_utw); (void)hipFree(ctx->d_vtw);
     (void)hipFree(ctx->d_sfwd); (void)hipFree(ctx->d_sinv);
     (void)hipFree(ctx->d_pinv_f); (void)hipFree(ctx->d_moddown_hat_pin);
@@ -1263,15 +1262,17 @@ extern "C" int hisa_mul_no_relin(hisa_ctx* ctx, const hisa_ct* a, const hisa_ct*
 // hybrid key switching
 // ---------------------------------------------------------------------------
 // Conversion tables of the integer kernels (layout: IntArgs), one allocation: the digits of level l at 2^15 + l, the division
-// by P at 2^16, the rescale of level l at 2^17 + l
+// by P at 2^16, the rescale of level l at 2^17 + l.  factor(i), i < n_factor: asked for only where the table is made, so that
+// a call that finds it does no modular inversions (8 limbs of 58 bits: 5 us of host time before the first launch).
 struct IntTables { const u64 *close, *hat, *off, *factor, *factor_sh; };
 static u64 pack30(u64 x) { return ((x >> 30) << 32) | (x & 0x3fffffff); }
 
-static int int_tables(hisa_ctx* ctx, u64 key, int src_prime0, int n_src, int alpha, const std::vector<u64>& factor, IntTables* out) {
+template <class F>
+static int int_tables(hisa_ctx* ctx, u64 key, int src_prime0, int n_src, int alpha, size_t n_factor, F factor, IntTables* out) {
     const size_t total = ctx->total, digits = (n_src + alpha - 1) / alpha;
     auto it = ctx->aux.find(key);
     if (it == ctx->aux.end()) {
-        std::vector<u64> close, hat, off(digits * total, 0), fac, fac_sh;
+        std::vector<u64> t, hat, off(digits * total, 0), fac, fac_sh;
         for (size_t j = 0; j < digits; j++) {
             std::vector<int> src;
             for (int i = (int)j * alpha; i < n_src && i < (int)(j + 1) * alpha; i++) src.push_back(src_prime0 + i);
@@ -1280,28 +1281,30 @@ static int int_tables(hisa_ctx* ctx, u64 key, int src_prime0, int n_src, int alp
             for (size_t i = 0; i < src.size(); i++) {
                 const u64 c = ctx->mod[src[i]], f = hm::mul(ctx->pc[src[i]].n_inv, ih[i], c);
                 for (u64 v : {f, hm::mul(f, ctx->last_itw[src[i]], c)}) {
-                    close.push_back(v);
-                    close.push_back(hm::shoup(v, c));
+                    t.push_back(v);
+                    t.push_back(hm::shoup(v, c));
                 }
-                for (size_t t = 0; t < total; t++) {
-                    const u64 q = ctx->mod[t], v = h[i * total + t];
+                for (size_t m = 0; m < total; m++) {
+                    const u64 q = ctx->mod[m], v = h[i * total + m];
                     hat.push_back(pack30(v));
-                    off[j * total + t] = (off[j * total + t] + q - hm::mul(v, (c / 2) % q, q)) % q;
+                    off[j * total + m] = (off[j * total + m] + q - hm::mul(v, (c / 2) % q, q)) % q;
                 }
             }
         }
-        for (size_t i = 0; i < factor.size(); i++) fac_sh.push_back(hm::shoup(factor[i], ctx->mod[i]));
-        fac = close;
-        for (const std::vector<u64>* v : std::initializer_list<const std::vector<u64>*>{&hat, &off, &factor, &fac_sh}) fac.insert(fac.end(), v->begin(), v->end());
+        for (size_t i = 0; i < n_factor; i++) {
+            fac.push_back(factor(i));
+            fac_sh.push_back(hm::shoup(fac[i], ctx->mod[i]));
+        }
+        for (const std::vector<u64>* v : {&hat, &off, &fac, &fac_sh}) t.insert(t.end(), v->begin(), v->end());
         u64* d = nullptr;
-        HIP_TRY(ctx, upload(&d, fac));
-        it = ctx->aux.emplace(key, SwitchKey{new DevBlock{d, fac.size() * sizeof(u64), 1}, d}).first;
+        HIP_TRY(ctx, upload(&d, t));
+        it = ctx->aux.emplace(key, SwitchKey{new DevBlock{d, t.size() * sizeof(u64), 1}, d}).first;
     }
     out->close = it->second.data;
     out->hat = out->close + 4 * (size_t)n_src;
     out->off = out->hat + (size_t)n_src * total;
     out->factor = out->off + digits * total;
-    out->factor_sh = out->factor + factor.size();
+    out->factor_sh = out->factor + n_factor;
     return HISA_OK;
 }
 
@@ -1321,14 +1324,9 @@ static int key_switch_core_int(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois
     const size_t n = ctx->N;
     const int K = (int)ctx->K, alpha = (int)ctx->alpha, ext_limbs = l + K, digits = (l + alpha - 1) / alpha;
     IntTables up, down;
-    TRY(int_tables(ctx, ((u64)1 << 15) + (u64)l, 0, l, alpha, {}, &up));
-    std::vector<u64> pinv;
-    for (uint32_t i = 0; i < ctx->L; i++) {
-        u64 p = 1;
-        for (int m = 0; m < K; m++) p = hm::mul(p, ctx->mod[ctx->L + m] % ctx->mod[i], ctx->mod[i]);
-        pinv.push_back(hm::inv(p, ctx->mod[i]));
-    }
-    TRY(int_tables(ctx, (u64)1 << 16, (int)ctx->L, K, K, pinv, &down));
+    const auto p_inv = [ctx](size_t i) { return ctx->pinv[i]; };
+    TRY(int_tables(ctx, ((u64)1 << 15) + (u64)l, 0, l, alpha, 0, p_inv, &up));
+    TRY(int_tables(ctx, (u64)1 << 16, (int)ctx->L, K, K, ctx->L, p_inv, &down));
     // the launches take at most 65535 entries, two per polynomial in the division
     const size_t chunk = std::min<size_t>(B, 32767);
     Temp mid(ctx, chunk * l * n * sizeof(u64)), ext(ctx, chunk * (size_t)digits * ext_limbs * n * sizeof(u64));
@@ -2145,10 +2143,9 @@ static int rescale_core_fp(hisa_ctx* ctx, const u64* in, size_t n_bp, int l, u64
 // the same in integers
 static int rescale_core_int(hisa_ctx* ctx, const u64* in, size_t n_bp, int l, u64* out) {
     const size_t nn = ctx->N, chunk = std::min<size_t>(n_bp, 65535);
-    std::vector<u64> qlinv;
-    for (int i = 0; i < l - 1; i++) qlinv.push_back(hm::inv(ctx->mod[l - 1] % ctx->mod[i], ctx->mod[i]));
     IntTables t;
-    TRY(int_tables(ctx, ((u64)1 << 17) + (u64)l, l - 1, 1, 1, qlinv, &t));
+    TRY(int_tables(ctx, ((u64)1 << 17) + (u64)l, l - 1, 1, 1, (size_t)(l - 1),
+                   [&](size_t i) { return hm::inv(ctx->mod[l - 1] % ctx->mod[i], ctx->mod[i]); }, &t));
     Temp mid(ctx, chunk * nn * sizeof(u64));
     if (!mid.ok()) return HISA_ERR_OOM;
     for (size_t b0 = 0; b0 < n_bp; b0 += chunk) {

@@ -121,8 +121,7 @@ struct hisa_ctx {
     std::map<u64, SwitchKey> aux;   // small derived device tables, built on first use
     std::map<std::pair<int, int>, ConvTable> modup_tabs;  // (digit, size)
     ConvTable* moddown_tab;
-    u64* d_pinv;      // [L] P^-1 mod q_i
-    u64* d_pinv_sh;
+    std::vector<u64> pinv;       // [L] P^-1 mod q_i
     u64* d_consts;    // NttTables::consts
     std::vector<u64> last_itw;   // inverse twiddle of the level that pairs the two halves, per prime
     u64* d_pmod;      // [L] P mod q_i

@@ -47,3 +47,26 @@ def test_key_switch_and_rescale(log_n, q_bits, dnum, special, l, batch):
         assert np.array_equal(g.ct_export(out[i]), o.export(o.rot_left(ref[i], 3)))
         assert np.array_equal(g.ct_export(prod[i]), o.export(o.rescale(o.mul(ref[i], ref[i]))))
     g.close()
+
+
+def test_tables_of_every_level_made_once_and_found_again():
+    """Rotation, relinearisation and rescale at every level, downwards and again upwards: the first call at a level makes its
+    tables, the later ones find them."""
+    from oracle import Oracle
+    from paper_1810_00845_amd import hisa, synth
+    print("[case] levels of N = 2^11, 5 limbs, dnum 2", flush=True)
+    args = (11, [60, 59, 58, 57, 56], 2, 60, 5)
+    g, o = hisa.Context(*args), Oracle(*args)
+    g.keygen(); o.keygen()
+    g.gen_rot_keys([3]); o.gen_rot_keys([3])
+    for l in (5, 4, 3, 2, 1, 2, 3, 4, 5):
+        coeff = synth.uniform_residues(l, (1, 2, l, g.N), g.primes[:l])
+        ct, ref = g.ct_import_batch(coeff, 2.0 ** 50)[0], o.import_ct(coeff[0], 2.0 ** 50)
+        assert np.array_equal(g.ct_export(g.rot_left(ct, 3)), o.export(o.rot_left(ref, 3)))
+        prod, want = g.mul_no_relin(ct, ct), o.mul(ref, ref)
+        g.relinearize(prod)
+        assert np.array_equal(g.ct_export(prod), o.export(want))
+        if l > 1:
+            g.rescale(prod)
+            assert np.array_equal(g.ct_export(prod), o.export(o.rescale(want)))
+    g.close()
