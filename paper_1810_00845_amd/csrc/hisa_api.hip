@@ -234,26 +234,24 @@ void dev_release(hisa_ctx* ctx, DevBlock* b) {
 
 
 
-void* pinned_block(hisa_ctx* ctx, size_t bytes) {
+int pinned_block(hisa_ctx* ctx, size_t bytes, double** out) {
     bytes = (bytes + 255) & ~(size_t)255;
-    if (bytes > PIN_BYTES) return nullptr;
+    if (bytes > PIN_BYTES) return fail(ctx, HISA_ERR_OOM, "%zu bytes of pinned host memory asked for", bytes);
     if (!ctx->pin) {
         if (hipHostMalloc((void**)&ctx->pin, PIN_BYTES, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             ctx->pin = nullptr;
-            fail(ctx, HISA_ERR_OOM, "no pinned host memory");
-            return nullptr;
+            return fail(ctx, HISA_ERR_OOM, "no pinned host memory");
         }
-        ctx->pin_bytes = PIN_BYTES;
         ctx->pin_pos = 0;
     }
-    if (ctx->pin_pos + bytes > ctx->pin_bytes) {
-        if (hipStreamSynchronize(ctx->stream) != hipSuccess) return nullptr;
+    if (ctx->pin_pos + bytes > PIN_BYTES) {
+        HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
         ctx->pin_pos = 0;
     }
-    void* p = ctx->pin + ctx->pin_pos;
+    *out = (double*)(ctx->pin + ctx->pin_pos);
     ctx->pin_pos += bytes;
-    return p;
+    return HISA_OK;
 }
 
 // n ciphertext handles that are views of one allocation, [n][polys][limbs][N]
@@ -816,8 +814,8 @@ extern "C" int hisa_encode(hisa_ctx* ctx, const double* re, const double* im, si
     if (!ctx || !out || (!re && count) || limbs < 1 || limbs > ctx->L || count > ctx->N / 2 || !(scale > 0))
         return fail(ctx, HISA_ERR_ARG, "bad argument");
     // coefficients must fit a signed 64-bit integer: |m_k| <= scale * max|z| * ~1
-    double* v = (double*)pinned_block(ctx, (im ? 2 : 1) * count * sizeof(double));
-    if (!v) return HISA_ERR_OOM;
+    double* v;
+    TRY(pinned_block(ctx, (im ? 2 : 1) * count * sizeof(double), &v));
     if (count) memcpy(v, re, count * sizeof(double));
     if (im && count) memcpy(v + count, im, count * sizeof(double));
     TRY(alloc_pt(ctx, limbs, scale, out));
@@ -910,9 +908,9 @@ int decode_dense(hisa_ctx* ctx, const u64* pts, int n_pts, int limbs, double sca
 
 extern "C" int hisa_decode(hisa_ctx* ctx, const hisa_pt* pt, double* re, double* im, size_t count) {
     if (!ctx || !valid_pt(pt) || !re || count > ctx->N / 2) return fail(ctx, HISA_ERR_ARG, "bad argument");
-    const double* z = (const double*)pinned_block(ctx, 2 * count * sizeof(double));
-    if (!z) return HISA_ERR_OOM;
-    TRY(decode_dense(ctx, pt->data, 1, (int)pt->limbs, pt->scale, (int)count, (double*)z));
+    double* z;
+    TRY(pinned_block(ctx, 2 * count * sizeof(double), &z));
+    TRY(decode_dense(ctx, pt->data, 1, (int)pt->limbs, pt->scale, (int)count, z));
     for (size_t j = 0; j < count; j++) re[j] = z[2 * j];
     if (im)
         for (size_t j = 0; j < count; j++) im[j] = z[2 * j + 1];
@@ -921,9 +919,9 @@ extern "C" int hisa_decode(hisa_ctx* ctx, const hisa_pt* pt, double* re, double*
 
 extern "C" int hisa_decode_complex(hisa_ctx* ctx, const hisa_pt* pt, double* values, size_t count) {
     if (!ctx || !valid_pt(pt) || !values || count > ctx->N / 2) return fail(ctx, HISA_ERR_ARG, "bad argument");
-    const void* z = pinned_block(ctx, 2 * count * sizeof(double));
-    if (!z) return HISA_ERR_OOM;
-    TRY(decode_dense(ctx, pt->data, 1, (int)pt->limbs, pt->scale, (int)count, (double*)z));
+    double* z;
+    TRY(pinned_block(ctx, 2 * count * sizeof(double), &z));
+    TRY(decode_dense(ctx, pt->data, 1, (int)pt->limbs, pt->scale, (int)count, z));
     memcpy(values, z, 2 * count * sizeof(double));
     return HISA_OK;
 }

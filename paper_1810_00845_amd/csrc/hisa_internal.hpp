@@ -135,7 +135,7 @@ struct hisa_ctx {
     double* d_moddown_hat_pin = nullptr;   // [K][total] (P/p_m) * P^-1 mod q_i, centred: ModDown's conversion with the division folded in
     double* d_sfft_tw = nullptr;           // [N/2] complex: stage twiddles of the encode / decode transform
     unsigned char* pin = nullptr;          // pinned host memory that uploads and decoded values pass through (pinned_block)
-    size_t pin_bytes = 0, pin_pos = 0;
+    size_t pin_pos = 0;
     std::unordered_map<size_t, std::vector<void*>> pool;
     size_t pool_bytes;
     std::map<uintptr_t, size_t> live;   // blocks handed out by dev_alloc and not yet back in the pool: start -> bytes
@@ -167,10 +167,11 @@ void dev_release(hisa_ctx* ctx, DevBlock* b);
 // 8-byte words from p to the end of the live pool block that holds p; 0 when no live block does
 u64 dev_words_behind(const hisa_ctx* ctx, const void* p);
 
-// `bytes` of pinned host memory, readable and writable by kernels, valid until later calls have asked for PIN_BYTES more
-// (the memory is a ring: before it is handed out again the stream is waited for); null on failure or beyond PIN_BYTES
+// `bytes` (at most PIN_BYTES) of pinned host memory, readable and writable by kernels.  The host may use it until the next
+// call of this function, kernels enqueued before that call for as long as they run: the memory is a ring, and before it starts
+// over the stream is waited for.  A caller that needs two blocks at a time asks for one of twice the size.
 #define PIN_BYTES ((size_t)4 << 20)
-void* pinned_block(hisa_ctx* ctx, size_t bytes);
+int pinned_block(hisa_ctx* ctx, size_t bytes, double** out);
 // slot values in pinned memory, [n_pts][count] -> plaintexts out [n_pts][limbs][N]; im may be null
 int encode_dense(hisa_ctx* ctx, const double* re, const double* im, int count, int n_pts, double scale, int limbs, u64* out);
 // plaintexts [n_pts][limbs][N] (device) -> the first `count` slots, complex z [n_pts][count] in pinned memory; waits

@@ -2802,12 +2802,14 @@ extern "C" int hisa_tensor_encrypt(hisa_ctx* ctx, const double* x, double scale,
                 memcpy(&packed[((b * per + c / ci) * ci + c % ci) * hw], x + (b * t->channels + c) * hw, hw * sizeof(double));
         values = packed.data();
     }
+    // a few ciphertexts: their slot vectors are laid out in pinned memory (where there is any), from which the first launch of
+    // the encoding reads
+    const size_t top = (size_t)*std::max_element(slots.begin(), slots.end()) + 1;
+    double* dense = nullptr;
+    int rc = nct * top * sizeof(double) <= PIN_BYTES / 4 ? pinned_block(ctx, nct * top * sizeof(double), &dense) : HISA_OK;
+    if (rc != HISA_OK && rc != HISA_ERR_OOM) return rc;
     DevBlock* blk = dev_alloc(ctx, nct * limbs * n * sizeof(u64));
     if (!blk) return HISA_ERR_OOM;
-    // a few ciphertexts: their slot vectors are laid out in pinned memory, from which the first launch of the encoding reads
-    const size_t top = (size_t)*std::max_element(slots.begin(), slots.end()) + 1;
-    double* dense = nct * top * sizeof(double) <= PIN_BYTES / 4 ? (double*)pinned_block(ctx, nct * top * sizeof(double)) : nullptr;
-    int rc;
     if (dense) {
         memset(dense, 0, nct * top * sizeof(double));
         for (size_t i = 0; i < nct; i++)
@@ -2850,8 +2852,8 @@ extern "C" int hisa_tensor_decrypt(hisa_ctx* ctx, const hisa_tensor* t, double* 
         BatchIn bi;
         TRY(gather_batch(ctx, (const hisa_ct* const*)t->cts + i, cnt, &bi));
         Temp pt(ctx, cnt * l * ctx->N * sizeof(u64));
-        double* z = (double*)pinned_block(ctx, cnt * 2 * count * sizeof(double));
-        int rc = pt.ok() && z ? HISA_OK : HISA_ERR_OOM;
+        double* z;
+        int rc = pt.ok() ? pinned_block(ctx, cnt * 2 * count * sizeof(double), &z) : HISA_ERR_OOM;
         if (rc == HISA_OK) {
             hipError_t e = launch_decrypt(ctx->d_primes, ctx->d_secret, bi.base, bi.stride, pt.u(), (int)l, (int)polys, cnt, (int)ctx->log_n,
                                           ctx->stream);

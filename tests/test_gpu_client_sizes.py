@@ -109,3 +109,19 @@ def test_tensor_encrypt_in_groups(log_n, q_bits, special, batch, height, width):
     # slots the largest below seven times that
     assert np.abs(got - x).max() < 2e-6
     g.close()
+
+
+def test_vectors_handed_over_faster_than_they_are_read():
+    """100 vectors of 128 KB, encoded without a wait in between, and decoded at the end: three times round the pinned memory
+    that they pass through."""
+    from paper_1810_00845_amd import hisa
+    print("[case] 100 vectors, N = 2^14", flush=True)
+    g = hisa.Context(14, [50, 40], 1, 50, 5)
+    rng = np.random.default_rng(7)
+    x = rng.uniform(-1, 1, (100, g.slots)) + 1j * rng.uniform(-1, 1, (100, g.slots))
+    pts = [g.encode(v, 2.0 ** 30, 2) for v in x]
+    # a slot's error is a sum of N roundings of at most 1/2: sqrt(N / 12) / scale = 3.5e-8, of 819200 slots the largest below
+    # seven times that
+    for v, pt in zip(x, pts):
+        assert np.abs(g.decode(pt) - v).max() < 2.5e-7
+    g.close()
