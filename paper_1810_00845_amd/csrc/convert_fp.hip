@@ -696,7 +696,7 @@ __device__ __forceinline__ void plain_columns(const FpArgs& a, const FpTask& tk)
 #pragma unroll
             for (int r = 0; r < NR; r++) v[r] = residue_of_i64((i64)c[r], q);
         } else {
-            const rsrc_t src = make_rsrc(a.in + b * a.in_bs + (u64)(tk.pos[e] + a.in_pos_shift) * n, (uint32_t)n * 8u);
+            const rsrc_t src = make_rsrc(a.in + b * a.in_bs + (u64)tk.pos[e] * n, (uint32_t)n * 8u);
             u64 c[NR];
 #pragma unroll
             for (int r = 0; r < NR; r++) c[r] = bload(src, first, column_row<K3, true>(r));
@@ -726,7 +726,7 @@ __device__ __forceinline__ void plain_rows(const FpArgs& a, const FpTask& tk, do
     float m[16];
     RowTwiddles w;
     if (INV) {
-        load_row_through<K3>(v, a.in + b * a.in_bs + (u64)(tk.pos[e] + a.in_pos_shift) * n, a.galois, (uint32_t)row, lane);
+        load_row_through<K3>(v, a.in + b * a.in_bs + (u64)tk.pos[e] * n, 0, (uint32_t)row, lane);
         load_row_twiddles(w, a.sinv, a.table_stride, prime, (uint32_t)row, lane);
 #pragma unroll
         for (int r = 0; r < 16; r++) { v[r] = fp_from_u64((u64)__double_as_longlong(v[r])); m[r] = 1.0f; }

@@ -887,9 +887,7 @@ int decode_dense(hisa_ctx* ctx, const u64* pts, int n_pts, int limbs, double sca
         HIP_TRY(ctx, launch_crt_fp(ctx->d_fprimes, co.as<double>(), limbs, ginv, (int)ctx->L, 1.0 / scale, m.as<double>(), n_pts, log_n,
                                    ctx->stream));
     } else {
-        InttExtra ex = {};
-        ex.in = pts; ex.in_batch_stride = (u64)limbs * n;
-        HIP_TRY(ctx, launch_intt(ctx->tabs, log_n, co.u(), (u64)limbs * n, n_pts * limbs, identity_map(limbs), &ex, ctx->stream));
+        HIP_TRY(ctx, launch_intt(ctx->tabs, log_n, pts, co.u(), (u64)limbs * n, n_pts * limbs, identity_map(limbs), ctx->stream));
         u64 *ginv, *ginv_sh;
         TRY(garner_tables(ctx, &ginv, &ginv_sh));
         HIP_TRY(ctx, launch_crt_to_double(ctx->d_primes, co.u(), limbs, ginv, ginv_sh, (int)ctx->L, 1.0 / scale, m.as<double>(), n_pts,
@@ -931,10 +929,7 @@ extern "C" int hisa_pt_export(hisa_ctx* ctx, const hisa_pt* pt, uint64_t* host) 
     const size_t words = (size_t)pt->limbs * ctx->N;
     Temp co(ctx, words * sizeof(u64));
     if (!co.ok()) return HISA_ERR_OOM;
-    InttExtra ex = {};
-    ex.in = pt->data;
-    HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, co.u(), 0, (int)pt->limbs, identity_map((int)pt->limbs), &ex,
-                             ctx->stream));
+    HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, pt->data, co.u(), 0, (int)pt->limbs, identity_map((int)pt->limbs), ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(host, co.u(), words * sizeof(u64), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return HISA_OK;
@@ -2229,10 +2224,8 @@ extern "C" int hisa_ct_export(hisa_ctx* ctx, const hisa_ct* ct, uint64_t* host) 
     const size_t words = ct_words(ctx, ct->polys, ct->limbs);
     Temp co(ctx, words * sizeof(u64));
     if (!co.ok()) return HISA_ERR_OOM;
-    InttExtra ex = {};
-    ex.in = ct->data; ex.in_batch_stride = (u64)ct->limbs * ctx->N;
-    HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, co.u(), (u64)ct->limbs * ctx->N, (int)(ct->polys * ct->limbs),
-                             identity_map((int)ct->limbs), &ex, ctx->stream));
+    HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, ct->data, co.u(), (u64)ct->limbs * ctx->N, (int)(ct->polys * ct->limbs),
+                             identity_map((int)ct->limbs), ctx->stream));
     HIP_TRY(ctx, hipMemcpyAsync(host, co.u(), words * sizeof(u64), hipMemcpyDeviceToHost, ctx->stream));
     HIP_TRY(ctx, hipStreamSynchronize(ctx->stream));
     return HISA_OK;
@@ -2271,7 +2264,7 @@ extern "C" int hisa_ntt_raw(hisa_ctx* ctx, uint64_t* dev_buf, uint32_t prime_ind
     PolyMap pm = {};
     pm.period = 1;
     pm.prime_of[0] = (int16_t)prime_index;
-    if (inverse) HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, dev_buf, ctx->N, (int)n_polys, pm, nullptr, ctx->stream));
+    if (inverse) HIP_TRY(ctx, launch_intt(ctx->tabs, (int)ctx->log_n, dev_buf, dev_buf, ctx->N, (int)n_polys, pm, ctx->stream));
     else HIP_TRY(ctx, launch_ntt(ctx->tabs, (int)ctx->log_n, dev_buf, ctx->N, (int)n_polys, pm, ctx->stream));
     return HISA_OK;
 }

@@ -57,14 +57,6 @@ struct PolyMap {
     int16_t prime_of[HISA_MAX_PERIOD];
 };
 
-// Optional extras of an inverse transform.
-struct InttExtra {
-    const u64* in;          // read from here instead of data (same PolyMap addressing with in_batch_stride); may be null
-    u64 in_batch_stride;
-    u64 galois;             // != 0: input index i reads the element that sigma_g moves to i (NTT-form automorphism)
-    int out_entry0;         // output polynomial of entry e sits at (e - out_entry0) * N within its batch slot
-};
-
 // One fast base conversion: source primes src[0..a), all primes as targets.
 struct ConvTable {
     int a;
@@ -279,15 +271,16 @@ hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride
 hipError_t launch_ntt_i64(const NttTables& t, int log_n, const i64* coeffs, u64* out, int limbs, int n_pts, hipStream_t st);
 // NTT form [n_pts][limbs][N] -> coefficients as centred doubles (fp64 contexts only)
 hipError_t launch_intt_centred(const NttTables& t, int log_n, const u64* in, double* out, int limbs, int n_pts, hipStream_t st);
-hipError_t launch_intt(const NttTables& t, int log_n, u64* data, u64 batch_stride, int n_polys, const PolyMap& map,
-                       const InttExtra* extra, hipStream_t st);
+// `in` and `out` have the same layout and may be the same
+hipError_t launch_intt(const NttTables& t, int log_n, const u64* in, u64* out, u64 batch_stride, int n_polys, const PolyMap& map,
+                       hipStream_t st);
 
 // ---- fp64 transforms (primes below 2^50, N = 2^12 .. 2^15) ----
 // The stages a launch can belong to: 0 and 1 are the whole-polynomial transforms of ntt_fp.hip, the others the row and
 // column kernels of convert_fp.hip.
 enum FpMode {
     FP_FWD_PLAIN = 0,      // u64 coefficients in, u64 NTT form out
-    FP_INV_PLAIN = 1,      // u64 NTT form in (optionally gathered through sigma_g), u64 coefficients out
+    FP_INV_PLAIN = 1,      // u64 NTT form in, u64 coefficients out
     FP_INV_TO_Y = 2,       // rows: inverse levels of the source limbs of a conversion
     FP_FWD_CONV = 3,       // columns, rows: conversion of the digits and forward levels -> extended digits (doubles)
     FP_FWD_CONV_FINAL = 4, // columns, rows: the same for a division: out = (acc - transform) * P^-1 (+ addend), canonical
@@ -298,7 +291,7 @@ enum FpMode {
 
 struct FpTask {
     int32_t period;                      // tasks per batch entry
-    int16_t pos[HISA_MAX_PRIMES];        // limb position of the task's polynomial inside a batch entry (output side)
+    int16_t pos[HISA_MAX_PRIMES];        // limb position of the task's polynomial inside a batch entry
     int16_t prime[HISA_MAX_PRIMES];      // its prime
 };
 
@@ -312,8 +305,6 @@ struct FpArgs {
     int n_tasks;                       // filled in by the launcher
     const u64* in; u64 in_bs;          // input [batch][..][N]
     u64* out; u64 out_bs;
-    int in_pos_shift;                  // input limb position = pos + in_pos_shift
-    u64 galois;                        // inverse: gather through sigma_g (0 = none)
     // by columns and rows (launch_ntt_fp_split)
     const double *sfwd, *sinv;
     u64 table_stride;                  // filled in by the launcher, like n_entries

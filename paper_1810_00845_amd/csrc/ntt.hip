@@ -5,13 +5,13 @@
 #include "hisa_internal.hpp"
 
 // PolyMap -> compact task list of the fp64 single-launch transform; false when it does not fit
-static bool fp_tasks(const NttTables& t, int log_n, const PolyMap& map, int n_polys, int out_entry0, FpTask* tk) {
+static bool fp_tasks(const NttTables& t, int log_n, const PolyMap& map, int n_polys, FpTask* tk) {
     if (!t.fp_ok || log_n < 12 || log_n > 15 || n_polys % map.period != 0) return false;
     int cnt = 0;
     for (int e = 0; e < map.period; e++) {
         if (map.prime_of[e] < 0) continue;
         if (cnt >= HISA_MAX_PRIMES) return false;
-        tk->pos[cnt] = (int16_t)(e - out_entry0);
+        tk->pos[cnt] = (int16_t)e;
         tk->prime[cnt] = map.prime_of[e];
         cnt++;
     }
@@ -19,11 +19,11 @@ static bool fp_tasks(const NttTables& t, int log_n, const PolyMap& map, int n_po
     return cnt > 0;
 }
 
-static void int_tasks(const PolyMap& map, int out_entry0, IntTasks* tk) {
+static void int_tasks(const PolyMap& map, IntTasks* tk) {
     tk->n = 0;
     for (int e = 0; e < map.period; e++) {
         if (map.prime_of[e] < 0) continue;
-        tk->pos[tk->n] = (int16_t)(e - out_entry0);
+        tk->pos[tk->n] = (int16_t)e;
         tk->prime[tk->n++] = map.prime_of[e];
     }
 }
@@ -55,14 +55,14 @@ hipError_t launch_ntt_i64(const NttTables& t, int log_n, const i64* coeffs, u64*
     if (n_pts <= 0) return hipSuccess;
     const PolyMap map = identity_map(limbs);
     FpTask tk;
-    if (fp_tasks(t, log_n, map, n_pts * limbs, 0, &tk) && few_polynomials(log_n, (u64)n_pts * limbs)) {
+    if (fp_tasks(t, log_n, map, n_pts * limbs, &tk) && few_polynomials(log_n, (u64)n_pts * limbs)) {
         FpArgs fa = fp_base_args(t);
         fa.coeffs = coeffs; fa.out = out; fa.out_bs = (u64)limbs << log_n;
         return launch_ntt_fp_split(FP_FWD_PLAIN, log_n, fa, tk, (u64)n_pts, st);
     }
     if (!t.fp_ok) {
         IntTasks it;
-        int_tasks(map, 0, &it);
+        int_tasks(map, &it);
         IntArgs a = int_base_args(t, log_n);
         a.n_entries = (unsigned)n_pts;
         a.coeffs = coeffs; a.out = out; a.out_bs = (u64)limbs << log_n;
@@ -76,7 +76,7 @@ hipError_t launch_ntt_i64(const NttTables& t, int log_n, const i64* coeffs, u64*
 hipError_t launch_intt_centred(const NttTables& t, int log_n, const u64* in, double* out, int limbs, int n_pts, hipStream_t st) {
     DRY_RUN_RETURN();
     FpTask tk;
-    if (!fp_tasks(t, log_n, identity_map(limbs), n_pts * limbs, 0, &tk)) return hipErrorInvalidValue;
+    if (!fp_tasks(t, log_n, identity_map(limbs), n_pts * limbs, &tk)) return hipErrorInvalidValue;
     FpArgs fa = fp_base_args(t);
     fa.in = in; fa.in_bs = (u64)limbs << log_n; fa.out = (u64*)out; fa.out_bs = (u64)limbs << log_n; fa.centred_out = 1;
     return launch_ntt_fp_split(FP_INV_PLAIN, log_n, fa, tk, (u64)n_pts, st);
@@ -87,13 +87,13 @@ hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride
     DRY_RUN_RETURN();
     if (n_polys <= 0) return hipSuccess;
     FpTask tk;
-    if (fp_tasks(t, log_n, map, n_polys, 0, &tk)) {
+    if (fp_tasks(t, log_n, map, n_polys, &tk)) {
         FpArgs fa = fp_base_args(t);
         fa.in = data; fa.in_bs = batch_stride; fa.out = data; fa.out_bs = batch_stride;
         return transform_fp(FP_FWD_PLAIN, log_n, fa, tk, (u64)(n_polys / map.period), st);
     }
     IntTasks it;
-    int_tasks(map, 0, &it);
+    int_tasks(map, &it);
     if (n_polys % map.period) return hipErrorInvalidValue;
     IntArgs a = int_base_args(t, log_n);
     a.n_entries = (unsigned)(n_polys / map.period);
@@ -101,29 +101,21 @@ hipError_t launch_ntt(const NttTables& t, int log_n, u64* data, u64 batch_stride
     return it.n ? launch_ntt_int(a, it, st) : hipSuccess;
 }
 
-hipError_t launch_intt(const NttTables& t, int log_n, u64* data, u64 batch_stride, int n_polys, const PolyMap& map,
-                       const InttExtra* extra, hipStream_t st) {
+hipError_t launch_intt(const NttTables& t, int log_n, const u64* in, u64* out, u64 batch_stride, int n_polys, const PolyMap& map,
+                       hipStream_t st) {
     DRY_RUN_RETURN();
     if (n_polys <= 0) return hipSuccess;
     FpTask tk;
-    if (fp_tasks(t, log_n, map, n_polys, extra ? extra->out_entry0 : 0, &tk)) {
+    if (fp_tasks(t, log_n, map, n_polys, &tk)) {
         FpArgs fa = fp_base_args(t);
-        fa.in = (extra && extra->in) ? extra->in : data;
-        fa.in_bs = (extra && extra->in) ? extra->in_batch_stride : batch_stride;
-        fa.in_pos_shift = extra ? extra->out_entry0 : 0;
-        fa.galois = extra ? extra->galois : 0;
-        fa.out = data; fa.out_bs = batch_stride;
+        fa.in = in; fa.in_bs = batch_stride; fa.out = out; fa.out_bs = batch_stride;
         return transform_fp(FP_INV_PLAIN, log_n, fa, tk, (u64)(n_polys / map.period), st);
     }
     IntTasks it;
-    int_tasks(map, extra ? extra->out_entry0 : 0, &it);
+    int_tasks(map, &it);
     if (n_polys % map.period) return hipErrorInvalidValue;
     IntArgs a = int_base_args(t, log_n);
     a.n_entries = (unsigned)(n_polys / map.period);
-    a.in = (extra && extra->in) ? extra->in : data;
-    a.in_bs = (extra && extra->in) ? extra->in_batch_stride : batch_stride;
-    a.in_pos_shift = extra ? extra->out_entry0 : 0;
-    a.galois = extra ? extra->galois : 0;
-    a.out = data; a.out_bs = batch_stride;
+    a.in = in; a.in_bs = batch_stride; a.out = out; a.out_bs = batch_stride;
     return it.n ? launch_intt_int(a, it, st) : hipSuccess;
 }

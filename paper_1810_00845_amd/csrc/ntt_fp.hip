@@ -211,19 +211,9 @@ __global__ __launch_bounds__(Geo<K3>::THREADS, NTT_FP_MIN_WAVES(K3)) void ntt_fp
 
     // ---- load (mapping P1: lane <-> consecutive coefficients; register r holds coefficient r*THREADS + t) ----
     {
-        const rsrc_t src = make_rsrc(a.in + b * a.in_bs + (u64)(pos + a.in_pos_shift) * G::N, LB);
-        if (INV && a.galois) {
-            // a private copy of the lane id: keeps the 32 gather indices from being kept alive (and spilled) for the
-            // address arithmetic of the store stage
-            int tg = t_in;
-            asm volatile("" : "+v"(tg));
+        const rsrc_t src = make_rsrc(a.in + b * a.in_bs + (u64)pos * G::N, LB);
 #pragma unroll
-            for (int r = 0; r < 32; r++)
-                v[r] = fp_from_u64(bload(src, galois_src_fp((uint32_t)(G::template reg_idx<MIN>(r) | tg), a.galois, G::LOGN) * 8u, 0));
-        } else {
-#pragma unroll
-            for (int r = 0; r < 32; r++) v[r] = fp_from_u64(bload(src, t8_in, (uint32_t)G::template reg_idx<MIN>(r) * 8u));
-        }
+        for (int r = 0; r < 32; r++) v[r] = fp_from_u64(bload(src, t8_in, (uint32_t)G::template reg_idx<MIN>(r) * 8u));
     }
 
     if (!INV) {
