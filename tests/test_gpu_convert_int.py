@@ -70,3 +70,34 @@ def test_tables_of_every_level_made_once_and_found_again():
             g.rescale(prod)
             assert np.array_equal(g.ct_export(prod), o.export(o.rescale(want)))
     g.close()
+
+
+def test_more_ciphertexts_than_one_set_of_launches_takes():
+    """Key switches of 32769 ciphertexts and a rescale of their 65538 polynomials are two sets of launches each (32767
+    ciphertexts, 65535 polynomials): the first ciphertexts, those on both sides of the lines and the last equal single calls."""
+    from paper_1810_00845_amd import hisa
+    print("[case] 32769 ciphertexts, N = 2^10, 2 limbs", flush=True)
+    g = hisa.Context(10, [60, 51], 1, 60, 5)
+    g.keygen()
+    g.gen_rot_keys([3])
+    two = g.ct_random_batch(2, 2, 2.0 ** 40, 9)
+    n = 32769
+    batch = [two[i % 2] for i in range(n)]
+    single = [g.rot_left(ct, 3) for ct in two]
+    out = g.rot_left_batch(batch, 3)
+    for i in (0, 1, 32766, 32767, 32768):
+        assert np.array_equal(g.ct_export(out[i]), g.ct_export(single[i % 2]))
+    g.rescale_batch(out)
+    for ct in single:
+        g.rescale(ct)
+    for i in (0, 1, 32766, 32767, 32768):
+        assert np.array_equal(g.ct_export(out[i]), g.ct_export(single[i % 2]))
+    # relinearisation, whose addends have two polynomials and stand three polynomials apart
+    want = [g.mul_no_relin(ct, ct) for ct in two]
+    prod = g.mul_no_relin_batch(batch, batch)
+    g.relinearize_batch(prod)
+    for ct in want:
+        g.relinearize(ct)
+    for i in (0, 1, 32766, 32767, 32768):
+        assert np.array_equal(g.ct_export(prod[i]), g.ct_export(want[i % 2]))
+    g.close()
