@@ -479,7 +479,7 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
     for (int r = 0; r < 16; r++) va[r] = bload(acc, lane8, (uint32_t)r * 512u);
     if (with_add) {
         double vb[16];
-        load_row_through<K3>(vb, a.add + (b / a.add_div) * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, a.add_galois, row, lane);
+        load_row_through<K3>(vb, a.add + (b / a.add_div) * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, 0, row, lane);
 #pragma unroll
         for (int r = 0; r < 16; r++)
             bstore(dst, lane8, (uint32_t)r * 512u,
@@ -497,7 +497,7 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
 // One pair of waves per (limb x, row, entry).  The digits' rows are shared out between the two: forward levels (or, for the
 // limb's own digit, the input polynomial itself, read through sigma_g), result left in LDS; then wave p multiplies all of
 // them by the key's rows of polynomial p.  The sums never leave the registers before they are what the next launch reads:
-// limbs below n_acc leave as sum * c1[x] + addend * c2[x], limbs from n_acc on (the sources of the division that follows)
+// limbs below n_acc leave as sum * c1[x] + addend, limbs from n_acc on (the sources of the division that follows)
 // go straight through the inverse levels of the row.  A wave that kept both sums beside a row and its twiddles needed 168
 // registers and spilled; a pair keeps each wave within 128, four waves per SIMD.
 // Per entry the launch reads (digits' limbs) + own + addend and writes 2 (n_acc + sources) limbs: bound by memory.
@@ -595,14 +595,8 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     if (x < a.l && poly < g.add_polys) {
         double t[16];
         load_row_through<K3>(t, g.add + ct * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, galois, row, lane);
-        const double c2 = g.c2 ? as_const(g.c2)[x] : 1.0;
-        if (g.c2) {
 #pragma unroll
-            for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(fp_from_u64((u64)__double_as_longlong(t[r])), c2, q.p, q.pinv);
-        } else {
-#pragma unroll
-            for (int r = 0; r < 16; r++) sum[r] += fp_from_u64((u64)__double_as_longlong(t[r]));
-        }
+        for (int r = 0; r < 16; r++) sum[r] += fp_from_u64((u64)__double_as_longlong(t[r]));
     }
     SCHED_FENCE();
     const u64 out_limb = source ? (b * 2 + poly) * (u64)(a.ext_limbs - g.n_acc) + (u64)(x - g.n_acc) : (b * 2 + poly) * (u64)g.n_acc + (u64)x;

@@ -23,11 +23,6 @@ __device__ __forceinline__ u64 bload(rsrc_t r, uint32_t lane_off, uint32_t row_o
     const u32x2_t d = __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)row_off, 0);
     return ((u64)d.y << 32) | d.x;
 }
-// the same, bypassing the CU's L1 (data that another point in time of this workgroup wrote)
-__device__ __forceinline__ u64 bload_glc(rsrc_t r, uint32_t lane_off, uint32_t row_off) {
-    const u32x2_t d = __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane_off, (int)row_off, 1);
-    return ((u64)d.y << 32) | d.x;
-}
 __device__ __forceinline__ double bloadf(rsrc_t r, uint32_t lane_off, uint32_t row_off) {
     return __longlong_as_double((long long)bload(r, lane_off, row_off));
 }

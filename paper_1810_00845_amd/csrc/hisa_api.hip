@@ -1472,9 +1472,8 @@ static int divide_fp(hisa_ctx* ctx, const ConvertArgs& c) {
     return HISA_OK;
 }
 
-// acc [B][2][l + K][N] (NTT form) -> out[B][2][l][N] = ModDown(acc) (+ addend, gathered through add_galois if set)
-int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64 add_galois,
-                   u64* out) {
+// acc [B][2][l + K][N] (NTT form) -> out[B][2][l][N] = ModDown(acc) (+ addend)
+int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64* out) {
     const size_t n = ctx->N;
     const int K = (int)ctx->K, ext_limbs = l + K;
     Temp y2(ctx, B * 2 * (size_t)K * n * sizeof(double));
@@ -1485,7 +1484,7 @@ int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* ad
     c.in = acc; c.in_bs = (u64)ext_limbs * n; c.src_pos0 = l; c.n_src = K; c.post = post_p; c.mid = y2.as<double>();
     c.n_digits = 1; c.dg[0] = {ctx->moddown_tab->d_hat_f, 0, K, 0, 0, 0}; c.ext_limbs = l; c.out = out; c.out_bs = (u64)l * n;
     c.acc = acc; c.acc_bs = (u64)ext_limbs * n; c.pinv_tab = ctx->d_pinv_f;
-    c.add = add; c.add_bs = add_bs; c.add_ps = (u64)l * n; c.add_div = 2; c.add_polys = add_polys; c.add_galois = add_galois;
+    c.add = add; c.add_bs = add_bs; c.add_ps = (u64)l * n; c.add_div = 2; c.add_polys = add_polys;
     return divide_fp(ctx, c);
 }
 
@@ -1627,7 +1626,7 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
                                       shared_input ? 1 : 0, l,
                                       (int)ctx->log_n, ctx->stream));
     if (rescale) return moddown_rescale_fp(ctx, acc.u(), Bn, l, addend.u(), (u64)2 * l * n, 2, out);
-    return moddown_add_fp(ctx, acc.u(), Bn, l, addend.u(), (u64)2 * l * n, 2, 0, out);
+    return moddown_add_fp(ctx, acc.u(), Bn, l, addend.u(), (u64)2 * l * n, 2, out);
 }
 
 int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n_cts, int l, u64* out) {
@@ -1650,7 +1649,7 @@ int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n_
     const u64* d2 = cts3 + 2 * lw;
     TRY(key_switch_modup_fp(ctx, d2, stride, n_cts, x));
     HIP_TRY(ctx, launch_inner_product_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, it->second.data, total, d2,
-                                         stride, 0, 0, acc.u(), (u64)2 * ext_limbs * n, n_cts, (int)ctx->log_n, ctx->stream));
+                                         stride, acc.u(), (u64)2 * ext_limbs * n, n_cts, (int)ctx->log_n, ctx->stream));
     return moddown_rescale_fp(ctx, acc.u(), n_cts, l, cts3, stride, 2, out);
 }
 
@@ -2159,12 +2158,11 @@ extern "C" int hisa_rescale_batch(hisa_ctx* ctx, hisa_ct* const* cts, size_t n) 
     const int l = (int)cts[0]->limbs, polys = (int)cts[0]->polys;
     if (l < 2) return fail(ctx, HISA_ERR_DEPTH_EXHAUSTED, "rescale of a one-limb ciphertext");
     if (t_analysis) TALLY(rescale, HISA_OP_RESCALE, n, l);
-    const size_t nn = ctx->N, n_bp = n * polys;
+    const size_t n_bp = n * polys;
     BatchIn bi;
     TRY(gather_batch(ctx, (const hisa_ct* const*)cts, n, &bi));
-    int rc = HISA_OK;
     std::vector<hisa_ct*> fresh(n);
-    rc = alloc_ct_batch(ctx, n, (uint32_t)polys, (uint32_t)(l - 1), 0.0, fresh.data());
+    int rc = alloc_ct_batch(ctx, n, (uint32_t)polys, (uint32_t)(l - 1), 0.0, fresh.data());
     if (rc == HISA_OK) {
         rc = ctx->tabs.fp_ok ? rescale_core_fp(ctx, bi.base, n_bp, l, fresh[0]->data) : rescale_core_int(ctx, bi.base, n_bp, l, fresh[0]->data);
         for (size_t i = 0; i < n; i++) {

@@ -230,8 +230,7 @@ int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add,
 // Relinearisation of n three-polynomial ciphertexts ([3][l][N], stride words apart) whose division by P is taken
 // together with the divScalar by q_{l-1}: out [n][2][l - 1][N] = ((d0, d1) + KS_relin(d2)) / q_{l-1}.
 int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n, int l, u64* out);
-int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64 add_galois,
-                   u64* out);
+int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64* out);
 // exact integer nearest to the double v (ties away from zero), reduced modulo q
 u64 double_to_residue(double v, u64 q);
 
@@ -359,7 +358,6 @@ struct ConvertArgs {
     const double* pinv_tab;              // [prime] P^-1 mod q, centred
     // FP_FWD_CONV_FINAL: addend of entry b: add + (b / add_div) * add_bs + (b % add_div) * add_ps, if b % add_div < add_polys
     const u64* add; u64 add_bs, add_ps; int add_div, add_polys;
-    u64 add_galois;
 };
 hipError_t launch_inverse_rows_fp(const ConvertArgs& a, hipStream_t st);              // in -> mid
 hipError_t launch_columns_fp(int mode, const ConvertArgs& a, hipStream_t st);         // mid -> out (modes 3, 4, 6)
@@ -367,8 +365,8 @@ hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st
 // The rows behind the columns of a key switch's digits (ConvertArgs::out: [n_entries][digits][ext_limbs][N]), with the inner
 // product with `key` and the neighbouring halves of the division that follows, for the limbs x_begin .. x_end - 1.
 // FP_INV_D_TO_Y: limbs from n_acc on are sources of that division: down [n_entries * 2][ext_limbs - n_acc][N] =
-// (sum * c1[x] (+ addend * c2[x])) after the inverse rows, `mid` of the division's columns; limbs below n_acc leave as
-// acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend * c2[x]), lazily reduced doubles for FP_FWD_SUB.
+// (sum * c1[x] (+ addend)) after the inverse rows, `mid` of the division's columns; limbs below n_acc leave as
+// acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend), lazily reduced doubles for FP_FWD_SUB.
 // FP_FWD_CONV_SUB (limbs below n_acc): out holds the division's columns and receives its result.
 // Own digits and addend are read through sigma_g.
 // With StepArgs: several rotations of the same step_B ciphertexts, entry b being rotation b / step_B of ciphertext b % step_B.
@@ -383,7 +381,7 @@ struct InnerArgs {
     const u64* own; u64 own_bs;
     u64 galois;
     int n_acc, x_begin, x_end;
-    const double *c1, *c2;               // [ext_limbs]; c2 null: ones
+    const double* c1;                    // [ext_limbs]
     const u64* add; u64 add_bs, add_ps; int add_polys;
     double* acc;
     u64* out;
@@ -445,10 +443,10 @@ hipError_t launch_key_to_doubles(const FpPrime* fprimes, u64* key, int n_rows, i
 hipError_t launch_key_to_residues(const FpPrime* fprimes, const u64* key, u64* out, int n_rows, int total, int log_n, hipStream_t st);
 
 // acc[b][p][x] = sum_j e_j[x] * key[j][p][prime(x)] in fp64; e_j[x] comes from ext unless x lies in digit j, then
-// from own_src (the NTT-form input itself, read through sigma_g when galois != 0)
+// from own_src (the NTT-form input itself)
 hipError_t launch_inner_product_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
-                                   int alpha, const u64* key, int total, const u64* own_src, u64 own_bs, u64 galois,
-                                   int gather_ext, u64* acc, u64 acc_bs, u64 n_batch, int log_n, hipStream_t st);
+                                   int alpha, const u64* key, int total, const u64* own_src, u64 own_bs, u64* acc, u64 acc_bs,
+                                   u64 n_batch, int log_n, hipStream_t st);
 // The same for n_steps rotations of the same n_batch ciphertexts (extended digits computed once from the unrotated
 // polynomial): rotation s uses keys[s] and gathers through galois[s]; acc entries are ordered rotation-major.
 // c0_src (with pmod[i] = P mod q_i): the b accumulator also takes P * sigma_s(c0) on the limbs of q, c0 read at

@@ -1779,7 +1779,7 @@ static int conv_run_shared(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv
         if (e != hipSuccess) rc = mac_fail(ctx, e, "conv");
     }
     if (rc == HISA_OK && one_division) rc = moddown_rescale_fp(ctx, E.u(), n_out, (int)l, Z.u(), 2 * lw, 2, outs[0]->data);
-    else if (rc == HISA_OK) rc = moddown_add_fp(ctx, E.u(), n_out, (int)l, Z.u(), 2 * lw, 2, 0, outs[0]->data);
+    else if (rc == HISA_OK) rc = moddown_add_fp(ctx, E.u(), n_out, (int)l, Z.u(), 2 * lw, 2, outs[0]->data);
     if (rc == HISA_OK && g->mode == HISA_CONV_MASKED) {
         hipError_t e = launch_mul_plain(ctx->d_primes, outs[0]->data, cw.mask->u(), outs[0]->data, (int)l, 2, n_out, 2 * lw, 2 * lw,
                                         (int)ctx->log_n, ctx->stream);
