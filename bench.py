@@ -15,7 +15,6 @@ Prints ONE JSON line.  Besides the contract fields it carries
 import argparse
 import json
 import os
-import re
 import sys
 import time
 
@@ -32,18 +31,20 @@ def algorithmic_bytes_rot_left(N, l, K, alpha, B):
     digits = (l + alpha - 1) // alpha
     sizes = [min(alpha, l - j * alpha) for j in range(digits)]
     conv_out = sum(ext - a for a in sizes)
-    # kernel names as rocprofv3 prints them, without the third argument (the launch over columns or over rows): the
-    # stages of convert_fp.hip, what each must read and write once
+    # kernel names as rocprofv3 prints them, the third argument being the launch over columns (true) or rows: the stages A to
+    # E of convert_fp.hip, what each must read and write once
     k3 = "%d" % (N.bit_length() - 1 - 10)
     return {
         # inverse rows of c1
-        "ntt_fp_kernel<%s, 2>" % k3: 2 * LP * B * l,
+        "ntt_fp_kernel<%s, 2, false>" % k3: 2 * LP * B * l,
         # columns: the limbs of c1 to the extended digits
-        "ntt_fp_kernel<%s, 3>" % k3: LP * B * (l + conv_out),
+        "ntt_fp_kernel<%s, 3, true>" % k3: LP * B * (l + conv_out),
         # rows of the special limbs: extended digits and key to the sources of the division by P
-        "ntt_fp_kernel<%s, 5>" % k3: LP * (B * (digits * K + 2 * K) + digits * 2 * K),
-        # the division's columns; rows of the limbs of q: extended digits, own limbs, addend, key and columns to the result
-        "ntt_fp_kernel<%s, 6>" % k3: LP * (B * (2 * K + 2 * l + sum(l - a for a in sizes) + l + l + 2 * l + 2 * l) + digits * 2 * l),
+        "ntt_fp_kernel<%s, 5, false>" % k3: LP * (B * (digits * K + 2 * K) + digits * 2 * K),
+        # the division's columns
+        "ntt_fp_kernel<%s, 6, true>" % k3: LP * B * (2 * K + 2 * l),
+        # rows of the limbs of q: extended digits, own limbs, addend, key and the division's columns to the result
+        "ntt_fp_kernel<%s, 6, false>" % k3: LP * (B * (sum(l - a for a in sizes) + l + l + 2 * l + 2 * l) + digits * 2 * l),
     }
 
 
@@ -59,11 +60,11 @@ def algorithmic_flops_rot_left(N, l, K, alpha, B):
     rows, cols = 10 * (N // 2) * 10, 10 * (N // 2) * (log_n - 10)      # the levels inside a row of 1024 and those across rows
     k3 = "%d" % (log_n - 10)
     return {
-        "ntt_fp_kernel<%s, 2>" % k3: B * l * rows,
-        "ntt_fp_kernel<%s, 3>" % k3: B * (l * (cols + 8 * N) + sum((ext - a) * (cols + 9 * a * N) for a in sizes)),
-        "ntt_fp_kernel<%s, 5>" % k3: B * (digits * K * rows + 2 * K * (9 * digits * N + 8 * N + rows)),
-        "ntt_fp_kernel<%s, 6>" % k3: B * (2 * K * (cols + 8 * N) + 2 * l * (cols + 9 * K * N)
-                                          + sum(l - a for a in sizes) * rows + 2 * l * (9 * digits * N + 9 * N + rows)),
+        "ntt_fp_kernel<%s, 2, false>" % k3: B * l * rows,
+        "ntt_fp_kernel<%s, 3, true>" % k3: B * (l * (cols + 8 * N) + sum((ext - a) * (cols + 9 * a * N) for a in sizes)),
+        "ntt_fp_kernel<%s, 5, false>" % k3: B * (digits * K * rows + 2 * K * (9 * digits * N + 8 * N + rows)),
+        "ntt_fp_kernel<%s, 6, true>" % k3: B * (2 * K * (cols + 8 * N) + 2 * l * (cols + 9 * K * N)),
+        "ntt_fp_kernel<%s, 6, false>" % k3: B * (sum(l - a for a in sizes) * rows + 2 * l * (9 * digits * N + 9 * N + rows)),
     }
 
 
@@ -128,7 +129,6 @@ def summarize_counters(root):
     import collections
     import csv
     import glob
-    import re
 
     def load(sub, pattern):
         rows = []
@@ -138,7 +138,7 @@ def summarize_counters(root):
         return rows
 
     def short(name):
-        return re.sub(r", (true|false)>$", ">", name.replace("void ", "").split("(")[0])
+        return name.replace("void ", "").split("(")[0]
 
     def counters(sub):
         agg = collections.defaultdict(lambda: collections.defaultdict(list))
@@ -354,14 +354,8 @@ def main():
     ctx.profile_enable(False)
     alg = algorithmic_bytes_rot_left(N, L, K, alpha, B)
     flops = algorithmic_flops_rot_left(N, L, K, alpha, B)
-    # the transform kernel's name carries a third template argument (columns or rows); the launches of a stage are summed
-    merged = {}
-    for name, (cnt, ms) in prof.items():
-        key = re.sub(r", (true|false)>$", ">", name)
-        c0, m0 = merged.get(key, (0, 0.0))
-        merged[key] = (c0 + cnt, m0 + ms)
     kernels = {}
-    for name, (cnt, ms) in merged.items():
+    for name, (cnt, ms) in prof.items():
         per_step_ms = ms / prof_steps
         gbs = alg.get(name, 0) / (per_step_ms * 1e-3) / 1e9 if per_step_ms > 0 else 0.0
         kernels[name] = {"launches_per_step": cnt / prof_steps, "ms_per_step": round(per_step_ms, 4),
@@ -378,14 +372,11 @@ def main():
     fp64_measured = 2.0 * cal["fma_f64"]
     counters, counter_src = read_counters() if headline else ({}, {"file": None, "note": "counters exist for the headline configuration only"})
 
-    def counter_key(name):     # the counter summary keeps rocprofv3's names, without the third template argument
-        return name
-
     launches = max(kernels[dom]["launches_per_step"], 1)
     hbm_side = {"achieved_GBs": kernels[dom]["algorithmic_GBs"], "frac": round(kernels[dom]["algorithmic_GBs"] / HBM_PEAK_GBS, 4),
                 "frac_of_measured_copy": round(kernels[dom]["algorithmic_GBs"] / cal["copy_GBs"], 4) if cal["copy_GBs"] else None,
                 "algorithmic_bytes_per_launch": int(alg.get(dom, 0) / launches)}
-    cnt = counters.get(counter_key(dom), {})
+    cnt = counters.get(dom, {})
     if dom in flops:
         # rows move a limb for ten levels, columns convert many limbs for each they move: the bound is the resource of
         # whose measured rate the kernel reaches more, the other reading stays beside it
@@ -414,7 +405,7 @@ def main():
     roofline["avg_launch_us"] = kernels[dom]["avg_launch_us"]
     roofline["share_of_step"] = round(kernels[dom]["ms_per_step"] / sum(k["ms_per_step"] for k in kernels.values()), 3)
     for name, k in kernels.items():      # counter readings of every kernel of the step, where the summary has them
-        c = counters.get(counter_key(name))
+        c = counters.get(name)
         if c:
             k["counters_per_launch"] = c
     staged, strict = staged_bytes_rot_left(N, L, K, alpha, dnum, L, B)
