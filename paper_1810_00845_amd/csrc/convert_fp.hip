@@ -937,7 +937,11 @@ static hipError_t launch_columns_k3(const ConvertArgs& a_in, hipStream_t st) {
         if (e != hipSuccess) return e;
         attr_set = true;
     }
-    // sixteen waves where only one workgroup fits a compute unit's LDS, else eight
+    // Sixteen waves where only one workgroup fits a compute unit's LDS (more than 80 KB of sources: 10 of them from N = 2^14
+    // on, 20 at 2^13), else eight.  rotLeft in us, eight -> sixteen waves, batches of 64, 16 and 1.  Above the line: 11 sources at
+    // N = 2^15 1893 -> 1835, 515 -> 490, 70 -> 74; 16 sources 1473 -> 1438, 394 -> 381, 69 -> 81; 16 at N = 2^14 715 -> 737,
+    // 198 -> 191, 61 -> 74; 21 at N = 2^13 562 -> 522, 163 -> 148, 50 -> 53: single ciphertexts would be served better by eight.
+    // Below it: 8 sources at N = 2^15 611 -> 649, 171 -> 178, 51 -> 50; 7 sources 1768 -> 1817, 479 -> 496, 72 -> 70.
     const unsigned threads = lds > 81920 ? 1024 : 512;
     // Few entries: several workgroups share a tile's targets (each forms the conversion inputs for itself), so that the
     // launch reaches about two workgroups per compute unit before a workgroup takes a second round of targets.
