@@ -272,6 +272,9 @@ __device__ __forceinline__ void rows_inverse(const ConvertArgs& a, int n_tasks, 
 // ---------------------------------------------------------------------------
 // columns
 // ---------------------------------------------------------------------------
+// Bound by fp64 issue beside memory: 64 rotations at N = 2^15, 16 limbs, with the products and levels left out the launch over
+// the digits takes 207 us (its bytes), with the stores left out 240 us, whole 284 us.  Its conversion sums are FpSums: products
+// reduced one by one made it 305 us, those of the division by P 208 us against 188 now.
 template <int RB>
 struct Col {
     static constexpr int NR = RB == 5 ? 16 : (1 << RB);      // coefficients per lane
@@ -365,7 +368,6 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
         double v[NR];
 #pragma unroll
         for (int r = 0; r < NR; r++) v[r] = 0.0;
-        int since = 0;
         for (int c0 = 0; c0 < n_src; c0 += a.chunk) {
             const int c1 = min(c0 + a.chunk, n_src);
             if (!resident || round == 0) {
@@ -394,15 +396,37 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
                 __syncthreads();
             }
             if (mine) {
-                for (int i = c0; i < c1; i++) {
-                    const double hat = as_const(a.dg[digit].hat)[(u64)i * a.total + prime];
-                    const double* y = ylds + (i - c0) * NR * 64 + lane;
+                const cdouble_ptr hat = as_const(a.dg[digit].hat) + prime;
+                const double* y0 = ylds + lane;
+                if (n_src == 1) {                      // rescale, digits of one limb: the sum's reduction costs more than a product
+                    const double f = hat[0];
 #pragma unroll
-                    for (int r = 0; r < NR; r++) v[r] += fp_mulmod(y[r * 64], hat, q.p, q.pinv);
-                    if (++since == 12) {           // twelve terms of at most 0.6 p on top of a normalised sum
-                        since = 0;
+                    for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_mulmod(y0[r * 64], f, q.p, q.pinv), q.p, q.pinv);
+                } else {
+                    for (int i0 = c0; i0 < c1; i0 += FP_SUM_TERMS) {
+                        FpSum s[NR];
 #pragma unroll
-                        for (int r = 0; r < NR; r++) v[r] = fp_norm(v[r], q.p, q.pinv);
+                        for (int r = 0; r < NR; r++) s[r] = FpSum{FP_SUM_BASE, v[r]};
+                        const int i1 = min(i0 + FP_SUM_TERMS, c1);
+                        const double* y = y0 + (i0 - c0) * NR * 64;
+                        // in pairs: a term leaves its sum in another register, which the end of a loop would copy back
+                        int i = i0;
+#pragma unroll 1
+                        for (; i + 1 < i1; i += 2, y += 2 * NR * 64) {
+                            const double f0 = hat[(u64)i * a.total], f1 = hat[(u64)(i + 1) * a.total];
+#pragma unroll
+                            for (int r = 0; r < NR; r++) {
+                                fp_sum_add(s[r], y[r * 64], f0);
+                                fp_sum_add(s[r], y[(NR + r) * 64], f1);
+                            }
+                        }
+                        if (i < i1) {
+                            const double f0 = hat[(u64)i * a.total];
+#pragma unroll
+                            for (int r = 0; r < NR; r++) fp_sum_add(s[r], y[r * 64], f0);
+                        }
+#pragma unroll
+                        for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_sum_value(s[r], q.p, q.pinv), q.p, q.pinv);
                     }
                 }
             }
@@ -414,8 +438,6 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
 #pragma unroll
                 for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
             }
-#pragma unroll
-            for (int r = 0; r < NR; r++) v[r] = fp_norm(v[r], q.p, q.pinv);
             fwd_columns<RB>(v, head, last, q);
             const rsrc_t dst = make_rsrc((double*)a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n, (uint32_t)n * 8u);
 #pragma unroll
@@ -831,9 +853,11 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a)
 // MODE (enum FpMode) names the stage a launch belongs to, so that a profile tells the ModUp's columns from the ModDown's;
 // COLUMNS: the launch in which all target limbs of a digit share one pass over its sources, else the rows.
 constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : (mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB) ? 128 : ROWS_NT; }
+// waves per SIMD to leave room for: the columns of N = 2^14 and 2^13 come out a few registers above a whole workgroup more
+constexpr int fp_waves(int k3, bool columns) { return !columns ? 4 : k3 == 4 ? 6 : k3 == 3 ? 8 : 4; }
 
 template <int K3, int MODE, bool COLUMNS>
-__global__ __launch_bounds__(fp_threads(MODE, COLUMNS), 4) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
+__global__ __launch_bounds__(fp_threads(MODE, COLUMNS), fp_waves(K3, COLUMNS)) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
     if constexpr (COLUMNS) {
         extern __shared__ double ylds[];
         columns<K3>(a, ylds);

@@ -30,6 +30,29 @@ FP_HD double fp_mulmod(double a, double b, double p, double pinv) {
     return r + l;
 }
 
+// Sums of products a_i * b_i with one reduction for all of them.  h holds FP_SUM_BASE + (the sum, each product rounded to the
+// unit in the last place of the base, 2^50, as it is added), l what the roundings left out: h stays in the binade of the base, so
+// both differences below are exact.  Four instructions a term where a modular product and an addition are seven, and
+// six to get the value out.
+//   |a_i * b_i| <= 2^98, at most FP_SUM_TERMS of them: |h - base| <= 2^101, |l| <= 2^52 beside what it started from
+//   fp_sum_value: an integer congruent to the sum plus the start of l, |result| <= 1.5 p + |l|
+#define FP_SUM_TERMS 8
+#define FP_SUM_BASE 0x1.8p102
+struct FpSum {
+    double h, l;
+};
+FP_HD void fp_sum_add(FpSum& s, double a, double b) {
+    const double t = __builtin_fma(a, b, s.h);
+    const double d = t - s.h;
+    s.l += __builtin_fma(a, b, -d);
+    s.h = t;
+}
+FP_HD double fp_sum_value(const FpSum& s, double p, double pinv) {
+    const double h = s.h - FP_SUM_BASE;
+    const double q = __builtin_rint(h * pinv);
+    return __builtin_fma(-q, p, h) + s.l;
+}
+
 // v - rint(v/p) * p
 FP_HD double fp_norm(double v, double p, double pinv) {
     const double q = __builtin_rint(v * pinv);

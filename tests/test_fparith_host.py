@@ -18,6 +18,12 @@ double t_norm(double v, double p, double pinv) { return fp_norm(v, p, pinv); }
 uint64_t t_canonical(double v, double p, double pinv) { return fp_canonical(v, p, pinv); }
 double t_from_u64(uint64_t x) { return fp_from_u64(x); }
 uint64_t t_to_u64(double v) { return fp_to_u64(v); }
+double t_sum(const double* a, const double* b, int n, double start, double p, double pinv) {
+    FpSum s = {FP_SUM_BASE, start};
+    for (int i = 0; i < n; i++) fp_sum_add(s, a[i], b[i]);
+    return fp_sum_value(s, p, pinv);
+}
+int t_sum_terms() { return FP_SUM_TERMS; }
 double t_centred(uint64_t x, double p, double half) { return fp_centred_from_u64(x, p, half); }
 }
 """
@@ -39,6 +45,7 @@ def fp(tmp_path_factory):
     l.t_canonical.restype = U; l.t_canonical.argtypes = [D] * 3
     l.t_from_u64.restype = D; l.t_from_u64.argtypes = [U]
     l.t_to_u64.restype = U; l.t_to_u64.argtypes = [D]
+    l.t_sum.restype = D; l.t_sum.argtypes = [ctypes.POINTER(D), ctypes.POINTER(D), ctypes.c_int, D, D, D]
     l.t_centred.restype = D; l.t_centred.argtypes = [U, D, D]
     return l
 
@@ -120,3 +127,29 @@ def test_eight_term_sums_stay_exact(fp):
                 assert abs(s) < 2 ** 53 and is_int(s)
             assert (int(s) - true) % p == 0
             assert (fp.t_canonical(s, pf, pinv) - true) % p == 0
+
+
+def test_sums_with_one_reduction(fp):
+    """FpSum: as many terms as it may hold, all at +-2^49 times +-2^49 in size (the largest centred representatives there are)
+    or mixed, on top of a normalised value: an exact integer below 2^53, congruent to the true sum, also for a modulus far
+    below the factors; the normalised result is the centred representative up to the quotient's rounding."""
+    rnd = random.Random(8)
+    D, terms = ctypes.c_double, fp.t_sum_terms()
+    top = 2 ** 49 - 1
+    for p in primes():
+        pf, pinv = float(p), 1.0 / float(p)
+        for trial in range(1200):
+            n = rnd.randrange(1, terms + 1)
+            kind = trial % 4
+            ys = [top * rnd.choice([1, -1]) if kind < 2 else rnd.randrange(-top, top + 1) for _ in range(n)]
+            hs = [top * rnd.choice([1, -1]) if kind == 0 else (p // 2) * rnd.choice([1, -1]) if kind == 1 else
+                  rnd.randrange(-(p // 2), p // 2 + 1) for _ in range(n)]
+            if trial < 4:
+                n, ys, hs = terms, [top] * terms, [top if trial < 2 else -top] * terms
+            start = rnd.choice([0, p // 2, -(p // 2), rnd.randrange(-(p // 2), p // 2)])
+            r = fp.t_sum((D * n)(*map(float, ys)), (D * n)(*map(float, hs)), n, float(start), pf, pinv)
+            true = start + sum(y * h for y, h in zip(ys, hs))
+            assert is_int(r) and abs(r) < 2 ** 53 and (int(r) - true) % p == 0, (p, ys, hs, start, r)
+            assert abs(r) <= 1.5 * p + 2 ** 52 + abs(start), (p, ys, hs, start, r)
+            v = fp.t_norm(r, pf, pinv)
+            assert is_int(v) and (int(v) - true) % p == 0 and abs(v) <= p / 2 * (1 + 2.0 ** -48) + 2, (p, r, v)

@@ -15,6 +15,8 @@ POINTS = [
     (13, [50, 45, 45, 45, 45, 45, 45], 4, 49, 5, 5),   # ragged last digit below the top level
     (13, [50, 50], 1, 50, 2, 33),
     (15, [50, 50, 50, 50], 4, 50, 3, 9),
+    (13, [50] * 9, 1, 50, 9, 2),                       # conversion sums of eight terms and one more
+    (12, [50] * 16, 1, 50, 16, 1),                     # twice eight
 ]
 
 
