@@ -392,18 +392,33 @@ __device__ __forceinline__ void rows_divide(const IntArgs& a, int n_tasks, u64* 
 // LDS in 30-bit halves.  Then the waves share out the coefficients, groups of INNER_GROUP registers: sums of the digits
 // times both polynomials of the key.  Limbs of q leave as accumulators (below 8 q); those of special limbs replace the first
 // two rows in LDS and two waves take them through the inverse levels of the row, which the division by P starts with.
+//
+// Workgroups go round the XCDs by number.  An XCD takes every eighth row (or, with fewer than eight rows, its share of the
+// limbs of one) and works through the limbs of its rows, the special ones first: they take longest, and with the limbs
+// handed out in order three XCDs had all of them (16 rotations at N = 2^15, 8 limbs of 58 bits: 166 us a launch, 127 so; 64 rotations at
+// N = 2^13: 41 -> 31).  The entries of a row and limb follow one another: they share its key rows.
+struct InnerTask { int x; uint32_t row; u64 b; };
+__host__ __device__ constexpr uint32_t inner_rows(int k3) { return k3 < 3 ? 1u : 1u << (k3 - 3); }             // of an XCD
+__host__ __device__ constexpr uint32_t inner_parts(int k3) { return k3 < 3 ? 8u >> k3 : 1u; }                   // XCDs to a row
+template <int K3>
+__device__ __forceinline__ InnerTask inner_task(const IntArgs& a) {
+    const uint32_t xcd = blockIdx.x & 7, unit = (uint32_t)uniform((int)((blockIdx.x >> 3) / a.n_entries));
+    const u64 b = (blockIdx.x >> 3) - unit * a.n_entries;
+    constexpr uint32_t ROWS = inner_rows(K3), PARTS = inner_parts(K3);
+    const uint32_t row = K3 < 3 ? xcd / PARTS : xcd + 8 * (unit % ROWS);
+    return InnerTask{a.ext_limbs - 1 - (int)(unit / ROWS * PARTS + (K3 < 3 ? xcd % PARTS : 0)), row, b};
+}
 #define INNER_CHUNK 4    // four terms below 2 q times q keep the middle accumulator below 2^64 and the sum below 2^63 q
 #define INNER_GROUP 2    // times two polynomials: 24 registers of accumulators
 template <int K3>
-__device__ __forceinline__ void rows_inner(const IntArgs& a, int n_tasks, u64* lds) {
-    const int per = (n_tasks + 7) >> 3;
-    const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
+__device__ __forceinline__ void rows_inner(const IntArgs& a, u64* lds) {
     const int lane = threadIdx.x & 63, h = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), waves = (int)(blockDim.x >> 6);
-    const uint32_t unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1);
-    const u64 b = (uint32_t)task - unit * a.n_entries;
-    const int x = a.ext_limbs - 1 - (int)(unit >> K3);          // the special limbs, the longest tasks, first
+    const InnerTask it = inner_task<K3>(a);
+    if (it.x < 0) return;
+    const uint32_t row = it.row;
+    const u64 b = it.b;
+    const int x = it.x;
     const int prime = prime_at(x, a.l, a.L);
     const ModI q = mod_int(a.primes, prime);
     const WideMod wide = wide_mod(a.consts, prime);
@@ -728,7 +743,7 @@ void ntt_int_kernel(IntArgs a, IntTasks tk, int n_tasks) {
     } else {
         if constexpr (MODE == INT_INVERSE) rows_inverse<K3>(a, tk, n_tasks, lds);
         else if constexpr (MODE == INT_FORWARD) rows_forward<K3>(a, tk, n_tasks, lds);
-        else if constexpr (MODE == INT_INNER) rows_inner<K3>(a, n_tasks, lds);
+        else if constexpr (MODE == INT_INNER) rows_inner<K3>(a, lds);
         else rows_divide<K3>(a, n_tasks, lds);
     }
 }
@@ -768,8 +783,13 @@ static hipError_t launch_waves(const IntArgs& a, const IntTasks& tk, u64 tasks, 
     const u64 per_block = inner ? 1 : ROWS_NT / 64;
     const unsigned threads = inner && slots == 2 ? 128 : ROWS_NT;
     const size_t lds = COLUMNS ? 0 : (size_t)(inner ? slots : ROWS_NT / 64) * ROW_LDS * 8;
-    return launch_any<MODE, COLUMNS>(a.log_n, dim3((unsigned)(((tasks + per_block - 1) / per_block + 7) / 8 * 8)), threads, lds, a,
-                                     tk, tasks, st);
+    u64 blocks = ((tasks + per_block - 1) / per_block + 7) / 8 * 8;
+    if (inner) {                                               // eight times what the first XCD takes
+        const uint32_t parts = inner_parts(a.log_n - 10);
+        blocks = (u64)((a.ext_limbs + parts - 1) / parts * inner_rows(a.log_n - 10)) * a.n_entries * 8;
+        if (blocks > 0x7fffff00u) return hipErrorInvalidValue;
+    }
+    return launch_any<MODE, COLUMNS>(a.log_n, dim3((unsigned)blocks), threads, lds, a, tk, tasks, st);
 }
 
 static bool base_ok(const IntArgs& a) {
