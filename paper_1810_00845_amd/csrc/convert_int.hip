@@ -7,8 +7,9 @@
 //                -> rows (forward levels, difference, addend)
 //   rescale      rows -> columns -> rows, the same with one source limb
 //   transforms   columns -> rows, or rows -> columns
-// Five launches where one launch per step and digit made 22 (N = 2^12, 3 limbs, one rotation: 153 -> 45 us), and levels in
-// registers where every level was a pass through LDS (N = 2^15, 8 limbs of 58 bits, 16 rotations: 685 -> 374 us).
+// Five launches where one launch per step and digit made 22 (N = 2^12, 3 limbs, one rotation: 153 -> 45 us, 29 with the
+// rows shared by four waves), and levels in registers where every level was a pass through LDS (N = 2^15, 8 limbs of 58 bits, 16
+// rotations: 685 -> 374 us, 332 with the inner products shared out over the XCDs).
 //
 // Arithmetic: a product with a constant w uses its companion floor(2^64 w / q); the quotient is formed without the product
 // of the low halves and with the two middle ones truncated, so it is short by at most 3 and the product lies below 4 q
@@ -250,14 +251,6 @@ __device__ __forceinline__ void row_inverse_lds(u64 (&v)[16], int (&m)[16], cons
     inv_level<3>(v, m, t3, q); inv_level<2>(v, m, t2, q); inv_level<1>(v, m, t1, q); inv_level<0>(v, m, t0, q);
     cap_bounds(v, m, 8, q);
 }
-template <int K3>
-__device__ __forceinline__ void row_inverse(u64 (&v)[16], int (&m)[16], const RowTables<K3>& w, u64* lds, int lane, u64 q) {
-    xchg_sync<true>();
-#pragma unroll
-    for (int r = 0; r < 16; r++) lds[66 * r + lane + (lane >> 5)] = v[r];
-    xchg_sync<true>();
-    row_inverse_lds(v, m, w, lds, lane, q);
-}
 
 // the row's 1024 words of a limb, read through sigma_g when galois != 0
 template <int K3>
@@ -305,32 +298,6 @@ __device__ __forceinline__ Tw table_tw(const u64* t, u64 i) { return Tw{as_const
 // ---------------------------------------------------------------------------
 // rows
 // ---------------------------------------------------------------------------
-template <int K3>
-__device__ __forceinline__ void rows_inverse(const IntArgs& a, const IntTasks& tk, int n_tasks, u64* lds_all) {
-    const int task = row_task(n_tasks);
-    if (task < 0) return;
-    const int lane = threadIdx.x & 63;
-    const uint32_t unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1), e = unit >> K3;
-    const u64 b = (uint32_t)task - unit * a.n_entries;
-    const int prime = uniform(tk.prime[e]), pos = uniform(tk.pos[e]);
-    const ModI q = mod_int(a.primes, prime);
-    constexpr u64 n = (u64)1 << (10 + K3);
-    u64 v[16];
-    int m[16];
-    load_row<K3>(v, a.in + b * a.in_bs + (u64)(pos + a.in_pos_shift) * n, a.galois, row, lane);
-#pragma unroll
-    for (int r = 0; r < 16; r++) m[r] = 1;
-    row_inverse<K3>(v, m, RowTables<K3>(a.itw, a.itw_sh, prime, row, lane), lds_all + (threadIdx.x >> 6) * ROW_LDS, lane, q.q);
-    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)pos * n + (uint32_t)uniform(row) * 1024u, 8192u);
-    if (K3 == 0 && a.whole) {            // no columns behind
-        const Tw f = table_tw(a.consts, (u64)prime * CONST_WORDS);
-#pragma unroll
-        for (int r = 0; r < 16; r++) v[r] = canonical(mul4(v[r], f, q.q), 4, q.q);
-    }
-#pragma unroll
-    for (int r = 0; r < 16; r++) bstore(dst, (uint32_t)lane * 8u, (uint32_t)r * 512u, v[r]);
-}
-
 template <int K3>
 __device__ __forceinline__ void rows_forward(const IntArgs& a, const IntTasks& tk, int n_tasks, u64* lds_all) {
     const int task = row_task(n_tasks);
@@ -493,6 +460,228 @@ __device__ __forceinline__ void rows_inner(const IntArgs& a, u64* lds) {
     row_inverse_lds(v, m, RowTables<K3>(a.itw, a.itw_sh, prime, row, lane), lds + wave * ROW_LDS, lane, q.q);
 #pragma unroll
     for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)(wave * poly_words * 8u) + (uint32_t)r * 512u, v[r]);
+}
+
+// ---------------------------------------------------------------------------
+// rows by four waves each: calls with few rows
+// ---------------------------------------------------------------------------
+// A wave that keeps a row to itself works through eighty butterflies a lane one after the other, 1600 instructions, and
+// fetches its twiddles in five batches; with fewer rows than the chip has SIMDs nothing covers either.  Here a thread holds four
+// coefficients, two levels at a time, and all fifteen of its twiddles are on their way before the first level; only the
+// exchange behind the first two levels crosses waves.
+//   stage s, levels 2 s and 2 s + 1: register r of thread t is element 2^p-strided, p = 8 - 2 s (wide_element)
+#define WIDE_NT 256
+#define WIDE_LDS 1280    // 64-bit words per row: four words of padding per sixteen, so that a thread's four stay together
+__device__ __forceinline__ uint32_t wide_at(uint32_t i) { return i + ((i >> 4) << 2); }
+template <int S>
+__device__ __forceinline__ uint32_t wide_element(uint32_t t, uint32_t r) {
+    constexpr int p = 8 - 2 * S;
+    return ((t >> p) << (p + 2)) | (r << p) | (t & ((1u << p) - 1));
+}
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, u64& x, u64& y) {
+    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
+    x = ((u64)d.y << 32) | d.x;
+    y = ((u64)d.w << 32) | d.z;
+}
+__device__ __forceinline__ void bstore2(rsrc_t r, uint32_t lane_off, uint32_t row_off, u64 x, u64 y) {
+    const u32x4_t d = {(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
+    __builtin_amdgcn_raw_buffer_store_b128(d, r, (int)lane_off, (int)row_off, 0);
+}
+struct WideTwiddles { Tw w[5][3]; };     // per stage: level 2 s, then the two groups of level 2 s + 1
+template <int K3>
+__device__ __forceinline__ void wide_twiddles(WideTwiddles& w, const u64* tw, const u64* tw_sh, int prime, uint32_t row, uint32_t t) {
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const rsrc_t wr = make_rsrc(tw + (u64)prime * n, (uint32_t)n * 8u), sr = make_rsrc(tw_sh + (u64)prime * n, (uint32_t)n * 8u);
+#pragma unroll
+    for (int s = 0; s < 5; s++) {
+        const uint32_t node = (((1u << K3) + row) << (2 * s)) + (t >> (8 - 2 * s));
+        w.w[s][0] = Tw{bload(wr, node * 8u, 0), bload(sr, node * 8u, 0)};
+        bload2(wr, node * 16u, 0, w.w[s][1].w, w.w[s][2].w);
+        bload2(sr, node * 16u, 0, w.w[s][1].s, w.w[s][2].s);
+    }
+}
+// registers of stage FROM to registers of stage TO; the waves keep to their quarter of the row except between stages 0 and 1
+template <int FROM, int TO>
+__device__ __forceinline__ void wide_exchange(u64 (&v)[4], int (&m)[4], u64* lds, uint32_t t) {
+    int top = 0;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        lds[wide_at(wide_element<FROM>(t, r))] = v[r];
+        top = m[r] > top ? m[r] : top;
+    }
+    xchg_sync<FROM + TO != 1>();
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        v[r] = lds[wide_at(wide_element<TO>(t, r))];
+        m[r] = top;
+    }
+    xchg_sync<true>();
+}
+template <int S>
+__device__ __forceinline__ void wide_fwd_stage(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64 q) {
+    fwd_bfly(v[0], v[2], m[0], m[2], w.w[S][0], q);
+    fwd_bfly(v[1], v[3], m[1], m[3], w.w[S][0], q);
+    fwd_bfly(v[0], v[1], m[0], m[1], w.w[S][1], q);
+    fwd_bfly(v[2], v[3], m[2], m[3], w.w[S][2], q);
+}
+template <int S>
+__device__ __forceinline__ void wide_inv_stage(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64 q) {
+    inv_bfly(v[0], v[1], m[0], m[1], w.w[S][1], q);
+    inv_bfly(v[2], v[3], m[2], m[3], w.w[S][2], q);
+    inv_bfly(v[0], v[2], m[0], m[2], w.w[S][0], q);
+    inv_bfly(v[1], v[3], m[1], m[3], w.w[S][0], q);
+}
+// in: coefficient 256 r + t; out: 4 t + r, below cap q.  The row's LDS is free when the first of its threads comes here.
+__device__ __forceinline__ void wide_forward(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64* lds, uint32_t t, u64 q, int cap) {
+    wide_fwd_stage<0>(v, m, w, q); wide_exchange<0, 1>(v, m, lds, t);
+    wide_fwd_stage<1>(v, m, w, q); wide_exchange<1, 2>(v, m, lds, t);
+    wide_fwd_stage<2>(v, m, w, q); wide_exchange<2, 3>(v, m, lds, t);
+    wide_fwd_stage<3>(v, m, w, q); wide_exchange<3, 4>(v, m, lds, t);
+    wide_fwd_stage<4>(v, m, w, q);
+#pragma unroll
+    for (int r = 0; r < 4; r++) cap_to(v[r], m[r], cap, q);
+}
+// in: coefficient 4 t + r; out: 256 r + t, below 8 q
+__device__ __forceinline__ void wide_inverse(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64* lds, uint32_t t, u64 q) {
+    wide_inv_stage<4>(v, m, w, q); wide_exchange<4, 3>(v, m, lds, t);
+    wide_inv_stage<3>(v, m, w, q); wide_exchange<3, 2>(v, m, lds, t);
+    wide_inv_stage<2>(v, m, w, q); wide_exchange<2, 1>(v, m, lds, t);
+    wide_inv_stage<1>(v, m, w, q); wide_exchange<1, 0>(v, m, lds, t);
+    wide_inv_stage<0>(v, m, w, q);
+#pragma unroll
+    for (int r = 0; r < 4; r++) cap_to(v[r], m[r], 8, q);
+}
+// coefficients 4 t + r of a limb's row, read through sigma_g when galois != 0
+template <int K3>
+__device__ __forceinline__ void wide_load(u64 (&v)[4], const u64* limb, u64 galois, uint32_t row, uint32_t t) {
+    if (galois) {
+        const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = bload(src, galois_src_fp(row * 1024u + 4u * t + (uint32_t)r, galois, 10 + K3) * 8u, 0);
+    } else {
+        const rsrc_t src = make_rsrc(limb + row * 1024u, 8192u);
+        bload2(src, t * 32u, 0, v[0], v[1]);
+        bload2(src, t * 32u, 16, v[2], v[3]);
+    }
+}
+
+template <int K3>
+__device__ __forceinline__ void wide_rows_inverse(const IntArgs& a, const IntTasks& tk, int task, u64* lds) {
+    const uint32_t t = threadIdx.x, unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1), e = unit >> K3;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const int prime = uniform(tk.prime[e]), pos = uniform(tk.pos[e]);
+    const u64 q = mod_int(a.primes, prime).q;
+    constexpr u64 n = (u64)1 << (10 + K3);
+    u64 v[4];
+    int m[4] = {1, 1, 1, 1};
+    WideTwiddles w;
+    wide_load<K3>(v, a.in + b * a.in_bs + (u64)(pos + a.in_pos_shift) * n, a.galois, row, t);
+    wide_twiddles<K3>(w, a.itw, a.itw_sh, prime, row, t);
+    wide_inverse(v, m, w, lds, t, q);
+    if (K3 == 0 && a.whole) {            // no columns behind
+        const Tw f = table_tw(a.consts, (u64)prime * CONST_WORDS);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = canonical(mul4(v[r], f, q), 4, q);
+    }
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)pos * n + row * 1024u, 8192u);
+#pragma unroll
+    for (int r = 0; r < 4; r++) bstore(dst, t * 8u, (uint32_t)r * 2048u, v[r]);
+}
+
+template <int K3>
+__device__ __forceinline__ void wide_rows_divide(const IntArgs& a, int task, u64* lds) {
+    const uint32_t t = threadIdx.x, unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1), e = unit >> K3;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const u64 q = mod_int(a.primes, (int)e).q;
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)e * n + row * 1024u, 8192u);
+    const bool with_add = a.add && (int)(b % a.add_div) < a.add_polys;
+    u64 v[4], acc[4], add[4] = {};
+    int m[4] = {16, 16, 16, 16};
+    WideTwiddles w;
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = bload(dst, t * 8u, (uint32_t)r * 2048u);
+    wide_twiddles<K3>(w, a.tw, a.tw_sh, (int)e, row, t);
+    wide_load<K3>(acc, a.acc + b * a.acc_bs + (u64)e * n, 0, row, t);
+    if (with_add)
+        wide_load<K3>(add, a.add + (b / a.add_div) * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, a.add_galois, row, t);
+    const Tw f = Tw{as_constu(a.factor)[e], as_constu(a.factor_sh)[e]};
+    wide_forward(v, m, w, lds, t, q, 8);
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = canonical(mul4(acc[r] + (q << 3) - v[r], f, q) + add[r], 5, q);     // acc is below 8 q
+    bstore2(dst, t * 32u, 0, v[0], v[1]);
+    bstore2(dst, t * 32u, 16, v[2], v[3]);
+}
+
+// A workgroup per (limb x, row, entry), four waves per digit (two digits at least, INNER_CHUNK at most: the caller's rule).  Each
+// four leave their digit's row in LDS in 30-bit halves; then the first eight waves form the sums of a polynomial each, and
+// take those of a special limb through the inverse levels.
+template <int K3>
+__device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64* lds) {
+    const uint32_t t = threadIdx.x & (WIDE_NT - 1);
+    const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WIDE_NT));
+    const uint32_t unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1);
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const int x = a.ext_limbs - 1 - (int)(unit >> K3);
+    const int prime = prime_at(x, a.l, a.L);
+    const u64 q = mod_int(a.primes, prime).q;
+    const WideMod wide = wide_mod(a.consts, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const bool special = x >= a.l, sums = part < 2;
+    u64 v[4], k[INNER_CHUNK][4];
+    int m[4] = {16, 16, 16, 16};
+    WideTwiddles w;
+    u64* slot = lds + part * WIDE_LDS;
+    const bool mine = part < a.n_digits, own = mine && x >= part * a.alpha && x < min((part + 1) * a.alpha, a.l);
+    if (own) {
+        wide_load<K3>(v, a.in + b * a.in_bs + (u64)x * n, a.galois, row, t);
+    } else if (mine) {
+        const rsrc_t src = make_rsrc(a.ext + b * a.ext_bs + (u64)(part * a.ext_limbs + x) * n + row * 1024u, 8192u);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = bload(src, t * 8u, (uint32_t)r * 2048u);
+        wide_twiddles<K3>(w, a.tw, a.tw_sh, prime, row, t);
+    }
+    if (sums) {
+#pragma unroll
+        for (int d = 0; d < INNER_CHUNK; d++)
+            if (d < a.n_digits) wide_load<K3>(k[d], a.key + ((u64)(2 * d + part) * a.total + prime) * n, 0, row, t);
+    }
+    // (the exchange between the first stages is the workgroup's: who transforms nothing keeps it company)
+    if (mine && !own) wide_forward(v, m, w, slot, t, q, 2);
+    else __syncthreads();
+    if (mine) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) slot[wide_at(4 * t + r)] = split30(v[r]);
+    }
+    if (sums && special) wide_twiddles<K3>(w, a.itw, a.itw_sh, prime, row, t);   // on their way while the sums are formed
+    __syncthreads();
+    if (sums) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            Acc3 acc = {0, 0, 0};
+#pragma unroll
+            for (int d = 0; d < INNER_CHUNK; d++)
+                if (d < a.n_digits) acc3_mad(acc, lds[d * WIDE_LDS + wide_at(4 * t + r)], split30(k[d][r]));
+            v[r] = acc3_reduce(acc, wide, q);
+            m[r] = 8;
+        }
+        if (!special) {
+            const rsrc_t dst = make_rsrc(a.sums + ((b * 2 + part) * a.l + x) * n + row * 1024u, 8192u);
+            bstore2(dst, t * 32u, 0, v[0], v[1]);
+            bstore2(dst, t * 32u, 16, v[2], v[3]);
+        }
+    }
+    if (!special) return;
+    __syncthreads();                                            // everyone has read the digits
+    if (!sums) {
+        __syncthreads();                                        // the exchange inside wide_inverse
+        return;
+    }
+    wide_inverse(v, m, w, slot, t, q);
+    const rsrc_t dst = make_rsrc(a.down + ((b * 2 + part) * (u64)(a.ext_limbs - a.l) + (u64)(x - a.l)) * n + row * 1024u, 8192u);
+#pragma unroll
+    for (int r = 0; r < 4; r++) bstore(dst, t * 8u, (uint32_t)r * 2048u, v[r]);
 }
 
 // ---------------------------------------------------------------------------
@@ -741,10 +930,47 @@ void ntt_int_kernel(IntArgs a, IntTasks tk, int n_tasks) {
         if constexpr (MODE == INT_CONVERT) convert_columns<K3>(a, lds);
         else plain_columns<K3, MODE == INT_INVERSE>(a, tk, n_tasks);
     } else {
-        if constexpr (MODE == INT_INVERSE) rows_inverse<K3>(a, tk, n_tasks, lds);
-        else if constexpr (MODE == INT_FORWARD) rows_forward<K3>(a, tk, n_tasks, lds);
+        if constexpr (MODE == INT_FORWARD) rows_forward<K3>(a, tk, n_tasks, lds);
         else if constexpr (MODE == INT_INNER) rows_inner<K3>(a, lds);
         else rows_divide<K3>(a, n_tasks, lds);
+    }
+}
+
+template <int K3, int MODE>
+__global__ __launch_bounds__(MODE == INT_INNER ? INNER_CHUNK * WIDE_NT : WIDE_NT, 4) void ntt_int_wide_kernel(IntArgs a, IntTasks tk, int first, int n_tasks) {
+    extern __shared__ u64 lds[];
+    const int per = (n_tasks + 7) >> 3, mine = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3), task = first + mine;
+    if ((int)(blockIdx.x >> 3) >= per || mine >= n_tasks) return;
+    if constexpr (MODE == INT_INVERSE) wide_rows_inverse<K3>(a, tk, task, lds);
+    else if constexpr (MODE == INT_INNER) wide_rows_inner<K3>(a, task, lds);
+    else wide_rows_divide<K3>(a, task, lds);
+}
+template <int K3, int MODE>
+static hipError_t launch_wide_k3(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
+    static char name[40] = "";      // what rocprofv3 prints for this instantiation
+    if (!name[0]) snprintf(name, sizeof name, "ntt_int_wide_kernel<%d, %d>", K3, MODE);
+    const unsigned rows = MODE != INT_INNER ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
+    ProfScope prof__(name, st);
+    for (u64 first = 0; first < tasks; first += 1 << 22) {           // a grid holds fewer than 2^32 threads
+        const u64 count = tasks - first < (1 << 22) ? tasks - first : 1 << 22;
+        hipLaunchKernelGGL((ntt_int_wide_kernel<K3, MODE>), dim3((unsigned)((count + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st,
+                           a, tk, (int)first, (int)count);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+template <int MODE>
+static hipError_t launch_wide(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
+    switch (a.log_n) {
+        case 10: return launch_wide_k3<0, MODE>(a, tk, tasks, st);
+        case 11: return launch_wide_k3<1, MODE>(a, tk, tasks, st);
+        case 12: return launch_wide_k3<2, MODE>(a, tk, tasks, st);
+        case 13: return launch_wide_k3<3, MODE>(a, tk, tasks, st);
+        case 14: return launch_wide_k3<4, MODE>(a, tk, tasks, st);
+        case 15: return launch_wide_k3<5, MODE>(a, tk, tasks, st);
+        case 16: return launch_wide_k3<6, MODE>(a, tk, tasks, st);
+        default: return hipErrorInvalidValue;
     }
 }
 
@@ -775,21 +1001,34 @@ static hipError_t launch_any(int log_n, dim3 grid, unsigned threads, size_t lds,
         default: return hipErrorInvalidValue;
     }
 }
+// Rows by four waves or by one.  Inverse rows: always four (8 rows 8.5 -> 4.7 us, 512 rows 10 -> 6.3, 4096 rows 29 -> 25, 16384
+// rows 89 -> 90).  Rows of a division: 24 rows 10.3 -> 5.2 us, 1024 rows 15 -> 9.7, 8192 rows 63 -> 62, but 32768 rows 223 -> 247:
+// the wave of its own waits for fewer exchanges.  Inner products: while all workgroups are resident at once, 512 of eight
+// waves (up to two digits) or 256 of twelve or sixteen: one wave a digit -> four, 16 tasks of three digits 17.6 -> 12.8 us, 256 of
+// them 18.5 -> 14.4, 352 23 -> 26; of two digits 512 tasks 22 -> 17.6, 768 24.7 -> 24.3, 1024 29 -> 30.
+#define WIDE_DIVIDE_ROWS 8192
+static u64 wide_inner_tasks(int n_digits) { return n_digits > INNER_CHUNK ? 0 : n_digits <= 2 ? 512 : 256; }
+
 template <int MODE, bool COLUMNS>
 static hipError_t launch_waves(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
     if (tasks > 0x7fffff00u) return hipErrorInvalidValue;
-    constexpr bool inner = MODE == INT_INNER;                  // a task per workgroup
-    const int slots = a.n_digits < 2 ? 2 : a.n_digits < INNER_CHUNK ? a.n_digits : INNER_CHUNK;
-    const u64 per_block = inner ? 1 : ROWS_NT / 64;
-    const unsigned threads = inner && slots == 2 ? 128 : ROWS_NT;
-    const size_t lds = COLUMNS ? 0 : (size_t)(inner ? slots : ROWS_NT / 64) * ROW_LDS * 8;
-    u64 blocks = ((tasks + per_block - 1) / per_block + 7) / 8 * 8;
-    if (inner) {                                               // eight times what the first XCD takes
-        const uint32_t parts = inner_parts(a.log_n - 10);
-        blocks = (u64)((a.ext_limbs + parts - 1) / parts * inner_rows(a.log_n - 10)) * a.n_entries * 8;
-        if (blocks > 0x7fffff00u) return hipErrorInvalidValue;
+    if constexpr (MODE == INT_INVERSE && !COLUMNS) {
+        return launch_wide<MODE>(a, tk, tasks, st);
+    } else {
+        const u64 blocks = ((tasks + ROWS_NT / 64 - 1) / (ROWS_NT / 64) + 7) / 8 * 8;
+        const size_t lds = COLUMNS ? 0 : (size_t)(ROWS_NT / 64) * ROW_LDS * 8;
+        return launch_any<MODE, COLUMNS>(a.log_n, dim3((unsigned)blocks), ROWS_NT, lds, a, tk, tasks, st);
     }
-    return launch_any<MODE, COLUMNS>(a.log_n, dim3((unsigned)blocks), threads, lds, a, tk, tasks, st);
+}
+static hipError_t launch_inner(const IntArgs& a, hipStream_t st) {
+    const u64 tasks = ((u64)a.ext_limbs * a.n_entries) << (a.log_n - 10);
+    if (tasks <= wide_inner_tasks(a.n_digits)) return launch_wide<INT_INNER>(a, IntTasks{}, tasks, st);
+    const int slots = a.n_digits < 2 ? 2 : a.n_digits < INNER_CHUNK ? a.n_digits : INNER_CHUNK;
+    const uint32_t parts = inner_parts(a.log_n - 10);             // a workgroup per task, eight times what the first XCD takes
+    const u64 blocks = (u64)((a.ext_limbs + parts - 1) / parts * inner_rows(a.log_n - 10)) * a.n_entries * 8;
+    if (blocks > 0x7fffff00u) return hipErrorInvalidValue;
+    return launch_any<INT_INNER, false>(a.log_n, dim3((unsigned)blocks), slots == 2 ? 128 : ROWS_NT, (size_t)slots * ROW_LDS * 8, a,
+                                        IntTasks{}, tasks, st);
 }
 
 static bool base_ok(const IntArgs& a) {
@@ -871,7 +1110,8 @@ hipError_t launch_divide_rows_int(const IntArgs& a, hipStream_t st) {
     DRY_RUN_RETURN();
     if (!convert_ok(a) || a.n_digits != 1 || a.own || !a.acc || !a.factor || !a.factor_sh || a.ext_limbs > a.l || (a.add && a.add_div < 1))
         return hipErrorInvalidValue;
-    return launch_waves<INT_CONVERT, false>(a, IntTasks{}, ((u64)a.ext_limbs * a.n_entries) << (a.log_n - 10), st);
+    const u64 rows = ((u64)a.ext_limbs * a.n_entries) << (a.log_n - 10);
+    return rows <= WIDE_DIVIDE_ROWS ? launch_wide<INT_CONVERT>(a, IntTasks{}, rows, st) : launch_waves<INT_CONVERT, false>(a, IntTasks{}, rows, st);
 }
 
 hipError_t launch_inner_rows_int(const IntArgs& a, hipStream_t st) {
@@ -879,5 +1119,5 @@ hipError_t launch_inner_rows_int(const IntArgs& a, hipStream_t st) {
     if (!base_ok(a) || !a.in || !a.ext || !a.key || !a.sums || !a.down || a.alpha < 1 || a.n_digits < 1 || a.n_digits * a.alpha < a.l ||
         (a.n_digits - 1) * a.alpha >= a.l || a.ext_limbs <= a.l || a.ext_limbs - a.l + a.L > a.total)
         return hipErrorInvalidValue;
-    return launch_waves<INT_INNER, false>(a, IntTasks{}, ((u64)a.ext_limbs * a.n_entries) << (a.log_n - 10), st);
+    return launch_inner(a, st);
 }

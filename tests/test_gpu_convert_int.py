@@ -20,6 +20,13 @@ POINTS = [
     (15, [58] * 8, 1, 60, 8, 1),
     (16, [60] * 6, 1, 60, 6, 1),                 # more sources than fit the LDS at once
     (16, [52, 51, 30], 3, 60, 3, 2),
+    (10, [60, 59, 58], 3, 60, 3, 70),            # inner products: few limbs shared out over eight XCDs, one row
+    (11, [60, 59, 58, 57], 2, 60, 4, 42),        # rows by four waves: 504 inner products of two digits, then more than 512
+    (11, [60, 59, 58, 57], 2, 60, 4, 43),
+    (12, [60, 45, 30], 3, 60, 3, 16),            # 256 of three digits, then more
+    (12, [60, 45, 30], 3, 60, 3, 17),
+    (14, [55, 51, 60, 30], 4, 60, 4, 3),         # four digits: sixteen waves
+    (15, [58] * 8, 3, 60, 8, 17),                # more than 8192 rows of a division
 ]
 
 
