@@ -13,9 +13,9 @@
 // whatever else is idle, so a call with fewer limb-polynomials than compute units is bound by that latency.  Here a
 // polynomial at N = 2^15 is 32 waves of rows and 32 tiles of columns, nothing waits for a whole polynomial except
 // the launch boundary, and the conversion inputs never travel through memory.  rotLeft against whole-polynomial workgroups
-// (which also sent the extended digits through memory once more): 64 ciphertexts at N = 2^15, 16 limbs, 1.84 -> 1.33 ms;
-// 3 at 17 limbs 223 -> 109 us; one at N = 2^13, 8 limbs, 64 -> 32 us.  Large batches are bound by fp64 issue in the columns
-// and by memory in the rows, single ciphertexts by five launches of 5-8 us, each a chain of dependent levels.
+// (which also sent the extended digits through memory once more): 64 ciphertexts at N = 2^15, 16 limbs, 1.84 -> 1.31 ms;
+// 3 at 17 limbs 223 -> 105 us; one at N = 2^13, 8 limbs, 64 -> 27 us.  Large batches are bound by fp64 issue in the columns
+// and by memory in the rows, single ciphertexts by five launches of 4-8 us, each a chain of dependent levels.
 //
 // A wave holds 1024 coefficients, 16 per lane.  Five levels on a five-bit field take four in registers and the one on
 // the field's lowest bit after exchanging that bit (lane bit 5) with a register bit by v_permlane32_swap, so a row needs
@@ -650,6 +650,281 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
 }
 
 // ---------------------------------------------------------------------------
+// rows by four waves each: calls with few rows
+// ---------------------------------------------------------------------------
+// A wave that keeps a row to itself is a chain of eighty butterflies a lane with its loads, twiddles and products in between, and
+// with fewer rows than the chip has SIMDs nothing runs beside it.  Here a thread holds four coefficients, two levels at a time,
+// and everything it will need is on its way before the first level; only the exchange behind the first two levels crosses waves.
+//   stage s, levels 2 s and 2 s + 1: registers 0 .. 3 of thread t are 2^p apart, p = 8 - 2 s (wide_element)
+#define WIDE_NT 256
+#define WIDE_LDS 1280    // 64-bit words per row: four words of padding per sixteen, so that a thread's four stay together
+#define WIDE_DIGITS 4    // at most, in an inner product: four waves each
+__device__ __forceinline__ uint32_t wide_at(uint32_t i) { return i + ((i >> 4) << 2); }
+template <int S>
+__device__ __forceinline__ uint32_t wide_element(uint32_t t, uint32_t r) {
+    constexpr int p = 8 - 2 * S;
+    return ((t >> p) << (p + 2)) | (r << p) | (t & ((1u << p) - 1));
+}
+struct WideTwiddles { double w[5][3]; };     // per stage: level 2 s, then the two groups of level 2 s + 1
+// (t: thread of the row; tables as split_table_words lays them out)
+__device__ __forceinline__ void wide_twiddles(WideTwiddles& w, const double* table, u64 stride, int prime, uint32_t row, uint32_t t, Modulus q) {
+    const double* head = table + (u64)prime * stride;
+    const double* tab = head + HEAD + (u64)row * SPLIT_ROW;
+    const rsrc_t tr = make_rsrc(tab, SPLIT_ROW * 8), hr = make_rsrc(head + 32, 16 * 8);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(t >> 6));
+    const uint32_t g = t >> 4, b = t >> 3, k = t & 7, odd = (t >> 2) & 1;
+    w.w[2][0] = bloadf(tr, ((g & 1) * 8 + (g >> 1)) * 8u, 16 * 8);
+    bload2(tr, g * 16u, 32 * 8, w.w[2][1], w.w[2][2]);
+    const double c1 = bloadf(tr, b * 8u, 64 * 8), c2 = bloadf(tr, b * 8u, 96 * 8), c3 = bloadf(tr, b * 8u, 128 * 8);
+    const double f1 = bloadf(hr, odd * 8u, 0), f3 = bloadf(hr, k * 8u, 0);
+    double f20, f21;
+    bload2(hr, odd * 16u, 0, f20, f21);
+    const uint32_t last = ((k >> 1) * 128 + b * 2 + (k & 1)) * 8u;
+    w.w[4][1] = bloadf(tr, last, 160 * 8);
+    w.w[4][2] = bloadf(tr, last, 160 * 8 + 512);
+    w.w[0][0] = as_const(tab)[1]; w.w[0][1] = as_const(tab)[2]; w.w[0][2] = as_const(tab)[3];
+    w.w[1][0] = as_const(tab)[4 + wave]; w.w[1][1] = as_const(tab)[8 + 2 * wave]; w.w[1][2] = as_const(tab)[9 + 2 * wave];
+    w.w[3][0] = fp_mulmod(c1, f1, q.p, q.pinv);
+    w.w[3][1] = fp_mulmod(c2, f20, q.p, q.pinv);
+    w.w[3][2] = fp_mulmod(c2, f21, q.p, q.pinv);
+    w.w[4][0] = fp_mulmod(c3, f3, q.p, q.pinv);
+}
+// registers of stage FROM to registers of stage TO; the waves keep to their quarter of the row except between stages 0 and 1
+template <int FROM, int TO>
+__device__ __forceinline__ void wide_exchange(double (&v)[4], float (&m)[4], double* lds, uint32_t t) {
+    float top = 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        lds[wide_at(wide_element<FROM>(t, r))] = v[r];
+        top = fmaxf(top, m[r]);
+    }
+    xchg_sync<FROM + TO != 1>();
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        v[r] = lds[wide_at(wide_element<TO>(t, r))];
+        m[r] = top;
+    }
+    xchg_sync<true>();
+}
+template <int S>
+__device__ __forceinline__ void wide_fwd_stage(double (&v)[4], float (&m)[4], const WideTwiddles& w, Modulus q) {
+    constexpr float mw = S < 3 ? 0.5f : 0.6f;
+    fwd_bfly(v[0], v[2], m[0], m[2], w.w[S][0], mw, q);
+    fwd_bfly(v[1], v[3], m[1], m[3], w.w[S][0], mw, q);
+    fwd_bfly(v[0], v[1], m[0], m[1], w.w[S][1], mw, q);
+    fwd_bfly(v[2], v[3], m[2], m[3], w.w[S][2], mw, q);
+}
+template <int S>
+__device__ __forceinline__ void wide_inv_stage(double (&v)[4], float (&m)[4], const WideTwiddles& w, Modulus q) {
+    constexpr float mw = S < 3 ? 0.5f : 0.6f;
+    inv_bfly(v[0], v[1], m[0], m[1], w.w[S][1], mw, q);
+    inv_bfly(v[2], v[3], m[2], m[3], w.w[S][2], mw, q);
+    inv_bfly(v[0], v[2], m[0], m[2], w.w[S][0], mw, q);
+    inv_bfly(v[1], v[3], m[1], m[3], w.w[S][0], mw, q);
+}
+__device__ __forceinline__ void wide_cap(double (&v)[4], float (&m)[4], float cap, Modulus q) {
+#pragma unroll
+    for (int r = 0; r < 4; r++)
+        if (m[r] > cap) v[r] = fp_norm(v[r], q.p, q.pinv);
+}
+// in: coefficient 256 r + t, below m p; out: 4 t + r, below cap p.  The row's LDS is free when the first of its threads comes here.
+__device__ __forceinline__ void wide_forward(double (&v)[4], float bound, const WideTwiddles& w, double* lds, uint32_t t, Modulus q, float cap) {
+    float m[4] = {bound, bound, bound, bound};
+    wide_fwd_stage<0>(v, m, w, q); wide_exchange<0, 1>(v, m, lds, t);
+    wide_fwd_stage<1>(v, m, w, q); wide_exchange<1, 2>(v, m, lds, t);
+    wide_fwd_stage<2>(v, m, w, q); wide_exchange<2, 3>(v, m, lds, t);
+    wide_fwd_stage<3>(v, m, w, q); wide_exchange<3, 4>(v, m, lds, t);
+    wide_fwd_stage<4>(v, m, w, q);
+    wide_cap(v, m, cap, q);
+}
+// in: coefficient 4 t + r, below m p; out: 256 r + t, below 1.01 p
+__device__ __forceinline__ void wide_inverse(double (&v)[4], float bound, const WideTwiddles& w, double* lds, uint32_t t, Modulus q) {
+    float m[4] = {bound, bound, bound, bound};
+    wide_inv_stage<4>(v, m, w, q); wide_exchange<4, 3>(v, m, lds, t);
+    wide_inv_stage<3>(v, m, w, q); wide_exchange<3, 2>(v, m, lds, t);
+    wide_inv_stage<2>(v, m, w, q); wide_exchange<2, 1>(v, m, lds, t);
+    wide_inv_stage<1>(v, m, w, q); wide_exchange<1, 0>(v, m, lds, t);
+    wide_inv_stage<0>(v, m, w, q);
+    wide_cap(v, m, 1.01f, q);
+}
+// coefficients 4 t + r of a limb's row, read through sigma_g when galois != 0
+template <int K3>
+__device__ __forceinline__ void wide_load(double (&v)[4], const void* limb, u64 galois, uint32_t row, uint32_t t) {
+    if (galois) {
+        const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = bloadf(src, galois_src_fp(row * 1024u + 4u * t + (uint32_t)r, galois, 10 + K3) * 8u, 0);
+    } else {
+        const rsrc_t src = make_rsrc((const u64*)limb + row * 1024u, 8192u);
+        bload2(src, t * 32u, 0, v[0], v[1]);
+        bload2(src, t * 32u, 16, v[2], v[3]);
+    }
+}
+__device__ __forceinline__ void wide_from_residues(double (&v)[4]) {
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = fp_from_u64((u64)__double_as_longlong(v[r]));
+}
+__device__ __forceinline__ void wide_store(rsrc_t dst, uint32_t t, const double (&v)[4]) {      // 4 t + r
+#pragma unroll
+    for (int r = 0; r < 4; r += 2) {
+        const u32x4_t d = {lo32(v[r]), hi32(v[r]), lo32(v[r + 1]), hi32(v[r + 1])};
+        __builtin_amdgcn_raw_buffer_store_b128(d, dst, (int)(t * 32u), r * 8, 0);
+    }
+}
+__device__ __forceinline__ void wide_store_residues(rsrc_t dst, uint32_t t, double (&v)[4], Modulus q) {
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = __longlong_as_double((long long)fp_canonical(v[r], q.p, q.pinv));
+    wide_store(dst, t, v);
+}
+
+template <int K3>
+__device__ __forceinline__ void wide_rows_inverse(const ConvertArgs& a, int task, double* lds) {
+    const uint32_t t = threadIdx.x, unit = (uint32_t)task / a.n_entries, b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t row = unit & ((1u << K3) - 1), k = unit >> K3;
+    const int prime = prime_at(a.src_pos0 + (int)k, a.l, a.L);
+    const Modulus q = modulus(a.fprimes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    double v[4];
+    WideTwiddles w;
+    wide_load<K3>(v, a.in + (u64)b * a.in_bs + (u64)(a.src_pos0 + (int)k) * n, a.galois, row, t);
+    wide_twiddles(w, a.sinv, a.table_stride, prime, row, t, q);
+    wide_from_residues(v);
+    wide_inverse(v, 1.0f, w, lds, t, q);
+    const rsrc_t dst = make_rsrc(a.mid + ((u64)b * a.n_src + k) * n + row * 1024u, 8192u);
+#pragma unroll
+    for (int r = 0; r < 4; r++) bstoref(dst, t * 8u, (uint32_t)r * 2048u, v[r]);
+}
+
+template <int K3, int MODE>
+__device__ __forceinline__ void wide_rows_forward(const ConvertArgs& a, int task, double* lds) {
+    const uint32_t t = threadIdx.x, unit = (uint32_t)task / a.n_entries;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t row = unit & ((1u << K3) - 1);
+    int e = (int)(unit >> K3), digit = 0;
+    while (digit + 1 < a.n_digits && e >= a.ext_limbs - a.dg[digit].own_n) { e -= a.ext_limbs - a.dg[digit].own_n; digit++; }
+    if (e >= a.dg[digit].own_lo) e += a.dg[digit].own_n;
+    const int prime = prime_at(e, a.l, a.L);
+    const Modulus q = modulus(a.fprimes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n + row * 1024u, 8192u);
+    double v[4], acc[4], add[4];
+    WideTwiddles w;
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = bloadf(dst, t * 8u, (uint32_t)r * 2048u);
+    wide_twiddles(w, a.sfwd, a.table_stride, prime, row, t, q);
+    const bool with_add = MODE == FP_FWD_CONV_FINAL && a.add && (int)(b % a.add_div) < a.add_polys;
+    if (MODE != FP_FWD_CONV) wide_load<K3>(acc, a.acc + b * a.acc_bs + (u64)e * n, 0, row, t);
+    if (with_add) wide_load<K3>(add, a.add + (b / a.add_div) * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, 0, row, t);
+    wide_forward(v, COLUMNS_BOUND, w, lds, t, q, MODE == FP_FWD_CONV ? BOUND_LIMIT : 5.2f);
+    if (MODE == FP_FWD_CONV) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = fp_norm(v[r], q.p, q.pinv);
+        wide_store(dst, t, v);
+        return;
+    }
+    if (MODE == FP_FWD_SUB) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = acc[r] - v[r];
+    } else {
+        const double pin = as_const(a.pinv_tab)[prime];
+        wide_from_residues(acc);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = fp_mulmod(acc[r] - v[r], pin, q.p, q.pinv);
+        if (with_add) {
+            wide_from_residues(add);
+#pragma unroll
+            for (int r = 0; r < 4; r++) v[r] += add[r];
+        }
+    }
+    wide_store_residues(dst, t, v, q);
+}
+
+// A workgroup per (limb x, row, entry), four waves per digit.  Each four leave their digit's row in LDS; the first two take a
+// polynomial each from there on: sums, and the inverse rows of a source or the division's rows, as rows_inner does.
+template <int K3, int MODE>
+__device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const InnerArgs& g, int task, double* lds) {
+    const uint32_t t = threadIdx.x & (WIDE_NT - 1);
+    const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WIDE_NT));
+    const uint32_t unit = (uint32_t)task / a.n_entries;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t row = unit & ((1u << K3) - 1);
+    const int x = g.x_end - 1 - (int)(unit >> K3);
+    const int prime = prime_at(x, a.l, a.L);
+    const Modulus q = modulus(a.fprimes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const bool sums = part < 2, source = MODE == FP_INV_D_TO_Y && x >= g.n_acc, mine = part < a.n_digits;
+    const bool own = mine && x >= a.dg[part].own_lo && x < a.dg[part].own_lo + a.dg[part].own_n;
+    const bool with_add = sums && x < a.l && part < g.add_polys;
+    const u64 out_limb = source ? (b * 2 + part) * (u64)(a.ext_limbs - g.n_acc) + (u64)(x - g.n_acc) : (b * 2 + part) * (u64)g.n_acc + (u64)x;
+    double* dst_p = (source ? g.down : MODE == FP_FWD_CONV_SUB ? (double*)g.out : g.acc) + (sums ? out_limb : 0) * n + row * 1024u;
+    const rsrc_t dst = make_rsrc(dst_p, 8192u);
+    double v[4], k[WIDE_DIGITS][4], add[4], div[4];
+    WideTwiddles w;
+    double* slot = lds + part * WIDE_LDS;
+    if (own) {
+        wide_load<K3>(v, g.own + b * g.own_bs + (u64)x * n, g.galois, row, t);
+    } else if (mine) {
+        const rsrc_t src = make_rsrc((const double*)a.out + b * a.out_bs + (u64)(a.dg[part].out_pos0 + x) * n + row * 1024u, 8192u);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = bloadf(src, t * 8u, (uint32_t)r * 2048u);
+    }
+    if (!own || MODE == FP_FWD_CONV_SUB) wide_twiddles(w, a.sfwd, a.table_stride, prime, row, t, q);
+    if (sums) {
+#pragma unroll
+        for (int d = 0; d < WIDE_DIGITS; d++)
+            if (d < a.n_digits) wide_load<K3>(k[d], g.key + (((u64)d * 2 + part) * a.total + prime) * n, 0, row, t);
+        if (with_add) wide_load<K3>(add, g.add + b * g.add_bs + (u64)part * g.add_ps + (u64)x * n, g.galois, row, t);
+        if (MODE == FP_FWD_CONV_SUB) {
+#pragma unroll
+            for (int r = 0; r < 4; r++) div[r] = bloadf(dst, t * 8u, (uint32_t)r * 2048u);
+        }
+    }
+    // (the exchange between the first stages is the workgroup's: who transforms nothing keeps it company)
+    if (mine && !own) wide_forward(v, COLUMNS_BOUND, w, slot, t, q, IP_CAP);
+    else __syncthreads();
+    if (own) wide_from_residues(v);
+    if (mine) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) slot[wide_at(4 * t + r)] = v[r];
+    }
+    if (sums && source) wide_twiddles(w, a.sinv, a.table_stride, prime, row, t, q);      // on their way while the sums are formed
+    __syncthreads();
+    if (sums) {
+        const double c1 = as_const(g.c1)[x];
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            double sum = 0.0;
+#pragma unroll
+            for (int d = 0; d < WIDE_DIGITS; d++)
+                if (d < a.n_digits) sum += fp_mulmod(lds[d * WIDE_LDS + wide_at(4 * t + r)], k[d][r], q.p, q.pinv);
+            v[r] = fp_mulmod(sum, c1, q.p, q.pinv);
+        }
+        if (with_add) {
+            wide_from_residues(add);
+#pragma unroll
+            for (int r = 0; r < 4; r++) v[r] += add[r];
+        }
+        if (!source && MODE == FP_INV_D_TO_Y) wide_store(dst, t, v);
+    }
+    if (!source && MODE == FP_INV_D_TO_Y) return;
+    __syncthreads();                                            // everyone has read the digits
+    if (!sums) {
+        __syncthreads();                                        // the exchange inside the transforms below
+        return;
+    }
+    if (MODE == FP_FWD_CONV_SUB) {
+        wide_forward(div, COLUMNS_BOUND, w, slot, t, q, 5.2f);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] -= div[r];
+        wide_store_residues(dst, t, v, q);
+    } else {
+        wide_inverse(v, 2.75f, w, slot, t, q);
+#pragma unroll
+        for (int r = 0; r < 4; r++) bstoref(dst, t * 8u, (uint32_t)r * 2048u, v[r]);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // whole polynomials by columns and rows: calls with few of them (encode, decode, encryption of a few vectors)
 // ---------------------------------------------------------------------------
 // The single-launch transform of ntt_fp.hip reads and writes a polynomial once but takes 13 / 20 / 35 us at N = 2^13 / 14 /
@@ -759,6 +1034,37 @@ __device__ __forceinline__ void plain_rows(const FpArgs& a, const FpTask& tk, do
     }
 }
 
+// the same by four waves a row
+template <int K3, int MODE>
+__global__ __launch_bounds__(WIDE_NT, 4) void ntt_fp_split_wide_kernel(FpArgs a, FpTask tk) {
+    __shared__ double lds[WIDE_LDS];
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const int per = (a.n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || task >= a.n_tasks) return;
+    const uint32_t t = threadIdx.x, row = (uint32_t)task & ((1u << K3) - 1);
+    const int unit = task >> K3, e = unit / a.n_entries;
+    const u64 b = unit - e * a.n_entries;
+    const int prime = tk.prime[e];
+    const Modulus q = modulus(a.fprimes, prime);
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)tk.pos[e] * n + (u64)row * 1024u, 8192u);
+    double v[4];
+    WideTwiddles w;
+    if (MODE == FP_INV_PLAIN) {
+        wide_load<K3>(v, a.in + b * a.in_bs + (u64)tk.pos[e] * n, 0, row, t);
+        wide_twiddles(w, a.sinv, a.table_stride, prime, row, t, q);
+        wide_from_residues(v);
+        wide_inverse(v, 1.0f, w, lds, t, q);
+#pragma unroll
+        for (int r = 0; r < 4; r++) bstoref(dst, t * 8u, (uint32_t)r * 2048u, v[r]);
+    } else {
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] = bloadf(dst, t * 8u, (uint32_t)r * 2048u);
+        wide_twiddles(w, a.sfwd, a.table_stride, prime, row, t, q);
+        wide_forward(v, COLUMNS_BOUND, w, lds, t, q, BOUND_LIMIT);
+        wide_store_residues(dst, t, v, q);
+    }
+}
+
 template <int K3, int MODE, bool COLUMNS>
 __global__ __launch_bounds__(ROWS_NT, 4) void ntt_fp_split_kernel(FpArgs a, FpTask tk) {
     if constexpr (COLUMNS) {
@@ -847,6 +1153,47 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a)
     for (int r = 0; r < 16; r++) bstore(r0, lane8, (uint32_t)r * 512u, fp_canonical(e[r] + fp_from_u64(s[r]), q.p, q.pinv));
 }
 
+// the same by four waves a row, the two transforms side by side
+template <int K3>
+__global__ __launch_bounds__(2 * WIDE_NT, 4) void encrypt_rows_wide_kernel(EncryptArgs a) {
+    __shared__ double lds[2 * WIDE_LDS];
+    constexpr u64 n = (u64)1 << (10 + K3);
+    const int n_tasks = (a.n_entries * a.limbs) << K3, per = (n_tasks + 7) >> 3;
+    const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
+    const uint32_t t = threadIdx.x & (WIDE_NT - 1);
+    const int poly = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WIDE_NT));
+    const int unit = task / a.n_entries;
+    const u64 b = task - unit * a.n_entries;
+    const uint32_t row = (uint32_t)unit & ((1u << K3) - 1);
+    const int limb = unit >> K3;
+    const Modulus q = modulus(a.fprimes, limb);
+    const rsrc_t dst = make_rsrc(a.ct + ((b * 2 + poly) * a.limbs + limb) * n + (u64)row * 1024u, 8192u);
+    double v[4], s[4], m[4];
+    WideTwiddles w;
+    double* slot = lds + poly * WIDE_LDS;
+#pragma unroll
+    for (int r = 0; r < 4; r++) v[r] = bloadf(dst, t * 8u, (uint32_t)r * 2048u);
+    wide_twiddles(w, a.sfwd, a.table_stride, limb, row, t, q);
+    if (poly == 0) {
+        wide_load<K3>(s, a.secret + limb * n, 0, row, t);
+        wide_load<K3>(m, a.pt[b] + limb * n, 0, row, t);
+    }
+    wide_forward(v, COLUMNS_BOUND, w, slot, t, q, poly ? 5.2f : 3.0f);       // 3 + 1 (message) + 2.5 (a s) stays within 8 p
+    if (poly) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) slot[wide_at(4 * t + r)] = v[r];
+    }
+    __syncthreads();
+    if (poly == 0) {
+        wide_from_residues(s);
+        wide_from_residues(m);
+#pragma unroll
+        for (int r = 0; r < 4; r++) v[r] += m[r] - fp_mulmod(lds[WIDE_LDS + wide_at(4 * t + r)], s[r], q.p, q.pinv);
+    }
+    wide_store_residues(dst, t, v, q);
+}
+
 // ---------------------------------------------------------------------------
 // the kernel family and its launches
 // ---------------------------------------------------------------------------
@@ -867,6 +1214,17 @@ __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), fp_waves(K3, COLUMNS)) v
         else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE>(a, g, OneStep{}, n_tasks, lds);
         else rows_forward<K3, MODE>(a, n_tasks, lds);
     }
+}
+
+constexpr bool fp_inner(int mode) { return mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB; }
+template <int K3, int MODE>
+__global__ __launch_bounds__(fp_inner(MODE) ? WIDE_DIGITS * WIDE_NT : WIDE_NT, 4) void ntt_fp_wide_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
+    extern __shared__ double wide_lds[];
+    const int per = (n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
+    if constexpr (MODE == FP_INV_TO_Y) wide_rows_inverse<K3>(a, task, wide_lds);
+    else if constexpr (fp_inner(MODE)) wide_rows_inner<K3, MODE>(a, g, task, wide_lds);
+    else wide_rows_forward<K3, MODE>(a, task, wide_lds);
 }
 
 // the inner products' rows for several rotations of the same digits
@@ -912,10 +1270,36 @@ static hipError_t launch_one(dim3 grid, unsigned threads, size_t lds, const Conv
     return hipGetLastError();
 }
 
+// Rows by four waves or by one: up to about eight waves a SIMD of the former (inverse rows 64: 5.8 -> 4.0 us, 1088: 9.3 -> 7.4, 2176:
+// 12.7 -> 10.2, 4352: 18.1 -> 18.4, 26112: 76 -> 93; rows of a rescale 192: 6.5 -> 4.9, 2048: 12.6 -> 11.6, 2816: 13.4 -> 14.0, 16384:
+// 65 -> 89: four exchanges a row instead of two).  Inner products: while all workgroups are resident at once, 512 of eight waves (up to
+// two digits) or 256 of twelve or sixteen (two digits 24: 8.9 -> 8.0 us, 384: 13.8 -> 12.7, 768: 16.3 -> 18.0; three digits 128: 12.1 -> 9.4,
+// 256: 13.2 -> 10.7, 736: 21 -> 26; four digits 256: 14.9 -> 11.4, 320: 19.3 -> 20.1).
+#define WIDE_ROWS 2048
+static u64 wide_inner_tasks(int n_digits) { return n_digits > WIDE_DIGITS ? 0 : n_digits <= 2 ? 512 : 256; }
+template <int K3, int MODE>
+static hipError_t launch_wide_k3(const ConvertArgs& a, const InnerArgs& g, u64 tasks, hipStream_t st) {
+    static char name[40] = "";      // the stage's, as for rows by one wave; rocprofv3 prints ntt_fp_wide_kernel<K3, MODE>
+    if (!name[0]) snprintf(name, sizeof name, "ntt_fp_kernel<%d, %d, false>", K3, MODE);
+    const unsigned rows = !fp_inner(MODE) ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
+    ProfScope prof__(name, st);
+    hipLaunchKernelGGL((ntt_fp_wide_kernel<K3, MODE>), dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st, a, g,
+                       (int)tasks);
+    return hipGetLastError();
+}
+
 template <int MODE>
 static hipError_t launch_rows(const ConvertArgs& a, const InnerArgs& g, u64 limbs, hipStream_t st) {
     const u64 tasks = (limbs * a.n_entries) << (a.log_n - 10);
     if (tasks > 0x7fffff00u) return hipErrorInvalidValue;
+    if (tasks <= (fp_inner(MODE) ? wide_inner_tasks(a.n_digits) : WIDE_ROWS)) {
+        switch (a.log_n) {
+            case 12: return launch_wide_k3<2, MODE>(a, g, tasks, st);
+            case 13: return launch_wide_k3<3, MODE>(a, g, tasks, st);
+            case 14: return launch_wide_k3<4, MODE>(a, g, tasks, st);
+            default: return launch_wide_k3<5, MODE>(a, g, tasks, st);
+        }
+    }
     constexpr unsigned threads = fp_threads(MODE, false);
     const u64 per_block = threads == 128 ? 1 : threads / 64;     // a pair of waves shares a task of the inner products
     const dim3 grid((unsigned)(((tasks + per_block - 1) / per_block + 7) / 8 * 8));
@@ -1067,14 +1451,16 @@ static hipError_t launch_split(int log_n, FpArgs a, const FpTask& tk, bool colum
     const u64 polys = (u64)tk.period * a.n_entries;
     const int tiles = log_n == 15 ? 32 : 16;
     a.n_tasks = (int)(columns ? polys * tiles : polys << (log_n - 10));
-    const dim3 grid((unsigned)((((u64)a.n_tasks + 3) / 4 + 7) / 8 * 8));
-    static char names[4][2][40];
+    const bool wide = !columns && a.n_tasks <= WIDE_ROWS;
+    const dim3 grid((unsigned)((((u64)a.n_tasks + (wide ? 0 : 3)) / (wide ? 1 : 4) + 7) / 8 * 8));
+    static char names[4][2][40];    // the stage's, whether a row goes by one wave or by four
     char* name = names[log_n - 12][columns];
     if (!name[0]) snprintf(name, 40, "ntt_fp_split_kernel<%d, %d, %s>", log_n - 10, MODE, columns ? "true" : "false");
     ProfScope prof__(name, st);
 #define SPLIT_CASE(K3)                                                                                             \
     case 10 + K3:                                                                                                  \
         if (columns) hipLaunchKernelGGL((ntt_fp_split_kernel<K3, MODE, true>), grid, dim3(ROWS_NT), 0, st, a, tk); \
+        else if (wide) hipLaunchKernelGGL((ntt_fp_split_wide_kernel<K3, MODE>), grid, dim3(WIDE_NT), 0, st, a, tk); \
         else hipLaunchKernelGGL((ntt_fp_split_kernel<K3, MODE, false>), grid, dim3(ROWS_NT), 0, st, a, tk);        \
         break;
     switch (log_n) {
@@ -1110,6 +1496,11 @@ static hipError_t launch_encrypt_k3(const EncryptArgs& a, hipStream_t st) {
         hipLaunchKernelGGL(encrypt_columns_kernel<K3>, dim3((unsigned)(((cols + 3) / 4 + 7) / 8 * 8)), dim3(ROWS_NT), 0, st, a);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
+    }
+    if (rows <= WIDE_ROWS / 2) {
+        ProfScope prof__("encrypt_rows_kernel", st);
+        hipLaunchKernelGGL(encrypt_rows_wide_kernel<K3>, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(2 * WIDE_NT), 0, st, a);
+        return hipGetLastError();
     }
     ProfScope prof__("encrypt_rows_kernel", st);
     hipLaunchKernelGGL(encrypt_rows_kernel<K3>, dim3((unsigned)(((rows + 3) / 4 + 7) / 8 * 8)), dim3(ROWS_NT), 0, st, a);

@@ -17,6 +17,11 @@ POINTS = [
     (15, [50, 50, 50, 50], 4, 50, 3, 9),
     (13, [50] * 9, 1, 50, 9, 2),                       # conversion sums of eight terms and one more
     (12, [50] * 16, 1, 50, 16, 1),                     # twice eight
+    (12, [50, 45, 44, 50, 40, 49], 3, 50, 6, 8),       # rows by four waves: 256 inner products of three digits, then more
+    (12, [50, 45, 44, 50, 40, 49], 3, 50, 6, 9),
+    (12, [50, 45, 44, 50], 1, 50, 4, 32),              # 512 of one digit in both launches, then more
+    (12, [50, 45, 44, 50], 1, 50, 4, 33),
+    (15, [50, 45, 44, 50], 4, 50, 4, 1),               # four digits: sixteen waves
 ]
 
 
