@@ -426,7 +426,7 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
                             for (int r = 0; r < NR; r++) fp_sum_add(s[r], y[r * 64], f0);
                         }
 #pragma unroll
-                        for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_sum_value(s[r], q.p, q.pinv), q.p, q.pinv);
+                        for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_sum_value(s[r], FP_SUM_BASE, q.p, q.pinv), q.p, q.pinv);
                     }
                 }
             }

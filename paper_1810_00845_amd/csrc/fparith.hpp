@@ -30,12 +30,14 @@ FP_HD double fp_mulmod(double a, double b, double p, double pinv) {
     return r + l;
 }
 
-// Sums of products a_i * b_i with one reduction for all of them.  h holds FP_SUM_BASE + (the sum, each product rounded to the
-// unit in the last place of the base, 2^50, as it is added), l what the roundings left out: h stays in the binade of the base, so
-// both differences below are exact.  Four instructions a term where a modular product and an addition are seven, and
-// six to get the value out.
-//   |a_i * b_i| <= 2^98, at most FP_SUM_TERMS of them: |h - base| <= 2^101, |l| <= 2^52 beside what it started from
-//   fp_sum_value: an integer congruent to the sum plus the start of l, |result| <= 1.5 p + |l|
+// Sums of products a_i * b_i with one reduction for all of them.  h holds a base + (the sum, each product rounded to the unit in the
+// last place of the base as it is added), l what the roundings left out: h stays in the binade of the base, so both
+// differences below are exact.  Four instructions a term where a modular product and an addition are seven, and six to
+// get the value out.  With base 1.5 * 2^(2 e + t):
+//   |a_i * b_i| <= 2^(2 e - 2), at most 2^(t + 1) of them: |h - base| <= 2^(2 e + t - 1), |l| <= 2^(2 e + 2 t - 52) beside
+//   what it started from; 2 e + 2 t <= 104 keeps that below 2^52
+//   fp_sum_value: an integer congruent to the sum plus the start of l, |result| <= 1.5 p + |l|, for p < 2^e
+// e = 50, t = 2 serves any prime here (FP_SUM_BASE); smaller primes take more terms (fp_sum_plan: factors within +-p / 2).
 #define FP_SUM_TERMS 8
 #define FP_SUM_BASE 0x1.8p102
 struct FpSum {
@@ -47,10 +49,23 @@ FP_HD void fp_sum_add(FpSum& s, double a, double b) {
     s.l += __builtin_fma(a, b, -d);
     s.h = t;
 }
-FP_HD double fp_sum_value(const FpSum& s, double p, double pinv) {
-    const double h = s.h - FP_SUM_BASE;
+FP_HD double fp_sum_value(const FpSum& s, double base, double p, double pinv) {
+    const double h = s.h - base;
     const double q = __builtin_rint(h * pinv);
     return __builtin_fma(-q, p, h) + s.l;
+}
+struct FpSumPlan {
+    double base;
+    int terms;
+};
+FP_HD FpSumPlan fp_sum_plan(double p) {
+    union { double d; uint64_t u; } c;
+    c.d = p;
+    const int e = (int)(c.u >> 52) - 1022;                       // 2^(e - 1) <= p < 2^e
+    int t = (104 - 2 * e) / 2;
+    t = t > 6 ? 6 : t;
+    c.u = ((uint64_t)(1023 + 2 * e + t) << 52) | ((uint64_t)1 << 51);
+    return FpSumPlan{c.d, 2 << t};
 }
 
 // v - rint(v/p) * p

@@ -1587,7 +1587,6 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
     const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total, ext_limbs = l + K;
     if (ct_bs < (u64)2 * l * n || (plain && plain_bs < (u64)2 * l * n)) return fail(ctx, HISA_ERR_ARG, "bad rotation sum strides");
     IpSteps st = {};
-    GaloisTab tab = {};
     for (int s = 0; s < n_steps; s++) {
         const u64 g = galois_of(ctx, steps[s]);
         if (g == 0) return fail(ctx, HISA_ERR_ARG, "rotation by a multiple of the slot count");
@@ -1601,7 +1600,6 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
             return fail(ctx, HISA_ERR_NO_KEY, "no rotation key for %d slots (galois element %llu)", steps[s], (unsigned long long)g);
         st.key[s] = it->second.data;
         st.galois[s] = (uint32_t)g;
-        tab.g[s] = (uint32_t)g;
     }
     if (t_analysis) {
         TALLY(rot_left, HISA_OP_ROT_LEFT, (u64)n_steps * Bn, l);
@@ -1615,18 +1613,14 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
     const size_t E = shared_input ? Bn : (size_t)n_steps * Bn;
     FpExt x(ctx, E, l, K, alpha);
     Temp acc(ctx, Bn * 2 * (size_t)ext_limbs * n * sizeof(u64));
-    Temp addend(ctx, Bn * 2 * (size_t)l * n * sizeof(u64));
-    if (!x.ok() || !acc.ok() || !addend.ok()) return HISA_ERR_OOM;
+    if (!x.ok() || !acc.ok()) return HISA_ERR_OOM;
     const u64* c1 = rot + (size_t)l * n;
     TRY(key_switch_modup_fp(ctx, c1, ct_bs, E, x));
     HIP_TRY(ctx, launch_inner_product_sum_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, st, n_steps, total,
-                                             c1, ct_bs, acc.u(), (u64)2 * ext_limbs * n, Bn, shared_input ? 1 : 0, (int)ctx->log_n,
-                                             ctx->stream));
-    HIP_TRY(ctx, launch_automorph_sum(ctx->d_primes, rot, ct_bs, n_steps, tab, plain, plain_bs, addend.u(), (u64)2 * l * n, Bn,
-                                      shared_input ? 1 : 0, l,
-                                      (int)ctx->log_n, ctx->stream));
-    if (rescale) return moddown_rescale_fp(ctx, acc.u(), Bn, l, addend.u(), (u64)2 * l * n, 2, out);
-    return moddown_add_fp(ctx, acc.u(), Bn, l, addend.u(), (u64)2 * l * n, 2, out);
+                                             c1, ct_bs, acc.u(), (u64)2 * ext_limbs * n, Bn, shared_input ? 1 : 0, rot, plain,
+                                             plain_bs, ctx->d_pmod, (int)ctx->log_n, ctx->stream));
+    if (rescale) return moddown_rescale_fp(ctx, acc.u(), Bn, l, nullptr, 0, 0, out);
+    return moddown_add_fp(ctx, acc.u(), Bn, l, nullptr, 0, 0, out);
 }
 
 int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n_cts, int l, u64* out) {

@@ -457,10 +457,13 @@ hipError_t launch_inner_product_steps_fp(const FpPrime* fprimes, const double* e
                                          const u64* c0_src = nullptr, const u64* pmod = nullptr);
 
 // The sum over n_steps rotations of different ciphertexts: ext / own_src entry s * n_batch + b is term s of output b
-// (digits from the unrotated polynomial); acc[b] = sum_s sum_j sigma_s(e_j) * key_s[j] on the l + K limbs.
+// (digits from the unrotated polynomial); acc[b] = sum_s sum_j sigma_s(e_j) * key_s[j] on the l + K limbs.  On the limbs of q
+// the accumulators also take P (pmod[i] = P mod q_i) times sum_s sigma_s(c0) (c0_src, entries as own_src) and times the
+// polynomials of plain[b] (null: none).  shared_input: every term of output b is entry b.
 hipError_t launch_inner_product_sum_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
                                        int alpha, const IpSteps& steps, int n_steps, int total, const u64* own_src, u64 own_bs,
-                                       u64* acc, u64 acc_bs, u64 n_batch, int shared_input, int log_n, hipStream_t st);
+                                       u64* acc, u64 acc_bs, u64 n_batch, int shared_input, const u64* c0_src, const u64* plain,
+                                       u64 plain_bs, const u64* pmod, int log_n, hipStream_t st);
 
 // sampling (counter-based generator, both sides of the parity tests implement it)
 hipError_t launch_sample_uniform(const PrimeConst* primes, u64 seed, u64 kind, u64 ctr, const PolyMap& map, int n_polys,
@@ -498,11 +501,6 @@ struct GaloisTab { uint32_t g[GALOIS_TAB_MAX]; };
 // several automorphisms of the same inputs: out entry (s, b) = sigma_{tab.g[s]}(in entry b), entries out_bs words apart
 hipError_t launch_automorph_steps(const u64* in, u64 in_bs, u64* out, u64 out_bs, const GaloisTab& tab, int n_steps,
                                   int n_polys, u64 n_batch, int log_n, hipStream_t st);
-// out[b] = (plain[b].c0 + sum_s sigma_{tab.g[s]}(rot[s * n_batch + b].c0), plain[b].c1) on l limbs; plain may be null;
-// shared_input: every term of output b is rot[b]
-hipError_t launch_automorph_sum(const PrimeConst* primes, const u64* rot, u64 rot_bs, int n_rot, const GaloisTab& tab,
-                                const u64* plain, u64 plain_bs, u64* out, u64 out_bs, u64 n_batch, int shared_input, int l,
-                                int log_n, hipStream_t st);
 // acc entries (ciphertext, polynomial), acc_bs apart: acc += P * add on the first l limbs, for polynomials < add_polys
 hipError_t launch_fold_addend(const PrimeConst* primes, u64* acc, u64 acc_bs, const u64* add, u64 add_bs, u64 add_ps,
                               int add_polys, const u64* pmod, u64 n_cts, int l, int log_n, hipStream_t st);

@@ -462,85 +462,173 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_steps_fp_kernel(const Fp
 // The sum over rotations, before the division by P: entry (s, b) of ext / own_src is term s of output b (its digits
 // computed from the unrotated polynomial, gathered here through sigma_s like the own-digit limbs) -- or, with
 // shared_input, entry b for every s: all terms of an output rotate the same ciphertext --
-// acc[b] = sum_s sum_j sigma_s(e_{s,b,j}) * key_s[j].  A rotation's key values stay in registers across the IPS_BCH
-// outputs of a block (4: many blocks for the few outputs of a layer; the blocks of a limb run together, so the key
-// rows that each of them reads come from the L2 after the first); partial sums are normalised per rotation (eight terms of at most
-// 0.875 * 2^50 stay below 2^53) and the running sums every eight rotations.
-template <int IPS_BCH>
+// acc[b] = sum_s sum_j sigma_s(e_{s,b,j}) * key_s[j], and on the limbs of q P times what needs no key: sum_s sigma_s(c0 of
+// term s) and the two polynomials of `plain` (null: none).  P c divided by P is c again, and it leaves the special limbs
+// alone: the division that follows needs no addend.
+// A thread owns a coefficient of a limb and up to IPS_BCH outputs, for which a rotation's key values serve once loaded; the
+// workgroups of a limb run together, so the key rows that each of them reads come from the L2 after the first.  GROUPS = 4: where
+// workgroups are few, a thread would be a chain of up to 32 rounds of dependent loads; the four waves of a workgroup then take
+// the same 64 coefficients and every fourth rotation each, and their sums meet in LDS.
+// Against sums in one chain a thread, a reduction a product, and c0 and addend in two launches of their own (us, all sums of a network):
+// LeNet-small 203 -> 105, LeNet-medium 1095 -> 678, SqueezeNet-style 2087 -> 1758 (there the keys, 640 MB a launch of one output, bound
+// it).  In one wave or over four, by workgroups of whole chains: 288 of them 40 -> 32 us a launch, 1792 50 -> 41, 2560 and more even.
+// Ranges: all factors within p / 2; the sums are reduced before they hold more terms than their plan allows.  At most eight rotations
+// a wave add canonical c0 values when GROUPS = 4, and those are normalised every eighth rotation otherwise.
+#define IPS_BCH 4
+#define IPS_FEW 2048    // workgroups of whole chains
+template <int GROUPS, int DIGITS>
 __global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(const FpPrime* fprimes, const double* ext, u64 ext_bs,
                                                                       int digits, int l, int K, int L, int alpha, IpSteps steps,
                                                                       int n_steps, int total, const u64* own_src, u64 own_bs,
                                                                       u64* acc, u64 acc_bs, u64 n_batch, int shared_input,
+                                                                      const u64* c0_src, const u64* plain, u64 plain_bs, const u64* pmod,
                                                                       int log_n) {
+    constexpr int COEFFS = IPF_NT / GROUPS, MAXD = DIGITS ? DIGITS : IPF_MAXD;
     const u64 n = (u64)1 << log_n;
-    const uint32_t j = blockIdx.x * IPF_NT + threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
+    const uint32_t j = blockIdx.x * COEFFS + (GROUPS == 1 ? threadIdx.x : lane);
     const int x = blockIdx.z;      // the groups of outputs of a limb run together: they read the same key rows
     const u64 b0 = (u64)blockIdx.y * IPS_BCH;
+    const int live = (int)(n_batch - b0 < IPS_BCH ? n_batch - b0 : IPS_BCH);
     const int ext_limbs = l + K;
     const int prime = x < l ? x : L + (x - l);
     const int own_digit = x < l ? x / alpha : -1;
     const double p = as_const(&fprimes[prime].p)[0], pinv = as_const(&fprimes[prime].p)[1];
-    double tb[IPS_BCH], ta[IPS_BCH];
+    const FpSumPlan plan = fp_sum_plan(p);
+    const int fold_every = plan.terms / digits;                  // rotations
+    FpSum sb[IPS_BCH], sa[IPS_BCH];
+    double tc[IPS_BCH];
 #pragma unroll
-    for (int u = 0; u < IPS_BCH; u++) tb[u] = ta[u] = 0.0;
-    for (int s = 0; s < n_steps; s++) {
-        const u64* key = steps.key[s];
+    for (int u = 0; u < IPS_BCH; u++) { sb[u] = sa[u] = FpSum{plan.base, 0.0}; tc[u] = 0.0; }
+    auto fold = [&](FpSum& s) { s = FpSum{plan.base, fp_norm(fp_sum_value(s, plan.base, p, pinv), p, pinv)}; };
+    int pending = 0, c0_pending = 0;
+    for (int s = GROUPS == 1 ? 0 : wave; s < n_steps; s += GROUPS) {
+        const double* key = (const double*)steps.key[s] + (u64)prime * n + j;
         const uint32_t jsrc = galois_src_fp(j, steps.galois[s], log_n);
-        double kb[IPF_MAXD], ka[IPF_MAXD];
+        const u64 entry0 = (shared_input ? 0 : (u64)s * n_batch) + b0;
+        // a rotation's loads all together: with the digits known to the compiler they are one wait
+        double kb[MAXD], ka[MAXD], e[MAXD][IPS_BCH], c0[IPS_BCH];
 #pragma unroll
-        for (int d = 0; d < IPF_MAXD; d++) {
-            if (d < digits) {
-                kb[d] = ((const double*)key)[(((u64)d * 2 + 0) * total + prime) * n + j];
-                ka[d] = ((const double*)key)[(((u64)d * 2 + 1) * total + prime) * n + j];
+        for (int d = 0; d < MAXD; d++) {
+            if (DIGITS || d < digits) {
+                kb[d] = key[(u64)(d * 2) * total * n];
+                ka[d] = key[(u64)(d * 2 + 1) * total * n];
+                const bool own = d == own_digit;
+                const double* src = own ? (const double*)own_src + entry0 * own_bs + (u64)x * n + jsrc
+                                        : ext + entry0 * ext_bs + ((u64)d * ext_limbs + x) * n + jsrc;
+                const u64 bs = own ? own_bs : ext_bs;
+#pragma unroll
+                for (int u = 0; u < IPS_BCH; u++)
+                    if (u < live) e[d][u] = src[u * bs];
             }
         }
+        if (x < l) {
 #pragma unroll
-        for (int u = 0; u < IPS_BCH; u++) {
-            if (b0 + u < n_batch) {
-                const u64 entry = (shared_input ? 0 : (u64)s * n_batch) + b0 + u;
-                double sb = 0.0, sa = 0.0;
+            for (int u = 0; u < IPS_BCH; u++)
+                if (u < live) c0[u] = ((const double*)c0_src)[(entry0 + u) * own_bs + (u64)x * n + jsrc];
+        }
 #pragma unroll
-                for (int d = 0; d < IPF_MAXD; d++) {
-                    if (d < digits) {
-                        const double e = d == own_digit ? fp_from_u64(own_src[entry * own_bs + (u64)x * n + jsrc])
-                                                        : ext[entry * ext_bs + ((u64)d * ext_limbs + x) * n + jsrc];
-                        sb += fp_mulmod(e, kb[d], p, pinv);
-                        sa += fp_mulmod(e, ka[d], p, pinv);
-                    }
+        for (int d = 0; d < MAXD; d++) {
+            if (DIGITS || d < digits) {
+#pragma unroll
+                for (int u = 0; u < IPS_BCH; u++) {
+                    if (u >= live) break;
+                    if (d == own_digit) e[d][u] = fp_norm(fp_from_u64((u64)__double_as_longlong(e[d][u])), p, pinv);
+                    fp_sum_add(sb[u], e[d][u], kb[d]);
+                    fp_sum_add(sa[u], e[d][u], ka[d]);
                 }
-                tb[u] += fp_norm(sb, p, pinv);
-                ta[u] += fp_norm(sa, p, pinv);
-                if ((s & 7) == 7) { tb[u] = fp_norm(tb[u], p, pinv); ta[u] = fp_norm(ta[u], p, pinv); }
             }
+        }
+        if (x < l) {
+#pragma unroll
+            for (int u = 0; u < IPS_BCH; u++)
+                if (u < live) tc[u] += fp_from_u64((u64)__double_as_longlong(c0[u]));
+            if (GROUPS == 1 && ++c0_pending == 6) {              // six and a normalised value
+                c0_pending = 0;
+#pragma unroll
+                for (int u = 0; u < IPS_BCH; u++) tc[u] = fp_norm(tc[u], p, pinv);
+            }
+        }
+        if (++pending == fold_every) {
+            pending = 0;
+#pragma unroll
+            for (int u = 0; u < IPS_BCH; u++) { fold(sb[u]); fold(sa[u]); }
         }
     }
-#pragma unroll
-    for (int u = 0; u < IPS_BCH; u++) {
-        if (b0 + u < n_batch) {
-            u64* dst = acc + (b0 + u) * acc_bs;
-            dst[(u64)x * n + j] = fp_canonical(tb[u], p, pinv);
-            dst[((u64)ext_limbs + x) * n + j] = fp_canonical(ta[u], p, pinv);
+    static_assert(FP_MAX_STEPS <= 32, "eight rotations a wave of four");
+    auto finish = [&](u64 b, double vb, double va, double vc) {
+        if (x < l) {
+            const double pm = fp_from_u64(pmod[prime]);
+            if (plain) {
+                const u64* add = plain + b * plain_bs + (u64)x * n + j;
+                vc += fp_from_u64(add[0]);
+                va += fp_mulmod(fp_from_u64(add[(u64)l * n]), pm, p, pinv);
+            }
+            vb += fp_mulmod(vc, pm, p, pinv);
         }
+        u64* dst = acc + b * acc_bs;
+        dst[(u64)x * n + j] = fp_canonical(vb, p, pinv);
+        dst[((u64)ext_limbs + x) * n + j] = fp_canonical(va, p, pinv);
+    };
+#pragma unroll
+    for (int u = 0; u < IPS_BCH; u++) { fold(sb[u]); fold(sa[u]); tc[u] = fp_norm(tc[u], p, pinv); }
+    if constexpr (GROUPS == 1) {
+#pragma unroll
+        for (int u = 0; u < IPS_BCH; u++)
+            if (u < live) finish(b0 + u, sb[u].l, sa[u].l, tc[u]);
+    } else {
+        static_assert(GROUPS == IPS_BCH, "a wave finishes an output");
+        __shared__ double part[GROUPS][IPS_BCH][3][64];
+#pragma unroll
+        for (int u = 0; u < IPS_BCH; u++) {
+            part[wave][u][0][lane] = sb[u].l;
+            part[wave][u][1][lane] = sa[u].l;
+            part[wave][u][2][lane] = tc[u];
+        }
+        __syncthreads();
+        if (wave >= live) return;
+        double sum[3] = {};
+#pragma unroll
+        for (int w = 0; w < GROUPS; w++)
+#pragma unroll
+            for (int i = 0; i < 3; i++) sum[i] += part[w][wave][i][lane];
+        finish(b0 + wave, sum[0], sum[1], sum[2]);
     }
 }
 
 hipError_t launch_inner_product_sum_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
                                        int alpha, const IpSteps& steps, int n_steps, int total, const u64* own_src, u64 own_bs,
-                                       u64* acc, u64 acc_bs, u64 n_batch, int shared_input, int log_n, hipStream_t st) {
+                                       u64* acc, u64 acc_bs, u64 n_batch, int shared_input, const u64* c0_src, const u64* plain,
+                                       u64 plain_bs, const u64* pmod, int log_n, hipStream_t st) {
     DRY_RUN_RETURN();
     if (digits < 1 || digits > IPF_MAXD || n_steps < 1 || n_steps > FP_MAX_STEPS || l < 1 || K < 1 || alpha < 1) return hipErrorInvalidValue;
-    if (!fprimes || !ext || !own_src || !acc || n_batch == 0 || n_batch > 65535u * 4 || l + K > 65535) return hipErrorInvalidValue;
+    if (!fprimes || !ext || !own_src || !acc || !c0_src || !pmod || n_batch == 0 || n_batch > 65535 || l + K > 65535)
+        return hipErrorInvalidValue;
     // an entry holds `digits` extended digits of l + K limbs; an accumulator two polynomials of l + K limbs; an own-digit
-    // source the l limbs of the polynomial
+    // source and a c0 the l limbs of a polynomial, a plain entry both
     const u64 n = (u64)1 << log_n;
-    if (ext_bs < (u64)digits * (l + K) * n || acc_bs < (u64)2 * (l + K) * n || own_bs < (u64)l * n) return hipErrorInvalidValue;
+    if (ext_bs < (u64)digits * (l + K) * n || acc_bs < (u64)2 * (l + K) * n || own_bs < (u64)l * n || (plain && plain_bs < (u64)2 * l * n))
+        return hipErrorInvalidValue;
     for (int s = 0; s < n_steps; s++)
         if (!steps.key[s] || steps.galois[s] == 0) return hipErrorInvalidValue;
-    const unsigned bch = 4;
-    dim3 grid((1u << log_n) / IPF_NT, (unsigned)((n_batch + bch - 1) / bch), l + K);
+    const unsigned groups_of_outputs = (unsigned)((n_batch + IPS_BCH - 1) / IPS_BCH);
+    const bool few = ((u64)groups_of_outputs * (l + K) << log_n) / IPF_NT < IPS_FEW;
+    dim3 grid((1u << log_n) / (few ? 64 : IPF_NT), groups_of_outputs, l + K);
     ProfScope prof__("inner_product_sum_fp_kernel", st);
-    hipLaunchKernelGGL(inner_product_sum_fp_kernel<4>, grid, dim3(IPF_NT), 0, st, fprimes, ext, ext_bs, digits, l, K, L, alpha,
-                       steps, n_steps, total, own_src, own_bs, acc, acc_bs, n_batch, shared_input, log_n);
+#define SUM_LAUNCH(G, D)                                                                                                                 \
+    hipLaunchKernelGGL((inner_product_sum_fp_kernel<G, D>), grid, dim3(IPF_NT), 0, st, fprimes, ext, ext_bs, digits, l, K, L, alpha, steps, \
+                       n_steps, total, own_src, own_bs, acc, acc_bs, n_batch, shared_input, c0_src, plain, plain_bs, pmod, log_n)
+    switch ((few ? 4 : 0) + (digits < 4 ? digits : 0)) {
+        case 1: SUM_LAUNCH(1, 1); break;
+        case 2: SUM_LAUNCH(1, 2); break;
+        case 3: SUM_LAUNCH(1, 3); break;
+        case 0: SUM_LAUNCH(1, 0); break;
+        case 5: SUM_LAUNCH(4, 1); break;
+        case 6: SUM_LAUNCH(4, 2); break;
+        case 7: SUM_LAUNCH(4, 3); break;
+        default: SUM_LAUNCH(4, 0); break;
+    }
+#undef SUM_LAUNCH
     return hipGetLastError();
 }
 

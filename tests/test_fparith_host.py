@@ -21,9 +21,16 @@ uint64_t t_to_u64(double v) { return fp_to_u64(v); }
 double t_sum(const double* a, const double* b, int n, double start, double p, double pinv) {
     FpSum s = {FP_SUM_BASE, start};
     for (int i = 0; i < n; i++) fp_sum_add(s, a[i], b[i]);
-    return fp_sum_value(s, p, pinv);
+    return fp_sum_value(s, FP_SUM_BASE, p, pinv);
+}
+double t_plan_sum(const double* a, const double* b, int n, double start, double p, double pinv) {
+    const FpSumPlan plan = fp_sum_plan(p);
+    FpSum s = {plan.base, start};
+    for (int i = 0; i < n; i++) fp_sum_add(s, a[i], b[i]);
+    return fp_sum_value(s, plan.base, p, pinv);
 }
 int t_sum_terms() { return FP_SUM_TERMS; }
+int t_plan_terms(double p) { return fp_sum_plan(p).terms; }
 double t_centred(uint64_t x, double p, double half) { return fp_centred_from_u64(x, p, half); }
 }
 """
@@ -45,6 +52,8 @@ def fp(tmp_path_factory):
     l.t_canonical.restype = U; l.t_canonical.argtypes = [D] * 3
     l.t_from_u64.restype = D; l.t_from_u64.argtypes = [U]
     l.t_to_u64.restype = U; l.t_to_u64.argtypes = [D]
+    l.t_plan_sum.restype = D; l.t_plan_sum.argtypes = [ctypes.POINTER(D), ctypes.POINTER(D), ctypes.c_int, D, D, D]
+    l.t_plan_terms.restype = ctypes.c_int; l.t_plan_terms.argtypes = [D]
     l.t_sum.restype = D; l.t_sum.argtypes = [ctypes.POINTER(D), ctypes.POINTER(D), ctypes.c_int, D, D, D]
     l.t_centred.restype = D; l.t_centred.argtypes = [U, D, D]
     return l
@@ -153,3 +162,20 @@ def test_sums_with_one_reduction(fp):
             assert abs(r) <= 1.5 * p + 2 ** 52 + abs(start), (p, ys, hs, start, r)
             v = fp.t_norm(r, pf, pinv)
             assert is_int(v) and (int(v) - true) % p == 0 and abs(v) <= p / 2 * (1 + 2.0 ** -48) + 2, (p, r, v)
+
+
+def test_sums_as_long_as_the_prime_allows(fp):
+    """fp_sum_plan: as many products of values within p / 2 as it allows, all of one sign or mixed."""
+    rnd = random.Random(9)
+    D = ctypes.c_double
+    assert fp.t_plan_terms(float(2 ** 50 - 27)) == 8 and fp.t_plan_terms(float(2 ** 49 - 1)) == 16 and fp.t_plan_terms(float(2 ** 36 + 1)) == 128
+    for p in primes() + [2 ** 49 - 1, 2 ** 48 + 1, 2 ** 47 - 1, 2 ** 46 - 1, 2 ** 30 + 3]:
+        pf, pinv = float(p), 1.0 / float(p)
+        n, half = fp.t_plan_terms(pf), p // 2
+        for trial in range(300):
+            ys = [half] * n if trial < 2 else [rnd.choice([half, -half, rnd.randrange(-half, half + 1)]) for _ in range(n)]
+            hs = [half if trial == 0 else -half] * n if trial < 2 else [rnd.choice([half, -half, rnd.randrange(-half, half + 1)]) for _ in range(n)]
+            start = rnd.choice([0, half, -half])
+            r = fp.t_plan_sum((D * n)(*map(float, ys)), (D * n)(*map(float, hs)), n, float(start), pf, pinv)
+            true = start + sum(y * h for y, h in zip(ys, hs))
+            assert is_int(r) and abs(r) <= 1.5 * p + 2 ** 52 + half and (int(r) - true) % p == 0, (p, trial, r)

@@ -79,3 +79,41 @@ def test_more_entries_than_a_grid_has_rows():
     for i in (0, 1, 32766, 32767, 32768):
         assert np.array_equal(g.ct_export(out[i]), g.ct_export(single[i % 2]))
     g.close()
+
+
+# (log_n, q_bits, dnum, outputs, rotations): digits known to the kernel (1, 2, 3) and more, rotations in one wave and over four
+# (few outputs), primes that let sums run through and 50-bit ones that are reduced after every eight products
+SUMS = [
+    (12, [50, 50, 50], 3, 5, 32),
+    (12, [50, 40, 40], 1, 1, 31),
+    (13, [50] * 8, 8, 2, 17),
+    (12, [50, 46, 45, 36], 2, 4, 3),
+    (14, [50] * 6, 2, 17, 14),
+    (14, [50, 40, 40, 49, 49, 48], 3, 18, 13),
+    (14, [50, 40, 40, 49], 4, 33, 5),
+]
+
+
+@pytest.mark.parametrize("log_n,q_bits,dnum,outputs,rotations", SUMS)
+def test_sums_of_many_rotations(log_n, q_bits, dnum, outputs, rotations):
+    from oracle import Oracle
+    from oracle.layers import SharedModDown
+    from paper_1810_00845_amd import hisa, synth
+    print("[case]", log_n, len(q_bits), dnum, outputs, rotations, flush=True)
+    g, o = hisa.Context(log_n, q_bits, dnum, 50, 5), Oracle(log_n, q_bits, dnum, 50, 5)
+    steps = list(range(1, rotations + 1))
+    g.gen_rot_keys(steps); o.gen_rot_keys(steps)
+    l, n = len(q_bits), outputs + 2
+    coeff = synth.uniform_residues(log_n + l + n, (n, 2, l, g.N), g.primes[:l])
+    for i in range(l):
+        coeff[0, :, i, :] = g.primes[i] - 1           # the largest residues: every coefficient of these transforms alike
+        coeff[1, 0, i, ::2] = g.primes[i] // 2
+    cts = g.ct_import_batch(coeff, 2.0 ** 50)
+    ref = [o.import_ct(c, 2.0 ** 50) for c in coeff[:3]] + [None] * (n - 3)
+    for terms_of, sample in ((lambda s, b: b + (s % 3 if b < outputs - 1 else 0), 0), (lambda s, b: b, min(2, outputs - 1))):
+        out = g.rot_left_sum_batch([[cts[terms_of(s, b)] for b in range(outputs)] for s in [0] + steps], [0] + steps)
+        want = SharedModDown(o, ref[:3]).total([(terms_of(s, sample), s, 1, None) for s in [0] + steps], 2.0 ** 50)
+        assert np.array_equal(g.ct_export(out[sample]), o.export(want))
+        single = g.rot_left_sum_batch([[cts[terms_of(s, outputs - 1)]] for s in [0] + steps], [0] + steps)
+        assert np.array_equal(g.ct_export(out[-1]), g.ct_export(single[0]))
+    g.close()
