@@ -618,7 +618,14 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
         double t[16];
         load_row_through<K3>(t, g.add + ct * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, galois, row, lane);
 #pragma unroll
-        for (int r = 0; r < 16; r++) sum[r] += fp_from_u64((u64)__double_as_longlong(t[r]));
+        for (int r = 0; r < 16; r++) t[r] = fp_from_u64((u64)__double_as_longlong(t[r]));
+        if (g.c2) {
+            const double c2 = as_const(g.c2)[x];
+#pragma unroll
+            for (int r = 0; r < 16; r++) t[r] = fp_mulmod(t[r], c2, q.p, q.pinv);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; r++) sum[r] += t[r];
     }
     SCHED_FENCE();
     const u64 out_limb = source ? (b * 2 + poly) * (u64)(a.ext_limbs - g.n_acc) + (u64)(x - g.n_acc) : (b * 2 + poly) * (u64)g.n_acc + (u64)x;
@@ -901,8 +908,9 @@ __device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const Inne
         }
         if (with_add) {
             wide_from_residues(add);
+            const double c2 = g.c2 ? as_const(g.c2)[x] : 1.0;
 #pragma unroll
-            for (int r = 0; r < 4; r++) v[r] += add[r];
+            for (int r = 0; r < 4; r++) v[r] += fp_mulmod(add[r], c2, q.p, q.pinv);
         }
         if (!source && MODE == FP_INV_D_TO_Y) wide_store(dst, t, v);
     }

@@ -1522,6 +1522,48 @@ static int moddown_rescale_tables(hisa_ctx* ctx, int l, ConvTable** tab, double*
     return HISA_OK;
 }
 
+// The division behind the inner products of a key switch at level l, by P or by q_{l-1} P: the limbs from n_acc on are its
+// sources; what the accumulators (c1, one per limb) and the addend (c2, limbs of q; null: one) are multiplied by so that the
+// sources are conversion inputs and the other limbs carry the inverse of the divisor; the conversion table with that inverse.
+struct Division { int n_acc; const double *c1, *c2, *hat; };
+
+static int division_by_p(hisa_ctx* ctx, int l, bool lookup_only, Division* d) {
+    double* c1;
+    TRY(fp_inner_tables(ctx, l, &c1, lookup_only));
+    *d = {l, c1, nullptr, ctx->d_moddown_hat_pin};
+    return HISA_OK;
+}
+static int division_by_p_and_last(hisa_ctx* ctx, int l, Division* d) {
+    const u64 KEY = 20480 + (u64)l;
+    const size_t ext = (size_t)l + ctx->K;
+    auto it = ctx->aux.find(KEY);
+    if (it == ctx->aux.end()) {
+        ConvTable* tab;
+        double *post, *dinv;
+        TRY(moddown_rescale_tables(ctx, l, &tab, &post, &dinv));
+        std::vector<double> t(ext + l + (size_t)tab->a * ctx->total, 0.0);
+        const u64 last = ctx->mod[l - 1];
+        for (int i = 0; i < l - 1; i++) {
+            const u64 q = ctx->mod[i];
+            u64 div = 1 % q;
+            for (int m = 0; m < tab->a; m++) div = hm::mul(div, ctx->mod[tab->src[m]] % q, q);
+            const u64 div_inv = hm::inv(div, q);
+            t[i] = centred_double(div_inv, q);
+            t[ext + i] = centred_double(hm::inv(last % q, q), q);
+            for (int m = 0; m < tab->a; m++)
+                t[ext + l + (size_t)m * ctx->total + i] = centred_double(hm::mul(tab->hat[(size_t)m * ctx->total + i], div_inv, q), q);
+        }
+        for (int m = 0; m < tab->a; m++) t[l - 1 + m] = centred_double(tab->inv_hat[m], ctx->mod[tab->src[m]]);
+        t[ext + l - 1] = 1.0;      // P times (q_{l-1} P / q_{l-1})^-1
+        double* dev = nullptr;
+        HIP_TRY(ctx, upload(&dev, t));
+        it = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{dev, t.size() * sizeof(double), 1}, (u64*)dev}).first;
+    }
+    const double* t = (const double*)it->second.data;
+    *d = {l - 1, t, t + ext, t + ext + l};
+    return HISA_OK;
+}
+
 int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64* out) {
     if (!fused_key_switch_available(ctx)) return fail(ctx, HISA_ERR_ARG, "no fused key-switch path for these parameters");
     if (l < 2) return fail(ctx, HISA_ERR_DEPTH_EXHAUSTED, "no level to rescale into");
@@ -1623,30 +1665,6 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
     return moddown_add_fp(ctx, acc.u(), Bn, l, nullptr, 0, 0, out);
 }
 
-int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n_cts, int l, u64* out) {
-    if (!fused_key_switch_available(ctx)) return fail(ctx, HISA_ERR_ARG, "no fused key-switch path for these parameters");
-    if (l < 2) return fail(ctx, HISA_ERR_DEPTH_EXHAUSTED, "no level to rescale into");
-    if (t_analysis) {
-        TALLY(relinearize, HISA_OP_RELINEARIZE, n_cts, l);
-        TALLY(rescale, HISA_OP_RESCALE, n_cts, l);
-        TALLY(key_switch_calls, HISA_OP_KEY_SWITCH_CALLS, 1, l);
-        return HISA_OK;
-    }
-    auto it = ctx->keys.find(0);
-    if (it == ctx->keys.end()) return fail(ctx, HISA_ERR_NO_KEY, "no relinearisation key: call hisa_keygen");
-    const size_t n = ctx->N, lw = (size_t)l * n;
-    const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total, ext_limbs = l + K;
-    if (stride < 3 * lw) return fail(ctx, HISA_ERR_ARG, "bad stride");
-    FpExt x(ctx, n_cts, l, K, alpha);
-    Temp acc(ctx, n_cts * 2 * (size_t)ext_limbs * n * sizeof(u64));
-    if (!x.ok() || !acc.ok()) return HISA_ERR_OOM;
-    const u64* d2 = cts3 + 2 * lw;
-    TRY(key_switch_modup_fp(ctx, d2, stride, n_cts, x));
-    HIP_TRY(ctx, launch_inner_product_fp(ctx->tabs.fprimes, x.extp, x.ext_bs, x.digits, l, K, L, alpha, it->second.data, total, d2,
-                                         stride, acc.u(), (u64)2 * ext_limbs * n, n_cts, (int)ctx->log_n, ctx->stream));
-    return moddown_rescale_fp(ctx, acc.u(), n_cts, l, cts3, stride, 2, out);
-}
-
 extern "C" int hisa_set_fused_rescale(hisa_ctx* ctx, uint32_t on) {
     if (!ctx) return HISA_ERR_ARG;
     if (on > 1) return fail(ctx, HISA_ERR_ARG, "on is 0 or 1");
@@ -1715,22 +1733,23 @@ extern "C" int hisa_rot_left_sum_batch(hisa_ctx* ctx, const hisa_ct* const* in, 
 // C, D and E: the inner products of `entries` key switches on the digits that c names, and the division by P.
 // g.acc != null ([entries][2][l][N] doubles): the limbs of q are summed in launch C too and E only subtracts -- the shorter
 // chain of launches where they do not fill the chip.
-static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, const StepArgs* steps, int l, size_t entries, u64* out) {
+static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, const Division& by, const StepArgs* steps, int l, size_t entries,
+                                u64* out) {
     const size_t n = ctx->N;
-    const int K = (int)ctx->K;
-    g.n_acc = l;
-    g.x_begin = g.acc ? 0 : l; g.x_end = l + K;
+    const int ext_limbs = l + (int)ctx->K, left = by.n_acc, sources = ext_limbs - left;
+    g.n_acc = left; g.c1 = by.c1; g.c2 = by.c2;
+    g.x_begin = g.acc ? 0 : left; g.x_end = ext_limbs;
     c.n_entries = (unsigned)entries;
     HIP_TRY(ctx, launch_inner_rows_fp(FP_INV_D_TO_Y, c, g, steps, ctx->stream));
     ConvertArgs m = convert_base(ctx, l, entries * 2);      // entries are (ciphertext, b|a) pairs
-    m.src_pos0 = l; m.n_src = K; m.mid = g.down;
-    m.n_digits = 1; m.dg[0] = {ctx->d_moddown_hat_pin, 0, K, 0, 0, 0}; m.ext_limbs = l; m.out = out; m.out_bs = (u64)l * n;
+    m.src_pos0 = left; m.n_src = sources; m.mid = g.down;
+    m.n_digits = 1; m.dg[0] = {by.hat, 0, sources, 0, 0, 0}; m.ext_limbs = left; m.out = out; m.out_bs = (u64)left * n;
     HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV_SUB, m, ctx->stream));
     if (g.acc) {
-        m.acc = (const u64*)g.acc; m.acc_bs = (u64)l * n;
+        m.acc = (const u64*)g.acc; m.acc_bs = (u64)left * n;
         HIP_TRY(ctx, launch_forward_rows_fp(FP_FWD_SUB, m, ctx->stream));
     } else {
-        g.out = out; g.x_begin = 0; g.x_end = l;
+        g.out = out; g.x_begin = 0; g.x_end = left;
         HIP_TRY(ctx, launch_inner_rows_fp(FP_FWD_CONV_SUB, c, g, steps, ctx->stream));
     }
     return HISA_OK;
@@ -1738,22 +1757,22 @@ static int key_switch_divide_fp(hisa_ctx* ctx, ConvertArgs& c, InnerArgs& g, con
 
 // One key switch of B polynomials as five launches (A to E above).  acc: see key_switch_divide_fp.
 static int key_switch_fused_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, const SwitchKey& key, const u64* add,
-                               u64 add_bs, int add_polys, u64* out, const FpExt& x, double* acc, double* down, bool no_alloc) {
+                               u64 add_bs, int add_polys, u64* out, const FpExt& x, const Division& by, double* acc, double* down,
+                               bool no_alloc) {
     const size_t n = ctx->N;
     const int l = x.l;
-    double *post_q, *post_p, *c1;
+    double *post_q, *post_p;
     TRY(fp_post_tables(ctx, l, &post_q, &post_p, no_alloc));
-    TRY(fp_inner_tables(ctx, l, &c1, no_alloc));
     ConvertArgs c = convert_base(ctx, l, B);
     TRY(modup_digits(ctx, c, x, no_alloc));
     c.in = d; c.in_bs = d_bs; c.galois = galois; c.post = post_q;
     HIP_TRY(ctx, launch_inverse_rows_fp(c, ctx->stream));
     HIP_TRY(ctx, launch_columns_fp(FP_FWD_CONV, c, ctx->stream));
     InnerArgs g = {};
-    g.key = key.data; g.own = d; g.own_bs = d_bs; g.galois = galois; g.c1 = c1;
+    g.key = key.data; g.own = d; g.own_bs = d_bs; g.galois = galois;
     g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = add ? add_polys : 0;
     g.acc = acc; g.down = down;
-    return key_switch_divide_fp(ctx, c, g, nullptr, l, B, out);
+    return key_switch_divide_fp(ctx, c, g, by, nullptr, l, B, out);
 }
 
 // Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic
@@ -1774,34 +1793,57 @@ static int key_switch_finish_steps_fp(hisa_ctx* ctx, const FpExt& x, const u64* 
     const bool stored = store_accumulators(ctx, E, x.ext_limbs);
     Temp acc(ctx, E * 2 * (size_t)l * n * sizeof(double), stored), down(ctx, E * 2 * (size_t)ctx->K * n * sizeof(double));
     if ((stored && !acc.ok()) || !down.ok()) return HISA_ERR_OOM;
-    double* c1;
-    TRY(fp_inner_tables(ctx, l, &c1, false));
+    Division by;
+    TRY(division_by_p(ctx, l, false, &by));
     ConvertArgs c = convert_base(ctx, l, B);
     TRY(modup_digits(ctx, c, x, false));
     InnerArgs g = {};
-    g.own = d; g.own_bs = d_bs; g.c1 = c1;
+    g.own = d; g.own_bs = d_bs;
     g.add = add; g.add_bs = add_bs; g.add_ps = (u64)l * n; g.add_polys = 1;
     g.acc = stored ? acc.as<double>() : nullptr; g.down = down.as<double>();
     StepArgs st = {};
     st.step_B = (unsigned)B;
     for (int s = 0; s < n_steps; s++) { st.steps.key[s] = keys[s]->data; st.steps.galois[s] = (uint32_t)galois[s]; }
-    return key_switch_divide_fp(ctx, c, g, &st, l, E, out);
+    return key_switch_divide_fp(ctx, c, g, by, &st, l, E, out);
 }
 
 static int key_switch_core_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key,
-                              const u64* add, u64 add_bs, int add_polys, u64* out) {
+                              const u64* add, u64 add_bs, int add_polys, const Division& by, u64* out) {
     FpExt x(ctx, B, l, (int)ctx->K, (int)ctx->alpha);
     const bool stored = store_accumulators(ctx, B, x.ext_limbs);
-    Temp acc(ctx, B * 2 * (size_t)l * ctx->N * sizeof(double), stored), down(ctx, B * 2 * (size_t)ctx->K * ctx->N * sizeof(double));
+    const size_t poly = B * 2 * (size_t)ctx->N * sizeof(double);
+    Temp acc(ctx, poly * (size_t)by.n_acc, stored), down(ctx, poly * (size_t)(x.ext_limbs - by.n_acc));
     if (!x.ok() || (stored && !acc.ok()) || !down.ok()) return HISA_ERR_OOM;
-    return key_switch_fused_fp(ctx, d, d_bs, galois, B, key, add, add_bs, add_polys, out, x, stored ? acc.as<double>() : nullptr,
+    return key_switch_fused_fp(ctx, d, d_bs, galois, B, key, add, add_bs, add_polys, out, x, by, stored ? acc.as<double>() : nullptr,
                                down.as<double>(), false);
+}
+
+// Key switch of the third polynomials and the rescale of the result as one division by q_{l-1} P: cts3 [n_cts], stride words apart, of three
+// polynomials -> out [n_cts][2][l - 1][N]
+int relinearize_rescale_fp(hisa_ctx* ctx, const u64* cts3, u64 stride, size_t n_cts, int l, u64* out) {
+    if (!fused_key_switch_available(ctx)) return fail(ctx, HISA_ERR_ARG, "no fused key-switch path for these parameters");
+    if (l < 2) return fail(ctx, HISA_ERR_DEPTH_EXHAUSTED, "no level to rescale into");
+    if (t_analysis) {
+        TALLY(relinearize, HISA_OP_RELINEARIZE, n_cts, l);
+        TALLY(rescale, HISA_OP_RESCALE, n_cts, l);
+        TALLY(key_switch_calls, HISA_OP_KEY_SWITCH_CALLS, 1, l);
+        return HISA_OK;
+    }
+    auto it = ctx->keys.find(0);
+    if (it == ctx->keys.end()) return fail(ctx, HISA_ERR_NO_KEY, "no relinearisation key: call hisa_keygen");
+    const size_t lw = (size_t)l * ctx->N;
+    if (stride < 3 * lw) return fail(ctx, HISA_ERR_ARG, "bad stride");
+    Division by;
+    TRY(division_by_p_and_last(ctx, l, &by));
+    return key_switch_core_fp(ctx, cts3 + 2 * lw, stride, 0, n_cts, l, it->second, cts3, stride, 2, by, out);
 }
 
 static int key_switch_core(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois, size_t B, int l, const SwitchKey& key, const u64* add,
                            u64 add_bs, int add_polys, u64* out) {
-    return fused_key_switch_available(ctx) ? key_switch_core_fp(ctx, d, d_bs, galois, B, l, key, add, add_bs, add_polys, out)
-                                           : key_switch_core_int(ctx, d, d_bs, galois, B, l, key, add, add_bs, add_polys, out);
+    if (!fused_key_switch_available(ctx)) return key_switch_core_int(ctx, d, d_bs, galois, B, l, key, add, add_bs, add_polys, out);
+    Division by;
+    TRY(division_by_p(ctx, l, false, &by));
+    return key_switch_core_fp(ctx, d, d_bs, galois, B, l, key, add, add_bs, add_polys, by, out);
 }
 
 extern "C" int hisa_analysis_begin(hisa_ctx* ctx) {
@@ -2023,7 +2065,9 @@ extern "C" int hisa_rot_left_noalloc(hisa_ctx* ctx, const hisa_ct* a, int32_t st
     unsigned char* ws = (unsigned char*)ctx->noalloc_ws;
     FpExt x(ctx, l, K, alpha, (double*)ws, (double*)(ws + y_b));
     const size_t lw = (size_t)l * n;
-    TRY(key_switch_fused_fp(ctx, a->data + lw, words, g, 1, it->second, a->data, words, 1, out->data, x,
+    Division by;
+    TRY(division_by_p(ctx, l, true, &by));
+    TRY(key_switch_fused_fp(ctx, a->data + lw, words, g, 1, it->second, a->data, words, 1, out->data, x, by,
                             (double*)(ws + y_b + ext_b), (double*)(ws + y_b + ext_b + acc_b), true));
     out->scale = a->scale;
     return HISA_OK;

@@ -365,8 +365,8 @@ hipError_t launch_forward_rows_fp(int mode, const ConvertArgs& a, hipStream_t st
 // The rows behind the columns of a key switch's digits (ConvertArgs::out: [n_entries][digits][ext_limbs][N]), with the inner
 // product with `key` and the neighbouring halves of the division that follows, for the limbs x_begin .. x_end - 1.
 // FP_INV_D_TO_Y: limbs from n_acc on are sources of that division: down [n_entries * 2][ext_limbs - n_acc][N] =
-// (sum * c1[x] (+ addend)) after the inverse rows, `mid` of the division's columns; limbs below n_acc leave as
-// acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend), lazily reduced doubles for FP_FWD_SUB.
+// (sum * c1[x] (+ addend * c2[x])) after the inverse rows, `mid` of the division's columns; limbs below n_acc leave as
+// acc [n_entries][2][n_acc][N] = sum * c1[x] (+ addend * c2[x]), lazily reduced doubles for FP_FWD_SUB.
 // FP_FWD_CONV_SUB (limbs below n_acc): out holds the division's columns and receives its result.
 // Own digits and addend are read through sigma_g.
 // With StepArgs: several rotations of the same step_B ciphertexts, entry b being rotation b / step_B of ciphertext b % step_B.
@@ -382,6 +382,7 @@ struct InnerArgs {
     u64 galois;
     int n_acc, x_begin, x_end;
     const double* c1;                    // [ext_limbs]
+    const double* c2;                    // factors of the addend, limbs of q; null: one
     const u64* add; u64 add_bs, add_ps; int add_polys;
     double* acc;
     u64* out;
@@ -442,12 +443,9 @@ IntArgs int_base_args(const NttTables& t, int log_n);
 hipError_t launch_key_to_doubles(const FpPrime* fprimes, u64* key, int n_rows, int total, int log_n, hipStream_t st);
 hipError_t launch_key_to_residues(const FpPrime* fprimes, const u64* key, u64* out, int n_rows, int total, int log_n, hipStream_t st);
 
-// acc[b][p][x] = sum_j e_j[x] * key[j][p][prime(x)] in fp64; e_j[x] comes from ext unless x lies in digit j, then
+// acc[s][b][p][x] = sum_j e_j[x] * key_s[j][p][prime(x)] in fp64; e_j[x] comes from ext unless x lies in digit j, then
 // from own_src (the NTT-form input itself)
-hipError_t launch_inner_product_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
-                                   int alpha, const u64* key, int total, const u64* own_src, u64 own_bs, u64* acc, u64 acc_bs,
-                                   u64 n_batch, int log_n, hipStream_t st);
-// The same for n_steps rotations of the same n_batch ciphertexts (extended digits computed once from the unrotated
+// For n_steps rotations of the same n_batch ciphertexts (extended digits computed once from the unrotated
 // polynomial): rotation s uses keys[s] and gathers through galois[s]; acc entries are ordered rotation-major.
 // c0_src (with pmod[i] = P mod q_i): the b accumulator also takes P * sigma_s(c0) on the limbs of q, c0 read at
 // c0_src + b * own_bs like the own-digit limbs.

@@ -365,52 +365,8 @@ hipError_t launch_ntt_fp(int mode, int log_n, const FpArgs& a, const FpTask& tk,
 // inner product with the switching key, fp64
 // ---------------------------------------------------------------------------
 #define IPF_NT 256
-#define IPF_ZSPLIT 8
 #define IPF_MAXD 8
-// Keys are centred doubles here (key_to_doubles_kernel).  One thread owns one coefficient of one extended limb: the
-// 2*digits key values stay in registers while the
-// thread walks over its share of the batch, so the key is read IPF_ZSPLIT times per batch (from the L2 after the
-// first: see the launch order below), not once per ciphertext.
-__global__ __launch_bounds__(IPF_NT) void inner_product_fp_kernel(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits,
-                                                                  int l, int K, int L, int alpha, const u64* key, int total,
-                                                                  const u64* own_src, u64 own_bs, u64* acc, u64 acc_bs,
-                                                                  u64 n_batch, int log_n) {
-    const u64 n = (u64)1 << log_n;
-    const uint32_t j = blockIdx.x * IPF_NT + threadIdx.x;
-    // the limb is the slowest index of the launch: the blocks that share a limb's key rows (and sit on the same XCD,
-    // the number of blocks along x being a multiple of 8) run together and find them in that L2
-    const int x = blockIdx.z;
-    const int ext_limbs = l + K;
-    const int prime = x < l ? x : L + (x - l);
-    const int own_digit = x < l ? x / alpha : -1;
-    const double p = as_const(&fprimes[prime].p)[0], pinv = as_const(&fprimes[prime].p)[1];
-    const u64 per = (n_batch + IPF_ZSPLIT - 1) / IPF_ZSPLIT;
-    const u64 b0 = (u64)blockIdx.y * per;
-    const u64 b1 = b0 + per < n_batch ? b0 + per : n_batch;
-    double kb[IPF_MAXD], ka[IPF_MAXD];
-#pragma unroll
-    for (int d = 0; d < IPF_MAXD; d++) {
-        if (d < digits) {
-            kb[d] = ((const double*)key)[(((u64)d * 2 + 0) * total + prime) * n + j];
-            ka[d] = ((const double*)key)[(((u64)d * 2 + 1) * total + prime) * n + j];
-        }
-    }
-    for (u64 b = b0; b < b1; b++) {
-        double sb = 0.0, sa = 0.0;
-#pragma unroll
-        for (int d = 0; d < IPF_MAXD; d++) {
-            if (d < digits) {
-                const double e = d == own_digit ? fp_from_u64(own_src[b * own_bs + (u64)x * n + j])
-                                                : ext[b * ext_bs + ((u64)d * ext_limbs + x) * n + j];
-                sb += fp_mulmod(e, kb[d], p, pinv);
-                sa += fp_mulmod(e, ka[d], p, pinv);
-            }
-        }
-        acc[b * acc_bs + (u64)x * n + j] = fp_canonical(sb, p, pinv);
-        acc[b * acc_bs + ((u64)ext_limbs + x) * n + j] = fp_canonical(sa, p, pinv);
-    }
-}
-
+// Keys are centred doubles here (key_to_doubles_kernel).
 // Several rotations of the same ciphertexts: blockIdx.z is the rotation; its key values stay in registers while the
 // thread walks over the batch.  The extended digits come from the unrotated polynomial and are gathered through the
 // rotation's automorphism like the own-digit limbs.
@@ -645,18 +601,5 @@ hipError_t launch_inner_product_steps_fp(const FpPrime* fprimes, const double* e
     ProfScope prof__("inner_product_steps_fp_kernel", st);
     hipLaunchKernelGGL(inner_product_steps_fp_kernel, grid, dim3(IPF_NT), 0, st, fprimes, ext, ext_bs, digits, l, K, L, alpha,
                        steps, total, own_src, own_bs, acc, acc_bs, n_batch, c0_src, pmod, log_n);
-    return hipGetLastError();
-}
-
-hipError_t launch_inner_product_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
-                                   int alpha, const u64* key, int total, const u64* own_src, u64 own_bs, u64* acc, u64 acc_bs,
-                                   u64 n_batch, int log_n, hipStream_t st) {
-    DRY_RUN_RETURN();
-    if (digits > IPF_MAXD) return hipErrorInvalidValue;  // the caller falls back to the integer path
-    if (!fprimes || !ext || !key || !own_src || !acc) return hipErrorInvalidValue;
-    dim3 grid((1u << log_n) / IPF_NT, IPF_ZSPLIT, l + K);
-    ProfScope prof__("inner_product_fp_kernel", st);
-    hipLaunchKernelGGL(inner_product_fp_kernel, grid, dim3(IPF_NT), 0, st, fprimes, ext, ext_bs, digits, l, K, L, alpha, key,
-                       total, own_src, own_bs, acc, acc_bs, n_batch, log_n);
     return hipGetLastError();
 }
