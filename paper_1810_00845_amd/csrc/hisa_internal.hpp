@@ -483,6 +483,9 @@ hipError_t launch_mul_const(const PrimeConst* primes, const u64* a, u64* out, co
                             int log_n, hipStream_t st);
 hipError_t launch_mul_no_relin(const PrimeConst* primes, const u64* a, const u64* b, u64* out, int limbs, u64 n_batch,
                                u64 a_bs, u64 b_bs, u64 o_bs, int log_n, hipStream_t st);
+// x^2 + c x of two-polynomial entries as three-polynomial ones; consts: [limbs] residues of c, null: none
+hipError_t launch_square_linear(const PrimeConst* primes, const u64* a, u64* out, const u64* consts, int limbs, u64 n_batch, u64 a_bs,
+                                u64 o_bs, int log_n, hipStream_t st);
 hipError_t launch_encrypt_combine(const PrimeConst* primes, const u64* secret, const u64* pt, const u64* e, u64* ct,
                                   int limbs, u64 n_batch, u64 pt_bs, int log_n, hipStream_t st);
 // n_batch ciphertexts ct_bs words apart -> pt [n_batch][limbs][N]
