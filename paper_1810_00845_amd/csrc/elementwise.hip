@@ -10,6 +10,15 @@
 
 #define NT 256
 
+// Two coefficients a thread, 16 bytes an access (polynomials start at multiples of 8 KB of a pool block), and where a kernel
+// treats several polynomials alike, all of them: 24 products of two polynomials at N = 2^14, 8 limbs were 24576 workgroups of 2 KB
+// each way, 23 us, and are 18 now; the sums 25 us, 22 now.
+typedef u64 u64x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ u64x2 ld2(const u64* p) { return *(const u64x2*)p; }
+__device__ __forceinline__ void st2(u64* p, u64x2 v) { *(u64x2*)p = v; }
+#define PAIR_BLOCKS(log_n) ((1u << (log_n)) / (2 * NT))
+__device__ __forceinline__ u64 pair_at() { return 2 * ((u64)blockIdx.x * NT + threadIdx.x); }
+
 __global__ __launch_bounds__(NT) void sample_uniform_kernel(const PrimeConst* primes, u64 seed, u64 kind, u64 ctr,
                                                             PolyMap map, u64 batch_stride, u64 ctr_step, u64* out,
                                                             int log_n) {
@@ -82,24 +91,26 @@ __global__ __launch_bounds__(NT) void addsub_kernel(const PrimeConst* primes, co
                                                     int limbs, int polys_a, int polys_b, u64 a_bs, u64 b_bs, u64 o_bs,
                                                     int log_n) {
     const u64 n = (u64)1 << log_n;
-    const int limb = blockIdx.y % limbs, poly = blockIdx.y / limbs;
+    const int limb = blockIdx.y;
     const u64 bi = blockIdx.z;
     const u64 q = primes[limb].q;
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
-    const u64 off = ((u64)poly * limbs + limb) * n + j;
-    u64 x = a[bi * a_bs + off];
-    if (poly < polys_b) {
-        u64 y = b[bi * b_bs + off];
-        x = op == OP_ADD ? addmod(x, y, q) : submod(x, y, q);
+    const u64 j = (u64)limb * n + pair_at();
+    for (int poly = 0; poly < polys_a; poly++) {
+        const u64 off = (u64)poly * limbs * n + j;
+        u64x2 x = ld2(a + bi * a_bs + off);
+        if (poly < polys_b) {
+            const u64x2 y = ld2(b + bi * b_bs + off);
+            x = op == OP_ADD ? u64x2{addmod(x.x, y.x, q), addmod(x.y, y.y, q)} : u64x2{submod(x.x, y.x, q), submod(x.y, y.y, q)};
+        }
+        st2(out + bi * o_bs + off, x);
     }
-    out[bi * o_bs + off] = x;
 }
 
 hipError_t launch_addsub(const PrimeConst* primes, const u64* a, const u64* b, u64* out, int op, int limbs, int polys_a,
                          int polys_b, u64 n_batch, u64 a_bs, u64 b_bs, u64 o_bs, int log_n, hipStream_t st) {
     if (t_analysis) TALLY(add, HISA_OP_ADD, n_batch, limbs);
     DRY_RUN_RETURN();
-    dim3 grid((1u << log_n) / NT, limbs * polys_a, (unsigned)n_batch);
+    dim3 grid(PAIR_BLOCKS(log_n), limbs, (unsigned)n_batch);
     ProfScope prof__("addsub_kernel", st);
     hipLaunchKernelGGL(addsub_kernel, grid, dim3(NT), 0, st, primes, a, b, out, op, limbs, polys_a, polys_b, a_bs, b_bs,
                        o_bs, log_n);
@@ -138,15 +149,18 @@ hipError_t launch_add_const(const PrimeConst* primes, const u64* a, u64* out, co
 // ---- multiply ---------------------------------------------------------------
 // batch entry b is multiplied by plaintext b % pt_period (plaintexts [limbs][N], one after the other)
 __global__ __launch_bounds__(NT) void mul_plain_kernel(const PrimeConst* primes, const u64* a, const u64* pt, u64* out,
-                                                       int limbs, u64 a_bs, u64 o_bs, unsigned pt_period, int log_n) {
+                                                       int limbs, int polys, u64 a_bs, u64 o_bs, unsigned pt_period, int log_n) {
     const u64 n = (u64)1 << log_n;
-    const int limb = blockIdx.y % limbs, poly = blockIdx.y / limbs;
+    const int limb = blockIdx.y;
     const u64 bi = blockIdx.z;
     const PrimeConst pc = primes[limb];
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
-    const u64 off = ((u64)poly * limbs + limb) * n + j;
-    const u64* p = pt + (bi % pt_period) * (u64)limbs * n;
-    out[bi * o_bs + off] = mulmod_barrett(a[bi * a_bs + off], p[(u64)limb * n + j], pc.q, pc.r1, pc.r0);
+    const u64 j = (u64)limb * n + pair_at();
+    const u64x2 w = ld2(pt + (bi % pt_period) * (u64)limbs * n + j);
+    for (int poly = 0; poly < polys; poly++) {
+        const u64 off = (u64)poly * limbs * n + j;
+        const u64x2 x = ld2(a + bi * a_bs + off);
+        st2(out + bi * o_bs + off, u64x2{mulmod_barrett(x.x, w.x, pc.q, pc.r1, pc.r0), mulmod_barrett(x.y, w.y, pc.q, pc.r1, pc.r0)});
+    }
 }
 
 hipError_t launch_mul_plain(const PrimeConst* primes, const u64* a, const u64* pt, u64* out, int limbs, int polys,
@@ -154,9 +168,9 @@ hipError_t launch_mul_plain(const PrimeConst* primes, const u64* a, const u64* p
     if (t_analysis) TALLY(mul_plain, HISA_OP_MUL_PLAIN, n_batch, limbs);
     DRY_RUN_RETURN();
     if (pt_period == 0 || n_batch == 0 || n_batch > 65535) return hipErrorInvalidValue;
-    dim3 grid((1u << log_n) / NT, limbs * polys, (unsigned)n_batch);
+    dim3 grid(PAIR_BLOCKS(log_n), limbs, (unsigned)n_batch);
     ProfScope prof__("mul_plain_kernel", st);
-    hipLaunchKernelGGL(mul_plain_kernel, grid, dim3(NT), 0, st, primes, a, pt, out, limbs, a_bs, o_bs, pt_period, log_n);
+    hipLaunchKernelGGL(mul_plain_kernel, grid, dim3(NT), 0, st, primes, a, pt, out, limbs, polys, a_bs, o_bs, pt_period, log_n);
     return hipGetLastError();
 }
 
@@ -165,8 +179,9 @@ __global__ __launch_bounds__(NT) void mul_const_kernel(const PrimeConst* primes,
     const u64 n = (u64)1 << log_n;
     const int limb = blockIdx.y % limbs;
     const u64 q = primes[limb].q;
-    const u64 off = (u64)blockIdx.y * n + (u64)blockIdx.x * NT + threadIdx.x;
-    out[off] = shoup_mul(a[off], c.v[limb], c.v_sh[limb], q);
+    const u64 off = (u64)blockIdx.y * n + pair_at();
+    const u64x2 x = ld2(a + off);
+    st2(out + off, u64x2{shoup_mul(x.x, c.v[limb], c.v_sh[limb], q), shoup_mul(x.y, c.v[limb], c.v_sh[limb], q)});
 }
 
 hipError_t launch_mul_const(const PrimeConst* primes, const u64* a, u64* out, const u64* consts, int limbs, int polys,
@@ -176,7 +191,7 @@ hipError_t launch_mul_const(const PrimeConst* primes, const u64* a, u64* out, co
     // consts: [limbs] values followed by [limbs] Shoup companions
     LimbConsts c = {};
     for (int i = 0; i < limbs; i++) { c.v[i] = consts[i]; c.v_sh[i] = consts[limbs + i]; }
-    dim3 grid((1u << log_n) / NT, limbs * polys);
+    dim3 grid(PAIR_BLOCKS(log_n), limbs * polys);
     ProfScope prof__("mul_const_kernel", st);
     hipLaunchKernelGGL(mul_const_kernel, grid, dim3(NT), 0, st, primes, a, out, c, limbs, log_n);
     return hipGetLastError();
@@ -189,23 +204,27 @@ __global__ __launch_bounds__(NT) void mul_no_relin_kernel(const PrimeConst* prim
     const int limb = blockIdx.y;
     const u64 bi = blockIdx.z;
     const PrimeConst pc = primes[limb];
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
+    const u64 j = pair_at();
     const u64 o0 = (u64)limb * n + j, o1 = ((u64)limbs + limb) * n + j, o2 = ((u64)2 * limbs + limb) * n + j;
-    const u64 a0 = a[bi * a_bs + o0], a1 = a[bi * a_bs + o1];
-    const u64 b0 = b[bi * b_bs + o0], b1 = b[bi * b_bs + o1];
-    out[bi * o_bs + o0] = mulmod_barrett(a0, b0, pc.q, pc.r1, pc.r0);
-    Acc128 acc = {0, 0};
-    acc_mad(acc, a0, b1);
-    acc_mad(acc, a1, b0);
-    out[bi * o_bs + o1] = acc_reduce(acc, pc.q, pc.r1, pc.r0);
-    out[bi * o_bs + o2] = mulmod_barrett(a1, b1, pc.q, pc.r1, pc.r0);
+    const u64x2 a0 = ld2(a + bi * a_bs + o0), a1 = ld2(a + bi * a_bs + o1);
+    const u64x2 b0 = ld2(b + bi * b_bs + o0), b1 = ld2(b + bi * b_bs + o1);
+    auto product = [&](u64 x, u64 y) { return mulmod_barrett(x, y, pc.q, pc.r1, pc.r0); };
+    auto cross = [&](u64 x0, u64 y1, u64 x1, u64 y0) {
+        Acc128 acc = {0, 0};
+        acc_mad(acc, x0, y1);
+        acc_mad(acc, x1, y0);
+        return acc_reduce(acc, pc.q, pc.r1, pc.r0);
+    };
+    st2(out + bi * o_bs + o0, u64x2{product(a0.x, b0.x), product(a0.y, b0.y)});
+    st2(out + bi * o_bs + o1, u64x2{cross(a0.x, b1.x, a1.x, b0.x), cross(a0.y, b1.y, a1.y, b0.y)});
+    st2(out + bi * o_bs + o2, u64x2{product(a1.x, b1.x), product(a1.y, b1.y)});
 }
 
 hipError_t launch_mul_no_relin(const PrimeConst* primes, const u64* a, const u64* b, u64* out, int limbs, u64 n_batch,
                                u64 a_bs, u64 b_bs, u64 o_bs, int log_n, hipStream_t st) {
     if (t_analysis) TALLY(mul, HISA_OP_MUL, n_batch, limbs);
     DRY_RUN_RETURN();
-    dim3 grid((1u << log_n) / NT, limbs, (unsigned)n_batch);
+    dim3 grid(PAIR_BLOCKS(log_n), limbs, (unsigned)n_batch);
     ProfScope prof__("mul_no_relin_kernel", st);
     hipLaunchKernelGGL(mul_no_relin_kernel, grid, dim3(NT), 0, st, primes, a, b, out, limbs, a_bs, b_bs, o_bs, log_n);
     return hipGetLastError();
@@ -220,13 +239,14 @@ __global__ __launch_bounds__(NT) void square_linear_kernel(const PrimeConst* pri
     const int limb = blockIdx.y;
     const u64 bi = blockIdx.z;
     const PrimeConst pc = primes[limb];
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
+    const u64 j = pair_at();
     const u64 o0 = (u64)limb * n + j, o1 = ((u64)limbs + limb) * n + j, o2 = ((u64)2 * limbs + limb) * n + j;
-    const u64 a0 = a[bi * a_bs + o0], a1 = a[bi * a_bs + o1];
-    const u64 s = addmod(a0, c.v[limb], pc.q);
-    out[bi * o_bs + o0] = mulmod_barrett(a0, s, pc.q, pc.r1, pc.r0);
-    out[bi * o_bs + o1] = mulmod_barrett(a1, addmod(a0, s, pc.q), pc.q, pc.r1, pc.r0);
-    out[bi * o_bs + o2] = mulmod_barrett(a1, a1, pc.q, pc.r1, pc.r0);
+    const u64x2 a0 = ld2(a + bi * a_bs + o0), a1 = ld2(a + bi * a_bs + o1);
+    const u64x2 s = {addmod(a0.x, c.v[limb], pc.q), addmod(a0.y, c.v[limb], pc.q)};
+    auto product = [&](u64 x, u64 y) { return mulmod_barrett(x, y, pc.q, pc.r1, pc.r0); };
+    st2(out + bi * o_bs + o0, u64x2{product(a0.x, s.x), product(a0.y, s.y)});
+    st2(out + bi * o_bs + o1, u64x2{product(a1.x, addmod(a0.x, s.x, pc.q)), product(a1.y, addmod(a0.y, s.y, pc.q))});
+    st2(out + bi * o_bs + o2, u64x2{product(a1.x, a1.x), product(a1.y, a1.y)});
 }
 
 hipError_t launch_square_linear(const PrimeConst* primes, const u64* a, u64* out, const u64* consts, int limbs, u64 n_batch, u64 a_bs,
@@ -241,7 +261,7 @@ hipError_t launch_square_linear(const PrimeConst* primes, const u64* a, u64* out
     DRY_RUN_RETURN();
     LimbConsts c = {};
     for (int i = 0; i < limbs && consts; i++) c.v[i] = consts[i];
-    dim3 grid((1u << log_n) / NT, limbs, (unsigned)n_batch);
+    dim3 grid(PAIR_BLOCKS(log_n), limbs, (unsigned)n_batch);
     ProfScope prof__("square_linear_kernel", st);
     hipLaunchKernelGGL(square_linear_kernel, grid, dim3(NT), 0, st, primes, a, out, c, limbs, a_bs, o_bs, log_n);
     return hipGetLastError();
@@ -428,10 +448,10 @@ __global__ __launch_bounds__(NT) void fold_addend_kernel(const PrimeConst* prime
     const int poly = (int)(e & 1);
     if (poly >= add_polys) return;
     const PrimeConst pc = primes[limb];
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
-    u64* dst = acc + e * acc_bs + (u64)limb * n + j;
-    const u64 v = add[ct * add_bs + (u64)poly * add_ps + (u64)limb * n + j];
-    *dst = addmod(*dst, mulmod_barrett(v, pmod[limb], pc.q, pc.r1, pc.r0), pc.q);
+    const u64 j = (u64)limb * n + pair_at(), pm = pmod[limb];
+    u64* dst = acc + e * acc_bs + j;
+    const u64x2 v = ld2(add + ct * add_bs + (u64)poly * add_ps + j), x = ld2(dst);
+    st2(dst, u64x2{addmod(x.x, mulmod_barrett(v.x, pm, pc.q, pc.r1, pc.r0), pc.q), addmod(x.y, mulmod_barrett(v.y, pm, pc.q, pc.r1, pc.r0), pc.q)});
 }
 
 hipError_t launch_fold_addend(const PrimeConst* primes, u64* acc, u64 acc_bs, const u64* add, u64 add_bs, u64 add_ps,
@@ -441,7 +461,7 @@ hipError_t launch_fold_addend(const PrimeConst* primes, u64* acc, u64 acc_bs, co
     if (!primes || !acc || !add || !pmod || n_cts == 0 || 2 * n_cts > 65535 || l < 1 || add_polys < 1 || add_polys > 2)
         return hipErrorInvalidValue;
     if (acc_bs < (u64)l * n || add_ps < (u64)l * n || add_bs < (u64)add_polys * l * n) return hipErrorInvalidValue;
-    dim3 grid((1u << log_n) / NT, l, (unsigned)(2 * n_cts));
+    dim3 grid(PAIR_BLOCKS(log_n), l, (unsigned)(2 * n_cts));
     ProfScope prof__("fold_addend_kernel", st);
     hipLaunchKernelGGL(fold_addend_kernel, grid, dim3(NT), 0, st, primes, acc, acc_bs, add, add_bs, add_ps, add_polys, pmod, log_n);
     return hipGetLastError();
