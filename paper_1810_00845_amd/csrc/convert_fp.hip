@@ -18,8 +18,9 @@
 // and by memory in the rows, single ciphertexts by five launches of 4-8 us, each a chain of dependent levels.
 //
 // A wave holds 1024 coefficients, 16 per lane.  Five levels on a five-bit field take four in registers and the one on
-// the field's lowest bit after exchanging that bit (lane bit 5) with a register bit by v_permlane32_swap, so a row needs
-// two passes through LDS in all (one 64-bit exchange each way) and loads and stores are whole 512-byte lines.
+// the field's lowest bit after exchanging that bit (lane bit 5) with a register bit by v_permlane32_swap; those on b take
+// three in registers and two behind exchanges, since a lane's register pairs are neighbours in memory.  A row needs
+// two passes through LDS in all (one 64-bit exchange each way) and loads and stores are whole kilobytes.
 //
 // Ranges: values are exact integers |v| <= m p with m p < 2^53; every butterfly knows the bound m of its operands at
 // compile time (Bound below: plain floats that fold away after unrolling) and normalises only where the result could
@@ -70,6 +71,14 @@ __device__ __forceinline__ void inv_bfly(double& x, double& y, float& bx, float&
 __device__ __forceinline__ void swap_halves(double& x, double& y) {
     const auto lo = __builtin_amdgcn_permlane32_swap(lo32(x), lo32(y), false, false);
     const auto hi = __builtin_amdgcn_permlane32_swap(hi32(x), hi32(y), false, false);
+    x = mk64(lo[0], hi[0]);
+    y = mk64(lo[1], hi[1]);
+}
+
+// the same for lane bit 4
+__device__ __forceinline__ void swap_quarters(double& x, double& y) {
+    const auto lo = __builtin_amdgcn_permlane16_swap(lo32(x), lo32(y), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(hi32(x), hi32(y), false, false);
     x = mk64(lo[0], hi[0]);
     y = mk64(lo[1], hi[1]);
 }
@@ -138,6 +147,79 @@ __device__ __forceinline__ void cap_bounds(double (&v)[16], float (&m)[16], floa
     for (int r = 0; r < 16; r++) m[r] = top;
 }
 
+// The five levels on b of a row whose neighbouring coefficients share a lane: register 2 k + p of lane i holds element
+// b = 4 k + (i >> 4) of column c = 2 (i & 15) + p, so that the row is loaded and stored in 16-byte accesses (rows_inner tells
+// why).  Three levels in registers; the one on bit 1 of b behind an exchange of it (lane bit 5) with the register bit p, the one
+// on bit 0 behind an exchange (lane bit 4) with that register bit again.  Out: element 4 k + 2 (lane bit 4) + p of column
+// 2 (i & 15) + (lane bit 5).  last[k]: twiddle of level 4, group 2 k + (lane bit 4).
+__device__ __forceinline__ void unify(float& a, float& b) { a = b = fmaxf(a, b); }
+template <class TW>
+__device__ __forceinline__ void fwd_levels_b(double (&v)[16], float (&m)[16], TW tw, const double (&last)[8], Modulus q) {
+#pragma unroll
+    for (int j = 0; j < 3; j++) {
+        const int half = 2 - j;
+#pragma unroll
+        for (int g = 0; g < (1 << j); g++) {
+            const double w = tw(j, g);
+#pragma unroll
+            for (int lo = 0; lo < (2 << half); lo++) {
+                const int r0 = (g << (half + 2)) | lo, r1 = r0 + (2 << half);
+                fwd_bfly(v[r0], v[r1], m[r0], m[r1], w, 0.5f, q);
+            }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        swap_halves(v[2 * k], v[2 * k + 1]);
+        unify(m[2 * k], m[2 * k + 1]);
+        fwd_bfly(v[2 * k], v[2 * k + 1], m[2 * k], m[2 * k + 1], tw(3, k), 0.5f, q);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        swap_quarters(v[2 * k], v[2 * k + 1]);
+        unify(m[2 * k], m[2 * k + 1]);
+        fwd_bfly(v[2 * k], v[2 * k + 1], m[2 * k], m[2 * k + 1], last[k], 0.5f, q);
+    }
+}
+template <class TW>
+__device__ __forceinline__ void inv_levels_b(double (&v)[16], float (&m)[16], TW tw, const double (&last)[8], Modulus q) {
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        inv_bfly(v[2 * k], v[2 * k + 1], m[2 * k], m[2 * k + 1], last[k], 0.5f, q);
+        swap_quarters(v[2 * k], v[2 * k + 1]);
+        unify(m[2 * k], m[2 * k + 1]);
+    }
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        inv_bfly(v[2 * k], v[2 * k + 1], m[2 * k], m[2 * k + 1], tw(3, k), 0.5f, q);
+        swap_halves(v[2 * k], v[2 * k + 1]);
+        unify(m[2 * k], m[2 * k + 1]);
+    }
+#pragma unroll
+    for (int j = 2; j >= 0; j--) {
+        const int half = 2 - j;
+#pragma unroll
+        for (int g = 0; g < (1 << j); g++) {
+            const double w = tw(j, g);
+#pragma unroll
+            for (int lo = 0; lo < (2 << half); lo++) {
+                const int r0 = (g << (half + 2)) | lo, r1 = r0 + (2 << half);
+                inv_bfly(v[r0], v[r1], m[r0], m[r1], w, 0.5f, q);
+            }
+        }
+    }
+}
+// Words of a row in LDS.  In order: coefficient i at i + i / 32; of register 2 k + p: row_at + 132 k + p.  Between the levels on
+// b and on c: element b of column c at 33 rho(b) + c / 2 + 16 (c & 1), rho putting bit 1 of b on top, which spreads what the
+// lanes of either side touch over all banks; of register r before the levels on c: mid_c + r, of register r behind those on b: mid_b + 33 r.
+__device__ __forceinline__ int row_at(int lane) { return 33 * (lane >> 4) + 2 * (lane & 15); }
+__device__ __forceinline__ int mid_b(int lane) { return 528 * ((lane >> 4) & 1) + (lane & 15) + 16 * (lane >> 5); }
+__device__ __forceinline__ int mid_c(int lane) {
+    const int b = lane & 31;
+    return 33 * (((b & 2) << 3) | ((b >> 2) << 1) | (b & 1)) + 16 * (lane >> 5);
+}
+#define ROW_REG(r) (132 * ((r) >> 1) + ((r) & 1))
+
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, double& x, double& y) {
     const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
@@ -157,7 +239,7 @@ __device__ __forceinline__ void row_tables(RowTwiddles& w, const double* table, 
 __device__ __forceinline__ void load_twiddles_b(RowTwiddles& w, int lane) {
     const rsrc_t r = make_rsrc(w.tab, SPLIT_ROW * 8);
 #pragma unroll
-    for (int k = 0; k < 4; k++) bload2(r, (uint32_t)(lane >> 5) * 64u, 128u + (uint32_t)k * 16u, w.last_b[2 * k], w.last_b[2 * k + 1]);
+    for (int k = 0; k < 4; k++) bload2(r, (uint32_t)((lane >> 4) & 1) * 64u, 128u + (uint32_t)k * 16u, w.last_b[2 * k], w.last_b[2 * k + 1]);
 }
 __device__ __forceinline__ void load_twiddles_c(RowTwiddles& w, int lane) {
     const rsrc_t r = make_rsrc(w.tab, SPLIT_ROW * 8);
@@ -172,13 +254,13 @@ __device__ __forceinline__ void load_row_twiddles(RowTwiddles& w, const double* 
     load_twiddles_b(w, lane);
 }
 
-// The ten levels of a row; register r of lane i is coefficient 64 r + i before and after.  m: bounds, in and out.
+// The ten levels of a row; register 2 k + p of lane i is coefficient 128 k + 2 i + p before and after.  m: bounds, in and out.
 // LATE: the twiddles of c are fetched behind the levels on b (a caller short of registers).  LEAVE: the result stays in
-// the wave's LDS part, coefficient i at i + i / 32.
+// the wave's LDS part, in order.
 template <bool LATE = false, bool LEAVE = false>
 __device__ __forceinline__ void row_forward(double (&v)[16], float (&m)[16], RowTwiddles& w, double* lds, int lane, Modulus q, float cap) {
     const int h = lane >> 5, s = lane & 31;
-    fwd_levels5(v, m, [&](int j, int g) { return as_const(w.tab)[(1 << j) + g]; }, 0.5f, w.last_b, q);
+    fwd_levels_b(v, m, [&](int j, int g) { return as_const(w.tab)[(1 << j) + g]; }, w.last_b, q);
     cap_bounds(v, m, BOUND_LIMIT, q);
     if (LATE) {
         SCHED_FENCE();
@@ -186,10 +268,10 @@ __device__ __forceinline__ void row_forward(double (&v)[16], float (&m)[16], Row
     }
     xchg_sync<true>();
 #pragma unroll
-    for (int r = 0; r < 16; r++) lds[(2 * h + (r >> 1) * 4 + (r & 1)) * 33 + s] = v[r];
+    for (int r = 0; r < 16; r++) lds[mid_b(lane) + 33 * r] = v[r];
     xchg_sync<true>();
 #pragma unroll
-    for (int r = 0; r < 16; r++) v[r] = lds[s * 33 + h + 2 * r];
+    for (int r = 0; r < 16; r++) v[r] = lds[mid_c(lane) + r];
     fwd_levels5(v, m, [&](int j, int g) { return g == 0 ? w.base[j] : fp_mulmod(w.base[j], as_const(w.head)[32 + g], q.p, q.pinv); },
                 0.6f, w.last_c, q);
     cap_bounds(v, m, cap, q);
@@ -199,14 +281,14 @@ __device__ __forceinline__ void row_forward(double (&v)[16], float (&m)[16], Row
     if (LEAVE) return;
     xchg_sync<true>();
 #pragma unroll
-    for (int r = 0; r < 16; r++) v[r] = lds[66 * r + lane + h];
+    for (int r = 0; r < 16; r++) v[r] = lds[row_at(lane) + ROW_REG(r)];
 }
 
 __device__ __forceinline__ void row_inverse(double (&v)[16], float (&m)[16], RowTwiddles& w, double* lds, int lane, Modulus q) {
     const int h = lane >> 5, s = lane & 31;
     xchg_sync<true>();
 #pragma unroll
-    for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = v[r];
+    for (int r = 0; r < 16; r++) lds[row_at(lane) + ROW_REG(r)] = v[r];
     xchg_sync<true>();
 #pragma unroll
     for (int r = 0; r < 16; r++) v[r] = lds[s * 33 + 2 * h + (r >> 1) * 4 + (r & 1)];     // lane b = s, elements of c
@@ -215,26 +297,53 @@ __device__ __forceinline__ void row_inverse(double (&v)[16], float (&m)[16], Row
     cap_bounds(v, m, 2.01f, q);
     xchg_sync<true>();
 #pragma unroll
-    for (int r = 0; r < 16; r++) lds[s * 33 + h + 2 * r] = v[r];
+    for (int r = 0; r < 16; r++) lds[mid_c(lane) + r] = v[r];
     xchg_sync<true>();
 #pragma unroll
-    for (int r = 0; r < 16; r++) v[r] = lds[(2 * h + (r >> 1) * 4 + (r & 1)) * 33 + s];   // lane c = s, elements of b
-    inv_levels5(v, m, [&](int j, int g) { return as_const(w.tab)[(1 << j) + g]; }, 0.5f, w.last_b, q);
+    for (int r = 0; r < 16; r++) v[r] = lds[mid_b(lane) + 33 * r];
+    inv_levels_b(v, m, [&](int j, int g) { return as_const(w.tab)[(1 << j) + g]; }, w.last_b, q);
     cap_bounds(v, m, 1.01f, q);
 }
 
-// the row's 1024 words of a limb, read through sigma_g when galois != 0
+__device__ __forceinline__ void load_row(double (&v)[16], rsrc_t row, int lane) {
+#pragma unroll
+    for (int k = 0; k < 8; k++) bload2(row, (uint32_t)lane * 16u, (uint32_t)k * 1024u, v[2 * k], v[2 * k + 1]);
+}
+__device__ __forceinline__ void store_row(rsrc_t row, int lane, const double (&v)[16]) {
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const u32x4_t d = {lo32(v[2 * k]), hi32(v[2 * k]), lo32(v[2 * k + 1]), hi32(v[2 * k + 1])};
+        __builtin_amdgcn_raw_buffer_store_b128(d, row, (int)((uint32_t)lane * 16u), k * 1024, 0);
+    }
+}
+__device__ __forceinline__ void from_residues(double (&v)[16]) {
+#pragma unroll
+    for (int r = 0; r < 16; r++) v[r] = fp_from_u64((u64)__double_as_longlong(v[r]));
+}
+__device__ __forceinline__ void store_residues(rsrc_t row, int lane, double (&v)[16], Modulus q) {
+#pragma unroll
+    for (int r = 0; r < 16; r++) v[r] = __longlong_as_double((long long)fp_canonical(v[r], q.p, q.pinv));
+    store_row(row, lane, v);
+}
+
+// the row's 1024 words of a limb, read through sigma_g when galois != 0: neighbours come from a pair of neighbours, in either
+// order (their exponents are N apart, and stay so under an odd factor)
 template <int K3>
 __device__ __forceinline__ void load_row_through(double (&v)[16], const u64* limb, u64 galois, uint32_t row, int lane) {
     if (galois) {
         const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
-        const Gather t = make_gather(galois, row, lane, 10 + K3);
+        const Gather t = make_gather(galois, row, 2 * lane, 10 + K3);
 #pragma unroll
-        for (int r = 0; r < 16; r++) v[r] = bloadf(src, gather_offset(t, r), 0);
+        for (int k = 0; k < 8; k++) {
+            const uint32_t at = gather_offset(t, 2 * k);
+            double x, y;
+            bload2(src, at & ~8u, 0, x, y);
+            const bool turned = (at & 8u) != 0;
+            v[2 * k] = turned ? y : x;
+            v[2 * k + 1] = turned ? x : y;
+        }
     } else {
-        const rsrc_t src = make_rsrc(limb + row * 1024u, 8192u);
-#pragma unroll
-        for (int r = 0; r < 16; r++) v[r] = bloadf(src, (uint32_t)lane * 8u, (uint32_t)r * 512u);
+        load_row(v, make_rsrc(limb + row * 1024u, 8192u), lane);
     }
 }
 
@@ -258,15 +367,11 @@ __device__ __forceinline__ void rows_inverse(const ConvertArgs& a, int n_tasks, 
     load_row_through<K3>(v, src_p, a.galois, row, lane);
     RowTwiddles w;
     load_row_twiddles(w, a.sinv, a.table_stride, prime, row, lane);
+    from_residues(v);
 #pragma unroll
-    for (int r = 0; r < 16; r++) {
-        v[r] = fp_from_u64((u64)__double_as_longlong(v[r]));
-        m[r] = 1.0f;
-    }
+    for (int r = 0; r < 16; r++) m[r] = 1.0f;
     row_inverse(v, m, w, lds, lane, q);
-    const rsrc_t dst = make_rsrc(a.mid + ((u64)b * a.n_src + k) * n + row * 1024u, 8192u);
-#pragma unroll
-    for (int r = 0; r < 16; r++) bstoref(dst, (uint32_t)lane * 8u, (uint32_t)r * 512u, v[r]);
+    store_row(make_rsrc(a.mid + ((u64)b * a.n_src + k) * n + row * 1024u, 8192u), lane, v);
 }
 
 // ---------------------------------------------------------------------------
@@ -468,12 +573,12 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
     constexpr u64 n = (u64)1 << (10 + K3);
     u64* out_p = a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n + row * 1024u;
     const rsrc_t dst = make_rsrc(out_p, 8192u);
-    const uint32_t lane8 = (uint32_t)lane * 8u;
 
     double v[16];
     float m[16];
+    load_row(v, dst, lane);
 #pragma unroll
-    for (int r = 0; r < 16; r++) { v[r] = bloadf(dst, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+    for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
     RowTwiddles w;
     load_row_twiddles(w, a.sfwd, a.table_stride, prime, row, lane);
     row_forward(v, m, w, lds, lane, q, MODE == FP_FWD_CONV ? BOUND_LIMIT : 5.2f);    // 5.2 p and the accumulator's 2.75 p stay below 8 p
@@ -481,36 +586,33 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
     if (MODE == FP_FWD_CONV) {
         // the extended digits stay doubles: their only readers multiply them by key values in the same arithmetic
 #pragma unroll
-        for (int r = 0; r < 16; r++) bstoref(dst, lane8, (uint32_t)r * 512u, fp_norm(v[r], q.p, q.pinv));
+        for (int r = 0; r < 16; r++) v[r] = fp_norm(v[r], q.p, q.pinv);
+        store_row(dst, lane, v);
         return;
     }
-    const rsrc_t acc = make_rsrc(a.acc + b * a.acc_bs + (u64)e * n + row * 1024u, 8192u);
+    double va[16];
+    load_row(va, make_rsrc(a.acc + b * a.acc_bs + (u64)e * n + row * 1024u, 8192u), lane);
     if (MODE == FP_FWD_SUB) {      // out = acc - transform: acc already is (sum * P^-1 + addend), the table carries the P^-1
-        double va[16];
 #pragma unroll
-        for (int r = 0; r < 16; r++) va[r] = bloadf(acc, lane8, (uint32_t)r * 512u);
-#pragma unroll
-        for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(va[r] - v[r], q.p, q.pinv));
+        for (int r = 0; r < 16; r++) v[r] = va[r] - v[r];
+        store_residues(dst, lane, v, q);
         return;
     }
     // out = (acc - transform) * P^-1 (+ addend)
     const double pin = as_const(a.pinv_tab)[prime];
     const bool with_add = a.add && (int)(b % a.add_div) < a.add_polys;
-    u64 va[16];
-#pragma unroll
-    for (int r = 0; r < 16; r++) va[r] = bload(acc, lane8, (uint32_t)r * 512u);
+    from_residues(va);
     if (with_add) {
         double vb[16];
         load_row_through<K3>(vb, a.add + (b / a.add_div) * a.add_bs + (b % a.add_div) * a.add_ps + (u64)e * n, 0, row, lane);
+        from_residues(vb);
 #pragma unroll
-        for (int r = 0; r < 16; r++)
-            bstore(dst, lane8, (uint32_t)r * 512u,
-                   fp_canonical(fp_mulmod(fp_from_u64(va[r]) - v[r], pin, q.p, q.pinv) + fp_from_u64((u64)__double_as_longlong(vb[r])), q.p, q.pinv));
+        for (int r = 0; r < 16; r++) v[r] = fp_mulmod(va[r] - v[r], pin, q.p, q.pinv) + vb[r];
     } else {
 #pragma unroll
-        for (int r = 0; r < 16; r++)
-            bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(fp_mulmod(fp_from_u64(va[r]) - v[r], pin, q.p, q.pinv), q.p, q.pinv));
+        for (int r = 0; r < 16; r++) v[r] = fp_mulmod(va[r] - v[r], pin, q.p, q.pinv);
     }
+    store_residues(dst, lane, v, q);
 }
 
 // ---------------------------------------------------------------------------
@@ -530,6 +632,10 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
 // the digits of a limb (the same for all of them) stay in the L2; the keys, each read once, are what the launches stream.
 // 24 rotations of one ciphertext at N = 2^14, 12 limbs: 187 -> 162 us against inner products and a division as separate
 // launches with the accumulators in memory between them.
+// Accesses are 16 bytes a lane: at four waves a SIMD, each waiting for one row at a time, three reads and a write in 8-byte
+// accesses run at 4.9 TB/s here and at 5.4 in 16-byte ones (5.3 and 5.4 with all wave slots filled).  64 rotations at N = 2^15, 16 limbs:
+// the limbs of q 550 -> 517 us, the special ones 199 -> 190.  Tried and taken back there: two waves a SIMD with everything fetched
+// ahead (603 and 235), two entries a workgroup for the sake of the key rows (557), other orders of the tasks (549 .. 556).
 #define IP_CAP 5.5f
 struct OneStep {};
 template <int K3, int MODE, class S>
@@ -538,7 +644,7 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     const int per = (n_tasks + 7) >> 3;
     const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     if (task >= n_tasks) return;
-    const int lane = threadIdx.x & 63, h = lane >> 5;
+    const int lane = threadIdx.x & 63, at = row_at(lane);
     const int poly = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     double* lds = lds_all + poly * ROW_LDS;
     const uint32_t unit = (uint32_t)task / a.n_entries;
@@ -548,7 +654,6 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     const int prime = prime_at(x, a.l, a.L);
     const Modulus q = modulus(a.fprimes, prime);
     constexpr u64 n = (u64)1 << (10 + K3);
-    const uint32_t lane8 = (uint32_t)lane * 8u;
     u64 ct = b, galois = g.galois;
     const u64* key = g.key;
     if constexpr (STEPS) {
@@ -567,17 +672,19 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
             double v[16];
             if (x >= a.dg[d].own_lo && x < a.dg[d].own_lo + a.dg[d].own_n) {
                 load_row_through<K3>(v, g.own + ct * g.own_bs + (u64)x * n, galois, row, lane);
+                from_residues(v);
 #pragma unroll
-                for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = fp_from_u64((u64)__double_as_longlong(v[r]));
+                for (int r = 0; r < 16; r++) lds[at + ROW_REG(r)] = v[r];
             } else if (STEPS) {
                 load_row_through<K3>(v, a.out + ct * a.out_bs + (u64)(a.dg[d].out_pos0 + x) * n, galois, row, lane);
 #pragma unroll
-                for (int r = 0; r < 16; r++) lds[66 * r + lane + h] = v[r];
+                for (int r = 0; r < 16; r++) lds[at + ROW_REG(r)] = v[r];
             } else {
                 const rsrc_t src = make_rsrc((const double*)a.out + b * a.out_bs + (u64)(a.dg[d].out_pos0 + x) * n + row * 1024u, 8192u);
                 float m[16];
+                load_row(v, src, lane);
 #pragma unroll
-                for (int r = 0; r < 16; r++) { v[r] = bloadf(src, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+                for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
                 RowTwiddles w;
                 row_tables(w, a.sfwd, a.table_stride, prime, row);
                 int tl = lane;
@@ -591,18 +698,16 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
         const bool two = d0 + 1 < a.n_digits;
         const rsrc_t k0r = make_rsrc(key_p, 8192u), k1r = make_rsrc(two ? key_p + (u64)2 * a.total * n : key_p, 8192u);
         double k0[16], k1[16];
-#pragma unroll
-        for (int r = 0; r < 16; r++) k0[r] = bloadf(k0r, lane8, (uint32_t)r * 512u);
+        load_row(k0, k0r, lane);
         // (also without a second digit, then of the first: words left undefined would stay live through the loop)
-#pragma unroll
-        for (int r = 0; r < 16; r++) k1[r] = bloadf(k1r, lane8, (uint32_t)r * 512u);
+        load_row(k1, k1r, lane);
         SCHED_FENCE();
         __syncthreads();
 #pragma unroll
-        for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(lds_all[66 * r + lane + h], k0[r], q.p, q.pinv);
+        for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(lds_all[at + ROW_REG(r)], k0[r], q.p, q.pinv);
         if (two) {
 #pragma unroll
-            for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(lds_all[ROW_LDS + 66 * r + lane + h], k1[r], q.p, q.pinv);
+            for (int r = 0; r < 16; r++) sum[r] += fp_mulmod(lds_all[ROW_LDS + at + ROW_REG(r)], k1[r], q.p, q.pinv);
         }
         if (d0 % 4 == 2 && d0 + 2 < a.n_digits) {
 #pragma unroll
@@ -617,8 +722,7 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     if (x < a.l && poly < g.add_polys) {
         double t[16];
         load_row_through<K3>(t, g.add + ct * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, galois, row, lane);
-#pragma unroll
-        for (int r = 0; r < 16; r++) t[r] = fp_from_u64((u64)__double_as_longlong(t[r]));
+        from_residues(t);
         if (g.c2) {
             const double c2 = as_const(g.c2)[x];
 #pragma unroll
@@ -642,18 +746,19 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
     } else if (MODE == FP_FWD_CONV_SUB) {  // the division's columns are there already: its rows, and the difference
         double v[16];
         float m[16];
+        load_row(v, dst, lane);
 #pragma unroll
-        for (int r = 0; r < 16; r++) { v[r] = bloadf(dst, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+        for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
         RowTwiddles w;
         load_row_twiddles(w, a.sfwd, a.table_stride, prime, row, lane);
         __syncthreads();
         row_forward(v, m, w, lds, lane, q, 5.2f);
 #pragma unroll
-        for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(sum[r] - v[r], q.p, q.pinv));
+        for (int r = 0; r < 16; r++) v[r] = sum[r] - v[r];
+        store_residues(dst, lane, v, q);
         return;
     }
-#pragma unroll
-    for (int r = 0; r < 16; r++) bstoref(dst, lane8, (uint32_t)r * 512u, sum[r]);
+    store_row(dst, lane, sum);
 }
 
 // ---------------------------------------------------------------------------
@@ -1020,25 +1125,24 @@ __device__ __forceinline__ void plain_rows(const FpArgs& a, const FpTask& tk, do
     const int prime = tk.prime[e];
     const Modulus q = modulus(a.fprimes, prime);
     const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)tk.pos[e] * n + (u64)row * 1024u, 8192u);
-    const uint32_t lane8 = (uint32_t)lane * 8u;
     double v[16];
     float m[16];
     RowTwiddles w;
     if (INV) {
         load_row_through<K3>(v, a.in + b * a.in_bs + (u64)tk.pos[e] * n, 0, (uint32_t)row, lane);
         load_row_twiddles(w, a.sinv, a.table_stride, prime, (uint32_t)row, lane);
+        from_residues(v);
 #pragma unroll
-        for (int r = 0; r < 16; r++) { v[r] = fp_from_u64((u64)__double_as_longlong(v[r])); m[r] = 1.0f; }
+        for (int r = 0; r < 16; r++) m[r] = 1.0f;
         row_inverse(v, m, w, lds, lane, q);
-#pragma unroll
-        for (int r = 0; r < 16; r++) bstoref(dst, lane8, (uint32_t)r * 512u, v[r]);
+        store_row(dst, lane, v);
     } else {
+        load_row(v, dst, lane);
 #pragma unroll
-        for (int r = 0; r < 16; r++) { v[r] = bloadf(dst, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+        for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
         load_row_twiddles(w, a.sfwd, a.table_stride, prime, (uint32_t)row, lane);
         row_forward(v, m, w, lds, lane, q, BOUND_LIMIT);
-#pragma unroll
-        for (int r = 0; r < 16; r++) bstore(dst, lane8, (uint32_t)r * 512u, fp_canonical(v[r], q.p, q.pinv));
+        store_residues(dst, lane, v, q);
     }
 }
 
@@ -1133,32 +1237,32 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a)
     const u64 b = task - unit * a.n_entries;
     const int row = unit & ((1 << K3) - 1), limb = unit >> K3;
     const Modulus q = modulus(a.fprimes, limb);
-    const uint32_t lane8 = (uint32_t)lane * 8u;
     u64* c0 = a.ct + ((b * 2) * a.limbs + limb) * n + (u64)row * 1024u;
     const rsrc_t r0 = make_rsrc(c0, 8192u), r1 = make_rsrc(c0 + a.limbs * n, 8192u);
     const rsrc_t sk = make_rsrc(a.secret + limb * n + (u64)row * 1024u, 8192u), pt = make_rsrc(a.pt[b] + limb * n + (u64)row * 1024u, 8192u);
-    double e[16], v[16];
+    double e[16], v[16], s[16];
     float m[16];
     RowTwiddles w;
     load_row_twiddles(w, a.sfwd, a.table_stride, limb, (uint32_t)row, lane);
+    load_row(e, r0, lane);
 #pragma unroll
-    for (int r = 0; r < 16; r++) { e[r] = bloadf(r0, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+    for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
     row_forward(e, m, w, lds, lane, q, 3.0f);       // 3 + 1 (message) + 2.5 (a s, below) stays within 8 p
+    load_row(v, r1, lane);
 #pragma unroll
-    for (int r = 0; r < 16; r++) { v[r] = bloadf(r1, lane8, (uint32_t)r * 512u); m[r] = COLUMNS_BOUND; }
+    for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
     row_forward(v, m, w, lds, lane, q, 5.2f);
-    u64 s[16];
+    load_row(s, sk, lane);
+    from_residues(s);
 #pragma unroll
-    for (int r = 0; r < 16; r++) s[r] = bload(sk, lane8, (uint32_t)r * 512u);
-#pragma unroll
-    for (int r = 0; r < 16; r++) bstore(r1, lane8, (uint32_t)r * 512u, fp_canonical(v[r], q.p, q.pinv));
-#pragma unroll
-    for (int r = 0; r < 16; r++) e[r] -= fp_mulmod(v[r], fp_from_u64(s[r]), q.p, q.pinv);
+    for (int r = 0; r < 16; r++) e[r] -= fp_mulmod(v[r], s[r], q.p, q.pinv);
+    store_residues(r1, lane, v, q);
     SCHED_FENCE();
+    load_row(s, pt, lane);
+    from_residues(s);
 #pragma unroll
-    for (int r = 0; r < 16; r++) s[r] = bload(pt, lane8, (uint32_t)r * 512u);
-#pragma unroll
-    for (int r = 0; r < 16; r++) bstore(r0, lane8, (uint32_t)r * 512u, fp_canonical(e[r] + fp_from_u64(s[r]), q.p, q.pinv));
+    for (int r = 0; r < 16; r++) e[r] += s[r];
+    store_residues(r0, lane, e, q);
 }
 
 // the same by four waves a row, the two transforms side by side
