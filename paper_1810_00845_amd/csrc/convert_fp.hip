@@ -378,8 +378,9 @@ __device__ __forceinline__ void rows_inverse(const ConvertArgs& a, int n_tasks, 
 // columns
 // ---------------------------------------------------------------------------
 // Bound by fp64 issue beside memory: 64 rotations at N = 2^15, 16 limbs, with the products and levels left out the launch over
-// the digits takes 207 us (its bytes), with the stores left out 240 us, whole 284 us.  Its conversion sums are FpSums: products
-// reduced one by one made it 305 us, those of the division by P 208 us against 188 now.
+// the digits takes 207 us (its bytes), with the stores left out 240 us, whole 265 us.  Its conversion sums are FpSums: products
+// reduced one by one made it 305 us, those of the division by P 208 us against 183 now.  The sums are not held over the sources'
+// levels, so that 80 registers do and three workgroups share a compute unit (277 us with two).
 template <int RB>
 struct Col {
     static constexpr int NR = RB == 5 ? 16 : (1 << RB);      // coefficients per lane
@@ -470,9 +471,6 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
         const int prime = mine ? prime_at(e, a.l, a.L) : 0;
         const Modulus q = modulus(a.fprimes, prime);
         const double* head = a.sfwd + (u64)prime * a.table_stride;
-        double v[NR];
-#pragma unroll
-        for (int r = 0; r < NR; r++) v[r] = 0.0;
         for (int c0 = 0; c0 < n_src; c0 += a.chunk) {
             const int c1 = min(c0 + a.chunk, n_src);
             if (!resident || round == 0) {
@@ -503,6 +501,15 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
             if (mine) {
                 const cdouble_ptr hat = as_const(a.dg[digit].hat) + prime;
                 const double* y0 = ylds + lane;
+                const rsrc_t dst = make_rsrc((double*)a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n, (uint32_t)n * 8u);
+                double v[NR];
+                if (c0) {                              // sums over earlier chunks wait where the result goes
+#pragma unroll
+                    for (int r = 0; r < NR; r++) v[r] = bloadf(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u);
+                } else {
+#pragma unroll
+                    for (int r = 0; r < NR; r++) v[r] = 0.0;
+                }
                 if (n_src == 1) {                      // rescale, digits of one limb: the sum's reduction costs more than a product
                     const double f = hat[0];
 #pragma unroll
@@ -534,20 +541,19 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
                         for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_sum_value(s[r], FP_SUM_BASE, q.p, q.pinv), q.p, q.pinv);
                     }
                 }
-            }
-        }
-        if (mine) {
-            double last[8] = {};
-            if (RB == 5) {
-                const rsrc_t hr = make_rsrc(head, HEAD * 8);
+                if (c1 == n_src) {
+                    double last[8] = {};
+                    if (RB == 5) {
+                        const rsrc_t hr = make_rsrc(head, HEAD * 8);
 #pragma unroll
-                for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
-            }
-            fwd_columns<RB>(v, head, last, q);
-            const rsrc_t dst = make_rsrc((double*)a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n, (uint32_t)n * 8u);
+                        for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
+                    }
+                    fwd_columns<RB>(v, head, last, q);
+                }
 #pragma unroll
-            for (int r = 0; r < NR; r++)
-                bstoref(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u, v[r]);
+                for (int r = 0; r < NR; r++)
+                    bstoref(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u, v[r]);
+            }
         }
     }
 }
@@ -1312,8 +1318,8 @@ __global__ __launch_bounds__(2 * WIDE_NT, 4) void encrypt_rows_wide_kernel(Encry
 // MODE (enum FpMode) names the stage a launch belongs to, so that a profile tells the ModUp's columns from the ModDown's;
 // COLUMNS: the launch in which all target limbs of a digit share one pass over its sources, else the rows.
 constexpr int fp_threads(int mode, bool columns) { return columns ? 1024 : (mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB) ? 128 : ROWS_NT; }
-// waves per SIMD to leave room for: the columns of N = 2^14 and 2^13 come out a few registers above a whole workgroup more
-constexpr int fp_waves(int k3, bool columns) { return !columns ? 4 : k3 == 4 ? 6 : k3 == 3 ? 8 : 4; }
+// waves per SIMD to leave room for: three workgroups of eight waves of the columns at N = 2^15 and 2^14, four at 2^13
+constexpr int fp_waves(int k3, bool columns) { return !columns ? 4 : k3 >= 4 ? 6 : k3 == 3 ? 8 : 4; }
 
 template <int K3, int MODE, bool COLUMNS>
 __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), fp_waves(K3, COLUMNS)) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
