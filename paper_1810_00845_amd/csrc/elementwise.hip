@@ -95,14 +95,22 @@ __global__ __launch_bounds__(NT) void addsub_kernel(const PrimeConst* primes, co
     const u64 bi = blockIdx.z;
     const u64 q = primes[limb].q;
     const u64 j = (u64)limb * n + pair_at();
-    for (int poly = 0; poly < polys_a; poly++) {
-        const u64 off = (u64)poly * limbs * n + j;
-        u64x2 x = ld2(a + bi * a_bs + off);
-        if (poly < polys_b) {
-            const u64x2 y = ld2(b + bi * b_bs + off);
-            x = op == OP_ADD ? u64x2{addmod(x.x, y.x, q), addmod(x.y, y.y, q)} : u64x2{submod(x.x, y.x, q), submod(x.y, y.y, q)};
+    // two polynomials' loads ahead of the first store: a small call waits once
+    for (int poly = 0; poly < polys_a; poly += 2) {
+        u64x2 x[2], y[2];
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            const u64 off = (u64)(poly + k) * limbs * n + j;
+            if (poly + k < polys_a) x[k] = ld2(a + bi * a_bs + off);
+            if (poly + k < polys_b) y[k] = ld2(b + bi * b_bs + off);
         }
-        st2(out + bi * o_bs + off, x);
+#pragma unroll
+        for (int k = 0; k < 2; k++) {
+            if (poly + k >= polys_a) break;
+            if (poly + k < polys_b)
+                x[k] = op == OP_ADD ? u64x2{addmod(x[k].x, y[k].x, q), addmod(x[k].y, y[k].y, q)} : u64x2{submod(x[k].x, y[k].x, q), submod(x[k].y, y[k].y, q)};
+            st2(out + bi * o_bs + (u64)(poly + k) * limbs * n + j, x[k]);
+        }
     }
 }
 
@@ -156,10 +164,16 @@ __global__ __launch_bounds__(NT) void mul_plain_kernel(const PrimeConst* primes,
     const PrimeConst pc = primes[limb];
     const u64 j = (u64)limb * n + pair_at();
     const u64x2 w = ld2(pt + (bi % pt_period) * (u64)limbs * n + j);
-    for (int poly = 0; poly < polys; poly++) {
-        const u64 off = (u64)poly * limbs * n + j;
-        const u64x2 x = ld2(a + bi * a_bs + off);
-        st2(out + bi * o_bs + off, u64x2{mulmod_barrett(x.x, w.x, pc.q, pc.r1, pc.r0), mulmod_barrett(x.y, w.y, pc.q, pc.r1, pc.r0)});
+    for (int poly = 0; poly < polys; poly += 2) {
+        u64x2 x[2];
+#pragma unroll
+        for (int k = 0; k < 2; k++)
+            if (poly + k < polys) x[k] = ld2(a + bi * a_bs + (u64)(poly + k) * limbs * n + j);
+#pragma unroll
+        for (int k = 0; k < 2; k++)
+            if (poly + k < polys)
+                st2(out + bi * o_bs + (u64)(poly + k) * limbs * n + j,
+                    u64x2{mulmod_barrett(x[k].x, w.x, pc.q, pc.r1, pc.r0), mulmod_barrett(x[k].y, w.y, pc.q, pc.r1, pc.r0)});
     }
 }
 
