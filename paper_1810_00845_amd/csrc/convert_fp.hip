@@ -1397,8 +1397,8 @@ static hipError_t launch_one(dim3 grid, unsigned threads, size_t lds, const Conv
 static u64 wide_inner_tasks(int n_digits) { return n_digits > WIDE_DIGITS ? 0 : n_digits <= 2 ? 512 : 256; }
 template <int K3, int MODE>
 static hipError_t launch_wide_k3(const ConvertArgs& a, const InnerArgs& g, u64 tasks, hipStream_t st) {
-    static char name[40] = "";      // the stage's, as for rows by one wave; rocprofv3 prints ntt_fp_wide_kernel<K3, MODE>
-    if (!name[0]) snprintf(name, sizeof name, "ntt_fp_kernel<%d, %d, false>", K3, MODE);
+    static char name[40] = "";
+    if (!name[0]) snprintf(name, sizeof name, "ntt_fp_wide_kernel<%d, %d>", K3, MODE);
     const unsigned rows = !fp_inner(MODE) ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
     ProfScope prof__(name, st);
     hipLaunchKernelGGL((ntt_fp_wide_kernel<K3, MODE>), dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st, a, g,
@@ -1571,9 +1571,10 @@ static hipError_t launch_split(int log_n, FpArgs a, const FpTask& tk, bool colum
     a.n_tasks = (int)(columns ? polys * tiles : polys << (log_n - 10));
     const bool wide = !columns && a.n_tasks <= WIDE_ROWS;
     const dim3 grid((unsigned)((((u64)a.n_tasks + (wide ? 0 : 3)) / (wide ? 1 : 4) + 7) / 8 * 8));
-    static char names[4][2][40];    // the stage's, whether a row goes by one wave or by four
-    char* name = names[log_n - 12][columns];
-    if (!name[0]) snprintf(name, 40, "ntt_fp_split_kernel<%d, %d, %s>", log_n - 10, MODE, columns ? "true" : "false");
+    static char names[4][3][40];
+    char* name = names[log_n - 12][wide ? 2 : columns];
+    if (!name[0] && wide) snprintf(name, 40, "ntt_fp_split_wide_kernel<%d, %d>", log_n - 10, MODE);
+    else if (!name[0]) snprintf(name, 40, "ntt_fp_split_kernel<%d, %d, %s>", log_n - 10, MODE, columns ? "true" : "false");
     ProfScope prof__(name, st);
 #define SPLIT_CASE(K3)                                                                                             \
     case 10 + K3:                                                                                                  \
@@ -1616,7 +1617,7 @@ static hipError_t launch_encrypt_k3(const EncryptArgs& a, hipStream_t st) {
         if (e != hipSuccess) return e;
     }
     if (rows <= WIDE_ROWS / 2) {
-        ProfScope prof__("encrypt_rows_kernel", st);
+        ProfScope prof__("encrypt_rows_wide_kernel", st);
         hipLaunchKernelGGL(encrypt_rows_wide_kernel<K3>, dim3((unsigned)((rows + 7) / 8 * 8)), dim3(2 * WIDE_NT), 0, st, a);
         return hipGetLastError();
     }

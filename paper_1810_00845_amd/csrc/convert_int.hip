@@ -947,8 +947,8 @@ __global__ __launch_bounds__(MODE == INT_INNER ? INNER_CHUNK * WIDE_NT : WIDE_NT
 }
 template <int K3, int MODE>
 static hipError_t launch_wide_k3(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
-    static char name[40] = "";      // the stage's, as for rows by one wave; rocprofv3 prints ntt_int_wide_kernel<K3, MODE>
-    if (!name[0]) snprintf(name, sizeof name, "ntt_int_kernel<%d, %d, false>", K3, MODE);
+    static char name[40] = "";
+    if (!name[0]) snprintf(name, sizeof name, "ntt_int_wide_kernel<%d, %d>", K3, MODE);
     const unsigned rows = MODE != INT_INNER ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
     ProfScope prof__(name, st);
     for (u64 first = 0; first < tasks; first += 1 << 22) {           // a grid holds fewer than 2^32 threads
