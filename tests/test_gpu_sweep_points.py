@@ -29,11 +29,13 @@ def by_four_waves(launch, g, batch):
     """Whether the rows of a launch over `batch` ciphertexts at the top level go by four waves each: up to 2048 rows, or as
     many inner products as are resident at once (512 of one or two digits, 256 of three or four)."""
     mode, columns = launch
+    if columns:
+        return False
     rows, l, K, digits = g.N // 1024, g.L, g.K, -(-g.L // g.alpha)
     stored = batch * (l + K) * rows < 1024
     inner = 512 if digits <= 2 else 256 if digits <= 4 else 0
     limbs = {2: l, 5: l + K if stored else K, 6: l, 7: 2 * l}[mode]
-    return not columns and batch * limbs * rows <= (inner if mode in (5, 6) else 2048)
+    return batch * limbs * rows <= (inner if mode in (5, 6) else 2048)
 
 
 def launches(g, batch, call):
