@@ -428,8 +428,12 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_steps_fp_kernel(const Fp
 // Against sums in one chain a thread, a reduction a product, and c0 and addend in two launches of their own (us, all sums of a network):
 // LeNet-small 203 -> 105, LeNet-medium 1095 -> 678, SqueezeNet-style 2087 -> 1758 (there the keys, 640 MB a launch of one output, bound
 // it).  In one wave or over four, by workgroups of whole chains: 288 of them 40 -> 32 us a launch, 1792 50 -> 41, 2560 and more even.
+// DIGITS: up to three are known to the compiler and a rotation's loads are one wait; more go one after the other.  (All of four
+// to eight at once took 160 registers: 64 outputs of nine rotations at N = 2^13, 8 limbs, us: four digits 1618 against 1358, eight
+// 2638 against 2292, with a reduction a product 1461 and 2392; one output at N = 2^15, 12 limbs, four digits 289, 215, 225.)
 // Ranges: all factors within p / 2; the sums are reduced before they hold more terms than their plan allows.  At most eight rotations
-// a wave add canonical c0 values when GROUPS = 4, and those are normalised every eighth rotation otherwise.
+// a wave add canonical c0 values when GROUPS = 4; otherwise those are normalised every sixth rotation, on top of a normalised
+// value: 6.5 p < 2^53.
 #define IPS_BCH 4
 #define IPS_FEW 2048    // workgroups of whole chains
 template <int GROUPS, int DIGITS>
@@ -439,7 +443,7 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(const FpPr
                                                                       u64* acc, u64 acc_bs, u64 n_batch, int shared_input,
                                                                       const u64* c0_src, const u64* plain, u64 plain_bs, const u64* pmod,
                                                                       int log_n) {
-    constexpr int COEFFS = IPF_NT / GROUPS, MAXD = DIGITS ? DIGITS : IPF_MAXD;
+    constexpr int COEFFS = IPF_NT / GROUPS, AT_ONCE = DIGITS ? DIGITS : 1;
     const u64 n = (u64)1 << log_n;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
     const uint32_t j = blockIdx.x * COEFFS + (GROUPS == 1 ? threadIdx.x : lane);
@@ -462,47 +466,48 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(const FpPr
         const double* key = (const double*)steps.key[s] + (u64)prime * n + j;
         const uint32_t jsrc = galois_src_fp(j, steps.galois[s], log_n);
         const u64 entry0 = (shared_input ? 0 : (u64)s * n_batch) + b0;
-        // a rotation's loads all together: with the digits known to the compiler they are one wait
-        double kb[MAXD], ka[MAXD], e[MAXD][IPS_BCH], c0[IPS_BCH];
+        // a rotation's loads all together where the digits are known to the compiler: one wait
+#pragma unroll 1
+        for (int d0 = 0; d0 < (DIGITS ? DIGITS : digits); d0 += AT_ONCE) {
+            double kb[AT_ONCE], ka[AT_ONCE], e[AT_ONCE][IPS_BCH], c0[IPS_BCH];
+            const bool with_c0 = d0 == 0 && x < l;
 #pragma unroll
-        for (int d = 0; d < MAXD; d++) {
-            if (DIGITS || d < digits) {
-                kb[d] = key[(u64)(d * 2) * total * n];
-                ka[d] = key[(u64)(d * 2 + 1) * total * n];
+            for (int i = 0; i < AT_ONCE; i++) {
+                const int d = d0 + i;
+                kb[i] = key[(u64)(d * 2) * total * n];
+                ka[i] = key[(u64)(d * 2 + 1) * total * n];
                 const bool own = d == own_digit;
                 const double* src = own ? (const double*)own_src + entry0 * own_bs + (u64)x * n + jsrc
                                         : ext + entry0 * ext_bs + ((u64)d * ext_limbs + x) * n + jsrc;
                 const u64 bs = own ? own_bs : ext_bs;
 #pragma unroll
                 for (int u = 0; u < IPS_BCH; u++)
-                    if (u < live) e[d][u] = src[u * bs];
+                    if (u < live) e[i][u] = src[u * bs];
             }
-        }
-        if (x < l) {
+            if (with_c0) {
 #pragma unroll
-            for (int u = 0; u < IPS_BCH; u++)
-                if (u < live) c0[u] = ((const double*)c0_src)[(entry0 + u) * own_bs + (u64)x * n + jsrc];
-        }
+                for (int u = 0; u < IPS_BCH; u++)
+                    if (u < live) c0[u] = ((const double*)c0_src)[(entry0 + u) * own_bs + (u64)x * n + jsrc];
+            }
 #pragma unroll
-        for (int d = 0; d < MAXD; d++) {
-            if (DIGITS || d < digits) {
+            for (int i = 0; i < AT_ONCE; i++) {
 #pragma unroll
                 for (int u = 0; u < IPS_BCH; u++) {
                     if (u >= live) break;
-                    if (d == own_digit) e[d][u] = fp_norm(fp_from_u64((u64)__double_as_longlong(e[d][u])), p, pinv);
-                    fp_sum_add(sb[u], e[d][u], kb[d]);
-                    fp_sum_add(sa[u], e[d][u], ka[d]);
+                    if (d0 + i == own_digit) e[i][u] = fp_norm(fp_from_u64((u64)__double_as_longlong(e[i][u])), p, pinv);
+                    fp_sum_add(sb[u], e[i][u], kb[i]);
+                    fp_sum_add(sa[u], e[i][u], ka[i]);
                 }
             }
-        }
-        if (x < l) {
+            if (with_c0) {
 #pragma unroll
-            for (int u = 0; u < IPS_BCH; u++)
-                if (u < live) tc[u] += fp_from_u64((u64)__double_as_longlong(c0[u]));
-            if (GROUPS == 1 && ++c0_pending == 6) {              // six and a normalised value
-                c0_pending = 0;
+                for (int u = 0; u < IPS_BCH; u++)
+                    if (u < live) tc[u] += fp_from_u64((u64)__double_as_longlong(c0[u]));
+                if (GROUPS == 1 && ++c0_pending == 6) {              // six and a normalised value
+                    c0_pending = 0;
 #pragma unroll
-                for (int u = 0; u < IPS_BCH; u++) tc[u] = fp_norm(tc[u], p, pinv);
+                    for (int u = 0; u < IPS_BCH; u++) tc[u] = fp_norm(tc[u], p, pinv);
+                }
             }
         }
         if (++pending == fold_every) {

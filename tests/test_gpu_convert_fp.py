@@ -91,6 +91,8 @@ SUMS = [
     (14, [50] * 6, 2, 17, 14),
     (14, [50, 40, 40, 49, 49, 48], 3, 18, 13),
     (14, [50, 40, 40, 49], 4, 33, 5),
+    (12, [50, 46, 45, 44, 43], 5, 3, 9),            # five digits over four waves
+    (13, [50] * 8, 8, 30, 3),                       # eight in one
 ]
 
 
