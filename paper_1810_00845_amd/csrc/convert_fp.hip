@@ -380,7 +380,10 @@ __device__ __forceinline__ void rows_inverse(const ConvertArgs& a, int n_tasks, 
 // Bound by fp64 issue beside memory: 64 rotations at N = 2^15, 16 limbs, with the products and levels left out the launch over
 // the digits takes 207 us (its bytes), with the stores left out 240 us, whole 265 us.  Its conversion sums are FpSums: products
 // reduced one by one made it 305 us, those of the division by P 208 us against 183 now.  The sums are not held over the sources'
-// levels, so that 80 registers do and three workgroups share a compute unit (277 us with two).
+// levels, so that 80 registers do and three workgroups share a compute unit (277 us with two; without the limit the compiler takes
+// 81, so seven sources and more, whose LDS admits two workgroups, lose nothing by it).  Only digits of more sources than the LDS holds
+// keep them, in 92 registers (HELD below): 64 rotations at N = 2^15, 21 limbs, one digit, 2228 us against 2342 with the sums in memory
+// between chunks, 16 at N = 2^14, 24 limbs, 318 against 348.
 template <int RB>
 struct Col {
     static constexpr int NR = RB == 5 ? 16 : (1 << RB);      // coefficients per lane
@@ -444,8 +447,9 @@ __device__ __forceinline__ void fwd_columns(double (&v)[Col<RB>::NR], const doub
 }
 #define COLUMNS_BOUND 4.85f   // of the stored values: five levels from normalised sums
 
-// ylds: [source of the chunk][NR][64 lanes]
-template <int RB>
+// ylds: [source of the chunk][NR][64 lanes].  HELD: the sources come in several chunks, and a target's sums stay in registers from one
+// to the next; else they are all in LDS.
+template <int RB, bool HELD>
 __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
     constexpr int NR = Col<RB>::NR, WIDTH = Col<RB>::WIDTH, TILES = 1024 / WIDTH;
     const int lane = threadIdx.x & 63, h = lane >> 5;
@@ -463,7 +467,8 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
     const uint32_t in_lane = (uint32_t)((RB == 5 ? 2 * h * 1024 : 0) + col) * 8u;
     const rsrc_t mid = make_rsrc(a.mid + (b * a.n_src + src0) * n, (uint32_t)(n_src * n * 8u));
     const int rounds = (t_end - t_first + waves - 1) / waves;
-    const bool resident = n_src <= a.chunk;
+    const int chunk = HELD ? a.chunk : n_src;
+    const bool resident = n_src <= chunk;
     for (int round = 0; round < rounds; round++) {
         const int t = t_first + round * waves + wave;
         const bool mine = t < t_end;
@@ -471,8 +476,10 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
         const int prime = mine ? prime_at(e, a.l, a.L) : 0;
         const Modulus q = modulus(a.fprimes, prime);
         const double* head = a.sfwd + (u64)prime * a.table_stride;
-        for (int c0 = 0; c0 < n_src; c0 += a.chunk) {
-            const int c1 = min(c0 + a.chunk, n_src);
+        const rsrc_t dst = make_rsrc((double*)a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n, (uint32_t)n * 8u);
+        double v[NR];
+        for (int c0 = 0; c0 < n_src; c0 += chunk) {
+            const int c1 = min(c0 + chunk, n_src);
             if (!resident || round == 0) {
                 if (c0 || round) __syncthreads();      // every wave is done with the chunk before
                 for (int i = c0 + wave; i < c1; i += waves) {
@@ -501,12 +508,7 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
             if (mine) {
                 const cdouble_ptr hat = as_const(a.dg[digit].hat) + prime;
                 const double* y0 = ylds + lane;
-                const rsrc_t dst = make_rsrc((double*)a.out + b * a.out_bs + (u64)(a.dg[digit].out_pos0 + e) * n, (uint32_t)n * 8u);
-                double v[NR];
-                if (c0) {                              // sums over earlier chunks wait where the result goes
-#pragma unroll
-                    for (int r = 0; r < NR; r++) v[r] = bloadf(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u);
-                } else {
+                if (!HELD || c0 == 0) {
 #pragma unroll
                     for (int r = 0; r < NR; r++) v[r] = 0.0;
                 }
@@ -541,7 +543,7 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
                         for (int r = 0; r < NR; r++) v[r] = fp_norm(fp_sum_value(s[r], FP_SUM_BASE, q.p, q.pinv), q.p, q.pinv);
                     }
                 }
-                if (c1 == n_src) {
+                if (!HELD || c1 == n_src) {
                     double last[8] = {};
                     if (RB == 5) {
                         const rsrc_t hr = make_rsrc(head, HEAD * 8);
@@ -549,10 +551,10 @@ __device__ __forceinline__ void columns(const ConvertArgs& a, double* ylds) {
                         for (int k = 0; k < 4; k++) bload2(hr, (uint32_t)h * 64u, 128u + (uint32_t)k * 16u, last[2 * k], last[2 * k + 1]);
                     }
                     fwd_columns<RB>(v, head, last, q);
-                }
 #pragma unroll
-                for (int r = 0; r < NR; r++)
-                    bstoref(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u, v[r]);
+                    for (int r = 0; r < NR; r++)
+                        bstoref(dst, in_lane, (uint32_t)(RB == 5 ? (r >> 1) * 4 + (r & 1) : r) * 8192u, v[r]);
+                }
             }
         }
     }
@@ -1325,13 +1327,20 @@ template <int K3, int MODE, bool COLUMNS>
 __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), fp_waves(K3, COLUMNS)) void ntt_fp_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
     if constexpr (COLUMNS) {
         extern __shared__ double ylds[];
-        columns<K3>(a, ylds);
+        columns<K3, false>(a, ylds);
     } else {
         __shared__ double lds[fp_threads(MODE, false) / 64 * ROW_LDS];
         if constexpr (MODE == FP_INV_TO_Y) rows_inverse<K3>(a, n_tasks, lds);
         else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE>(a, g, OneStep{}, n_tasks, lds);
         else rows_forward<K3, MODE>(a, n_tasks, lds);
     }
+}
+
+// columns of digits with more sources than the LDS holds
+template <int K3, int MODE>
+__global__ __launch_bounds__(1024, 4) void ntt_fp_chunks_kernel(ConvertArgs a) {
+    extern __shared__ double ylds[];
+    columns<K3, true>(a, ylds);
 }
 
 constexpr bool fp_inner(int mode) { return mode == FP_INV_D_TO_Y || mode == FP_FWD_CONV_SUB; }
@@ -1452,6 +1461,7 @@ static hipError_t launch_columns_k3(const ConvertArgs& a_in, hipStream_t st) {
     ConvertArgs a = a_in;
     constexpr int NR = Col<K3>::NR, TILES = 1024 / Col<K3>::WIDTH;
     constexpr int PER_SRC = NR * 64 * 8, MAX_CHUNK = 20 * 8192 / PER_SRC;
+    constexpr int MOST_SOURCES = HISA_MAX_PRIMES / 2 + 1;        // as many special primes as primes, and the last prime
     int most = 1;
     for (int d = 0; d < a.n_digits; d++) most = a.dg[d].a > most ? a.dg[d].a : most;
     a.chunk = most < MAX_CHUNK ? most : MAX_CHUNK;
@@ -1460,6 +1470,9 @@ static hipError_t launch_columns_k3(const ConvertArgs& a_in, hipStream_t st) {
     if (!attr_set) {
         hipError_t e = hipFuncSetAttribute((const void*)ntt_fp_kernel<K3, MODE, true>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                            MAX_CHUNK * PER_SRC);
+        if constexpr (MAX_CHUNK < MOST_SOURCES)
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void*)ntt_fp_chunks_kernel<K3, MODE>, hipFuncAttributeMaxDynamicSharedMemorySize, MAX_CHUNK * PER_SRC);
         if (e != hipSuccess) return e;
         attr_set = true;
     }
@@ -1484,8 +1497,17 @@ static hipError_t launch_columns_k3(const ConvertArgs& a_in, hipStream_t st) {
         a.n_entries = a_in.n_entries - e0 < 65535 ? a_in.n_entries - e0 : 65535;
         a.mid = a_in.mid + (u64)e0 * a.n_src * ((u64)1 << a.log_n);
         a.out = a_in.out + (u64)e0 * a.out_bs;
-        hipError_t e = launch_one<K3, MODE, true>(dim3((unsigned)(TILES * a.n_digits * a.n_splits), a.n_entries), threads, lds, a,
-                                                  InnerArgs{}, 0, st);
+        const dim3 grid((unsigned)(TILES * a.n_digits * a.n_splits), a.n_entries);
+        hipError_t e = hipErrorInvalidValue;
+        if (most <= MAX_CHUNK) {
+            e = launch_one<K3, MODE, true>(grid, threads, lds, a, InnerArgs{}, 0, st);
+        } else if constexpr (MAX_CHUNK < MOST_SOURCES) {
+            static char name[40] = "";
+            if (!name[0]) snprintf(name, sizeof name, "ntt_fp_chunks_kernel<%d, %d>", K3, MODE);
+            ProfScope prof__(name, st);
+            hipLaunchKernelGGL((ntt_fp_chunks_kernel<K3, MODE>), grid, dim3(threads), lds, st, a);
+            e = hipGetLastError();
+        }
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

@@ -59,6 +59,27 @@ def test_key_switch_and_rescale(log_n, q_bits, dnum, special, l, batch):
     g.close()
 
 
+@pytest.mark.parametrize("log_n,sources,chunks", [(13, 21, False), (14, 20, False), (14, 21, True), (15, 20, False), (15, 21, True)])
+def test_columns_of_more_sources_than_the_lds_holds(log_n, sources, chunks):
+    """20 sources at N = 2^14 and 2^15 (40 at 2^13) are in LDS together; more come in chunks, in a kernel of their own."""
+    from oracle import Oracle
+    from paper_1810_00845_amd import hisa, synth
+    print("[case]", log_n, sources, flush=True)
+    g, o = hisa.Context(log_n, [50] * sources, 1, 50, 5), Oracle(log_n, [50] * sources, 1, 50, 5)
+    g.gen_rot_keys([3]); o.gen_rot_keys([3])
+    coeff = synth.uniform_residues(log_n + sources, (1, 2, sources, g.N), g.primes[:sources])
+    ct = g.ct_import(coeff[0], 2.0 ** 50)
+    g.profile_enable(True)
+    out = g.rot_left(ct, 3)
+    names = set(g.profile_read())
+    g.profile_enable(False)
+    form = "ntt_fp_chunks_kernel<%d, %%d>" if chunks else "ntt_fp_kernel<%d, %%d, true>"
+    columns = {n for n in names if n.endswith("true>") or "chunks" in n}
+    assert columns == {form % (log_n - 10) % mode for mode in (3, 6)}, names
+    assert np.array_equal(g.ct_export(out), o.export(o.rot_left(o.import_ct(coeff[0], 2.0 ** 50), 3)))
+    g.close()
+
+
 def test_more_entries_than_a_grid_has_rows():
     """The ModDown's columns of 32769 ciphertexts are 65538 entries, three more than one launch takes: the first ciphertexts, those
     on both sides of the line and the last equal single calls."""
