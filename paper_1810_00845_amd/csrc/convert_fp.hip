@@ -1233,6 +1233,9 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_columns_kernel(EncryptArgs
     for (int r = 0; r < NR; r++) bstoref(dst, other, column_row<K3, false>(r), v[r]);
 }
 
+// Two transforms of a row and its products, bound by memory in large batches.  Twiddles fetched per transform, those of c behind the
+// levels on b: without spills, us a batch, 8 registers spilled -> none: 64 vectors at N = 2^14, 12 limbs 158.3 -> 156, at N = 2^15, 16
+// limbs 467 -> 458; 20 at N = 2^14 68.5 -> 67.2.
 template <int K3>
 __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a) {
     __shared__ double lds_all[4 * ROW_LDS];
@@ -1251,15 +1254,19 @@ __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_rows_kernel(EncryptArgs a)
     double e[16], v[16], s[16];
     float m[16];
     RowTwiddles w;
-    load_row_twiddles(w, a.sfwd, a.table_stride, limb, (uint32_t)row, lane);
+    row_tables(w, a.sfwd, a.table_stride, limb, (uint32_t)row);
+    load_twiddles_b(w, lane);
     load_row(e, r0, lane);
 #pragma unroll
     for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
-    row_forward(e, m, w, lds, lane, q, 3.0f);       // 3 + 1 (message) + 2.5 (a s, below) stays within 8 p
+    row_forward<true>(e, m, w, lds, lane, q, 3.0f);       // 3 + 1 (message) + 2.5 (a s, below) stays within 8 p
     load_row(v, r1, lane);
 #pragma unroll
     for (int r = 0; r < 16; r++) m[r] = COLUMNS_BOUND;
-    row_forward(v, m, w, lds, lane, q, 5.2f);
+    int tl = lane;
+    asm volatile("" : "+v"(tl));           // the twiddles are fetched again: kept beside two rows they spilled
+    load_twiddles_b(w, tl);
+    row_forward<true>(v, m, w, lds, tl, q, 5.2f);
     load_row(s, sk, lane);
     from_residues(s);
 #pragma unroll
