@@ -251,6 +251,14 @@ __device__ __forceinline__ void row_inverse_lds(u64 (&v)[16], int (&m)[16], cons
     inv_level<3>(v, m, t3, q); inv_level<2>(v, m, t2, q); inv_level<1>(v, m, t1, q); inv_level<0>(v, m, t0, q);
     cap_bounds(v, m, 8, q);
 }
+template <int K3>
+__device__ __forceinline__ void row_inverse(u64 (&v)[16], int (&m)[16], const RowTables<K3>& w, u64* lds, int lane, u64 q) {
+    xchg_sync<true>();
+#pragma unroll
+    for (int r = 0; r < 16; r++) lds[66 * r + lane + (lane >> 5)] = v[r];
+    xchg_sync<true>();
+    row_inverse_lds(v, m, w, lds, lane, q);
+}
 
 // the row's 1024 words of a limb, read through sigma_g when galois != 0
 template <int K3>
@@ -298,6 +306,32 @@ __device__ __forceinline__ Tw table_tw(const u64* t, u64 i) { return Tw{as_const
 // ---------------------------------------------------------------------------
 // rows
 // ---------------------------------------------------------------------------
+template <int K3>
+__device__ __forceinline__ void rows_inverse(const IntArgs& a, const IntTasks& tk, int n_tasks, u64* lds_all) {
+    const int task = row_task(n_tasks);
+    if (task < 0) return;
+    const int lane = threadIdx.x & 63;
+    const uint32_t unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1), e = unit >> K3;
+    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const int prime = uniform(tk.prime[e]), pos = uniform(tk.pos[e]);
+    const ModI q = mod_int(a.primes, prime);
+    constexpr u64 n = (u64)1 << (10 + K3);
+    u64 v[16];
+    int m[16];
+    load_row<K3>(v, a.in + b * a.in_bs + (u64)(pos + a.in_pos_shift) * n, a.galois, row, lane);
+#pragma unroll
+    for (int r = 0; r < 16; r++) m[r] = 1;
+    row_inverse<K3>(v, m, RowTables<K3>(a.itw, a.itw_sh, prime, row, lane), lds_all + (threadIdx.x >> 6) * ROW_LDS, lane, q.q);
+    const rsrc_t dst = make_rsrc(a.out + b * a.out_bs + (u64)pos * n + (uint32_t)uniform(row) * 1024u, 8192u);
+    if (K3 == 0 && a.whole) {            // no columns behind
+        const Tw f = table_tw(a.consts, (u64)prime * CONST_WORDS);
+#pragma unroll
+        for (int r = 0; r < 16; r++) v[r] = canonical(mul4(v[r], f, q.q), 4, q.q);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; r++) bstore(dst, (uint32_t)lane * 8u, (uint32_t)r * 512u, v[r]);
+}
+
 template <int K3>
 __device__ __forceinline__ void rows_forward(const IntArgs& a, const IntTasks& tk, int n_tasks, u64* lds_all) {
     const int task = row_task(n_tasks);
@@ -930,17 +964,18 @@ void ntt_int_kernel(IntArgs a, IntTasks tk, int n_tasks) {
         if constexpr (MODE == INT_CONVERT) convert_columns<K3>(a, lds);
         else plain_columns<K3, MODE == INT_INVERSE>(a, tk, n_tasks);
     } else {
-        if constexpr (MODE == INT_FORWARD) rows_forward<K3>(a, tk, n_tasks, lds);
+        if constexpr (MODE == INT_INVERSE) rows_inverse<K3>(a, tk, n_tasks, lds);
+        else if constexpr (MODE == INT_FORWARD) rows_forward<K3>(a, tk, n_tasks, lds);
         else if constexpr (MODE == INT_INNER) rows_inner<K3>(a, lds);
         else rows_divide<K3>(a, n_tasks, lds);
     }
 }
 
 template <int K3, int MODE>
-__global__ __launch_bounds__(MODE == INT_INNER ? INNER_CHUNK * WIDE_NT : WIDE_NT, 4) void ntt_int_wide_kernel(IntArgs a, IntTasks tk, int first, int n_tasks) {
+__global__ __launch_bounds__(MODE == INT_INNER ? INNER_CHUNK * WIDE_NT : WIDE_NT, 4) void ntt_int_wide_kernel(IntArgs a, IntTasks tk, int n_tasks) {
     extern __shared__ u64 lds[];
-    const int per = (n_tasks + 7) >> 3, mine = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3), task = first + mine;
-    if ((int)(blockIdx.x >> 3) >= per || mine >= n_tasks) return;
+    const int per = (n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
     if constexpr (MODE == INT_INVERSE) wide_rows_inverse<K3>(a, tk, task, lds);
     else if constexpr (MODE == INT_INNER) wide_rows_inner<K3>(a, task, lds);
     else wide_rows_divide<K3>(a, task, lds);
@@ -951,14 +986,9 @@ static hipError_t launch_wide_k3(const IntArgs& a, const IntTasks& tk, u64 tasks
     if (!name[0]) snprintf(name, sizeof name, "ntt_int_wide_kernel<%d, %d>", K3, MODE);
     const unsigned rows = MODE != INT_INNER ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
     ProfScope prof__(name, st);
-    for (u64 first = 0; first < tasks; first += 1 << 22) {           // a grid holds fewer than 2^32 threads
-        const u64 count = tasks - first < (1 << 22) ? tasks - first : 1 << 22;
-        hipLaunchKernelGGL((ntt_int_wide_kernel<K3, MODE>), dim3((unsigned)((count + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st,
-                           a, tk, (int)first, (int)count);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    hipLaunchKernelGGL((ntt_int_wide_kernel<K3, MODE>), dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st,
+                       a, tk, (int)tasks);
+    return hipGetLastError();
 }
 template <int MODE>
 static hipError_t launch_wide(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
@@ -1001,24 +1031,24 @@ static hipError_t launch_any(int log_n, dim3 grid, unsigned threads, size_t lds,
         default: return hipErrorInvalidValue;
     }
 }
-// Rows by four waves or by one.  Inverse rows: always four (8 rows 8.5 -> 4.7 us, 512 rows 10 -> 6.3, 4096 rows 29 -> 25, 16384
-// rows 89 -> 90).  Rows of a division: 24 rows 10.3 -> 5.2 us, 1024 rows 15 -> 9.7, 8192 rows 63 -> 62, but 32768 rows 223 -> 247:
+// Rows by four waves or by one.  Inverse rows: 8 rows 8.5 -> 4.7 us, 512 rows 10 -> 6.3, 4096 rows 29 -> 25; with the columns behind
+// them 32768 rows 228 -> 226 us at N = 2^15, but 49152 rows there 386 -> 392 and 65536 rows 516 -> 520, 131072 rows at 2^12 988 -> 1010
+// (at 2^10, where the rows are all there is, either within 2 % from 16384 rows on).  Rows of a division: 24 rows 10.3 -> 5.2 us, 1024 rows 15 -> 9.7, 8192 rows 63 -> 62, but 32768 rows 223 -> 247:
 // the wave of its own waits for fewer exchanges.  Inner products: while all workgroups are resident at once, 512 of eight
 // waves (up to two digits) or 256 of twelve or sixteen: one wave a digit -> four, 16 tasks of three digits 17.6 -> 12.8 us, 256 of
 // them 18.5 -> 14.4, 352 23 -> 26; of two digits 512 tasks 22 -> 17.6, 768 24.7 -> 24.3, 1024 29 -> 30.
+#define WIDE_INVERSE_ROWS 32768
 #define WIDE_DIVIDE_ROWS 8192
 static u64 wide_inner_tasks(int n_digits) { return n_digits > INNER_CHUNK ? 0 : n_digits <= 2 ? 512 : 256; }
 
 template <int MODE, bool COLUMNS>
 static hipError_t launch_waves(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
     if (tasks > 0x7fffff00u) return hipErrorInvalidValue;
-    if constexpr (MODE == INT_INVERSE && !COLUMNS) {
-        return launch_wide<MODE>(a, tk, tasks, st);
-    } else {
-        const u64 blocks = ((tasks + ROWS_NT / 64 - 1) / (ROWS_NT / 64) + 7) / 8 * 8;
-        const size_t lds = COLUMNS ? 0 : (size_t)(ROWS_NT / 64) * ROW_LDS * 8;
-        return launch_any<MODE, COLUMNS>(a.log_n, dim3((unsigned)blocks), ROWS_NT, lds, a, tk, tasks, st);
-    }
+    if constexpr (MODE == INT_INVERSE && !COLUMNS)
+        if (tasks <= WIDE_INVERSE_ROWS) return launch_wide<MODE>(a, tk, tasks, st);
+    const u64 blocks = ((tasks + ROWS_NT / 64 - 1) / (ROWS_NT / 64) + 7) / 8 * 8;
+    const size_t lds = COLUMNS ? 0 : (size_t)(ROWS_NT / 64) * ROW_LDS * 8;
+    return launch_any<MODE, COLUMNS>(a.log_n, dim3((unsigned)blocks), ROWS_NT, lds, a, tk, tasks, st);
 }
 static hipError_t launch_inner(const IntArgs& a, hipStream_t st) {
     const u64 tasks = ((u64)a.ext_limbs * a.n_entries) << (a.log_n - 10);

@@ -79,6 +79,33 @@ def test_tables_of_every_level_made_once_and_found_again():
     g.close()
 
 
+@pytest.mark.parametrize("log_n", [10, 11, 13, 15, 16])
+def test_inverse_rows_by_four_waves_and_by_one(log_n):
+    """32768 rows go by four waves each, one polynomial more by one wave a row: the same values, and back to what they were."""
+    import torch
+    from oracle import Oracle
+    from paper_1810_00845_amd import hisa
+    print("[case] inverse rows, N = 2^%d" % log_n, flush=True)
+    g, o = hisa.Context(log_n, [60], 1, 60, 5), Oracle(log_n, [60], 1, 60, 5)
+    few = 1 << (25 - log_n)
+    torch.manual_seed(log_n)
+    a = torch.randint(0, g.primes[0], (few + 1, g.N), dtype=torch.int64, device="cuda")
+    a[0, :3], a[few, -3:] = 0, g.primes[0] - 1
+    many = a.clone()
+    g.ntt_raw(many, 0)
+    for r in (0, few):
+        assert np.array_equal(many[r].cpu().numpy().view(np.uint64), o.ntt(a[r].cpu().numpy().view(np.uint64), 0))
+    some = many[:few].clone()
+    for t, rows in ((some, "ntt_int_wide_kernel<%d, 0>"), (many, "ntt_int_kernel<%d, 0, false>")):
+        g.profile_enable(True)
+        g.ntt_raw(t, 0, inverse=True)
+        names = set(g.profile_read())
+        g.profile_enable(False)
+        assert {n for n in names if not n.endswith("true>")} == {rows % (log_n - 10)}, names
+    assert torch.equal(some, a[:few]) and torch.equal(many, a)
+    g.close()
+
+
 def test_more_ciphertexts_than_one_set_of_launches_takes():
     """Key switches of 32769 ciphertexts and a rescale of their 65538 polynomials are two sets of launches each (32767
     ciphertexts, 65535 polynomials): the first ciphertexts, those on both sides of the lines and the last equal single calls."""
