@@ -1488,9 +1488,8 @@ int moddown_add_fp(hisa_ctx* ctx, const u64* acc, size_t B, int l, const u64* ad
     return divide_fp(ctx, c);
 }
 
-// Tables of the combined division at level l: sources q_{l-1}, p_0 .. p_{K-1} (conversion table; (D/s_m)^-1 as centred
-// doubles, D = q_{l-1} P) and D^-1 mod q_i as centred doubles indexed by prime
-static int moddown_rescale_tables(hisa_ctx* ctx, int l, ConvTable** tab, double** post, double** dinv) {
+// The combined division at level l, by D = q_{l-1} P: conversion table of its sources q_{l-1}, p_0 .. p_{K-1}
+static int moddown_rescale_sources(hisa_ctx* ctx, int l, ConvTable** tab) {
     const auto key = std::make_pair(-l, (int)ctx->K + 1);
     auto it = ctx->modup_tabs.find(key);
     if (it == ctx->modup_tabs.end()) {
@@ -1501,24 +1500,31 @@ static int moddown_rescale_tables(hisa_ctx* ctx, int l, ConvTable** tab, double*
         it = ctx->modup_tabs.emplace(key, t).first;
     }
     *tab = &it->second;
+    return HISA_OK;
+}
+// D^-1 mod q_i
+static u64 inverse_divisor(const hisa_ctx* ctx, const ConvTable& t, int i) {
+    const u64 q = ctx->mod[i];
+    u64 d = 1 % q;
+    for (int m = 0; m < t.a; m++) d = hm::mul(d, ctx->mod[t.src[m]] % q, q);
+    return hm::inv(d, q);
+}
+// its constants for accumulators in memory: (D/s_m)^-1 and D^-1 mod q_i as centred doubles, indexed by source and by prime
+static int moddown_rescale_tables(hisa_ctx* ctx, int l, ConvTable** tab, double** post, double** dinv) {
+    TRY(moddown_rescale_sources(ctx, l, tab));
     const u64 KEY = 12288 + (u64)l;     // (8192 + l: the constants of the plain rescale)
-    auto ia = ctx->aux.find(KEY);
-    if (ia == ctx->aux.end()) {
-        const ConvTable& t = it->second;
+    auto it = ctx->aux.find(KEY);
+    if (it == ctx->aux.end()) {
+        const ConvTable& t = **tab;
         std::vector<double> v((size_t)t.a + ctx->total, 0.0);
         for (int m = 0; m < t.a; m++) v[m] = centred_double(t.inv_hat[m], ctx->mod[t.src[m]]);
-        for (int i = 0; i < l - 1; i++) {
-            const u64 q = ctx->mod[i];
-            u64 d = 1 % q;
-            for (int m = 0; m < t.a; m++) d = hm::mul(d, ctx->mod[t.src[m]] % q, q);
-            v[(size_t)t.a + i] = centred_double(hm::inv(d, q), q);
-        }
+        for (int i = 0; i < l - 1; i++) v[(size_t)t.a + i] = centred_double(inverse_divisor(ctx, t, i), ctx->mod[i]);
         double* dev = nullptr;
         HIP_TRY(ctx, upload(&dev, v));
-        ia = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{dev, v.size() * sizeof(double), 1}, (u64*)dev}).first;
+        it = ctx->aux.emplace(KEY, SwitchKey{new DevBlock{dev, v.size() * sizeof(double), 1}, (u64*)dev}).first;
     }
-    *post = (double*)ia->second.data;
-    *dinv = (double*)ia->second.data + it->second.a;
+    *post = (double*)it->second.data;
+    *dinv = (double*)it->second.data + (*tab)->a;
     return HISA_OK;
 }
 
@@ -1539,15 +1545,11 @@ static int division_by_p_and_last(hisa_ctx* ctx, int l, Division* d) {
     auto it = ctx->aux.find(KEY);
     if (it == ctx->aux.end()) {
         ConvTable* tab;
-        double *post, *dinv;
-        TRY(moddown_rescale_tables(ctx, l, &tab, &post, &dinv));
+        TRY(moddown_rescale_sources(ctx, l, &tab));
         std::vector<double> t(ext + l + (size_t)tab->a * ctx->total, 0.0);
         const u64 last = ctx->mod[l - 1];
         for (int i = 0; i < l - 1; i++) {
-            const u64 q = ctx->mod[i];
-            u64 div = 1 % q;
-            for (int m = 0; m < tab->a; m++) div = hm::mul(div, ctx->mod[tab->src[m]] % q, q);
-            const u64 div_inv = hm::inv(div, q);
+            const u64 q = ctx->mod[i], div_inv = inverse_divisor(ctx, *tab, i);
             t[i] = centred_double(div_inv, q);
             t[ext + i] = centred_double(hm::inv(last % q, q), q);
             for (int m = 0; m < tab->a; m++)
