@@ -663,6 +663,57 @@ def test_activation_with_fused_rescale_bit_exact():
     g.close()
 
 
+# (log_n, q_bits, dnum, ciphertexts, accumulators in memory, rows by four waves in the inner products of the special limbs and
+# of the others): one set of launches for each form of the key switch, on both sides of the lines between them
+COMBINED = [
+    (12, [50, 45, 44, 50, 40, 49], 3, 8, True, True, True),
+    (12, [50, 45, 44, 50, 40, 49], 3, 9, True, False, False),
+    (12, [50, 45, 44, 50, 40, 49], 3, 31, True, False, False),
+    (12, [50, 45, 44, 50, 40, 49], 3, 32, False, False, False),
+    (12, [50, 45, 44, 50, 40, 49], 2, 29, False, True, False),
+    (12, [50, 45], 1, 64, False, False, True),
+    (13, [50] * 8, 3, 20, False, False, False),
+    (13, [50, 46, 45, 44, 43], 5, 26, False, False, False),
+    (14, [50] * 20, 1, 1, True, False, False),        # 21 sources, one more than the LDS holds
+    (14, [50] * 20, 1, 2, False, False, False),
+]
+
+
+@pytest.mark.parametrize("log_n,q_bits,dnum,n,stored,wide_special,wide", COMBINED)
+def test_combined_division_in_every_form(log_n, q_bits, dnum, n, stored, wide_special, wide):
+    """The activation's division by q_last P, with and without a linear term, bit for bit."""
+    import re
+    from oracle import layers
+    from paper_1810_00845_amd import hisa, synth
+    print("[case]", log_n, len(q_bits), dnum, n, flush=True)
+    g, o = make_pair(log_n, q_bits, dnum, 50, 31)
+    g.keygen(); o.keygen()
+    g.set_fused_rescale(True)
+    l = len(q_bits)
+    coeff = synth.uniform_residues(log_n + l + n, (n, 2, l, g.N), g.primes[:l])
+    coeff[0, :, :, :3] = 0
+    for i in range(l):
+        coeff[0, :, i, 3:6] = coeff[n - 1, 0, i, 7:] = g.primes[i] - 1
+    sample = sorted({0, n // 2, n - 1})
+    gt = hisa.CipherTensor(g, g.ct_import_batch(coeff, 2.0 ** 40), 1, n, 4, 4, 4, 1, 0, 1)
+    ot = layers.OTensor([o.import_ct(coeff[i], 2.0 ** 40) for i in sample], 1, len(sample), 4, 4, 4, 1, 0, 1)
+    for a, b in ((0.4, 0.3), (0.5, 0.0)):
+        g.profile_enable(True)
+        got = g.poly2_act(gt, a, b)
+        names = set(g.profile_read())
+        g.profile_enable(False)
+        ran = {re.sub(r"<\d+, ", "<", k) for k in names if k.startswith("ntt_fp")}
+        special = "ntt_fp_wide_kernel<5>" if wide_special else "ntt_fp_kernel<5, false>"
+        assert special in ran and len([k for k in ran if "7" in k]) == (1 if stored else 0), names
+        assert stored or ("ntt_fp_wide_kernel<6>" if wide else "ntt_fp_kernel<6, false>") in ran, names
+        assert (l < 20) != any("chunks" in k for k in ran), names
+        want = layers.poly2_act(o, ot, a, b, fused_rescale=True)
+        for i, w in zip(sample, want.cts):
+            assert np.array_equal(g.ct_export(got.cts[i]), o.export(w))
+            assert abs(got.cts[i].scale - w.scale) <= 1e-12 * w.scale
+    g.close()
+
+
 def test_mask_layer_then_chw_conv_on_a_pooled_tensor():
     """pool (not clean) -> masking multiply -> CHW convolution, every step bit for bit; the convolution refuses the
     unmasked tensor."""
