@@ -220,13 +220,6 @@ __device__ __forceinline__ int mid_c(int lane) {
 }
 #define ROW_REG(r) (132 * ((r) >> 1) + ((r) & 1))
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, double& x, double& y) {
-    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
-    x = mk64(d.x, d.y);
-    y = mk64(d.z, d.w);
-}
-
 // What a wave keeps of the twiddles of its row (layout: split_table_words)
 struct RowTwiddles {
     double last_c[8], last_b[8], base[4];
@@ -311,10 +304,7 @@ __device__ __forceinline__ void load_row(double (&v)[16], rsrc_t row, int lane) 
 }
 __device__ __forceinline__ void store_row(rsrc_t row, int lane, const double (&v)[16]) {
 #pragma unroll
-    for (int k = 0; k < 8; k++) {
-        const u32x4_t d = {lo32(v[2 * k]), hi32(v[2 * k]), lo32(v[2 * k + 1]), hi32(v[2 * k + 1])};
-        __builtin_amdgcn_raw_buffer_store_b128(d, row, (int)((uint32_t)lane * 16u), k * 1024, 0);
-    }
+    for (int k = 0; k < 8; k++) bstore2(row, (uint32_t)lane * 16u, (uint32_t)k * 1024u, v[2 * k], v[2 * k + 1]);
 }
 __device__ __forceinline__ void from_residues(double (&v)[16]) {
 #pragma unroll
@@ -772,19 +762,7 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
 // ---------------------------------------------------------------------------
 // rows by four waves each: calls with few rows
 // ---------------------------------------------------------------------------
-// A wave that keeps a row to itself is a chain of eighty butterflies a lane with its loads, twiddles and products in between, and
-// with fewer rows than the chip has SIMDs nothing runs beside it.  Here a thread holds four coefficients, two levels at a time,
-// and everything it will need is on its way before the first level; only the exchange behind the first two levels crosses waves.
-//   stage s, levels 2 s and 2 s + 1: registers 0 .. 3 of thread t are 2^p apart, p = 8 - 2 s (wide_element)
-#define WIDE_NT 256
-#define WIDE_LDS 1280    // 64-bit words per row: four words of padding per sixteen, so that a thread's four stay together
 #define WIDE_DIGITS 4    // at most, in an inner product: four waves each
-__device__ __forceinline__ uint32_t wide_at(uint32_t i) { return i + ((i >> 4) << 2); }
-template <int S>
-__device__ __forceinline__ uint32_t wide_element(uint32_t t, uint32_t r) {
-    constexpr int p = 8 - 2 * S;
-    return ((t >> p) << (p + 2)) | (r << p) | (t & ((1u << p) - 1));
-}
 struct WideTwiddles { double w[5][3]; };     // per stage: level 2 s, then the two groups of level 2 s + 1
 // (t: thread of the row; tables as split_table_words lays them out)
 __device__ __forceinline__ void wide_twiddles(WideTwiddles& w, const double* table, u64 stride, int prime, uint32_t row, uint32_t t, Modulus q) {
@@ -809,87 +787,32 @@ __device__ __forceinline__ void wide_twiddles(WideTwiddles& w, const double* tab
     w.w[3][2] = fp_mulmod(c2, f21, q.p, q.pinv);
     w.w[4][0] = fp_mulmod(c3, f3, q.p, q.pinv);
 }
-// registers of stage FROM to registers of stage TO; the waves keep to their quarter of the row except between stages 0 and 1
-template <int FROM, int TO>
-__device__ __forceinline__ void wide_exchange(double (&v)[4], float (&m)[4], double* lds, uint32_t t) {
-    float top = 0.f;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-        lds[wide_at(wide_element<FROM>(t, r))] = v[r];
-        top = fmaxf(top, m[r]);
-    }
-    xchg_sync<FROM + TO != 1>();
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-        v[r] = lds[wide_at(wide_element<TO>(t, r))];
-        m[r] = top;
-    }
-    xchg_sync<true>();
-}
-template <int S>
-__device__ __forceinline__ void wide_fwd_stage(double (&v)[4], float (&m)[4], const WideTwiddles& w, Modulus q) {
-    constexpr float mw = S < 3 ? 0.5f : 0.6f;
-    fwd_bfly(v[0], v[2], m[0], m[2], w.w[S][0], mw, q);
-    fwd_bfly(v[1], v[3], m[1], m[3], w.w[S][0], mw, q);
-    fwd_bfly(v[0], v[1], m[0], m[1], w.w[S][1], mw, q);
-    fwd_bfly(v[2], v[3], m[2], m[3], w.w[S][2], mw, q);
-}
-template <int S>
-__device__ __forceinline__ void wide_inv_stage(double (&v)[4], float (&m)[4], const WideTwiddles& w, Modulus q) {
-    constexpr float mw = S < 3 ? 0.5f : 0.6f;
-    inv_bfly(v[0], v[1], m[0], m[1], w.w[S][1], mw, q);
-    inv_bfly(v[2], v[3], m[2], m[3], w.w[S][2], mw, q);
-    inv_bfly(v[0], v[2], m[0], m[2], w.w[S][0], mw, q);
-    inv_bfly(v[1], v[3], m[1], m[3], w.w[S][0], mw, q);
-}
 __device__ __forceinline__ void wide_cap(double (&v)[4], float (&m)[4], float cap, Modulus q) {
 #pragma unroll
     for (int r = 0; r < 4; r++)
         if (m[r] > cap) v[r] = fp_norm(v[r], q.p, q.pinv);
 }
-// in: coefficient 256 r + t, below m p; out: 4 t + r, below cap p.  The row's LDS is free when the first of its threads comes here.
+// bounds of the twiddles: tables up to stage 2, products behind
+#define WIDE_TW_BOUND(s) (s < 3 ? 0.5f : 0.6f)
+// in: below `bound` p; out: below cap p
 __device__ __forceinline__ void wide_forward(double (&v)[4], float bound, const WideTwiddles& w, double* lds, uint32_t t, Modulus q, float cap) {
     float m[4] = {bound, bound, bound, bound};
-    wide_fwd_stage<0>(v, m, w, q); wide_exchange<0, 1>(v, m, lds, t);
-    wide_fwd_stage<1>(v, m, w, q); wide_exchange<1, 2>(v, m, lds, t);
-    wide_fwd_stage<2>(v, m, w, q); wide_exchange<2, 3>(v, m, lds, t);
-    wide_fwd_stage<3>(v, m, w, q); wide_exchange<3, 4>(v, m, lds, t);
-    wide_fwd_stage<4>(v, m, w, q);
+    wide_forward_levels(v, m, lds, t, [&](auto s, double& x, double& y, float& bx, float& by, int k) {
+        fwd_bfly(x, y, bx, by, w.w[s][k], WIDE_TW_BOUND(s), q);
+    });
     wide_cap(v, m, cap, q);
 }
-// in: coefficient 4 t + r, below m p; out: 256 r + t, below 1.01 p
+// in: below `bound` p; out: below 1.01 p
 __device__ __forceinline__ void wide_inverse(double (&v)[4], float bound, const WideTwiddles& w, double* lds, uint32_t t, Modulus q) {
     float m[4] = {bound, bound, bound, bound};
-    wide_inv_stage<4>(v, m, w, q); wide_exchange<4, 3>(v, m, lds, t);
-    wide_inv_stage<3>(v, m, w, q); wide_exchange<3, 2>(v, m, lds, t);
-    wide_inv_stage<2>(v, m, w, q); wide_exchange<2, 1>(v, m, lds, t);
-    wide_inv_stage<1>(v, m, w, q); wide_exchange<1, 0>(v, m, lds, t);
-    wide_inv_stage<0>(v, m, w, q);
+    wide_inverse_levels(v, m, lds, t, [&](auto s, double& x, double& y, float& bx, float& by, int k) {
+        inv_bfly(x, y, bx, by, w.w[s][k], WIDE_TW_BOUND(s), q);
+    });
     wide_cap(v, m, 1.01f, q);
-}
-// coefficients 4 t + r of a limb's row, read through sigma_g when galois != 0
-template <int K3>
-__device__ __forceinline__ void wide_load(double (&v)[4], const void* limb, u64 galois, uint32_t row, uint32_t t) {
-    if (galois) {
-        const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
-#pragma unroll
-        for (int r = 0; r < 4; r++) v[r] = bloadf(src, galois_src_fp(row * 1024u + 4u * t + (uint32_t)r, galois, 10 + K3) * 8u, 0);
-    } else {
-        const rsrc_t src = make_rsrc((const u64*)limb + row * 1024u, 8192u);
-        bload2(src, t * 32u, 0, v[0], v[1]);
-        bload2(src, t * 32u, 16, v[2], v[3]);
-    }
 }
 __device__ __forceinline__ void wide_from_residues(double (&v)[4]) {
 #pragma unroll
     for (int r = 0; r < 4; r++) v[r] = fp_from_u64((u64)__double_as_longlong(v[r]));
-}
-__device__ __forceinline__ void wide_store(rsrc_t dst, uint32_t t, const double (&v)[4]) {      // 4 t + r
-#pragma unroll
-    for (int r = 0; r < 4; r += 2) {
-        const u32x4_t d = {lo32(v[r]), hi32(v[r]), lo32(v[r + 1]), hi32(v[r + 1])};
-        __builtin_amdgcn_raw_buffer_store_b128(d, dst, (int)(t * 32u), r * 8, 0);
-    }
 }
 __device__ __forceinline__ void wide_store_residues(rsrc_t dst, uint32_t t, double (&v)[4], Modulus q) {
 #pragma unroll
@@ -999,9 +922,8 @@ __device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const Inne
             for (int r = 0; r < 4; r++) div[r] = bloadf(dst, t * 8u, (uint32_t)r * 2048u);
         }
     }
-    // (the exchange between the first stages is the workgroup's: who transforms nothing keeps it company)
     if (mine && !own) wide_forward(v, COLUMNS_BOUND, w, slot, t, q, IP_CAP);
-    else __syncthreads();
+    else wide_no_row();
     if (own) wide_from_residues(v);
     if (mine) {
 #pragma unroll
@@ -1030,7 +952,7 @@ __device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const Inne
     if (!source && MODE == FP_INV_D_TO_Y) return;
     __syncthreads();                                            // everyone has read the digits
     if (!sums) {
-        __syncthreads();                                        // the exchange inside the transforms below
+        wide_no_row();
         return;
     }
     if (MODE == FP_FWD_CONV_SUB) {
@@ -1159,8 +1081,8 @@ template <int K3, int MODE>
 __global__ __launch_bounds__(WIDE_NT, 4) void ntt_fp_split_wide_kernel(FpArgs a, FpTask tk) {
     __shared__ double lds[WIDE_LDS];
     constexpr u64 n = (u64)1 << (10 + K3);
-    const int per = (a.n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || task >= a.n_tasks) return;
+    const int task = wide_task(a.n_tasks);
+    if (task < 0) return;
     const uint32_t t = threadIdx.x, row = (uint32_t)task & ((1u << K3) - 1);
     const int unit = task >> K3, e = unit / a.n_entries;
     const u64 b = unit - e * a.n_entries;
@@ -1285,9 +1207,8 @@ template <int K3>
 __global__ __launch_bounds__(2 * WIDE_NT, 4) void encrypt_rows_wide_kernel(EncryptArgs a) {
     __shared__ double lds[2 * WIDE_LDS];
     constexpr u64 n = (u64)1 << (10 + K3);
-    const int n_tasks = (a.n_entries * a.limbs) << K3, per = (n_tasks + 7) >> 3;
-    const int task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
+    const int task = wide_task((a.n_entries * a.limbs) << K3);
+    if (task < 0) return;
     const uint32_t t = threadIdx.x & (WIDE_NT - 1);
     const int poly = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WIDE_NT));
     const int unit = task / a.n_entries;
@@ -1354,8 +1275,8 @@ constexpr bool fp_inner(int mode) { return mode == FP_INV_D_TO_Y || mode == FP_F
 template <int K3, int MODE>
 __global__ __launch_bounds__(fp_inner(MODE) ? WIDE_DIGITS * WIDE_NT : WIDE_NT, 4) void ntt_fp_wide_kernel(ConvertArgs a, InnerArgs g, int n_tasks) {
     extern __shared__ double wide_lds[];
-    const int per = (n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
+    const int task = wide_task(n_tasks);
+    if (task < 0) return;
     if constexpr (MODE == FP_INV_TO_Y) wide_rows_inverse<K3>(a, task, wide_lds);
     else if constexpr (fp_inner(MODE)) wide_rows_inner<K3, MODE>(a, g, task, wide_lds);
     else wide_rows_forward<K3, MODE>(a, task, wide_lds);

@@ -499,29 +499,6 @@ __device__ __forceinline__ void rows_inner(const IntArgs& a, u64* lds) {
 // ---------------------------------------------------------------------------
 // rows by four waves each: calls with few rows
 // ---------------------------------------------------------------------------
-// A wave that keeps a row to itself works through eighty butterflies a lane one after the other, 1600 instructions, and
-// fetches its twiddles in five batches; with fewer rows than the chip has SIMDs nothing covers either.  Here a thread holds four
-// coefficients, two levels at a time, and all fifteen of its twiddles are on their way before the first level; only the
-// exchange behind the first two levels crosses waves.
-//   stage s, levels 2 s and 2 s + 1: register r of thread t is element 2^p-strided, p = 8 - 2 s (wide_element)
-#define WIDE_NT 256
-#define WIDE_LDS 1280    // 64-bit words per row: four words of padding per sixteen, so that a thread's four stay together
-__device__ __forceinline__ uint32_t wide_at(uint32_t i) { return i + ((i >> 4) << 2); }
-template <int S>
-__device__ __forceinline__ uint32_t wide_element(uint32_t t, uint32_t r) {
-    constexpr int p = 8 - 2 * S;
-    return ((t >> p) << (p + 2)) | (r << p) | (t & ((1u << p) - 1));
-}
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-__device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, u64& x, u64& y) {
-    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
-    x = ((u64)d.y << 32) | d.x;
-    y = ((u64)d.w << 32) | d.z;
-}
-__device__ __forceinline__ void bstore2(rsrc_t r, uint32_t lane_off, uint32_t row_off, u64 x, u64 y) {
-    const u32x4_t d = {(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
-    __builtin_amdgcn_raw_buffer_store_b128(d, r, (int)lane_off, (int)row_off, 0);
-}
 struct WideTwiddles { Tw w[5][3]; };     // per stage: level 2 s, then the two groups of level 2 s + 1
 template <int K3>
 __device__ __forceinline__ void wide_twiddles(WideTwiddles& w, const u64* tw, const u64* tw_sh, int prime, uint32_t row, uint32_t t) {
@@ -535,69 +512,17 @@ __device__ __forceinline__ void wide_twiddles(WideTwiddles& w, const u64* tw, co
         bload2(sr, node * 16u, 0, w.w[s][1].s, w.w[s][2].s);
     }
 }
-// registers of stage FROM to registers of stage TO; the waves keep to their quarter of the row except between stages 0 and 1
-template <int FROM, int TO>
-__device__ __forceinline__ void wide_exchange(u64 (&v)[4], int (&m)[4], u64* lds, uint32_t t) {
-    int top = 0;
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-        lds[wide_at(wide_element<FROM>(t, r))] = v[r];
-        top = m[r] > top ? m[r] : top;
-    }
-    xchg_sync<FROM + TO != 1>();
-#pragma unroll
-    for (int r = 0; r < 4; r++) {
-        v[r] = lds[wide_at(wide_element<TO>(t, r))];
-        m[r] = top;
-    }
-    xchg_sync<true>();
-}
-template <int S>
-__device__ __forceinline__ void wide_fwd_stage(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64 q) {
-    fwd_bfly(v[0], v[2], m[0], m[2], w.w[S][0], q);
-    fwd_bfly(v[1], v[3], m[1], m[3], w.w[S][0], q);
-    fwd_bfly(v[0], v[1], m[0], m[1], w.w[S][1], q);
-    fwd_bfly(v[2], v[3], m[2], m[3], w.w[S][2], q);
-}
-template <int S>
-__device__ __forceinline__ void wide_inv_stage(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64 q) {
-    inv_bfly(v[0], v[1], m[0], m[1], w.w[S][1], q);
-    inv_bfly(v[2], v[3], m[2], m[3], w.w[S][2], q);
-    inv_bfly(v[0], v[2], m[0], m[2], w.w[S][0], q);
-    inv_bfly(v[1], v[3], m[1], m[3], w.w[S][0], q);
-}
-// in: coefficient 256 r + t; out: 4 t + r, below cap q.  The row's LDS is free when the first of its threads comes here.
+// out: below cap q
 __device__ __forceinline__ void wide_forward(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64* lds, uint32_t t, u64 q, int cap) {
-    wide_fwd_stage<0>(v, m, w, q); wide_exchange<0, 1>(v, m, lds, t);
-    wide_fwd_stage<1>(v, m, w, q); wide_exchange<1, 2>(v, m, lds, t);
-    wide_fwd_stage<2>(v, m, w, q); wide_exchange<2, 3>(v, m, lds, t);
-    wide_fwd_stage<3>(v, m, w, q); wide_exchange<3, 4>(v, m, lds, t);
-    wide_fwd_stage<4>(v, m, w, q);
+    wide_forward_levels(v, m, lds, t, [&](auto s, u64& x, u64& y, int& bx, int& by, int k) { fwd_bfly(x, y, bx, by, w.w[s][k], q); });
 #pragma unroll
     for (int r = 0; r < 4; r++) cap_to(v[r], m[r], cap, q);
 }
-// in: coefficient 4 t + r; out: 256 r + t, below 8 q
+// out: below 8 q
 __device__ __forceinline__ void wide_inverse(u64 (&v)[4], int (&m)[4], const WideTwiddles& w, u64* lds, uint32_t t, u64 q) {
-    wide_inv_stage<4>(v, m, w, q); wide_exchange<4, 3>(v, m, lds, t);
-    wide_inv_stage<3>(v, m, w, q); wide_exchange<3, 2>(v, m, lds, t);
-    wide_inv_stage<2>(v, m, w, q); wide_exchange<2, 1>(v, m, lds, t);
-    wide_inv_stage<1>(v, m, w, q); wide_exchange<1, 0>(v, m, lds, t);
-    wide_inv_stage<0>(v, m, w, q);
+    wide_inverse_levels(v, m, lds, t, [&](auto s, u64& x, u64& y, int& bx, int& by, int k) { inv_bfly(x, y, bx, by, w.w[s][k], q); });
 #pragma unroll
     for (int r = 0; r < 4; r++) cap_to(v[r], m[r], 8, q);
-}
-// coefficients 4 t + r of a limb's row, read through sigma_g when galois != 0
-template <int K3>
-__device__ __forceinline__ void wide_load(u64 (&v)[4], const u64* limb, u64 galois, uint32_t row, uint32_t t) {
-    if (galois) {
-        const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
-#pragma unroll
-        for (int r = 0; r < 4; r++) v[r] = bload(src, galois_src_fp(row * 1024u + 4u * t + (uint32_t)r, galois, 10 + K3) * 8u, 0);
-    } else {
-        const rsrc_t src = make_rsrc(limb + row * 1024u, 8192u);
-        bload2(src, t * 32u, 0, v[0], v[1]);
-        bload2(src, t * 32u, 16, v[2], v[3]);
-    }
 }
 
 template <int K3>
@@ -644,8 +569,7 @@ __device__ __forceinline__ void wide_rows_divide(const IntArgs& a, int task, u64
     wide_forward(v, m, w, lds, t, q, 8);
 #pragma unroll
     for (int r = 0; r < 4; r++) v[r] = canonical(mul4(acc[r] + (q << 3) - v[r], f, q) + add[r], 5, q);     // acc is below 8 q
-    bstore2(dst, t * 32u, 0, v[0], v[1]);
-    bstore2(dst, t * 32u, 16, v[2], v[3]);
+    wide_store(dst, t, v);
 }
 
 // A workgroup per (limb x, row, entry), four waves per digit (two digits at least, INNER_CHUNK at most: the caller's rule).  Each
@@ -681,9 +605,8 @@ __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64*
         for (int d = 0; d < INNER_CHUNK; d++)
             if (d < a.n_digits) wide_load<K3>(k[d], a.key + ((u64)(2 * d + part) * a.total + prime) * n, 0, row, t);
     }
-    // (the exchange between the first stages is the workgroup's: who transforms nothing keeps it company)
     if (mine && !own) wide_forward(v, m, w, slot, t, q, 2);
-    else __syncthreads();
+    else wide_no_row();
     if (mine) {
 #pragma unroll
         for (int r = 0; r < 4; r++) slot[wide_at(4 * t + r)] = split30(v[r]);
@@ -702,14 +625,13 @@ __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64*
         }
         if (!special) {
             const rsrc_t dst = make_rsrc(a.sums + ((b * 2 + part) * a.l + x) * n + row * 1024u, 8192u);
-            bstore2(dst, t * 32u, 0, v[0], v[1]);
-            bstore2(dst, t * 32u, 16, v[2], v[3]);
+            wide_store(dst, t, v);
         }
     }
     if (!special) return;
     __syncthreads();                                            // everyone has read the digits
     if (!sums) {
-        __syncthreads();                                        // the exchange inside wide_inverse
+        wide_no_row();
         return;
     }
     wide_inverse(v, m, w, slot, t, q);
@@ -974,8 +896,8 @@ void ntt_int_kernel(IntArgs a, IntTasks tk, int n_tasks) {
 template <int K3, int MODE>
 __global__ __launch_bounds__(MODE == INT_INNER ? INNER_CHUNK * WIDE_NT : WIDE_NT, 4) void ntt_int_wide_kernel(IntArgs a, IntTasks tk, int n_tasks) {
     extern __shared__ u64 lds[];
-    const int per = (n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || task >= n_tasks) return;
+    const int task = wide_task(n_tasks);
+    if (task < 0) return;
     if constexpr (MODE == INT_INVERSE) wide_rows_inverse<K3>(a, tk, task, lds);
     else if constexpr (MODE == INT_INNER) wide_rows_inner<K3>(a, task, lds);
     else wide_rows_divide<K3>(a, task, lds);

@@ -1,6 +1,8 @@
-// Device helpers shared by the fp64 kernels (ntt_fp.hip, convert_fp.hip): scalar table reads, buffer-resource
-// accesses, wave-local ordering of LDS traffic, the NTT-order automorphism.
+// Device helpers shared by the transforms (ntt_fp.hip, convert_fp.hip, convert_int.hip): scalar table reads, buffer-resource
+// accesses, wave-local ordering of LDS traffic, the NTT-order automorphism, rows by one wave and by four.
 #pragma once
+#include <type_traits>
+
 #include "hisa_internal.hpp"
 #include "fparith.hpp"
 
@@ -33,6 +35,27 @@ __device__ __forceinline__ void bstore(rsrc_t r, uint32_t lane_off, uint32_t row
 }
 __device__ __forceinline__ void bstoref(rsrc_t r, uint32_t lane_off, uint32_t row_off, double x) {
     bstore(r, lane_off, row_off, (u64)__double_as_longlong(x));
+}
+
+// two neighbouring words, 16 bytes
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, u64& x, u64& y) {
+    const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(r, (int)lane_off, (int)row_off, 0);
+    x = ((u64)d.y << 32) | d.x;
+    y = ((u64)d.w << 32) | d.z;
+}
+__device__ __forceinline__ void bload2(rsrc_t r, uint32_t lane_off, uint32_t row_off, double& x, double& y) {
+    u64 a, b;
+    bload2(r, lane_off, row_off, a, b);
+    x = __longlong_as_double((long long)a);
+    y = __longlong_as_double((long long)b);
+}
+__device__ __forceinline__ void bstore2(rsrc_t r, uint32_t lane_off, uint32_t row_off, u64 x, u64 y) {
+    const u32x4_t d = {(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
+    __builtin_amdgcn_raw_buffer_store_b128(d, r, (int)lane_off, (int)row_off, 0);
+}
+__device__ __forceinline__ void bstore2(rsrc_t r, uint32_t lane_off, uint32_t row_off, double x, double y) {
+    bstore2(r, lane_off, row_off, (u64)__double_as_longlong(x), (u64)__double_as_longlong(y));
 }
 
 // keeps the compiler from moving instructions across this point (loads issued in batches stay batches)
@@ -97,4 +120,94 @@ __device__ __forceinline__ int row_task(int n_tasks) {
     if ((int)(blockIdx.x >> 3) >= per) return -1;
     const int task = blk * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     return task < n_tasks ? task : -1;
+}
+
+// ---- rows of 1024 coefficients, four waves each: calls with few rows (V = double, B = float; V = u64, B = int) ----
+// A wave that keeps a row to itself works through eighty butterflies a lane one after the other and fetches its twiddles in
+// batches between them; with fewer rows than the chip has SIMDs nothing covers either.  Here a thread holds four
+// coefficients, two levels at a time, and everything it will need is on its way before the first level; only the exchange
+// behind the first two levels crosses waves.
+//   stage s, levels 2 s and 2 s + 1: registers 0 .. 3 of thread t are 2^p apart, p = 8 - 2 s (wide_element)
+#define WIDE_NT 256
+#define WIDE_LDS 1280    // 64-bit words per row: four words of padding per sixteen, so that a thread's four stay together
+__device__ __forceinline__ uint32_t wide_at(uint32_t i) { return i + ((i >> 4) << 2); }
+template <int S>
+__device__ __forceinline__ uint32_t wide_element(uint32_t t, uint32_t r) {
+    constexpr int p = 8 - 2 * S;
+    return ((t >> p) << (p + 2)) | (r << p) | (t & ((1u << p) - 1));
+}
+// registers of stage FROM to registers of stage TO; the waves keep to their quarter of the row except between stages 0 and 1
+template <int FROM, int TO, class V, class B>
+__device__ __forceinline__ void wide_exchange(V (&v)[4], B (&m)[4], V* lds, uint32_t t) {
+    B top = 0;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        lds[wide_at(wide_element<FROM>(t, r))] = v[r];
+        top = m[r] > top ? m[r] : top;
+    }
+    xchg_sync<FROM + TO != 1>();
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+        v[r] = lds[wide_at(wide_element<TO>(t, r))];
+        m[r] = top;
+    }
+    xchg_sync<true>();
+}
+// The ten levels, bounds m in and out; bfly(stage, x, y, bound of x, of y, k): butterfly by twiddle k of the stage, 0 of its
+// first level, 1 and 2 of the groups of its second.  The row's LDS is free when the first of its threads comes here.  Either
+// meets the workgroup's barrier once: its threads that transform no row meet it in wide_no_row instead.
+// forward: coefficient 256 r + t -> 4 t + r
+template <int S = 0, class V, class B, class F>
+__device__ __forceinline__ void wide_forward_levels(V (&v)[4], B (&m)[4], V* lds, uint32_t t, F bfly) {
+    constexpr std::integral_constant<int, S> s{};
+    bfly(s, v[0], v[2], m[0], m[2], 0);
+    bfly(s, v[1], v[3], m[1], m[3], 0);
+    bfly(s, v[0], v[1], m[0], m[1], 1);
+    bfly(s, v[2], v[3], m[2], m[3], 2);
+    if constexpr (S < 4) {
+        wide_exchange<S, S + 1>(v, m, lds, t);
+        wide_forward_levels<S + 1>(v, m, lds, t, bfly);
+    }
+}
+// inverse: coefficient 4 t + r -> 256 r + t
+template <int S = 4, class V, class B, class F>
+__device__ __forceinline__ void wide_inverse_levels(V (&v)[4], B (&m)[4], V* lds, uint32_t t, F bfly) {
+    constexpr std::integral_constant<int, S> s{};
+    bfly(s, v[0], v[1], m[0], m[1], 1);
+    bfly(s, v[2], v[3], m[2], m[3], 2);
+    bfly(s, v[0], v[2], m[0], m[2], 0);
+    bfly(s, v[1], v[3], m[1], m[3], 0);
+    if constexpr (S > 0) {
+        wide_exchange<S, S - 1>(v, m, lds, t);
+        wide_inverse_levels<S - 1>(v, m, lds, t, bfly);
+    }
+}
+__device__ __forceinline__ void wide_no_row() { xchg_sync<false>(); }
+
+// coefficients 4 t + r of a limb's row, read through sigma_g when galois != 0
+template <int K3, class V>
+__device__ __forceinline__ void wide_load(V (&v)[4], const void* limb, u64 galois, uint32_t row, uint32_t t) {
+    if (galois) {
+        const rsrc_t src = make_rsrc(limb, (uint32_t)8192 << K3);
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const uint32_t at = galois_src_fp(row * 1024u + 4u * t + (uint32_t)r, galois, 10 + K3) * 8u;
+            if constexpr (std::is_same_v<V, double>) v[r] = bloadf(src, at, 0);
+            else v[r] = bload(src, at, 0);
+        }
+    } else {
+        const rsrc_t src = make_rsrc((const u64*)limb + row * 1024u, 8192u);
+        bload2(src, t * 32u, 0, v[0], v[1]);
+        bload2(src, t * 32u, 16, v[2], v[3]);
+    }
+}
+template <class V>
+__device__ __forceinline__ void wide_store(rsrc_t dst, uint32_t t, const V (&v)[4]) {      // 4 t + r
+    bstore2(dst, t * 32u, 0, v[0], v[1]);
+    bstore2(dst, t * 32u, 16, v[2], v[3]);
+}
+// workgroups are tasks, (limb, row, entry) as above: a contiguous range of them per XCD
+__device__ __forceinline__ int wide_task(int n_tasks) {
+    const int per = (n_tasks + 7) >> 3, task = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    return (int)(blockIdx.x >> 3) < per && task < n_tasks ? task : -1;
 }
