@@ -12,10 +12,12 @@
 
 // Two coefficients a thread, 16 bytes an access (polynomials start at multiples of 8 KB of a pool block), and where a kernel
 // treats several polynomials alike, all of them: 24 products of two polynomials at N = 2^14, 8 limbs were 24576 workgroups of 2 KB
-// each way, 23 us, and are 18 now; the sums 25 us, 22 now.
+// each way, 23 us, and are 18 now; the sums 25 us, 22 now.  Beyond the last-level cache that is not the better form everywhere (launch_addsub).
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u64x2 ld2(const u64* p) { return *(const u64x2*)p; }
 __device__ __forceinline__ void st2(u64* p, u64x2 v) { *(u64x2*)p = v; }
+// what a launch reads and writes, in polynomials of one limb, does not fit the last-level cache
+static bool beyond_cache(u64 limb_polys, int log_n) { return limb_polys << (log_n + 3) > (u64)256 << 20; }
 #define PAIR_BLOCKS(log_n) ((1u << (log_n)) / (2 * NT))
 __device__ __forceinline__ u64 pair_at() { return 2 * ((u64)blockIdx.x * NT + threadIdx.x); }
 
@@ -86,27 +88,27 @@ hipError_t launch_sample_small(const PrimeConst* primes, u64 seed, u64 kind, u64
 }
 
 // ---- add / sub --------------------------------------------------------------
-// out[b][p][i] = a[b][p][i] (+|-) b[b][p][i] for p < polys_b, copy of a for the rest.
+// out[b][p][i] = a[b][p][i] (+|-) b[b][p][i] for p < polys_b, copy of a for the rest.  A workgroup: `polys` of the polynomials
 __global__ __launch_bounds__(NT) void addsub_kernel(const PrimeConst* primes, const u64* a, const u64* b, u64* out, int op,
-                                                    int limbs, int polys_a, int polys_b, u64 a_bs, u64 b_bs, u64 o_bs,
+                                                    int limbs, int polys, int polys_a, int polys_b, u64 a_bs, u64 b_bs, u64 o_bs,
                                                     int log_n) {
     const u64 n = (u64)1 << log_n;
-    const int limb = blockIdx.y;
+    const int limb = blockIdx.y % limbs, first = blockIdx.y / limbs * polys, end = first + polys;
     const u64 bi = blockIdx.z;
     const u64 q = primes[limb].q;
     const u64 j = (u64)limb * n + pair_at();
     // two polynomials' loads ahead of the first store: a small call waits once
-    for (int poly = 0; poly < polys_a; poly += 2) {
+    for (int poly = first; poly < end; poly += 2) {
         u64x2 x[2], y[2];
 #pragma unroll
         for (int k = 0; k < 2; k++) {
             const u64 off = (u64)(poly + k) * limbs * n + j;
-            if (poly + k < polys_a) x[k] = ld2(a + bi * a_bs + off);
-            if (poly + k < polys_b) y[k] = ld2(b + bi * b_bs + off);
+            if (poly + k < end) x[k] = ld2(a + bi * a_bs + off);
+            if (poly + k < end && poly + k < polys_b) y[k] = ld2(b + bi * b_bs + off);
         }
 #pragma unroll
         for (int k = 0; k < 2; k++) {
-            if (poly + k >= polys_a) break;
+            if (poly + k >= end) break;
             if (poly + k < polys_b)
                 x[k] = op == OP_ADD ? u64x2{addmod(x[k].x, y[k].x, q), addmod(x[k].y, y[k].y, q)} : u64x2{submod(x[k].x, y[k].x, q), submod(x[k].y, y[k].y, q)};
             st2(out + bi * o_bs + (u64)(poly + k) * limbs * n + j, x[k]);
@@ -118,9 +120,12 @@ hipError_t launch_addsub(const PrimeConst* primes, const u64* a, const u64* b, u
                          int polys_b, u64 n_batch, u64 a_bs, u64 b_bs, u64 o_bs, int log_n, hipStream_t st) {
     if (t_analysis) TALLY(add, HISA_OP_ADD, n_batch, limbs);
     DRY_RUN_RETURN();
-    dim3 grid(PAIR_BLOCKS(log_n), limbs, (unsigned)n_batch);
+    // All polynomials of an entry in a workgroup, or beyond the cache one: us, 64 sums at N = 2^15, 16 limbs 291 -> 285, and 308 -> 303 where
+    // a rescale follows; 60 at 9 limbs 163 -> 159 so; 96 at N = 2^14, 12 limbs 156 -> 153; 64 at N = 2^12, 16 limbs (200 MB) even.
+    const int polys = beyond_cache(3 * (u64)polys_a * limbs * n_batch, log_n) ? 1 : polys_a;
+    dim3 grid(PAIR_BLOCKS(log_n), limbs * (polys_a / polys), (unsigned)n_batch);
     ProfScope prof__("addsub_kernel", st);
-    hipLaunchKernelGGL(addsub_kernel, grid, dim3(NT), 0, st, primes, a, b, out, op, limbs, polys_a, polys_b, a_bs, b_bs,
+    hipLaunchKernelGGL(addsub_kernel, grid, dim3(NT), 0, st, primes, a, b, out, op, limbs, polys, polys_a, polys_b, a_bs, b_bs,
                        o_bs, log_n);
     return hipGetLastError();
 }

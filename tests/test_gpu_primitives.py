@@ -207,6 +207,38 @@ def test_batched_forms_match_single_calls(pair):
         same(g, o, a, o.rescale(b))
 
 
+@pytest.mark.parametrize("log_n,limbs", [(10, 3), (13, 8), (15, 5)])
+def test_sums_beyond_the_last_level_cache(log_n, limbs):
+    """The largest sums of 256 MB, operands and result together, and one ciphertext more, which go another way: single
+    calls' values."""
+    from paper_1810_00845_amd import hisa
+    print("[case]", log_n, limbs, flush=True)
+    g = hisa.Context(log_n, [50] * limbs, 1, 50, 5)
+
+    def both_sides(polys, fn):
+        few = (256 << 20) // (polys * limbs * 8 * g.N)
+        for n in (few, few + 1):
+            a, b = g.ct_random_batch(n, limbs, 1.0, 1000), g.ct_random_batch(n, limbs, 1.0, 500000)
+            g.profile_enable(True)
+            got, x, y = fn(a, b)
+            names = set(g.profile_read())
+            g.profile_enable(False)
+            for i in (0, 1, n // 2, n - 1):
+                assert np.array_equal(g.ct_export(got[i]), g.ct_export(fn([x[i]], [y[i]], True)))
+            yield names
+
+    def total(a, b, one=False):
+        return g.add(a[0], b[0]) if one else (g.add_batch(a, b), a, b)
+
+    def of_products(a, b, one=False):                   # three polynomials each
+        x, y = (a, b) if one else (g.mul_no_relin_batch(a, a), g.mul_no_relin_batch(a, b))
+        return g.add(x[0], y[0]) if one else (g.add_batch(x, y), x, y)
+
+    for names in list(both_sides(6, total)) + list(both_sides(9, of_products)):
+        assert "addsub_kernel" in names
+    g.close()
+
+
 def test_hoisted_rotations_equal_single_rotations(pair):
     """Several rotations sharing one decomposition of c1 give, bit for bit, what the oracle's rotLeft gives, at the
     top level and two levels down, with a step that is a plain copy and handles from different allocations."""
