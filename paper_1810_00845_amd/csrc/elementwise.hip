@@ -12,7 +12,8 @@
 
 // Two coefficients a thread, 16 bytes an access (polynomials start at multiples of 8 KB of a pool block), and where a kernel
 // treats several polynomials alike, all of them: 24 products of two polynomials at N = 2^14, 8 limbs were 24576 workgroups of 2 KB
-// each way, 23 us, and are 18 now; the sums 25 us, 22 now.  Beyond the last-level cache that is not the better form everywhere (launch_addsub).
+// each way, 23 us, and are 18 now; the sums 25 us, 22 now.  Beyond the last-level cache that is not the better form everywhere (launch_addsub,
+// launch_mul_no_relin).
 typedef u64 u64x2 __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ u64x2 ld2(const u64* p) { return *(const u64x2*)p; }
 __device__ __forceinline__ void st2(u64* p, u64x2 v) { *(u64x2*)p = v; }
@@ -239,10 +240,41 @@ __global__ __launch_bounds__(NT) void mul_no_relin_kernel(const PrimeConst* prim
     st2(out + bi * o_bs + o2, u64x2{product(a1.x, b1.x), product(a1.y, b1.y)});
 }
 
+// The same beyond the cache: a coefficient a thread, workgroups of 8 KB, and the two polynomials that relinearisation reads last leave
+// past the caches.
+#define MUL_STREAM_NT 1024
+__global__ __launch_bounds__(MUL_STREAM_NT) void mul_no_relin_stream_kernel(const PrimeConst* primes, const u64* a, const u64* b, u64* out,
+                                                                            int limbs, u64 a_bs, u64 b_bs, u64 o_bs, int log_n) {
+    const u64 n = (u64)1 << log_n;
+    const int limb = blockIdx.y;
+    const u64 bi = blockIdx.z;
+    const PrimeConst pc = primes[limb];
+    const u64 j = (u64)blockIdx.x * MUL_STREAM_NT + threadIdx.x;
+    const u64 o0 = (u64)limb * n + j, o1 = ((u64)limbs + limb) * n + j, o2 = ((u64)2 * limbs + limb) * n + j;
+    const u64 a0 = a[bi * a_bs + o0], a1 = a[bi * a_bs + o1];
+    const u64 b0 = b[bi * b_bs + o0], b1 = b[bi * b_bs + o1];
+    __builtin_nontemporal_store(mulmod_barrett(a0, b0, pc.q, pc.r1, pc.r0), out + bi * o_bs + o0);
+    Acc128 acc = {0, 0};
+    acc_mad(acc, a0, b1);
+    acc_mad(acc, a1, b0);
+    __builtin_nontemporal_store(acc_reduce(acc, pc.q, pc.r1, pc.r0), out + bi * o_bs + o1);
+    out[bi * o_bs + o2] = mulmod_barrett(a1, b1, pc.q, pc.r1, pc.r0);
+}
+
 hipError_t launch_mul_no_relin(const PrimeConst* primes, const u64* a, const u64* b, u64* out, int limbs, u64 n_batch,
                                u64 a_bs, u64 b_bs, u64 o_bs, int log_n, hipStream_t st) {
     if (t_analysis) TALLY(mul, HISA_OP_MUL, n_batch, limbs);
     DRY_RUN_RETURN();
+    // Bound by memory: seven streams.  Two coefficients a thread in workgroups of 4 KB -> one in 8 KB past the caches, us: 32 products at
+    // N = 2^14, 12 limbs 63 -> 53, 64 123 -> 119, 96 180 -> 179 (one coefficient in 2 KB: 60, 119, 177); at N = 2^15, 16 limbs 16 86 -> 80, 64
+    // 340 -> 326 (379); 24 at N = 2^14, 11 limbs (231 MB) 37.9 either way.  37 there with relinearisation and rescale 432 -> 423.  A batch's
+    // squares read two polynomials fewer and stay with pairs: 64 at N = 2^15, 16 limbs 237 against 261.
+    if (a != b && beyond_cache((u64)7 * limbs * n_batch, log_n)) {
+        dim3 grid((1u << log_n) / MUL_STREAM_NT, limbs, (unsigned)n_batch);
+        ProfScope prof__("mul_no_relin_stream_kernel", st);
+        hipLaunchKernelGGL(mul_no_relin_stream_kernel, grid, dim3(MUL_STREAM_NT), 0, st, primes, a, b, out, limbs, a_bs, b_bs, o_bs, log_n);
+        return hipGetLastError();
+    }
     dim3 grid(PAIR_BLOCKS(log_n), limbs, (unsigned)n_batch);
     ProfScope prof__("mul_no_relin_kernel", st);
     hipLaunchKernelGGL(mul_no_relin_kernel, grid, dim3(NT), 0, st, primes, a, b, out, limbs, a_bs, b_bs, o_bs, log_n);

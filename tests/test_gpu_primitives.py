@@ -208,9 +208,9 @@ def test_batched_forms_match_single_calls(pair):
 
 
 @pytest.mark.parametrize("log_n,limbs", [(10, 3), (13, 8), (15, 5)])
-def test_sums_beyond_the_last_level_cache(log_n, limbs):
-    """The largest sums of 256 MB, operands and result together, and one ciphertext more, which go another way: single
-    calls' values."""
+def test_products_and_sums_beyond_the_last_level_cache(log_n, limbs):
+    """The largest products and sums of 256 MB, operands and result together, and one ciphertext more, which go another way (squares
+    do not): single calls' values, and the launches that ran."""
     from paper_1810_00845_amd import hisa
     print("[case]", log_n, limbs, flush=True)
     g = hisa.Context(log_n, [50] * limbs, 1, 50, 5)
@@ -227,6 +227,12 @@ def test_sums_beyond_the_last_level_cache(log_n, limbs):
                 assert np.array_equal(g.ct_export(got[i]), g.ct_export(fn([x[i]], [y[i]], True)))
             yield names
 
+    def product(a, b, one=False):
+        return g.mul_no_relin(a[0], b[0]) if one else (g.mul_no_relin_batch(a, b), a, b)
+
+    def square(a, b, one=False):
+        return g.mul_no_relin(a[0], a[0]) if one else (g.mul_no_relin_batch(a, a), a, a)
+
     def total(a, b, one=False):
         return g.add(a[0], b[0]) if one else (g.add_batch(a, b), a, b)
 
@@ -234,6 +240,8 @@ def test_sums_beyond_the_last_level_cache(log_n, limbs):
         x, y = (a, b) if one else (g.mul_no_relin_batch(a, a), g.mul_no_relin_batch(a, b))
         return g.add(x[0], y[0]) if one else (g.add_batch(x, y), x, y)
 
+    assert list(both_sides(7, product)) == [{"mul_no_relin_kernel"}, {"mul_no_relin_stream_kernel"}]
+    assert list(both_sides(7, square)) == [{"mul_no_relin_kernel"}] * 2
     for names in list(both_sides(6, total)) + list(both_sides(9, of_products)):
         assert "addsub_kernel" in names
     g.close()
