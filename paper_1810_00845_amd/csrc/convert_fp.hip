@@ -13,8 +13,8 @@
 // whatever else is idle, so a call with fewer limb-polynomials than compute units is bound by that latency.  Here a
 // polynomial at N = 2^15 is 32 waves of rows and 32 tiles of columns, nothing waits for a whole polynomial except
 // the launch boundary, and the conversion inputs never travel through memory.  rotLeft against whole-polynomial workgroups
-// (which also sent the extended digits through memory once more): 64 ciphertexts at N = 2^15, 16 limbs, 1.84 -> 1.31 ms;
-// 3 at 17 limbs 223 -> 105 us; one at N = 2^13, 8 limbs, 64 -> 27 us.  Large batches are bound by fp64 issue in the columns
+// (which also sent the extended digits through memory once more): 64 ciphertexts at N = 2^15, 16 limbs, 1.84 -> 1.28 ms;
+// 3 at 17 limbs 223 -> 107 us; one at N = 2^13, 8 limbs, 64 -> 26 us.  Large batches are bound by fp64 issue in the columns
 // and by memory in the rows, single ciphertexts by five launches of 4-8 us, each a chain of dependent levels.
 //
 // A wave holds 1024 coefficients, 16 per lane.  Five levels on a five-bit field take four in registers and the one on

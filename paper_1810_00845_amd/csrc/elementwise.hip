@@ -282,7 +282,7 @@ hipError_t launch_mul_no_relin(const PrimeConst* primes, const u64* a, const u64
 }
 
 // x^2 + c x before relinearisation, (a0 (a0 + c), a1 (2 a0 + c), a1^2): what an activation starts from, in one pass over x.
-// Product, scaled copy and sum as launches of their own moved 14 polynomials where this moves five; bound by memory.
+// Product, scaled copy and sum as launches of their own moved 15 polynomials where this moves five; bound by memory.
 // All activations of a network, us: LeNet-medium 286 -> 94, SqueezeNet-style 442 -> 140 (and 16 copies of concatenated inputs).
 __global__ __launch_bounds__(NT) void square_linear_kernel(const PrimeConst* primes, const u64* a, u64* out, LimbConsts c, int limbs,
                                                            u64 a_bs, u64 o_bs, int log_n) {

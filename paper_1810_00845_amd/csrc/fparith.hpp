@@ -32,8 +32,8 @@ FP_HD double fp_mulmod(double a, double b, double p, double pinv) {
 
 // Sums of products a_i * b_i with one reduction for all of them.  h holds a base + (the sum, each product rounded to the unit in the
 // last place of the base as it is added), l what the roundings left out: h stays in the binade of the base, so both
-// differences below are exact.  Four instructions a term where a modular product and an addition are seven, and six to
-// get the value out.  With base 1.5 * 2^(2 e + t):
+// differences below are exact.  Four instructions a term where a modular product and an addition are seven, and five to
+// get the value out, eight with the fp_norm behind it.  With base 1.5 * 2^(2 e + t):
 //   |a_i * b_i| <= 2^(2 e - 2), at most 2^(t + 1) of them: |h - base| <= 2^(2 e + t - 1), |l| <= 2^(2 e + 2 t - 52) beside
 //   what it started from; 2 e + 2 t <= 104 keeps that below 2^52
 //   fp_sum_value: an integer congruent to the sum plus the start of l, |result| <= 1.5 p + |l|, for p < 2^e

@@ -1777,9 +1777,12 @@ static int key_switch_fused_fp(hisa_ctx* ctx, const u64* d, u64 d_bs, u64 galois
     return key_switch_divide_fp(ctx, c, g, by, nullptr, l, B, out);
 }
 
-// Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic
-// (rotLeft of 64 at N = 2^15, 16 limbs: 1.34 ms against 1.52), but makes the last launch's chain longer (one
-// rotation at N = 2^13: 36 us against 33).  The two meet where the rows of one launch fill about half of the chip.
+// Keeping the accumulators in registers until the division's transform is there saves a quarter of the memory traffic, but makes
+// the last launch's chain longer.  The two meet where the rows of one launch fill about half of the chip: rotLeft, us, in
+// memory / in registers: N = 2^13, 8 limbs: one 27.3 / 30.8, 10 (960 rows) 47.2 / 50.9, 11 (1056) 50.9 / 50.4, 43 118 / 110; N = 2^14, 12
+// limbs: 3 (768) 51.7 / 54.5, 4 (1024) 56.3 / 55.7; N = 2^15, 21 limbs: 64 1913 / 1641.  Behind the combined division memory stays ahead
+// for longer: activations of 3 ciphertexts at N = 2^14, 12 limbs 59.5 / 63.5, of 4 65 / 74, 8 (2048 rows) 96 / 101, of 4 at N = 2^15, 16
+// limbs (2816) 136 / 130.
 static bool store_accumulators(const hisa_ctx* ctx, size_t entries, int ext_limbs) {
     return entries * (size_t)ext_limbs * (ctx->N >> 10) < 1024;
 }

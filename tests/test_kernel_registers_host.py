@@ -17,7 +17,6 @@ def kernels():
     """{mangled name: (vector registers, spilled vector registers)}"""
     import __graft_entry__
     from paper_1810_00845_amd import build
-    import os
     if not os.path.exists(build.LIB):
         __graft_entry__.build()
     with open(build.LIB, "rb") as f:
