@@ -8,46 +8,46 @@
 
 #define NT 256
 
-// coeffs[p][k] = round( factor * sum_j ( re[p][j] cos(pi e/N) + im[p][j] sin(pi e/N) ) ),  e = g[j] k mod 2N,
-// g[j] = 5^(slot of entry j) mod 2N.  One launch encodes n_pts vectors that share the slot list g[count]
-// (dense input: g[j] = 5^j; sparse input: only the non-zero slots are listed).
-__global__ __launch_bounds__(NT) void encode_kernel(const double* cs, const double* sn, const uint32_t* g, const double* re,
-                                                    const double* im, int count, double factor, i64* coeffs, int log_n) {
-    const uint32_t k = blockIdx.x * NT + threadIdx.x;
+// coeffs[p][k] = round( factor * sum_j re[p][j] cos(pi e/N) ),  e = g[j] k mod 2N, g[j] = 5^(slot of entry j) mod 2N.  One
+// launch encodes n_pts real vectors that share the slot list g[count].  A real vector's coefficient N - k is minus
+// coefficient k (g[j] is odd): both come from one sum, so that the residues in NTT form mirror each other exactly.
+__global__ __launch_bounds__(NT) void encode_kernel(const double* cs, const uint32_t* g, const double* re, int count, double factor,
+                                                    i64* coeffs, int log_n) {
+    const uint32_t k = blockIdx.x * NT + threadIdx.x;     // < N / 2
     const uint32_t mask = (2u << log_n) - 1;
     const size_t p = blockIdx.y;
     const double* r = re + p * count;
-    const double* m = im ? im + p * count : nullptr;
     double acc = 0.0;
-    for (int j = 0; j < count; j++) {
-        uint32_t e = (g[j] * k) & mask;
-        acc += r[j] * cs[e];
-        if (m) acc += m[j] * sn[e];
-    }
-    coeffs[(p << log_n) + k] = (i64)round(acc * factor);
+    for (int j = 0; j < count; j++) acc += r[j] * cs[(g[j] * k) & mask];
+    const i64 v = (i64)round(acc * factor);
+    i64* out = coeffs + (p << log_n);
+    out[k] = v;
+    out[k ? (1u << log_n) - k : 1u << (log_n - 1)] = k ? -v : 0;
 }
 
-hipError_t launch_encode(const double* cs, const double* sn, const uint32_t* g, const double* re, const double* im,
-                         int count, int n_pts, double factor, i64* coeffs, int log_n, hipStream_t st) {
+hipError_t launch_encode(const double* cs, const uint32_t* g, const double* re, int count, int n_pts, double factor, i64* coeffs,
+                         int log_n, hipStream_t st) {
     DRY_RUN_RETURN();
     if (n_pts <= 0) return hipSuccess;
     ProfScope prof__("encode_kernel", st);
-    hipLaunchKernelGGL(encode_kernel, dim3((1u << log_n) / NT, n_pts), dim3(NT), 0, st, cs, sn, g, re, im, count, factor,
-                       coeffs, log_n);
+    hipLaunchKernelGGL(encode_kernel, dim3((1u << log_n) / 2 / NT, n_pts), dim3(NT), 0, st, cs, g, re, count, factor, coeffs, log_n);
     return hipGetLastError();
 }
 
 // Plaintexts that are piecewise constant -- value v[p][b] on slot set S_b, zero elsewhere -- are linear combinations of
 // the nb encodings of the indicator vectors of the S_b: coeffs[p][k] = round(factor * sum_b v[p][b] basis[b][k]) with
-// basis[b][k] = sum_{j in S_b} cos(pi g_j k / N), which costs nb terms per coefficient instead of one per slot.
+// basis[b][k] = sum_{j in S_b} cos(pi g_j k / N), which costs nb terms per coefficient instead of one per slot.  The second
+// half of a basis row is minus the first read backwards, exactly, and so is every combination.
 __global__ __launch_bounds__(NT) void encode_basis_kernel(const double* cs, const uint32_t* g, const int* set_begin,
                                                           double* basis, int log_n) {
-    const uint32_t k = blockIdx.x * NT + threadIdx.x;
+    const uint32_t k = blockIdx.x * NT + threadIdx.x;     // < N / 2
     const uint32_t mask = (2u << log_n) - 1;
     const int b = blockIdx.y;
     double acc = 0.0;
     for (int j = set_begin[b]; j < set_begin[b + 1]; j++) acc += cs[(g[j] * k) & mask];
-    basis[((size_t)b << log_n) + k] = acc;
+    double* row = basis + ((size_t)b << log_n);
+    row[k] = acc;
+    row[k ? (1u << log_n) - k : 1u << (log_n - 1)] = k ? -acc : 0.0;
 }
 
 __global__ __launch_bounds__(NT) void encode_combine_kernel(const double* basis, int nb, const double* v, double factor,
@@ -64,7 +64,7 @@ hipError_t launch_encode_basis(const double* cs, const uint32_t* g, const int* s
     DRY_RUN_RETURN();
     if (nb <= 0) return hipSuccess;
     ProfScope prof__("encode_basis_kernel", st);
-    hipLaunchKernelGGL(encode_basis_kernel, dim3((1u << log_n) / NT, nb), dim3(NT), 0, st, cs, g, set_begin, basis, log_n);
+    hipLaunchKernelGGL(encode_basis_kernel, dim3((1u << log_n) / 2 / NT, nb), dim3(NT), 0, st, cs, g, set_begin, basis, log_n);
     return hipGetLastError();
 }
 
@@ -233,11 +233,21 @@ __device__ __forceinline__ cplx sf_add(cplx a, cplx b) { return make_double2(a.x
 __device__ __forceinline__ cplx sf_sub(cplx a, cplx b) { return make_double2(a.x - b.x, a.y - b.y); }
 __device__ __forceinline__ int sf_pad(int i) { return i + (i >> 3); }    // 16-byte elements: spreads strides of 4, 16, .. over the banks
 
+// The end of an encoding: u_k = m_k + i m_{k+n} times factor, rounded.  mirror (real slot values): m_{N-k} = -m_k is taken from
+// the real part of u_k instead of the imaginary part of u_{n-k}, so that it holds exactly.
+__device__ __forceinline__ void store_coeffs(i64* m, uint32_t k, uint32_t n, cplx u, double factor, bool mirror) {
+    const i64 v = (i64)round(u.x * factor);
+    m[k] = v;
+    if (!mirror) m[k + n] = (i64)round(u.y * factor);
+    else m[k ? 2 * n - k : n] = k ? -v : 0;
+}
+
 // stages of length 2 .. 1024 of one chunk per workgroup.  DECODE: from the coefficients m[vec][N], bit-reversed, to
-// work[vec][n].  Else from work[vec][n] to coefficients k and k + n of the bit-reversed position, times factor, rounded.
+// work[vec][n].  Else from work[vec][n] to coefficients k and k + n of the bit-reversed position, times factor, rounded
+// (store_coeffs).
 template <bool DECODE>
 __global__ __launch_bounds__(SF_T) void sfft_local_kernel(const cplx* tw, const double* m, cplx* work, double factor, i64* coeffs,
-                                                          int log_n) {
+                                                          int log_n, bool mirror) {
     __shared__ cplx buf[SF_C + SF_C / 8];
     const uint32_t n = 1u << (log_n - 1), base = blockIdx.x * SF_C, t = threadIdx.x;
     const size_t vec = blockIdx.y;
@@ -290,8 +300,7 @@ __global__ __launch_bounds__(SF_T) void sfft_local_kernel(const cplx* tw, const 
 #pragma unroll
         for (int i = 0; i < 4; i++) {
             const uint32_t k = __brev(base + 4 * t + i) >> (32 - (log_n - 1));
-            cv[k] = (i64)round(x[i].x * factor);
-            cv[k + n] = (i64)round(x[i].y * factor);
+            store_coeffs(cv, k, n, x[i], factor, mirror);
         }
     }
 }
@@ -357,7 +366,7 @@ static hipError_t launch_long(const cplx* tw, cplx* work, const double* re, cons
 // -> coeffs.
 template <bool DECODE>
 __global__ __launch_bounds__(SF_T) void sfft_small_kernel(const cplx* tw, const double* m, const cplx* work, const double* re,
-                                                          const double* im, int count, cplx* z, double factor, i64* coeffs) {
+                                                          const double* im, int count, cplx* z, double factor, i64* coeffs, bool mirror) {
     __shared__ cplx buf[512];
     const size_t vec = blockIdx.x;
     for (uint32_t r = threadIdx.x; r < 512; r += SF_T) {
@@ -388,8 +397,7 @@ __global__ __launch_bounds__(SF_T) void sfft_small_kernel(const cplx* tw, const 
             if ((int)r < count) z[vec * count + r] = buf[r];
         } else {
             const uint32_t k = __brev(r) >> 23;
-            coeffs[vec * 1024 + k] = (i64)round(buf[r].x * factor);
-            coeffs[vec * 1024 + k + 512] = (i64)round(buf[r].y * factor);
+            store_coeffs(coeffs + vec * 1024, k, 512, buf[r], factor, mirror);
         }
     }
 }
@@ -411,20 +419,21 @@ hipError_t launch_decode_fft(const void* tw, const double* m, int count, int n_p
     ProfScope prof__("decode_fft", st);
     if (log_n == 10) {
         hipLaunchKernelGGL(sfft_small_kernel<true>, dim3(n_pts), dim3(SF_T), 0, st, (const cplx*)tw, m, nullptr, nullptr, nullptr, count,
-                           (cplx*)z, 1.0, nullptr);
+                           (cplx*)z, 1.0, nullptr, false);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(sfft_local_kernel<true>, dim3(n / SF_C, n_pts), dim3(SF_T), 0, st, (const cplx*)tw, m, (cplx*)work, 1.0, nullptr, log_n);
+    hipLaunchKernelGGL(sfft_local_kernel<true>, dim3(n / SF_C, n_pts), dim3(SF_T), 0, st, (const cplx*)tw, m, (cplx*)work, 1.0, nullptr, log_n, false);
     return launch_long<true>((const cplx*)tw, (cplx*)work, nullptr, nullptr, count, (cplx*)z, n_pts, log_n, st);
 }
 
 // n_pts slot vectors -> coeffs[n_pts][N] = round(factor * (inverse transform)); values re/im[n_pts][count] at slots
-// 0 .. count-1 (slots null; may be pinned host memory) or at slots[count] (device); work: n_pts * n complex numbers
+// 0 .. count-1 (slots null; may be pinned host memory) or at slots[count] (device); work: n_pts * n complex numbers; mirror:
+// store_coeffs (im null)
 hipError_t launch_encode_fft(const void* tw, const double* re, const double* im, const uint32_t* slots, int count, int n_pts,
-                             double factor, void* work, i64* coeffs, int log_n, hipStream_t st) {
+                             double factor, void* work, i64* coeffs, int log_n, hipStream_t st, bool mirror) {
     DRY_RUN_RETURN();
     if (n_pts <= 0) return hipSuccess;
-    if (!tw || (!re && count) || !work || !coeffs || log_n < 10 || log_n > 16 || count < 0 || count > (1 << (log_n - 1)) || n_pts > 65535)
+    if (!tw || (mirror && im) || (!re && count) || !work || !coeffs || log_n < 10 || log_n > 16 || count < 0 || count > (1 << (log_n - 1)) || n_pts > 65535)
         return hipErrorInvalidValue;
     const uint32_t n = 1u << (log_n - 1);
     ProfScope prof__("encode_fft", st);
@@ -436,12 +445,12 @@ hipError_t launch_encode_fft(const void* tw, const double* re, const double* im,
     }
     if (log_n == 10) {
         hipLaunchKernelGGL(sfft_small_kernel<false>, dim3(n_pts), dim3(SF_T), 0, st, (const cplx*)tw, nullptr, (const cplx*)work, re, im,
-                           count, nullptr, factor, coeffs);
+                           count, nullptr, factor, coeffs, mirror);
         return hipGetLastError();
     }
     hipError_t e = launch_long<false>((const cplx*)tw, (cplx*)work, re, im, count, nullptr, n_pts, log_n, st);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(sfft_local_kernel<false>, dim3(n / SF_C, n_pts), dim3(SF_T), 0, st, (const cplx*)tw, nullptr, (cplx*)work, factor,
-                       coeffs, log_n);
+                       coeffs, log_n, mirror);
     return hipGetLastError();
 }

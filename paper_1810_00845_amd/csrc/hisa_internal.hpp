@@ -512,8 +512,8 @@ hipError_t launch_reduce_i64(const PrimeConst* primes, const i64* coeffs, u64* o
                              int log_n, hipStream_t st);
 
 // encode / decode
-hipError_t launch_encode(const double* cs, const double* sn, const uint32_t* g, const double* re, const double* im,
-                         int count, int n_pts, double factor, i64* coeffs, int log_n, hipStream_t st);
+hipError_t launch_encode(const double* cs, const uint32_t* g, const double* re, int count, int n_pts, double factor, i64* coeffs,
+                         int log_n, hipStream_t st);
 // piecewise-constant plaintexts: indicator encodings of nb slot sets (g[set_begin[b] .. set_begin[b+1]) lists 5^slot
 // mod 2N of set b), then coeffs[p] = round(factor * sum_b v[p][b] * basis[b])
 hipError_t launch_encode_basis(const double* cs, const uint32_t* g, const int* set_begin, int nb, double* basis, int log_n,
@@ -524,7 +524,7 @@ hipError_t launch_encode_combine(const double* basis, int nb, const double* v, i
 // twiddle j of the stage of length 2 half; slot values and z may lie in pinned host memory
 hipError_t launch_decode_fft(const void* tw, const double* m, int count, int n_pts, void* work, void* z, int log_n, hipStream_t st);
 hipError_t launch_encode_fft(const void* tw, const double* re, const double* im, const uint32_t* slots, int count, int n_pts,
-                             double factor, void* work, i64* coeffs, int log_n, hipStream_t st);
+                             double factor, void* work, i64* coeffs, int log_n, hipStream_t st, bool mirror = false);
 hipError_t launch_crt_to_double(const PrimeConst* primes, const u64* coeff_form, int limbs, const u64* garner_inv,
                                 const u64* garner_inv_sh, int L, double inv_scale, double* out, int n_pts, int log_n, hipStream_t st);
 hipError_t launch_crt_fp(const FpPrime* fprimes, const double* centred, int limbs, const double* garner_inv, int L, double inv_scale,

@@ -34,9 +34,17 @@ struct MacArgs {
     // out2[b * OC + oc] (x2_words apart)
     const u64* x2; u64 x2_tap_words, x2_words; u64* out2;
     // plain, optional: the w_count plaintexts in the limb-major form of pack_plain_kernel (w_count = 0: [plaintext][limb]
-    // rows of eight-byte words; w_packed bit 0: limb 0 has six-byte residues, bit 1: the limbs after it have)
+    // rows of eight-byte words)
     u64 w_count; int w_packed;
 };
+
+// The rows of a plan's plaintexts, N / 2 residues each: for every 128 residues their 128 low 32-bit words, then their 128 high
+// parts of 1, 2 or 4 bytes.  w_packed: the bytes of a high part on limb 0 + 8 x those on the limbs after it.
+__host__ __device__ __forceinline__ int packed_high(int w_packed, int limb) { return limb ? w_packed >> 3 : w_packed & 7; }
+__host__ __device__ __forceinline__ u64 packed_row_bytes(int hb, u64 n) { return (u64)(4 + hb) * (n / 2); }
+__host__ __device__ __forceinline__ u64 packed_limb_offset(int w_packed, int limb, u64 n, u64 cnt) {   // limb = l: all bytes
+    return limb ? (packed_row_bytes(w_packed & 7, n) + (u64)(limb - 1) * packed_row_bytes(w_packed >> 3, n)) * cnt : 0;
+}
 
 __device__ __forceinline__ int mac_prime(const MacArgs& g, int limb) { return (g.lq && limb >= g.lq) ? limb + g.gap : limb; }
 static inline int mac_polys(const MacArgs& g) { return g.polys == 1 ? 1 : 2; }
@@ -55,7 +63,7 @@ static inline bool mac_shape_ok(const MacArgs& g, int log_n) {
 struct MacExtents {
     u64 tap[MAX_TAPS];
     u64 out, x2, out2;
-    u64 w;   // plain, eight-byte rows only; 0: not known (weights that live outside the context's pool)
+    u64 w;   // plain only; 0: not known (weights that live outside the context's pool)
 };
 
 // The last word each buffer is asked for, by the indexing of the kernels below: tap t reads entries 0 .. batch*IC-1
@@ -76,7 +84,9 @@ static const char* mac_extents_fault(const MacArgs& g, const MacExtents& ex, int
             return "second input past its allocation";
         if (!g.out2 || ((u64)batch * g.OC - 1) * g.x2_words + e2 > ex.out2) return "second output past its allocation";
     }
-    if (ex.w && !g.w_count) {
+    if (ex.w && g.w_count) {
+        if (packed_limb_offset(g.w_packed, g.l, n, g.w_count) > 8 * ex.w) return "plaintexts past their allocation";
+    } else if (ex.w) {
         const u64 wl = g.w_words ? g.w_words : (u64)g.l * n;
         const u64 last = ((u64)g.n_taps * g.IC - 1) * g.w_stride_t + (u64)(g.OC - 1) * g.w_stride_oc;
         if (last * wl + (u64)g.l * n > ex.w) return "plaintexts past their allocation";
@@ -375,7 +385,7 @@ __global__ __launch_bounds__(256) void scalar_mac_mfma_kernel(const FpPrime* fpr
 // WITH_X2: the optional second input is present (a separate instantiation, so that the common form keeps its
 // straight-line loads)
 template <bool WITH_X2, int OCP>
-__device__ __forceinline__ void plain_mac_fp_body(const FpPrime* fprimes, const MacArgs& g, int log_n) {
+__global__ __launch_bounds__(NT) void plain_mac_fp_kernel(const FpPrime* fprimes, MacArgs g, int log_n) {
     const u64 n = (u64)1 << log_n;
     const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
     // the groups of outputs of one limb are neighbours in launch order (and land on the same XCD: the number of
@@ -445,99 +455,154 @@ __device__ __forceinline__ void plain_mac_fp_body(const FpPrime* fprimes, const 
     }
 }
 
-// The plaintexts of a plan: limb-major -- the rows that a group of outputs reads for one term lie side by side -- and
-// with six bytes per residue where the prime is below 2^48 (the row layout of pack_plain_kernel), a quarter less of the
-// bytes that bound this kernel.  FORM of the rows this block reads: 1 eight-byte residues, 2 six-byte residues (a
-// template argument, so that the loads of a term stay one straight line).  Two neighbouring coefficients per thread:
-// sixteen-byte loads of the ciphertext words and of eight-byte rows, eight + four bytes of a six-byte row.
-// Two-polynomial entries on the primes q_0.. only.
-template <int OCP, int FORM>
-__device__ __forceinline__ void plain_mac_fp_body2(const FpPrime* fprimes, const MacArgs& g, int log_n) {
+// The plaintexts of a plan encode real slot vectors: m(1/X) = m(X), and coefficient N - k is minus coefficient k (the encoders
+// of layers.hip make it so exactly), so the residue at index N - 1 - j, the value at the inverse root of index j, is the one
+// at j.  A plan keeps the first half of each row (pack_plain_kernel), and a thread takes four coefficients, two neighbours
+// and the two they mirror, for OCP outputs.  Rows are limb-major -- the rows that a group of outputs reads for one term lie
+// side by side -- with HB bytes above the low word of a residue.  Two-polynomial entries on the primes q_0.. only.
+// The plaintexts are read once and bound this kernel; the inputs are read once for each group of outputs and stay in the L2
+// (the groups of a limb are neighbours in launch order; the plaintexts pass it by).  Largest launch of the SqueezeNet-style
+// network (72 outputs x 32 terms, 9 limbs at N = 2^15): whole rows of six bytes a residue 928 us, half rows 562 (2.1 GB of
+// plaintexts, 0.34 GB written); all fourteen 3.98 -> 2.26 ms.
+// KS waves of a workgroup share out the terms of the same coefficients and add their sums up through LDS: a launch whose
+// waves do not fill the chip waits for one load after the other otherwise.
+template <int HB> struct HighPair;
+template <> struct HighPair<1> { typedef uint16_t type; };
+template <> struct HighPair<2> { typedef uint32_t type; };
+template <> struct HighPair<4> { typedef uint32_t type __attribute__((ext_vector_type(2))); };
+// the two residues of a pair from their low words and the high parts side by side
+__device__ __forceinline__ void join_pair(uint32_t l0, uint32_t l1, uint16_t h, double (&w)[2]) {
+    w[0] = fp_from_u64((u64)l0 | ((u64)(h & 0xFFu) << 32));
+    w[1] = fp_from_u64((u64)l1 | ((u64)((uint32_t)h >> 8) << 32));
+}
+__device__ __forceinline__ void join_pair(uint32_t l0, uint32_t l1, uint32_t h, double (&w)[2]) {
+    w[0] = fp_from_u64((u64)l0 | ((u64)(h & 0xFFFFu) << 32));
+    w[1] = fp_from_u64((u64)l1 | ((u64)(h >> 16) << 32));
+}
+__device__ __forceinline__ void join_pair(uint32_t l0, uint32_t l1, HighPair<4>::type h, double (&w)[2]) {
+    w[0] = fp_from_u64((u64)l0 | ((u64)h.x << 32));
+    w[1] = fp_from_u64((u64)l1 | ((u64)h.y << 32));
+}
+
+template <int OCP, int HB, int KS>
+__device__ __forceinline__ void plain_mac_half_body(const FpPrime* fprimes, const MacArgs& g, int log_n, double* part) {
     typedef unsigned long long ull2_t __attribute__((ext_vector_type(2)));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    typedef typename HighPair<HB>::type high_t;
     const u64 n = (u64)1 << log_n;
-    const u64 j = ((u64)blockIdx.x * NT + threadIdx.x) * 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const u64 j = (KS > 1 ? (u64)blockIdx.x * 64 + lane : (u64)blockIdx.x * blockDim.x + threadIdx.x) * 2, jm = n - 2 - j;
     const int limb = blockIdx.z;
     const int ocblocks = (g.OC + OCP - 1) / OCP;
     const int b = blockIdx.y / ocblocks, oc0 = (blockIdx.y % ocblocks) * OCP;
     const mac_cdouble_ptr fp = (mac_cdouble_ptr)(unsigned long long)&fprimes[limb].p;
     const double p = fp[0], pinv = fp[1];
     const u64 ln = (u64)g.l * n;
-    double a0[OCP][2], a1[OCP][2];
+    // canonical operands: a term can reach 0.9 p; normalised every four terms below 2^50 (4.1 p), every sixteen below 2^48
+    const int every = HB < 4 ? 16 : 4;
+    double acc[OCP][2][4];
 #pragma unroll
-    for (int o = 0; o < OCP; o++) a0[o][0] = a0[o][1] = a1[o][0] = a1[o][1] = 0.0;
-    int pending = 0;
-    const u64 lo_off = (j >> 7) * 768 + (j & 127) * 4, hi_off = (j >> 7) * 768 + 512 + (j & 127) * 2;
-    const u64 b0 = (g.w_packed & 1) ? 6 : 8, b1 = (g.w_packed & 2) ? 6 : 8, rb = (FORM == 2 ? 6 : 8) * n;
+    for (int o = 0; o < OCP; o++)
+#pragma unroll
+        for (int c = 0; c < 8; c++) acc[o][c >> 2][c & 3] = 0.0;
+    const u64 rb = packed_row_bytes(HB, n), lo_off = (j >> 7) * (512 + 128 * HB) + (j & 127) * 4,
+              hi_off = (j >> 7) * (512 + 128 * HB) + 512 + (j & 127) * HB;
     // term = (tap, input): the loads of the next term are issued before the arithmetic of the current one
-    const char* wlimb = (const char*)g.w + (limb ? b0 + (u64)(limb - 1) * b1 : 0) * n * g.w_count + (u64)oc0 * g.w_stride_oc * rb;
-    auto load = [&](int t, int ic, ull2_t& xb, ull2_t& xa, ull2_t (&wv)[OCP]) {
-        const u64* x = g.tap_base[t] + ((u64)b * g.IC + ic) * g.ct_words + (u64)limb * n + j;
-        xb = *(const ull2_t*)x;
-        xa = *(const ull2_t*)(x + ln);
+    const char* wlimb = (const char*)g.w + packed_limb_offset(g.w_packed, limb, n, g.w_count) + (u64)oc0 * g.w_stride_oc * rb;
+    auto load = [&](int t, int ic, ull2_t (&x)[4], u32x2 (&lo)[OCP], high_t (&hi)[OCP]) {
+        const u64* xp = g.tap_base[t] + ((u64)b * g.IC + ic) * g.ct_words + (u64)limb * n;
+        x[0] = *(const ull2_t*)(xp + j);
+        x[1] = *(const ull2_t*)(xp + jm);
+        x[2] = *(const ull2_t*)(xp + ln + j);
+        x[3] = *(const ull2_t*)(xp + ln + jm);
         const char* wp = wlimb + ((u64)t * g.IC + ic) * g.w_stride_t * rb;
 #pragma unroll
         for (int o = 0; o < OCP; o++) {
-            const int oo = oc0 + o < g.OC ? o : 0;
-            const char* row = wp + (u64)oo * g.w_stride_oc * rb;
-            if (FORM == 2) {
-                const u32x2 lo = *(const u32x2*)(row + lo_off);
-                const uint32_t hi = *(const uint32_t*)(row + hi_off);
-                wv[o].x = (u64)lo.x | ((u64)(hi & 0xFFFFu) << 32);
-                wv[o].y = (u64)lo.y | ((u64)(hi >> 16) << 32);
-            } else {
-                wv[o] = *(const ull2_t*)(row + 8 * j);
-            }
+            const char* row = wp + (u64)(oc0 + o < g.OC ? o : 0) * g.w_stride_oc * rb;
+            lo[o] = __builtin_nontemporal_load((const u32x2*)(row + lo_off));
+            hi[o] = __builtin_nontemporal_load((const high_t*)(row + hi_off));
         }
     };
-    ull2_t xb, xa, wv[OCP], nxb, nxa, nwv[OCP];
-    load(0, 0, xb, xa, wv);
-    for (int t = 0; t < g.n_taps; t++) {
-        for (int ic = 0; ic < g.IC; ic++) {
-            const bool more = ic + 1 < g.IC || t + 1 < g.n_taps;
-            if (more) load(ic + 1 < g.IC ? t : t + 1, ic + 1 < g.IC ? ic + 1 : 0, nxb, nxa, nwv);
-            const double fb[2] = {fp_from_u64(xb.x), fp_from_u64(xb.y)}, fa[2] = {fp_from_u64(xa.x), fp_from_u64(xa.y)};
+    ull2_t x[4], nx[4];
+    u32x2 lo[OCP], nlo[OCP];
+    high_t hi[OCP], nhi[OCP];
+    int t = 0, ic = KS > 1 ? wave : 0, pending = 0;
+    while (ic >= g.IC) { ic -= g.IC; t++; }
+    if (t < g.n_taps) {
+        load(t, ic, x, lo, hi);
+        for (;;) {
+            ic += KS;
+            while (ic >= g.IC) { ic -= g.IC; t++; }
+            const bool more = t < g.n_taps;
+            if (more) load(t, ic, nx, nlo, nhi);
+            double xf[2][4];       // coefficients j, j + 1 and their mirrors N - 1 - j, N - 2 - j
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                xf[q][0] = fp_from_u64(x[2 * q].x); xf[q][1] = fp_from_u64(x[2 * q].y);
+                xf[q][2] = fp_from_u64(x[2 * q + 1].y); xf[q][3] = fp_from_u64(x[2 * q + 1].x);
+            }
 #pragma unroll
             for (int o = 0; o < OCP; o++) {
-                const double wf[2] = {fp_from_u64(wv[o].x), fp_from_u64(wv[o].y)};
+                double wf[2];
+                join_pair(lo[o].x, lo[o].y, hi[o], wf);
 #pragma unroll
-                for (int c = 0; c < 2; c++) {
-                    a0[o][c] += fp_mulmod(fb[c], wf[c], p, pinv);
-                    a1[o][c] += fp_mulmod(fa[c], wf[c], p, pinv);
-                }
+                for (int q = 0; q < 2; q++)
+#pragma unroll
+                    for (int c = 0; c < 4; c++) acc[o][q][c] += fp_mulmod(xf[q][c], wf[c & 1], p, pinv);
             }
-            if (++pending == 4) {   // canonical operands: a term can reach 0.9 p, four of them on a normalised value 4.1 p
+            if (++pending == every) {
 #pragma unroll
                 for (int o = 0; o < OCP; o++)
 #pragma unroll
-                    for (int c = 0; c < 2; c++) { a0[o][c] = fp_norm(a0[o][c], p, pinv); a1[o][c] = fp_norm(a1[o][c], p, pinv); }
+                    for (int c = 0; c < 8; c++) acc[o][c >> 2][c & 3] = fp_norm(acc[o][c >> 2][c & 3], p, pinv);
                 pending = 0;
             }
-            if (more) {
-                xb = nxb; xa = nxa;
+            if (!more) break;
 #pragma unroll
-                for (int o = 0; o < OCP; o++) wv[o] = nwv[o];
-            }
+            for (int i = 0; i < 4; i++) x[i] = nx[i];
+#pragma unroll
+            for (int o = 0; o < OCP; o++) { lo[o] = nlo[o]; hi[o] = nhi[o]; }
+        }
+    }
+    if (KS > 1) {     // output `wave` of the group is this wave's to finish (KS = OCP)
+#pragma unroll
+        for (int o = 0; o < OCP; o++)
+#pragma unroll
+            for (int c = 0; c < 8; c++) part[((wave * OCP + o) * 8 + c) * 64 + lane] = fp_norm(acc[o][c >> 2][c & 3], p, pinv);
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < 8; c++) {
+            double s = 0.0;
+#pragma unroll
+            for (int k = 0; k < KS; k++) s += part[((k * OCP + wave) * 8 + c) * 64 + lane];
+            acc[0][c >> 2][c & 3] = s;
         }
     }
 #pragma unroll
-    for (int o = 0; o < OCP; o++) {
+    for (int i = 0; i < (KS > 1 ? 1 : OCP); i++) {
+        const int o = KS > 1 ? wave : i;
         if (oc0 + o < g.OC) {
-            u64* dst = g.out + ((u64)b * g.OC + oc0 + o) * g.ct_words + (u64)limb * n + j;
-            ull2_t r0, r1;
-            r0.x = fp_canonical(a0[o][0], p, pinv); r0.y = fp_canonical(a0[o][1], p, pinv);
-            r1.x = fp_canonical(a1[o][0], p, pinv); r1.y = fp_canonical(a1[o][1], p, pinv);
-            *(ull2_t*)dst = r0;
-            *(ull2_t*)(dst + ln) = r1;
+            u64* dst = g.out + ((u64)b * g.OC + oc0 + o) * g.ct_words + (u64)limb * n;
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                ull2_t r, m;
+                r.x = fp_canonical(acc[i][q][0], p, pinv); r.y = fp_canonical(acc[i][q][1], p, pinv);
+                m.y = fp_canonical(acc[i][q][2], p, pinv); m.x = fp_canonical(acc[i][q][3], p, pinv);
+                *(ull2_t*)(dst + q * ln + j) = r;
+                *(ull2_t*)(dst + q * ln + jm) = m;
+            }
         }
     }
 }
 
-template <bool WITH_X2, int OCP, bool PACKED = false>
-__global__ __launch_bounds__(NT) void plain_mac_fp_kernel(const FpPrime* fprimes, MacArgs g, int log_n) {
-    if (!PACKED) plain_mac_fp_body<WITH_X2, OCP>(fprimes, g, log_n);
-    else if (g.w_packed >> (blockIdx.z ? 1 : 0) & 1) plain_mac_fp_body2<OCP, 2>(fprimes, g, log_n);
-    else plain_mac_fp_body2<OCP, 1>(fprimes, g, log_n);
+template <int OCP, int KS>
+__global__ __launch_bounds__(KS > 1 ? 64 * KS : 128) void plain_mac_half_kernel(const FpPrime* fprimes, MacArgs g, int log_n) {
+    static_assert(KS == 1 || KS == OCP, "a wave finishes one output");
+    __shared__ double part[KS > 1 ? KS * OCP * 8 * 64 : 1];
+    const int hb = packed_high(g.w_packed, blockIdx.z);
+    if (hb == 1) plain_mac_half_body<OCP, 1, KS>(fprimes, g, log_n, part);
+    else if (hb == 2) plain_mac_half_body<OCP, 2, KS>(fprimes, g, log_n, part);
+    else plain_mac_half_body<OCP, 4, KS>(fprimes, g, log_n, part);
 }
 
 // analysis mode: a multiply-accumulate launch stands for one term per (image, output, tap, input)
@@ -602,24 +667,19 @@ static hipError_t launch_scalar_mac_mfma(hisa_ctx* ctx, const FpPrime* fprimes, 
     return hipErrorInvalidValue;
 }
 
-// Plaintexts [cnt][l][N] of eight-byte residues -> the limb-major form [l][cnt] of rows of N residues: a packed row holds,
-// for every 128 residues, their 128 low 32-bit words followed by their 128 high 16-bit words (768 bytes); an unpacked one
-// is as it was (packed: bit 0 limb 0, bit 1 the rest).
-// One launch converts the plaintexts first .. first + gridDim.z - 1.
-__global__ __launch_bounds__(NT) void pack_plain_kernel(const u64* src, char* dst, int l, int packed, u64 cnt, u64 first, int log_n) {
+// Plaintexts [cnt][l][N] of eight-byte residues -> the limb-major form [l][plaintext] of half rows (packed_high above).
+// One launch converts the cnt plaintexts at src, the first .. first + cnt - 1 of total.
+__global__ __launch_bounds__(NT) void pack_plain_kernel(const u64* src, char* dst, int l, int packed, u64 total, u64 first, int log_n) {
     const u64 n = (u64)1 << log_n;
-    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;
-    const int limb = blockIdx.y;
-    const u64 b0 = (packed & 1) ? 6 : 8, b1 = (packed & 2) ? 6 : 8, c = first + blockIdx.z;
-    const bool pk = packed >> (limb ? 1 : 0) & 1;
-    const u64 v = src[(c * l + limb) * n + j];
-    char* row = dst + (limb ? b0 + (u64)(limb - 1) * b1 : 0) * n * cnt + c * (pk ? 6 : 8) * n;
-    if (pk) {
-        *(uint32_t*)(row + (j >> 7) * 768 + (j & 127) * 4) = (uint32_t)v;
-        *(uint16_t*)(row + (j >> 7) * 768 + 512 + (j & 127) * 2) = (uint16_t)(v >> 32);
-    } else {
-        ((u64*)row)[j] = v;
-    }
+    const u64 j = (u64)blockIdx.x * NT + threadIdx.x;     // < N / 2
+    const int limb = blockIdx.y, hb = packed_high(packed, limb);
+    const u64 v = src[((u64)blockIdx.z * l + limb) * n + j];
+    char* at = dst + packed_limb_offset(packed, limb, n, total) + (first + blockIdx.z) * packed_row_bytes(hb, n) + (j >> 7) * (512 + 128 * hb);
+    ((uint32_t*)at)[j & 127] = (uint32_t)v;
+    at += 512;
+    if (hb == 1) ((uint8_t*)at)[j & 127] = (uint8_t)(v >> 32);
+    else if (hb == 2) ((uint16_t*)at)[j & 127] = (uint16_t)(v >> 32);
+    else ((uint32_t*)at)[j & 127] = (uint32_t)(v >> 32);
 }
 
 static hipError_t launch_plain_mac_fp(hisa_ctx* ctx, const FpPrime* fprimes, const MacArgs& g, int batch, int log_n, hipStream_t st) {
@@ -631,16 +691,26 @@ static hipError_t launch_plain_mac_fp(hisa_ctx* ctx, const FpPrime* fprimes, con
     if (g.x2 && (!g.out2 || g.lq <= 0 || g.lq > g.l || g.x2_words == 0)) return hipErrorInvalidValue;
     if (g.w_count) {   // limb-major plaintexts: of exactly the limbs walked, on the primes q_0.., no second input
         const u64 last = ((u64)g.n_taps * g.IC - 1) * g.w_stride_t + (u64)(g.OC - 1) * g.w_stride_oc;
-        if (g.w_words || g.x2 || g.lq || g.polys == 1 || (g.w_packed & ~3) || last >= g.w_count || log_n < 9)
+        auto high_ok = [](int hb) { return hb == 1 || hb == 2 || hb == 4; };
+        if (g.w_words || g.x2 || g.lq || g.polys == 1 || !high_ok(g.w_packed & 7) || !high_ok(g.w_packed >> 3) || last >= g.w_count || log_n < 9)
             return hipErrorInvalidValue;
+        const int ocp = 4, groups = batch * ((g.OC + ocp - 1) / ocp);
+        if (groups > 65535) return hipErrorInvalidValue;
+        ProfScope prof__("plain_mac_half_kernel", st);
+        // Waves if each takes all terms of its coefficients; 3072 are resident.  Terms shared out over four waves: 33 -> 17 us at
+        // 288 waves, 56 -> 36 at 960, 74 -> 47 at 1280, 45 -> 43 at 1664, 52 -> 54 at 2176, 81 -> 81 at 2304, 91 -> 132 at 5632.
+        const u64 waves = ((u64)1 << log_n) / 256 * groups * g.l;
+        if (waves <= 2048 && g.n_taps * g.IC >= 8)
+            hipLaunchKernelGGL((plain_mac_half_kernel<4, 4>), dim3((1u << log_n) / 256, groups, g.l), dim3(256), 0, st, fprimes, g, log_n);
+        else
+            hipLaunchKernelGGL((plain_mac_half_kernel<4, 1>), dim3((1u << log_n) / 512, groups, g.l), dim3(128), 0, st, fprimes, g, log_n);
+        return hipGetLastError();
     }
-    const int ocp = (g.OC >= 8 && !g.w_count) ? 8 : 4;   // two coefficients per thread: four outputs fill the registers
+    const int ocp = g.OC >= 8 ? 8 : 4;
     if ((u64)batch * ((g.OC + ocp - 1) / ocp) > 65535) return hipErrorInvalidValue;
-    // the limb-major forms take two coefficients per thread
-    dim3 grid((1u << log_n) / NT / (g.w_count ? 2 : 1), batch * ((g.OC + ocp - 1) / ocp), g.l);
+    dim3 grid((1u << log_n) / NT, batch * ((g.OC + ocp - 1) / ocp), g.l);
     ProfScope prof__("plain_mac_fp_kernel", st);
-    if (g.w_count) hipLaunchKernelGGL((plain_mac_fp_kernel<false, 4, true>), grid, dim3(NT), 0, st, fprimes, g, log_n);
-    else if (g.x2 && ocp == 8) hipLaunchKernelGGL((plain_mac_fp_kernel<true, 8>), grid, dim3(NT), 0, st, fprimes, g, log_n);
+    if (g.x2 && ocp == 8) hipLaunchKernelGGL((plain_mac_fp_kernel<true, 8>), grid, dim3(NT), 0, st, fprimes, g, log_n);
     else if (g.x2) hipLaunchKernelGGL((plain_mac_fp_kernel<true, 4>), grid, dim3(NT), 0, st, fprimes, g, log_n);
     else if (ocp == 8) hipLaunchKernelGGL((plain_mac_fp_kernel<false, 8>), grid, dim3(NT), 0, st, fprimes, g, log_n);
     else hipLaunchKernelGGL((plain_mac_fp_kernel<false, 4>), grid, dim3(NT), 0, st, fprimes, g, log_n);
@@ -885,7 +955,8 @@ static std::vector<uint32_t> tensor_slots(const hisa_tensor* t) {
 }
 
 // Encodes n_pts slot vectors that are non-zero only on `slots` (values[n_pts][slots.size()], host) into
-// NTT-form plaintexts out[n_pts][limbs][N] (device).
+// NTT-form plaintexts out[n_pts][limbs][N] (device).  Here and in encode_piecewise_batch coefficient N - k is minus
+// coefficient k, as for any real vector, exactly: only half of them are computed.
 static int encode_sparse_batch(hisa_ctx* ctx, const std::vector<uint32_t>& slots, const double* values, size_t n_pts,
                                double scale, int limbs, u64* out) {
     const size_t nnz = slots.size(), n = ctx->N;
@@ -915,7 +986,7 @@ static int encode_sparse_batch(hisa_ctx* ctx, const std::vector<uint32_t>& slots
             const int cnt = (int)std::min<size_t>(group, n_pts - p0);
             HIP_TRY(ctx, launch_encode_fft(ctx->d_sfft_tw, dv.as<double>() + p0 * nnz, nullptr, dg.as<uint32_t>(),
                                            (int)nnz, cnt, 2.0 * scale / (double)n, work.blk->ptr, co.as<i64>() + p0 * n,
-                                           (int)ctx->log_n, ctx->stream));
+                                           (int)ctx->log_n, ctx->stream, true));
             HIP_TRY(ctx, launch_reduce_i64(ctx->d_primes, co.as<i64>() + p0 * n, out + p0 * limbs * n, limbs, cnt,
                                            (int)ctx->log_n, ctx->stream));
         }
@@ -923,8 +994,8 @@ static int encode_sparse_batch(hisa_ctx* ctx, const std::vector<uint32_t>& slots
     // grid.y carries the plaintext index: stay below its limit
     for (size_t p0 = 0; !fft && p0 < n_pts; p0 += 32768) {
         const int cnt = (int)std::min<size_t>(32768, n_pts - p0);
-        HIP_TRY(ctx, launch_encode(ctx->d_cos, ctx->d_sin, dg.as<uint32_t>(), dv.as<double>() + p0 * nnz, nullptr, (int)nnz,
-                                   cnt, 2.0 * scale / (double)n, co.as<i64>() + p0 * n, (int)ctx->log_n, ctx->stream));
+        HIP_TRY(ctx, launch_encode(ctx->d_cos, dg.as<uint32_t>(), dv.as<double>() + p0 * nnz, (int)nnz, cnt,
+                                   2.0 * scale / (double)n, co.as<i64>() + p0 * n, (int)ctx->log_n, ctx->stream));
         HIP_TRY(ctx, launch_reduce_i64(ctx->d_primes, co.as<i64>() + p0 * n, out + p0 * limbs * n, limbs, cnt,
                                        (int)ctx->log_n, ctx->stream));
     }
@@ -1353,8 +1424,8 @@ struct ConvWeights {
     DevWeights* dw_zero = nullptr;
     Temp* pts_zero = nullptr;
     Temp* mask = nullptr;
-    u64 pt_count = 0;           // PLAIN, converted by pack_plain_weights: plaintexts in the limb-major form (0: as encoded)
-    int pt_packed = 0;          // which limbs have six-byte residues (MacArgs::w_packed)
+    u64 pt_count = 0;           // PLAIN, converted by pack_plain_weights: plaintexts in a plan's form (0: as encoded)
+    int pt_packed = 0;          // bytes of their high parts (MacArgs::w_packed)
     ~ConvWeights() { delete dw; delete pts; delete dw_zero; delete pts_zero; delete mask; }
 };
 
@@ -1835,27 +1906,37 @@ extern "C" int hisa_conv2d(hisa_ctx* ctx, const hisa_tensor* in, const double* w
 }
 
 // The plaintexts of a plan are written once and read at every application, and those reads bound the multiply-accumulate
-// launch: they are kept limb-major and, where the primes allow (below 2^48), with six bytes per residue.  (A direct
-// call reads its plaintexts once either way, so it keeps the words the encoder wrote.)
-static int pack_plain_weights(hisa_ctx* ctx, ConvWeights& cw, uint32_t l) {
-    if (!ctx->tabs.fp_ok || !cw.pts || cw.shared || cw.pt_count || l < 1) return HISA_OK;
-    const u64 lim = (u64)1 << 48, n = ctx->N, words = (u64)l * n;
-    int packed = ctx->mod[0] < lim ? 1 : 0;
-    bool rest = l > 1;
-    for (uint32_t k = 1; k < l; k++) rest = rest && ctx->mod[k] < lim;
-    if (rest) packed |= 2;
-    if (cw.pts->blk->bytes % (words * sizeof(u64))) return HISA_OK;
-    const u64 cnt = cw.pts->blk->bytes / (words * sizeof(u64));
-    const u64 bytes = (((packed & 1) ? 6 : 8) + (u64)(l - 1) * ((packed & 2) ? 6 : 8)) * n * cnt;
-    Temp* dst = new Temp(ctx, bytes);
-    if (!dst->ok()) { delete dst; return HISA_ERR_OOM; }
+// launch: a plan keeps half rows with as few high bytes as the primes allow.  (A direct call reads its plaintexts once
+// either way, so it keeps the words the encoder wrote.)
+static int plain_packing(const hisa_ctx* ctx, uint32_t l) {
+    auto high = [](u64 q) { return q < (u64)1 << 40 ? 1 : q < (u64)1 << 48 ? 2 : 4; };
+    int rest = 1;
+    for (uint32_t k = 1; k < l; k++) rest = std::max(rest, high(ctx->mod[k]));
+    return high(ctx->mod[0]) + 8 * rest;
+}
+
+// cnt plaintexts src[cnt][l][N] -> rows first .. first + cnt - 1 of the total in dst
+static int pack_plaintexts(hisa_ctx* ctx, const u64* src, size_t cnt, char* dst, u64 total, u64 first, uint32_t l, int packed) {
     for (u64 c0 = 0; c0 < cnt; c0 += 32768) {
         const u64 c = std::min<u64>(32768, cnt - c0);
-        hipLaunchKernelGGL(pack_plain_kernel, dim3((unsigned)(n / NT), l, (unsigned)c), dim3(NT), 0, ctx->stream,
-                           cw.pts->u(), dst->as<char>(), (int)l, packed, cnt, c0, (int)ctx->log_n);
+        hipLaunchKernelGGL(pack_plain_kernel, dim3(ctx->N / 2 / NT, l, (unsigned)c), dim3(NT), 0, ctx->stream, src + c0 * l * ctx->N, dst,
+                           (int)l, packed, total, first + c0, (int)ctx->log_n);
         const hipError_t e = hipGetLastError();
-        if (e != hipSuccess) { delete dst; return fail(ctx, HISA_ERR_HIP, "plaintext packing: %s", hipGetErrorString(e)); }
+        if (e != hipSuccess) return fail(ctx, HISA_ERR_HIP, "plaintext packing: %s", hipGetErrorString(e));
     }
+    return HISA_OK;
+}
+
+static int pack_plain_weights(hisa_ctx* ctx, ConvWeights& cw, uint32_t l) {
+    if (!ctx->tabs.fp_ok || !cw.pts || cw.shared || cw.pt_count || l < 1) return HISA_OK;
+    const u64 n = ctx->N, words = (u64)l * n;
+    const int packed = plain_packing(ctx, l);
+    if (cw.pts->blk->bytes % (words * sizeof(u64))) return HISA_OK;
+    const u64 cnt = cw.pts->blk->bytes / (words * sizeof(u64));
+    Temp* dst = new Temp(ctx, packed_limb_offset(packed, (int)l, n, cnt));
+    if (!dst->ok()) { delete dst; return HISA_ERR_OOM; }
+    const int rc = pack_plaintexts(ctx, cw.pts->u(), cnt, dst->as<char>(), cnt, 0, l, packed);
+    if (rc != HISA_OK) { delete dst; return rc; }
     delete cw.pts;     // stream-ordered: the pool may hand the block out again only to later work on this stream
     cw.pts = dst;
     cw.pt_count = cnt;
@@ -1956,16 +2037,15 @@ extern "C" int hisa_conv2d_apply_multi(hisa_ctx* ctx, const hisa_tensor* in, con
 // ---------------------------------------------------------------------------
 // fully connected
 // ---------------------------------------------------------------------------
-// pts: NTT-form plaintexts [OUTC][C][l][N] for outputs o0 .. o0+OUTC-1
-static int fc_chunk(hisa_ctx* ctx, const hisa_tensor* in, const BatchIn& bi, const u64* pts, double pt_scale, uint32_t OUTC,
-                    hisa_ct** outs) {
+// pts: NTT-form plaintexts [OUTC][C][l][N] for outputs o0 .. o0+OUTC-1, or (pt_count) all of them in a plan's form
+static int fc_chunk(hisa_ctx* ctx, const hisa_tensor* in, const BatchIn& bi, const u64* pts, uint32_t OUTC, hisa_ct** outs,
+                    u64 pt_count = 0, int pt_packed = 0) {
     const uint32_t B = in->batch, C = in->channels, l = in->cts[0]->limbs;
     MacArgs ma = {};
     ma.tap_base[0] = bi.base; ma.n_taps = 1; ma.IC = (int)C; ma.OC = (int)OUTC; ma.l = (int)l;
     ma.ct_words = 2 * (u64)l * ctx->N;
-    ma.w = pts; ma.w_stride_t = 1; ma.w_stride_oc = C;
+    ma.w = pts; ma.w_stride_t = 1; ma.w_stride_oc = C; ma.w_count = pt_count; ma.w_packed = pt_packed;
     ma.out = outs[0]->data;
-    (void)pt_scale;
     const hipError_t e = ctx->tabs.fp_ok ? launch_plain_mac_fp(ctx, ctx->tabs.fprimes, ma, (int)B, (int)ctx->log_n, ctx->stream)
                                          : launch_plain_mac(ctx, ctx->d_primes, ma, (int)B, (int)ctx->log_n, ctx->stream);
     return e == hipSuccess ? HISA_OK : mac_fail(ctx, e, "matmul");
@@ -2016,7 +2096,7 @@ static int fc_common(hisa_ctx* ctx, const hisa_tensor* in, const double* w, cons
             one.base = bi.base + (size_t)b * C * bi.stride;
             hisa_tensor view = *in;
             view.batch = 1;
-            rc = fc_chunk(ctx, &view, one, pts.u(), pt_scale, cnt, &outs[(size_t)b * OUT + o0]);
+            rc = fc_chunk(ctx, &view, one, pts.u(), cnt, &outs[(size_t)b * OUT + o0]);
         }
     }
     dev_release(ctx, bi.tmp);
@@ -2055,7 +2135,9 @@ struct hisa_fc_plan {
     uint32_t magic;
     uint32_t out_features, channels, height, width, h_stride, w_stride, offset, limbs;
     double pt_scale;
-    DevBlock* pts;   // [OUT][C][limbs][N], NTT form
+    DevBlock* pts;   // [OUT][C][limbs][N], NTT form, or (pt_count) a plan's half rows of them
+    u64 pt_count;
+    int pt_packed;
 };
 
 extern "C" int hisa_fc_prepare(hisa_ctx* ctx, const hisa_tensor* like, const double* w, uint32_t OUT, hisa_fc_plan** plan) {
@@ -2069,7 +2151,10 @@ extern "C" int hisa_fc_prepare(hisa_ctx* ctx, const hisa_tensor* like, const dou
     if (l < 2) return fail(ctx, HISA_ERR_DEPTH_EXHAUSTED, "fc needs a level to rescale into");
     const size_t n = ctx->N, hw = (size_t)like->height * like->width;
     const size_t pt_bytes = (size_t)C * l * n * sizeof(u64);
-    DevBlock* blk = dev_alloc(ctx, (size_t)OUT * pt_bytes);
+    const bool half = ctx->tabs.fp_ok;
+    const u64 total = half ? (u64)OUT * C : 0;
+    const int packed = half ? plain_packing(ctx, l) : 0;
+    DevBlock* blk = dev_alloc(ctx, half ? packed_limb_offset(packed, (int)l, n, total) : (size_t)OUT * pt_bytes);
     if (!blk) return HISA_ERR_OOM;
     const double pt_scale = (double)ctx->mod[l - 1];
     const std::vector<uint32_t> slots = plane_slots(like->height, like->width, like->h_stride, like->w_stride, like->offset);
@@ -2077,12 +2162,15 @@ extern "C" int hisa_fc_prepare(hisa_ctx* ctx, const hisa_tensor* like, const dou
     int rc = HISA_OK;
     for (uint32_t o0 = 0; o0 < OUT && rc == HISA_OK; o0 += OUTC) {
         const uint32_t cnt = std::min(OUTC, OUT - o0);
-        rc = encode_sparse_batch(ctx, slots, w + (size_t)o0 * C * hw, (size_t)cnt * C, pt_scale, (int)l,
-                                 (u64*)blk->ptr + (size_t)o0 * C * l * n);
+        Temp stage(ctx, half ? (size_t)cnt * pt_bytes : 8);
+        if (!stage.ok()) { rc = HISA_ERR_OOM; break; }
+        u64* dst = half ? stage.u() : (u64*)blk->ptr + (size_t)o0 * C * l * n;
+        rc = encode_sparse_batch(ctx, slots, w + (size_t)o0 * C * hw, (size_t)cnt * C, pt_scale, (int)l, dst);
+        if (rc == HISA_OK && half) rc = pack_plaintexts(ctx, dst, (size_t)cnt * C, (char*)blk->ptr, total, (u64)o0 * C, l, packed);
     }
     if (rc != HISA_OK) { dev_release(ctx, blk); return rc; }
     hisa_fc_plan* p = new hisa_fc_plan{HISA_MAGIC_FCPLAN, OUT, C, like->height, like->width, like->h_stride, like->w_stride,
-                                       like->offset, l, pt_scale, blk};
+                                       like->offset, l, pt_scale, blk, total, packed};
     *plan = p;
     return HISA_OK;
 }
@@ -2115,7 +2203,7 @@ extern "C" int hisa_fc_apply(hisa_ctx* ctx, const hisa_tensor* in, const hisa_fc
         one.base = bi.base + (size_t)b * C * bi.stride;
         hisa_tensor view = *in;
         view.batch = 1;
-        rc = fc_chunk(ctx, &view, one, (const u64*)plan->pts->ptr, plan->pt_scale, OUT, &outs[(size_t)b * OUT]);
+        rc = fc_chunk(ctx, &view, one, (const u64*)plan->pts->ptr, OUT, &outs[(size_t)b * OUT], plan->pt_count, plan->pt_packed);
     }
     dev_release(ctx, bi.tmp);
     if (rc != HISA_OK) {
@@ -2443,9 +2531,9 @@ extern "C" int hisa_tensor_to_hw_fixed(hisa_ctx* ctx, const hisa_tensor* in, con
 }
 
 // masks: NTT-form plaintexts [per][l][N] (needed when R > 1 and the input is not clean), pts: [groups][per][l'][N] with
-// l' = l - 1 after the masking multiply, else l.
+// l' = l - 1 after the masking multiply, else l; (pt_count) a plan's half rows of them.
 static int matmul_run(hisa_ctx* ctx, const hisa_tensor* in, const MatmulGeom& g, const u64* masks, double mask_scale,
-                      const u64* pts, double pt_scale, uint32_t OUT, hisa_tensor* out) {
+                      const u64* pts, double pt_scale, uint32_t OUT, hisa_tensor* out, u64 pt_count = 0, int pt_packed = 0) {
     const uint32_t B = in->batch, per = (uint32_t)t_per(in), groups = (OUT + g.R - 1) / g.R;
     uint32_t l = in->cts[0]->limbs;
     const size_t n_in = (size_t)B * per, n = ctx->N;
@@ -2482,7 +2570,7 @@ static int matmul_run(hisa_ctx* ctx, const hisa_tensor* in, const MatmulGeom& g,
         MacArgs ma = {};
         ma.tap_base[0] = bi.base; ma.n_taps = 1; ma.IC = (int)per; ma.OC = (int)groups; ma.l = (int)l;
         ma.ct_words = 2 * (u64)l * n;
-        ma.w = pts; ma.w_stride_t = 1; ma.w_stride_oc = per;
+        ma.w = pts; ma.w_stride_t = 1; ma.w_stride_oc = per; ma.w_count = pt_count; ma.w_packed = pt_packed;
         ma.out = outs[0]->data;
         hipError_t e = ctx->tabs.fp_ok ? launch_plain_mac_fp(ctx, ctx->tabs.fprimes, ma, (int)B, (int)ctx->log_n, ctx->stream)
                                        : launch_plain_mac(ctx, ctx->d_primes, ma, (int)B, (int)ctx->log_n, ctx->stream);
@@ -2507,8 +2595,10 @@ struct hisa_matmul_plan {
     uint32_t out_features, replicas;
     uint32_t channels, height, width, h_stride, w_stride, offset, clean, c_inner, c_stride, limbs;   // built for this input
     double pt_scale, mask_scale;
-    DevBlock* pts;     // [groups][per][l'][N]
+    DevBlock* pts;     // [groups][per][l'][N], or (pt_count) a plan's half rows of them
     DevBlock* masks;   // [per][l][N], or null
+    u64 pt_count;
+    int pt_packed;
 };
 
 extern "C" int hisa_matmul_plan_free(hisa_ctx* ctx, hisa_matmul_plan* plan) {
@@ -2523,10 +2613,11 @@ extern "C" int hisa_matmul_plan_free(hisa_ctx* ctx, hisa_matmul_plan* plan) {
 static hisa_matmul_plan* new_matmul_plan(const hisa_tensor* like, uint32_t OUT, uint32_t replicas) {
     return new hisa_matmul_plan{HISA_MAGIC_MMPLAN, OUT, replicas, like->channels, like->height, like->width, like->h_stride,
                                 like->w_stride, like->offset, like->clean, t_ci(like), like->c_stride, like->cts[0]->limbs,
-                                1.0, 1.0, nullptr, nullptr};
+                                1.0, 1.0, nullptr, nullptr, 0, 0};
 }
 
-static int matmul_build(hisa_ctx* ctx, const hisa_tensor* like, const double* w, uint32_t OUT, uint32_t replicas,
+// keep: the plaintexts are for more than one application (half rows)
+static int matmul_build(hisa_ctx* ctx, const hisa_tensor* like, const double* w, uint32_t OUT, uint32_t replicas, bool keep,
                         hisa_matmul_plan** plan_out) {
     if (!ctx || !w || !plan_out || OUT == 0) return fail(ctx, HISA_ERR_ARG, "bad argument");
     TRY(check_tensor(ctx, like));
@@ -2549,7 +2640,8 @@ static int matmul_build(hisa_ctx* ctx, const hisa_tensor* like, const double* w,
     }
     if (rc == HISA_OK) {
         p->pt_scale = (double)ctx->mod[l - 1];
-        p->pts = dev_alloc(ctx, (size_t)groups * per * l * n * sizeof(u64));
+        if (keep && ctx->tabs.fp_ok) { p->pt_count = (u64)groups * per; p->pt_packed = plain_packing(ctx, l); }
+        p->pts = dev_alloc(ctx, p->pt_count ? packed_limb_offset(p->pt_packed, (int)l, n, p->pt_count) : (size_t)groups * per * l * n * sizeof(u64));
         if (!p->pts) rc = HISA_ERR_OOM;
     }
     if (rc == HISA_OK) {
@@ -2570,7 +2662,11 @@ static int matmul_build(hisa_ctx* ctx, const hisa_tensor* like, const double* w,
                         memcpy(&vals[q * nnz + ((size_t)r * ci + c) * hw], w + ((size_t)(gi * g.R + r) * C + j * ci + c) * hw,
                                hw * sizeof(double));
             }
-            rc = encode_sparse_batch(ctx, rslots, vals.data(), cnt, p->pt_scale, (int)l, (u64*)p->pts->ptr + p0 * l * n);
+            Temp stage(ctx, p->pt_count ? cnt * l * n * sizeof(u64) : 8);
+            if (!stage.ok()) { rc = HISA_ERR_OOM; break; }
+            u64* dst = p->pt_count ? stage.u() : (u64*)p->pts->ptr + p0 * l * n;
+            rc = encode_sparse_batch(ctx, rslots, vals.data(), cnt, p->pt_scale, (int)l, dst);
+            if (rc == HISA_OK && p->pt_count) rc = pack_plaintexts(ctx, dst, cnt, (char*)p->pts->ptr, p->pt_count, p0, l, p->pt_packed);
         }
     }
     if (rc != HISA_OK) { hisa_matmul_plan_free(ctx, p); return rc; }
@@ -2581,7 +2677,7 @@ static int matmul_build(hisa_ctx* ctx, const hisa_tensor* like, const double* w,
 extern "C" int hisa_matmul_prepare(hisa_ctx* ctx, const hisa_tensor* like, const double* w, uint32_t OUT, uint32_t replicas,
                                    hisa_matmul_plan** plan_out) {
     if (t_analysis) return fail(ctx, HISA_ERR_ARG, "plans cannot be prepared during an analysis (no kernel runs)");
-    return matmul_build(ctx, like, w, OUT, replicas, plan_out);
+    return matmul_build(ctx, like, w, OUT, replicas, true, plan_out);
 }
 
 extern "C" int hisa_matmul_apply(hisa_ctx* ctx, const hisa_tensor* in, const hisa_matmul_plan* plan, hisa_tensor* out) {
@@ -2598,13 +2694,13 @@ extern "C" int hisa_matmul_apply(hisa_ctx* ctx, const hisa_tensor* in, const his
     MatmulGeom g;
     TRY(matmul_geom(ctx, in, plan->replicas, &g));
     return matmul_run(ctx, in, g, plan->masks ? (const u64*)plan->masks->ptr : nullptr, plan->mask_scale,
-                      (const u64*)plan->pts->ptr, plan->pt_scale, plan->out_features, out);
+                      (const u64*)plan->pts->ptr, plan->pt_scale, plan->out_features, out, plan->pt_count, plan->pt_packed);
 }
 
 extern "C" int hisa_matmul(hisa_ctx* ctx, const hisa_tensor* in, const double* w, uint32_t OUT, uint32_t replicas,
                            hisa_tensor* out) {
     hisa_matmul_plan* plan = nullptr;
-    TRY(matmul_build(ctx, in, w, OUT, replicas, &plan));
+    TRY(matmul_build(ctx, in, w, OUT, replicas, false, &plan));
     const int rc = hisa_matmul_apply(ctx, in, plan, out);
     hisa_matmul_plan_free(ctx, plan);
     return rc;

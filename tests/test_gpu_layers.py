@@ -178,6 +178,30 @@ def test_activation_pool_fc_chain_bit_exact():
     g.close()
 
 
+@pytest.mark.parametrize("log_n,bits,channels,outs,side", [
+    (12, [50, 40, 40], 3, 1, 6),       # terms below the line of shared-out terms; 1 output; sparse direct sums; high parts of 4 and 1 bytes
+    (12, [48, 45, 45], 9, 5, 17),      # terms shared out unevenly over the waves; a ragged group; the transform's encoding; 2 bytes
+    (13, [40, 50, 40, 40], 11, 69, 5), # more waves than the line; high parts of 1 and 4 bytes
+])
+def test_half_rows_of_a_plan(log_n, bits, channels, outs, side):
+    """A plan keeps the first half of each plaintext row: bit for bit the layers whose plaintexts are read whole."""
+    from paper_1810_00845_amd import hisa, synth
+    g = hisa.Context(log_n, bits, 2, 50, 77)
+    x = np.stack([synth.image(k, channels, side, side) for k in (1, 2)])
+    w = synth.fc_weights(3, outs, channels, side, side)
+    t = g.tensor_encrypt(x, 2.0 ** 40, len(bits))
+    g.gen_rot_keys(sorted(set(g.fc_rot_steps(t)) | set(g.matmul_rot_steps(t, 1))))
+    for whole, plan, apply, free in ((g.fc(t, w), g.fc_prepare(t, w), g.fc_apply, g.fc_plan_free),
+                                     (g.matmul(t, w, 1), g.matmul_prepare(t, w, 1), g.matmul_apply, g.matmul_plan_free)):
+        half = apply(t, plan)
+        assert len(half.cts) == len(whole.cts) > 0
+        for a, b in zip(whole.cts, half.cts):
+            assert np.array_equal(g.ct_export(a), g.ct_export(b)) and a.scale == b.scale
+        free(plan)
+    assert np.abs(g.tensor_decrypt(whole)[:, :, 0, 0] - plain_net.fc(x, w).reshape(2, outs)).max() <= 1e-3
+    g.close()
+
+
 def test_layer_error_paths():
     from paper_1810_00845_amd import hisa, synth
     g, o = make_pair(11, [45, 45], 2, 50, 5)
