@@ -1589,6 +1589,32 @@ int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add,
 
 bool fused_key_switch_available(const hisa_ctx* ctx) { return ctx->tabs.fp_ok && ctx->dnum <= 8; }
 
+// the automorphisms of n_steps real rotations whose keys are there
+static int rotation_elements(hisa_ctx* ctx, const int32_t* steps, int n_steps, u64* gs) {
+    for (int s = 0; s < n_steps; s++) {
+        gs[s] = galois_of(ctx, steps[s]);
+        if (gs[s] == 0) return fail(ctx, HISA_ERR_ARG, "rotation by a multiple of the slot count");
+        if (ctx->keys.find(gs[s]) == ctx->keys.end())
+            return fail(ctx, HISA_ERR_NO_KEY, "no rotation key for %d slots (galois element %llu)", steps[s], (unsigned long long)gs[s]);
+    }
+    return HISA_OK;
+}
+
+// What a kernel that forms the accumulators of rotations itself reads: the extended digits of B ciphertexts, transformed
+// (ext: rotation_digits_bytes of memory, [B][digits][l + K][N]), the rotations' keys and automorphisms
+size_t rotation_digits_bytes(const hisa_ctx* ctx, size_t B, int l) { return FpExt::ext_bytes(ctx, B, l, (int)ctx->K, (int)ctx->alpha); }
+int rotation_digits_fp(hisa_ctx* ctx, const u64* cts, u64 ct_bs, size_t B, int l, const int32_t* steps, int n_steps, IpSteps* st, double* ext) {
+    if (!fused_key_switch_available(ctx)) return fail(ctx, HISA_ERR_ARG, "no fused key-switch path for these parameters");
+    if (n_steps < 1 || n_steps > FP_MAX_STEPS) return fail(ctx, HISA_ERR_ARG, "bad rotation count");
+    u64 gs[FP_MAX_STEPS];
+    TRY(rotation_elements(ctx, steps, n_steps, gs));
+    for (int s = 0; s < n_steps; s++) { st->key[s] = ctx->keys.find(gs[s])->second.data; st->galois[s] = (uint32_t)gs[s]; }
+    Temp y(ctx, FpExt::y_bytes(ctx, B, l));
+    if (!y.ok()) return HISA_ERR_OOM;
+    FpExt x(ctx, l, (int)ctx->K, (int)ctx->alpha, y.as<double>(), ext);
+    return key_switch_modup_fp(ctx, cts + (size_t)l * ctx->N, ct_bs, B, x);
+}
+
 // The key-switch accumulators -- before the division by P -- of n_steps rotations of B ciphertexts (cts: [B][2][l][N],
 // ct_bs words apart): one decomposition + ModUp of c1, then per rotation the inner product with its key, gathered
 // through its automorphism.  acc: [n_steps][B][2][l + K][N].  Every amount must be a real rotation with its key present.
@@ -1601,12 +1627,7 @@ int rotation_accumulators_fp(hisa_ctx* ctx, const u64* cts, u64 ct_bs, size_t B,
     const size_t n = ctx->N;
     const int K = (int)ctx->K, L = (int)ctx->L, alpha = (int)ctx->alpha, total = (int)ctx->total, ext_limbs = l + K;
     std::vector<u64> gs(n_steps);
-    for (int s = 0; s < n_steps; s++) {
-        gs[s] = galois_of(ctx, steps[s]);
-        if (gs[s] == 0) return fail(ctx, HISA_ERR_ARG, "rotation by a multiple of the slot count");
-        if (ctx->keys.find(gs[s]) == ctx->keys.end())
-            return fail(ctx, HISA_ERR_NO_KEY, "no rotation key for %d slots (galois element %llu)", steps[s], (unsigned long long)gs[s]);
-    }
+    TRY(rotation_elements(ctx, steps, n_steps, gs.data()));
     FpExt x(ctx, B, l, K, alpha);
     if (!x.ok()) return HISA_ERR_OOM;
     const u64* c1 = cts + (size_t)l * n;

@@ -226,6 +226,9 @@ int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const i
 // The division by P and the divScalar by q_{l-1} in one base conversion: acc [B][2][l + K][N] (overwritten: the addend
 // [B][add_polys][l][N] is first folded in, times P) -> out [B][2][l - 1][N] = (acc + P add) / (q_{l-1} P), rounded as a
 // centred conversion rounds.  l >= 2.
+struct IpSteps;
+size_t rotation_digits_bytes(const hisa_ctx* ctx, size_t B, int l);
+int rotation_digits_fp(hisa_ctx* ctx, const u64* cts, u64 ct_bs, size_t B, int l, const int32_t* steps, int n_steps, IpSteps* st, double* ext);
 int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64* out);
 // Relinearisation of n three-polynomial ciphertexts ([3][l][N], stride words apart) whose division by P is taken
 // together with the divScalar by q_{l-1}: out [n][2][l - 1][N] = ((d0, d1) + KS_relin(d2)) / q_{l-1}.

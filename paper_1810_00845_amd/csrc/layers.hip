@@ -9,9 +9,8 @@
 #include <algorithm>
 #include <set>
 
-#include "hisa_internal.hpp"
+#include "fp_device.hpp"
 #include "modarith.hpp"
-#include "fparith.hpp"
 
 #define NT 256
 #define OCB 4
@@ -272,12 +271,29 @@ __global__ __launch_bounds__(NT) void plain_mac_kernel(const PrimeConst* primes,
 #define MT_OC 64
 #define MT_K 64
 #define MAC_DIGITS 7   // most digits of either factor
+#define MFMA_MIN_K 32
+#define MFMA_MAX_K 16384   // 7 K 2^14 must stay below 2^31
 typedef int v4i_t __attribute__((ext_vector_type(4)));
 
 // the seven signed base-256 digits of x (|x| < 2^55) in the low seven bytes: (x + B) ^ B with B = 0x80 in each of them
 __host__ __device__ __forceinline__ u64 balanced_digits(u64 x) {
     const u64 B = 0x0080808080808080ULL;
     return (x + B) ^ B;
+}
+
+// sum_s D_s 256^s mod p of result register r: three diagonals at a time are combined exactly in a double (below 2^48), then
+// up to five modular products with 2^(24 g) mod p
+template <int DIAGS>
+__device__ __forceinline__ u64 sum_diagonals(const v4i_t (&acc)[DIAGS], int r, mac_cdouble_ptr cg, double p, double pinv) {
+    double sum = 0.0;
+#pragma unroll
+    for (int gq = 0; 3 * gq < DIAGS; gq++) {
+        double G = (double)acc[3 * gq][r];
+        if (3 * gq + 1 < DIAGS) G = __builtin_fma((double)acc[3 * gq + 1][r], 256.0, G);
+        if (3 * gq + 2 < DIAGS) G = __builtin_fma((double)acc[3 * gq + 2][r], 65536.0, G);
+        sum += fp_mulmod(G, cg[gq], p, pinv);
+    }
+    return fp_canonical(sum, p, pinv);
 }
 
 template <int DA, int DB>
@@ -353,8 +369,6 @@ __global__ __launch_bounds__(256) void scalar_mac_mfma_kernel(const FpPrime* fpr
         __syncthreads();
     }
 
-    // sum_s D_s 256^s mod p: three diagonals at a time are combined exactly in a double (below 2^48), then five
-    // modular products with 2^(24 g) mod p
     const mac_cdouble_ptr fp = (mac_cdouble_ptr)(unsigned long long)&fprimes[mac_prime(g, limb)].p;
     const double p = fp[0], pinv = fp[1];
     const mac_cdouble_ptr cg = (mac_cdouble_ptr)(unsigned long long)(c3 + limb * 5);
@@ -363,16 +377,233 @@ __global__ __launch_bounds__(256) void scalar_mac_mfma_kernel(const FpPrime* fpr
 #pragma unroll
         for (int r = 0; r < 4; r++) {
             const int oc = oc0 + 4 * (lane >> 4) + r;
-            double sum = 0.0;
+            const u64 v = sum_diagonals<MAC_DIAGS>(acc[ct], r, cg, p, pinv);
+            if (oc < g.OC) g.out[((u64)b * g.OC + oc) * g.ct_words + (u64)pl * n + e0 + ct * 16 + (lane & 15)] = v;
+        }
+    }
+}
+
+// The same contraction for rotated inputs whose weighted sum is all that is wanted (one division by P per output): the X of
+// (tap, channel) -- an accumulator of the key switch, the inner product of the digits gathered through the tap's automorphism
+// with the tap's key -- is formed here, straight into the digit planes of the matrix operand, and never goes through memory.
+// An unrotated tap enters as P times its polynomial on the limbs of q (nothing on the special ones), as sigma(c0) does on
+// the first polynomial: the division by P turns both back, so the sums need no second part.
+//   block: 8 waves, 64 coefficients of a limb, both polynomials (they share the gathered digits), 64 outputs.  Wave w forms
+//   groups 2 w and 2 w + 1 of four channels of the 64 terms of a step -- channels are padded to a multiple of four, so a
+//   group has one tap: one gather index, one set of key words -- and multiplies for polynomial w / 4, outputs 16 (w % 4)...
+//   Two buffers of operand planes: the next step's are formed while the matrix cores work on this one's.
+//   Digits: x' = x - rint((x + delta) / p) p lies in [-p/2 - delta, p/2 - delta], which DB = 5 or 6 signed bytes hold for
+//   any p < 2^(8 DB) with delta = 0x80..80 of one byte less; + 0x80..80 of DB bytes it is an unsigned integer whose
+//   bytes are the digits xor 0x80.  DB = 7 (p < 2^50): the top digit is what is left above six bytes.
+// LeNet-medium's second convolution (24 rotations of 20 ciphertexts, 50 outputs, 10 + 4 limbs at N = 2^14): accumulators written
+// by one kernel and read by the other 782 + 850 us, the unrotated tap and its addition 98 + 58; this kernel 444 us for the nine
+// limbs of 40 bits and 307 for the five of 50.  Two waves a SIMD: the vector unit issues in 0.41 of the cycles, the matrix cores in
+// 0.22, the rest are waits for the gathered words.  Tried and taken back: all waves fetching ahead of their products (498 and 590: the words
+// beside the accumulators cost too many registers), one descriptor a digit with 32-bit offsets (476 and 317).  With seven digits of
+// weights it spills (695 and 655) and still is ahead.
+#define RM_DIGITS 3
+struct RotMacArgs {
+    const FpPrime* fprimes;
+    const double* ext; u64 ext_bs;      // [batch * IC][digits][le][N], transformed digits of the inputs' c1
+    const u64* ct; u64 ct_bs;           // [batch * IC]: c0, c1 (l limbs each)
+    const u64* pmod;                    // P mod q_i
+    int n_rot, n_zero, IC, G, digits, OC, l, le, L, total, alpha, K_pad, log_n;
+    uint32_t g_magic;                   // ceil(2^32 / G) for G > 1, G = groups of four channels of a tap
+    u64* out; u64 out_bs;               // [batch * OC][2][le][N]
+    const int8_t* wd;                   // [limb][MAC_DIGITS][64][K_pad]
+    const double* c3;
+    uint8_t limb[2 * HISA_MAX_Q];       // of blockIdx.y
+    IpSteps steps;
+};
+
+// four values' digits as bytes: w[d] = digit d of x[0..3]
+template <int DB>
+__device__ __forceinline__ void digit_words(const double (&x)[4], double p, double pinv, uint32_t (&w)[DB]) {
+    constexpr u64 B = DB == 5 ? 0x8080808080ull : 0x808080808080ull;
+    constexpr double delta = DB == 5 ? (double)0x80808080u : DB == 6 ? (double)0x8080808080ull : 0.0;
+    constexpr double magic = (DB == 7 ? 6755399441055744.0 : 4503599627370496.0) + (double)B;
+    uint32_t lo[4], hi[4];
 #pragma unroll
-            for (int gq = 0; 3 * gq < MAC_DIAGS; gq++) {
-                double G = (double)acc[ct][3 * gq][r];
-                if (3 * gq + 1 < MAC_DIAGS) G = __builtin_fma((double)acc[ct][3 * gq + 1][r], 256.0, G);
-                if (3 * gq + 2 < MAC_DIAGS) G = __builtin_fma((double)acc[ct][3 * gq + 2][r], 65536.0, G);
-                sum += fp_mulmod(G, cg[gq], p, pinv);
+    for (int i = 0; i < 4; i++) {
+        const double r = __builtin_fma(-__builtin_rint(__builtin_fma(x[i], pinv, delta * pinv)), p, x[i]);
+        const u64 t = (u64)__double_as_longlong(r + magic);
+        lo[i] = (uint32_t)t; hi[i] = (uint32_t)(t >> 32);
+    }
+    const uint32_t a = __builtin_amdgcn_perm(lo[1], lo[0], 0x05010400u), b = __builtin_amdgcn_perm(lo[3], lo[2], 0x05010400u);
+    const uint32_t c = __builtin_amdgcn_perm(lo[1], lo[0], 0x07030602u), d = __builtin_amdgcn_perm(lo[3], lo[2], 0x07030602u);
+    const uint32_t e = __builtin_amdgcn_perm(hi[1], hi[0], 0x05010400u), f = __builtin_amdgcn_perm(hi[3], hi[2], 0x05010400u);
+    w[0] = __builtin_amdgcn_perm(b, a, 0x05040100u) ^ 0x80808080u;
+    w[1] = __builtin_amdgcn_perm(b, a, 0x07060302u) ^ 0x80808080u;
+    w[2] = __builtin_amdgcn_perm(d, c, 0x05040100u) ^ 0x80808080u;
+    w[3] = __builtin_amdgcn_perm(d, c, 0x07060302u) ^ 0x80808080u;
+    w[4] = __builtin_amdgcn_perm(f, e, 0x05040100u) ^ 0x80808080u;
+    if (DB >= 6) w[DB >= 6 ? 5 : 0] = __builtin_amdgcn_perm(f, e, 0x07060302u) ^ 0x80808080u;
+    if (DB == 7) {
+        uint32_t top = 0;
+#pragma unroll
+        for (int i = 0; i < 4; i++) top |= ((((hi[i] >> 16) & 15u) - 8u) & 0xFFu) << (8 * i);
+        w[DB - 1] = top;
+    }
+}
+
+// A limb's blocks of 64 coefficients in an order in which a rotation by one slot leads to the neighbour.  Block j holds the
+// roots whose exponents are 2 bitrev(j) + 1 modulo 2 nb, nb = 2^log_nb blocks, and a rotation by s multiplies those by 5^s:
+// with +-5^t as the order, the blocks that an XCD works on at a time (t of an interval, both signs) are read by the taps of a
+// row of the filter one after the other as an interval that moves by one, so that the XCD's L2 holds what the next tap reads
+// (1.78 -> 0.90 GB from beyond it for the nine limbs above, 458 -> 444 us).
+__device__ __forceinline__ uint32_t rotation_order(uint32_t id, int log_nb) {
+    const uint32_t xcd = id & 7, q = id >> 3, mask = (2u << log_nb) - 1;
+    uint32_t t = (xcd << (log_nb - 4)) + (q >> 1), power = 5, u = 1;
+    for (int i = 0; i < log_nb - 1; i++, t >>= 1, power = power * power & mask)
+        if (t & 1) u = u * power & mask;
+    if (q & 1) u = (0u - u) & mask;
+    return __brev((u - 1) >> 1) >> (32 - log_nb);
+}
+
+template <int DA, int DB, int DIGITS>
+__global__ __launch_bounds__(512, 2) void rotated_mac_mfma_kernel(RotMacArgs g) {
+    constexpr int DIAGS = DA + DB - 1;
+    __shared__ uint32_t xd[2][2][DB][MT_K / 16][MT_E][4];      // [buffer][polynomial][digit][k / 16][coefficient][k % 16]
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int x = __builtin_amdgcn_readfirstlane((int)g.limb[blockIdx.y]), prime = prime_at(x, g.l, g.L);
+    const u64 n = (u64)1 << g.log_n;
+    const uint32_t block = rotation_order(blockIdx.x, g.log_n - 6), e = block * MT_E + lane;
+    const u64 first = (u64)blockIdx.z * g.IC;
+    const double p = as_const(&g.fprimes[prime].p)[0], pinv = as_const(&g.fprimes[prime].p)[1];
+    const bool on_q = x < g.l;
+    const int own = on_q ? x / g.alpha : -1;
+    // special limbs: zero times a word of limb 0
+    const double pm = on_q ? fp_from_u64(((const __attribute__((address_space(4))) u64*)(unsigned long long)g.pmod)[prime]) : 0.0;
+    const u64* c0 = g.ct + first * g.ct_bs + (on_q ? (u64)x * n : 0);
+    const u64* c1 = c0 + (u64)g.l * n;
+    const double* ext = g.ext + first * g.ext_bs + (u64)x * n;
+    // a digit's rows: of ext, or of the input polynomial (residues, not doubles) where the limb is the digit's own
+    const u64* dig[DIGITS];
+    u64 dig_bs[DIGITS];
+    uint32_t dig_or[DIGITS];
+    double dig_sub[DIGITS];
+#pragma unroll
+    for (int d = 0; d < DIGITS; d++) {
+        dig[d] = d == own ? c1 : (const u64*)ext + (u64)d * g.le * n;
+        dig_bs[d] = d == own ? g.ct_bs : g.ext_bs;
+        dig_or[d] = d == own ? 0x43300000u : 0u;
+        dig_sub[d] = d == own ? 4503599627370496.0 : 0.0;
+    }
+    // a word of a row (uniform base): the address costs the vector unit nothing
+    const uint32_t row_bytes = 8u << g.log_n;
+    auto word_at = [&](const void* row, uint32_t off) { return bload(make_rsrc(row, row_bytes), off, 0); };
+    auto fill = [&](int buf, int kc) {
+#pragma unroll
+        for (int gq = 0; gq < 2; gq++) {
+            SCHED_FENCE();          // one group's loads and sums at a time: both together spill
+            const uint32_t kg = (uint32_t)(kc >> 2) + 2 * wave + gq, tap = g.G == 1 ? kg : __umulhi(kg, g.g_magic);
+            const int ic0 = (int)(kg - tap * g.G) * 4;
+            double xs[2][4];
+            if ((int)tap < g.n_rot) {
+                const uint32_t at = galois_src_fp(e, g.steps.galois[tap], g.log_n) * 8;
+                const double* key = (const double*)g.steps.key[tap] + (u64)prime * n;
+                double k[DIGITS][2], f[4];
+                u64 v[DIGITS][4];
+#pragma unroll
+                for (int d = 0; d < DIGITS; d++)
+#pragma unroll
+                    for (int i = 0; i < 4; i++)      // padded channels have no weight
+                        v[d][i] = word_at(dig[d] + (u64)(uint32_t)min(ic0 + i, g.IC - 1) * dig_bs[d], at);
+#pragma unroll
+                for (int d = 0; d < DIGITS; d++)
+#pragma unroll
+                    for (int q = 0; q < 2; q++) k[d][q] = __longlong_as_double((long long)word_at(key + (u64)(2 * d + q) * g.total * n, 8 * e));
+#pragma unroll
+                for (int i = 0; i < 4; i++) f[i] = __longlong_as_double((long long)word_at(c0 + (u64)(uint32_t)min(ic0 + i, g.IC - 1) * g.ct_bs, at));
+#pragma unroll
+                for (int i0 = 0; i0 < 4; i0 += 2) {
+                    SCHED_FENCE();
+                    FpSum s[2][2];
+#pragma unroll
+                    for (int i = 0; i < 2; i++) s[0][i] = s[1][i] = FpSum{FP_SUM_BASE, 0.0};
+#pragma unroll
+                    for (int d = 0; d < DIGITS; d++) {
+#pragma unroll
+                        for (int i = 0; i < 2; i++) {
+                            const u64 raw = v[d][i0 + i];
+                            const double val = mk64((uint32_t)raw, (uint32_t)(raw >> 32) | dig_or[d]) - dig_sub[d];
+                            fp_sum_add(s[0][i], val, k[d][0]);
+                            fp_sum_add(s[1][i], val, k[d][1]);
+                        }
+                    }
+#pragma unroll
+                    for (int i = 0; i < 2; i++) {
+                        xs[0][i0 + i] = fp_sum_value(s[0][i], FP_SUM_BASE, p, pinv) +
+                                        fp_mulmod(fp_from_u64((u64)__double_as_longlong(f[i0 + i])), pm, p, pinv);
+                        xs[1][i0 + i] = fp_sum_value(s[1][i], FP_SUM_BASE, p, pinv);
+                    }
+                }
+            } else if (on_q && (int)tap < g.n_rot + g.n_zero) {
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    const u64 ic = (u64)(uint32_t)min(ic0 + i, g.IC - 1);
+                    xs[0][i] = fp_mulmod(fp_from_u64(word_at(c0 + ic * g.ct_bs, 8 * e)), pm, p, pinv);
+                    xs[1][i] = fp_mulmod(fp_from_u64(word_at(c1 + ic * g.ct_bs, 8 * e)), pm, p, pinv);
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < 4; i++) xs[0][i] = xs[1][i] = 0.0;
             }
-            if (oc < g.OC)
-                g.out[((u64)b * g.OC + oc) * g.ct_words + (u64)pl * n + e0 + ct * 16 + (lane & 15)] = fp_canonical(sum, p, pinv);
+#pragma unroll
+            for (int q = 0; q < 2; q++) {
+                uint32_t w[DB];
+                digit_words<DB>(xs[q], p, pinv, w);
+#pragma unroll
+                for (int d = 0; d < DB; d++) xd[buf][q][d][wave >> 1][lane][2 * (wave & 1) + gq] = w[d];
+            }
+        }
+    };
+
+    v4i_t acc[4][DIAGS];
+#pragma unroll
+    for (int ct = 0; ct < 4; ct++)
+#pragma unroll
+        for (int sdiag = 0; sdiag < DIAGS; sdiag++) acc[ct][sdiag] = (v4i_t){0, 0, 0, 0};
+    const int poly = wave >> 2, oc0 = (wave & 3) * 16;
+    const int8_t* wrow = g.wd + ((u64)x * MAC_DIGITS * MT_OC + oc0 + (lane & 15)) * g.K_pad + 16 * (lane >> 4);
+    auto multiply = [&](int buf, int kc) {
+        SCHED_FENCE();
+        v4i_t A[DA];
+#pragma unroll
+        for (int a = 0; a < DA; a++) A[a] = *(const v4i_t*)(wrow + (u64)a * MT_OC * g.K_pad + kc);
+#pragma unroll
+        for (int ct = 0; ct < 4; ct++) {
+            v4i_t Bv[DB];
+#pragma unroll
+            for (int bb = 0; bb < DB; bb++) Bv[bb] = *(const v4i_t*)xd[buf][poly][bb][lane >> 4][ct * 16 + (lane & 15)];
+#pragma unroll
+            for (int a = 0; a < DA; a++)
+#pragma unroll
+                for (int bb = 0; bb < DB; bb++)
+                    acc[ct][a + bb] = __builtin_amdgcn_mfma_i32_16x16x64_i8(A[a], Bv[bb], acc[ct][a + bb], 0, 0, 0);
+        }
+        SCHED_FENCE();
+    };
+    // the two waves of a SIMD take the halves of a step in opposite order: one's sums beside the other's matrix products
+    fill(0, 0);
+    __syncthreads();
+    int buf = 0;
+    for (int kc = 0; kc < g.K_pad; kc += MT_K, buf ^= 1) {
+        const bool more = kc + MT_K < g.K_pad;
+        if (poly) multiply(buf, kc);
+        if (more) fill(buf ^ 1, kc + MT_K);
+        if (!poly) multiply(buf, kc);
+        __syncthreads();
+    }
+    const mac_cdouble_ptr cg = (mac_cdouble_ptr)(unsigned long long)(g.c3 + x * 5);
+    u64* out = g.out + ((u64)poly * g.le + x) * n + block * MT_E;
+#pragma unroll
+    for (int ct = 0; ct < 4; ct++) {
+#pragma unroll
+        for (int r = 0; r < 4; r++) {
+            const int oc = oc0 + 4 * (lane >> 4) + r;
+            const u64 v = sum_diagonals<DIAGS>(acc[ct], r, cg, p, pinv);
+            if (oc < g.OC) out[((u64)blockIdx.z * g.OC + oc) * g.out_bs + ct * 16 + (lane & 15)] = v;
         }
     }
 }
@@ -665,6 +896,47 @@ static hipError_t launch_scalar_mac_mfma(hisa_ctx* ctx, const FpPrime* fprimes, 
     MFMA_CASE(3, 7); MFMA_CASE(4, 7); MFMA_CASE(5, 7); MFMA_CASE(6, 7); MFMA_CASE(7, 7);
 #undef MFMA_CASE
     return hipErrorInvalidValue;
+}
+
+// One launch per class of primes, by the digits that hold its residues.
+static hipError_t launch_rotated_mac(hisa_ctx* ctx, RotMacArgs& a, int da, int batch, hipStream_t st) {
+    DRY_RUN_RETURN();
+    const u64 n = (u64)1 << a.log_n, entries = (u64)batch * a.IC;
+    if (batch < 1 || batch > 65535 || a.n_rot < 1 || a.n_rot > FP_MAX_STEPS || a.n_zero < 0 || a.IC < 1 || a.OC < 1 || a.OC > MT_OC || a.digits < 1 ||
+        a.digits > RM_DIGITS || a.l < 1 || a.le > 2 * HISA_MAX_Q || a.G != (a.IC + 3) / 4 || a.K_pad % MT_K ||
+        a.K_pad < (a.n_rot + a.n_zero) * a.G * 4 || a.K_pad > MFMA_MAX_K || da < 1 || da > MAC_DIGITS || a.log_n < 10)
+        return hipErrorInvalidValue;
+    // every buffer holds what the kernel walks over
+    if (entries * a.ext_bs > dev_words_behind(ctx, a.ext) || a.ext_bs < (u64)a.digits * a.le * n || a.ct_bs < 2 * (u64)a.l * n ||
+        (entries - 1) * a.ct_bs + 2 * (u64)a.l * n > dev_words_behind(ctx, a.ct) || a.out_bs < 2 * (u64)a.le * n ||
+        (u64)batch * a.OC * a.out_bs > dev_words_behind(ctx, a.out) ||
+        (u64)a.le * MAC_DIGITS * MT_OC * a.K_pad > 8 * dev_words_behind(ctx, a.wd) || (u64)a.le * 5 > dev_words_behind(ctx, a.c3))
+        return hipErrorInvalidValue;
+    for (int s = 0; s < a.n_rot; s++)
+        if (!a.steps.key[s] || !a.steps.galois[s]) return hipErrorInvalidValue;
+    ProfScope prof__("rotated_mac_mfma_kernel", st);
+    for (int db = 5; db <= MAC_DIGITS; db++) {
+        int limbs = 0;
+        for (int x = 0; x < a.le; x++) {
+            const u64 q = ctx->mod[x < a.l ? x : a.L + (x - a.l)];
+            if ((q < (u64)1 << 40 ? 5 : q < (u64)1 << 48 ? 6 : 7) == db) a.limb[limbs++] = (uint8_t)x;
+        }
+        if (!limbs) continue;
+        const dim3 grid((unsigned)(n / MT_E), limbs, batch);
+#define ROT_MAC(A_, B_) do { \
+            if (a.digits == 1) hipLaunchKernelGGL((rotated_mac_mfma_kernel<A_, B_, 1>), grid, dim3(512), 0, st, a); \
+            else if (a.digits == 2) hipLaunchKernelGGL((rotated_mac_mfma_kernel<A_, B_, 2>), grid, dim3(512), 0, st, a); \
+            else hipLaunchKernelGGL((rotated_mac_mfma_kernel<A_, B_, 3>), grid, dim3(512), 0, st, a); \
+        } while (0)
+#define ROT_MAC_DA(B_) do { if (da <= 3) ROT_MAC(3, B_); else if (da <= 5) ROT_MAC(5, B_); else ROT_MAC(7, B_); } while (0)
+        if (db == 5) ROT_MAC_DA(5);
+        else if (db == 6) ROT_MAC_DA(6);
+        else ROT_MAC_DA(7);
+#undef ROT_MAC_DA
+#undef ROT_MAC
+        if (hipError_t e = hipGetLastError()) return e;
+    }
+    return hipSuccess;
 }
 
 // Plaintexts [cnt][l][N] of eight-byte residues -> the limb-major form [l][plaintext] of half rows (packed_high above).
@@ -1145,8 +1417,6 @@ static int conv_plan(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv_geom*
 // Fixed-point weights w[K][OC] (K = taps x input channels) on the device: residues per limb for the integer kernel;
 // when every prime is below 2^50 also centred doubles [l][K][OC] for the fp64 kernel and, for contractions long enough
 // to fill the matrix cores, signed base-256 digits [l][7][OC_pad][K_pad] with the constants 2^(24 g) mod q.
-#define MFMA_MIN_K 32
-#define MFMA_MAX_K 16384   // 7 K 2^14 must stay below 2^31
 struct DevWeights {
     size_t K, OC, K_pad, OC_pad;
     int da = MAC_DIGITS;   // signed base-256 digits the largest weight needs
@@ -1421,12 +1691,13 @@ struct ConvWeights {
     Temp* pts = nullptr;        // MASKED: the mask [l][N]; PLAIN: [T][OC][l][N]
     double w_scale = 1.0, pt_scale = 1.0;
     bool shared = false;
+    DevWeights* dw_all = nullptr;   // scalar weights of both, rotated first, channels padded to four: rotated_mac_mfma_kernel
     DevWeights* dw_zero = nullptr;
     Temp* pts_zero = nullptr;
     Temp* mask = nullptr;
     u64 pt_count = 0;           // PLAIN, converted by pack_plain_weights: plaintexts in a plan's form (0: as encoded)
     int pt_packed = 0;          // bytes of their high parts (MacArgs::w_packed)
-    ~ConvWeights() { delete dw; delete pts; delete dw_zero; delete pts_zero; delete mask; }
+    ~ConvWeights() { delete dw; delete dw_all; delete pts; delete dw_zero; delete pts_zero; delete mask; }
 };
 
 // taps (entries of plan.steps) with and without a rotation
@@ -1465,6 +1736,14 @@ static std::vector<int> ext_prime_list(const hisa_ctx* ctx, uint32_t l) {
     return p;
 }
 
+// What rotated_mac_mfma_kernel takes: the rotations of one launch, up to RM_DIGITS digits, one block of outputs (another would
+// form the operand again), and terms enough for the matrix cores.  The rest goes through accumulators in memory.
+static bool rotated_mac_fits(const hisa_ctx* ctx, const TapSplit& ts, uint32_t IC, uint32_t OC, uint32_t l) {
+    const size_t taps = ts.rot.size() + ts.zero.size(), digits = (l + ctx->alpha - 1) / ctx->alpha;
+    return ctx->tabs.fp_ok && !ts.rot.empty() && ts.rot.size() <= FP_MAX_STEPS && digits <= RM_DIGITS && OC <= MT_OC &&
+           taps * IC >= MFMA_MIN_K && taps * ((IC + 3) / 4 * 4) <= MFMA_MAX_K;
+}
+
 // scalar weights w_int[T][OC] -> device forms; shared: split by tap, the rotated ones on the l + K limbs
 static int build_scalar_weights(hisa_ctx* ctx, const int64_t* w_int, const ConvPlan& plan, uint32_t ICm, uint32_t OC, uint32_t l,
                                 bool shared, ConvWeights& cw) {
@@ -1475,6 +1754,18 @@ static int build_scalar_weights(hisa_ctx* ctx, const int64_t* w_int, const ConvP
         return upload_weight_residues(ctx, w_int, l, *cw.dw);
     }
     const TapSplit ts = split_taps(plan);
+    if (rotated_mac_fits(ctx, ts, ICm, OC, l)) {
+        const size_t IC4 = (ICm + 3) / 4 * 4, taps = ts.rot.size() + ts.zero.size();
+        std::vector<int64_t> all(taps * IC4 * OC, 0);
+        for (size_t k = 0; k < taps; k++) {
+            const size_t tap = k < ts.rot.size() ? ts.rot[k] : ts.zero[k - ts.rot.size()];
+            memcpy(all.data() + k * IC4 * OC, w_int + tap * ICm * OC, (size_t)ICm * OC * sizeof(int64_t));
+        }
+        cw.dw_all = new DevWeights(ctx, taps * IC4, OC, l + ctx->K);
+        if (!cw.dw_all->ok()) return HISA_ERR_OOM;
+        cw.dw_all->primes = ext_prime_list(ctx, l);
+        return upload_weight_residues(ctx, all.data(), l + ctx->K, *cw.dw_all);
+    }
     const std::vector<int64_t> wr = pick_taps(w_int, ts.rot, ICm, OC), wz = pick_taps(w_int, ts.zero, ICm, OC);
     cw.dw = new DevWeights(ctx, ts.rot.size() * ICm, OC, l + ctx->K);
     if (!cw.dw->ok()) return HISA_ERR_OOM;
@@ -1748,6 +2039,28 @@ static hipError_t shared_mac(hisa_ctx* ctx, MacArgs ma, const DevWeights* dw, co
     return launch_scalar_mac_fp(ctx, ctx->tabs.fprimes, ma, dw->resf.as<double>(), batch, (int)ctx->log_n, ctx->stream);
 }
 
+// E[b][oc] = the weighted sum of the accumulators of the inputs' rotations and P times that of the unrotated taps, in one pass
+// over the digits (rotated_mac_mfma_kernel)
+static int rotated_sums(hisa_ctx* ctx, const BatchIn& bi, size_t n_zero, const std::vector<int32_t>& steps, const DevWeights& dw, uint32_t B,
+                        uint32_t IC, uint32_t OC, int l, u64* out) {
+    const size_t n = ctx->N, nct = (size_t)B * IC;
+    Temp ext(ctx, rotation_digits_bytes(ctx, nct, l));
+    if (!ext.ok()) return HISA_ERR_OOM;
+    RotMacArgs a = {};
+    TRY(rotation_digits_fp(ctx, bi.base, bi.stride, nct, l, steps.data(), (int)steps.size(), &a.steps, ext.as<double>()));
+    a.fprimes = ctx->tabs.fprimes;
+    a.l = l; a.le = l + (int)ctx->K; a.L = (int)ctx->L; a.total = (int)ctx->total; a.alpha = (int)ctx->alpha; a.log_n = (int)ctx->log_n;
+    a.digits = (l + a.alpha - 1) / a.alpha;
+    a.ext = ext.as<double>(); a.ext_bs = (u64)a.digits * a.le * n;
+    a.ct = bi.base; a.ct_bs = bi.stride; a.pmod = ctx->d_pmod;
+    a.n_rot = (int)steps.size(); a.n_zero = (int)n_zero; a.IC = (int)IC; a.OC = (int)OC;
+    a.G = (int)((IC + 3) / 4); a.g_magic = (uint32_t)((((u64)1 << 32) + a.G - 1) / a.G);
+    a.K_pad = (int)dw.K_pad; a.wd = (const int8_t*)dw.digits.blk->ptr; a.c3 = dw.c3.as<double>();
+    a.out = out; a.out_bs = 2 * (u64)a.le * n;
+    const hipError_t e = launch_rotated_mac(ctx, a, dw.da, (int)B, ctx->stream);
+    return e == hipSuccess ? HISA_OK : fail(ctx, e == hipErrorInvalidValue ? HISA_ERR_ARG : HISA_ERR_HIP, "conv: %s", hipGetErrorString(e));
+}
+
 // The convolution with ONE division by P per output ciphertext (the rotations of a convolution are only ever used
 // inside its sums): the inputs' c1 is decomposed and raised once, every rotated tap contributes its key-switch
 // accumulators -- on l + K limbs, before the division -- times its weight taken on those limbs (E), and sigma(c0)
@@ -1786,15 +2099,16 @@ static int conv_run_shared(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv
     // scalar weights: sigma(c0) enters the first accumulators times P (rotation_accumulators_fp), so the weighted sum
     // of the accumulators is all there is; plaintext weights keep sigma(c0) apart (it rides along in their one pass
     // over the plaintexts, on l limbs instead of l + K)
-    const bool fold_c0 = !plain;
-    Temp acc(ctx, S * nct * acc_bs * sizeof(u64));      // [S][nct][2][l + K][N]
+    const bool fold_c0 = !plain, in_one = cw.dw_all != nullptr;
+    Temp acc(ctx, in_one ? 8 : S * nct * acc_bs * sizeof(u64));      // [S][nct][2][l + K][N]
     Temp r0(ctx, (fold_c0 ? 1 : S * nct * lw) * sizeof(u64));   // sigma(c0): [S][nct][l][N]
-    Temp E(ctx, n_out * acc_bs * sizeof(u64)), Q0(ctx, n_out * lw * sizeof(u64)), Z(ctx, n_out * 2 * lw * sizeof(u64));
+    Temp E(ctx, n_out * acc_bs * sizeof(u64)), Q0(ctx, (plain ? n_out * lw : 1) * sizeof(u64)), Z(ctx, (in_one ? 1 : n_out * 2 * lw) * sizeof(u64));
     std::vector<hisa_ct*> outs(n_out, nullptr);
     if (rc == HISA_OK && !(acc.ok() && r0.ok() && E.ok() && Q0.ok() && Z.ok())) rc = HISA_ERR_OOM;
     std::vector<int32_t> rot_steps;
     for (int t : ts.rot) rot_steps.push_back(plan.steps[t]);
-    if (rc == HISA_OK) rc = rotation_accumulators_fp(ctx, bi.base, bi.stride, nct, (int)l, rot_steps.data(), (int)S, acc.u(), fold_c0);
+    if (rc == HISA_OK && in_one) rc = rotated_sums(ctx, bi, ts.zero.size(), rot_steps, *cw.dw_all, B, IC, OCm, (int)l, E.u());
+    else if (rc == HISA_OK) rc = rotation_accumulators_fp(ctx, bi.base, bi.stride, nct, (int)l, rot_steps.data(), (int)S, acc.u(), fold_c0);
     if (!fold_c0) {   // sigma(c0) for every rotated tap, as many taps per launch as the grid allows
         const size_t per_launch = std::max<size_t>(1, std::min<size_t>(GALOIS_TAB_MAX, 65535 / nct));
         for (size_t k0 = 0; k0 < S && rc == HISA_OK; k0 += per_launch) {
@@ -1818,7 +2132,7 @@ static int conv_run_shared(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv
     if (rc == HISA_OK)
         rc = alloc_ct_batch(ctx, n_out, 2, one_division ? l - 1 : l, one_division ? mac_scale / (double)ctx->mod[l - 1] : mac_scale,
                             outs.data());
-    if (rc == HISA_OK) {
+    if (rc == HISA_OK && !in_one) {
         hipError_t e;
         MacArgs ma = {};
         ma.IC = (int)IC; ma.OC = (int)OCm;
@@ -1849,8 +2163,9 @@ static int conv_run_shared(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv
                               ctx->stream);
         if (e != hipSuccess) rc = mac_fail(ctx, e, "conv");
     }
-    if (rc == HISA_OK && one_division) rc = moddown_rescale_fp(ctx, E.u(), n_out, (int)l, Z.u(), 2 * lw, 2, outs[0]->data);
-    else if (rc == HISA_OK) rc = moddown_add_fp(ctx, E.u(), n_out, (int)l, Z.u(), 2 * lw, 2, outs[0]->data);
+    const u64* unrotated = in_one ? nullptr : Z.u();
+    if (rc == HISA_OK && one_division) rc = moddown_rescale_fp(ctx, E.u(), n_out, (int)l, unrotated, 2 * lw, 2, outs[0]->data);
+    else if (rc == HISA_OK) rc = moddown_add_fp(ctx, E.u(), n_out, (int)l, unrotated, 2 * lw, 2, outs[0]->data);
     if (rc == HISA_OK && g->mode == HISA_CONV_MASKED) {
         hipError_t e = launch_mul_plain(ctx->d_primes, outs[0]->data, cw.mask->u(), outs[0]->data, (int)l, 2, n_out, 2 * lw, 2 * lw,
                                         (int)ctx->log_n, ctx->stream);

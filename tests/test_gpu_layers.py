@@ -798,6 +798,32 @@ def test_layout_switches_bit_exact():
         g.close()
 
 
+@pytest.mark.parametrize("bits,dnum,channels,outs,filt,same,batch", [
+    ([45, 38, 38], 3, 4, 64, 3, True, 1),       # one group of channels a tap, all outputs of a block; residues of 5, 6 and 7 digits
+    ([50, 46, 44], 2, 7, 1, 3, False, 2),       # padded channels, one output, two key digits, two images
+    ([40, 40], 1, 2, 3, 5, True, 1),            # channels padded to twice their number, one key digit
+    ([50, 50], 2, 33, 5, 1, False, 1),          # no rotation: the other schedule
+    ([50, 50], 2, 9, 2, 2, False, 1),           # weights of seven digits; the first tap unrotated
+])
+def test_rotated_sums_on_the_matrix_cores(bits, dnum, channels, outs, filt, same, batch):
+    """The convolution whose matrix operand is formed from the key switch's digits, bit for bit against the oracle."""
+    from oracle import layers
+    from paper_1810_00845_amd import synth
+    g, o = make_pair(12, bits, dnum, 50, 5)
+    x = np.stack([synth.image(20 + k, channels, 4, 5) for k in range(batch)])
+    gt, ot = both_tensors(g, o, x, 2.0 ** 36, len(bits), h_stride=9, offset=20)
+    steps = g.conv2d_rot_steps(gt, filt, filt, pad_same=same)
+    g.gen_rot_keys(steps); o.gen_rot_keys(steps)
+    w = synth.conv_weights(30, filt, filt, channels, outs)
+    for fused in (False, True):
+        g.set_fused_rescale(fused)
+        oout, ints = layers.conv2d(o, ot, w, mode=layers.CONV_SCALAR, shared_moddown=True, fused_rescale=fused, pad_same=same)
+        gout = g.conv2d_fixed(gt, ints["w_int"], ints["w_scale"], None, 1.0, outs, filt, filt, mode=layers.CONV_SCALAR, shared_moddown=True,
+                              pad_same=same)
+        same_tensor(g, o, gout, oout)
+    g.close()
+
+
 def test_shared_moddown_convolutions_bit_exact():
     """The convolution with one division by P per output ciphertext through the C ABI against the oracle's
     SharedModDown schedule, bit for bit: HW-tiled with scalar weights (literal and masked; short contraction on the
