@@ -168,7 +168,7 @@ __global__ __launch_bounds__(NT) void scalar_mac_kernel(const PrimeConst* primes
 // (centred doubles) are the same for every thread and arrive through scalar loads.
 // Range: a term is at most 0.7 p in magnitude, eight of them on top of a normalised value stay below 6.1 p < 2^53.
 #define OCF 16
-#define ICU 4
+#define MACU 8
 typedef const __attribute__((address_space(4))) double* mac_cdouble_ptr;
 // wf: [l][T][OC] (the OCF weights of one x value are contiguous: wide scalar loads)
 __global__ __launch_bounds__(NT) void scalar_mac_fp_kernel(const FpPrime* fprimes, MacArgs g, const double* wf, int log_n) {
@@ -183,40 +183,42 @@ __global__ __launch_bounds__(NT) void scalar_mac_fp_kernel(const FpPrime* fprime
     double acc[OCF];
 #pragma unroll
     for (int o = 0; o < OCF; o++) acc[o] = 0.0;
-    int pending = 0;
-    for (int t = 0; t < g.n_taps; t++) {
-        const u64* x = g.tap_base[t] + (u64)b * g.IC * g.ct_words + (u64)pl * n + j;
-        const mac_cdouble_ptr w =
-            (mac_cdouble_ptr)(unsigned long long)(wf + ((u64)limb * g.n_taps + t) * g.IC * g.OC + oc0);
-        for (int ic0 = 0; ic0 < g.IC; ic0 += ICU) {
-            // the loads of ICU input channels first, then their arithmetic
-            double xv[ICU];
+    // terms k = (tap, channel) in groups of MACU, the next group's loads ahead of this one's arithmetic (past the end the last term's)
+    const int K = g.n_taps * g.IC;
+    const u64 off = (u64)b * g.IC * g.ct_words + (u64)pl * n + j;
+    const mac_cdouble_ptr w = (mac_cdouble_ptr)(unsigned long long)(wf + (u64)limb * K * g.OC + oc0);
+    int t = 0, ic = 0;
+    u64 xn[MACU];
+    auto load = [&]() {
 #pragma unroll
-            for (int u = 0; u < ICU; u++) {
-                const int ic = ic0 + u < g.IC ? ic0 + u : g.IC - 1;
-                xv[u] = fp_from_u64(x[(u64)ic * g.ct_words]);
-            }
+        for (int u = 0; u < MACU; u++) {
+            xn[u] = g.tap_base[t][off + (u64)ic * g.ct_words];
+            if (ic + 1 < g.IC) ic++;
+            else if (t + 1 < g.n_taps) { ic = 0; t++; }
+        }
+    };
+    load();
+    for (int k0 = 0; k0 < K; k0 += MACU) {
+        double xv[MACU];
 #pragma unroll
-            for (int u = 0; u < ICU; u++) {
-                if (ic0 + u < g.IC) {
-                    const mac_cdouble_ptr wi = w + (u64)(ic0 + u) * g.OC;
-                    if (full) {
+        for (int u = 0; u < MACU; u++) xv[u] = fp_from_u64(xn[u]);
+        if (k0 + MACU < K) load();
 #pragma unroll
-                        for (int o = 0; o < OCF; o++) acc[o] += fp_mulmod(xv[u], wi[o], p, pinv);
-                    } else {
+        for (int u = 0; u < MACU; u++) {
+            if (k0 + u < K) {
+                const mac_cdouble_ptr wi = w + (u64)(k0 + u) * g.OC;
+                if (full) {
 #pragma unroll
-                        for (int o = 0; o < OCF; o++)
-                            if (oc0 + o < g.OC) acc[o] += fp_mulmod(xv[u], wi[o], p, pinv);
-                    }
+                    for (int o = 0; o < OCF; o++) acc[o] += fp_mulmod(xv[u], wi[o], p, pinv);
+                } else {
+#pragma unroll
+                    for (int o = 0; o < OCF; o++)
+                        if (oc0 + o < g.OC) acc[o] += fp_mulmod(xv[u], wi[o], p, pinv);
                 }
             }
-            pending += ICU;
-            if (pending >= 8) {
-#pragma unroll
-                for (int o = 0; o < OCF; o++) acc[o] = fp_norm(acc[o], p, pinv);
-                pending = 0;
-            }
         }
+#pragma unroll
+        for (int o = 0; o < OCF; o++) acc[o] = fp_norm(acc[o], p, pinv);
     }
 #pragma unroll
     for (int o = 0; o < OCF; o++)
