@@ -883,22 +883,26 @@ __device__ __forceinline__ void wide_rows_forward(const ConvertArgs& a, int task
 }
 
 // A workgroup per (limb x, row, entry), four waves per digit.  Each four leave their digit's row in LDS; the first two take a
-// polynomial each from there on: sums, and the inverse rows of a source or the division's rows, as rows_inner does.
+// polynomial each from there on: sums, and the inverse rows of a source or the division's rows, as rows_inner does.  split: a workgroup
+// per polynomial too, for launches that leave compute units idle (the rule stands at the launch): the digits' rows are transformed for
+// either, and what follows them is left to four waves that have waited with keys and twiddles in registers (with four digits, to those of
+// the first).
 template <int K3, int MODE>
 __device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const InnerArgs& g, int task, double* lds) {
     const uint32_t t = threadIdx.x & (WIDE_NT - 1);
     const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WIDE_NT));
-    const uint32_t unit = (uint32_t)task / a.n_entries;
-    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t entry = (uint32_t)task >> g.split, unit = entry / a.n_entries;
+    const u64 b = entry - unit * a.n_entries;
+    const int summer = a.n_digits < WIDE_DIGITS ? a.n_digits : 0, poly = g.split ? task & 1 : part;
     const uint32_t row = unit & ((1u << K3) - 1);
     const int x = g.x_end - 1 - (int)(unit >> K3);
     const int prime = prime_at(x, a.l, a.L);
     const Modulus q = modulus(a.fprimes, prime);
     constexpr u64 n = (u64)1 << (10 + K3);
-    const bool sums = part < 2, source = MODE == FP_INV_D_TO_Y && x >= g.n_acc, mine = part < a.n_digits;
+    const bool sums = g.split ? part == summer : part < 2, source = MODE == FP_INV_D_TO_Y && x >= g.n_acc, mine = part < a.n_digits;
     const bool own = mine && x >= a.dg[part].own_lo && x < a.dg[part].own_lo + a.dg[part].own_n;
-    const bool with_add = sums && x < a.l && part < g.add_polys;
-    const u64 out_limb = source ? (b * 2 + part) * (u64)(a.ext_limbs - g.n_acc) + (u64)(x - g.n_acc) : (b * 2 + part) * (u64)g.n_acc + (u64)x;
+    const bool with_add = sums && x < a.l && poly < g.add_polys;
+    const u64 out_limb = source ? (b * 2 + poly) * (u64)(a.ext_limbs - g.n_acc) + (u64)(x - g.n_acc) : (b * 2 + poly) * (u64)g.n_acc + (u64)x;
     double* dst_p = (source ? g.down : MODE == FP_FWD_CONV_SUB ? (double*)g.out : g.acc) + (sums ? out_limb : 0) * n + row * 1024u;
     const rsrc_t dst = make_rsrc(dst_p, 8192u);
     double v[4], k[WIDE_DIGITS][4], add[4], div[4];
@@ -911,12 +915,14 @@ __device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const Inne
 #pragma unroll
         for (int r = 0; r < 4; r++) v[r] = bloadf(src, t * 8u, (uint32_t)r * 2048u);
     }
-    if (!own || MODE == FP_FWD_CONV_SUB) wide_twiddles(w, a.sfwd, a.table_stride, prime, row, t, q);
+    const bool waits = sums && !mine;                            // has no digit
+    if (waits && source) wide_twiddles(w, a.sinv, a.table_stride, prime, row, t, q);
+    else if (!own || MODE == FP_FWD_CONV_SUB) wide_twiddles(w, a.sfwd, a.table_stride, prime, row, t, q);
     if (sums) {
 #pragma unroll
         for (int d = 0; d < WIDE_DIGITS; d++)
-            if (d < a.n_digits) wide_load<K3>(k[d], g.key + (((u64)d * 2 + part) * a.total + prime) * n, 0, row, t);
-        if (with_add) wide_load<K3>(add, g.add + b * g.add_bs + (u64)part * g.add_ps + (u64)x * n, g.galois, row, t);
+            if (d < a.n_digits) wide_load<K3>(k[d], g.key + (((u64)d * 2 + poly) * a.total + prime) * n, 0, row, t);
+        if (with_add) wide_load<K3>(add, g.add + b * g.add_bs + (u64)poly * g.add_ps + (u64)x * n, g.galois, row, t);
         if (MODE == FP_FWD_CONV_SUB) {
 #pragma unroll
             for (int r = 0; r < 4; r++) div[r] = bloadf(dst, t * 8u, (uint32_t)r * 2048u);
@@ -929,7 +935,7 @@ __device__ __forceinline__ void wide_rows_inner(const ConvertArgs& a, const Inne
 #pragma unroll
         for (int r = 0; r < 4; r++) slot[wide_at(4 * t + r)] = v[r];
     }
-    if (sums && source) wide_twiddles(w, a.sinv, a.table_stride, prime, row, t, q);      // on their way while the sums are formed
+    if (sums && source && !waits) wide_twiddles(w, a.sinv, a.table_stride, prime, row, t, q);      // on their way while the sums are formed
     __syncthreads();
     if (sums) {
         const double c1 = as_const(g.c1)[x];
@@ -1329,7 +1335,8 @@ static hipError_t launch_one(dim3 grid, unsigned threads, size_t lds, const Conv
 // 12.7 -> 10.2, 4352: 18.1 -> 18.4, 26112: 76 -> 93; rows of a rescale 192: 6.5 -> 4.9, 2048: 12.6 -> 11.6, 2816: 13.4 -> 14.0, 16384:
 // 65 -> 89: four exchanges a row instead of two).  Inner products: while all workgroups are resident at once, 512 of eight waves (up to
 // two digits) or 256 of twelve or sixteen (two digits 24: 8.9 -> 8.0 us, 384: 13.8 -> 12.7, 768: 16.3 -> 18.0; three digits 128: 12.1 -> 9.4,
-// 256: 13.2 -> 10.7, 736: 21 -> 26; four digits 256: 14.9 -> 11.4, 320: 19.3 -> 20.1).
+// 256: 13.2 -> 10.7, 736: 21 -> 26; four digits 256: 14.9 -> 11.4, 320: 19.3 -> 20.1).  Of these a workgroup for each polynomial while both fit
+// the chip's 256 compute units (WIDE_SPLIT): one rotation at N = 2^13, 8 limbs, 26.3 -> 25.6 us.
 // Forward transforms with their columns, us, 8-byte rows by one wave / 16-byte ones / these: 1280 rows at N = 2^14 13.5 / 14.2 / 12.5, 2048
 // 15.5 / 16.3 / 16.0; of 4096, the one place where 16-byte rows lose (two exchanges of lanes a row, nothing to hide them behind), 23.0 / 24.1,
 // of 6144 and more even.
@@ -1339,9 +1346,12 @@ template <int K3, int MODE>
 static hipError_t launch_wide_k3(const ConvertArgs& a, const InnerArgs& g, u64 tasks, hipStream_t st) {
     static char name[40] = "";
     if (!name[0]) snprintf(name, sizeof name, "ntt_fp_wide_kernel<%d, %d>", K3, MODE);
-    const unsigned rows = !fp_inner(MODE) ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
+    InnerArgs ga = g;
+    ga.split = fp_inner(MODE) && 2 * tasks <= WIDE_SPLIT;
+    const unsigned digits = (unsigned)a.n_digits, rows = !fp_inner(MODE) ? 1 : ga.split ? std::min(digits + 1, (unsigned)WIDE_DIGITS) : std::max(digits, 2u);
+    tasks <<= ga.split;
     ProfScope prof__(name, st);
-    hipLaunchKernelGGL((ntt_fp_wide_kernel<K3, MODE>), dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st, a, g,
+    hipLaunchKernelGGL((ntt_fp_wide_kernel<K3, MODE>), dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st, a, ga,
                        (int)tasks);
     return hipGetLastError();
 }

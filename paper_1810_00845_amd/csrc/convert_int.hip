@@ -574,19 +574,20 @@ __device__ __forceinline__ void wide_rows_divide(const IntArgs& a, int task, u64
 
 // A workgroup per (limb x, row, entry), four waves per digit (two digits at least, INNER_CHUNK at most: the caller's rule).  Each
 // four leave their digit's row in LDS in 30-bit halves; then the first eight waves form the sums of a polynomial each, and
-// take those of a special limb through the inverse levels.
+// take those of a special limb through the inverse levels.  split: a workgroup per polynomial too, as in convert_fp.hip.
 template <int K3>
 __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64* lds) {
     const uint32_t t = threadIdx.x & (WIDE_NT - 1);
     const int part = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / WIDE_NT));
-    const uint32_t unit = uniform((uint32_t)task / a.n_entries), row = unit & ((1u << K3) - 1);
-    const u64 b = (uint32_t)task - unit * a.n_entries;
+    const uint32_t entry = (uint32_t)task >> a.split, unit = uniform(entry / a.n_entries), row = unit & ((1u << K3) - 1);
+    const u64 b = entry - unit * a.n_entries;
+    const int summer = a.n_digits < INNER_CHUNK ? a.n_digits : 0, poly = a.split ? task & 1 : part;
     const int x = a.ext_limbs - 1 - (int)(unit >> K3);
     const int prime = prime_at(x, a.l, a.L);
     const u64 q = mod_int(a.primes, prime).q;
     const WideMod wide = wide_mod(a.consts, prime);
     constexpr u64 n = (u64)1 << (10 + K3);
-    const bool special = x >= a.l, sums = part < 2;
+    const bool special = x >= a.l, sums = a.split ? part == summer : part < 2;
     u64 v[4], k[INNER_CHUNK][4];
     int m[4] = {16, 16, 16, 16};
     WideTwiddles w;
@@ -600,10 +601,12 @@ __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64*
         for (int r = 0; r < 4; r++) v[r] = bload(src, t * 8u, (uint32_t)r * 2048u);
         wide_twiddles<K3>(w, a.tw, a.tw_sh, prime, row, t);
     }
+    const bool waits = sums && !mine;                            // has no digit
+    if (waits && special) wide_twiddles<K3>(w, a.itw, a.itw_sh, prime, row, t);
     if (sums) {
 #pragma unroll
         for (int d = 0; d < INNER_CHUNK; d++)
-            if (d < a.n_digits) wide_load<K3>(k[d], a.key + ((u64)(2 * d + part) * a.total + prime) * n, 0, row, t);
+            if (d < a.n_digits) wide_load<K3>(k[d], a.key + ((u64)(2 * d + poly) * a.total + prime) * n, 0, row, t);
     }
     if (mine && !own) wide_forward(v, m, w, slot, t, q, 2);
     else wide_no_row();
@@ -611,7 +614,7 @@ __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64*
 #pragma unroll
         for (int r = 0; r < 4; r++) slot[wide_at(4 * t + r)] = split30(v[r]);
     }
-    if (sums && special) wide_twiddles<K3>(w, a.itw, a.itw_sh, prime, row, t);   // on their way while the sums are formed
+    if (sums && special && !waits) wide_twiddles<K3>(w, a.itw, a.itw_sh, prime, row, t);   // on their way while the sums are formed
     __syncthreads();
     if (sums) {
 #pragma unroll
@@ -624,7 +627,7 @@ __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64*
             m[r] = 8;
         }
         if (!special) {
-            const rsrc_t dst = make_rsrc(a.sums + ((b * 2 + part) * a.l + x) * n + row * 1024u, 8192u);
+            const rsrc_t dst = make_rsrc(a.sums + ((b * 2 + poly) * a.l + x) * n + row * 1024u, 8192u);
             wide_store(dst, t, v);
         }
     }
@@ -635,7 +638,7 @@ __device__ __forceinline__ void wide_rows_inner(const IntArgs& a, int task, u64*
         return;
     }
     wide_inverse(v, m, w, slot, t, q);
-    const rsrc_t dst = make_rsrc(a.down + ((b * 2 + part) * (u64)(a.ext_limbs - a.l) + (u64)(x - a.l)) * n + row * 1024u, 8192u);
+    const rsrc_t dst = make_rsrc(a.down + ((b * 2 + poly) * (u64)(a.ext_limbs - a.l) + (u64)(x - a.l)) * n + row * 1024u, 8192u);
 #pragma unroll
     for (int r = 0; r < 4; r++) bstore(dst, t * 8u, (uint32_t)r * 2048u, v[r]);
 }
@@ -906,10 +909,13 @@ template <int K3, int MODE>
 static hipError_t launch_wide_k3(const IntArgs& a, const IntTasks& tk, u64 tasks, hipStream_t st) {
     static char name[40] = "";
     if (!name[0]) snprintf(name, sizeof name, "ntt_int_wide_kernel<%d, %d>", K3, MODE);
-    const unsigned rows = MODE != INT_INNER ? 1 : a.n_digits < 2 ? 2 : (unsigned)a.n_digits;
+    IntArgs s = a;
+    s.split = MODE == INT_INNER && 2 * tasks <= WIDE_SPLIT;
+    const unsigned digits = (unsigned)a.n_digits, rows = MODE != INT_INNER ? 1 : s.split ? std::min(digits + 1, (unsigned)INNER_CHUNK) : std::max(digits, 2u);
+    tasks <<= s.split;
     ProfScope prof__(name, st);
     hipLaunchKernelGGL((ntt_int_wide_kernel<K3, MODE>), dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(rows * WIDE_NT), rows * WIDE_LDS * 8, st,
-                       a, tk, (int)tasks);
+                       s, tk, (int)tasks);
     return hipGetLastError();
 }
 template <int MODE>
@@ -959,6 +965,8 @@ static hipError_t launch_any(int log_n, dim3 grid, unsigned threads, size_t lds,
 // the wave of its own waits for fewer exchanges.  Inner products: while all workgroups are resident at once, 512 of eight
 // waves (up to two digits) or 256 of twelve or sixteen: one wave a digit -> four, 16 tasks of three digits 17.6 -> 12.8 us, 256 of
 // them 18.5 -> 14.4, 352 23 -> 26; of two digits 512 tasks 22 -> 17.6, 768 24.7 -> 24.3, 1024 29 -> 30.
+// Of these a workgroup for each polynomial while both fit the chip's 256 compute units (WIDE_SPLIT): one rotation at N = 2^12,
+// 3 limbs, 28.4 -> 28.0 us.
 #define WIDE_INVERSE_ROWS 32768
 #define WIDE_DIVIDE_ROWS 8192
 static u64 wide_inner_tasks(int n_digits) { return n_digits > INNER_CHUNK ? 0 : n_digits <= 2 ? 512 : 256; }

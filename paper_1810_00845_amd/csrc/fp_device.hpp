@@ -1,6 +1,7 @@
 // Device helpers shared by the transforms (ntt_fp.hip, convert_fp.hip, convert_int.hip): scalar table reads, buffer-resource
 // accesses, wave-local ordering of LDS traffic, the NTT-order automorphism, rows by one wave and by four.
 #pragma once
+#include <algorithm>
 #include <type_traits>
 
 #include "hisa_internal.hpp"
@@ -129,6 +130,7 @@ __device__ __forceinline__ int row_task(int n_tasks) {
 // behind the first two levels crosses waves.
 //   stage s, levels 2 s and 2 s + 1: registers 0 .. 3 of thread t are 2^p apart, p = 8 - 2 s (wide_element)
 #define WIDE_NT 256
+#define WIDE_SPLIT 256   // inner products: workgroups of one polynomial each, while there is a compute unit for every one
 #define WIDE_LDS 1280    // 64-bit words per row: four words of padding per sixteen, so that a thread's four stay together
 __device__ __forceinline__ uint32_t wide_at(uint32_t i) { return i + ((i >> 4) << 2); }
 template <int S>

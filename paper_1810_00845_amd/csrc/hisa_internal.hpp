@@ -390,6 +390,7 @@ struct InnerArgs {
     double* acc;
     u64* out;
     double* down;
+    int split;                           // set by the launcher: a workgroup a polynomial
 };
 struct StepArgs {
     unsigned step_B;
@@ -434,6 +435,7 @@ struct IntArgs {
     const u64* ext; u64 ext_bs;
     const u64* key;
     u64 *sums, *down;
+    int split;                           // set by the launcher: a workgroup a polynomial
 };
 hipError_t launch_ntt_int(const IntArgs& a, const IntTasks& tk, hipStream_t st);
 hipError_t launch_intt_int(const IntArgs& a, const IntTasks& tk, hipStream_t st);

@@ -22,6 +22,12 @@ POINTS = [
     (12, [50, 45, 44, 50], 1, 50, 4, 32),              # 512 of one digit in both launches, then more
     (12, [50, 45, 44, 50], 1, 50, 4, 33),
     (15, [50, 45, 44, 50], 4, 50, 4, 1),               # four digits: sixteen waves
+    (12, [50, 45, 44], 1, 50, 3, 5),                   # a workgroup a polynomial: 120 inner products of one digit, then more than 128
+    (12, [50, 45, 44], 1, 50, 3, 6),
+    (12, [50, 45, 44, 50, 40, 49], 3, 50, 6, 4),       # 128 of three digits, then more
+    (12, [50, 45, 44, 50, 40, 49], 3, 50, 6, 5),
+    (12, [50, 45, 44, 50], 4, 50, 4, 6),               # four digits: no waves to spare
+    (12, [50] * 16, 1, 50, 2, 15),                     # behind columns of the division
 ]
 
 

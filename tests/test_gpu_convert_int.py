@@ -26,6 +26,10 @@ POINTS = [
     (12, [60, 45, 30], 3, 60, 3, 16),            # 256 of three digits, then more
     (12, [60, 45, 30], 3, 60, 3, 17),
     (14, [55, 51, 60, 30], 4, 60, 4, 3),         # four digits: sixteen waves
+    (10, [60, 59, 58, 57], 2, 60, 4, 21),        # a workgroup a polynomial: 126 inner products of two digits, then more than 128
+    (10, [60, 59, 58, 57], 2, 60, 4, 22),
+    (12, [60, 45, 30], 1, 60, 3, 1),
+    (10, [55, 51, 60, 30], 4, 60, 4, 25),        # four digits: no waves to spare
     (15, [58] * 8, 3, 60, 8, 17),                # more than 8192 rows of a division
 ]
 
