@@ -25,3 +25,16 @@ __device__ __forceinline__ i64 gaussian_from_word(u64 w, const u64* cdt, int cdt
     for (int k = 0; k < cdt_n; k++) mag += (mag_src >= cdt[k]);
     return (w & 1) ? -mag : mag;
 }
+// the same for R words at once: an entry of the table, which is fetched from memory, serves them all
+template <int R>
+__device__ __forceinline__ void gaussians_from_words(double (&v)[R], const u64 (&w)[R], const u64* cdt, int cdt_n) {
+    int mag[R] = {};
+#pragma unroll 4
+    for (int k = 0; k < cdt_n; k++) {
+        const u64 c = cdt[k];
+#pragma unroll
+        for (int r = 0; r < R; r++) mag[r] += (w[r] >> 1) >= c;
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) v[r] = (double)(w[r] & 1 ? -mag[r] : mag[r]);
+}
