@@ -302,6 +302,16 @@ __device__ __forceinline__ void load_row(double (&v)[16], rsrc_t row, int lane) 
 #pragma unroll
     for (int k = 0; k < 8; k++) bload2(row, (uint32_t)lane * 16u, (uint32_t)k * 1024u, v[2 * k], v[2 * k + 1]);
 }
+template <bool ONCE>
+__device__ __forceinline__ void load_key_row(double (&v)[16], rsrc_t row, int lane) {
+    if (!ONCE) return load_row(v, row, lane);
+#pragma unroll
+    for (int k = 0; k < 8; k++) {
+        const u32x4_t d = __builtin_amdgcn_raw_buffer_load_b128(row, lane * 16, k * 1024, NONTEMPORAL);
+        v[2 * k] = mk64(d.x, d.y);
+        v[2 * k + 1] = mk64(d.z, d.w);
+    }
+}
 __device__ __forceinline__ void store_row(rsrc_t row, int lane, const double (&v)[16]) {
 #pragma unroll
     for (int k = 0; k < 8; k++) bstore2(row, (uint32_t)lane * 16u, (uint32_t)k * 1024u, v[2 * k], v[2 * k + 1]);
@@ -636,7 +646,7 @@ __device__ __forceinline__ void rows_forward(const ConvertArgs& a, int n_tasks, 
 // ahead (603 and 235), two entries a workgroup for the sake of the key rows (557), other orders of the tasks (549 .. 556).
 #define IP_CAP 5.5f
 struct OneStep {};
-template <int K3, int MODE, class S>
+template <int K3, int MODE, bool ONCE, class S>
 __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs& g, const S& s, int n_tasks, double* lds_all) {
     constexpr bool STEPS = !std::is_same<S, OneStep>::value;
     const int per = (n_tasks + 7) >> 3;
@@ -696,9 +706,9 @@ __device__ __forceinline__ void rows_inner(const ConvertArgs& a, const InnerArgs
         const bool two = d0 + 1 < a.n_digits;
         const rsrc_t k0r = make_rsrc(key_p, 8192u), k1r = make_rsrc(two ? key_p + (u64)2 * a.total * n : key_p, 8192u);
         double k0[16], k1[16];
-        load_row(k0, k0r, lane);
+        load_key_row<ONCE>(k0, k0r, lane);
         // (also without a second digit, then of the first: words left undefined would stay live through the loop)
-        load_row(k1, k1r, lane);
+        load_key_row<ONCE>(k1, k1r, lane);
         SCHED_FENCE();
         __syncthreads();
 #pragma unroll
@@ -1266,7 +1276,7 @@ __global__ __launch_bounds__(fp_threads(MODE, COLUMNS), fp_waves(K3, COLUMNS)) v
     } else {
         __shared__ double lds[fp_threads(MODE, false) / 64 * ROW_LDS];
         if constexpr (MODE == FP_INV_TO_Y) rows_inverse<K3>(a, n_tasks, lds);
-        else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE>(a, g, OneStep{}, n_tasks, lds);
+        else if constexpr (MODE == FP_INV_D_TO_Y || MODE == FP_FWD_CONV_SUB) rows_inner<K3, MODE, false>(a, g, OneStep{}, n_tasks, lds);
         else rows_forward<K3, MODE>(a, n_tasks, lds);
     }
 }
@@ -1289,11 +1299,11 @@ __global__ __launch_bounds__(fp_inner(MODE) ? WIDE_DIGITS * WIDE_NT : WIDE_NT, 4
     else wide_rows_forward<K3, MODE>(a, task, wide_lds);
 }
 
-// the inner products' rows for several rotations of the same digits
-template <int K3, int MODE>
+// the inner products' rows for several rotations of the same digits; ONCE: the keys pass the caches by
+template <int K3, int MODE, bool ONCE>
 __global__ __launch_bounds__(128, 4) void inner_product_steps_rows_kernel(ConvertArgs a, InnerArgs g, StepArgs s, int n_tasks) {
     __shared__ double lds[2 * ROW_LDS];
-    rows_inner<K3, MODE>(a, g, s, n_tasks, lds);
+    rows_inner<K3, MODE, ONCE>(a, g, s, n_tasks, lds);
 }
 
 // Twiddles of one prime for the three kernels, psi^(sign bitrev(i)) as the caller's w(i) gives them (centred doubles):
@@ -1386,9 +1396,11 @@ static hipError_t launch_step_rows(const ConvertArgs& a, const InnerArgs& g, con
     if (tasks > 0x7fffff00u) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((tasks + 7) / 8 * 8));
     ProfScope prof__("inner_product_steps_rows_kernel", st);
-#define STEPS_CASE(K3)                                                                                                           \
-    case 10 + K3:                                                                                                                \
-        hipLaunchKernelGGL((inner_product_steps_rows_kernel<K3, MODE>), grid, dim3(128), 0, st, a, g, s, (int)tasks);            \
+    const bool once = s.step_B == 1 && (((u64)a.ext_limbs * a.n_digits * 2 * a.n_entries) << (a.log_n + 3)) > STREAMED_KEY_BYTES;
+#define STEPS_CASE(K3)                                                                                                            \
+    case 10 + K3:                                                                                                                 \
+        if (once) hipLaunchKernelGGL((inner_product_steps_rows_kernel<K3, MODE, true>), grid, dim3(128), 0, st, a, g, s, (int)tasks); \
+        else hipLaunchKernelGGL((inner_product_steps_rows_kernel<K3, MODE, false>), grid, dim3(128), 0, st, a, g, s, (int)tasks);     \
         break;
     switch (a.log_n) {
         STEPS_CASE(2) STEPS_CASE(3) STEPS_CASE(4) STEPS_CASE(5)

@@ -424,7 +424,8 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_steps_fp_kernel(const Fp
 // A thread owns a coefficient of a limb and up to IPS_BCH outputs, for which a rotation's key values serve once loaded; the
 // workgroups of a limb run together, so the key rows that each of them reads come from the L2 after the first.  GROUPS = 4: where
 // workgroups are few, a thread would be a chain of up to 32 rounds of dependent loads; the four waves of a workgroup then take
-// the same 64 coefficients and every fourth rotation each, and their sums meet in LDS.
+// the same 64 coefficients and every fourth rotation each, and their sums meet in LDS.  ONCE: one group of outputs, keys that pass the
+// caches by (STREAMED_KEY_BYTES; three digits, 28 limbs at N = 2^15 308 -> 296 us, 22 limbs 190 -> 164).
 // Against sums in one chain a thread, a reduction a product, and c0 and addend in two launches of their own (us, all sums of a network):
 // LeNet-small 203 -> 105, LeNet-medium 1095 -> 678, SqueezeNet-style 2087 -> 1758 (there the keys, 640 MB a launch of one output, bound
 // it).  In one wave or over four, by workgroups of whole chains: 288 of them 40 -> 32 us a launch, 1792 50 -> 41, 2560 and more even.
@@ -436,13 +437,11 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_steps_fp_kernel(const Fp
 // value: 6.5 p < 2^53.
 #define IPS_BCH 4
 #define IPS_FEW 2048    // workgroups of whole chains
-template <int GROUPS, int DIGITS>
-__global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(const FpPrime* fprimes, const double* ext, u64 ext_bs,
-                                                                      int digits, int l, int K, int L, int alpha, IpSteps steps,
-                                                                      int n_steps, int total, const u64* own_src, u64 own_bs,
-                                                                      u64* acc, u64 acc_bs, u64 n_batch, int shared_input,
-                                                                      const u64* c0_src, const u64* plain, u64 plain_bs, const u64* pmod,
-                                                                      int log_n) {
+template <int GROUPS, int DIGITS, bool ONCE>
+__device__ __forceinline__ void inner_product_sum(
+    const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L, int alpha, const IpSteps& steps, int n_steps, int total,
+    const u64* own_src, u64 own_bs, u64* acc, u64 acc_bs, u64 n_batch, int shared_input, const u64* c0_src, const u64* plain, u64 plain_bs,
+    const u64* pmod, int log_n) {
     constexpr int COEFFS = IPF_NT / GROUPS, AT_ONCE = DIGITS ? DIGITS : 1;
     const u64 n = (u64)1 << log_n;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
@@ -474,8 +473,9 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(const FpPr
 #pragma unroll
             for (int i = 0; i < AT_ONCE; i++) {
                 const int d = d0 + i;
-                kb[i] = key[(u64)(d * 2) * total * n];
-                ka[i] = key[(u64)(d * 2 + 1) * total * n];
+                const double *key_b = key + (u64)(d * 2) * total * n, *key_a = key_b + (u64)total * n;
+                kb[i] = ONCE ? __builtin_nontemporal_load(key_b) : *key_b;
+                ka[i] = ONCE ? __builtin_nontemporal_load(key_a) : *key_a;
                 const bool own = d == own_digit;
                 const double* src = own ? (const double*)own_src + entry0 * own_bs + (u64)x * n + jsrc
                                         : ext + entry0 * ext_bs + ((u64)d * ext_limbs + x) * n + jsrc;
@@ -557,6 +557,22 @@ __global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(const FpPr
     }
 }
 
+#define SUM_PARAMS                                                                                                                        \
+    const FpPrime *fprimes, const double *ext, u64 ext_bs, int digits, int l, int K, int L, int alpha, IpSteps steps, int n_steps, int total, \
+        const u64 *own_src, u64 own_bs, u64 *acc, u64 acc_bs, u64 n_batch, int shared_input, const u64 *c0_src, const u64 *plain,         \
+        u64 plain_bs, const u64 *pmod, int log_n
+#define SUM_ARGS                                                                                                                   \
+    fprimes, ext, ext_bs, digits, l, K, L, alpha, steps, n_steps, total, own_src, own_bs, acc, acc_bs, n_batch, shared_input, c0_src, \
+        plain, plain_bs, pmod, log_n
+template <int GROUPS, int DIGITS>
+__global__ __launch_bounds__(IPF_NT) void inner_product_sum_fp_kernel(SUM_PARAMS) {
+    inner_product_sum<GROUPS, DIGITS, false>(SUM_ARGS);
+}
+template <int GROUPS, int DIGITS>
+__global__ __launch_bounds__(IPF_NT) void inner_product_sum_once_kernel(SUM_PARAMS) {
+    inner_product_sum<GROUPS, DIGITS, true>(SUM_ARGS);
+}
+
 hipError_t launch_inner_product_sum_fp(const FpPrime* fprimes, const double* ext, u64 ext_bs, int digits, int l, int K, int L,
                                        int alpha, const IpSteps& steps, int n_steps, int total, const u64* own_src, u64 own_bs,
                                        u64* acc, u64 acc_bs, u64 n_batch, int shared_input, const u64* c0_src, const u64* plain,
@@ -575,21 +591,25 @@ hipError_t launch_inner_product_sum_fp(const FpPrime* fprimes, const double* ext
     const unsigned groups_of_outputs = (unsigned)((n_batch + IPS_BCH - 1) / IPS_BCH);
     const bool few = ((u64)groups_of_outputs * (l + K) << log_n) / IPF_NT < IPS_FEW;
     dim3 grid((1u << log_n) / (few ? 64 : IPF_NT), groups_of_outputs, l + K);
-    ProfScope prof__("inner_product_sum_fp_kernel", st);
-#define SUM_LAUNCH(G, D)                                                                                                                 \
-    hipLaunchKernelGGL((inner_product_sum_fp_kernel<G, D>), grid, dim3(IPF_NT), 0, st, fprimes, ext, ext_bs, digits, l, K, L, alpha, steps, \
-                       n_steps, total, own_src, own_bs, acc, acc_bs, n_batch, shared_input, c0_src, plain, plain_bs, pmod, log_n)
+    const bool once = groups_of_outputs == 1 && ((u64)n_steps * digits * 2 * (l + K) << (log_n + 3)) > STREAMED_KEY_BYTES;
+    ProfScope prof__(once ? "inner_product_sum_once_kernel" : "inner_product_sum_fp_kernel", st);
+#define SUM_LAUNCH(G, D)                                                                                                \
+    if (once) hipLaunchKernelGGL((inner_product_sum_once_kernel<G, D>), grid, dim3(IPF_NT), 0, st, SUM_ARGS);            \
+    else hipLaunchKernelGGL((inner_product_sum_fp_kernel<G, D>), grid, dim3(IPF_NT), 0, st, SUM_ARGS);                   \
+    break
     switch ((few ? 4 : 0) + (digits < 4 ? digits : 0)) {
-        case 1: SUM_LAUNCH(1, 1); break;
-        case 2: SUM_LAUNCH(1, 2); break;
-        case 3: SUM_LAUNCH(1, 3); break;
-        case 0: SUM_LAUNCH(1, 0); break;
-        case 5: SUM_LAUNCH(4, 1); break;
-        case 6: SUM_LAUNCH(4, 2); break;
-        case 7: SUM_LAUNCH(4, 3); break;
-        default: SUM_LAUNCH(4, 0); break;
+        case 1: SUM_LAUNCH(1, 1);
+        case 2: SUM_LAUNCH(1, 2);
+        case 3: SUM_LAUNCH(1, 3);
+        case 0: SUM_LAUNCH(1, 0);
+        case 5: SUM_LAUNCH(4, 1);
+        case 6: SUM_LAUNCH(4, 2);
+        case 7: SUM_LAUNCH(4, 3);
+        default: SUM_LAUNCH(4, 0);
     }
 #undef SUM_LAUNCH
+#undef SUM_ARGS
+#undef SUM_PARAMS
     return hipGetLastError();
 }
 

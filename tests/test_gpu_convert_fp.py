@@ -146,3 +146,25 @@ def test_sums_of_many_rotations(log_n, q_bits, dnum, outputs, rotations):
         single = g.rot_left_sum_batch([[cts[terms_of(s, outputs - 1)]] for s in [0] + steps], [0] + steps)
         assert np.array_equal(g.ct_export(out[-1]), g.ct_export(single[0]))
     g.close()
+
+
+# keys beyond the last-level cache, read once (STREAMED_KEY_BYTES, 208 MB a call) and just below it, by one ciphertext and by two
+@pytest.mark.parametrize("log_n,q_bits,dnum,rotations,batch",
+                         [(14, [50] * 8, 8, 12, 1), (14, [50] * 8, 8, 11, 1), (15, [50, 45, 45, 45, 45, 45], 3, 18, 1), (14, [50] * 8, 8, 12, 2)])
+def test_rotations_with_keys_beyond_the_caches(log_n, q_bits, dnum, rotations, batch):
+    from paper_1810_00845_amd import hisa
+    print("[case]", log_n, len(q_bits), dnum, rotations, batch, flush=True)
+    g = hisa.Context(log_n, q_bits, dnum, 50, 5)
+    steps = list(range(1, rotations + 1))
+    g.gen_rot_keys(steps)
+    l = len(q_bits)
+    cts = g.ct_random_batch(batch, l, 2.0 ** 50, 11)
+    hoisted = g.rot_left_hoisted_batch(cts, steps)
+    for s, row in zip(steps, hoisted):
+        for ct, out in zip(cts, row):
+            assert np.array_equal(g.ct_export(out), g.ct_export(g.rot_left(ct, s)))
+    # the sum of the rotations, from their sums over a group of outputs that keeps the keys and over one that does not
+    many = g.rot_left_sum_batch([[cts[0]] * 5 for _ in steps], steps)
+    one = g.rot_left_sum_batch([[cts[0]] for _ in steps], steps)
+    assert np.array_equal(g.ct_export(one[0]), g.ct_export(many[4]))
+    g.close()
