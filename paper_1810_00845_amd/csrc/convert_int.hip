@@ -1046,6 +1046,27 @@ static bool convert_ok(const IntArgs& a) {
            a.ext_limbs - a.l + a.L <= a.total && a.n_entries <= 65535 && (!a.own || (a.src_pos0 == 0 && a.n_src <= a.ext_limbs));
 }
 
+// Waves of a workgroup of the columns where there are twice as many workgroups as are resident with eight waves each: those with the
+// highest throughput, when `slots` waves share a compute unit and a round over the targets takes 1.6 times one over the sources.  A wave
+// without a target in the last round, or without a source, only holds its registers, and those admit four waves a SIMD.  rotLeft, us, as few
+// waves as the rounds need (five, of 9 targets and 3 sources) -> these (three): 16 at N = 2^15, 8 limbs, three digits 331 -> 320, 64 at N = 2^14
+// 564 -> 538, 16 at N = 2^16, 4 limbs, two digits 321 -> 299, 64 at N = 2^11, 7 limbs 79 -> 76; even where the waves stay.  With fewer
+// workgroups the rounds are what counts: 12 at N = 2^15, 5 limbs, in 768 workgroups 163 -> 174.
+static int columns_waves(const IntArgs& a, size_t lds, int slots) {
+    int best = 8;
+    double best_rate = 0;
+    for (int w = 2; w <= 8; w++) {
+        double time = 0;
+        for (int d = 0; d < a.n_digits; d++) {
+            const int src = std::min(a.alpha, a.n_src - d * a.alpha), tgt = a.ext_limbs - (a.own ? src : 0);
+            time += (src + w - 1) / w + 1.6 * ((tgt + w - 1) / w);
+        }
+        const double rate = std::min(slots / w, (int)(163840 / lds)) / time;
+        if (rate > best_rate) { best_rate = rate; best = w; }
+    }
+    return best;
+}
+
 hipError_t launch_columns_int(const IntArgs& a_in, hipStream_t st) {
     DRY_RUN_RETURN();
     IntArgs a = a_in;
@@ -1058,7 +1079,10 @@ hipError_t launch_columns_int(const IntArgs& a_in, hipStream_t st) {
     const int fit = (int)(131072 / per_src), limit = fit < CONV_CHUNK ? fit : CONV_CHUNK;
     a.chunk = most_src < limit ? most_src : limit;
     // a target per wave, and as few waves as the rounds over the targets need
-    const int rounds = (most_tgt + 7) / 8, waves = (most_tgt + rounds - 1) / rounds;
+    const int rounds = (most_tgt + 7) / 8;
+    int waves = (most_tgt + rounds - 1) / rounds;
+    const int slots = a.log_n < 14 ? 28 : a.log_n < 16 ? 16 : 8;
+    if (most_src <= a.chunk && (u64)a.n_entries * a.n_digits * tiles >= 64u * slots) waves = columns_waves(a, a.chunk * per_src, slots);
     // few entries: several workgroups share a tile's targets (each forms the conversion inputs for itself)
     a.n_splits = 1;
     while (a.n_splits < rounds && (u64)a.n_entries * a.n_digits * tiles * (a.n_splits + 1) <= 512) a.n_splits++;

@@ -30,6 +30,10 @@ POINTS = [
     (10, [60, 59, 58, 57], 2, 60, 4, 22),
     (12, [60, 45, 30], 1, 60, 3, 1),
     (10, [55, 51, 60, 30], 4, 60, 4, 25),        # four digits: no waves to spare
+    (15, [58] * 8, 3, 60, 8, 10),                # columns: 960 workgroups of five waves, then 1056 of three
+    (15, [58] * 8, 3, 60, 8, 11),
+    (16, [55, 52, 51, 30], 2, 60, 4, 8),         # 512 workgroups and more
+    (13, [58] * 5, 5, 60, 5, 24),                # one source, one digit more than targets of a round
     (15, [58] * 8, 3, 60, 8, 17),                # more than 8192 rows of a division
 ]
 
