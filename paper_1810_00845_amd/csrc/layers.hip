@@ -1740,10 +1740,28 @@ static std::vector<int> ext_prime_list(const hisa_ctx* ctx, uint32_t l) {
 
 // What rotated_mac_mfma_kernel takes: the rotations of one launch, up to RM_DIGITS digits, one block of outputs (another would
 // form the operand again), and terms enough for the matrix cores.  The rest goes through accumulators in memory.
-static bool rotated_mac_fits(const hisa_ctx* ctx, const TapSplit& ts, uint32_t IC, uint32_t OC, uint32_t l) {
-    const size_t taps = ts.rot.size() + ts.zero.size(), digits = (l + ctx->alpha - 1) / ctx->alpha;
-    return ctx->tabs.fp_ok && !ts.rot.empty() && ts.rot.size() <= FP_MAX_STEPS && digits <= RM_DIGITS && OC <= MT_OC &&
-           taps * IC >= MFMA_MIN_K && taps * ((IC + 3) / 4 * 4) <= MFMA_MAX_K;
+// Of what it takes, it is given the convolutions it is ahead in.  It pays for every term of its steps of 64 -- channels padded to four,
+// taps to a whole step -- and for 64 outputs, and beyond five digits of weights its accumulators spill.  Times of a convolution, accumulators
+// in memory / this kernel, over 698 points (1 .. 32 channels, 2x2 .. 5x5, 1 .. 64 outputs, one to three key digits, N = 2^12 .. 2^15):
+//   up to five digits, 32 rotated terms and more: 1.0 .. 2.3 with 35 % of the terms used or more (0.95 at one point of N = 2^12);
+//   more digits, by the primes of the launch (10, 12 or 16 sixteenths of the terms for a limb below 2^40, 2^48, or above): at N = 2^13, two key
+//   digits, 40-bit primes (79 %) 0.88 .. 0.99 at 56 .. 66 % of the terms, 1.04 .. 1.10 at 77 .. 78 %, 1.26 at 98 %; 45-bit primes (86 %) 0.93 at 78 %,
+//   1.05 at 94 %; 50-bit primes (all) 0.82 at 78 %, 0.98 at 98 %.  Behind the line 0.93 remains at N = 2^12 for one image, 25 taps of 20
+//   channels and up to five outputs, where a launch has fewer workgroups than the chip compute units;
+//   fewer than 32 rotated terms, which the other schedule multiplies by sixteen outputs at a time in fp64 (2x2, 8 .. 10 channels, N = 2^13,
+//   2^14): up to five digits 0.7 .. 1.0 for 1 .. 8 outputs, 0.93 .. 1.14 for 16, 1.0 .. 1.17 for 17, 1.3 for 50; more digits 0.4 .. 0.8 for 2 .. 8,
+//   0.8 .. 0.9 for 32, 1.0 .. 1.1 for 50.
+static bool rotated_mac_fits(const hisa_ctx* ctx, const TapSplit& ts, const int64_t* w_int, uint32_t IC, uint32_t OC, uint32_t l) {
+    const size_t taps = ts.rot.size() + ts.zero.size(), digits = (l + ctx->alpha - 1) / ctx->alpha, padded = taps * ((IC + 3) / 4 * 4);
+    if (!ctx->tabs.fp_ok || ts.rot.empty() || ts.rot.size() > FP_MAX_STEPS || digits > RM_DIGITS || OC > MT_OC || taps * IC < MFMA_MIN_K ||
+        padded > MFMA_MAX_K)
+        return false;
+    bool small = true;       // five balanced digits hold every weight
+    for (size_t i = 0; i < taps * IC * OC; i++) small = small && w_int[i] <= 0x7f7f7f7f7fll && w_int[i] >= -0x8080808080ll;
+    if (ts.rot.size() * IC < MFMA_MIN_K) return OC > (small ? 16u : 48u);
+    size_t need = 0;
+    for (int prime : ext_prime_list(ctx, l)) need += ctx->mod[prime] < (u64)1 << 40 ? 10 : ctx->mod[prime] < (u64)1 << 48 ? 12 : 16;
+    return small || 16 * (l + ctx->K) * taps * IC >= need * ((padded + MT_K - 1) / MT_K * MT_K);
 }
 
 // scalar weights w_int[T][OC] -> device forms; shared: split by tap, the rotated ones on the l + K limbs
@@ -1756,7 +1774,7 @@ static int build_scalar_weights(hisa_ctx* ctx, const int64_t* w_int, const ConvP
         return upload_weight_residues(ctx, w_int, l, *cw.dw);
     }
     const TapSplit ts = split_taps(plan);
-    if (rotated_mac_fits(ctx, ts, ICm, OC, l)) {
+    if (rotated_mac_fits(ctx, ts, w_int, ICm, OC, l)) {
         const size_t IC4 = (ICm + 3) / 4 * 4, taps = ts.rot.size() + ts.zero.size();
         std::vector<int64_t> all(taps * IC4 * OC, 0);
         for (size_t k = 0; k < taps; k++) {

@@ -824,6 +824,49 @@ def test_rotated_sums_on_the_matrix_cores(bits, dnum, channels, outs, filt, same
     g.close()
 
 
+@pytest.mark.parametrize("log_n,bits,level,dnum,channels,outs,filt,std,batch,one_kernel", [
+    (12, [50, 46, 44], 3, 2, 15, 1, 2, 0.0, 2, True),           # a padded channel; two key digits; weights of six digits
+    (12, [40, 40], 2, 1, 16, 3, 2, 0.0, 1, True),               # one key digit
+    (12, [50, 50, 50], 3, 3, 16, 5, 2, 0.0, 1, True),           # residues and weights of seven digits, every term of a step used
+    (13, [45, 38, 38, 38, 38, 38], 5, 3, 5, 3, 3, 0.1, 1, True),    # below the top level, the last key digit ragged; N = 2^13
+    (12, [50, 40, 40, 40], 3, 2, 20, 7, 3, 0.1, 1, True),       # three steps of terms; below the top level
+    (15, [45, 38], 2, 1, 4, 2, 3, 0.1, 1, True),                # N = 2^15: the order of the blocks has nine bits
+    (12, [50, 40, 40], 3, 3, 9, 4, 2, 1e-6, 1, False),          # 27 rotated terms, few outputs
+    (12, [50, 40, 40], 3, 3, 9, 17, 2, 1e-6, 1, True),          # ... more than sixteen; weights of three digits
+    (12, [50, 40, 40], 2, 3, 1, 17, 5, 0.1, 1, False),          # 25 terms; below the top level
+    (12, [50, 40, 40], 3, 3, 4, 65, 3, 0.1, 1, False),          # more outputs than a block has
+    (12, [50, 40, 40, 40], 4, 4, 4, 3, 3, 0.1, 2, False),       # four key digits
+    (12, [50, 40, 40, 40], 3, 2, 5, 8, 3, 0.0, 1, False),       # weights of six digits, 45 of 128 terms
+    (12, [50, 40, 40, 40], 3, 2, 5, 8, 3, 0.1, 1, True),        # ... of five
+    (12, [50, 50], 2, 2, 15, 2, 2, 0.0, 1, False),              # residues and weights of seven digits, 60 of 64 terms
+    (12, [50, 40, 40], 3, 3, 9, 49, 2, 0.0, 1, True),           # 27 rotated terms, weights of six digits, more than 48 outputs
+])
+def test_both_schedules_of_rotated_sums(log_n, bits, level, dnum, channels, outs, filt, std, batch, one_kernel):
+    """Scalar weights with one division by P per output, bit for bit against the oracle: the matrix operand formed from the key switch's
+    digits, and accumulators in memory, each where the rule gives the convolution to it."""
+    from oracle import layers
+    from paper_1810_00845_amd import synth
+    print("[case]", log_n, bits, level, dnum, channels, outs, filt, std, batch, flush=True)
+    g, o = make_pair(log_n, bits, dnum, 50, 5)
+    x = np.stack([synth.image(20 + k, channels, 4, 5) for k in range(batch)])
+    gt, ot = both_tensors(g, o, x, 2.0 ** 36, level, h_stride=9, offset=20)
+    steps = g.conv2d_rot_steps(gt, filt, filt, pad_same=True)
+    g.gen_rot_keys(steps); o.gen_rot_keys(steps)
+    w = synth.conv_weights(30, filt, filt, channels, outs, dist="normal" if std else "uniform", std=std)
+    for fused in (False, True):
+        g.set_fused_rescale(fused)
+        oout, ints = layers.conv2d(o, ot, w, mode=layers.CONV_SCALAR, shared_moddown=True, fused_rescale=fused, pad_same=True)
+        g.profile_enable(True)
+        g.profile_read()
+        gout = g.conv2d_fixed(gt, ints["w_int"], ints["w_scale"], None, 1.0, outs, filt, filt, mode=layers.CONV_SCALAR, shared_moddown=True,
+                              pad_same=True)
+        ran = g.profile_read()
+        g.profile_enable(False)
+        assert ("rotated_mac_mfma_kernel" in ran) == one_kernel
+        same_tensor(g, o, gout, oout)
+    g.close()
+
+
 def test_shared_moddown_convolutions_bit_exact():
     """The convolution with one division by P per output ciphertext through the C ABI against the oracle's
     SharedModDown schedule, bit for bit: HW-tiled with scalar weights (literal and masked; short contraction on the
