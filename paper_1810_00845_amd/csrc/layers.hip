@@ -167,8 +167,13 @@ __global__ __launch_bounds__(NT) void scalar_mac_kernel(const PrimeConst* primes
 // instead of a 64x64 high/low product pair at quarter rate, and OCF outputs share each load of x.  The weights
 // (centred doubles) are the same for every thread and arrive through scalar loads.
 // Range: a term is at most 0.7 p in magnitude, eight of them on top of a normalised value stay below 6.1 p < 2^53.
+// Terms k = (tap, channel) in groups of MACU, whose loads go ahead of their arithmetic: channels of a tap where it has as many left,
+// else on into the next taps (past the end the last term again).  Six waves a SIMD hide them; registers for the next group's
+// loads would cost two of the waves (four ahead and five waves, eight and four: 0.87 .. 0.96 of the speed with three channels or more).  us
+// a launch, groups of a tap alone / eight ahead / this: 31 channels, 1x1, 31 outputs at N = 2^14, 10 limbs 102 / 128 / 102; three channels, 3x3,
+// 64 outputs, 4 images 599 / 660 / 558; one channel, 5x5, 20 outputs 101 / 77 / 64.
 #define OCF 16
-#define MACU 8
+#define MACU 4
 typedef const __attribute__((address_space(4))) double* mac_cdouble_ptr;
 // wf: [l][T][OC] (the OCF weights of one x value are contiguous: wide scalar loads)
 __global__ __launch_bounds__(NT) void scalar_mac_fp_kernel(const FpPrime* fprimes, MacArgs g, const double* wf, int log_n) {
@@ -183,26 +188,30 @@ __global__ __launch_bounds__(NT) void scalar_mac_fp_kernel(const FpPrime* fprime
     double acc[OCF];
 #pragma unroll
     for (int o = 0; o < OCF; o++) acc[o] = 0.0;
-    // terms k = (tap, channel) in groups of MACU, the next group's loads ahead of this one's arithmetic (past the end the last term's)
     const int K = g.n_taps * g.IC;
     const u64 off = (u64)b * g.IC * g.ct_words + (u64)pl * n + j;
     const mac_cdouble_ptr w = (mac_cdouble_ptr)(unsigned long long)(wf + (u64)limb * K * g.OC + oc0);
+    const u64* x = g.tap_base[0] + off;
     int t = 0, ic = 0;
-    u64 xn[MACU];
-    auto load = [&]() {
-#pragma unroll
-        for (int u = 0; u < MACU; u++) {
-            xn[u] = g.tap_base[t][off + (u64)ic * g.ct_words];
-            if (ic + 1 < g.IC) ic++;
-            else if (t + 1 < g.n_taps) { ic = 0; t++; }
-        }
-    };
-    load();
     for (int k0 = 0; k0 < K; k0 += MACU) {
+        u64 xn[MACU];
+        if (ic + MACU <= g.IC) {
+#pragma unroll
+            for (int u = 0; u < MACU; u++) xn[u] = x[(u64)(ic + u) * g.ct_words];
+            ic += MACU;
+            if (ic == g.IC && t + 1 < g.n_taps) { ic = 0; x = g.tap_base[++t] + off; }
+        } else {
+#pragma unroll
+            for (int u = 0; u < MACU; u++) {
+                xn[u] = g.tap_base[t][off + (u64)ic * g.ct_words];
+                if (ic + 1 < g.IC) ic++;
+                else if (t + 1 < g.n_taps) { ic = 0; t++; }
+            }
+            x = g.tap_base[t] + off;
+        }
         double xv[MACU];
 #pragma unroll
         for (int u = 0; u < MACU; u++) xv[u] = fp_from_u64(xn[u]);
-        if (k0 + MACU < K) load();
 #pragma unroll
         for (int u = 0; u < MACU; u++) {
             if (k0 + u < K) {
@@ -217,8 +226,10 @@ __global__ __launch_bounds__(NT) void scalar_mac_fp_kernel(const FpPrime* fprime
                 }
             }
         }
+        if ((k0 & MACU) && k0 + MACU < K) {      // every eight terms
 #pragma unroll
-        for (int o = 0; o < OCF; o++) acc[o] = fp_norm(acc[o], p, pinv);
+            for (int o = 0; o < OCF; o++) acc[o] = fp_norm(acc[o], p, pinv);
+        }
     }
 #pragma unroll
     for (int o = 0; o < OCF; o++)

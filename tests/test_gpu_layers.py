@@ -98,6 +98,24 @@ def test_multichannel_same_strided_masked_conv():
     g.close()
 
 
+@pytest.mark.parametrize("channels,filt,outs", [(1, 1, 1), (4, 1, 16), (5, 1, 17), (9, 1, 3), (1, 3, 5), (2, 2, 20), (3, 3, 2), (4, 2, 3),
+                                                 (5, 2, 1), (6, 2, 4), (7, 2, 16), (31, 1, 2)])
+def test_short_contraction_conv_bit_exact(channels, filt, outs):
+    """Sums of up to 31 terms (fp64 kernel): groups of four channels of a tap, groups across taps, both in turn, ragged ends; outputs
+    against blocks of sixteen."""
+    from oracle import layers
+    from paper_1810_00845_amd import synth
+    g, o = make_pair(12, [50, 45, 45], 2, 50, 8)
+    x = np.stack([synth.image(5 + k, channels, 3, 4) for k in range(2)])
+    gt, ot = both_tensors(g, o, x, 2.0 ** 40, 2, h_stride=8, offset=9)
+    steps = g.conv2d_rot_steps(gt, filt, filt, pad_same=True)
+    g.gen_rot_keys(steps); o.gen_rot_keys(steps)
+    oout, ints = layers.conv2d(o, ot, synth.conv_weights(6, filt, filt, channels, outs), pad_same=True, mode=layers.CONV_SCALAR)
+    gout = g.conv2d_fixed(gt, ints["w_int"], ints["w_scale"], None, 1.0, outs, filt, filt, pad_same=True, mode=layers.CONV_SCALAR)
+    same_tensor(g, o, gout, oout)
+    g.close()
+
+
 def test_long_contraction_conv_bit_exact():
     """A convolution whose sum over (tap, input channel) is long enough for the matrix-core multiply-accumulate
     (36 and 72 terms, ragged against its 64-wide tiles; 5 and 3 outputs against its 64-output blocks), compared bit

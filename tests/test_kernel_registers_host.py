@@ -31,6 +31,7 @@ FIT = [
     (r"_Z27inner_product_sum_fp_kernelILi[14]ELi0EE.*", 2, 96),     # four to eight digits: five waves
     (r"_Z13ntt_fp_kernelILi[45]ELi[346]ELb1EE.*", 6, 80),           # columns at N = 2^14, 2^15: three workgroups of eight waves
     (r"_Z20ntt_fp_chunks_kernelILi[45]ELi[346]EE.*", 6, 128),       # sixteen waves
+    (r"_Z20scalar_mac_fp_kernel.*", 1, 80),                         # six waves
     (r"_Z19encrypt_rows_kernelILi[2345]EE.*", 4, 128),              # four waves
 ]
 
