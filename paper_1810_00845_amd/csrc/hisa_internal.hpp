@@ -384,13 +384,13 @@ struct InnerArgs {
     const u64* own; u64 own_bs;
     u64 galois;
     int n_acc, x_begin, x_end;
+    int split;                           // set by the launcher: a workgroup a polynomial
     const double* c1;                    // [ext_limbs]
     const double* c2;                    // factors of the addend, limbs of q; null: one
     const u64* add; u64 add_bs, add_ps; int add_polys;
     double* acc;
     u64* out;
     double* down;
-    int split;                           // set by the launcher: a workgroup a polynomial
 };
 struct StepArgs {
     unsigned step_B;
@@ -418,6 +418,7 @@ struct IntArgs {
     const i64* coeffs;                   // forward transforms: signed coefficients [entry][N] instead of `in`
     u64* out; u64 out_bs;
     int whole;                           // set by the launcher
+    int split;                           // set by the launcher: a workgroup a polynomial
     u64* mid;                            // conversions: workspace [n_entries][n_src][N]
     int src_pos0, n_src, alpha, n_digits, own, ext_limbs;
     const u64* close;                    // [n_src] factor of the source, the same times the last inverse twiddle, with companions
@@ -435,7 +436,6 @@ struct IntArgs {
     const u64* ext; u64 ext_bs;
     const u64* key;
     u64 *sums, *down;
-    int split;                           // set by the launcher: a workgroup a polynomial
 };
 hipError_t launch_ntt_int(const IntArgs& a, const IntTasks& tk, hipStream_t st);
 hipError_t launch_intt_int(const IntArgs& a, const IntTasks& tk, hipStream_t st);
