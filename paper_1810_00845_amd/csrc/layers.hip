@@ -991,9 +991,13 @@ static hipError_t launch_plain_mac_fp(hisa_ctx* ctx, const FpPrime* fprimes, con
         if (groups > 65535) return hipErrorInvalidValue;
         ProfScope prof__("plain_mac_half_kernel", st);
         // Waves if each takes all terms of its coefficients; 3072 are resident.  Terms shared out over four waves: 33 -> 17 us at
-        // 288 waves, 56 -> 36 at 960, 74 -> 47 at 1280, 45 -> 43 at 1664, 52 -> 54 at 2176, 81 -> 81 at 2304, 91 -> 132 at 5632.
+        // 288 waves, 56 -> 36 at 960, 74 -> 47 at 1280, 45 -> 43 at 1664, 52 -> 54 at 2176, 81 -> 81 at 2304, 91 -> 132 at 5632.  The
+        // fewer the terms the earlier: eight 21.8 -> 20.9 us at 1280 waves, 19.1 -> 21.0 at 1536; five 10.7 -> 7.8 at 144, 11.8 -> 9.8 at
+        // 384, 14.5 -> 13.2 at 672, 16.2 -> 17.8 at 1152; three 10.8 -> 8.9 at 480, 11.7 -> 11.7 at 768, 13.1 -> 15.2 at 1152; two
+        // 8.9 -> 8.1 at 384 and 6.3 -> 7.5 at 48.
         const u64 waves = ((u64)1 << log_n) / 256 * groups * g.l;
-        if (waves <= 2048 && g.n_taps * g.IC >= 8)
+        const int terms = g.n_taps * g.IC;
+        if (waves <= (terms >= 12 ? 2048u : terms >= 8 ? 1280u : terms >= 3 ? 768u : 0u))
             hipLaunchKernelGGL((plain_mac_half_kernel<4, 4>), dim3((1u << log_n) / 256, groups, g.l), dim3(256), 0, st, fprimes, g, log_n);
         else
             hipLaunchKernelGGL((plain_mac_half_kernel<4, 1>), dim3((1u << log_n) / 512, groups, g.l), dim3(128), 0, st, fprimes, g, log_n);

@@ -197,7 +197,8 @@ def test_activation_pool_fc_chain_bit_exact():
 
 
 @pytest.mark.parametrize("log_n,bits,channels,outs,side", [
-    (12, [50, 40, 40], 3, 1, 6),       # terms below the line of shared-out terms; 1 output; sparse direct sums; high parts of 4 and 1 bytes
+    (12, [50, 40, 40], 2, 5, 6),       # terms below the line of shared-out terms
+    (12, [50, 40, 40], 3, 1, 6),       # fewer terms than waves that share them out; 1 output; sparse direct sums; high parts of 4 and 1 bytes
     (12, [48, 45, 45], 9, 5, 17),      # terms shared out unevenly over the waves; a ragged group; the transform's encoding; 2 bytes
     (13, [40, 50, 40, 40], 11, 69, 5), # more waves than the line; high parts of 1 and 4 bytes
 ])
