@@ -35,6 +35,7 @@ struct MacArgs {
     // plain, optional: the w_count plaintexts in the limb-major form of pack_plain_kernel (w_count = 0: [plaintext][limb]
     // rows of eight-byte words)
     u64 w_count; int w_packed;
+    unsigned first_group;                // of outputs, set by the launcher (packed plaintexts)
 };
 
 // The rows of a plan's plaintexts, N / 2 residues each: for every 128 residues their 128 low 32-bit words, then their 128 high
@@ -745,8 +746,8 @@ __device__ __forceinline__ void plain_mac_half_body(const FpPrime* fprimes, cons
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const u64 j = (KS > 1 ? (u64)blockIdx.x * 64 + lane : (u64)blockIdx.x * blockDim.x + threadIdx.x) * 2, jm = n - 2 - j;
     const int limb = blockIdx.z;
-    const int ocblocks = (g.OC + OCP - 1) / OCP;
-    const int b = blockIdx.y / ocblocks, oc0 = (blockIdx.y % ocblocks) * OCP;
+    const uint32_t ocblocks = (g.OC + OCP - 1) / OCP, group = g.first_group + blockIdx.y;
+    const int b = group / ocblocks, oc0 = (group % ocblocks) * OCP;
     const mac_cdouble_ptr fp = (mac_cdouble_ptr)(unsigned long long)&fprimes[limb].p;
     const double p = fp[0], pinv = fp[1];
     const u64 ln = (u64)g.l * n;
@@ -987,8 +988,8 @@ static hipError_t launch_plain_mac_fp(hisa_ctx* ctx, const FpPrime* fprimes, con
         auto high_ok = [](int hb) { return hb == 1 || hb == 2 || hb == 4; };
         if (g.w_words || g.x2 || g.lq || g.polys == 1 || !high_ok(g.w_packed & 7) || !high_ok(g.w_packed >> 3) || last >= g.w_count || log_n < 9)
             return hipErrorInvalidValue;
-        const int ocp = 4, groups = batch * ((g.OC + ocp - 1) / ocp);
-        if (groups > 65535) return hipErrorInvalidValue;
+        const u64 groups = (u64)batch * (((u64)g.OC + 3) / 4);
+        if (groups > 0x7fffffffu) return hipErrorInvalidValue;
         ProfScope prof__("plain_mac_half_kernel", st);
         // Waves if each takes all terms of its coefficients; 3072 are resident.  Terms shared out over four waves: 33 -> 17 us at
         // 288 waves, 56 -> 36 at 960, 74 -> 47 at 1280, 45 -> 43 at 1664, 52 -> 54 at 2176, 81 -> 81 at 2304, 91 -> 132 at 5632.  The
@@ -997,10 +998,14 @@ static hipError_t launch_plain_mac_fp(hisa_ctx* ctx, const FpPrime* fprimes, con
         // 8.9 -> 8.1 at 384 and 6.3 -> 7.5 at 48.
         const u64 waves = ((u64)1 << log_n) / 256 * groups * g.l;
         const int terms = g.n_taps * g.IC;
-        if (waves <= (terms >= 12 ? 2048u : terms >= 8 ? 1280u : terms >= 3 ? 768u : 0u))
-            hipLaunchKernelGGL((plain_mac_half_kernel<4, 4>), dim3((1u << log_n) / 256, groups, g.l), dim3(256), 0, st, fprimes, g, log_n);
-        else
-            hipLaunchKernelGGL((plain_mac_half_kernel<4, 1>), dim3((1u << log_n) / 512, groups, g.l), dim3(128), 0, st, fprimes, g, log_n);
+        const bool shared = waves <= (terms >= 12 ? 2048u : terms >= 8 ? 1280u : terms >= 3 ? 768u : 0u);
+        MacArgs part = g;
+        for (u64 g0 = 0; g0 < groups; g0 += 65535) {        // the rows of a grid
+            const unsigned cnt = (unsigned)std::min<u64>(65535, groups - g0);
+            part.first_group = (unsigned)g0;
+            if (shared) hipLaunchKernelGGL((plain_mac_half_kernel<4, 4>), dim3((1u << log_n) / 256, cnt, g.l), dim3(256), 0, st, fprimes, part, log_n);
+            else hipLaunchKernelGGL((plain_mac_half_kernel<4, 1>), dim3((1u << log_n) / 512, cnt, g.l), dim3(128), 0, st, fprimes, part, log_n);
+        }
         return hipGetLastError();
     }
     const int ocp = g.OC >= 8 ? 8 : 4;

@@ -221,6 +221,24 @@ def test_half_rows_of_a_plan(log_n, bits, channels, outs, side):
     g.close()
 
 
+def test_more_groups_of_outputs_than_rows_of_a_grid():
+    """A fully connected plan of more outputs than four times the 65535 rows of a grid: the last ones are those of a plan of their own."""
+    from paper_1810_00845_amd import hisa, synth
+    g = hisa.Context(12, [45, 45], 2, 50, 77)
+    t = g.tensor_encrypt(synth.image(1, 1, 1, 2)[None], 2.0 ** 40, 2)
+    g.gen_rot_keys(g.fc_rot_steps(t))
+    w = synth.fc_weights(3, 4 * 65535 + 5, 1, 1, 2)
+    plan, few = g.fc_prepare(t, w), g.fc_prepare(t, w[-7:])
+    all_outs, last = g.fc_apply(t, plan), g.fc_apply(t, few)
+    assert len(all_outs.cts) == len(w)
+    for a, b in zip(all_outs.cts[-7:], last.cts):
+        assert np.array_equal(g.ct_export(a), g.ct_export(b)) and a.scale == b.scale
+    g.fc_plan_free(plan)
+    g.fc_plan_free(few)
+    all_outs.free()
+    g.close()
+
+
 def test_layer_error_paths():
     from paper_1810_00845_amd import hisa, synth
     g, o = make_pair(11, [45, 45], 2, 50, 5)
