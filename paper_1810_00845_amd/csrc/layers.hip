@@ -1446,25 +1446,27 @@ static int conv_plan(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv_geom*
 
 // Fixed-point weights w[K][OC] (K = taps x input channels) on the device: residues per limb for the integer kernel;
 // when every prime is below 2^50 also centred doubles [l][K][OC] for the fp64 kernel and, for contractions long enough
-// to fill the matrix cores, signed base-256 digits [l][7][OC_pad][K_pad] with the constants 2^(24 g) mod q.
+// to fill the matrix cores, signed base-256 digits [l][7][OC_pad][K_pad] with the constants 2^(24 g) mod q.  digits_only: for a reader of
+// nothing but those.
 struct DevWeights {
     size_t K, OC, K_pad, OC_pad;
     int da = MAC_DIGITS;   // signed base-256 digits the largest weight needs
-    bool fp, mfma;
+    bool fp, mfma, digits_only;
     std::vector<int> primes;   // prime of every limb position (empty: position i is prime i)
     Temp res, resf, digits, c3;
-    DevWeights(hisa_ctx* ctx, size_t K_, size_t OC_, uint32_t l)
+    DevWeights(hisa_ctx* ctx, size_t K_, size_t OC_, uint32_t l, bool digits_only_ = false)
         : K(K_), OC(OC_), K_pad((K_ + MT_K - 1) / MT_K * MT_K), OC_pad((OC_ + MT_OC - 1) / MT_OC * MT_OC),
           fp(ctx->tabs.fp_ok), mfma(ctx->tabs.fp_ok && K_ >= MFMA_MIN_K && K_ <= MFMA_MAX_K),
-          res(ctx, K_ * OC_ * l * sizeof(u64)), resf(ctx, fp ? K_ * OC_ * l * sizeof(double) : 8),
+          digits_only(digits_only_), res(ctx, digits_only ? 8 : K_ * OC_ * l * sizeof(u64)),
+          resf(ctx, fp && !digits_only ? K_ * OC_ * l * sizeof(double) : 8),
           digits(ctx, mfma ? (size_t)l * MAC_DIGITS * OC_pad * K_pad : 8), c3(ctx, mfma ? (size_t)l * 5 * sizeof(double) : 8) {}
     bool ok() const { return res.ok() && resf.ok() && digits.ok() && c3.ok(); }
 };
 
 static int upload_weight_residues(hisa_ctx* ctx, const int64_t* w_int, uint32_t l, DevWeights& dst) {
-    const size_t count = dst.K * dst.OC;
-    std::vector<u64> res(count * l);
-    std::vector<double> resf(dst.fp ? count * l : 0), c3(dst.mfma ? (size_t)l * 5 : 0);
+    const size_t count = dst.K * dst.OC, words = dst.digits_only ? 0 : count * l;
+    std::vector<u64> res(words);
+    std::vector<double> resf(dst.fp ? words : 0), c3(dst.mfma ? (size_t)l * 5 : 0);
     std::vector<int8_t> dig(dst.mfma ? (size_t)l * MAC_DIGITS * dst.OC_pad * dst.K_pad : 0, 0);
     u64 used = 0;   // OR of all digit words: its highest non-zero byte is the last digit in use
     for (uint32_t k = 0; k < l; k++) {
@@ -1475,10 +1477,10 @@ static int upload_weight_residues(hisa_ctx* ctx, const int64_t* w_int, uint32_t 
                 const i64 wv = w_int[i];
                 // weights are almost always far below the modulus: the remainder is then the value itself
                 const u64 r = (wv >= 0 && (u64)wv < q) ? (u64)wv : ((wv < 0 && wv > -(i64)q) ? q - (u64)(-wv) : mod_i64(wv, q));
-                res[i * l + k] = r;
+                if (words) res[i * l + k] = r;
                 if (!dst.fp) continue;
                 const i64 c = r > q / 2 ? -(i64)(q - r) : (i64)r;
-                resf[(size_t)k * count + i] = (double)c;   // [l][K][OC]
+                if (words) resf[(size_t)k * count + i] = (double)c;   // [l][K][OC]
                 if (!dst.mfma) continue;
                 const u64 d = balanced_digits((u64)c);
                 used |= d;
@@ -1497,8 +1499,8 @@ static int upload_weight_residues(hisa_ctx* ctx, const int64_t* w_int, uint32_t 
     dst.da = 1;
     for (int a = 1; a < MAC_DIGITS; a++)
         if ((used >> (8 * a)) & 0xFF) dst.da = a + 1;
-    HIP_TRY(ctx, hipMemcpyAsync(dst.res.blk->ptr, res.data(), res.size() * sizeof(u64), hipMemcpyHostToDevice, ctx->stream));
-    if (dst.fp)
+    if (words) HIP_TRY(ctx, hipMemcpyAsync(dst.res.blk->ptr, res.data(), res.size() * sizeof(u64), hipMemcpyHostToDevice, ctx->stream));
+    if (words && dst.fp)
         HIP_TRY(ctx, hipMemcpyAsync(dst.resf.blk->ptr, resf.data(), resf.size() * sizeof(double), hipMemcpyHostToDevice,
                                     ctx->stream));
     if (dst.mfma) {
@@ -1809,7 +1811,7 @@ static int build_scalar_weights(hisa_ctx* ctx, const int64_t* w_int, const ConvP
             const size_t tap = k < ts.rot.size() ? ts.rot[k] : ts.zero[k - ts.rot.size()];
             memcpy(all.data() + k * IC4 * OC, w_int + tap * ICm * OC, (size_t)ICm * OC * sizeof(int64_t));
         }
-        cw.dw_all = new DevWeights(ctx, taps * IC4, OC, l + ctx->K);
+        cw.dw_all = new DevWeights(ctx, taps * IC4, OC, l + ctx->K, true);
         if (!cw.dw_all->ok()) return HISA_ERR_OOM;
         cw.dw_all->primes = ext_prime_list(ctx, l);
         return upload_weight_residues(ctx, all.data(), l + ctx->K, *cw.dw_all);

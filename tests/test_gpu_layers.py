@@ -904,6 +904,20 @@ def test_both_schedules_of_rotated_sums(log_n, bits, level, dnum, channels, outs
     g.close()
 
 
+def test_a_plan_of_rotated_sums_keeps_the_digits_of_its_weights_only():
+    """1600 terms x 64 outputs on 16 limbs: 11.5 MB of digits, and not the 26 MB of residues that this schedule does not read."""
+    import torch
+    from paper_1810_00845_amd import hisa, synth
+    g = hisa.Context(12, [50] + [40] * 11, 3, 50, 5)
+    t = hisa.CipherTensor(g, g.ct_random_batch(64, 12, 2.0 ** 36, 3), 1, 64, 4, 5, 9, 1, 20, 1)
+    g.sync()
+    free = torch.cuda.mem_get_info()[0]
+    plan = g.conv2d_prepare(t, synth.conv_weights(30, 5, 5, 64, 64, dist="normal", std=0.05), 5, 5, pad_same=True, shared_moddown=True)
+    assert free - torch.cuda.mem_get_info()[0] < 20 << 20
+    g.conv_plan_free(plan)
+    g.close()
+
+
 def test_shared_moddown_convolutions_bit_exact():
     """The convolution with one division by P per output ciphertext through the C ABI against the oracle's
     SharedModDown schedule, bit for bit: HW-tiled with scalar weights (literal and masked; short contraction on the
