@@ -1136,7 +1136,9 @@ __global__ __launch_bounds__(ROWS_NT, 4) void ntt_fp_split_kernel(FpArgs a, FpTa
 // Encryption of a batch: the columns launch draws the uniform polynomial a (into polynomial 1 of the ciphertexts) and the
 // error e (polynomial 0) while it loads them, the rows launch finishes both transforms of a row and stores (-a s + e + m, a).
 // Few vectors are bound by the chain of a wave: the table of e fetched anew for each of sixteen samples was most of it (4 vectors
-// at N = 2^14, 12 limbs, 23.5 us against 14.8 with an entry serving all of them).
+// at N = 2^14, 12 limbs, 23.5 us against 14.8 with an entry serving all of them).  The samples held for that take registers -- five waves a
+// SIMD instead of eight at N = 2^14, four instead of six at 2^15 -- and it is ahead all the same for many: both launches, us, 1, 4, 16 and 64
+// vectors at N = 2^14, 12 limbs 22.8, 29.1, 56.6, 166 -> 12.3, 19.6, 45.2, 148; at 2^15, 21 limbs 29, 56, 157, 620 -> 19, 42, 136, 565.
 template <int K3>
 __global__ __launch_bounds__(ROWS_NT, 4) void encrypt_columns_kernel(EncryptArgs a) {
     constexpr int NR = Col<K3>::NR, TILES = 1024 / Col<K3>::WIDTH;

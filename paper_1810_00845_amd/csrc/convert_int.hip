@@ -1048,7 +1048,8 @@ static bool convert_ok(const IntArgs& a) {
 
 // Waves of a workgroup of the columns where there are twice as many workgroups as are resident with eight waves each: those with the
 // highest throughput, when `slots` waves share a compute unit and a round over the targets takes 1.6 times one over the sources.  A wave
-// without a target in the last round, or without a source, only holds its registers, and those admit four waves a SIMD.  rotLeft, us, as few
+// without a target in the last round, or without a source, only holds its registers, and those admit seven waves a SIMD (more below 2^13)
+// up to N = 2^13, four at 2^14 and 2^15, two at 2^16 (tests/test_kernel_registers_host.py).  rotLeft, us, as few
 // waves as the rounds need (five, of 9 targets and 3 sources) -> these (three): 16 at N = 2^15, 8 limbs, three digits 331 -> 320, 64 at N = 2^14
 // 564 -> 538, 16 at N = 2^16, 4 limbs, two digits 321 -> 299, 64 at N = 2^11, 7 limbs 79 -> 76; even where the waves stay.  With fewer
 // workgroups the rounds are what counts: 12 at N = 2^15, 5 limbs, in 768 workgroups 163 -> 174.

@@ -59,8 +59,8 @@ __device__ __forceinline__ void bstore2(rsrc_t r, uint32_t lane_off, uint32_t ro
     bstore2(r, lane_off, row_off, (u64)__double_as_longlong(x), (u64)__double_as_longlong(y));
 }
 
-// The keys of a call that reads each of them once pass the caches by (nontemporal) when the last-level cache, 256 MB, will not hold
-// them until the next call: they only displace the digits and what the next launch reads.  Rotations of one ciphertext, us, kept /
+// The keys of a launch (up to 32 rotations) that reads each of them once pass the caches by (nontemporal) when the last-level cache, 256 MB,
+// will not hold them until the next call: they only displace the digits and what the next launch reads.  Rotations of one ciphertext, us, kept /
 // passed by: N = 2^14, 12 limbs, 189 MB of keys (15 rotations) 101 / 106, 227 MB 124 / 122, 302 MB 153 / 142; N = 2^15, 20 limbs, 213 MB
 // 146 / 143, 340 MB 191 / 175, 680 MB 344 / 298.  Keys that three or four entries read are better kept (N = 2^14, 24 rotations of four 389 / 415).
 #define STREAMED_KEY_BYTES ((u64)208 << 20)

@@ -223,12 +223,14 @@ int rotation_accumulators_fp(hisa_ctx* ctx, const u64* cts, u64 ct_bs, size_t B,
 // rescale: the sum's divScalar is taken together with its division by P (moddown_rescale_fp): out [Bn][2][l - 1][N].
 int rotate_sum_fp(hisa_ctx* ctx, const u64* rot, u64 ct_bs, int n_steps, const int32_t* steps, size_t Bn, int l,
                   const u64* plain, u64 plain_bs, u64* out, bool shared_input = false, bool rescale = false);
-// The division by P and the divScalar by q_{l-1} in one base conversion: acc [B][2][l + K][N] (overwritten: the addend
-// [B][add_polys][l][N] is first folded in, times P) -> out [B][2][l - 1][N] = (acc + P add) / (q_{l-1} P), rounded as a
-// centred conversion rounds.  l >= 2.
+// What a kernel that forms the accumulators of rotations itself reads: the extended digits of B ciphertexts, transformed (ext), the
+// keys and automorphisms of the rotations (st)
 struct IpSteps;
 size_t rotation_digits_bytes(const hisa_ctx* ctx, size_t B, int l);
 int rotation_digits_fp(hisa_ctx* ctx, const u64* cts, u64 ct_bs, size_t B, int l, const int32_t* steps, int n_steps, IpSteps* st, double* ext);
+// The division by P and the divScalar by q_{l-1} in one base conversion: acc [B][2][l + K][N] (overwritten: the addend
+// [B][add_polys][l][N] is first folded in, times P) -> out [B][2][l - 1][N] = (acc + P add) / (q_{l-1} P), rounded as a
+// centred conversion rounds.  l >= 2.
 int moddown_rescale_fp(hisa_ctx* ctx, u64* acc, size_t B, int l, const u64* add, u64 add_bs, int add_polys, u64* out);
 // Relinearisation of n three-polynomial ciphertexts ([3][l][N], stride words apart) whose division by P is taken
 // together with the divScalar by q_{l-1}: out [n][2][l - 1][N] = ((d0, d1) + KS_relin(d2)) / q_{l-1}.

@@ -920,22 +920,32 @@ static hipError_t launch_scalar_mac_mfma(hisa_ctx* ctx, const FpPrime* fprimes, 
     return hipErrorInvalidValue;
 }
 
-// One launch per class of primes, by the digits that hold its residues.
-static hipError_t launch_rotated_mac(hisa_ctx* ctx, RotMacArgs& a, int da, int batch, hipStream_t st) {
-    DRY_RUN_RETURN();
+// The check of a launch of rotated sums: its shape, then the words behind every pointer, by the indexing of the kernel.
+static const char* rotated_mac_fault(const hisa_ctx* ctx, const RotMacArgs& a, int da, int batch) {
     const u64 n = (u64)1 << a.log_n, entries = (u64)batch * a.IC;
     if (batch < 1 || batch > 65535 || a.n_rot < 1 || a.n_rot > FP_MAX_STEPS || a.n_zero < 0 || a.IC < 1 || a.OC < 1 || a.OC > MT_OC || a.digits < 1 ||
         a.digits > RM_DIGITS || a.l < 1 || a.le > 2 * HISA_MAX_Q || a.G != (a.IC + 3) / 4 || a.K_pad % MT_K ||
         a.K_pad < (a.n_rot + a.n_zero) * a.G * 4 || a.K_pad > MFMA_MAX_K || da < 1 || da > MAC_DIGITS || a.log_n < 10)
-        return hipErrorInvalidValue;
-    // every buffer holds what the kernel walks over
-    if (entries * a.ext_bs > dev_words_behind(ctx, a.ext) || a.ext_bs < (u64)a.digits * a.le * n || a.ct_bs < 2 * (u64)a.l * n ||
-        (entries - 1) * a.ct_bs + 2 * (u64)a.l * n > dev_words_behind(ctx, a.ct) || a.out_bs < 2 * (u64)a.le * n ||
-        (u64)batch * a.OC * a.out_bs > dev_words_behind(ctx, a.out) ||
-        (u64)a.le * MAC_DIGITS * MT_OC * a.K_pad > 8 * dev_words_behind(ctx, a.wd) || (u64)a.le * 5 > dev_words_behind(ctx, a.c3))
-        return hipErrorInvalidValue;
+        return "shape";
+    if (a.ext_bs < (u64)a.digits * a.le * n || entries * a.ext_bs > dev_words_behind(ctx, a.ext)) return "digits past their allocation";
+    if (a.ct_bs < 2 * (u64)a.l * n || (entries - 1) * a.ct_bs + 2 * (u64)a.l * n > dev_words_behind(ctx, a.ct)) return "input past its allocation";
+    if (a.out_bs < 2 * (u64)a.le * n || (u64)batch * a.OC * a.out_bs > dev_words_behind(ctx, a.out)) return "output past its allocation";
+    if ((u64)a.le * MAC_DIGITS * MT_OC * a.K_pad > 8 * dev_words_behind(ctx, a.wd) || (u64)a.le * 5 > dev_words_behind(ctx, a.c3))
+        return "weights past their allocation";
     for (int s = 0; s < a.n_rot; s++)
-        if (!a.steps.key[s] || !a.steps.galois[s]) return hipErrorInvalidValue;
+        if (!a.steps.key[s] || !a.steps.galois[s]) return "a rotation without its key";
+    return nullptr;
+}
+
+// One launch per class of primes, by the digits that hold its residues.
+static hipError_t launch_rotated_mac(hisa_ctx* ctx, RotMacArgs& a, int da, int batch, hipStream_t st) {
+    DRY_RUN_RETURN();
+    if (const char* why = rotated_mac_fault(ctx, a, da, batch)) {
+        fail(ctx, HISA_ERR_ARG, "rotated sums refused: %s (l %d of %d, key digits %d, IC %d, OC %d, taps %d + %d, batch %d)", why, a.l, a.le,
+             a.digits, a.IC, a.OC, a.n_rot, a.n_zero, batch);
+        return hipErrorInvalidDevicePointer;
+    }
+    const u64 n = (u64)1 << a.log_n;
     ProfScope prof__("rotated_mac_mfma_kernel", st);
     for (int db = 5; db <= MAC_DIGITS; db++) {
         int limbs = 0;
@@ -2108,7 +2118,7 @@ static int rotated_sums(hisa_ctx* ctx, const BatchIn& bi, size_t n_zero, const s
     a.K_pad = (int)dw.K_pad; a.wd = (const int8_t*)dw.digits.blk->ptr; a.c3 = dw.c3.as<double>();
     a.out = out; a.out_bs = 2 * (u64)a.le * n;
     const hipError_t e = launch_rotated_mac(ctx, a, dw.da, (int)B, ctx->stream);
-    return e == hipSuccess ? HISA_OK : fail(ctx, e == hipErrorInvalidValue ? HISA_ERR_ARG : HISA_ERR_HIP, "conv: %s", hipGetErrorString(e));
+    return e == hipSuccess ? HISA_OK : mac_fail(ctx, e, "conv");
 }
 
 // The convolution with ONE division by P per output ciphertext (the rotations of a convolution are only ever used
@@ -2116,6 +2126,7 @@ static int rotated_sums(hisa_ctx* ctx, const BatchIn& bi, size_t n_zero, const s
 // accumulators -- on l + K limbs, before the division -- times its weight taken on those limbs (E), and sigma(c0)
 // times the weight on the l limbs (Q0); unrotated taps contribute weight * (c0, c1) (Z); out = ModDown(E) + (Z0 + Q0,
 // Z1), then the mask (MASKED) and the divScalar as usual.  Same result as conv_run up to the rounding of the division.
+// Scalar weights that rotated_mac_fits gives to rotated_mac_mfma_kernel have P times the other two in E: no Q0, no Z.
 static int conv_run_shared(hisa_ctx* ctx, const hisa_tensor* in, const hisa_conv_geom* g, const ConvPlan& plan, uint32_t OC,
                            const ConvWeights& cw, hisa_tensor* out) {
     const uint32_t B = in->batch, ci = t_ci(in), IC = (uint32_t)t_per(in), OCm = (OC + ci - 1) / ci, l = in->cts[0]->limbs;

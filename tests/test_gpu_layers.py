@@ -837,13 +837,14 @@ def test_layout_switches_bit_exact():
 
 @pytest.mark.parametrize("bits,dnum,channels,outs,filt,same,batch", [
     ([45, 38, 38], 3, 4, 64, 3, True, 1),       # one group of channels a tap, all outputs of a block; residues of 5, 6 and 7 digits
-    ([50, 46, 44], 2, 7, 1, 3, False, 2),       # padded channels, one output, two key digits, two images
-    ([40, 40], 1, 2, 3, 5, True, 1),            # channels padded to twice their number, one key digit
-    ([50, 50], 2, 33, 5, 1, False, 1),          # no rotation: the other schedule
-    ([50, 50], 2, 9, 2, 2, False, 1),           # weights of seven digits; the first tap unrotated
+    ([50, 46, 44], 2, 7, 1, 3, False, 2),       # padded channels, one output, two key digits, two images; weights of six digits: in memory
+    ([40, 40], 1, 2, 3, 5, True, 1),            # channels padded to twice their number, one key digit; six digits: in memory
+    ([50, 50], 2, 33, 5, 1, False, 1),          # no rotation: neither
+    ([50, 50], 2, 9, 2, 2, False, 1),           # weights of seven digits; the first tap unrotated; 27 rotated terms: in memory
 ])
 def test_rotated_sums_on_the_matrix_cores(bits, dnum, channels, outs, filt, same, batch):
-    """The convolution whose matrix operand is formed from the key switch's digits, bit for bit against the oracle."""
+    """Convolutions that the kernel whose matrix operand is formed from the key switch's digits can take, bit for bit against the oracle;
+    which of them it is given, and which go through accumulators in memory, is test_both_schedules_of_rotated_sums' subject."""
     from oracle import layers
     from paper_1810_00845_amd import synth
     g, o = make_pair(12, bits, dnum, 50, 5)
@@ -920,8 +921,8 @@ def test_a_plan_of_rotated_sums_keeps_the_digits_of_its_weights_only():
 
 def test_shared_moddown_convolutions_bit_exact():
     """The convolution with one division by P per output ciphertext through the C ABI against the oracle's
-    SharedModDown schedule, bit for bit: HW-tiled with scalar weights (literal and masked; short contraction on the
-    fp64 kernel, long one on the matrix cores), HW-tiled with plaintext weights, CHW-tiled (with the copy behind the
+    SharedModDown schedule, bit for bit: HW-tiled with scalar weights (literal and masked; accumulators in memory, the 32 rotated
+    terms on the matrix cores, the four unrotated ones on the fp64 kernel), HW-tiled with plaintext weights, CHW-tiled (with the copy behind the
     blocks); batch of two; plan and float entry point; and against the fp64 convolution."""
     from oracle import layers
     from paper_1810_00845_amd import hisa, synth

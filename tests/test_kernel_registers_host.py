@@ -28,9 +28,15 @@ def kernels():
 
 # (mangled name, how many instantiations, most registers)
 FIT = [
-    (r"_Z27inner_product_sum_fp_kernelILi[14]ELi0EE.*", 2, 96),     # four to eight digits: five waves
+    (r"_Z\d+inner_product_sum_(fp|once)_kernelILi[14]ELi0EE.*", 4, 96),     # four to eight digits: five waves
     (r"_Z13ntt_fp_kernelILi[45]ELi[346]ELb1EE.*", 6, 80),           # columns at N = 2^14, 2^15: three workgroups of eight waves
     (r"_Z20ntt_fp_chunks_kernelILi[45]ELi[346]EE.*", 6, 128),       # sixteen waves
+    (r"_Z14ntt_int_kernelILi[012]ELi2ELb1EE.*", 3, 64),             # integer columns, columns_waves: eight waves at N <= 2^12,
+    (r"_Z14ntt_int_kernelILi3ELi2ELb1EE.*", 1, 72),                 # seven at 2^13,
+    (r"_Z14ntt_int_kernelILi[45]ELi2ELb1EE.*", 2, 128),             # four at 2^14 and 2^15,
+    (r"_Z14ntt_int_kernelILi6ELi2ELb1EE.*", 1, 256),                # two at 2^16
+    (r"_Z21plain_mac_half_kernel.*", 2, 168),                       # three waves: 3072 on the chip
+    (r"_Z23rotated_mac_mfma_kernelILi(3ELi[567]|5ELi[56])ELi[123]EE.*", 15, 256),   # two waves, nothing spilled
     (r"_Z20scalar_mac_fp_kernel.*", 1, 80),                         # six waves
     (r"_Z19encrypt_rows_kernelILi[2345]EE.*", 4, 128),              # four waves
 ]
