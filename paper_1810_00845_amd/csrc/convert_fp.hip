@@ -1349,7 +1349,9 @@ static hipError_t launch_one(dim3 grid, unsigned threads, size_t lds, const Conv
 // 65 -> 89: four exchanges a row instead of two).  Inner products: while all workgroups are resident at once, 512 of eight waves (up to
 // two digits) or 256 of twelve or sixteen (two digits 24: 8.9 -> 8.0 us, 384: 13.8 -> 12.7, 768: 16.3 -> 18.0; three digits 128: 12.1 -> 9.4,
 // 256: 13.2 -> 10.7, 736: 21 -> 26; four digits 256: 14.9 -> 11.4, 320: 19.3 -> 20.1).  Of these a workgroup for each polynomial while both fit
-// the chip's 256 compute units (WIDE_SPLIT): one rotation at N = 2^13, 8 limbs, 26.3 -> 25.6 us.
+// the chip's 256 compute units (WIDE_SPLIT): one rotation at N = 2^13, 8 limbs, 26.3 -> 25.6 us; whole rotations with 32, 64, 96 and 128 tasks
+// of one digit 22.3, 22.5, 22.9, 23.1 -> 21.3, 21.4, 21.9, 22.1, of three digits 23.9 .. 25.6 -> 23.3 .. 24.7; behind the line, 144 to 192
+// tasks, as without.
 // Forward transforms with their columns, us, 8-byte rows by one wave / 16-byte ones / these: 1280 rows at N = 2^14 13.5 / 14.2 / 12.5, 2048
 // 15.5 / 16.3 / 16.0; of 4096, the one place where 16-byte rows lose (two exchanges of lanes a row, nothing to hide them behind), 23.0 / 24.1,
 // of 6144 and more even.

@@ -966,7 +966,8 @@ static hipError_t launch_any(int log_n, dim3 grid, unsigned threads, size_t lds,
 // waves (up to two digits) or 256 of twelve or sixteen: one wave a digit -> four, 16 tasks of three digits 17.6 -> 12.8 us, 256 of
 // them 18.5 -> 14.4, 352 23 -> 26; of two digits 512 tasks 22 -> 17.6, 768 24.7 -> 24.3, 1024 29 -> 30.
 // Of these a workgroup for each polynomial while both fit the chip's 256 compute units (WIDE_SPLIT): one rotation at N = 2^12,
-// 3 limbs, 28.4 -> 28.0 us.
+// 3 limbs, 28.4 -> 28.0 us; with 6 .. 48 tasks of two digits at N = 2^10 25.8 .. 26.4 -> 24.7 .. 25.4, with 128 of three digits at N = 2^12
+// 31.1 -> 29.9; 144 and 192 tasks as without.
 #define WIDE_INVERSE_ROWS 32768
 #define WIDE_DIVIDE_ROWS 8192
 static u64 wide_inner_tasks(int n_digits) { return n_digits > INNER_CHUNK ? 0 : n_digits <= 2 ? 512 : 256; }
@@ -1047,13 +1048,14 @@ static bool convert_ok(const IntArgs& a) {
 }
 
 // Waves of a workgroup of the columns where there are twice as many workgroups as are resident with eight waves each: those with the
-// highest throughput, when `slots` waves share a compute unit and a round over the targets takes 1.6 times one over the sources.  A wave
-// without a target in the last round, or without a source, only holds its registers, and those admit seven waves a SIMD (more below 2^13)
-// up to N = 2^13, four at 2^14 and 2^15, two at 2^16 (tests/test_kernel_registers_host.py).  rotLeft, us, as few
+// highest throughput of the workgroups that there are (few waves leave room for more than those: 8 rotations at N = 2^16, 4 limbs, two
+// digits, in 512 workgroups of two waves 181 us, of four 157), when `slots` waves share a compute unit and a round over the targets takes
+// 1.6 times one over the sources.  A wave without a target in the last round, or without a source, only holds its registers, and those
+// admit seven waves a SIMD up to N = 2^13, four at 2^14 and 2^15, two at 2^16 (tests/test_kernel_registers_host.py).  rotLeft, us, as few
 // waves as the rounds need (five, of 9 targets and 3 sources) -> these (three): 16 at N = 2^15, 8 limbs, three digits 331 -> 320, 64 at N = 2^14
 // 564 -> 538, 16 at N = 2^16, 4 limbs, two digits 321 -> 299, 64 at N = 2^11, 7 limbs 79 -> 76; even where the waves stay.  With fewer
 // workgroups the rounds are what counts: 12 at N = 2^15, 5 limbs, in 768 workgroups 163 -> 174.
-static int columns_waves(const IntArgs& a, size_t lds, int slots) {
+static int columns_waves(const IntArgs& a, size_t lds, int slots, u64 workgroups) {
     int best = 8;
     double best_rate = 0;
     for (int w = 2; w <= 8; w++) {
@@ -1062,7 +1064,7 @@ static int columns_waves(const IntArgs& a, size_t lds, int slots) {
             const int src = std::min(a.alpha, a.n_src - d * a.alpha), tgt = a.ext_limbs - (a.own ? src : 0);
             time += (src + w - 1) / w + 1.6 * ((tgt + w - 1) / w);
         }
-        const double rate = std::min(slots / w, (int)(163840 / lds)) / time;
+        const double rate = std::min({(double)(slots / w), (double)(163840 / lds), workgroups / 256.0}) / time;
         if (rate > best_rate) { best_rate = rate; best = w; }
     }
     return best;
@@ -1083,7 +1085,8 @@ hipError_t launch_columns_int(const IntArgs& a_in, hipStream_t st) {
     const int rounds = (most_tgt + 7) / 8;
     int waves = (most_tgt + rounds - 1) / rounds;
     const int slots = a.log_n < 14 ? 28 : a.log_n < 16 ? 16 : 8;
-    if (most_src <= a.chunk && (u64)a.n_entries * a.n_digits * tiles >= 64u * slots) waves = columns_waves(a, a.chunk * per_src, slots);
+    const u64 workgroups = (u64)a.n_entries * a.n_digits * tiles;
+    if (most_src <= a.chunk && workgroups >= 64u * slots) waves = columns_waves(a, a.chunk * per_src, slots, workgroups);
     // few entries: several workgroups share a tile's targets (each forms the conversion inputs for itself)
     a.n_splits = 1;
     while (a.n_splits < rounds && (u64)a.n_entries * a.n_digits * tiles * (a.n_splits + 1) <= 512) a.n_splits++;
