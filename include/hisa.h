@@ -605,9 +605,10 @@ typedef struct {
 } hisa_calibration;
 int hisa_calibrate(hisa_ctx* ctx, hisa_calibration* out);
 
-/* The host-side check that every multiply-accumulate launch of the tensor kernels (Sec. "Runtime": convolution and
+/* The host-side check that a multiply-accumulate launch of the tensor kernels (Sec. "Runtime": convolution and
  * matrix multiplication over CipherTensors) passes before it reaches the GPU, callable on its own: no device, no
- * context, nothing is dereferenced.  A launch reads, per rotation amount ("tap"), batch * ic entries ct_words apart of
+ * context, nothing is dereferenced.  (Launches with a plan's packed plaintexts, and sums formed from a key switch's digits,
+ * pass a check of the same kind that these fields do not describe.)  A launch reads, per rotation amount ("tap"), batch * ic entries ct_words apart of
  * polys * limbs limbs of 2^log_n words, and writes batch * oc such entries; an optional second input (x2_extent != 0)
  * holds n_taps blocks x2_tap_words apart of batch * ic entries x2_words apart of lq limbs, its output batch * oc of
  * them; plaintext weights (w_extent != 0) are read at (T * w_stride_t + o * w_stride_oc) * w_words on limbs limbs
