@@ -419,10 +419,11 @@ __global__ __launch_bounds__(256) void scalar_mac_mfma_kernel(const FpPrime* fpr
 //   bytes are the digits xor 0x80.  DB = 7 (p < 2^50): the top digit is what is left above six bytes.
 // LeNet-medium's second convolution (24 rotations of 20 ciphertexts, 50 outputs, 10 + 4 limbs at N = 2^14): accumulators written
 // by one kernel and read by the other 782 + 850 us, the unrotated tap and its addition 98 + 58; this kernel 444 us for the nine
-// limbs of 40 bits and 307 for the five of 50.  Two waves a SIMD: the vector unit issues in 0.41 of the cycles, the matrix cores in
-// 0.22, the rest are waits for the gathered words.  Tried and taken back: all waves fetching ahead of their products (498 and 590: the words
+// limbs of 40 bits and 307 for the five of 50.  Two waves a SIMD: the vector unit issues in 0.43 of the cycles, the matrix cores in
+// 0.23, the rest are waits for the gathered words.  Tried and taken back: all waves fetching ahead of their products (498 and 590: the words
 // beside the accumulators cost too many registers), one descriptor a digit with 32-bit offsets (476 and 317).  With seven digits of
-// weights it spills (695 and 655) and still is ahead.
+// weights it spills (11 to 228 registers; 695 and 655) and still is ahead in this layer, which uses 500 of 512 terms; with five it spills 2 to
+// 13 where residues have seven.
 #define RM_DIGITS 3
 struct RotMacArgs {
     const FpPrime* fprimes;
